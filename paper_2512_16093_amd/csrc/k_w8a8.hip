@@ -19,6 +19,8 @@
 //                          asynchronous copies, three stages deep; a wavefront's activation
 //                          operands (8 KiB per feature block) go from global memory straight to
 //                          registers, one feature block ahead.  INT8 MFMA bound.
+//   w8a8_gemm_splitk_kernel  small workgroup tiles whose wavefronts split the contraction, for calls that do not
+//                          give every compute unit a 256 x 128 tile.
 #include "common.h"
 
 namespace sla {
@@ -139,6 +141,33 @@ __device__ __forceinline__ void w8_barrier() {
   asm volatile("" ::: "memory");
 }
 
+// The first product of a chain takes the pattern W8_BIAS_I as an inline constant (0.15915494 is
+// the assembler's spelling of 1 / (2 pi)); the compiler would keep the constant in sixteen
+// registers instead.  Every product of a chain is an assembly statement whose accumulator is ONE
+// in/out operand, so the chain accumulates in place by construction (destination = C operand,
+// the case the hardware interlocks) whatever registers are allocated, and each product still
+// takes its operands as they arrive.  The compiler does not know the statements hold
+// matrix products and adds no wait states before a vector instruction that reads the result, so
+// the data flow itself keeps every reader a whole chain (four dependent products, > 100 cycles)
+// behind: a chain's result may only be read after it has been handed through the SECOND product
+// of the next chain as `carry` (an in/out operand the statement does not touch; that product
+// cannot issue before the next chain's first one has finished, 64 cycles after the carried
+// chain's last one was issued), or, after the loop, through a statement of explicit wait states.
+__device__ __forceinline__ v16i w8_chain(const v4i (&b)[4], const v4i (&ar)[4], v16i& carry) {
+  v16i acc;
+  asm volatile("v_mfma_i32_32x32x32_i8 %0, %1, %2, 0.15915494" : "=&v"(acc) : "v"(b[0]), "v"(ar[0]));
+  asm volatile("v_mfma_i32_32x32x32_i8 %0, %2, %3, %0" : "+v"(acc), "+v"(carry) : "v"(b[1]), "v"(ar[1]));
+  asm volatile("v_mfma_i32_32x32x32_i8 %0, %1, %2, %0" : "+v"(acc) : "v"(b[2]), "v"(ar[2]));
+  asm volatile("v_mfma_i32_32x32x32_i8 %0, %1, %2, %0" : "+v"(acc) : "v"(b[3]), "v"(ar[3]));
+  return acc;
+}
+// The wait states a vector read of a matrix product's result needs, where no later chain keeps the distance.
+#define W8_READ_WAIT "s_nop 7\n\ts_nop 7\n\ts_nop 3"
+__device__ __forceinline__ void w8_scale_in(const v16i& acc, float sc, v16f& f) {
+#pragma unroll
+  for (int e = 0; e < 16; ++e) f[e] = __builtin_fmaf(__int_as_float(acc[e]), sc, f[e]);
+}
+
 constexpr int W8_DEAL_MT = 64;  // token tiles from which whole ones are dealt to the XCDs
 constexpr int W8_EPI_STRIDE = W8_WG_N * 2 + 16;  // bytes per staged output row
 
@@ -204,30 +233,6 @@ __global__ void __launch_bounds__(256, 2) w8a8_gemm_kernel(
   // One feature block: products against the staged weight tile, then one fma per element.  The
   // product is taken transposed (weights as the A operand) so that a lane owns ONE token and runs
   // of four consecutive outputs.
-  // The first product of a chain takes the pattern W8_BIAS_I as an inline constant (0.15915494 is
-  // the assembler's spelling of 1 / (2 pi)); the compiler would keep the constant in sixteen
-  // registers instead.  Every product of a chain is an assembly statement whose accumulator is ONE
-  // in/out operand, so the chain accumulates in place by construction (destination = C operand,
-  // the case the hardware interlocks) whatever registers are allocated, and each product still
-  // takes its operands as they arrive.  The compiler does not know the statements hold
-  // matrix products and adds no wait states before a vector instruction that reads the result, so
-  // the data flow itself keeps every reader a whole chain (four dependent products, > 100 cycles)
-  // behind: a chain's result may only be read after it has been handed through the SECOND product
-  // of the next chain as `carry` (an in/out operand the statement does not touch; that product
-  // cannot issue before the next chain's first one has finished, 64 cycles after the carried
-  // chain's last one was issued), or, after the loop, through a statement of explicit wait states.
-  auto chain = [&](const v4i (&b)[4], const v4i (&ar)[4], v16i& carry) {
-    v16i acc;
-    asm volatile("v_mfma_i32_32x32x32_i8 %0, %1, %2, 0.15915494" : "=&v"(acc) : "v"(b[0]), "v"(ar[0]));
-    asm volatile("v_mfma_i32_32x32x32_i8 %0, %2, %3, %0" : "+v"(acc), "+v"(carry) : "v"(b[1]), "v"(ar[1]));
-    asm volatile("v_mfma_i32_32x32x32_i8 %0, %1, %2, %0" : "+v"(acc) : "v"(b[2]), "v"(ar[2]));
-    asm volatile("v_mfma_i32_32x32x32_i8 %0, %1, %2, %0" : "+v"(acc) : "v"(b[3]), "v"(ar[3]));
-    return acc;
-  };
-  auto scale_in = [&](const v16i& acc, float sc, v16f& f) {
-#pragma unroll
-    for (int e = 0; e < 16; ++e) f[e] = __builtin_fmaf(__int_as_float(acc[e]), sc, f[e]);
-  };
   // The chains (4 output tiles x 2 token tiles per feature block) run back to back on the matrix
   // pipe, each with the fmas of the chain before it interleaved for the vector ALU -- across
   // feature blocks too: the last chain of a block is scaled in next to the first chain of the
@@ -249,18 +254,18 @@ __global__ void __launch_bounds__(256, 2) w8a8_gemm_kernel(
         x.u = st[(ct * 4 + ks) * 64 + lane];
         b[ks] = x.v;
       }
-      acc0 = chain(b, a[0], pend);       // (from here on the previous chain's result may be read)
+      acc0 = w8_chain(b, a[0], pend);       // (from here on the previous chain's result may be read)
       v16f& ftile = facc[1][(ct + 3) & 3];
-      scale_in(pend, pend_sc, ftile);
+      w8_scale_in(pend, pend_sc, ftile);
       asm volatile("" : "+v"(ftile) : : "memory");  // (the fmas stay in this window)
       asm volatile("" : "+v"(acc0) : : "memory");
       __builtin_amdgcn_sched_barrier(0);
       {
-        v16i fresh = chain(b, a[1], acc0);
+        v16i fresh = w8_chain(b, a[1], acc0);
         pend = fresh;
       }
       pend_sc = sc;
-      scale_in(acc0, sc, facc[0][ct]);
+      w8_scale_in(acc0, sc, facc[0][ct]);
       asm volatile("" : "+v"(facc[0][ct]) : : "memory");
       asm volatile("" : "+v"(pend) : : "memory");
       __builtin_amdgcn_sched_barrier(0);
@@ -294,9 +299,8 @@ __global__ void __launch_bounds__(256, 2) w8a8_gemm_kernel(
     if (kb < KB) W8_STEP(kb, a0, a1)
   }
 #undef W8_STEP
-  // (the last chain's result: the wait states a vector read of a matrix product's result needs)
-  asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 3" : "+v"(pend));
-  scale_in(pend, pend_sc, facc[1][3]);
+  asm volatile(W8_READ_WAIT : "+v"(pend));
+  w8_scale_in(pend, pend_sc, facc[1][3]);
 
   // Epilogue: constant share out, bias in, bf16, through LDS so that rows leave as 256 contiguous
   // bytes.  Lane = token 32 rt + l32 of this wavefront; registers 4 g .. 4 g + 3 of tile ct =
@@ -335,6 +339,132 @@ __global__ void __launch_bounds__(256, 2) w8a8_gemm_kernel(
 }
 
 // ---------------------------------------------------------------------------
+// The product for calls with few tokens or few outputs, where 256 x 128 tiles leave compute units without work
+// and every workgroup walks the whole contraction alone (512 x 5120 -> 5120: 80 tiles, 40 feature blocks each).
+// Workgroup tile (32 RT) tokens x (32 CT) outputs; its KS wavefronts split the CONTRACTION: each runs the whole
+// tile over a contiguous run of feature blocks (contiguous, so that the constants still alternate in sign from
+// block to block) and the partial sums meet in LDS in a fixed order.
+// Both operands go from memory straight to registers: they are in operand order, so a fragment is one contiguous
+// KiB, nothing is shared between the wavefronts, and there is no barrier in the loop.  A fragment is requested
+// again for the next feature block right behind the last product that reads it, half a block or more ahead of its
+// next use.  Bound by the CU's 64 bytes per clock from L2 (16 KiB per 16 products at RT = CT = 2).
+// ---------------------------------------------------------------------------
+template <int RT, int CT, int KS>
+__global__ void __launch_bounds__(64 * KS, 2) w8a8_gemm_splitk_kernel(
+    const int8_t* __restrict__ x8, const float* __restrict__ sx, const int8_t* __restrict__ w8,
+    const float* __restrict__ sw, const bf16_t* __restrict__ bias, bf16_t* __restrict__ y, int M, int N, int K,
+    int RTx, int RBx, int RTw, int RBw, int MT, int NT) {
+  constexpr int PITCH = 36;  // floats per staged row of 32 outputs (16-byte rows, skewed banks)
+  __shared__ __attribute__((aligned(16))) float part[KS][32 * RT][PITCH];
+  // XCD x takes a contiguous eighth of the tiles, token tiles fastest: a weight tile is fetched into one L2.
+  const int per = (MT * NT + 7) >> 3, xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  const int idx = __builtin_amdgcn_readfirstlane(xcd * per + slot);
+  if ((int)(blockIdx.x >> 3) >= per || idx >= MT * NT) return;
+  const int nt = __builtin_amdgcn_readfirstlane(idx / MT), mt = idx - nt * MT;
+  const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6), l32 = lane & 31, hf = lane >> 5;
+  const int KB = K / QB;
+  const int kb0 = KB * w / KS, kb1 = KB * (w + 1) / KS;  // this wavefront's feature blocks (none: an empty run)
+  const int rb = mt * RT / 4, nb = nt * CT / 4;          // quantisation blocks of the tile
+  const unsigned char* xa = (const unsigned char*)x8 + (size_t)(mt * RT) * 4096 + (size_t)lane * 16;
+  const unsigned char* wb = (const unsigned char*)w8 + (size_t)(nt * CT) * 4096 + (size_t)lane * 16;
+  const size_t xkb = (size_t)RTx * 4096, wkb = (size_t)RTw * 4096;
+
+  v16f facc[RT][CT];
+#pragma unroll
+  for (int r = 0; r < RT; ++r)
+#pragma unroll
+    for (int c = 0; c < CT; ++c) facc[r][c] = v16f{};
+  float csum = 0.f;
+  if (kb0 < kb1) {
+    v4i a[RT][4], b[CT][4];
+    auto load_frag = [&](const unsigned char* tile, v4i (&f)[4]) {
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) f[ks] = *(const v4i*)(tile + ks * 1024);
+    };
+    auto block_scale = [&](int kb) { return sx[(size_t)kb * RBx + rb] * sw[(size_t)kb * RBw + nb] * W8_STEP_INV; };
+#pragma unroll
+    for (int c = 0; c < CT; ++c) load_frag(wb + (size_t)kb0 * wkb + c * 4096, b[c]);
+#pragma unroll
+    for (int r = 0; r < RT; ++r) load_frag(xa + (size_t)kb0 * xkb + r * 4096, a[r]);
+    float mag = block_scale(kb0);
+    v16i pend;              // finished chain still to be scaled in; none yet: any finite pattern at scale 0
+#pragma unroll
+    for (int e = 0; e < 16; ++e) pend[e] = W8_BIAS_I;
+    float pend_sc = 0.f;
+    for (int kb = kb0; kb < kb1; ++kb) {
+      const float sc = (kb & 1) ? -mag : mag;
+      const int kn = min(kb + 1, kb1 - 1);   // (the last block is requested once more: the loop stays free of branches)
+      mag = block_scale(kn);
+#pragma unroll
+      for (int c = 0; c < CT; ++c)
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
+          v16i fresh = w8_chain(b[c], a[r], pend);   // (from here on the previous chain's result may be read)
+          v16f& prev = r > 0 ? facc[r - 1][c] : facc[RT - 1][(c + CT - 1) % CT];
+          w8_scale_in(pend, pend_sc, prev);
+          asm volatile("" : "+v"(prev) : : "memory");
+          asm volatile("" : "+v"(fresh) : : "memory");
+          if (c == CT - 1) load_frag(xa + (size_t)kn * xkb + r * 4096, a[r]);
+          if (r == RT - 1) load_frag(wb + (size_t)kn * wkb + c * 4096, b[c]);
+          __builtin_amdgcn_sched_barrier(0);
+          if constexpr (RT * CT == 1) {
+            // (a lone chain per block cannot be carried over the loop's back edge without a copy, which would
+            // read it too early: it is waited for and scaled in here, the other wavefronts fill the pipe)
+            asm volatile(W8_READ_WAIT : "+v"(fresh));
+            w8_scale_in(fresh, sc, facc[0][0]);
+          } else {
+            pend = fresh;
+            pend_sc = sc;
+          }
+        }
+      csum += sc;
+    }
+    if constexpr (RT * CT > 1) {
+      asm volatile(W8_READ_WAIT : "+v"(pend));
+      w8_scale_in(pend, pend_sc, facc[RT - 1][CT - 1]);
+    }
+  }
+
+  // Partial sums (constant share out) through LDS, one column tile at a time; lane = token, registers
+  // 4 g .. 4 g + 3 = outputs 8 g + 4 hf + 0..3.  Each thread then adds eight outputs of a token, in wavefront order.
+  const float corr = W8_C0 * csum;
+  for (int c = 0; c < CT; ++c) {
+    if (c > 0) __syncthreads();
+#pragma unroll
+    for (int r = 0; r < RT; ++r)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        v16f f = facc[r][0];
+#pragma unroll
+        for (int cc = 1; cc < CT; ++cc)
+          if (c == cc) f = facc[r][cc];
+        *(float4*)&part[w][32 * r + l32][8 * g + 4 * hf] =
+            make_float4(f[4 * g] - corr, f[4 * g + 1] - corr, f[4 * g + 2] - corr, f[4 * g + 3] - corr);
+      }
+    __syncthreads();
+    const int n0 = (nt * CT + c) * 32;
+    for (int u = t; u < 32 * RT * 4; u += 64 * KS) {
+      const int row = u >> 2, o = 8 * (u & 3), m = mt * 32 * RT + row;
+      if (m >= M) continue;
+      float v[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = part[0][row][o + e];
+#pragma unroll
+      for (int p = 1; p < KS; ++p)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] += part[p][row][o + e];
+      if (bias) {
+        const uint2 b0 = *(const uint2*)(bias + n0 + o), b1 = *(const uint2*)(bias + n0 + o + 4);
+        v[0] += bf16_lo(b0.x); v[1] += bf16_hi(b0.x); v[2] += bf16_lo(b0.y); v[3] += bf16_hi(b0.y);
+        v[4] += bf16_lo(b1.x); v[5] += bf16_hi(b1.x); v[6] += bf16_lo(b1.y); v[7] += bf16_hi(b1.y);
+      }
+      *(uint4*)(y + (size_t)m * N + n0 + o) = make_uint4(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]),
+                                                        pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7]));
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
 void launch_w8a8_quantize(const void* a, int R, int K, int RP, bool negate_odd, int8_t* codes, float* scales,
                           hipStream_t stream) {
   const unsigned grid = (unsigned)((RP / QB) * (K / QB));
@@ -346,9 +476,38 @@ void launch_w8a8_unpack(const int8_t* frag, const float* s, int R, int K, int RP
   w8a8_unpack_kernel<<<2048, 256, 0, stream>>>(frag, s, R, K, RP, negate_odd ? 1 : 0, codes, scales);
 }
 
+template <int RT, int CT, int KS>
+static void launch_splitk(const int8_t* x8, const float* sx, int MP, const int8_t* w8, const float* sw, const void* bias,
+                          void* y, int M, int N, int K, hipStream_t stream) {
+  const int MT = (M + 32 * RT - 1) / (32 * RT), NT = N / (32 * CT);
+  w8a8_gemm_splitk_kernel<RT, CT, KS><<<(unsigned)(8 * ((MT * NT + 7) / 8)), 64 * KS, 0, stream>>>(
+      x8, sx, w8, sw, (const bf16_t*)bias, (bf16_t*)y, M, N, K, MP / 32, MP / QB, N / 32, N / QB, MT, NT);
+}
+
 void launch_w8a8_gemm(const int8_t* x8, const float* sx, int MP, const int8_t* w8, const float* sw,
                       const void* bias, void* y, int M, int N, int K, hipStream_t stream) {
-  const int MT = MP / W8_WG_M, NT = N / W8_WG_N;
+  const int MT = MP / W8_WG_M, NT = N / W8_WG_N, KB = K / QB;
+  // Large tiles once every compute unit has one (256 of them), small split tiles below that.  Measured around the
+  // line, large / small in us: 5120 -> 5120 at 1536 tokens (240 tiles) 67.1 / 64.6, at 2048 (320) 79.9 / 85.2;
+  // 1536 -> 1536 at 4096 tokens (192) 22.6 / 20.0, at 8192 (384) 30.6 / 43.9.  A contraction of one or two blocks
+  // leaves the large kernel's pipeline empty: there the line lies higher (256 -> 5120 at 4096 tokens, 640 tiles,
+  // 21.5 / 17.2; at 16384 tokens, 2560 tiles, 56.5 / 80.9).
+  if (MT * NT < 256 || (KB <= 2 && MT * NT <= 640)) {
+    // Of the small variants the one with the most work per wavefront that still brings at least 1024 wavefronts,
+    // one per SIMD (5120 -> 5120 in us, the large kernel last: 1 token 6.0 | 67.6, 64: 8.5 | 68.2, 256: 16.1 | 69.3,
+    // 512: 23.8 | 72.9, 1024: 46 | 74.4).
+    auto waves = [&](int rt, int ct, int ks) { return (long long)((M + 32 * rt - 1) / (32 * rt)) * (N / (32 * ct)) * ks; };
+#define W8_SPLITK(RT, CT, KS) launch_splitk<RT, CT, KS>(x8, sx, MP, w8, sw, bias, y, M, N, K, stream)
+    if (waves(2, 2, 1) >= 1024) W8_SPLITK(2, 2, 1);
+    else if (waves(2, 2, 2) >= 1024) W8_SPLITK(2, 2, 2);
+    else if (waves(1, 2, 2) >= 1024) W8_SPLITK(1, 2, 2);
+    else if (waves(1, 2, 4) >= 1024 && KB >= 32) W8_SPLITK(2, 2, 8);  // (as many wavefronts; long runs: 128 tokens of 13824 features 23.2 against 28.5)
+    else if (waves(1, 2, 4) >= 1024) W8_SPLITK(1, 2, 4);
+    else if (waves(1, 1, 4) >= 1024) W8_SPLITK(1, 1, 4);
+    else W8_SPLITK(1, 1, 8);
+#undef W8_SPLITK
+    return;
+  }
   const unsigned grid = (unsigned)(8 * (MT >= W8_DEAL_MT ? (MT + 7) / 8 * NT : (MT * NT + 7) / 8));
   w8a8_gemm_kernel<<<grid, 256, 0, stream>>>(x8, sx, w8, sw, (const bf16_t*)bias, (bf16_t*)y, M, N, K, MP / 32,
                                              MP / QB, N / 32, N / QB, MT, NT);

@@ -161,3 +161,26 @@ def test_full_size_attention_projection_sampled():
         assert rel < 3e-3, (rb, rel)
         worst = max(worst, rel)
     print("w8a8 75600 x 5120 -> 5120: worst relative error of a sampled token block %.2e" % worst)
+
+
+@pytest.mark.parametrize("M,K,N", [
+    (1, 256, 128), (33, 640, 384),           # fewer feature blocks than wavefronts that split them; 32-row tiles, one row over
+    (31, 1024, 8192), (32, 256, 5120),       # 32 x 32 tiles, contraction split four and eight ways
+    (65, 384, 8192), (129, 4352, 5120),      # 32 x 64 tiles split four ways; 64 x 64 split eight ways (34 blocks, uneven runs)
+    (200, 384, 8192), (257, 640, 8192),      # 32 x 64 and 64 x 64 split in two
+    (1023, 384, 4096), (1025, 256, 5120),    # 64 x 64, not split; two feature blocks
+    (2049, 384, 3712),                       # the large tiles: nine bands of token tiles, a ragged last patch
+])
+def test_every_tile_and_split_of_the_product(M, K, N):
+    """The product's variants (tile size, ways the contraction is split) at the edges of what selects them, against
+    the oracle on the same codes, with the tolerance of the other product tests."""
+    x, w, b = synth.make_linear_inputs(M, K, N, seed=6)
+    wq = sla.w8a8_quantize_weight(w.cuda())
+    ws = sla.w8a8_quantize_act(x.cuda())
+    guard = torch.full((M + 64, N), 7.0, dtype=torch.bfloat16, device="cuda")   # rows past M must stay as they are
+    y = sla.w8a8_gemm_fwd(ws, wq, M, N, K, bias=b.cuda(), out=guard[:M]).float().cpu().numpy()
+    assert (guard[M:] == 7.0).all()
+    xc, xs = (t.cpu().numpy().astype(np.float64) for t in sla.w8a8_debug_unpack(ws, False, M, K))
+    wc, wsc = (t.cpu().numpy().astype(np.float64) for t in sla.w8a8_debug_unpack(wq, True, N, K))
+    ref = wo.linear_from_codes(xc, xs, wc, wsc, synth.as_f64(b))
+    assert np.all(np.abs(y - ref) <= product_tolerance(ref, xs, wsc, K)), np.abs(y - ref).max()
