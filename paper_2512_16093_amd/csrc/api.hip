@@ -128,12 +128,28 @@ Workspace fwd_workspace(const Problem& p, size_t n_c, size_t n_m, size_t code_te
   return make_workspace(p.BH, p.Tq, p.Tk, n_c, n_m, code_tensor_elems, q8_rows(p));
 }
 
+// What follows the statistics pass: the low-bit operands (mean of K, scale of V) and / or the projection in
+// operand order.  The maxima of V per 128 tokens live in the summaries' buffer, which prep_kv fills later.
+FinalizeArgs finalize_args(void* ws, const Workspace& W, const void* proj_w, bool quant, bool wfrag) {
+  return FinalizeArgs{at<float>(ws, W.hz), quant ? at<float>(ws, W.mu_k) : nullptr, at<float>(ws, W.amax_v), at<float>(ws, W.dv),
+                      (const bf16_t*)proj_w, wfrag ? at<bf16_t>(ws, W.wfrag) : nullptr};
+}
+// Statistics of Q and K (quant: and of V, and with want_q8 the codes of Q).
+void run_pool(const void* q, const void* k, const void* v, const Problem& p, void* ws, const Workspace& W, hipStream_t s,
+              bool quant, bool want_q8) {
+  launch_pool_stats(q, k, quant ? v : nullptr, p, at<float>(ws, W.qbar), at<float>(ws, W.kbar), at<float>(ws, W.dq),
+                    at<float>(ws, W.hz), want_q8 ? at<int8_t>(ws, W.q8) : nullptr, s);
+}
 void run_stats(const void* q, const void* k, const void* v, const void* proj_w, const Problem& p, void* ws,
                const Workspace& W, hipStream_t s, bool want_q8 = false) {
-  launch_pool_stats(q, k, v, p, at<float>(ws, W.qbar), at<float>(ws, W.kbar), at<float>(ws, W.dq),
-                    at<uint32_t>(ws, W.amax_v), want_q8 ? at<int8_t>(ws, W.q8) : nullptr, s);
-  launch_finalize_stats(p, at<float>(ws, W.kbar), at<uint32_t>(ws, W.amax_v), at<float>(ws, W.mu_k),
-                        at<float>(ws, W.dv), (const bf16_t*)proj_w, at<bf16_t>(ws, W.wfrag), s);
+  run_pool(q, k, v, p, ws, W, s, true, want_q8);
+  const FinalizeArgs fin = finalize_args(ws, W, proj_w, true, true);
+  launch_scores(p, at<float>(ws, W.qbar), at<float>(ws, W.kbar), nullptr, &fin, s);
+}
+// Block scores, with the rest of the statistics in front of them.
+void run_scores(const void* proj_w, const Problem& p, void* ws, const Workspace& W, hipStream_t s, bool quant, bool wfrag) {
+  const FinalizeArgs fin = finalize_args(ws, W, proj_w, quant, wfrag);
+  launch_scores(p, at<float>(ws, W.qbar), at<float>(ws, W.kbar), at<float>(ws, W.scores), &fin, s);
 }
 
 // The unquantised forward pass (bf16 products): the launch sequence of sla_attention_fwd with
@@ -146,14 +162,14 @@ int fwd_bf16(const void* q, const void* k, const void* v, void* out, const Probl
              void* save_os, bool codes16 = false) {
   const bool lin = p.n_m > 0;
   mark(s, rec, 0);
-  run_stats(q, k, v, proj_w, p, ws, W, s, codes16);
+  run_pool(q, k, v, p, ws, W, s, codes16, codes16);
   mark(s, rec, 1);
-  launch_scores(p, at<float>(ws, W.qbar), at<float>(ws, W.kbar), at<float>(ws, W.scores), s);
+  run_scores(proj_w, p, ws, W, s, codes16, lin);
   launch_select(p, at<float>(ws, W.scores), nullptr, at<int32_t>(ws, W.crit), nullptr,
-                lin ? at<uint32_t>(ws, W.m0) : nullptr, s);
+                lin ? at<uint32_t>(ws, W.m0) : nullptr, nullptr, nullptr, s);
   mark(s, rec, 2);
   if (lin || codes16)
-    launch_prep_kv(k, v, p, at<float>(ws, W.mu_k), at<uint32_t>(ws, W.amax_v), at<bf16_t>(ws, W.wfrag), phi_kind, codes16, lin,
+    launch_prep_kv(k, v, p, at<float>(ws, W.mu_k), at<float>(ws, W.amax_v), at<bf16_t>(ws, W.wfrag), phi_kind, codes16, lin,
                    at<int8_t>(ws, W.k8), at<uint8_t>(ws, W.v8), at<float>(ws, W.dk), at<bf16_t>(ws, W.hz), s);
   if (codes16)
     launch_code_tensors(p, at<int8_t>(ws, W.q8), at<int8_t>(ws, W.k8), at<bf16_t>(ws, W.qc), at<bf16_t>(ws, W.kc), s);
@@ -176,13 +192,14 @@ void run_prepass(const void* q, const void* k, const void* v, const void* proj_w
                  void* ws, const Workspace& W, hipStream_t s, int rec) {
   const bool lin = p.n_m > 0;
   mark(s, rec, 0);
-  run_stats(q, k, v, proj_w, p, ws, W, s, true);
+  run_pool(q, k, v, p, ws, W, s, true, true);
   mark(s, rec, 1);
-  launch_scores(p, at<float>(ws, W.qbar), at<float>(ws, W.kbar), at<float>(ws, W.scores), s);
-  launch_select(p, at<float>(ws, W.scores), nullptr, at<int32_t>(ws, W.crit), nullptr,
-                lin ? at<uint32_t>(ws, W.m0) : nullptr, s);
+  run_scores(proj_w, p, ws, W, s, true, lin);
+  const bool pairs = p.block_q == 64;   // (the attention kernel then walks merged lists of two query blocks)
+  launch_select(p, at<float>(ws, W.scores), nullptr, pairs ? nullptr : at<int32_t>(ws, W.crit), nullptr,
+                lin ? at<uint32_t>(ws, W.m0) : nullptr, pairs ? at<int32_t>(ws, W.pair_list) : nullptr, at<int32_t>(ws, W.pair_len), s);
   mark(s, rec, 2);
-  launch_prep_kv(k, v, p, at<float>(ws, W.mu_k), at<uint32_t>(ws, W.amax_v), at<bf16_t>(ws, W.wfrag), phi_kind, true, lin,
+  launch_prep_kv(k, v, p, at<float>(ws, W.mu_k), at<float>(ws, W.amax_v), at<bf16_t>(ws, W.wfrag), phi_kind, true, lin,
                  at<int8_t>(ws, W.k8), at<uint8_t>(ws, W.v8), at<float>(ws, W.dk), at<bf16_t>(ws, W.hz), s);
   mark(s, rec, 3);
   if (lin) launch_lin_accumulate(p, at<uint32_t>(ws, W.m0), at<bf16_t>(ws, W.hz), at<bf16_t>(ws, W.HZ), s);
@@ -400,12 +417,10 @@ int sla_classify_blocks(const void* q, const void* k, int B, int H, int N, int d
   if ((st = check_ws(workspace, workspace_bytes, W.total)) != SLA_OK) return st;
   hipStream_t s = (hipStream_t)stream;
   void* ws = workspace;
-  // V is not an input here: the statistics pass reads K in its place (its V outputs are unused)
-  launch_pool_stats(q, k, k, p, at<float>(ws, W.qbar), at<float>(ws, W.kbar), at<float>(ws, W.dq),
-                    at<uint32_t>(ws, W.amax_v), nullptr, s);
+  run_pool(q, k, nullptr, p, ws, W, s, false, false);
   float* sc = pooled_scores ? pooled_scores : at<float>(ws, W.scores);
-  launch_scores(p, at<float>(ws, W.qbar), at<float>(ws, W.kbar), sc, s);
-  launch_select(p, sc, mask, crit_idx, p.n_m > 0 ? marg_idx : nullptr, nullptr, s);
+  launch_scores(p, at<float>(ws, W.qbar), at<float>(ws, W.kbar), sc, nullptr, s);
+  launch_select(p, sc, mask, crit_idx, p.n_m > 0 ? marg_idx : nullptr, nullptr, nullptr, nullptr, s);
   return launch_status();
 }
 
@@ -421,12 +436,10 @@ int sla_classify_blocks_static(const void* q, const void* k, int B, int H, int N
   void* ws = static_scratch_ptr();
   if (!ws) return SLA_ERR_HIP;
   hipStream_t s = (hipStream_t)stream;
-  // the same kernels as sla_classify_blocks; the statistics pass zeroes what it accumulates into
-  launch_pool_stats(q, k, k, p, at<float>(ws, C.qbar), at<float>(ws, C.kbar), at<float>(ws, C.dq),
-                    at<uint32_t>(ws, C.amax_v), nullptr, s);
+  launch_pool_stats(q, k, nullptr, p, at<float>(ws, C.qbar), at<float>(ws, C.kbar), at<float>(ws, C.dq), nullptr, nullptr, s);
   float* sc = pooled_scores ? pooled_scores : at<float>(ws, C.scores);
-  launch_scores(p, at<float>(ws, C.qbar), at<float>(ws, C.kbar), sc, s);
-  launch_select(p, sc, mask, crit_idx, p.n_m > 0 ? marg_idx : nullptr, nullptr, s);
+  launch_scores(p, at<float>(ws, C.qbar), at<float>(ws, C.kbar), sc, nullptr, s);
+  launch_select(p, sc, mask, crit_idx, p.n_m > 0 ? marg_idx : nullptr, nullptr, nullptr, nullptr, s);
   return launch_status();
 }
 
@@ -446,7 +459,7 @@ int sla_sparse_attn_fwd(const void* q, const void* k, const void* v, const int32
   hipStream_t s = (hipStream_t)stream;
   void* ws = workspace;
   run_stats(q, k, v, nullptr, p, ws, Wmin, s, true);
-  launch_prep_kv(k, v, p, at<float>(ws, Wmin.mu_k), at<uint32_t>(ws, Wmin.amax_v), at<bf16_t>(ws, Wmin.wfrag), 0, true,
+  launch_prep_kv(k, v, p, at<float>(ws, Wmin.mu_k), at<float>(ws, Wmin.amax_v), at<bf16_t>(ws, Wmin.wfrag), 0, true,
                  false, at<int8_t>(ws, Wmin.k8), at<uint8_t>(ws, Wmin.v8), at<float>(ws, Wmin.dk), nullptr, s);
   launch_sparse_fwd(q, at<int8_t>(ws, Wmin.q8), p, crit_idx, n_crit, at<int8_t>(ws, Wmin.k8), at<uint8_t>(ws, Wmin.v8),
                     at<float>(ws, Wmin.dq), at<float>(ws, Wmin.dk), at<float>(ws, Wmin.dv), nullptr, nullptr, 0,
@@ -468,7 +481,7 @@ int sla_linear_attn_fwd(const void* q, const void* k, const void* v, const int8_
   hipStream_t s = (hipStream_t)stream;
   void* ws = workspace;
   run_stats(q, k, v, proj_w, p, ws, W, s, true);
-  launch_prep_kv(k, v, p, at<float>(ws, W.mu_k), at<uint32_t>(ws, W.amax_v), at<bf16_t>(ws, W.wfrag), phi_kind, false, true, nullptr,
+  launch_prep_kv(k, v, p, at<float>(ws, W.mu_k), at<float>(ws, W.amax_v), at<bf16_t>(ws, W.wfrag), phi_kind, false, true, nullptr,
                  nullptr, nullptr, at<bf16_t>(ws, W.hz), s);
   launch_marginal_bits(p, mask, at<uint32_t>(ws, W.m0), s);
   launch_lin_accumulate(p, at<uint32_t>(ws, W.m0), at<bf16_t>(ws, W.hz), at<bf16_t>(ws, W.HZ), s);
@@ -509,7 +522,7 @@ int sla_debug_quantize_kv(const void* k, const void* v, int B, int H, int N, int
   hipStream_t s = (hipStream_t)stream;
   void* ws = workspace;
   run_stats(k, k, v, nullptr, p, ws, W, s);
-  launch_prep_kv(k, v, p, at<float>(ws, W.mu_k), at<uint32_t>(ws, W.amax_v), at<bf16_t>(ws, W.wfrag), 0, true, false,
+  launch_prep_kv(k, v, p, at<float>(ws, W.mu_k), at<float>(ws, W.amax_v), at<bf16_t>(ws, W.wfrag), 0, true, false,
                  at<int8_t>(ws, W.k8), at<uint8_t>(ws, W.v8), at<float>(ws, W.dk), nullptr, s);
   launch_unfragment_kv(p, at<int8_t>(ws, W.k8), at<uint8_t>(ws, W.v8), k_codes, v_codes, s);
   const size_t bhd = (size_t)p.BH * D * 4;
@@ -529,8 +542,7 @@ int sla_debug_quantize_q(const void* q, int B, int H, int N, int d, int block_q,
   if ((st = check_ws(workspace, workspace_bytes, W.total)) != SLA_OK) return st;
   hipStream_t s = (hipStream_t)stream;
   void* ws = workspace;
-  launch_pool_stats(q, q, q, p, at<float>(ws, W.qbar), at<float>(ws, W.kbar), at<float>(ws, W.dq),
-                    at<uint32_t>(ws, W.amax_v), at<int8_t>(ws, W.q8), s);
+  run_pool(q, q, nullptr, p, ws, W, s, false, true);
   if (q_codes) launch_unpack_q8(p, at<int8_t>(ws, W.q8), q_codes, s);
   if (q_scale && hipMemcpyAsync(q_scale, at<float>(ws, W.dq), (size_t)p.BH * p.Tq * 4, hipMemcpyDeviceToDevice, s) != hipSuccess) return SLA_ERR_HIP;
   return launch_status();
@@ -633,10 +645,10 @@ int sla_attention_bwd_strided(const void* q, const void* k, const void* v, const
   mark(s, rec, 0);
 
   // the block mask, exactly as the forward pass finds it
-  run_stats(q, k, v, nullptr, p, ws, W, s);   // (no projection folded into the summaries here)
-  launch_scores(p, at<float>(ws, W.qbar), at<float>(ws, W.kbar), at<float>(ws, W.scores), s);
+  run_pool(q, k, v, p, ws, W, s, false, false);
+  run_scores(nullptr, p, ws, W, s, false, lin);   // (no projection folded into the summaries here)
   launch_select(p, at<float>(ws, W.scores), at<int8_t>(ws, W.mask), at<int32_t>(ws, W.crit), nullptr,
-                lin ? at<uint32_t>(ws, W.m0) : nullptr, s);
+                lin ? at<uint32_t>(ws, W.m0) : nullptr, nullptr, nullptr, s);
   mark(s, rec, 1);
   const float* lse2 = at<float>(ws, X.lse2);
   if (saved) {  // the forward pass's statistics: only delta = dO . O^s is left to do
@@ -653,7 +665,7 @@ int sla_attention_bwd_strided(const void* q, const void* k, const void* v, const
   if (dproj_b && !lin) launch_zero_u32((uint32_t*)dproj_b, (size_t)D, s);
   if (lin) {
     // H_i, Z_i of the forward pass (unprojected), then the linear branch's gradients
-    launch_prep_kv(k, v, p, at<float>(ws, W.mu_k), at<uint32_t>(ws, W.amax_v), at<bf16_t>(ws, W.wfrag), phi_kind, false, true,
+    launch_prep_kv(k, v, p, at<float>(ws, W.mu_k), at<float>(ws, W.amax_v), at<bf16_t>(ws, W.wfrag), phi_kind, false, true,
                    at<int8_t>(ws, W.k8), at<uint8_t>(ws, W.v8), at<float>(ws, W.dk), at<bf16_t>(ws, W.hz), s);
     launch_lin_accumulate(p, at<uint32_t>(ws, W.m0), at<bf16_t>(ws, W.hz), at<bf16_t>(ws, W.HZ), s);
     launch_bwd_wt((const bf16_t*)proj_w, at<bf16_t>(ws, X.wt), s);

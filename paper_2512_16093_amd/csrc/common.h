@@ -135,7 +135,7 @@ struct Workspace {
   size_t qbar, kbar;        // fp32 [BH,Tq,D], [BH,Tk,D] block means
   size_t dq;                // fp32 [BH,Tq]  per-query-block INT8 scale
   size_t q8;                // int8 [BH, ceil(N/128)*128, D]: codes of Q, a row's 128 bytes in q8_byte_offset order
-  size_t mu_k, amax_v, dv;  // fp32 [BH,D]   channel mean of K, max|V| (as uint bits), V scale
+  size_t mu_k, amax_v, dv;  // fp32 [BH,D]   channel mean of K, max|V|, V scale
   size_t dk;                // fp32 [BH,Tk]  per-key-block INT8 scale
   size_t scores;            // fp32 [BH,Tq,Tk]
   size_t mask;              // int8 [BH,Tq,Tk]
@@ -143,7 +143,7 @@ struct Workspace {
   size_t crit, marg;        // int32 [BH,Tq,n_c], [BH,Tq,n_m]
   size_t pair_list, pair_len;  // query blocks of 64: merged critical lists of adjacent pairs, int32 [BH,ceil(Tq/2),2 n_c], and their lengths
   size_t k8, v8;            // [BH,Tk] records of KV_FRAG_BYTES
-  size_t hz;                // bf16 [BH,Tk,HZ_ROWS,D]
+  size_t hz;                // bf16 [BH,Tk,HZ_ROWS,D] (before prep_kv: max|V| per 128 tokens, fp32 [BH,ceil(N/128),D])
   size_t HZ;                // bf16 [BH,Tq,HZ_ROWS,D]
   size_t wfrag;             // bf16 [D,D]: the projection (identity if none) in the operand order of prep_kv
   size_t qc, kc;            // bf16 [BH,N,D]: INT8 codes of Q and K as bf16 numbers (SLA_QUANT_QK_INT8 only)
@@ -209,14 +209,23 @@ struct Problem {
 };
 
 // Launchers (one per kernel file); every one only enqueues work on `stream`.
+// (v == nullptr: no statistics of V, vmax_part unused; vmax_part: fp32 [BH, ceil(N/128), D])
 void launch_pool_stats(const void* q, const void* k, const void* v, const Problem& p, float* qbar,
-                       float* kbar, float* dq, uint32_t* amax_v, int8_t* q8, hipStream_t stream);
-void launch_finalize_stats(const Problem& p, const float* kbar, const uint32_t* amax_v, float* mu_k,
-                           float* dv, const bf16_t* proj_w, bf16_t* wfrag, hipStream_t stream);
-void launch_scores(const Problem& p, const float* qbar, const float* kbar, float* scores, hipStream_t stream);
+                       float* kbar, float* dq, float* vmax_part, int8_t* q8, hipStream_t stream);
+// What rides in front of the scores launch: channel mean of K, max|V| and its scale (mu_k == nullptr: not wanted),
+// the projection in operand order (wfrag == nullptr: not wanted; proj_w == nullptr: the identity).
+struct FinalizeArgs {
+  const float* vmax_part;
+  float *mu_k, *amax_v, *dv;
+  const bf16_t* proj_w;
+  bf16_t* wfrag;
+};
+// (scores == nullptr: the finalising part alone; fin == nullptr: the scores alone)
+void launch_scores(const Problem& p, const float* qbar, const float* kbar, float* scores, const FinalizeArgs* fin, hipStream_t stream);
+// (pair_list: also the merged lists of adjacent query blocks, int32 [BH, ceil(Tq/2), 2 n_c], and their lengths)
 void launch_select(const Problem& p, const float* scores, int8_t* mask, int32_t* crit, int32_t* marg,
-                   uint32_t* mbits, hipStream_t stream);
-void launch_prep_kv(const void* k, const void* v, const Problem& p, const float* mu_k, const uint32_t* amax_v,
+                   uint32_t* mbits, int32_t* pair_list, int32_t* pair_len, hipStream_t stream);
+void launch_prep_kv(const void* k, const void* v, const Problem& p, const float* mu_k, const float* amax_v,
                     const bf16_t* wfrag, int phi_kind, bool want_quant, bool want_linear, int8_t* k8,
                     uint8_t* v8, float* dk, bf16_t* hz, hipStream_t stream);
 void launch_marginal_bits(const Problem& p, const int8_t* mask, uint32_t* mbits, hipStream_t stream);
@@ -225,7 +234,7 @@ void launch_lin_accumulate(const Problem& p, const uint32_t* mbits, const bf16_t
 void launch_sparse_fwd(const void* q, const int8_t* q8, const Problem& p, const int32_t* crit, int n_c, const int8_t* k8,
                        const uint8_t* v8, const float* dq, const float* dk, const float* dv,
                        const bf16_t* HZ, const bf16_t* proj_b, int phi_kind, bool has_linear,
-                       void* out, bool out_f32, float* lse, int32_t* pair_list, int32_t* pair_len,
+                       void* out, bool out_f32, float* lse, const int32_t* pair_list, const int32_t* pair_len,
                        hipStream_t stream);
 // Backward pass (k_bwd.hip, k_bwd_lin.hip; the transposed bit matrix lives with lin_accumulate).
 size_t marginal_bits_t_bytes(const Problem& p);

@@ -14,24 +14,28 @@ namespace sla {
 // ---------------------------------------------------------------------------
 // pool_stats: one workgroup per (b,h, 128-token group); 256 threads; thread
 // (rg = t/16, cg = t%16) reads 8 channels of rows rg + 16 r, r = 0..7.
-// HBM-bound: reads Q, K, V exactly once (6 N d bytes per slice).
+// HBM-bound: reads Q, K, V exactly once (6 N d bytes per slice); WANT_V = false (no low-bit branch behind it:
+// the 16-bit forward, the backward pass, the classification alone) leaves V out, a third of the reads.
+// The maxima of V leave as one row per workgroup, which finalize_block reduces: nothing has to be cleared
+// beforehand and there are no atomics (the clearing launch alone was 1.4 us of the smallest calls' 61).
 // ---------------------------------------------------------------------------
+template <bool WANT_V>
 __global__ void __launch_bounds__(256) pool_stats_kernel(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
     int N, int block_q, int Tq, int Tk, int groups, int H, Layout lq, Layout lk, Layout lv,
     float* __restrict__ qbar, float* __restrict__ kbar, float* __restrict__ dq,
-    uint32_t* __restrict__ amax_v, int8_t* __restrict__ q8) {
+    float* __restrict__ vmax_part, int8_t* __restrict__ q8) {
   __shared__ float sQ[16][2][D];
   __shared__ float s_qmax[2];
   __shared__ float sK[16][2][D];
-  __shared__ float sV[16][D];
+  __shared__ float sV[WANT_V ? 16 : 1][D];
   __shared__ float sQa[2][256];
   const int bh = blockIdx.x / groups, g = blockIdx.x % groups;
   const int t = threadIdx.x, cg = t & 15, rg = t >> 4;
   const int b_ = bh / H, h_ = bh - b_ * H;
   const bf16_t* qs_ = q + b_ * lq.sb + h_ * lq.sh;
   const bf16_t* ks_ = k + b_ * lk.sb + h_ * lk.sh;
-  const bf16_t* vs_ = v + b_ * lv.sb + h_ * lv.sh;
+  const bf16_t* vs_ = WANT_V ? v + b_ * lv.sb + h_ * lv.sh : nullptr;
   const int row0 = g * 128;
 
   float qs[2][8] = {}, ks[2][8] = {}, va[8] = {}, qa[2] = {0.f, 0.f};
@@ -44,7 +48,8 @@ __global__ void __launch_bounds__(256) pool_stats_kernel(
       const uint4 xq = *(const uint4*)(qs_ + row * lq.sn + cg * 8);
       qkeep[r] = xq;
       const uint4 xk = *(const uint4*)(ks_ + row * lk.sn + cg * 8);
-      const uint4 xv = *(const uint4*)(vs_ + row * lv.sn + cg * 8);
+      uint4 xv = make_uint4(0u, 0u, 0u, 0u);
+      if constexpr (WANT_V) xv = *(const uint4*)(vs_ + row * lv.sn + cg * 8);
       const uint32_t wq[4] = {xq.x, xq.y, xq.z, xq.w}, wk[4] = {xk.x, xk.y, xk.z, xk.w},
                      wv[4] = {xv.x, xv.y, xv.z, xv.w};
 #pragma unroll
@@ -55,8 +60,10 @@ __global__ void __launch_bounds__(256) pool_stats_kernel(
         qa[half] = fmaxf(qa[half], fmaxf(fabsf(q0), fabsf(q1)));
         ks[half][2 * e] += bf16_lo(wk[e]);
         ks[half][2 * e + 1] += bf16_hi(wk[e]);
-        va[2 * e] = fmaxf(va[2 * e], fabsf(bf16_lo(wv[e])));
-        va[2 * e + 1] = fmaxf(va[2 * e + 1], fabsf(bf16_hi(wv[e])));
+        if constexpr (WANT_V) {
+          va[2 * e] = fmaxf(va[2 * e], fabsf(bf16_lo(wv[e])));
+          va[2 * e + 1] = fmaxf(va[2 * e + 1], fabsf(bf16_hi(wv[e])));
+        }
       }
     }
   }
@@ -66,7 +73,7 @@ __global__ void __launch_bounds__(256) pool_stats_kernel(
     sQ[rg][1][cg * 8 + e] = qs[1][e];
     sK[rg][0][cg * 8 + e] = ks[0][e];
     sK[rg][1][cg * 8 + e] = ks[1][e];
-    sV[rg][cg * 8 + e] = va[e];
+    if constexpr (WANT_V) sV[rg][cg * 8 + e] = va[e];
   }
   sQa[0][t] = qa[0];
   sQa[1][t] = qa[1];
@@ -91,12 +98,13 @@ __global__ void __launch_bounds__(256) pool_stats_kernel(
     __syncthreads();
     if (half == 0) qbar[((size_t)bh * Tq + g) * D + c] = (sQ[0][0][c] + sQ[0][1][c]) / (float)(cnt0 + cnt1);
   }
-  if (t < 128) {
-    float m = 0.f;
+  if constexpr (WANT_V) {
+    if (t < 128) {
+      float m = 0.f;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) m = fmaxf(m, sV[r][t]);
-    // max of non-negative floats == max of their bit patterns: order-independent, exact
-    atomicMax(amax_v + (size_t)bh * D + t, __float_as_uint(m));
+      for (int r = 0; r < 16; ++r) m = fmaxf(m, sV[r][t]);
+      vmax_part[(size_t)blockIdx.x * D + t] = m;
+    }
   }
   if (t < 64) {  // wave 0 reduces the |Q| maxima of both halves
     float m0 = 0.f, m1 = 0.f;
@@ -147,62 +155,80 @@ __global__ void zero_u32_kernel(uint32_t* p, size_t n) {
   if (i < n) p[i] = 0u;
 }
 
-// finalize_stats: eight workgroups of 1024 threads per (b,h), each for 16 channels:
-// mu_K[c] = sum_j cnt_j kbar[j][c] / N (summed in a fixed order), delta_V[c] = max|V[:,c]| / 448
-// (1 if zero).  Workgroup 0 also lays the output projection (the identity if none is given) out
-// in the order in which prep_kv's first product takes it as the B operand of
-// v_mfma_f32_32x32x16_bf16: 16-byte chunk [tile of 32 output channels][step of 16 input
-// channels][lane] = W[32 tile + lane % 32][16 step + 8 (lane / 32) + 0..7], so that a wavefront
-// fetches an operand as one contiguous KiB.
-__global__ void __launch_bounds__(1024) finalize_stats_kernel(
-    const float* __restrict__ kbar, const uint32_t* __restrict__ amax_v, int N, int Tk,
-    float* __restrict__ mu_k, float* __restrict__ dv, const bf16_t* __restrict__ proj_w,
-    bf16_t* __restrict__ wfrag) {
-  __shared__ float red[64][17];
-  const int bh = blockIdx.x >> 3, c0 = (blockIdx.x & 7) * 16, t = threadIdx.x, cl = t & 15, rgrp = t >> 4;
-  float s = 0.f;
-  for (int j = rgrp; j < Tk; j += 64) {
-    const int cnt = min(BK, N - j * BK);
-    s += kbar[((size_t)bh * Tk + j) * D + c0 + cl] * (float)cnt;
-  }
-  red[rgrp][cl] = s;
+// What the statistics still need once every block's sums are known; runs as the first workgroups of the scores
+// launch (both depend on pool_stats alone, and a launch of its own cost the smallest calls 11 of 61 us).
+// Workgroups 0 .. 8 BH - 1, eight per (b,h), each for 16 channels: mu_K[c] = sum_j cnt_j kbar[j][c] / N (summed in a
+// fixed order), max|V[:,c]|, delta_V[c] = max|V[:,c]| / 448 (1 if zero).
+__device__ __forceinline__ void finalize_block(int blk, const float* __restrict__ kbar, const float* __restrict__ vmax_part,
+                                               int groups, int N, int Tk, float* __restrict__ mu_k,
+                                               float* __restrict__ amax_v, float* __restrict__ dv) {
+  __shared__ float red[2][16][17];
+  const int bh = blk >> 3, c0 = (blk & 7) * 16, t = threadIdx.x, cl = t & 15, rgrp = t >> 4;
+  float s = 0.f, m = 0.f;
+#pragma unroll 8
+  for (int j = rgrp; j < Tk; j += 16) s += kbar[((size_t)bh * Tk + j) * D + c0 + cl] * (float)min(BK, N - j * BK);
+#pragma unroll 8
+  for (int g = rgrp; g < groups; g += 16) m = fmaxf(m, vmax_part[((size_t)bh * groups + g) * D + c0 + cl]);
+  red[0][rgrp][cl] = s;
+  red[1][rgrp][cl] = m;
   __syncthreads();
   if (t < 16) {
-    float tot = 0.f;
-    for (int r = 0; r < 64; ++r) tot += red[r][t];
-    mu_k[(size_t)bh * D + c0 + t] = tot / (float)N;
-    const float am = __uint_as_float(amax_v[(size_t)bh * D + c0 + t]);
-    dv[(size_t)bh * D + c0 + t] = am > 0.f ? am / E4M3_MAX : 1.0f;
-  }
-  if (blockIdx.x == 0) {
-    for (int idx = t; idx < D * D / 8; idx += 1024) {
-      const int lane = idx & 63, row = 32 * (idx >> 9) + (lane & 31), col = 16 * ((idx >> 6) & 7) + 8 * (lane >> 5);
-      for (int e = 0; e < 8; ++e)
-        wfrag[idx * 8 + e] = proj_w ? proj_w[row * D + col + e] : (row == col + e ? (bf16_t)0x3f80 : (bf16_t)0);
+    s = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      s += red[0][r][t];
+      m = fmaxf(m, red[1][r][t]);
     }
+    const size_t o = (size_t)bh * D + c0 + t;
+    mu_k[o] = s / (float)N;
+    amax_v[o] = m;
+    dv[o] = m > 0.f ? m / E4M3_MAX : 1.0f;
   }
+}
+// The output projection (the identity if none is given) in the order in which prep_kv's first product takes it as
+// the B operand of v_mfma_f32_32x32x16_bf16: 16-byte chunk [tile of 32 output channels][step of 16 input
+// channels][lane] = W[32 tile + lane % 32][16 step + 8 (lane / 32) + 0..7], so that a wavefront fetches an operand as
+// one contiguous KiB.  One chunk per thread, WFRAG_BLOCKS workgroups.
+constexpr int WFRAG_BLOCKS = D * D / 8 / 256;
+__device__ __forceinline__ void wfrag_block(int blk, const bf16_t* __restrict__ proj_w, bf16_t* __restrict__ wfrag) {
+  const int idx = blk * 256 + threadIdx.x, lane = idx & 63, row = 32 * (idx >> 9) + (lane & 31), col = 16 * ((idx >> 6) & 7) + 8 * (lane >> 5);
+#pragma unroll
+  for (int e = 0; e < 8; ++e)
+    wfrag[idx * 8 + e] = proj_w ? proj_w[row * D + col + e] : (row == col + e ? (bf16_t)0x3f80 : (bf16_t)0);
 }
 
 // scores: s[bh][i][j] = qbar_i . kbar_j / sqrt(d) in fp32 on the matrix pipe
 // (v_mfma_f32_32x32x2_f32: fp32 operands and accumulation, the vector-fp32 rate without its issue
 // limits).  A wavefront owns a 32-row tile of query blocks, whose means it keeps in registers, and
-// sweeps SC_JT 32-column tiles of key blocks; the four wavefronts of a workgroup take four
+// sweeps jt_run 32-column tiles of key blocks; the four wavefronts of a workgroup take four
 // consecutive row tiles over the SAME columns, so three of their four reads of a key tile hit
 // the L1.  The instruction contracts two channels per step, one per lane half; which two is
 // free as long as both operands agree: lane half h holds channels 64 h .. 64 h + 63 of its row
 // (16 contiguous 16-byte loads) and step t contracts channels t and 64 + t.
-constexpr int SC_JT = 4;
 typedef float v16f_sc __attribute__((ext_vector_type(16)));
-__global__ void __launch_bounds__(256, 2) scores_kernel(const float* __restrict__ qbar,
-                                                        const float* __restrict__ kbar, int Tq, int Tk,
-                                                        float* __restrict__ scores) {
-  const int bh = blockIdx.z, lane = threadIdx.x & 63, w = threadIdx.x >> 6, l32 = lane & 31, h = lane >> 5;
-  const int i0 = (blockIdx.y * 4 + w) * 32;
-  if (i0 >= Tq) return;  // (whole wavefront; no barriers in this kernel)
-  const int jt0 = blockIdx.x * SC_JT, jts = (Tk + 31) / 32;
+struct ScoresArgs {
+  const float *qbar, *kbar;
+  float* scores;
+  int Tq, Tk, gx, gy, jt_run;     // workgroups per (b,h): gx runs of jt_run column tiles x gy groups of four row tiles
+  int fin_blocks, wfrag_blocks;   // leading workgroups that run finalize_block / wfrag_block
+  const float* vmax_part;
+  int groups, N;
+  float *mu_k, *amax_v, *dv;
+  const bf16_t* proj_w;
+  bf16_t* wfrag;
+};
+__global__ void __launch_bounds__(256, 2) scores_kernel(const ScoresArgs A) {
+  const int first = A.fin_blocks + A.wfrag_blocks;
+  if ((int)blockIdx.x < A.fin_blocks) return finalize_block(blockIdx.x, A.kbar, A.vmax_part, A.groups, A.N, A.Tk, A.mu_k, A.amax_v, A.dv);
+  if ((int)blockIdx.x < first) return wfrag_block(blockIdx.x - A.fin_blocks, A.proj_w, A.wfrag);
+  const int Tq = A.Tq, Tk = A.Tk, blk = blockIdx.x - first, bx = blk % A.gx, by = blk / A.gx % A.gy, bh = blk / (A.gx * A.gy);
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, l32 = lane & 31, h = lane >> 5;
+  const int i0 = (by * 4 + w) * 32;
+  if (i0 >= Tq) return;  // (whole wavefront; no barriers in this part of the kernel)
+  const int jt0 = bx * A.jt_run, jts = (Tk + 31) / 32;
   float a[64], b[64];
   {
-    const float4* src = (const float4*)(qbar + ((size_t)bh * Tq + min(i0 + l32, Tq - 1)) * D + 64 * h);
+    const float4* src = (const float4*)(A.qbar + ((size_t)bh * Tq + min(i0 + l32, Tq - 1)) * D + 64 * h);
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
       const float4 x = src[u];
@@ -210,14 +236,14 @@ __global__ void __launch_bounds__(256, 2) scores_kernel(const float* __restrict_
     }
   }
   auto load_b = [&](int jt) {
-    const float4* src = (const float4*)(kbar + ((size_t)bh * Tk + min(jt * 32 + l32, Tk - 1)) * D + 64 * h);
+    const float4* src = (const float4*)(A.kbar + ((size_t)bh * Tk + min(jt * 32 + l32, Tk - 1)) * D + 64 * h);
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
       const float4 x = src[u];
       b[4 * u] = x.x; b[4 * u + 1] = x.y; b[4 * u + 2] = x.z; b[4 * u + 3] = x.w;
     }
   };
-  for (int jt = jt0; jt < min(jt0 + SC_JT, jts); ++jt) {
+  for (int jt = jt0; jt < min(jt0 + A.jt_run, jts); ++jt) {
     load_b(jt);
     v16f_sc acc = {};
 #pragma unroll
@@ -227,7 +253,7 @@ __global__ void __launch_bounds__(256, 2) scores_kernel(const float* __restrict_
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int i = i0 + 8 * (r >> 2) + 4 * h + (r & 3);
-      if (i < Tq && j < Tk) scores[((size_t)bh * Tq + i) * Tk + j] = acc[r] / 11.313708498984761f;
+      if (i < Tq && j < Tk) A.scores[((size_t)bh * Tq + i) * Tk + j] = acc[r] / 11.313708498984761f;
     }
   }
 }
@@ -247,14 +273,30 @@ __device__ __forceinline__ uint32_t order_bits(float f) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-template <int KPL>
+// PAIR (query blocks of 64 in front of the low-bit attention kernel): two neighbouring wavefronts take the two
+// query blocks of a pair and the first of them also writes the pair's merged list, the ascending union of the two
+// critical lists (bit 30 / 31 of an entry = the first / second block of the pair has it), from their ballots.
+template <int KPL, bool PAIR>
 __global__ void __launch_bounds__(256) select_kernel(const float* __restrict__ scores, int rows, int Tq, int Tk,
                                                      int n_c, int n_m, int8_t* __restrict__ mask,
                                                      int32_t* __restrict__ crit, int32_t* __restrict__ marg,
-                                                     uint32_t* __restrict__ mbits) {
+                                                     uint32_t* __restrict__ mbits, int32_t* __restrict__ ulist,
+                                                     int32_t* __restrict__ ulen) {
+  __shared__ unsigned long long in_list[PAIR ? 4 : 1][PAIR ? KPL : 1];  // critical ballots of the wavefronts
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const size_t row = (size_t)blockIdx.x * 4 + w;
-  if (row >= (size_t)rows) return;  // whole wavefront; no workgroup barrier is used below
+  const unsigned long long lt = (1ull << lane) - 1ull;
+  size_t row = (size_t)blockIdx.x * 4 + w;
+  bool live = true;
+  int pair = 0;
+  if constexpr (PAIR) {
+    const int TqW = (Tq + 1) / 2, pairs = rows / Tq * TqW;
+    pair = (int)(row >> 1);
+    const int bh = min(pair, pairs - 1) / TqW, i = 2 * (min(pair, pairs - 1) - bh * TqW) + (w & 1);
+    live = pair < pairs && i < Tq;                       // (an odd last block has no partner)
+    row = (size_t)bh * Tq + min(i, Tq - 1);
+  } else {
+    if (row >= (size_t)rows) return;  // whole wavefront; no workgroup barrier is used below
+  }
   const float* srow = scores + row * Tk;
   uint32_t key[KPL];
 #pragma unroll
@@ -317,7 +359,6 @@ __global__ void __launch_bounds__(256) select_kernel(const float* __restrict__ s
     if (n_m > 0) t2 -= __popcll(__ballot(key[m] > k2));
   }
 
-  const unsigned long long lt = (1ull << lane) - 1ull;
   const int bh = (int)(row / Tq), i = (int)(row % Tq);
   const int KT = (Tk + 31) / 32, TqP = (Tq + 383) / 384 * 384 + 128;  // layout of the marginal bit matrix (see lin_accumulate)
   int eq1 = 0, eq2 = 0, nc = 0, nm = 0;  // running counts in ascending-j order
@@ -325,7 +366,7 @@ __global__ void __launch_bounds__(256) select_kernel(const float* __restrict__ s
   for (int m = 0; m < KPL; ++m) {
     const int j = lane + 64 * m;
     if (64 * m >= Tk) break;
-    const bool valid = j < Tk;
+    const bool valid = j < Tk && live;
     const bool e1 = valid && key[m] == k1, e2 = valid && n_m > 0 && key[m] == k2;
     const unsigned long long b1 = __ballot(e1), b2 = __ballot(e2);
     const int r1 = eq1 + __popcll(b1 & lt), r2 = eq2 + __popcll(b2 & lt);
@@ -339,10 +380,27 @@ __global__ void __launch_bounds__(256) select_kernel(const float* __restrict__ s
     if (marg && is_m) marg[row * n_m + nm + __popcll(bm & lt)] = j;
     nc += __popcll(bc);
     nm += __popcll(bm);
-    if (mbits && lane < 2) {  // the marginal ballot of these 64 key blocks = two words of the bit matrix
+    if constexpr (PAIR) {
+      if (lane == 0) in_list[w][m] = bc;
+    }
+    if (mbits && live && lane < 2) {  // the marginal ballot of these 64 key blocks = two words of the bit matrix
       const int kt = 2 * m + lane;
       if (kt < KT) mbits[((size_t)bh * KT + kt) * TqP + i] = (uint32_t)(bm >> (32 * lane));
     }
+  }
+  if constexpr (PAIR) {
+    __syncthreads();
+    const int TqW = (Tq + 1) / 2;
+    if ((w & 1) || pair >= rows / Tq * TqW) return;
+    int32_t* dst = ulist + (size_t)pair * (2 * n_c);
+    int n = 0;
+    for (int m = 0; 64 * m < Tk; ++m) {
+      const unsigned long long first = in_list[w][m], second = in_list[w + 1][m], either = first | second;
+      if ((either >> lane) & 1)
+        dst[n + __popcll(either & lt)] = (lane + 64 * m) | (int)(((first >> lane) & 1) << 30) | (int)(((second >> lane) & 1) << 31);
+      n += __popcll(either);
+    }
+    if (lane == 0) ulen[pair] = n;
   }
 }
 
@@ -352,46 +410,64 @@ void launch_zero_u32(uint32_t* p, size_t n, hipStream_t stream) {
 }
 
 void launch_pool_stats(const void* q, const void* k, const void* v, const Problem& p, float* qbar,
-                       float* kbar, float* dq, uint32_t* amax_v, int8_t* q8, hipStream_t stream) {
-  const size_t n = (size_t)p.BH * D;
-  zero_u32_kernel<<<(unsigned)((n + 255) / 256), 256, 0, stream>>>(amax_v, n);
+                       float* kbar, float* dq, float* vmax_part, int8_t* q8, hipStream_t stream) {
   const int groups = (p.N + 127) / 128;
-  pool_stats_kernel<<<p.BH * groups, 256, 0, stream>>>((const bf16_t*)q, (const bf16_t*)k,
-                                                        (const bf16_t*)v, p.N, p.block_q, p.Tq, p.Tk,
-                                                        groups, p.H, p.lq, p.lk, p.lv, qbar, kbar, dq,
-                                                        amax_v, q8);
+#define SLA_POOL(WANT_V) pool_stats_kernel<WANT_V><<<p.BH * groups, 256, 0, stream>>>((const bf16_t*)q, (const bf16_t*)k, \
+      (const bf16_t*)v, p.N, p.block_q, p.Tq, p.Tk, groups, p.H, p.lq, p.lk, p.lv, qbar, kbar, dq, vmax_part, q8)
+  if (v) SLA_POOL(true); else SLA_POOL(false);
+#undef SLA_POOL
 }
 
-void launch_finalize_stats(const Problem& p, const float* kbar, const uint32_t* amax_v, float* mu_k,
-                           float* dv, const bf16_t* proj_w, bf16_t* wfrag, hipStream_t stream) {
-  finalize_stats_kernel<<<p.BH * 8, 1024, 0, stream>>>(kbar, amax_v, p.N, p.Tk, mu_k, dv, proj_w, wfrag);
-}
-
-void launch_scores(const Problem& p, const float* qbar, const float* kbar, float* scores,
+void launch_scores(const Problem& p, const float* qbar, const float* kbar, float* scores, const FinalizeArgs* fin,
                    hipStream_t stream) {
-  dim3 grid(((p.Tk + 31) / 32 + SC_JT - 1) / SC_JT, (p.Tq + 127) / 128, p.BH);
-  scores_kernel<<<grid, 256, 0, stream>>>(qbar, kbar, p.Tq, p.Tk, scores);
+  ScoresArgs A{};
+  A.qbar = qbar; A.kbar = kbar; A.scores = scores;
+  A.Tq = p.Tq; A.Tk = p.Tk; A.N = p.N;
+  A.groups = (p.N + 127) / 128;
+  if (fin) {
+    A.vmax_part = fin->vmax_part;
+    A.mu_k = fin->mu_k; A.amax_v = fin->amax_v; A.dv = fin->dv;
+    A.proj_w = fin->proj_w; A.wfrag = fin->wfrag;
+    A.fin_blocks = fin->mu_k ? 8 * p.BH : 0;
+    A.wfrag_blocks = fin->wfrag ? WFRAG_BLOCKS : 0;
+  }
+  int n_scores = 0;
+  if (scores) {
+    const int jts = (p.Tk + 31) / 32;
+    A.gy = (p.Tq + 127) / 128;
+    // runs of four column tiles share a wavefront's query means; where those would leave compute units without a
+    // workgroup, one tile each (24 slices of 37 x 73 blocks: 24 workgroups, 13.6 us)
+    A.jt_run = (long long)((jts + 3) / 4) * A.gy * p.BH >= 512 ? 4 : 1;
+    A.gx = (jts + A.jt_run - 1) / A.jt_run;
+    n_scores = A.gx * A.gy * p.BH;
+  }
+  const int grid = A.fin_blocks + A.wfrag_blocks + n_scores;
+  if (grid > 0) scores_kernel<<<(unsigned)grid, 256, 0, stream>>>(A);
 }
 
 void launch_select(const Problem& p, const float* scores, int8_t* mask, int32_t* crit, int32_t* marg,
-                   uint32_t* mbits, hipStream_t stream) {
-  const int rows = p.BH * p.Tq;
-  const unsigned grid = (unsigned)((rows + 3) / 4);
-  const int need = (p.Tk + 63) / 64;
-#define SLA_SELECT(K) select_kernel<K><<<grid, 256, 0, stream>>>(scores, rows, p.Tq, p.Tk, p.n_c, p.n_m, mask, crit, marg, mbits)
+                   uint32_t* mbits, int32_t* pair_list, int32_t* pair_len, hipStream_t stream) {
+  const int rows = p.BH * p.Tq, need = (p.Tk + 63) / 64;
+  const int waves = pair_list ? 2 * p.BH * ((p.Tq + 1) / 2) : rows;
+  const unsigned grid = (unsigned)((waves + 3) / 4);
+#define SLA_SELECT(K)                                                                                              \
+  {                                                                                                                \
+    if (pair_list) select_kernel<K, true><<<grid, 256, 0, stream>>>(scores, rows, p.Tq, p.Tk, p.n_c, p.n_m, mask, crit, marg, mbits, pair_list, pair_len); \
+    else select_kernel<K, false><<<grid, 256, 0, stream>>>(scores, rows, p.Tq, p.Tk, p.n_c, p.n_m, mask, crit, marg, mbits, nullptr, nullptr);             \
+  }
   // registers per lane: the smallest instantiation that holds the row
-  if (need <= 2) SLA_SELECT(2);
-  else if (need <= 4) SLA_SELECT(4);
-  else if (need <= 8) SLA_SELECT(8);
-  else if (need <= 12) SLA_SELECT(12);
-  else if (need <= 16) SLA_SELECT(16);
-  else if (need <= 20) SLA_SELECT(20);
-  else if (need <= 24) SLA_SELECT(24);
-  else if (need <= 32) SLA_SELECT(32);
-  else if (need <= 48) SLA_SELECT(48);
-  else if (need <= 64) SLA_SELECT(64);
-  else if (need <= 96) SLA_SELECT(96);
-  else SLA_SELECT(128);
+  if (need <= 2) SLA_SELECT(2)
+  else if (need <= 4) SLA_SELECT(4)
+  else if (need <= 8) SLA_SELECT(8)
+  else if (need <= 12) SLA_SELECT(12)
+  else if (need <= 16) SLA_SELECT(16)
+  else if (need <= 20) SLA_SELECT(20)
+  else if (need <= 24) SLA_SELECT(24)
+  else if (need <= 32) SLA_SELECT(32)
+  else if (need <= 48) SLA_SELECT(48)
+  else if (need <= 64) SLA_SELECT(64)
+  else if (need <= 96) SLA_SELECT(96)
+  else SLA_SELECT(128)
 #undef SLA_SELECT
 }
 

@@ -731,56 +731,10 @@ __global__ void __launch_bounds__(NW * 64, 2) sparse_fwd_kernel(
   }
 }
 
-// Paired mode (query blocks of 64): per pair of adjacent query blocks, the ascending union of
-// their critical lists; bit 30 / 31 of an entry = the first / second block of the pair has it.
-// One workgroup of 256 threads per pair; thread t owns key blocks 32 t .. 32 t + 31 (Tk <= 8192).
-__global__ void __launch_bounds__(256) pair_union_kernel(const int32_t* __restrict__ crit, int Tq, int n_c, int TqW,
-                                                         int ustride, int32_t* __restrict__ ulist,
-                                                         int32_t* __restrict__ ulen) {
-  __shared__ uint32_t bm[2][256];
-  __shared__ int wave_cnt[4];
-  const int row = blockIdx.x, bh = row / TqW, i = row - bh * TqW, t = threadIdx.x;
-  bm[0][t] = 0u;
-  bm[1][t] = 0u;
-  __syncthreads();
-  const int32_t* ra = crit + ((size_t)bh * Tq + 2 * i) * n_c;
-  const bool has_b = 2 * i + 1 < Tq;
-  for (int idx = t; idx < n_c; idx += 256) {
-    const int a = ra[idx];
-    atomicOr(&bm[0][a >> 5], 1u << (a & 31));
-    if (has_b) {
-      const int b = ra[n_c + idx];
-      atomicOr(&bm[1][b >> 5], 1u << (b & 31));
-    }
-  }
-  __syncthreads();
-  const uint32_t wa = bm[0][t], wb = bm[1][t];
-  uint32_t u = wa | wb;
-  const int cnt = __popc(u);
-  // exclusive prefix sum of cnt over the 256 threads
-  int incl = cnt;
-  for (int o = 1; o < 64; o <<= 1) {
-    const int v = __shfl_up(incl, o);
-    if ((t & 63) >= o) incl += v;
-  }
-  if ((t & 63) == 63) wave_cnt[t >> 6] = incl;
-  __syncthreads();
-  int base = 0;
-  for (int k = 0; k < (t >> 6); ++k) base += wave_cnt[k];
-  int pos = base + incl - cnt;
-  int32_t* dst = ulist + (size_t)row * ustride;
-  while (u) {
-    const int bit = __ffs(u) - 1;
-    u &= u - 1;
-    dst[pos++] = (32 * t + bit) | (int)(((wa >> bit) & 1u) << 30) | (int)(((wb >> bit) & 1u) << 31);
-  }
-  if (t == 255) ulen[row] = base + incl;
-}
-
 void launch_sparse_fwd(const void* q, const int8_t* q8, const Problem& p, const int32_t* crit, int n_c, const int8_t* k8,
                        const uint8_t* v8, const float* dq, const float* dk, const float* dv,
                        const bf16_t* HZ, const bf16_t* proj_b, int phi_kind, bool has_linear,
-                       void* out, bool out_f32, float* lse, int32_t* pair_list, int32_t* pair_len,
+                       void* out, bool out_f32, float* lse, const int32_t* pair_list, const int32_t* pair_len,
                        hipStream_t stream) {
   SparseDims dm;
   dm.N = p.N;
@@ -802,8 +756,6 @@ void launch_sparse_fwd(const void* q, const int8_t* q8, const Problem& p, const 
   const bf16_t* bias = has_linear ? proj_b : nullptr;
   const unsigned grid = (unsigned)(8 * dm.per_xcd * p.BH);
   if (paired) {
-    pair_union_kernel<<<(unsigned)(p.BH * dm.TqW), 256, 0, stream>>>(crit, p.Tq, n_c, dm.TqW, dm.ustride, pair_list,
-                                                                     pair_len);
     sparse_fwd_kernel<4, true><<<grid, 256, 0, stream>>>((const bf16_t*)q, q8, pair_list, k8, v8, dq, dk, dv, HZ, bias, out,
                                                          lse, pair_len, dm);
   } else if (p.block_q == 128) {
