@@ -166,7 +166,7 @@ int fwd_bf16(const void* q, const void* k, const void* v, void* out, const Probl
   mark(s, rec, 1);
   run_scores(proj_w, p, ws, W, s, codes16, lin);
   launch_select(p, at<float>(ws, W.scores), nullptr, at<int32_t>(ws, W.crit), nullptr,
-                lin ? at<uint32_t>(ws, W.m0) : nullptr, nullptr, nullptr, s);
+                lin ? at<uint32_t>(ws, W.m0) : nullptr, s);
   mark(s, rec, 2);
   if (lin || codes16)
     launch_prep_kv(k, v, p, at<float>(ws, W.mu_k), at<float>(ws, W.amax_v), at<bf16_t>(ws, W.wfrag), phi_kind, codes16, lin,
@@ -195,9 +195,8 @@ void run_prepass(const void* q, const void* k, const void* v, const void* proj_w
   run_pool(q, k, v, p, ws, W, s, true, true);
   mark(s, rec, 1);
   run_scores(proj_w, p, ws, W, s, true, lin);
-  const bool pairs = p.block_q == 64;   // (the attention kernel then walks merged lists of two query blocks)
-  launch_select(p, at<float>(ws, W.scores), nullptr, pairs ? nullptr : at<int32_t>(ws, W.crit), nullptr,
-                lin ? at<uint32_t>(ws, W.m0) : nullptr, pairs ? at<int32_t>(ws, W.pair_list) : nullptr, at<int32_t>(ws, W.pair_len), s);
+  launch_select(p, at<float>(ws, W.scores), nullptr, at<int32_t>(ws, W.crit), nullptr,
+                lin ? at<uint32_t>(ws, W.m0) : nullptr, s);
   mark(s, rec, 2);
   launch_prep_kv(k, v, p, at<float>(ws, W.mu_k), at<float>(ws, W.amax_v), at<bf16_t>(ws, W.wfrag), phi_kind, true, lin,
                  at<int8_t>(ws, W.k8), at<uint8_t>(ws, W.v8), at<float>(ws, W.dk), at<bf16_t>(ws, W.hz), s);
@@ -210,8 +209,7 @@ void run_attend(const void* q, void* out, const void* proj_b, const Problem& p, 
                 const Workspace& W, hipStream_t s) {
   launch_sparse_fwd(q, at<int8_t>(ws, W.q8), p, at<int32_t>(ws, W.crit), p.n_c, at<int8_t>(ws, W.k8), at<uint8_t>(ws, W.v8),
                     at<float>(ws, W.dq), at<float>(ws, W.dk), at<float>(ws, W.dv), at<bf16_t>(ws, W.HZ),
-                    (const bf16_t*)proj_b, phi_kind, p.n_m > 0, out, false, nullptr, at<int32_t>(ws, W.pair_list),
-                    at<int32_t>(ws, W.pair_len), s);
+                    (const bf16_t*)proj_b, phi_kind, p.n_m > 0, out, false, nullptr, p.n_c == p.Tk, s);
 }
 
 // What sla_attention_fwd_train hands to sla_attention_bwd_saved: a header naming the problem the state
@@ -420,7 +418,7 @@ int sla_classify_blocks(const void* q, const void* k, int B, int H, int N, int d
   run_pool(q, k, nullptr, p, ws, W, s, false, false);
   float* sc = pooled_scores ? pooled_scores : at<float>(ws, W.scores);
   launch_scores(p, at<float>(ws, W.qbar), at<float>(ws, W.kbar), sc, nullptr, s);
-  launch_select(p, sc, mask, crit_idx, p.n_m > 0 ? marg_idx : nullptr, nullptr, nullptr, nullptr, s);
+  launch_select(p, sc, mask, crit_idx, p.n_m > 0 ? marg_idx : nullptr, nullptr, s);
   return launch_status();
 }
 
@@ -439,7 +437,7 @@ int sla_classify_blocks_static(const void* q, const void* k, int B, int H, int N
   launch_pool_stats(q, k, nullptr, p, at<float>(ws, C.qbar), at<float>(ws, C.kbar), at<float>(ws, C.dq), nullptr, nullptr, s);
   float* sc = pooled_scores ? pooled_scores : at<float>(ws, C.scores);
   launch_scores(p, at<float>(ws, C.qbar), at<float>(ws, C.kbar), sc, nullptr, s);
-  launch_select(p, sc, mask, crit_idx, p.n_m > 0 ? marg_idx : nullptr, nullptr, nullptr, nullptr, s);
+  launch_select(p, sc, mask, crit_idx, p.n_m > 0 ? marg_idx : nullptr, nullptr, s);
   return launch_status();
 }
 
@@ -463,7 +461,7 @@ int sla_sparse_attn_fwd(const void* q, const void* k, const void* v, const int32
                  false, at<int8_t>(ws, Wmin.k8), at<uint8_t>(ws, Wmin.v8), at<float>(ws, Wmin.dk), nullptr, s);
   launch_sparse_fwd(q, at<int8_t>(ws, Wmin.q8), p, crit_idx, n_crit, at<int8_t>(ws, Wmin.k8), at<uint8_t>(ws, Wmin.v8),
                     at<float>(ws, Wmin.dq), at<float>(ws, Wmin.dk), at<float>(ws, Wmin.dv), nullptr, nullptr, 0,
-                    false, out_s, true, lse, nullptr, nullptr, s);
+                    false, out_s, true, lse, false, s);
   return launch_status();
 }
 
@@ -488,7 +486,7 @@ int sla_linear_attn_fwd(const void* q, const void* k, const void* v, const int8_
   // the attention kernel with an empty critical list leaves only the linear term
   launch_sparse_fwd(q, at<int8_t>(ws, W.q8), p, nullptr, 0, at<int8_t>(ws, W.k8), at<uint8_t>(ws, W.v8), at<float>(ws, W.dq),
                     at<float>(ws, W.dk), at<float>(ws, W.dv), at<bf16_t>(ws, W.HZ), (const bf16_t*)proj_b,
-                    phi_kind, true, out_l, true, nullptr, nullptr, nullptr, s);
+                    phi_kind, true, out_l, true, nullptr, false, s);
   return launch_status();
 }
 
@@ -648,7 +646,7 @@ int sla_attention_bwd_strided(const void* q, const void* k, const void* v, const
   run_pool(q, k, v, p, ws, W, s, false, false);
   run_scores(nullptr, p, ws, W, s, false, lin);   // (no projection folded into the summaries here)
   launch_select(p, at<float>(ws, W.scores), at<int8_t>(ws, W.mask), at<int32_t>(ws, W.crit), nullptr,
-                lin ? at<uint32_t>(ws, W.m0) : nullptr, nullptr, nullptr, s);
+                lin ? at<uint32_t>(ws, W.m0) : nullptr, s);
   mark(s, rec, 1);
   const float* lse2 = at<float>(ws, X.lse2);
   if (saved) {  // the forward pass's statistics: only delta = dO . O^s is left to do

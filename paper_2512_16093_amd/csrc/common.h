@@ -141,7 +141,6 @@ struct Workspace {
   size_t mask;              // int8 [BH,Tq,Tk]
   size_t m0;                // uint32 marginal bit matrix [BH, ceil(Tk/32), Tq rounded up to 384, + 128]: bit e of word (kt, i) = block 32 kt + e marginal for query block i
   size_t crit, marg;        // int32 [BH,Tq,n_c], [BH,Tq,n_m]
-  size_t pair_list, pair_len;  // query blocks of 64: merged critical lists of adjacent pairs, int32 [BH,ceil(Tq/2),2 n_c], and their lengths
   size_t k8, v8;            // [BH,Tk] records of KV_FRAG_BYTES
   size_t hz;                // bf16 [BH,Tk,HZ_ROWS,D] (before prep_kv: max|V| per 128 tokens, fp32 [BH,ceil(N/128),D])
   size_t HZ;                // bf16 [BH,Tq,HZ_ROWS,D]
@@ -169,8 +168,6 @@ inline Workspace make_workspace(size_t BH, size_t Tq, size_t Tk, size_t n_c, siz
   w.mask = take(BH * Tq * Tk);
   w.m0 = take(BH * ((Tk + 31) / 32) * ((Tq + 383) / 384 * 384 + 128) * 4);
   w.crit = take(BH * Tq * n_c * 4);
-  w.pair_list = take(BH * ((Tq + 1) / 2) * 2 * n_c * 4);
-  w.pair_len = take(BH * ((Tq + 1) / 2) * 4);
   w.marg = take(BH * Tq * (n_m ? n_m : 1) * 4);
   w.k8 = take(BH * Tk * KV_FRAG_BYTES);
   w.v8 = take(BH * Tk * KV_FRAG_BYTES);
@@ -222,20 +219,19 @@ struct FinalizeArgs {
 };
 // (scores == nullptr: the finalising part alone; fin == nullptr: the scores alone)
 void launch_scores(const Problem& p, const float* qbar, const float* kbar, float* scores, const FinalizeArgs* fin, hipStream_t stream);
-// (pair_list: also the merged lists of adjacent query blocks, int32 [BH, ceil(Tq/2), 2 n_c], and their lengths)
 void launch_select(const Problem& p, const float* scores, int8_t* mask, int32_t* crit, int32_t* marg,
-                   uint32_t* mbits, int32_t* pair_list, int32_t* pair_len, hipStream_t stream);
+                   uint32_t* mbits, hipStream_t stream);
 void launch_prep_kv(const void* k, const void* v, const Problem& p, const float* mu_k, const float* amax_v,
                     const bf16_t* wfrag, int phi_kind, bool want_quant, bool want_linear, int8_t* k8,
                     uint8_t* v8, float* dk, bf16_t* hz, hipStream_t stream);
 void launch_marginal_bits(const Problem& p, const int8_t* mask, uint32_t* mbits, hipStream_t stream);
 void launch_lin_accumulate(const Problem& p, const uint32_t* mbits, const bf16_t* hz, bf16_t* HZ,
                            hipStream_t stream);
+// (all_critical: every list names all key blocks in ascending order)
 void launch_sparse_fwd(const void* q, const int8_t* q8, const Problem& p, const int32_t* crit, int n_c, const int8_t* k8,
                        const uint8_t* v8, const float* dq, const float* dk, const float* dv,
                        const bf16_t* HZ, const bf16_t* proj_b, int phi_kind, bool has_linear,
-                       void* out, bool out_f32, float* lse, const int32_t* pair_list, const int32_t* pair_len,
-                       hipStream_t stream);
+                       void* out, bool out_f32, float* lse, bool all_critical, hipStream_t stream);
 // Backward pass (k_bwd.hip, k_bwd_lin.hip; the transposed bit matrix lives with lin_accumulate).
 size_t marginal_bits_t_bytes(const Problem& p);
 void launch_marginal_bits_t(const Problem& p, const int8_t* mask, uint32_t* mbits_t, hipStream_t stream);

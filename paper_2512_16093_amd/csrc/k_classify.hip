@@ -273,30 +273,15 @@ __device__ __forceinline__ uint32_t order_bits(float f) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-// PAIR (query blocks of 64 in front of the low-bit attention kernel): two neighbouring wavefronts take the two
-// query blocks of a pair and the first of them also writes the pair's merged list, the ascending union of the two
-// critical lists (bit 30 / 31 of an entry = the first / second block of the pair has it), from their ballots.
-template <int KPL, bool PAIR>
+template <int KPL>
 __global__ void __launch_bounds__(256) select_kernel(const float* __restrict__ scores, int rows, int Tq, int Tk,
                                                      int n_c, int n_m, int8_t* __restrict__ mask,
                                                      int32_t* __restrict__ crit, int32_t* __restrict__ marg,
-                                                     uint32_t* __restrict__ mbits, int32_t* __restrict__ ulist,
-                                                     int32_t* __restrict__ ulen) {
-  __shared__ unsigned long long in_list[PAIR ? 4 : 1][PAIR ? KPL : 1];  // critical ballots of the wavefronts
+                                                     uint32_t* __restrict__ mbits) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const unsigned long long lt = (1ull << lane) - 1ull;
-  size_t row = (size_t)blockIdx.x * 4 + w;
-  bool live = true;
-  int pair = 0;
-  if constexpr (PAIR) {
-    const int TqW = (Tq + 1) / 2, pairs = rows / Tq * TqW;
-    pair = (int)(row >> 1);
-    const int bh = min(pair, pairs - 1) / TqW, i = 2 * (min(pair, pairs - 1) - bh * TqW) + (w & 1);
-    live = pair < pairs && i < Tq;                       // (an odd last block has no partner)
-    row = (size_t)bh * Tq + min(i, Tq - 1);
-  } else {
-    if (row >= (size_t)rows) return;  // whole wavefront; no workgroup barrier is used below
-  }
+  const size_t row = (size_t)blockIdx.x * 4 + w;
+  if (row >= (size_t)rows) return;  // whole wavefront; no workgroup barrier is used below
   const float* srow = scores + row * Tk;
   uint32_t key[KPL];
 #pragma unroll
@@ -366,7 +351,7 @@ __global__ void __launch_bounds__(256) select_kernel(const float* __restrict__ s
   for (int m = 0; m < KPL; ++m) {
     const int j = lane + 64 * m;
     if (64 * m >= Tk) break;
-    const bool valid = j < Tk && live;
+    const bool valid = j < Tk;
     const bool e1 = valid && key[m] == k1, e2 = valid && n_m > 0 && key[m] == k2;
     const unsigned long long b1 = __ballot(e1), b2 = __ballot(e2);
     const int r1 = eq1 + __popcll(b1 & lt), r2 = eq2 + __popcll(b2 & lt);
@@ -380,27 +365,10 @@ __global__ void __launch_bounds__(256) select_kernel(const float* __restrict__ s
     if (marg && is_m) marg[row * n_m + nm + __popcll(bm & lt)] = j;
     nc += __popcll(bc);
     nm += __popcll(bm);
-    if constexpr (PAIR) {
-      if (lane == 0) in_list[w][m] = bc;
-    }
-    if (mbits && live && lane < 2) {  // the marginal ballot of these 64 key blocks = two words of the bit matrix
+    if (mbits && lane < 2) {  // the marginal ballot of these 64 key blocks = two words of the bit matrix
       const int kt = 2 * m + lane;
       if (kt < KT) mbits[((size_t)bh * KT + kt) * TqP + i] = (uint32_t)(bm >> (32 * lane));
     }
-  }
-  if constexpr (PAIR) {
-    __syncthreads();
-    const int TqW = (Tq + 1) / 2;
-    if ((w & 1) || pair >= rows / Tq * TqW) return;
-    int32_t* dst = ulist + (size_t)pair * (2 * n_c);
-    int n = 0;
-    for (int m = 0; 64 * m < Tk; ++m) {
-      const unsigned long long first = in_list[w][m], second = in_list[w + 1][m], either = first | second;
-      if ((either >> lane) & 1)
-        dst[n + __popcll(either & lt)] = (lane + 64 * m) | (int)(((first >> lane) & 1) << 30) | (int)(((second >> lane) & 1) << 31);
-      n += __popcll(either);
-    }
-    if (lane == 0) ulen[pair] = n;
   }
 }
 
@@ -446,28 +414,23 @@ void launch_scores(const Problem& p, const float* qbar, const float* kbar, float
 }
 
 void launch_select(const Problem& p, const float* scores, int8_t* mask, int32_t* crit, int32_t* marg,
-                   uint32_t* mbits, int32_t* pair_list, int32_t* pair_len, hipStream_t stream) {
+                   uint32_t* mbits, hipStream_t stream) {
   const int rows = p.BH * p.Tq, need = (p.Tk + 63) / 64;
-  const int waves = pair_list ? 2 * p.BH * ((p.Tq + 1) / 2) : rows;
-  const unsigned grid = (unsigned)((waves + 3) / 4);
-#define SLA_SELECT(K)                                                                                              \
-  {                                                                                                                \
-    if (pair_list) select_kernel<K, true><<<grid, 256, 0, stream>>>(scores, rows, p.Tq, p.Tk, p.n_c, p.n_m, mask, crit, marg, mbits, pair_list, pair_len); \
-    else select_kernel<K, false><<<grid, 256, 0, stream>>>(scores, rows, p.Tq, p.Tk, p.n_c, p.n_m, mask, crit, marg, mbits, nullptr, nullptr);             \
-  }
+  const unsigned grid = (unsigned)((rows + 3) / 4);
+#define SLA_SELECT(K) select_kernel<K><<<grid, 256, 0, stream>>>(scores, rows, p.Tq, p.Tk, p.n_c, p.n_m, mask, crit, marg, mbits)
   // registers per lane: the smallest instantiation that holds the row
-  if (need <= 2) SLA_SELECT(2)
-  else if (need <= 4) SLA_SELECT(4)
-  else if (need <= 8) SLA_SELECT(8)
-  else if (need <= 12) SLA_SELECT(12)
-  else if (need <= 16) SLA_SELECT(16)
-  else if (need <= 20) SLA_SELECT(20)
-  else if (need <= 24) SLA_SELECT(24)
-  else if (need <= 32) SLA_SELECT(32)
-  else if (need <= 48) SLA_SELECT(48)
-  else if (need <= 64) SLA_SELECT(64)
-  else if (need <= 96) SLA_SELECT(96)
-  else SLA_SELECT(128)
+  if (need <= 2) SLA_SELECT(2);
+  else if (need <= 4) SLA_SELECT(4);
+  else if (need <= 8) SLA_SELECT(8);
+  else if (need <= 12) SLA_SELECT(12);
+  else if (need <= 16) SLA_SELECT(16);
+  else if (need <= 20) SLA_SELECT(20);
+  else if (need <= 24) SLA_SELECT(24);
+  else if (need <= 32) SLA_SELECT(32);
+  else if (need <= 48) SLA_SELECT(48);
+  else if (need <= 64) SLA_SELECT(64);
+  else if (need <= 96) SLA_SELECT(96);
+  else SLA_SELECT(128);
 #undef SLA_SELECT
 }
 

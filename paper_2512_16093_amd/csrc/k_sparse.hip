@@ -33,7 +33,7 @@ namespace sla {
 struct SparseDims {
   int N, Tq, Tk, n_c, total, per_xcd, phi, has_lin, out_f32, H;
   int q8_rows;       // rows per (b,h) of the Q code tensor (N rounded up to whole groups of 128)
-  int TqW, ustride;  // workgroup tiles per (b,h); entries per row of the paired lists (see PAIRED)
+  int TqW;           // workgroup tiles per (b,h)
   Layout lq, lo;  // of q and out
 };
 // The pointers are separate __restrict__ kernel parameters (not struct members) so the
@@ -54,8 +54,7 @@ struct SparseArgs {
   float* __restrict__ lse;
   int N, Tq, Tk, n_c, total, per_xcd, phi, has_lin, out_f32, H;
   Layout lq, lo;
-  int TqW, ustride, q8_rows;
-  const int32_t* __restrict__ ulen;
+  int TqW, q8_rows;
 };
 
 constexpr int EPI_STRIDE = 32 * 4 + 16;         // bytes per staged output row (32 fp32 + pad)
@@ -220,24 +219,25 @@ __device__ __forceinline__ void stage_barrier() {
   asm volatile("" ::: "memory");
 }
 
-// PAIRED (query blocks of 64, NW = 4): a workgroup serves TWO adjacent query blocks, wavefronts 0-1
-// the first and 2-3 the second, over the merged list of their critical key blocks (crit_ then
-// holds, per pair, the ascending union; bit 30 / 31 of an entry says that the first / second
-// block of the pair has this key block in its own list; ulen_ holds the lengths).  Every K/V
-// record is fetched once for both blocks and there are two wavefronts per SIMD (a workgroup of
-// two wavefronts per 64 KB of staging rings would leave one).  A wavefront whose block does not
-// have the current key block in its list goes through the step like the others and then drops
-// what it computed: zero codes contribute nothing, the reference level is put back.
-template <int NW, bool PAIRED>
+// Query blocks of 64 (NW = 2): a workgroup of two wavefronts per block, four of them on a compute unit.  Two
+// wavefronts per SIMD need staging rings of at most 40 KiB, so K has three slots and V two (of 8 KiB each): K(b + 3)
+// and V(b) are requested in step b, V at its start, and V has to land within the step -- the other three workgroups'
+// arithmetic covers that.  (A workgroup of four wavefronts over the merged lists of two adjacent blocks fetched
+// every record once for both, but a wavefront whose block did not have a key block idled through its step:
+// 40 heads x 75600 tokens, top 15 %, whole call: 18.2 ms against 14.4 ms.)
+// SHARED (query blocks of 64, NW = 4, every key block critical): all lists are the same, so a workgroup serves two
+// adjacent query blocks, wavefronts 0-1 the first and 2-3 the second, and fetches every record once for both
+// (12 heads x 32760 tokens, whole call: 3.43 ms against 3.90 ms one by one; 3.57 ms as merged lists).
+template <int NW, bool SHARED>
 __global__ void __launch_bounds__(NW * 64, 2) sparse_fwd_kernel(
     const bf16_t* __restrict__ q_, const int8_t* __restrict__ q8_, const int32_t* __restrict__ crit_, const int8_t* __restrict__ k8_,
     const uint8_t* __restrict__ v8_, const float* __restrict__ dq_, const float* __restrict__ dk_,
     const float* __restrict__ dv_, const bf16_t* __restrict__ HZ_, const bf16_t* __restrict__ bias_,
-    void* __restrict__ out_, float* __restrict__ lse_, const int32_t* __restrict__ ulen_, const SparseDims dims) {
-  static_assert(!PAIRED || NW == 4, "paired mode: four wavefronts, two per query block of 64");
+    void* __restrict__ out_, float* __restrict__ lse_, const SparseDims dims) {
+  static_assert(!SHARED || NW == 4, "shared lists: four wavefronts, two per query block of 64");
   const SparseArgs A = {q_, q8_, crit_, k8_, v8_, dq_, dk_, dv_, HZ_, bias_, out_, lse_, dims.N, dims.Tq, dims.Tk,
                         dims.n_c, dims.total, dims.per_xcd, dims.phi, dims.has_lin, dims.out_f32, dims.H,
-                        dims.lq, dims.lo, dims.TqW, dims.ustride, dims.q8_rows, ulen_};
+                        dims.lq, dims.lo, dims.TqW, dims.q8_rows};
   constexpr int NT = NW * 64;
   constexpr int CH = 2 * (KV_FRAG_BYTES / 16) / NT;  // 16-byte chunks per thread per block
   constexpr int BQ = NW * 32;
@@ -246,6 +246,9 @@ __global__ void __launch_bounds__(NW * 64, 2) sparse_fwd_kernel(
   // wavefront w reuses K buffer w for the output transposition.
   __shared__ uint4 kst0[KV_FRAG_BYTES / 16], kst1[KV_FRAG_BYTES / 16], kst2[KV_FRAG_BYTES / 16], kst3[KV_FRAG_BYTES / 16];
   __shared__ uint4 vst0[KV_FRAG_BYTES / 16], vst1[KV_FRAG_BYTES / 16], vst2[KV_FRAG_BYTES / 16], vst3[KV_FRAG_BYTES / 16];
+  constexpr int SLOT = KV_FRAG_BYTES / 16;
+  __shared__ uint4 ring[5 * SLOT];
+  constexpr bool SMALL = NW == 2;
   static_assert(32 * EPI_STRIDE <= KV_FRAG_BYTES, "output staging must fit one stage buffer");
 
   // Workgroup ids are dealt round-robin over the 8 XCDs.  All XCDs work on the SAME head at
@@ -260,10 +263,9 @@ __global__ void __launch_bounds__(NW * 64, 2) sparse_fwd_kernel(
   if (i >= A.TqW) return;
 
   const int t = threadIdx.x, lane = t & 63, w = t >> 6, l32 = lane & 31, hf = lane >> 5;
-  const int pair_half = PAIRED ? __builtin_amdgcn_readfirstlane(w >> 1) : 0;
-  // the query block whose scale, summaries and list membership this wavefront uses (an odd block
-  // count leaves the last pair's second half without queries: clamped, nothing of it is stored)
-  const int iq = PAIRED ? min(2 * i + pair_half, A.Tq - 1) : i;
+  // the query block whose scale and summaries this wavefront uses (an odd block count leaves the last
+  // pair's second half without queries: clamped, nothing of it is stored)
+  const int iq = SHARED ? min(2 * i + __builtin_amdgcn_readfirstlane(w >> 1), A.Tq - 1) : i;
   const int rowid = bh * A.Tq + iq;
   const int qrow = i * BQ + 32 * w + l32;
   const bool qok = qrow < A.N;
@@ -297,13 +299,9 @@ __global__ void __launch_bounds__(NW * 64, 2) sparse_fwd_kernel(
   for (int e = 0; e < 16; ++e) bias16[e] = BIAS_I;
   asm volatile("" : "+v"(bias16));  // kept in registers: the C operand of the first score MFMA of every half
 
-  const int listrow = bh * A.TqW + i;
-  const int n_c = PAIRED ? A.ulen[listrow] : A.n_c;
+  const int n_c = A.n_c;
   // the critical list and the K scales are read through the scalar unit (uniform addresses)
-  const int32_t* __restrict__ crow = PAIRED ? A.crit + (size_t)listrow * A.ustride : A.crit + (size_t)rowid * n_c;
-  constexpr int JMASK = PAIRED ? 0x3FFFFFFF : -1;  // an entry's key block index
-  // does this wavefront's query block have entry e in its own list?
-  auto mine = [&](int e) { return !PAIRED || ((e >> (30 + pair_half)) & 1); };
+  const int32_t* __restrict__ crow = A.crit + ((size_t)bh * A.Tq + (SHARED ? 2 * i : i)) * n_c;
   const float* __restrict__ dkrow = A.dk + (size_t)bh * A.Tk;
   const size_t rec0 = (size_t)bh * A.Tk * KV_FRAG_BYTES;
   // Asynchronous global -> LDS copy of one block's K or V record (no registers in between).
@@ -324,7 +322,7 @@ __global__ void __launch_bounds__(NW * 64, 2) sparse_fwd_kernel(
   auto fetch_rec = [&](const char* base_bh, int j, uint4* dst) {
     static_assert(KV_FRAG_BYTES == 1 << 13, "record size");
     const char* rec = base_bh + (unsigned)__builtin_amdgcn_readfirstlane(j << 13);
-    const unsigned lds_addr = (unsigned)(uintptr_t)(lds_ptr_t)(dst + w_s * PW * 64);
+    const unsigned lds_addr = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(lds_ptr_t)(dst + w_s * PW * 64));
     if constexpr (PW == 2) {
       asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\t"
                    "global_load_lds_dwordx4 %1, %0\n\t"
@@ -366,13 +364,15 @@ __global__ void __launch_bounds__(NW * 64, 2) sparse_fwd_kernel(
   // last entry of the (ascending) list; it is peeled off the loop so that masking its missing
   // keys costs the other blocks nothing.
   const int last = n_c - 1;
-  const bool has_tail = ragged && n_c > 0 && (crow[last] & JMASK) == A.Tk - 1;
+  const bool has_tail = ragged && n_c > 0 && (crow[last]) == A.Tk - 1;
   // (SLA_FULL_WAITS: a checking build that waits for EVERY copy at each step instead of counting the
   // copies still allowed in flight; results must be bit-identical to the counting build.)
 #ifdef SLA_FULL_WAITS
   constexpr int WAIT_KEEP2 = 0x0070;
 #else
-  constexpr int WAIT_KEEP2 = (2 * CH >= 16) ? 0x4070 : (0x0070 | (2 * CH));  // s_waitcnt vmcnt(2*CH) lgkmcnt(0)
+  constexpr int KEEP = SMALL ? PW : 2 * CH;           // copies that may stay in flight at the end of a step
+  static_assert(KEEP < 16, "the low counter field");
+  constexpr int WAIT_KEEP2 = 0x0070 | KEEP;           // s_waitcnt vmcnt(KEEP) lgkmcnt(0)
 #endif
   constexpr int WAIT_ALL = 0x0070;                                            // s_waitcnt vmcnt(0) lgkmcnt(0)
   constexpr int WAIT_KEEP_ALL_VM = 0xC07F;                                    // s_waitcnt lgkmcnt(0) only (vmcnt 63)
@@ -382,65 +382,7 @@ __global__ void __launch_bounds__(NW * 64, 2) sparse_fwd_kernel(
   int sc_prev = 127;          // E8M0 scale of the P codes of block b-1 (this lane's half of it)
 
 #define SB __builtin_amdgcn_sched_barrier(0);
-#define SLA_STEP_P(B, KNEXT, VPREV, KFILL, VFILL, PBP, PBN)                                           \
-  {                                                                                                   \
-    const int b_ = (B);                                                                               \
-    /* ---- phase 1 */                                                                                \
-    read4(VPREV, lane, 0, vfa);                                                                       \
-    read4(KNEXT, lane, 0, kfA);                                                                       \
-    fetch_rec(k8_bh, j4, KFILL);                                                                       \
-    const int jn_ = crow[min(b_ + 5, last)] & JMASK;                                                  \
-    const int eb_ = PAIRED ? crow[b_] : 0;                                                            \
-    const float rk_ = r;                                                                              \
-    const float dn_ = dk_of(j4);                                                                      \
-    const BlockConsts bc_ = block_consts(cq * d0);                                                    \
-    SB s1 = qk_step(kfB[0], q8[0], bias16);                                                           \
-    SB const int mA_ = half_max<false>(s0, 0, hf, 0);                                                 \
-    SB s1 = qk_step(kfB[1], q8[1], s1);                                                               \
-    SB const float offsA_ = new_reference(mA_, bc_, pos_inf, r);                                      \
-    const float rA_ = r;                                                                              \
-    SB s1 = qk_step(kfB[2], q8[2], s1);                                                               \
-    SB PBN[0] = codes_quad<false>(s0, 0, 0, hf, bc_.c2s, offsA_, 0, PBN[0]);                                      \
-    SB s1 = qk_step(kfB[3], q8[3], s1);                                                               \
-    SB PBN[1] = codes_quad<false>(s0, 1, 0, hf, bc_.c2s, offsA_, 0, PBN[1]);                                      \
-    SB pv_tile(vfa[0], vfa[1], PBP, sc_prev, acc[0]);                                                 \
-    SB PBN[2] = codes_quad<false>(s0, 2, 0, hf, bc_.c2s, offsA_, 0, PBN[2]);                                      \
-    SB pv_tile(vfa[2], vfa[3], PBP, sc_prev, acc[1]);                                                 \
-    SB PBN[3] = codes_quad<false>(s0, 3, 0, hf, bc_.c2s, offsA_, 0, PBN[3]);                                      \
-    /* ---- phase 2 */                                                                                \
-    read4(VPREV, lane, 4, vfb);                                                                       \
-    read4(KNEXT, lane, 4, kfB);                                                                       \
-    fetch_rec(v8_bh, j2, VFILL);                                                                       \
-    SB s0 = qk_step(kfA[0], q8[0], bias16);                                                           \
-    SB const int mB_ = half_max<false>(s1, 32, hf, 0);                                                \
-    SB s0 = qk_step(kfA[1], q8[1], s0);                                                               \
-    SB const float offsB_ = new_reference(mB_, bc_, pos_inf, r);                                      \
-    SB s0 = qk_step(kfA[2], q8[2], s0);                                                               \
-    SB PBN[4] = codes_quad<false>(s1, 0, 32, hf, bc_.c2s, offsB_, 0, PBN[4]);                                     \
-    SB s0 = qk_step(kfA[3], q8[3], s0);                                                               \
-    SB PBN[5] = codes_quad<false>(s1, 1, 32, hf, bc_.c2s, offsB_, 0, PBN[5]);                                     \
-    SB pv_tile(vfb[0], vfb[1], PBP, sc_prev, acc[2]);                                                 \
-    SB PBN[6] = codes_quad<false>(s1, 2, 32, hf, bc_.c2s, offsB_, 0, PBN[6]);                                     \
-    SB pv_tile(vfb[2], vfb[3], PBP, sc_prev, acc[3]);                                                 \
-    SB PBN[7] = codes_quad<false>(s1, 3, 32, hf, bc_.c2s, offsB_, 0, PBN[7]);                                     \
-    SB pv_rowsum(ones, PBP, sc_prev, accl);                                                           \
-    if constexpr (PAIRED) {                                                                           \
-      if (!mine(eb_)) { PBN = v8i{}; r = rk_; }                                                       \
-    }                                                                                                 \
-    SB const float rsel_ = (PAIRED && !mine(eb_)) ? rk_ : (hf ? r : rA_);   /* level of this lane's half of the new codes */ \
-    j2 = j3; j3 = j4; j4 = jn_;                                                                       \
-    d0 = d1; d1 = d2; d2 = d3; d3 = dn_;                                                              \
-    /* anchor: keeps every piece inside this step */                                                  \
-    asm volatile("" : "+v"(PBN), "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "+v"(accl),  \
-                 "+v"(s0), "+s"(j4), "+s"(d3));                                                       \
-    SB if (__any(r - R > 64.f)) renormalise(r, R, Rm127, acc, accl);                                  \
-    sc_prev = level_scale(rsel_, Rm127);                                                                  \
-    __builtin_amdgcn_s_waitcnt(WAIT_KEEP2);                                                           \
-    stage_barrier();                                                                                  \
-  }
-
-  // The same step for unpaired workgroups, with the reference bookkeeping off the common path.  A
-  // query's level r only ever rises, and after the first few blocks it has usually reached its
+  // The reference bookkeeping is off the common path: a query's level r only ever rises, and after the first few blocks it has usually reached its
   // final value: a half's maximum is first tested in each lane alone (one fma and one compare: r
   // is an integer, so the rounded-up level of a lane pair exceeds r exactly when one of its two
   // lanes' own value does), and only if some lane of the wavefront passes does the wavefront join
@@ -457,15 +399,15 @@ __global__ void __launch_bounds__(NW * 64, 2) sparse_fwd_kernel(
     offs_ = bc_.lnb - r;                                                                              \
     moved = 1;                                                                                        \
   }
-#define SLA_STEP_F(B, KNEXT, VPREV, KFILL, VFILL, PBP, PBN)                                           \
+#define SLA_STEP(B, KNEXT, VPREV, KFILL, VFILL, PBP, PBN)                                           \
   {                                                                                                   \
     const int b_ = (B);                                                                               \
     /* ---- phase 1 */                                                                                \
     read4(VPREV, lane, 0, vfa);                                                                       \
     read4(KNEXT, lane, 0, kfA);                                                                       \
-    fetch_rec(k8_bh, j4, KFILL);                                                                       \
-    const int jn_ = crow[min(b_ + 5, last)];                                                          \
-    const float dn_ = dk_of(j4);                                                                      \
+    if constexpr (SMALL) fetch_rec(v8_bh, j0, VFILL); else fetch_rec(k8_bh, j4, KFILL);               \
+    const int jn_ = crow[min(b_ + (SMALL ? 4 : 5), last)];                                            \
+    const float dn_ = dk_of(SMALL ? j3 : j4);                                                         \
     const BlockConsts bc_ = block_consts(cq * d0);                                                    \
     float offs_ = bc_.lnb - r;                                                                        \
     const int moved_before = moved;                                                                   \
@@ -488,7 +430,7 @@ __global__ void __launch_bounds__(NW * 64, 2) sparse_fwd_kernel(
     /* ---- phase 2 */                                                                                \
     read4(VPREV, lane, 4, vfb);                                                                       \
     read4(KNEXT, lane, 4, kfB);                                                                       \
-    fetch_rec(v8_bh, j2, VFILL);                                                                       \
+    if constexpr (SMALL) fetch_rec(k8_bh, j3, KFILL); else fetch_rec(v8_bh, j2, VFILL);               \
     SB s0 = qk_step(kfA[0], q8[0], bias16);                                                           \
     SB const int mB_ = half_max<false>(s1, 32, hf, 0);                                                \
     SB s0 = qk_step(kfA[1], q8[1], s0);                                                               \
@@ -502,11 +444,11 @@ __global__ void __launch_bounds__(NW * 64, 2) sparse_fwd_kernel(
     SB pv_tile(vfb[2], vfb[3], PBP, sc_prev, acc[3]);                                                 \
     SB PBN[7] = codes_quad<false>(s1, 3, 32, hf, bc_.c2s, offs_, 0, PBN[7]);                          \
     SB pv_rowsum(ones, PBP, sc_prev, accl);                                                           \
-    j2 = j3; j3 = j4; j4 = jn_;                                                                       \
-    d0 = d1; d1 = d2; d2 = d3; d3 = dn_;                                                              \
+    if constexpr (SMALL) { j0 = j1; j1 = j2; j2 = j3; j3 = jn_; d0 = d1; d1 = d2; d2 = dn_; }         \
+    else { j2 = j3; j3 = j4; j4 = jn_; d0 = d1; d1 = d2; d2 = d3; d3 = dn_; }                         \
     /* anchor: keeps every piece inside this step */                                                  \
     asm volatile("" : "+v"(PBN), "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "+v"(accl),  \
-                 "+v"(s0), "+s"(j4), "+s"(d3));                                                       \
+                 "+v"(s0), "+s"(SMALL ? j3 : j4), "+s"(SMALL ? d2 : d3));                             \
     SB if (moved | moved_before) {                                                                    \
       if (__any(r - R > 64.f)) renormalise(r, R, Rm127, acc, accl);                                   \
       sc_prev = level_scale(hf ? r : rA_, Rm127);   /* level of this lane's half of the new codes */  \
@@ -514,29 +456,33 @@ __global__ void __launch_bounds__(NW * 64, 2) sparse_fwd_kernel(
     __builtin_amdgcn_s_waitcnt(WAIT_KEEP2);                                                           \
     stage_barrier();                                                                                  \
   }
-#define SLA_STEP(B, KNEXT, VPREV, KFILL, VFILL, PBP, PBN)                                             \
-  if constexpr (PAIRED) SLA_STEP_P(B, KNEXT, VPREV, KFILL, VFILL, PBP, PBN)                           \
-  else SLA_STEP_F(B, KNEXT, VPREV, KFILL, VFILL, PBP, PBN)
   int moved = 1;              // did the reference level of any query of this wavefront rise in the last step?
 
   if (n_c > 0) {  // (an empty list leaves only the linear term of the epilogue)
     // step 0 has no previous block: it multiplies all-zero P codes with this all-zero V slot
-    for (int e = t; e < KV_FRAG_BYTES / 16; e += NT) vst3[e] = make_uint4(0, 0, 0, 0);
+    uint4* const vzero = SMALL ? ring + 4 * SLOT : vst3;
+    for (int e = t; e < KV_FRAG_BYTES / 16; e += NT) vzero[e] = make_uint4(0, 0, 0, 0);
     // indices of blocks 0..4 and K scales of blocks 0..3 (clamped to the list)
-    const int j0 = crow[0] & JMASK, j1 = crow[min(1, last)] & JMASK;
-    int j2 = crow[min(2, last)] & JMASK, j3 = crow[min(3, last)] & JMASK, j4 = crow[min(4, last)] & JMASK;
+    int j0 = crow[0], j1 = crow[min(1, last)];
+    int j2 = crow[min(2, last)], j3 = crow[min(3, last)], j4 = crow[min(4, last)];
     float d0 = dk_of(j0), d1 = dk_of(j1), d2 = dk_of(j2), d3 = dk_of(j3);
     // three groups of copies, in the order the steps will wait for them
-    fetch_rec(k8_bh, j0, kst0);
-    fetch_rec(k8_bh, j1, kst1);
-    fetch_rec(k8_bh, j2, kst2);
-    fetch_rec(v8_bh, j0, vst0);
-    fetch_rec(k8_bh, j3, kst3);
-    fetch_rec(v8_bh, j1, vst1);
+    if constexpr (SMALL) {
+      fetch_rec(k8_bh, j0, ring);
+      fetch_rec(k8_bh, j1, ring + SLOT);
+      fetch_rec(k8_bh, j2, ring + 2 * SLOT);
+    } else {
+      fetch_rec(k8_bh, j0, kst0);
+      fetch_rec(k8_bh, j1, kst1);
+      fetch_rec(k8_bh, j2, kst2);
+      fetch_rec(v8_bh, j0, vst0);
+      fetch_rec(k8_bh, j3, kst3);
+      fetch_rec(v8_bh, j1, vst1);
+    }
     __builtin_amdgcn_s_waitcnt(WAIT_KEEP2);  // K(0), K(1) have landed
     stage_barrier();
-    read4(kst0, lane, 0, kfA);
-    read4(kst0, lane, 4, kfB);
+    read4(SMALL ? ring : kst0, lane, 0, kfA);
+    read4(SMALL ? ring : kst0, lane, 4, kfB);
     // Step 0 refills K slot 0 right away: every wavefront must have its fragments of block 0 in
     // registers before any wavefront starts that copy (inside the loop the barrier that ends a step
     // plays this part for the slot the next step refills).
@@ -547,31 +493,49 @@ __global__ void __launch_bounds__(NW * 64, 2) sparse_fwd_kernel(
     for (int u = 1; u < 4; ++u) s0 = qk_step(kfA[u], q8[u], s0);
     const int nb_main = has_tail ? n_c - 1 : n_c;
     int b = 0;
-    for (; b + 4 <= nb_main; b += 4) {
-      SLA_STEP(b, kst1, vst3, kst0, vst2, pb_b, pb_a)
-      SLA_STEP(b + 1, kst2, vst0, kst1, vst3, pb_a, pb_b)
-      SLA_STEP(b + 2, kst3, vst1, kst2, vst0, pb_b, pb_a)
-      SLA_STEP(b + 3, kst0, vst2, kst3, vst1, pb_a, pb_b)
-    }
-    // the (up to three) remaining steps keep the a/b alternation by copying the codes back
-    if (b < nb_main) {
-      SLA_STEP(b, kst1, vst3, kst0, vst2, pb_b, pb_a)
-      pb_b = pb_a;
-    }
-    if (b + 1 < nb_main) {
-      SLA_STEP(b + 1, kst2, vst0, kst1, vst3, pb_b, pb_a)
-      pb_b = pb_a;
-    }
-    if (b + 2 < nb_main) {
-      SLA_STEP(b + 2, kst3, vst1, kst2, vst0, pb_b, pb_a)
-      pb_b = pb_a;
+    if constexpr (SMALL) {
+      int kn = SLOT, k2 = 2 * SLOT, kf = 0;   // K slots of blocks b + 1, b + 2 and of the retired block b (filled with b + 3)
+      uint4 *const v0 = ring + 3 * SLOT, *const v1 = ring + 4 * SLOT;
+#define SLA_TURN { const int t_ = kn; kn = k2; k2 = kf; kf = t_; }
+      for (; b + 2 <= nb_main; b += 2) {
+        SLA_STEP(b, ring + kn, v1, ring + kf, v0, pb_b, pb_a)
+        SLA_TURN
+        SLA_STEP(b + 1, ring + kn, v0, ring + kf, v1, pb_a, pb_b)
+        SLA_TURN
+      }
+      if (b < nb_main) {
+        SLA_STEP(b, ring + kn, v1, ring + kf, v0, pb_b, pb_a)
+        pb_b = pb_a;
+      }
+#undef SLA_TURN
+      if (has_tail) fetch_rec(v8_bh, j0, (last & 1) ? v1 : v0);   // (the main loop's steps copy their own block's V)
+    } else {
+      for (; b + 4 <= nb_main; b += 4) {
+        SLA_STEP(b, kst1, vst3, kst0, vst2, pb_b, pb_a)
+        SLA_STEP(b + 1, kst2, vst0, kst1, vst3, pb_a, pb_b)
+        SLA_STEP(b + 2, kst3, vst1, kst2, vst0, pb_b, pb_a)
+        SLA_STEP(b + 3, kst0, vst2, kst3, vst1, pb_a, pb_b)
+      }
+      // the (up to three) remaining steps keep the a/b alternation by copying the codes back
+      if (b < nb_main) {
+        SLA_STEP(b, kst1, vst3, kst0, vst2, pb_b, pb_a)
+        pb_b = pb_a;
+      }
+      if (b + 1 < nb_main) {
+        SLA_STEP(b + 1, kst2, vst0, kst1, vst3, pb_b, pb_a)
+        pb_b = pb_a;
+      }
+      if (b + 2 < nb_main) {
+        SLA_STEP(b + 2, kst3, vst1, kst2, vst0, pb_b, pb_a)
+        pb_b = pb_a;
+      }
     }
     // drain: wait for every copy (the repeated ones too) and publish; from here on plain reads
     __builtin_amdgcn_s_waitcnt(WAIT_ALL);
     stage_barrier();
     if (has_tail) {  // the ragged last key block: s0 and kfB are ready, P.V of the block before it is due
       const int sp = (nb_main + 3) & 3;
-      const uint4* vp = sp == 0 ? vst0 : sp == 1 ? vst1 : sp == 2 ? vst2 : vst3;
+      const uint4* vp = SMALL ? ring + (3 + (sp & 1)) * SLOT : sp == 0 ? vst0 : sp == 1 ? vst1 : sp == 2 ? vst2 : vst3;
       read4(vp, lane, 0, vfa);
       read4(vp, lane, 4, vfb);
       const BlockConsts bct = block_consts(cq * d0);
@@ -583,7 +547,6 @@ __global__ void __launch_bounds__(NW * 64, 2) sparse_fwd_kernel(
       pv_tile(vfb[0], vfb[1], pb_b, sc_prev, acc[2]);
       pv_tile(vfb[2], vfb[3], pb_b, sc_prev, acc[3]);
       pv_rowsum(ones, pb_b, sc_prev, accl);
-      const float rkt = r;
       const int mAt = half_max<true>(s0, 0, hf, kvalid_last);
       const float offsAt = new_reference(mAt, bct, pos_inf, r);
       const float rAt = r;
@@ -595,15 +558,12 @@ __global__ void __launch_bounds__(NW * 64, 2) sparse_fwd_kernel(
 #pragma unroll
       for (int g = 0; g < 4; ++g) pb_t[4 + g] = codes_quad<true>(s1, g, 32, hf, bct.c2s, offsBt, kvalid_last, pb_t[4 + g]);
       pb_b = pb_t;
-      if constexpr (PAIRED) {
-        if (!mine(crow[last])) { pb_b = v8i{}; r = rkt; }
-      }
       if (__any(r - R > 64.f)) renormalise(r, R, Rm127, acc, accl);
-      sc_prev = level_scale((PAIRED && !mine(crow[last])) ? rkt : (hf ? r : rAt), Rm127);
+      sc_prev = level_scale(hf ? r : rAt, Rm127);
     }
     {  // P.V of the last block
       const int sl = last & 3;
-      const uint4* vc = sl == 0 ? vst0 : sl == 1 ? vst1 : sl == 2 ? vst2 : vst3;
+      const uint4* vc = SMALL ? ring + (3 + (sl & 1)) * SLOT : sl == 0 ? vst0 : sl == 1 ? vst1 : sl == 2 ? vst2 : vst3;
       read4(vc, lane, 0, vfa);
       read4(vc, lane, 4, vfb);
       pv_tile(vfa[0], vfa[1], pb_b, sc_prev, acc[0]);
@@ -614,8 +574,6 @@ __global__ void __launch_bounds__(NW * 64, 2) sparse_fwd_kernel(
     }
   }
 #undef SLA_STEP
-#undef SLA_STEP_P
-#undef SLA_STEP_F
 #undef SLA_RAISE
 #undef SB
 
@@ -704,7 +662,7 @@ __global__ void __launch_bounds__(NW * 64, 2) sparse_fwd_kernel(
   // Wavefront w stages in K slot w, which nobody reads or fills any more (the drain barrier above came
   // after the last read of a K slot and after every copy had landed), so no workgroup barrier is
   // needed: a wavefront's LDS operations execute in the order it issues them.
-  unsigned char* my = (unsigned char*)(w == 0 ? kst0 : w == 1 ? kst1 : w == 2 ? kst2 : kst3);
+  unsigned char* my = (unsigned char*)(SMALL ? ring + w * SLOT : w == 0 ? kst0 : w == 1 ? kst1 : w == 2 ? kst2 : kst3);
 #pragma unroll
   for (int ct = 0; ct < 4; ++ct) {
     __builtin_amdgcn_wave_barrier();   // (compiler fence: the stores below stay behind the reads of the pass before)
@@ -734,8 +692,7 @@ __global__ void __launch_bounds__(NW * 64, 2) sparse_fwd_kernel(
 void launch_sparse_fwd(const void* q, const int8_t* q8, const Problem& p, const int32_t* crit, int n_c, const int8_t* k8,
                        const uint8_t* v8, const float* dq, const float* dk, const float* dv,
                        const bf16_t* HZ, const bf16_t* proj_b, int phi_kind, bool has_linear,
-                       void* out, bool out_f32, float* lse, const int32_t* pair_list, const int32_t* pair_len,
-                       hipStream_t stream) {
+                       void* out, bool out_f32, float* lse, bool all_critical, hipStream_t stream) {
   SparseDims dm;
   dm.N = p.N;
   dm.Tq = p.Tq;
@@ -749,22 +706,17 @@ void launch_sparse_fwd(const void* q, const int8_t* q8, const Problem& p, const 
   dm.q8_rows = (p.N + 127) / 128 * 128;
   dm.lq = p.lq;
   dm.lo = p.lo;
-  const bool paired = p.block_q == 64 && n_c > 0 && pair_list && pair_len;
-  dm.TqW = paired ? (p.Tq + 1) / 2 : p.Tq;
-  dm.ustride = 2 * n_c;
+  const bool shared = p.block_q == 64 && all_critical;
+  dm.TqW = shared ? (p.Tq + 1) / 2 : p.Tq;
   dm.per_xcd = (dm.TqW + 7) / 8;  // workgroup tiles of one head per XCD
   const bf16_t* bias = has_linear ? proj_b : nullptr;
   const unsigned grid = (unsigned)(8 * dm.per_xcd * p.BH);
-  if (paired) {
-    sparse_fwd_kernel<4, true><<<grid, 256, 0, stream>>>((const bf16_t*)q, q8, pair_list, k8, v8, dq, dk, dv, HZ, bias, out,
-                                                         lse, pair_len, dm);
-  } else if (p.block_q == 128) {
-    sparse_fwd_kernel<4, false><<<grid, 256, 0, stream>>>((const bf16_t*)q, q8, crit, k8, v8, dq, dk, dv, HZ, bias, out, lse,
-                                                          nullptr, dm);
-  } else {
-    sparse_fwd_kernel<2, false><<<grid, 128, 0, stream>>>((const bf16_t*)q, q8, crit, k8, v8, dq, dk, dv, HZ, bias, out, lse,
-                                                          nullptr, dm);
-  }
+#define SLA_SPARSE(NW, SHARED) sparse_fwd_kernel<NW, SHARED><<<grid, NW * 64, 0, stream>>>( \
+      (const bf16_t*)q, q8, crit, k8, v8, dq, dk, dv, HZ, bias, out, lse, dm)
+  if (shared) SLA_SPARSE(4, true);
+  else if (p.block_q == 128) SLA_SPARSE(4, false);
+  else SLA_SPARSE(2, false);
+#undef SLA_SPARSE
 }
 
 }  // namespace sla

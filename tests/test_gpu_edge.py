@@ -136,7 +136,7 @@ def test_every_list_length_through_the_sparse_stage(n_c, bq):
     """The attention kernel's main loop takes four list entries per round, up to three more one by one, and the
     ragged last key block apart: lists of every remainder, with and without the last block, chosen at random
     (ascending, as the classification delivers them), through sla_sparse_attn_fwd against the oracle on the same mask.
-    With query blocks of 64 the kernel merges the lists of adjacent blocks (17 query blocks: the last pair has one)."""
+    With query blocks of 64 the loop takes two entries per round and its copy rings are shorter."""
     cfg = synth.custom_config(1, 2, (6, 7, 25), block_q=bq, topk_ratio=0.2, marginal_ratio=0.4, cfg_id=710)   # N = 1050, Tk = 17
     q, k, v = synth.make_qkv(cfg)
     Tq, Tk = -(-cfg.N // bq), -(-cfg.N // 64)
@@ -159,6 +159,19 @@ def test_every_list_length_through_the_sparse_stage(n_c, bq):
         pu.check_output(out[0, h], ref, "n_c %d head %d" % (n_c, h))
         dl = np.abs(lse[0, h] - ref_lse)
         assert dl.max() < 2e-2 and np.median(dl) < 1e-5
+
+
+@pytest.mark.parametrize("grid", [(6, 7, 25), (1, 8, 24), (2, 8, 8), (1, 5, 5)])   # 17 (ragged), 3, 2 and 1 query blocks
+def test_all_critical_blocks_of_64_queries_share_a_workgroup(grid):
+    """Every key block critical at query blocks of 64: two adjacent blocks then share one walk over the records.
+    The stage entry point (which takes any lists) walks them one by one: the same arithmetic, so the same bits."""
+    cfg = synth.custom_config(1, 2, grid, block_q=64, topk_ratio=1.0, marginal_ratio=0.0, cfg_id=740)
+    q, k, v = pu.to_dev(*synth.make_qkv(cfg))
+    Tk = -(-cfg.N // 64)
+    crit = torch.arange(Tk, dtype=torch.int32, device="cuda").repeat(1, cfg.H, Tk, 1).contiguous()
+    out = sla.sla_attention_fwd(q, k, v, 64, 64, 1.0, 0.0)
+    stage, _ = sla.sla_sparse_attn_fwd(q, k, v, crit, 64, 64)
+    assert torch.equal(out, stage.to(torch.bfloat16))
 
 
 def test_codes_of_blocks_with_tiny_maxima():
