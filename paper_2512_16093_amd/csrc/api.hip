@@ -237,7 +237,6 @@ struct BwdWorkspace {
   size_t dql;                // fp32 [BH, N, D]: the linear branch's share of dQ
   size_t dHZ;                // bf16 [BH, Tq, HZ_ROWS, D]: per query block dH^T and dZ
   size_t mbits_t;            // transposed marginal bit matrix
-  size_t wt;                 // bf16 [D, D]: W^T
   size_t dw_part;            // fp32 per-workgroup partial sums of dW and db (bwd_lin_q_partial_bytes)
   size_t total;
 };
@@ -253,7 +252,6 @@ BwdWorkspace make_bwd_workspace(const Problem& p, const Workspace& W) {
   b.dql = take(grad);
   b.dHZ = take(lin ? BH * (size_t)p.Tq * HZ_ELEMS * 2 : 0);
   b.mbits_t = take(lin ? marginal_bits_t_bytes(p) : 0);
-  b.wt = take(D * D * 2);
   b.dw_part = take(lin ? bwd_lin_q_partial_bytes(p) : 0);
   b.total = o;
   return b;
@@ -666,8 +664,7 @@ int sla_attention_bwd_strided(const void* q, const void* k, const void* v, const
     launch_prep_kv(k, v, p, at<float>(ws, W.mu_k), at<float>(ws, W.amax_v), at<bf16_t>(ws, W.wfrag), phi_kind, false, true,
                    at<int8_t>(ws, W.k8), at<uint8_t>(ws, W.v8), at<float>(ws, W.dk), at<bf16_t>(ws, W.hz), s);
     launch_lin_accumulate(p, at<uint32_t>(ws, W.m0), at<bf16_t>(ws, W.hz), at<bf16_t>(ws, W.HZ), s);
-    launch_bwd_wt((const bf16_t*)proj_w, at<bf16_t>(ws, X.wt), s);
-    if (launch_bwd_lin_q(p, q, dout, at<bf16_t>(ws, W.HZ), at<bf16_t>(ws, X.wt), phi_kind, at<float>(ws, X.dql),
+    if (launch_bwd_lin_q(p, q, dout, at<bf16_t>(ws, W.HZ), (const bf16_t*)proj_w, phi_kind, at<float>(ws, X.dql),
                          at<bf16_t>(ws, X.dHZ), dproj_w, dproj_b, at<float>(ws, X.dw_part), s) != 0)
       return SLA_ERR_HIP;
     // G_j = sum of dH_i over the query blocks that hold key block j as marginal: the forward's

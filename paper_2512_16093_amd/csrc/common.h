@@ -130,6 +130,48 @@ __device__ __forceinline__ int vfrag_offset(int key, int ch) {
 }
 
 // ---------------------------------------------------------------------------
+// bf16 tiles (32 rows x 128 channels, row-major) in LDS as operands of v_mfma_f32_32x32x16_bf16.
+__device__ __forceinline__ v8bf as_v8bf(const uint4& x) { return __builtin_bit_cast(v8bf, x); }
+__device__ __forceinline__ v16f mfma_bf16(const uint4& a, const uint4& b, const v16f& c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_v8bf(a), as_v8bf(b), c, 0, 0, 0);
+}
+// Accumulator registers 8 s .. 8 s + 7 of a tile as a bf16 operand: contraction step s (16 rows) of
+// the product that contracts over the tile's rows.  Row of element kk for lane half hf:
+// 16 s + 8 (kk / 4) + 4 hf + kk % 4 -- the order t_op (below) reads a staged tile's rows in.
+__device__ __forceinline__ uint4 acc_operand(const v16f& a, int s) {
+  return uint4{pack_bf16x2(a[8 * s], a[8 * s + 1]), pack_bf16x2(a[8 * s + 2], a[8 * s + 3]),
+               pack_bf16x2(a[8 * s + 4], a[8 * s + 5]), pack_bf16x2(a[8 * s + 6], a[8 * s + 7])};
+}
+
+constexpr int TP = 304;             // bytes per staged row: 256 of data + 48 of skew (76 dwords: within a group of 16 lanes neither
+                                    // the 16-byte operand reads nor the transposing reads collide)
+constexpr int TILE_B = 32 * TP;     // one 32-token tile
+
+typedef short v4s __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ v4s read_tr(const unsigned char* p) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)p);
+}
+// Operand for a contraction over the channels: token (row) l32 of the tile, channels 16 ks + 8 hf + 0..7.
+__device__ __forceinline__ uint4 n_op(const unsigned char* tile, int l32, int hf, int ks) {
+  return *(const uint4*)(tile + l32 * TP + ks * 32 + hf * 16);
+}
+// This lane's address inside a 4-row x 16-column patch for the transposing read: in every group of
+// 16 lanes, lane i receives element i of rows 0..3 of the patch that the group's lanes address
+// (lane s: row s / 4, columns 4 (s % 4) .. + 3).  Lane group g = lane / 16 serves channels
+// 16 (g % 2) .. + 15 of a 32-channel tile and the token rows of lane half g / 2.
+__device__ __forceinline__ int tr_lane_offset(int lane) {
+  return (4 * (lane >> 5) + ((lane & 15) >> 2)) * TP + (16 * ((lane >> 4) & 1) + 4 * (lane & 3)) * 2;
+}
+// Operand for a contraction over the tile's tokens, step s (16 tokens), channel tile ct: channel
+// 32 ct + l32, tokens 16 s + 8 (kk / 4) + 4 hf + kk % 4 for kk = 0..7 -- the order in which
+// acc_operand hands over the rows of an accumulator tile.
+__device__ __forceinline__ uint4 t_op(const unsigned char* tile, int tr_off, int ct, int s) {
+  union { v4s h[2]; uint4 v; } u;
+  u.h[0] = read_tr(tile + tr_off + (16 * s) * TP + ct * 64);
+  u.h[1] = read_tr(tile + tr_off + (16 * s + 8) * TP + ct * 64);
+  return u.v;
+}
+// ---------------------------------------------------------------------------
 // Workspace map (all offsets 256-byte aligned).
 struct Workspace {
   size_t qbar, kbar;        // fp32 [BH,Tq,D], [BH,Tk,D] block means
@@ -255,10 +297,9 @@ int launch_bwd_dq(const Problem& p, const void* q, const void* dout, const void*
                    const float* lse2, const float* delta, const float* dq_lin, void* dq, hipStream_t stream);
 int launch_bwd_dkv(const Problem& p, const void* q, const void* dout, const void* k, const void* v, const int8_t* mask,
                     const float* lse2, const float* delta, const bf16_t* G, int phi_kind, void* dk, void* dv, hipStream_t stream);
-void launch_bwd_wt(const bf16_t* proj_w, bf16_t* wt, hipStream_t stream);
 size_t bwd_lin_q_partial_bytes(const Problem& p);
 double launch_mfma_rate(int kind, int iters, int n_cu, float* sink, hipStream_t stream);
-int launch_bwd_lin_q(const Problem& p, const void* q, const void* dout, const bf16_t* HZ, const bf16_t* wt,
+int launch_bwd_lin_q(const Problem& p, const void* q, const void* dout, const bf16_t* HZ, const bf16_t* proj_w,
                      int phi_kind, float* dq_lin, bf16_t* dHZ, float* dW, float* db, float* partials, hipStream_t stream);
 void launch_zero_u32(uint32_t* p, size_t n, hipStream_t stream);
 void launch_unfragment_kv(const Problem& p, const int8_t* k8, const uint8_t* v8, int8_t* k_codes,

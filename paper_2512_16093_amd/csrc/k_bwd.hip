@@ -28,46 +28,6 @@ namespace sla {
 constexpr float QK_LOG2 = LOG2E / 11.313708498984761f;   // log2(e) / sqrt(d)
 constexpr float INV_SQRT_D = 1.0f / 11.313708498984761f;
 
-__device__ __forceinline__ v8bf as_v8bf(const uint4& x) { return __builtin_bit_cast(v8bf, x); }
-__device__ __forceinline__ v16f mfma_bf16(const uint4& a, const uint4& b, const v16f& c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_v8bf(a), as_v8bf(b), c, 0, 0, 0);
-}
-// Accumulator registers 8 s .. 8 s + 7 of a tile as a bf16 operand: contraction step s (16 rows) of
-// the product that contracts over the tile's rows.  Row of element kk for lane half hf:
-// 16 s + 8 (kk / 4) + 4 hf + kk % 4 -- the order t_op (below) reads a staged tile's rows in.
-__device__ __forceinline__ uint4 acc_operand(const v16f& a, int s) {
-  return uint4{pack_bf16x2(a[8 * s], a[8 * s + 1]), pack_bf16x2(a[8 * s + 2], a[8 * s + 3]),
-               pack_bf16x2(a[8 * s + 4], a[8 * s + 5]), pack_bf16x2(a[8 * s + 6], a[8 * s + 7])};
-}
-
-constexpr int TP = 304;             // bytes per staged row: 256 of data + 48 of skew (76 dwords: within a group of 16 lanes neither
-                                    // the 16-byte operand reads nor the transposing reads collide)
-constexpr int TILE_B = 32 * TP;     // one 32-token tile
-
-typedef short v4s __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ v4s read_tr(const unsigned char* p) {
-  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)p);
-}
-// Operand for a contraction over the channels: token (row) l32 of the tile, channels 16 ks + 8 hf + 0..7.
-__device__ __forceinline__ uint4 n_op(const unsigned char* tile, int l32, int hf, int ks) {
-  return *(const uint4*)(tile + l32 * TP + ks * 32 + hf * 16);
-}
-// This lane's address inside a 4-row x 16-column patch for the transposing read: in every group of
-// 16 lanes, lane i receives element i of rows 0..3 of the patch that the group's lanes address
-// (lane s: row s / 4, columns 4 (s % 4) .. + 3).  Lane group g = lane / 16 serves channels
-// 16 (g % 2) .. + 15 of a 32-channel tile and the token rows of lane half g / 2.
-__device__ __forceinline__ int tr_lane_offset(int lane) {
-  return (4 * (lane >> 5) + ((lane & 15) >> 2)) * TP + (16 * ((lane >> 4) & 1) + 4 * (lane & 3)) * 2;
-}
-// Operand for a contraction over the tile's tokens, step s (16 tokens), channel tile ct: channel
-// 32 ct + l32, tokens 16 s + 8 (kk / 4) + 4 hf + kk % 4 for kk = 0..7 -- the order in which
-// acc_operand hands over the rows of an accumulator tile.
-__device__ __forceinline__ uint4 t_op(const unsigned char* tile, int tr_off, int ct, int s) {
-  union { v4s h[2]; uint4 v; } u;
-  u.h[0] = read_tr(tile + tr_off + (16 * s) * TP + ct * 64);
-  u.h[1] = read_tr(tile + tr_off + (16 * s + 8) * TP + ct * 64);
-  return u.v;
-}
 // The same operand as n_op straight from memory (a workgroup's own rows, read once).
 // (x: the (b,h) slice's first token; sn: elements from one token to the next)
 __device__ __forceinline__ void own_rows(const bf16_t* x, long long sn, long long row, int N, int hf, uint4 (&f)[8]) {

@@ -13,18 +13,13 @@
 //
 // As in the sparse-branch kernels a wavefront owns 32 tokens, one per lane pair, and every product
 // is formed with the tokens as accumulator columns, so per-token reductions stay in a lane pair.
+#include <algorithm>
+
 #include "common.h"
 
 namespace sla {
 
 namespace {
-
-constexpr int LP = 136;  // row pitch (elements) of the bf16 LDS matrices: 272 bytes, 16-byte aligned, bank-skewed
-
-__device__ __forceinline__ v16f mfma_bf16(const uint4& a, const uint4& b, const v16f& c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
-}
-__device__ __forceinline__ uint4 lds_frag(const bf16_t* m, int row, int k0) { return *(const uint4*)(m + row * LP + k0); }
 
 // Where entry [o][c .. c+3] (c a multiple of 4) of a 128 x 128 summary sits in the storage order of
 // hz / HZ (hz_frag_chunk): element offset of the 4-element run.
@@ -60,74 +55,156 @@ __device__ __forceinline__ uint4 pack8(const float* x) {
 
 }  // namespace
 
-// wt[c][r] = W[r][c] (identity when there is no projection): the A operand of dO^l = dO W.
-__global__ void __launch_bounds__(256) bwd_wt_kernel(const bf16_t* __restrict__ w, bf16_t* __restrict__ wt) {
-  for (int x = blockIdx.x * 256 + threadIdx.x; x < D * D; x += gridDim.x * 256) {
-    const int c = x >> 7, r = x & 127;
-    wt[x] = w ? w[r * D + c] : (bf16_t)(r == c ? 0x3F80 : 0);
+// Workgroup barrier that publishes LDS writes and retires LDS reads but leaves global loads and stores in flight
+// (__syncthreads() drains them: five times per query block it then waited for stores nobody in the workgroup reads).
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// A token's 16 channels of step ks, lane half hf holding 16 ks + 8 hf + 0..7, regrouped over the lane pair: lane half
+// hf gets channels 16 ks + 4 hf + 0..3 (x, y) and 16 ks + 8 + 4 hf + 0..3 (z, w) -- the row order of the accumulators
+// and of the transposing reads.
+__device__ __forceinline__ uint4 pair_order(const uint4& v) {
+  const auto a = __builtin_amdgcn_permlane32_swap(v.x, v.z, false, false);
+  const auto b = __builtin_amdgcn_permlane32_swap(v.y, v.w, false, false);
+  return uint4{(uint32_t)a[0], (uint32_t)b[0], (uint32_t)a[1], (uint32_t)b[1]};
+}
+
+// Column sums over the tokens of a staged [BQ][128] tile, weighted: thread (channel group t % 16, eight tokens from
+// 8 (t / 16)) adds its share to s[0..7]; tile_sums_finish adds the shares up (wavefront by wavefront into red).
+template <class F>
+__device__ __forceinline__ void tile_sums(const unsigned char* tile, int t, float (&s)[8], F weight) {
+  const int cg = t & 15, n0 = 8 * (t >> 4);
+#pragma unroll
+  for (int m = 0; m < 8; ++m) {
+    float x[8];
+    unpack8(*(const uint4*)(tile + (n0 + m) * TP + cg * 16), x);
+    const float wm = weight(n0 + m);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) s[e] = __builtin_fmaf(x[e], wm, s[e]);
+  }
+}
+__device__ __forceinline__ void tile_sums_finish(float (&s)[8], float* red, int lane, int w) {
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    s[e] += __shfl_xor(s[e], 16);
+    s[e] += __shfl_xor(s[e], 32);
+  }
+  if (lane < 16) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) red[w * 128 + 8 * lane + e] = s[e];
   }
 }
 
+// Per query block (BQ tokens): 33 KB of summaries, 2 x 32 KB of Q and dO in, 64 KB of dQ's share (fp32) and 33 KB of
+// dH out (BQ = 128) against 160 matrix products per wavefront: bound by memory if nothing else is waited for.  One
+// workgroup per compute unit walks over a contiguous run of (head, query block) items; the next item's summaries, Q
+// and dO are on their way into registers while the present one is computed, stores are never waited for, and every
+// operand that contracts over a tile's rows comes from the row-major tile by the transposing read.  (Before: loads,
+// stores and barriers of an item one after the other, transposed copies made by 2-byte writes:
+// 40 heads x 75600 tokens 2.82 -> 1.49 ms, 12 x 32760 385 -> 219 us, 4 x 2187 (blocks of 64) 41 -> 29 us.)
 template <int NW, int PHI>
 __global__ void __launch_bounds__(NW * 64, 1)
     bwd_lin_q_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ dout, const bf16_t* __restrict__ HZ,
-                     const bf16_t* __restrict__ wt, float* __restrict__ dq_lin, bf16_t* __restrict__ dHZ,
-                     float* __restrict__ dW_part, float* __restrict__ db_part, int N, int Tq, int H, Layout lq, Layout ld) {
-  constexpr int BQ = 32 * NW;
+                     const bf16_t* __restrict__ proj_w, float* __restrict__ dq_lin, bf16_t* __restrict__ dHZ,
+                     float* __restrict__ dW_part, float* __restrict__ db_part, int N, int Tq, int total, int H, Layout lq, Layout ld) {
+  constexpr int BQ = 32 * NW, NT = 64 * NW, PER = 2048 / NT;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  bf16_t* Wt = (bf16_t*)smem;              // [c'][r]
-  bf16_t* R1 = Wt + 128 * LP;              // Hn[o][c]            -> dnum[n][o]
-  bf16_t* R2 = R1 + 128 * LP;              // Ht[c][o]            -> aT[c][n]   -> gT[r][n]
-  bf16_t* R3 = R2 + 128 * LP;              // dnumT[o][n]         -> OlT[c][n]
-  float* zv = (float*)(R3 + 128 * LP);     // Z[c]
-  float* dden_s = zv + 128;                // dden[n]
-  const int bh = blockIdx.y, t = threadIdx.x, lane = t & 63, w = t >> 6, l32 = lane & 31, hf = lane >> 5;
-  const int nl = 32 * w + l32;             // this lane pair's token within the query block
+  unsigned char* const Wl = smem;              // W[r][c] (the identity when there is no projection)
+  unsigned char* const Hl = Wl + 128 * TP;     // H[o][c]            -> dO[n][r]
+  unsigned char* const Al = Hl + 128 * TP;     // a[n][c]            -> O^l[n][c]
+  unsigned char* const Dl = Al + BQ * TP;      // dnum[n][o]
+  float* const zv = (float*)(Dl + BQ * TP);    // Z[c]
+  float* const dden_s = zv + 128;              // dden[n]
+  float* const red = dden_s + 128;             // [NW][128]
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6, l32 = lane & 31, hf = lane >> 5;
+  const int nl = 32 * w + l32;                 // this lane pair's token within the query block
+  const int tr_off = tr_lane_offset(lane);
+  const int first = (int)((long long)total * blockIdx.x / gridDim.x), end = (int)((long long)total * (blockIdx.x + 1) / gridDim.x);
 
-  for (int x = t; x < 128 * 16; x += NW * 64) *(uint4*)(Wt + (x >> 4) * LP + (x & 15) * 8) = *(const uint4*)(wt + x * 8);
+  if (proj_w && ((uintptr_t)proj_w & 15) == 0) {
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int x = u * NT + t;
+      *(uint4*)(Wl + (x >> 4) * TP + (x & 15) * 16) = *(const uint4*)(proj_w + x * 8);
+    }
+  } else {
+    for (int x = t; x < D * D; x += NT)
+      *(bf16_t*)(Wl + (x >> 7) * TP + (x & 127) * 2) = proj_w ? proj_w[x] : (bf16_t)((x >> 7) == (x & 127) ? 0x3F80 : 0);
+  }
 
-  constexpr int RT = 4 / NW;               // row tiles of dW per wavefront
+  constexpr int RT = 4 / NW;                   // row tiles of dW per wavefront
   v16f dwacc[RT][4];
 #pragma unroll
   for (int a = 0; a < RT; ++a)
 #pragma unroll
     for (int ct = 0; ct < 4; ++ct) dwacc[a][ct] = v16f{};
-  float dbacc = 0.f;
-
-  for (int i = blockIdx.x; i < Tq; i += gridDim.x) {
-    // ---- stage H_i twice ([o][c] and [c][o]) and Z_i
-    const bf16_t* hz = HZ + ((size_t)bh * Tq + i) * HZ_ELEMS;
-    for (int x = t; x < 2048; x += NW * 64) {
-      const int ln = x & 63, ks = (x >> 6) & 7, ot = x >> 9;
-      const int o = 32 * ot + (ln & 31), c0 = 32 * (ks >> 1) + 16 * (ln >> 5) + 8 * (ks & 1);
-      const uint4 v = *(const uint4*)(hz + (size_t)x * 8);
-      *(uint4*)(R1 + o * LP + c0) = v;
-      const uint32_t wv[4] = {v.x, v.y, v.z, v.w};
+  // (names the sums' place: left alone the allocator moved them between ordinary registers and scratch memory, whose
+  // reloads waited for every load and store in flight)
+  auto hold_sums = [&]() __attribute__((always_inline)) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) R2[(c0 + e) * LP + o] = (bf16_t)(e & 1 ? wv[e >> 1] >> 16 : wv[e >> 1] & 0xffffu);
-    }
-    if (t < 128) zv[t] = bf16_to_f32(hz[128 * 128 + t]);
-    __syncthreads();
+    for (int a = 0; a < RT; ++a)
+#pragma unroll
+      for (int ct = 0; ct < 4; ++ct) asm volatile("" : "+a"(dwacc[a][ct]));
+  };
+  float dbacc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 
-    // ---- this wavefront's 32 tokens
-    const long long n = (long long)i * BQ + nl;
-    const bool ok = n < N;
-    const size_t row = ((size_t)bh * N + (ok ? n : 0)) * D;   // (in the library's own dq_lin)
-    const int b_ = bh / H, h_ = bh - b_ * H;
-    const bf16_t* qrow = q + b_ * lq.sb + h_ * lq.sh + (long long)(ok ? n : 0) * lq.sn;
-    const bf16_t* drow = dout + b_ * ld.sb + h_ * ld.sh + (long long)(ok ? n : 0) * ld.sn;
-    float av[64];                // a = phi(Q[n]) at channels 16 ks + 8 hf + kk  (index 8 ks + kk)
-    uint4 af[8], gf[8];
+  // The next item's summaries and rows (rows beyond N come as row N - 1 and are given no weight).  Two wavefronts
+  // would need 64 registers each for the summaries beside 128 of dW: they load them when they are due.
+  constexpr bool HZ_AHEAD = NW == 4;
+  uint4 hzp[PER], qp[8], gp[8];
+  bf16_t zp = 0;
+  auto fetch_hz = [&](int item) __attribute__((always_inline)) {
+    const bf16_t* hz = HZ + (size_t)item * HZ_ELEMS;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const uint4 got = *(const uint4*)(hz + (size_t)(u * NT + t) * 8);
+      hzp[u] = got;
+    }
+    zp = hz[D * D + (t & 127)];
+  };
+  auto fetch = [&](int item) __attribute__((always_inline)) {
+    const int bh = item / Tq, i = item - bh * Tq, b_ = bh / H, h_ = bh - b_ * H;
+    if constexpr (HZ_AHEAD) fetch_hz(item);
+    const long long n = min(i * BQ + nl, N - 1);
+    const bf16_t* qrow = q + b_ * lq.sb + h_ * lq.sh + n * lq.sn + 8 * hf;
+    const bf16_t* drow = dout + b_ * ld.sb + h_ * ld.sh + n * ld.sn + 8 * hf;
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) {
-      uint4 qv = uint4{0u, 0u, 0u, 0u};
-      gf[ks] = qv;
-      if (ok) {
-        qv = *(const uint4*)(qrow + 16 * ks + 8 * hf);
-        gf[ks] = *(const uint4*)(drow + 16 * ks + 8 * hf);
-      }
-      unpack8(qv, &av[8 * ks]);
+      const uint4 a = *(const uint4*)(qrow + 16 * ks), b = *(const uint4*)(drow + 16 * ks);
+      qp[ks] = a;
+      gp[ks] = b;
     }
+  };
+  if (first < end) fetch(first);
+
+  for (int item = first; item < end; ++item) {
+    // ---- publish H_i and Z_i
+    hold_sums();
+    if constexpr (!HZ_AHEAD) fetch_hz(item);
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int x = u * NT + t, ln = x & 63, ks = (x >> 6) & 7, ot = x >> 9;
+      *(uint4*)(Hl + (32 * ot + (ln & 31)) * TP + (32 * (ks >> 1) + 16 * (ln >> 5) + 8 * (ks & 1)) * 2) = hzp[u];
+    }
+    if (t < 128) zv[t] = bf16_to_f32(zp);
+    const int bh = item / Tq, i = item - bh * Tq;
+    const int n = i * BQ + nl;
+    const bool ok = n < N;
+    const uint32_t keep = ok ? ~0u : 0u;
+    uint4 af[8], gf[8], qs[8];
+    float av[64];                // a = phi(Q[n]) at channels 16 ks + 8 hf + kk  (index 8 ks + kk)
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+      unpack8(qp[ks], &av[8 * ks]);
+      qs[ks] = pair_order(qp[ks]);
+      gf[ks] = uint4{gp[ks].x & keep, gp[ks].y & keep, gp[ks].z & keep, gp[ks].w & keep};
+    }
+    lds_barrier();
+
     float qmax = 0.f, rsum = 1.0f;
     if constexpr (PHI == 0) softmax_stats(av, qmax, rsum);
     else {
@@ -144,6 +221,7 @@ __global__ void __launch_bounds__(NW * 64, 1)
         den += av[8 * ks + kk] * zv[16 * ks + 8 * hf + kk];
       }
       af[ks] = pack8(&av[8 * ks]);
+      *(uint4*)(Al + nl * TP + (16 * ks + 8 * hf) * 2) = af[ks];
     }
     den += partner_f32(den);
     const float rden = den > 0.f ? 1.0f / den : 0.f;
@@ -154,21 +232,27 @@ __global__ void __launch_bounds__(NW * 64, 1)
     // left alone the compiler issues each read right before its product and waits for it every time)
 #pragma unroll
     for (int ot = 0; ot < 4; ++ot) {
-      uint4 ah[8], aw[8];
+      uint4 ah[8];
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks) {
-        ah[ks] = lds_frag(R1, 32 * ot + l32, 16 * ks + 8 * hf);
-        aw[ks] = lds_frag(Wt, 32 * ot + l32, 16 * ks + 8 * hf);
-      }
+      for (int ks = 0; ks < 8; ++ks) ah[ks] = n_op(Hl + 32 * ot * TP, l32, hf, ks);
+      __builtin_amdgcn_sched_barrier(0);
       ol[ot] = v16f{};
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks) ol[ot] = mfma_bf16(ah[ks], af[ks], ol[ot]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) af[ks] = pair_order(gf[ks]);   // (a is not needed in registers any more)
+#pragma unroll
+    for (int ot = 0; ot < 4; ++ot) {
+      uint4 aw[8];
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks) aw[ks] = t_op(Wl + 32 * (ks >> 1) * TP, tr_off, ot, ks & 1);
+      __builtin_amdgcn_sched_barrier(0);
       gl[ot] = v16f{};
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks) {
-        ol[ot] = mfma_bf16(ah[ks], af[ks], ol[ot]);
-        gl[ot] = mfma_bf16(aw[ks], gf[ks], gl[ot]);
-      }
-      __builtin_amdgcn_sched_group_barrier(0x100, 16, 0);
-      __builtin_amdgcn_sched_group_barrier(0x008, 16, 0);
+      for (int ks = 0; ks < 8; ++ks) gl[ot] = mfma_bf16(aw[ks], af[ks], gl[ot]);
+      __builtin_amdgcn_sched_barrier(0);
     }
     float dden = 0.f;
 #pragma unroll
@@ -181,187 +265,148 @@ __global__ void __launch_bounds__(NW * 64, 1)
       }
     dden += partner_f32(dden);
     dden *= -rden;
-    uint2 olp[4][4];             // O^l rounded to bf16 (all that is used of it from here on: the dW product)
+    uint4 olp[4][2], dn[4][2];   // O^l (all that is used of it from here on: the dW product) and dnum, rounded to bf16
 #pragma unroll
     for (int ot = 0; ot < 4; ++ot)
 #pragma unroll
-      for (int g = 0; g < 4; ++g)
-        olp[ot][g] = uint2{pack_bf16x2(ol[ot][4 * g], ol[ot][4 * g + 1]), pack_bf16x2(ol[ot][4 * g + 2], ol[ot][4 * g + 3])};
-    __syncthreads();             // every wavefront is done with Hn
+      for (int s = 0; s < 2; ++s) {
+        olp[ot][s] = acc_operand(ol[ot], s);
+        dn[ot][s] = acc_operand(gl[ot], s);
+        unsigned char* dst = Dl + nl * TP + (32 * ot + 16 * s + 4 * hf) * 2;
+        *(uint2*)dst = uint2{dn[ot][s].x, dn[ot][s].y};
+        *(uint2*)(dst + 16) = uint2{dn[ot][s].z, dn[ot][s].w};
+      }
+    if (hf == 0) dden_s[nl] = dden;
 
     // ---- d phi(Q) = dnum H^T + dden Z, then through the softmax
-#pragma unroll
-    for (int ot = 0; ot < 4; ++ot)
-#pragma unroll
-      for (int g = 0; g < 4; ++g)
-        *(uint2*)(R1 + nl * LP + 32 * ot + 8 * g + 4 * hf) =
-            uint2{pack_bf16x2(gl[ot][4 * g], gl[ot][4 * g + 1]), pack_bf16x2(gl[ot][4 * g + 2], gl[ot][4 * g + 3])};
-    // (own rows only: written and read back by this wavefront, in program order)
     v16f da[4];
-    uint4 bn[8];                 // this token's dnum row: the B operand of all four tiles
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) bn[ks] = lds_frag(R1, nl, 16 * ks + 8 * hf);
-    __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
 #pragma unroll
     for (int ct = 0; ct < 4; ++ct) {
       uint4 ah[8];
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks) ah[ks] = lds_frag(R2, 32 * ct + l32, 16 * ks + 8 * hf);
+      for (int ks = 0; ks < 8; ++ks) ah[ks] = t_op(Hl + 32 * (ks >> 1) * TP, tr_off, ct, ks & 1);
+      __builtin_amdgcn_sched_barrier(0);
       da[ct] = v16f{};
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks) da[ct] = mfma_bf16(ah[ks], bn[ks], da[ct]);
-      __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
-      __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
+      for (int ks = 0; ks < 8; ++ks) da[ct] = mfma_bf16(ah[ks], dn[ks >> 1][ks & 1], da[ct]);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    // a at the accumulator's channels 32 ct + 8 g + 4 hf + e: from Q again (its words are kept, a
-    // itself is formed twice rather than held in 64 registers)
-    uint2 qw[4][4];
+    // a at the accumulator's channels 32 ct + 8 g + 4 hf + e, formed again from Q's words
     float sdot = 0.f;
 #pragma unroll
     for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
-        const int c0 = 32 * ct + 8 * g + 4 * hf;
-        qw[ct][g] = ok ? *(const uint2*)(qrow + c0) : uint2{0u, 0u};
-        const float xq[4] = {bf16_lo(qw[ct][g].x), bf16_hi(qw[ct][g].x), bf16_lo(qw[ct][g].y), bf16_hi(qw[ct][g].y)};
+        const uint4& qq = qs[2 * ct + (g >> 1)];
+        const uint32_t q0 = g & 1 ? qq.z : qq.x, q1 = g & 1 ? qq.w : qq.y;
+        const float xq[4] = {bf16_lo(q0), bf16_hi(q0), bf16_lo(q1), bf16_hi(q1)};
+        const float4 z4 = *(const float4*)(zv + 32 * ct + 8 * g + 4 * hf);
+        const float zz[4] = {z4.x, z4.y, z4.z, z4.w};
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          da[ct][4 * g + e] += zv[c0 + e] * dden;
+          da[ct][4 * g + e] += zz[e] * dden;
           if constexpr (PHI == 0) sdot += phi_value<0>(xq[e], qmax, rsum) * da[ct][4 * g + e];
         }
       }
     sdot += partner_f32(sdot);
+    lds_barrier();               // every wavefront is done with H_i and Z_i; a and dnum are complete
+    asm volatile("" : "+v"(qmax));  // (a is formed once more below, not kept in 64 registers)
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) *(uint4*)(Hl + nl * TP + (16 * ks + 8 * hf) * 2) = gf[ks];
     if (ok) {
+      float* drow = dq_lin + ((size_t)bh * N + n) * D;   // (the library's own tensor)
 #pragma unroll
       for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-          const float xq[4] = {bf16_lo(qw[ct][g].x), bf16_hi(qw[ct][g].x), bf16_lo(qw[ct][g].y), bf16_hi(qw[ct][g].y)};
+          const uint4& qq = qs[2 * ct + (g >> 1)];
+          const uint32_t q0 = g & 1 ? qq.z : qq.x, q1 = g & 1 ? qq.w : qq.y;
+          const float xq[4] = {bf16_lo(q0), bf16_hi(q0), bf16_lo(q1), bf16_hi(q1)};
           float o[4];
 #pragma unroll
           for (int e = 0; e < 4; ++e)
             o[e] = phi_backward<PHI>(xq[e], phi_value<PHI>(xq[e], qmax, rsum), da[ct][4 * g + e], sdot);
-          *(float4*)(dq_lin + row + 32 * ct + 8 * g + 4 * hf) = float4{o[0], o[1], o[2], o[3]};
+          *(float4*)(drow + 32 * ct + 8 * g + 4 * hf) = float4{o[0], o[1], o[2], o[3]};
         }
     }
-    __syncthreads();             // every wavefront is done with Ht (and with its dnum rows)
 
-    // ---- dH_i^T[o][c] = sum_n dnum[n][o] a[n][c], dZ_i[c] = sum_n a[n][c] dden[n]: transposed copies with the tokens contiguous
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-      const uint32_t aw[4] = {af[ks].x, af[ks].y, af[ks].z, af[ks].w};
-#pragma unroll
-      for (int kk = 0; kk < 8; ++kk)
-        R2[(16 * ks + 8 * hf + kk) * LP + nl] = (bf16_t)(kk & 1 ? aw[kk >> 1] >> 16 : aw[kk >> 1] & 0xffffu);
-    }
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {  // dnum: this token's row of R1 again (written above), not 64 registers held since
-      const uint4 dv = lds_frag(R1, nl, 16 * ks + 8 * hf);
-      const uint32_t dw[4] = {dv.x, dv.y, dv.z, dv.w};
-#pragma unroll
-      for (int kk = 0; kk < 8; ++kk)
-        R3[(16 * ks + 8 * hf + kk) * LP + nl] = (bf16_t)(kk & 1 ? dw[kk >> 1] >> 16 : dw[kk >> 1] & 0xffffu);
-    }
-    if (hf == 0) dden_s[nl] = dden;
-    __syncthreads();
-    bf16_t* dst = dHZ + ((size_t)bh * Tq + i) * HZ_ELEMS;
+    // ---- dH_i^T[o][c] = sum_n dnum[n][o] a[n][c], dZ_i[c] = sum_n a[n][c] dden[n]
+    hold_sums();
+    // the next item: requested here, where the registers have room for it, used after the sections below
+    __builtin_amdgcn_sched_barrier(0);
+    fetch(min(item + 1, end - 1));
+    __builtin_amdgcn_sched_barrier(0);
+    bf16_t* dst = dHZ + (size_t)item * HZ_ELEMS;
     // (the store offsets below are formed from a value the compiler cannot see through: as loop
     // invariants they were kept in scratch memory, and each reload made its store wait for the one before)
     int lane_o = l32;
     asm volatile("" : "+v"(lane_o));
     for (int ct = w; ct < 4; ct += NW) {
-      v16f acc[4];
+      uint4 aa[BQ / 16];
+#pragma unroll
+      for (int ks = 0; ks < BQ / 16; ++ks) aa[ks] = t_op(Al + 32 * (ks >> 1) * TP, tr_off, ct, ks & 1);
 #pragma unroll
       for (int ot = 0; ot < 4; ++ot) {
-        acc[ot] = v16f{};
-        uint4 aa[BQ / 16], bb[BQ / 16];
+        v16f acc = v16f{};
+        uint4 bb[BQ / 16];
 #pragma unroll
-        for (int ks = 0; ks < BQ / 16; ++ks) {
-          aa[ks] = lds_frag(R2, 32 * ct + l32, 16 * ks + 8 * hf);
-          bb[ks] = lds_frag(R3, 32 * ot + l32, 16 * ks + 8 * hf);
-        }
+        for (int ks = 0; ks < BQ / 16; ++ks) bb[ks] = t_op(Dl + 32 * (ks >> 1) * TP, tr_off, ot, ks & 1);
 #pragma unroll
-        for (int ks = 0; ks < BQ / 16; ++ks) acc[ot] = mfma_bf16(aa[ks], bb[ks], acc[ot]);
-        __builtin_amdgcn_sched_group_barrier(0x100, BQ / 8, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, BQ / 16, 0);
+        for (int ks = 0; ks < BQ / 16; ++ks) acc = mfma_bf16(aa[ks], bb[ks], acc);
+        __builtin_amdgcn_sched_barrier(0);
         // lane: o = 32 ot + l32; registers: c = 32 ct + 8 g + 4 hf + e
 #pragma unroll
         for (int g = 0; g < 4; ++g)
           *(uint2*)(dst + hz_run_offset(32 * ot + lane_o, 32 * ct + 8 * g + 4 * hf)) =
-              uint2{pack_bf16x2(acc[ot][4 * g], acc[ot][4 * g + 1]), pack_bf16x2(acc[ot][4 * g + 2], acc[ot][4 * g + 3])};
+              uint2{pack_bf16x2(acc[4 * g], acc[4 * g + 1]), pack_bf16x2(acc[4 * g + 2], acc[4 * g + 3])};
       }
     }
-    if (t < 128) {  // dZ_i[c = t] = sum_n a[n][c] dden[n], eight tokens per read
-      float s = 0.f;
+    __builtin_amdgcn_sched_barrier(0);
+    float dz[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    tile_sums(Al, t, dz, [&](int m) { return dden_s[m]; });
+    tile_sums_finish(dz, red, lane, w);
+    lds_barrier();               // a and dnum are consumed
+    if (t < 128) {
+      float s = red[t];
 #pragma unroll
-      for (int m = 0; m < BQ; m += 8) {
-        float a8[8];
-        unpack8(*(const uint4*)(R2 + t * LP + m), a8);
-        const float4 d0 = *(const float4*)(dden_s + m), d1 = *(const float4*)(dden_s + m + 4);
-        s += a8[0] * d0.x + a8[1] * d0.y + a8[2] * d0.z + a8[3] * d0.w + a8[4] * d1.x + a8[5] * d1.y + a8[6] * d1.z + a8[7] * d1.w;
-      }
-      dst[128 * 128 + t] = f32_to_bf16(s);
+      for (int u = 1; u < NW; ++u) s += red[u * 128 + t];
+      dst[D * D + t] = f32_to_bf16(s);
     }
-    __syncthreads();             // aT and dnumT are consumed
 
     // ---- dW[r][c] += sum_n dO[n][r] O^l[n][c],  db[r] += sum_n dO[n][r]
-    if (dW_part || db_part) {
-#pragma unroll
-      for (int ks = 0; ks < 8; ++ks) {
-        const uint32_t gw[4] = {gf[ks].x, gf[ks].y, gf[ks].z, gf[ks].w};
-#pragma unroll
-        for (int kk = 0; kk < 8; ++kk)
-          R2[(16 * ks + 8 * hf + kk) * LP + nl] = (bf16_t)(kk & 1 ? gw[kk >> 1] >> 16 : gw[kk >> 1] & 0xffffu);
-      }
+    if (dW_part) {
 #pragma unroll
       for (int ot = 0; ot < 4; ++ot)
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int c0 = 32 * ot + 8 * g + 4 * hf;
-          R3[(c0 + 0) * LP + nl] = (bf16_t)(olp[ot][g].x & 0xffffu);
-          R3[(c0 + 1) * LP + nl] = (bf16_t)(olp[ot][g].x >> 16);
-          R3[(c0 + 2) * LP + nl] = (bf16_t)(olp[ot][g].y & 0xffffu);
-          R3[(c0 + 3) * LP + nl] = (bf16_t)(olp[ot][g].y >> 16);
+        for (int s = 0; s < 2; ++s) {
+          unsigned char* dst_o = Al + nl * TP + (32 * ot + 16 * s + 4 * hf) * 2;
+          *(uint2*)dst_o = uint2{olp[ot][s].x, olp[ot][s].y};
+          *(uint2*)(dst_o + 16) = uint2{olp[ot][s].z, olp[ot][s].w};
         }
-      __syncthreads();
-      if (dW_part) {             // (only the bias gradient wanted: no products)
+      lds_barrier();
 #pragma unroll
       for (int a = 0; a < RT; ++a) {
-        const int rt = w + a * NW;
         uint4 ag[BQ / 16];       // this row tile of dO^T: the A operand of all four column tiles
 #pragma unroll
-        for (int ks = 0; ks < BQ / 16; ++ks) ag[ks] = lds_frag(R2, 32 * rt + l32, 16 * ks + 8 * hf);
-        __builtin_amdgcn_sched_group_barrier(0x100, BQ / 16, 0);
+        for (int ks = 0; ks < BQ / 16; ++ks) ag[ks] = t_op(Hl + 32 * (ks >> 1) * TP, tr_off, w + a * NW, ks & 1);
 #pragma unroll
         for (int ct = 0; ct < 4; ++ct) {
           uint4 bo[BQ / 16];
 #pragma unroll
-          for (int ks = 0; ks < BQ / 16; ++ks) bo[ks] = lds_frag(R3, 32 * ct + l32, 16 * ks + 8 * hf);
+          for (int ks = 0; ks < BQ / 16; ++ks) bo[ks] = t_op(Al + 32 * (ks >> 1) * TP, tr_off, ct, ks & 1);
 #pragma unroll
           for (int ks = 0; ks < BQ / 16; ++ks) dwacc[a][ct] = mfma_bf16(ag[ks], bo[ks], dwacc[a][ct]);
-          __builtin_amdgcn_sched_group_barrier(0x100, BQ / 16, 0);
-          __builtin_amdgcn_sched_group_barrier(0x008, BQ / 16, 0);
+          __builtin_amdgcn_sched_barrier(0);
         }
       }
-      }
-      if (t < 128) {  // db[r = t] += sum_n dO[n][r]
-        float s = 0.f;
-#pragma unroll
-        for (int m = 0; m < BQ; m += 8) {
-          float g8[8];
-          unpack8(*(const uint4*)(R2 + t * LP + m), g8);
-          s += ((g8[0] + g8[1]) + (g8[2] + g8[3])) + ((g8[4] + g8[5]) + (g8[6] + g8[7]));
-        }
-        dbacc += s;
-      }
-      __syncthreads();
     }
+    if (db_part) tile_sums(Hl, t, dbacc, [](int) { return 1.0f; });
+    lds_barrier();               // every tile is consumed
   }
   // This workgroup's share of dW and db goes to its own slice; bwd_reduce_partials_kernel adds the
   // slices in a fixed order, so the sums do not depend on which workgroup finishes first.
-  const size_t wg = (size_t)blockIdx.y * gridDim.x + blockIdx.x;
   if (dW_part) {
-    float* mine = dW_part + wg * (D * D);
+    float* mine = dW_part + (size_t)blockIdx.x * (D * D);
 #pragma unroll
     for (int a = 0; a < RT; ++a)
 #pragma unroll
@@ -370,82 +415,80 @@ __global__ void __launch_bounds__(NW * 64, 1)
         for (int r = 0; r < 16; ++r)
           mine[(32 * (w + a * NW) + 8 * (r >> 2) + 4 * hf + (r & 3)) * D + 32 * ct + l32] = dwacc[a][ct][r];
   }
-  if (db_part && t < 128) db_part[wg * D + t] = dbacc;
+  if (db_part) {
+    tile_sums_finish(dbacc, red, lane, w);
+    lds_barrier();
+    if (t < 128) {
+      float s = red[t];
+#pragma unroll
+      for (int u = 1; u < NW; ++u) s += red[u * 128 + t];
+      db_part[(size_t)blockIdx.x * D + t] = s;
+    }
+  }
 }
 
-// out[x] = sum over p of part[p][x], p ascending: one thread per entry, a fixed order of additions.
-__global__ void __launch_bounds__(256) bwd_reduce_partials_kernel(const float* __restrict__ part, int n_part, int n,
-                                                                  float* __restrict__ out) {
-  const int x = blockIdx.x * 256 + threadIdx.x;
-  if (x >= n) return;
-  float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;   // four chains for latency; the order is still fixed
-  int p = 0;
-  for (; p + 4 <= n_part; p += 4) {
-    s0 += part[(size_t)p * n + x];
-    s1 += part[(size_t)(p + 1) * n + x];
-    s2 += part[(size_t)(p + 2) * n + x];
-    s3 += part[(size_t)(p + 3) * n + x];
+// dW[x] and db[x] = sum over p of part[p][x] in a fixed order.  Workgroups 0 .. 255 take 64 entries of dW each (dw
+// given), the last two 64 of db: 16 threads of four adjacent entries, 16 threads along p (every 16th partial, four
+// loads in flight), added up in LDS.  Bound by reading the partials; with one thread per entry a chain of additions
+// as long as the list bound it (768 partials of 64 KiB, dW and db: 141 us in two launches, now 256 partials and 5 us).
+constexpr int RED_ENTRIES = 64;
+__global__ void __launch_bounds__(256) bwd_reduce_partials_kernel(const float* __restrict__ dw_part, const float* __restrict__ db_part,
+                                                                  int n_part, float* __restrict__ dw, float* __restrict__ db) {
+  __shared__ float4 red[16][16];
+  const int dw_blocks = dw ? D * D / RED_ENTRIES : 0, blk = blockIdx.x, t = threadIdx.x, col = t & 15, row = t >> 4;
+  const bool is_db = blk >= dw_blocks;
+  const int n = is_db ? D : D * D, x = (is_db ? blk - dw_blocks : blk) * RED_ENTRIES + 4 * col;
+  const float* part = (is_db ? db_part : dw_part) + x;
+  float4 s = float4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+  for (int p = row; p < n_part; p += 16) {
+    const float4 v = *(const float4*)(part + (size_t)p * n);
+    s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
   }
-  for (; p < n_part; ++p) s0 += part[(size_t)p * n + x];
-  out[x] = (s0 + s1) + (s2 + s3);
+  red[row][col] = s;
+  __syncthreads();
+  if (t < 16) {
+#pragma unroll
+    for (int r = 1; r < 16; ++r) {
+      const float4 v = red[r][t];
+      s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+    }
+    *(float4*)((is_db ? db : dw) + x) = s;
+  }
 }
 
 // ---------------------------------------------------------------------------------------------
-void launch_bwd_wt(const bf16_t* proj_w, bf16_t* wt, hipStream_t stream) {
-  bwd_wt_kernel<<<64, 256, 0, stream>>>(proj_w, wt);
-}
-
-size_t bwd_lin_q_lds_bytes() { return (size_t)4 * 128 * LP * 2 + 128 * 4 + 128 * 4; }
-
-// Workgroups per head of bwd_lin_q_kernel are at most this many (the partial sums' buffer is sized by it).
-constexpr int LIN_Q_MAX_CHUNKS = 64;
-size_t bwd_lin_q_partial_bytes(const Problem& p) { return (size_t)LIN_Q_MAX_CHUNKS * p.BH * (D * D + D) * 4; }
+// One workgroup per compute unit at most: the partial sums' buffer is sized by it.
+constexpr int LIN_Q_WORKGROUPS = 256;
+static int lin_q_grid(const Problem& p) { return (int)std::min<long long>(LIN_Q_WORKGROUPS, (long long)p.BH * p.Tq); }
+size_t bwd_lin_q_partial_bytes(const Problem& p) { return (size_t)lin_q_grid(p) * (D * D + D) * 4; }
 
 template <int PHI>
-static int launch_bwd_lin_q_phi(const Problem& p, const void* q, const void* dout, const bf16_t* HZ, const bf16_t* wt,
+static int launch_bwd_lin_q_phi(const Problem& p, const void* q, const void* dout, const bf16_t* HZ, const bf16_t* proj_w,
                                 float* dq_lin, bf16_t* dHZ, float* dW, float* db, float* partials, hipStream_t stream) {
-  // workgroups per head: enough of them to fill the compute units a whole number of times where
-  // that is possible (one workgroup per unit), few enough that the per-workgroup partial sums of dW, db stay small
-  static int n_cu = 0;
-  if (n_cu == 0) {
-    int dev = 0, v = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0) v = 256;
-    n_cu = v;
-  }
-  int chunks = 16;
-  for (int c = 16; c <= LIN_Q_MAX_CHUNKS; ++c)
-    if ((long long)c * p.BH % n_cu == 0) {
-      chunks = c;
-      break;
-    }
-  if (chunks > p.Tq) chunks = p.Tq;
-  const dim3 grid((unsigned)chunks, (unsigned)p.BH);
-  const size_t lds = bwd_lin_q_lds_bytes();
-  static bool attr_set = false;
-  if (!attr_set) {
-    if (hipFuncSetAttribute((const void*)bwd_lin_q_kernel<4, PHI>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
-        hipFuncSetAttribute((const void*)bwd_lin_q_kernel<2, PHI>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-      return -1;
-    attr_set = true;
-  }
+  constexpr int LDS4 = 4 * 128 * TP + (2 + 4) * 128 * 4, LDS2 = (2 * 128 + 2 * 64) * TP + (2 + 2) * 128 * 4;
+  static const bool ok =
+      hipFuncSetAttribute((const void*)bwd_lin_q_kernel<4, PHI>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS4) == hipSuccess &&
+      hipFuncSetAttribute((const void*)bwd_lin_q_kernel<2, PHI>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS2) == hipSuccess;
+  if (!ok) return -1;
   // per-workgroup partial sums: dW slices first, then db slices
-  const int n_part = chunks * p.BH;
+  const int n_part = lin_q_grid(p);
   float* dW_part = dW ? partials : nullptr;
-  float* db_part = db ? partials + (size_t)LIN_Q_MAX_CHUNKS * p.BH * D * D : nullptr;
-  if (p.block_q == 128)
-    bwd_lin_q_kernel<4, PHI><<<grid, 256, lds, stream>>>((const bf16_t*)q, (const bf16_t*)dout, HZ, wt, dq_lin, dHZ, dW_part, db_part, p.N, p.Tq, p.H, p.lq, p.ld);
-  else
-    bwd_lin_q_kernel<2, PHI><<<grid, 128, lds, stream>>>((const bf16_t*)q, (const bf16_t*)dout, HZ, wt, dq_lin, dHZ, dW_part, db_part, p.N, p.Tq, p.H, p.lq, p.ld);
-  if (dW) bwd_reduce_partials_kernel<<<(D * D + 255) / 256, 256, 0, stream>>>(dW_part, n_part, D * D, dW);
-  if (db) bwd_reduce_partials_kernel<<<1, 256, 0, stream>>>(db_part, n_part, D, db);
+  float* db_part = db ? partials + (size_t)n_part * D * D : nullptr;
+#define SLA_LIN_Q(NW, LDS) bwd_lin_q_kernel<NW, PHI><<<(unsigned)n_part, NW * 64, LDS, stream>>>( \
+      (const bf16_t*)q, (const bf16_t*)dout, HZ, proj_w, dq_lin, dHZ, dW_part, db_part, p.N, p.Tq, p.BH * p.Tq, p.H, p.lq, p.ld)
+  if (p.block_q == 128) SLA_LIN_Q(4, LDS4); else SLA_LIN_Q(2, LDS2);
+#undef SLA_LIN_Q
+  const int blocks = (dW ? D * D / RED_ENTRIES : 0) + (db ? D / RED_ENTRIES : 0);
+  if (blocks > 0) bwd_reduce_partials_kernel<<<(unsigned)blocks, 256, 0, stream>>>(dW_part, db_part, n_part, dW, db);
   return 0;
 }
 
-int launch_bwd_lin_q(const Problem& p, const void* q, const void* dout, const bf16_t* HZ, const bf16_t* wt,
+int launch_bwd_lin_q(const Problem& p, const void* q, const void* dout, const bf16_t* HZ, const bf16_t* proj_w,
                      int phi_kind, float* dq_lin, bf16_t* dHZ, float* dW, float* db, float* partials, hipStream_t stream) {
-  if (phi_kind == 0) return launch_bwd_lin_q_phi<0>(p, q, dout, HZ, wt, dq_lin, dHZ, dW, db, partials, stream);
-  if (phi_kind == 1) return launch_bwd_lin_q_phi<1>(p, q, dout, HZ, wt, dq_lin, dHZ, dW, db, partials, stream);
-  return launch_bwd_lin_q_phi<2>(p, q, dout, HZ, wt, dq_lin, dHZ, dW, db, partials, stream);
+  if (phi_kind == 0) return launch_bwd_lin_q_phi<0>(p, q, dout, HZ, proj_w, dq_lin, dHZ, dW, db, partials, stream);
+  if (phi_kind == 1) return launch_bwd_lin_q_phi<1>(p, q, dout, HZ, proj_w, dq_lin, dHZ, dW, db, partials, stream);
+  return launch_bwd_lin_q_phi<2>(p, q, dout, HZ, proj_w, dq_lin, dHZ, dW, db, partials, stream);
 }
 
 }  // namespace sla
