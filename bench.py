@@ -533,7 +533,7 @@ def main():
                    "n_crit": n_c, "n_marg": n_m, "Tq": Tq, "Tk": Tk},
         "stage_ms": dict(zip(sla.STAGE_NAMES, [round(x, 4) for x in stage_ms])),
         "stage_hbm": stage_hbm,
-        "roofline": {"kernel": "sparse_fwd_kernel" if low_bit else "bwd_stats_kernel<NW, true> (bf16 forward)",
+        "roofline": {"kernel": "sparse_fwd_kernel" if low_bit else "fwd_bf16_kernel",
                      "bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak,
                      "traffic": traffic if low_bit else None, "traffic_unit": "bytes per launch",
                      "traffic_source": traffic_src if low_bit else None,

@@ -246,3 +246,21 @@ def test_saved_state_of_another_problem_poisons_the_gradients():
     junk = torch.zeros_like(saved)
     assert torch.isnan(sla.sla_attention_bwd(qd, kd, vd, dd, 128, 64, 0.25, 0.5, proj_w=Wd, saved=junk)[0].float()).any()
 
+
+
+@pytest.mark.parametrize("bq", [128, 64])
+def test_backward_of_many_heads(bq):
+    """Enough query blocks for two tiles of 32 queries per wavefront in the statistics pass (fewer take one), on a
+    ragged sequence (N = 1000: 15 key blocks and 40 keys, a query tile that ends inside it): first and last head
+    against the oracle."""
+    H = 64
+    cfg = synth.custom_config(1, H, (5, 10, 20), block_q=bq, topk_ratio=0.25, marginal_ratio=0.5, use_proj=False, cfg_id=310)
+    q, k, v = synth.make_qkv(cfg)
+    dout = synth.make_qkv(cfg, seed=7)[2]
+    qd, kd, vd, dd = (t.cuda() for t in (q, k, v, dout))
+    mask = sla.sla_classify_blocks(qd, kd, bq, 64, 0.25, 0.5, want_scores=False)[0].cpu().numpy()
+    dq, dk, dv, _, _ = sla.sla_attention_bwd(qd, kd, vd, dd, bq, 64, 0.25, 0.5, want_dw=False, want_db=False)
+    for h in (0, H - 1):
+        r = bo.sla_backward_head(*(synth.as_f64(t[0, h]) for t in (q, k, v, dout)), mask[0, h], bq, 64)
+        for name, got in (("dQ", dq), ("dK", dk), ("dV", dv)):
+            _compare("%s head %d" % (name, h), got[0, h].float().cpu().numpy(), r[name])
