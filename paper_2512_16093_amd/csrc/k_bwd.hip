@@ -124,11 +124,12 @@ __device__ __forceinline__ v16f score_tile(const unsigned char* ktile, const uin
 // ---- asynchronous copies of 32-row tiles (32 x 256 bytes) global -> LDS, without registers in between
 //
 // A tile is eight pieces of 1 KiB (four rows); a wavefront's copy instruction writes one piece, lane l its bytes
-// [16 l, 16 l + 16).  A row's sixteen 16-byte chunks are stored permuted, chunk c of row r at position c ^ (r % 16):
-// the copy cannot pad rows, and with the permutation the 16 lanes of a group that read the same chunk of 16
-// consecutive rows hit all banks once (n_op_swz).  The compiler does not know these copies are in flight (it would wait
-// for all of them before every LDS read): the callers wait by count.
+// [16 l, 16 l + 16).  The copy cannot pad rows, so a row's sixteen 16-byte chunks are stored permuted, chunk c of row r
+// at position c ^ swz(r): the 16 lanes of a group that read the same chunk of 16 consecutive rows hit all banks once
+// (n_op_swz), and so do the 32 lanes that read a 4-row x 64-byte patch (t_op_swz).  The compiler does not know these
+// copies are in flight (it would wait for all of them before every LDS read): the callers wait by count.
 constexpr int SWZ_TILE_B = 32 * 256;
+__device__ __forceinline__ int swz(int r) { return ((r & 3) << 2) | ((r >> 2) & 3); }
 __device__ __forceinline__ void copy_piece(const char* base, unsigned off, unsigned lds_addr) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %0" : : "s"(base), "v"(off), "s"(lds_addr) : "memory", "m0");
 }
@@ -151,7 +152,7 @@ struct TileCopy {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int r = 4 * i + (lane >> 4);
-      off[i] = (unsigned)((4 * PPW * w + r) * snb) + (((lane & 15) ^ ((4 * PPW * w + r) & 15)) << 4);
+      off[i] = (unsigned)((4 * PPW * w + r) * snb) + (((lane & 15) ^ swz(4 * PPW * w + r)) << 4);
     }
   }
   // rows row0 .. row0 + 31; rows beyond N come as row N - 1 (their weight is zero)
@@ -167,15 +168,30 @@ struct TileCopy {
 #pragma unroll 1
       for (int i = 0; i < PPW; ++i) {
         const int r = 4 * (PPW * w + i) + (ln >> 4);
-        copy_piece(slice + min(row0 + r, N - 1) * snb + (((ln & 15) ^ (r & 15)) << 4), dst + i * 1024);
+        copy_piece(slice + min(row0 + r, N - 1) * snb + (((ln & 15) ^ swz(r)) << 4), dst + i * 1024);
       }
     }
   }
 };
 // n_op on such a tile: swz_lane_offset once per lane, the step's bits flipped in.
-__device__ __forceinline__ int swz_lane_offset(int l32, int hf) { return l32 * 256 + ((hf ^ (l32 & 15)) << 4); }
+__device__ __forceinline__ int swz_lane_offset(int l32, int hf) { return l32 * 256 + ((hf ^ swz(l32)) << 4); }
 __device__ __forceinline__ uint4 n_op_swz(const unsigned char* tile, int lane_off, int ks) {
   return *(const uint4*)(tile + (lane_off ^ (ks << 5)));
+}
+// t_op on such a tile (the same lane, row and channel assignment).
+__device__ __forceinline__ int swz_tr_lane_offset(int lane) {
+  const int hf = lane >> 5, row = 4 * hf + ((lane & 15) >> 2), chunk = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
+  return row * 256 + ((chunk ^ swz(row)) << 4) + 8 * (lane & 1);
+}
+__device__ __forceinline__ uint4 t_op_swz(const unsigned char* tile, int tr_off, int ct, int s) {
+  union { v4s h[2]; uint4 v; } u;
+  u.h[0] = read_tr(tile + 16 * s * 256 + (tr_off ^ (ct << 6)));
+  u.h[1] = read_tr(tile + (16 * s + 8) * 256 + (tr_off ^ (ct << 6) ^ (2 << 4)));   // (eight rows on: swz flips bit 1)
+  return u.v;
+}
+// 64 consecutive floats global -> LDS, one per lane.
+__device__ __forceinline__ void copy_floats(const float* base, unsigned off, unsigned lds_addr) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %1, %0" : : "s"(base), "v"(off), "s"(lds_addr) : "memory", "m0");
 }
 // Waits for all but KEEP of this wavefront's copies and for its LDS reads, then meets the workgroup's other wavefronts.
 template <int KEEP>
@@ -794,7 +810,12 @@ __device__ __forceinline__ void linear_kv_share(const bf16_t* __restrict__ k, co
 // a wavefront whose block is not critical for the current query block sits the step out.
 // (KB = 2, 64 query rows per step.)  With KB = 1 a workgroup of two wavefronts serves one key block
 // over its own list, 64 query rows per step as well, and two workgroups share a compute unit: every
-// staged tile then serves one key block only, but no wavefront ever sits out.
+// staged tile then serves one key block only, but no wavefront ever sits out.  With KB = 1 rows are copied straight to
+// LDS (no registers, no padding: see TileCopy), the scores are formed in ordinary registers and dK, dV, K, V held in the
+// accumulation registers, so a step is its 64 products, 160 vector instructions and 112 LDS reads with no register
+// copies between the two files (there were 77 a step, and the copies through registers took 56 more).  40 heads x
+// 75600 tokens 29.9 -> 26.7 ms, 12 x 32760 token-major 2.17 -> 2.05 ms; 164 GB past L2 = 6.1 TB/s at 2.0 GHz, the matrix
+// pipe 43 % busy: bound by the lone wavefront's waits between the sections and by the stream.
 template <int KB, int TILES, int PHI, bool ST = false>
 __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ dout,
                                                       const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
@@ -805,7 +826,7 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
   constexpr int NT = 128 * KB, ROWS = 32 * TILES;  // threads; query rows per step
   // two buffers of: Q (TILES tiles) then dO (TILES tiles) of ROWS consecutive query rows; then their lse, delta
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  constexpr int BUF_B = 2 * TILES * TILE_B;
+  constexpr int BUF_B = KB == 1 ? 4 * SWZ_TILE_B : 2 * TILES * TILE_B;
   float (*stat)[2][ROWS] = (float (*)[2][ROWS])(lds + 2 * BUF_B);
   unsigned short* qlist = (unsigned short*)(lds + 2 * BUF_B + 2 * 2 * ROWS * 4);  // [Tq]
   __shared__ int wcnt[4];
@@ -841,9 +862,16 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
   const bf16_t* doh = slice_of(dout, L_d, bh, dm.H);
   const long long key = 64ll * (KB * J + half) + 32 * (w & 1) + l32;
   const bool kok = key < dm.N;
-  uint4 kf[8], vf[8];
-  own_rows(kh, L_k.sn, key, dm.N, hf, kf);
-  own_rows(vh, L_v.sn, key, dm.N, hf, vf);
+  v4i kf[8], vf[8];
+  {
+    uint4 f[8];
+    own_rows(kh, L_k.sn, key, dm.N, hf, f);
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) kf[ks] = __builtin_bit_cast(v4i, f[ks]);
+    own_rows(vh, L_v.sn, key, dm.N, hf, f);
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) vf[ks] = __builtin_bit_cast(v4i, f[ks]);
+  }
   // the accumulators start from the linear branch's share (G = nullptr: there is none); dK is scaled
   // by 1 / sqrt(d) at the end, so its share goes in multiplied by sqrt(d)
   v16f dkt[4], dvt[4];
@@ -865,11 +893,10 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
       dvt[ct] = v16f{};
     }
   }
-  // Steps = (list entry, pair of tiles of its query block): 64 query rows at a time.  They travel
+  // Steps = (list entry, pair of tiles of its query block): 64 query rows at a time.  With KB = 2 they travel
   // memory -> registers -> LDS: while step s is computed from one LDS buffer, step s + 1 is moved from
-  // registers to the other buffer and, where the registers allow a second set (KB = 2), step s + 2 is
-  // on its way from memory; one barrier per step.  Within a step the two tiles are independent, which
-  // lets the matrix products of one run under the exponentials of the other.
+  // registers to the other buffer and step s + 2 is on its way from memory; one barrier per step.  Within a step
+  // the two tiles are independent, which lets the matrix products of one run under the exponentials of the other.
   const int steps = nq << pair_shift, pair_mask = (1 << pair_shift) - 1;
   RowStage<NT, ROWS> sq0, sd0, sq1, sd1;
   float ps0 = 0.f, ps1 = 0.f;
@@ -912,8 +939,8 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
       dp[u] = v16f{};
 #pragma unroll
       for (int ks = 0; ks < 8; ++ks) {
-        s[u] = mfma_bf16(aq[ks], kf[ks], s[u]);
-        dp[u] = mfma_bf16(ad[ks], vf[ks], dp[u]);
+        s[u] = mfma_bf16(aq[ks], __builtin_bit_cast(uint4, kf[ks]), s[u]);
+        dp[u] = mfma_bf16(ad[ks], __builtin_bit_cast(uint4, vf[ks]), dp[u]);
       }
       __builtin_amdgcn_sched_group_barrier(0x100, 24, 0);  // 24 LDS reads (operands, then lse and delta)
       __builtin_amdgcn_sched_group_barrier(0x008, 16, 0);  // then 16 matrix products
@@ -952,18 +979,31 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
   // The same for two tiles per step (one key block per workgroup), laid out so that the vector work of
   // one tile (exponentials, dS, conversions) is issued between the matrix products of the other: a
   // lone wavefront per SIMD has nobody else to fill the matrix pipe while it computes exponentials.
-  auto compute_interleaved = [&](int step, int buf) __attribute__((always_inline)) {
-    if (!((qlist[step >> pair_shift] >> (14 + half)) & 1)) return;  // (always set; keeps the compiler from hoisting reads over the step boundary)
+  // Products whose result the vector ALU works on, written so that they sit in ordinary registers (the compiler put them
+  // into accumulation registers beside dK and dV and copied every element back: 64 copies a step).  The hardware does
+  // not hold back a vector instruction that reads a product's result too early, and the compiler does not see these
+  // products: scores_ready() is that wait (18 states after the last one) and hands the results over.
+  auto score0 = [&](v16f& d, const uint4& a, const v4i& b) __attribute__((always_inline)) {
+    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(__builtin_bit_cast(v4i, a)), "a"(b));
+  };
+  auto score = [&](v16f& d, const uint4& a, const v4i& b) __attribute__((always_inline)) {
+    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(__builtin_bit_cast(v4i, a)), "a"(b));
+  };
+  auto scores_ready = [&](v16f& x, v16f& y) __attribute__((always_inline)) {
+    asm volatile("s_nop 15\n\ts_nop 3" : "+v"(x), "+v"(y));
+  };
+  const int n_off = swz_lane_offset(l32, hf), t_off = swz_tr_lane_offset(lane);
+  auto compute_interleaved = [&](int buf) __attribute__((always_inline)) {
     const unsigned char* qt0 = lds + buf * BUF_B;
-    const unsigned char* dt0 = qt0 + TILES * TILE_B;
+    const unsigned char* dt0 = qt0 + 2 * SWZ_TILE_B;
     v16f s[2], dp[2], p[2];
     float4 ls[4], dl[4];
     uint4 aq[8], ad[8];
     auto read_ops = [&](int u) __attribute__((always_inline)) {
 #pragma unroll
       for (int ks = 0; ks < 8; ++ks) {
-        aq[ks] = n_op(qt0 + u * TILE_B, l32, hf, ks);
-        ad[ks] = n_op(dt0 + u * TILE_B, l32, hf, ks);
+        aq[ks] = n_op_swz(qt0 + u * SWZ_TILE_B, n_off, ks);
+        ad[ks] = n_op_swz(dt0 + u * SWZ_TILE_B, n_off, ks);
       }
     };
     auto read_stats = [&](int u) __attribute__((always_inline)) {
@@ -992,34 +1032,37 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
     uint4 td[4], tq[4], te[4], tr[4];  // transposed operands of the gradient products, two sets in turn
     read_ops(0);
     FENCE
-    s[0] = v16f{};
-    dp[0] = v16f{};
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) {
-      s[0] = mfma_bf16(aq[ks], kf[ks], s[0]);
-      dp[0] = mfma_bf16(ad[ks], vf[ks], dp[0]);
-      bq[ks] = n_op(qt0 + TILE_B, l32, hf, ks);
-      bd[ks] = n_op(dt0 + TILE_B, l32, hf, ks);
+      if (ks == 0) {
+        score0(s[0], aq[0], kf[0]);
+        score0(dp[0], ad[0], vf[0]);
+      } else {
+        score(s[0], aq[ks], kf[ks]);
+        score(dp[0], ad[ks], vf[ks]);
+      }
+      bq[ks] = n_op_swz(qt0 + SWZ_TILE_B, n_off, ks);
+      bd[ks] = n_op_swz(dt0 + SWZ_TILE_B, n_off, ks);
       FENCE
     }
     read_stats(0);
+    scores_ready(s[0], dp[0]);
     FENCE
-    s[1] = v16f{};
-    dp[1] = v16f{};
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) {
-      s[1] = mfma_bf16(bq[ks], kf[ks], s[1]);
+      if (ks == 0) score0(s[1], bq[0], kf[0]); else score(s[1], bq[ks], kf[ks]);
       weight(0, 2 * ks);
       FENCE
-      dp[1] = mfma_bf16(bd[ks], vf[ks], dp[1]);
+      if (ks == 0) score0(dp[1], bd[0], vf[0]); else score(dp[1], bd[ks], vf[ks]);
       weight(0, 2 * ks + 1);
       if (ks & 1) {
-        td[ks >> 1] = t_op(dt0, tr_off, ks >> 1, 0);
-        tq[ks >> 1] = t_op(qt0, tr_off, ks >> 1, 0);
+        td[ks >> 1] = t_op_swz(dt0, t_off, ks >> 1, 0);
+        tq[ks >> 1] = t_op_swz(qt0, t_off, ks >> 1, 0);
       }
       FENCE
     }
     read_stats(1);
+    scores_ready(s[1], dp[1]);
     {
       const uint4 pb = acc_operand(p[0], 0), dsb = acc_operand(s[0], 0);
       FENCE
@@ -1030,8 +1073,8 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
         FENCE
         dkt[ct] = mfma_bf16(tq[ct], dsb, dkt[ct]);
         weight(1, 2 * ct + 1);
-        te[ct] = t_op(dt0, tr_off, ct, 1);
-        tr[ct] = t_op(qt0, tr_off, ct, 1);
+        te[ct] = t_op_swz(dt0, t_off, ct, 1);
+        tr[ct] = t_op_swz(qt0, t_off, ct, 1);
         FENCE
       }
     }
@@ -1045,8 +1088,8 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
         FENCE
         dkt[ct] = mfma_bf16(tr[ct], dsb, dkt[ct]);
         weight(1, 8 + 2 * ct + 1);
-        td[ct] = t_op(dt0 + TILE_B, tr_off, ct, 0);
-        tq[ct] = t_op(qt0 + TILE_B, tr_off, ct, 0);
+        td[ct] = t_op_swz(dt0 + SWZ_TILE_B, t_off, ct, 0);
+        tq[ct] = t_op_swz(qt0 + SWZ_TILE_B, t_off, ct, 0);
         FENCE
       }
     }
@@ -1057,8 +1100,8 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
       for (int ct = 0; ct < 4; ++ct) {
         dvt[ct] = mfma_bf16(td[ct], pb, dvt[ct]);
         dkt[ct] = mfma_bf16(tq[ct], dsb, dkt[ct]);
-        te[ct] = t_op(dt0 + TILE_B, tr_off, ct, 1);
-        tr[ct] = t_op(qt0 + TILE_B, tr_off, ct, 1);
+        te[ct] = t_op_swz(dt0 + SWZ_TILE_B, t_off, ct, 1);
+        tr[ct] = t_op_swz(qt0 + SWZ_TILE_B, t_off, ct, 1);
         FENCE
       }
     }
@@ -1084,26 +1127,64 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
 #define DKV_STEP(S, AHEAD, BUF, SQL, SDL, PSL, SQN, SDN, PSN)  \
   if ((S) >= steps) break;                                     \
   DKV_LOAD(SQL, SDL, PSL, (S) + (AHEAD))                       \
-  if constexpr (KB == 1 && TILES == 2) compute_interleaved((S), BUF); else compute((S), BUF); \
+  compute((S), BUF);                                           \
   DKV_STORE(SQN, SDN, PSN, 1 - (BUF))                          \
   __syncthreads();
-  if (steps > 0) {
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the workgroup's own K, V rows are in (else the loop would wait for them each time round)
-    DKV_LOAD(sq0, sd0, ps0, 0)
-    if constexpr (NT * 2 >= ROWS * 8) {  // two register sets in rotation, two steps in flight
+  if constexpr (KB == 1) {
+    // Copies straight to LDS: while step s is computed from one buffer, step s + 1 travels into the other (the last
+    // step is copied again past the end); 16 pieces and one row of lse or delta per wavefront and step.
+    if (steps > 0) {
+      const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
+      const int ws = __builtin_amdgcn_readfirstlane(w);
+      TileCopy<2> cq, cd;
+      cq.init(qh, L_q.sn, ws, lane);
+      cd.init(doh, L_d.sn, ws, lane);
+      const float* srow = (ws ? delta : lse2) + (size_t)bh * dm.T32q * 32;
+      auto request = [&](int r0, int buf) __attribute__((always_inline)) {
+        const unsigned dst = lds0 + buf * BUF_B;
+        cq.tile(r0, dm.N, dst);
+        cq.tile(r0 + 32, dm.N, dst + SWZ_TILE_B);
+        cd.tile(r0, dm.N, dst + 2 * SWZ_TILE_B);
+        cd.tile(r0 + 32, dm.N, dst + 3 * SWZ_TILE_B);
+        copy_floats(srow + r0, lane * 4, lds0 + 2 * BUF_B + (buf * 2 + ws) * ROWS * 4);
+      };
+      auto row_of = [&](int step) __attribute__((always_inline)) { return __builtin_amdgcn_readfirstlane(rows_of(min(step, steps - 1))); };
+      // (names the place of what lives through the loop: the allocator parked operands beside it otherwise)
+      auto hold = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int ct = 0; ct < 4; ++ct) asm volatile("" : "+a"(dkt[ct]), "+a"(dvt[ct]));
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) asm volatile("" : "+a"(kf[ks]), "+a"(vf[ks]));
+      };
+      int r1 = row_of(1);
+      __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the workgroup's own K, V rows are in
+      request(row_of(0), 0);
+      copies_barrier<0>();
+      for (int step = 0; step < steps; step += 2) {  // (every exit test is uniform over the workgroup)
+        hold();
+        request(r1, 1);
+        r1 = row_of(step + 2);
+        compute_interleaved(0);
+        hold();
+        copies_barrier<0>();
+        if (step + 1 >= steps) break;
+        request(r1, 0);
+        r1 = row_of(step + 3);
+        compute_interleaved(1);
+        hold();
+        copies_barrier<0>();
+      }
+    }
+  } else {
+    if (steps > 0) {
+      __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the workgroup's own K, V rows are in (else the loop would wait for them each time round)
+      DKV_LOAD(sq0, sd0, ps0, 0)
       DKV_LOAD(sq1, sd1, ps1, 1)
       DKV_STORE(sq0, sd0, ps0, 0)
       __syncthreads();
       for (int step = 0;; step += 2) {  // (every exit test is uniform over the workgroup)
         DKV_STEP(step, 2, 0, sq0, sd0, ps0, sq1, sd1, ps1)
         DKV_STEP(step + 1, 2, 1, sq1, sd1, ps1, sq0, sd0, ps0)
-      }
-    } else {                             // (a set is 64 registers here) one set, one step ahead
-      DKV_STORE(sq0, sd0, ps0, 0)
-      __syncthreads();
-      for (int step = 0;; step += 2) {
-        DKV_STEP(step, 1, 0, sq0, sd0, ps0, sq0, sd0, ps0)
-        DKV_STEP(step + 1, 1, 1, sq0, sd0, ps0, sq0, sd0, ps0)
       }
     }
   }
@@ -1270,17 +1351,16 @@ int launch_bwd_dq(const Problem& p, const void* q, const void* dout, const void*
   return 0;
 }
 
-constexpr int DKV1_TILES = 2;  // tiles per step of the one-key-block variant: 2 (78 KB of LDS per workgroup) runs compute_interleaved, 1 the plain step
 template <int PHI, bool ST>
 static int launch_bwd_dkv_phi(const Problem& p, const void* q, const void* dout, const void* k, const void* v, const int8_t* mask,
                                const float* lse2, const float* delta, const bf16_t* G, void* dk, void* dv, hipStream_t stream) {
   // dynamic LDS: two staging buffers, the rows' lse and delta, the list of query blocks
   const int list_bytes = (2 * p.Tq + 15) & ~15;
   const int lds2 = 2 * 4 * TILE_B + 2 * 2 * 64 * 4 + list_bytes;
-  const int lds1 = 2 * 2 * DKV1_TILES * TILE_B + 2 * 2 * 32 * DKV1_TILES * 4 + list_bytes;
+  const int lds1 = 2 * 4 * SWZ_TILE_B + 2 * 2 * 64 * 4 + list_bytes;
   static const bool ok =
       hipFuncSetAttribute((const void*)bwd_dkv_kernel<2, 2, PHI, ST>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 256) == hipSuccess &&
-      hipFuncSetAttribute((const void*)bwd_dkv_kernel<1, DKV1_TILES, PHI, ST>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 256) == hipSuccess;
+      hipFuncSetAttribute((const void*)bwd_dkv_kernel<1, 2, PHI, ST>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 256) == hipSuccess;
   if (!ok) return -1;
   const int tiles = p.block_q / 32;  // of a query block: 2 or 4
   // Two key blocks per workgroup halve the bytes streamed where their lists coincide and idle half
@@ -1293,9 +1373,9 @@ static int launch_bwd_dkv_phi(const Problem& p, const void* q, const void* dout,
         (const bf16_t*)q, (const bf16_t*)dout, (const bf16_t*)k, (const bf16_t*)v, mask, lse2, delta, G,
         (bf16_t*)dk, (bf16_t*)dv, tiles == 4 ? 1 : 0, bwd_dims(p));
   } else {
-    bwd_dkv_kernel<1, DKV1_TILES, PHI, ST><<<(unsigned)(8 * ((p.Tk + 7) / 8) * p.BH), 128, lds1, stream>>>(
+    bwd_dkv_kernel<1, 2, PHI, ST><<<(unsigned)(8 * ((p.Tk + 7) / 8) * p.BH), 128, lds1, stream>>>(
         (const bf16_t*)q, (const bf16_t*)dout, (const bf16_t*)k, (const bf16_t*)v, mask, lse2, delta, G,
-        (bf16_t*)dk, (bf16_t*)dv, (tiles == 4 ? 2 : 1) - (DKV1_TILES == 2 ? 1 : 0), bwd_dims(p));
+        (bf16_t*)dk, (bf16_t*)dv, tiles == 4 ? 1 : 0, bwd_dims(p));
   }
   return 0;
 }
