@@ -20,6 +20,7 @@
 // product that contracts over the tile's tokens reads the same tile with the transposing LDS read
 // of gfx950 (ds_read_b64_tr_b16), so no transposed copy of any tensor is ever made.
 #include <initializer_list>
+#include <type_traits>
 
 #include "common.h"
 
@@ -158,7 +159,7 @@ struct TileCopy {
   // rows row0 .. row0 + 31; rows beyond N come as row N - 1 (their weight is zero)
   __device__ __forceinline__ void tile(int row0, int N, unsigned lds_tile) const {
     const unsigned dst = __builtin_amdgcn_readfirstlane(lds_tile + w * PPW * 1024);
-    if (row0 + 32 <= N && snb < (1 << 26)) {  // (uniform; beyond that stride the 32-bit offsets do not reach)
+    if (__builtin_expect(row0 + 32 <= N && snb < (1 << 26), 1)) {  // (uniform; beyond that stride the 32-bit offsets do not reach)
       const char* b = slice + row0 * snb;
 #pragma unroll
       for (int i = 0; i < PPW; ++i) copy_piece(i < 4 ? b : b + 16 * snb, off[i & 3], dst + i * 1024);
@@ -578,115 +579,233 @@ __device__ __forceinline__ void store_grad4(bf16_t* dst, const float* lin, float
   *(uint2*)dst = uint2{pack_bf16x2(a0, a1), pack_bf16x2(a2, a3)};
 }
 
-template <int NW, bool ST = false>
-__global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) bwd_dq_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ dout,
-                                                         const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
-                                                         const int32_t* __restrict__ crit, const float* __restrict__ lse2,
-                                                         const float* __restrict__ delta, const float* __restrict__ dq_lin,
-                                                         bf16_t* __restrict__ dq, BwdDims dm) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char lds_all[];  // two buffers of: K (2 tiles) then V (2 tiles) of a key block
+// Products whose result the vector ALU works on, written so that they sit in ordinary registers (where a wavefront has
+// 512, the compiler put them into accumulation registers beside the sums and copied every element back).  The hardware
+// does not hold back a vector instruction that reads a product's result too early (11 wait states after a product of
+// this size), and the compiler does not see these products.  score_done() hands a result over and has to stand behind
+// at least two further products: a product is issued only when the one before has left the pipe (8 states), so they
+// put 16 states between.  score_wait() is the wait by itself, where no products follow.
+__device__ __forceinline__ void score0(v16f& d, const uint4& a, const v4i& b) {
+  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(__builtin_bit_cast(v4i, a)), "a"(b));
+}
+__device__ __forceinline__ void score(v16f& d, const uint4& a, const v4i& b) {
+  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(__builtin_bit_cast(v4i, a)), "a"(b));
+}
+__device__ __forceinline__ void score_done(v16f& x) { asm volatile("" : "+v"(x)); }
+__device__ __forceinline__ void score_wait(v16f& x) { asm volatile("s_nop 15\n\ts_nop 3" : "+v"(x)); }
+
+// dQ, per query block over its critical key blocks: dS = P o (dP - delta) with P = 2^(S - lse), dQ += dS K / sqrt(d).
+//
+// A wavefront owns QT tiles of 32 queries (two: an operand read from LDS serves two products; with 32 queries each,
+// the reads of four wavefronts at full matrix rate ask for all the LDS delivers), K and V come in tiles of 32 keys
+// through a ring of R, copied up to R - 1 steps ahead.  A lone wavefront per SIMD, so a step is written in the order of
+// issue, one piece per product, and runs across two tiles: S of tile t + 1 with dS of tile t behind its products, dQ of
+// tile t with exponentials of tile t + 1, dP of tile t + 1 with the rest of them.  Operands are read a section early,
+// and the barrier that publishes a tile stands in the middle of a section, whose products cover the first reads of it.
+// 40 heads x 75600 tokens 16.8 -> 16.1 ms (half the LDS traffic lets the clock rise from 1.78 to 1.87 GHz; the matrix pipe
+// is 56 % busy), query blocks of 64 (12 x 32760) 1.42 -> 1.00 ms; 12 x 32760 at 128 token-major 0.96 -> 0.97 ms.
+template <int WAVES, int QT, bool ST>
+__global__ void __launch_bounds__(WAVES * 64, 1) bwd_dq_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ dout,
+                                                              const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
+                                                              const int32_t* __restrict__ crit, const float* __restrict__ lse2,
+                                                              const float* __restrict__ delta, const float* __restrict__ dq_lin,
+                                                              bf16_t* __restrict__ dq, BwdDims dm) {
+  constexpr int R = WAVES == 1 ? 2 : 4;   // (four workgroups of one wavefront have 40 KB of LDS each)
+  __shared__ __attribute__((aligned(16))) unsigned char ring[R * 2 * SWZ_TILE_B];  // K, V tile by tile
   int i, bh;
   if (!xcd_block(dm.Tq, i, bh)) return;
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6, l32 = lane & 31, hf = lane >> 5;
-  const int tr_off = tr_lane_offset(lane);
-  const int T = i * NW + w;
-  const long long qrow = 32ll * T + l32;
   SLA_BWD_LAYOUTS
-  const size_t head = (size_t)bh * dm.N * D;   // (of the library's own contiguous tensors)
-  const bf16_t* kh = slice_of(k, L_k, bh, dm.H);
-  const bf16_t* vh = slice_of(v, L_v, bh, dm.H);
-  uint4 qf[8], dof[8];
-  own_rows(slice_of(q, L_q, bh, dm.H), L_q.sn, qrow, dm.N, hf, qf);
-  own_rows(slice_of(dout, L_d, bh, dm.H), L_d.sn, qrow, dm.N, hf, dof);
-  const size_t sidx = (size_t)bh * dm.T32q * 32 + 32 * T + l32;
-  const float lse_q = lse2[sidx], delta_q = delta[sidx];
-  const int32_t* crow = crit + ((size_t)bh * dm.Tq + i) * dm.n_c;
-  RowStage<NW * 64, 64> sk, sv;
-  v16f acc[4];
+  const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6), l32 = lane & 31, hf = lane >> 5;
+  const int row0 = 32 * QT * (i * WAVES + w);
+  v4i qf[QT][8], dof[QT][8];
+  v16f acc[QT][4];
+  float lse[QT], del[QT];
 #pragma unroll
-  for (int ct = 0; ct < 4; ++ct) acc[ct] = v16f{};
+  for (int x = 0; x < QT; ++x)
+#pragma unroll
+    for (int ct = 0; ct < 4; ++ct) acc[x][ct] = v16f{};
   if (dm.n_c > 0) {
-    sk.load(kh, L_k.sn, 64ll * crow[0], dm.N, t);
-    sv.load(vh, L_v.sn, 64ll * crow[0], dm.N, t);
-    sk.store(lds_all, t);
-    sv.store(lds_all + 2 * TILE_B, t);
-  }
-  // Everything requested so far has to be in before the loop: a load the compiler cannot prove
-  // finished on every path into the loop would be waited for each time round, in the middle of the
-  // products and together with the loads of the next block just issued.  For the same reason the
-  // loop's own loads and stores are unconditional (rows beyond N come as row N - 1; their P is 0).
-  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-  __syncthreads();
-  for (int b = 0; b < dm.n_c; ++b) {
-    const int j = crow[b];
-    const unsigned char* lds = lds_all + (b & 1) * 4 * TILE_B;
-    unsigned char* lds_next = lds_all + ((b + 1) & 1) * 4 * TILE_B;
-    {  // the next block (after the last one: the last one again), the same loads every time round -- see below
-      const int jn = 64 * crow[min(b + 1, dm.n_c - 1)];
-      sk.load_clamped(kh, L_k.sn, jn, dm.N, t);
-      sv.load_clamped(vh, L_v.sn, jn, dm.N, t);
+    const int32_t* __restrict__ crow = crit + ((size_t)bh * dm.Tq + i) * dm.n_c;
+    const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void*)ring;
+    TileCopy<WAVES> ck, cv;
+    ck.init(slice_of(k, L_k, bh, dm.H), L_k.sn, w, lane);
+    cv.init(slice_of(v, L_v, bh, dm.H), L_v.sn, w, lane);
+    constexpr int PER_TILE = 2 * TileCopy<WAVES>::PPW;
+    const int n_off = swz_lane_offset(l32, hf), t_off = swz_tr_lane_offset(lane);
+    const int tiles = 2 * dm.n_c;
+    auto block_at = [&](int b) __attribute__((always_inline)) { return crow[min(b, dm.n_c - 1)]; };   // (past the end: the last block again)
+    auto request = [&](int tile, int key) __attribute__((always_inline)) {
+      const unsigned dst = lds0 + (tile & (R - 1)) * 2 * SWZ_TILE_B;
+      ck.tile(key, dm.N, dst);
+      cv.tile(key, dm.N, dst + SWZ_TILE_B);
+    };
+    // (names the place of what lives through the loop)
+    auto hold = [&]() __attribute__((always_inline)) {
+#pragma unroll
+      for (int x = 0; x < QT; ++x) {
+#pragma unroll
+        for (int ct = 0; ct < 4; ++ct) asm volatile("" : "+a"(acc[x][ct]));
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) asm volatile("" : "+a"(qf[x][ks]), "+a"(dof[x][ks]));
+      }
+    };
+#pragma unroll
+    for (int tile = 0; tile < R; ++tile) request(tile, 64 * block_at(tile >> 1) + 32 * (tile & 1));
+#pragma unroll
+    for (int x = 0; x < QT; ++x) {
+      // (rows beyond N come as row N - 1: their lse is +inf, so their P and dS are zero)
+      const long long row = min(row0 + 32 * x + l32, dm.N - 1);
+      const bf16_t *qr = slice_of(q, L_q, bh, dm.H) + row * L_q.sn + 8 * hf, *dr = slice_of(dout, L_d, bh, dm.H) + row * L_d.sn + 8 * hf;
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks) {
+        qf[x][ks] = *(const v4i*)(qr + 16 * ks);
+        dof[x][ks] = *(const v4i*)(dr + 16 * ks);
+      }
+      const size_t sidx = (size_t)bh * dm.T32q * 32 + row0 + 32 * x + l32;
+      lse[x] = lse2[sidx];
+      del[x] = delta[sidx];
     }
+    copies_barrier<0>();                       // (the wavefront's own rows and the first R tiles)
+    uint4 ak[8], av[8], tk[4][2];
 #pragma unroll
-    for (int kt = 0; kt < 2; ++kt) {
-      const unsigned char* ktile = lds + kt * TILE_B;
-      const unsigned char* vtile = lds + (2 + kt) * TILE_B;
-      // operand reads grouped ahead of the matrix products that use them
-      uint4 ak[8], av[8];
+    for (int ks = 0; ks < 8; ++ks) ak[ks] = n_op_swz(ring, n_off, ks);
+    v16f sa[QT], sb[QT], dp[QT];
+    // the sequence's last key block can only be the last entry of the ascending list: from tile `whole` on keys are missing
+    const int whole = crow[dm.n_c - 1] * 64 + 64 <= dm.N ? tiles : tiles - 2;
+#define FENCE __builtin_amdgcn_sched_barrier(0);
+    auto weight = [&](v16f (&s)[QT], int e) __attribute__((always_inline)) {   // P: element e % 16 of query tile e / 16
+      s[e >> 4][e & 15] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e >> 4][e & 15], QK_LOG2, -lse[e >> 4]));
+    };
+    auto dscore = [&](v16f (&s)[QT], int e) __attribute__((always_inline)) { s[e >> 4][e & 15] *= dp[e >> 4][e & 15] - del[e >> 4]; };
+    // Keys beyond N (the sequence's last key block only) came as key N - 1, so their P and dS are finite: their column
+    // of K^T is cleared.
+    auto clear_missing = [&](int key0) __attribute__((always_inline)) {
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks) {
-        ak[ks] = n_op(ktile, l32, hf, ks);
-        av[ks] = n_op(vtile, l32, hf, ks);
-      }
-      v16f s = v16f{}, dp = v16f{};
+      for (int y = 0; y < 2; ++y)
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks) s = mfma_bf16(ak[ks], qf[ks], s);
+        for (int j = 0; j < 4; ++j) {
+          const int key = key0 + 16 * y + 8 * (j >> 1) + 4 * hf + 2 * (j & 1);
+          const uint32_t keep = (key < dm.N ? 0xffffu : 0u) | (key + 1 < dm.N ? 0xffff0000u : 0u);
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks) dp = mfma_bf16(av[ks], dof[ks], dp);
-      // K reads; the score products, one V read behind each; the dO V^T products
-      __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
-#pragma unroll
-      for (int ks = 0; ks < 8; ++ks) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-      }
-      __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
-      if (64 * j + 64 <= dm.N) {  // (uniform) only the sequence's last key block can hold keys that do not exist
-#pragma unroll
-        for (int r = 0; r < 16; ++r) s[r] = __builtin_amdgcn_exp2f(s[r] * QK_LOG2 - lse_q) * (dp[r] - delta_q);
-      } else {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int key = 64 * j + 32 * kt + 8 * (r >> 2) + 4 * hf + (r & 3);
-          const float p = key < dm.N ? __builtin_amdgcn_exp2f(s[r] * QK_LOG2 - lse_q) : 0.f;
-          s[r] = p * (dp[r] - delta_q);
+          for (int ct = 0; ct < 4; ++ct) {
+            uint32_t* word = (uint32_t*)&tk[ct][y];
+            word[j] &= keep;
+          }
         }
+    };
+    // dP of a tile (V operands in av); behind its products the second part of its exponentials and, once the tile is
+    // consumed and the next one has landed, the reads of the next one's K
+    constexpr int M = 8 * QT, E = 16 * QT;   // products of a section; elements per lane of the query tiles' P, dS
+    auto dp_products = [&](v16f (&s)[QT], int tile, int key_far) __attribute__((always_inline)) {   // key_far: of tile + R
+      const unsigned char* next = ring + ((tile + 1) & (R - 1)) * 2 * SWZ_TILE_B;
+#pragma unroll
+      for (int m = 0; m < M; ++m) {
+        const int ks = m / QT, x = m % QT;
+        if (ks == 0) score0(dp[x], av[0], dof[x][0]); else score(dp[x], av[ks], dof[x][ks]);
+#pragma unroll
+        for (int e = M - 3 + m * (E - M + 3) / M; e < M - 3 + (m + 1) * (E - M + 3) / M; ++e) weight(s, e);
+        if (m == M / 2 - 1) {
+          FENCE
+          copies_barrier<(R - 2) * PER_TILE>();    // the next tile has landed; this one is consumed
+          request(tile + R, key_far);
+        }
+        if (m >= M / 2 && x == 0) {
+          ak[2 * (ks - 4)] = n_op_swz(next, n_off, 2 * (ks - 4));
+          ak[2 * (ks - 4) + 1] = n_op_swz(next, n_off, 2 * (ks - 4) + 1);
+        }
+        FENCE
+      }
+    };
+    {  // the first tile's S, P and dP
+#pragma unroll
+      for (int m = 0; m < M; ++m) {
+        const int ks = m / QT, x = m % QT;
+        if (ks == 0) score0(sa[x], ak[0], qf[x][0]); else score(sa[x], ak[ks], qf[x][ks]);
+        if (x == 0) av[ks] = n_op_swz(ring + SWZ_TILE_B, n_off, ks);
+        FENCE
       }
 #pragma unroll
-      for (int sx = 0; sx < 2; ++sx) {
-        const uint4 dsb = acc_operand(s, sx);
-        uint4 tk[4];
+      for (int x = 0; x < QT; ++x) score_wait(sa[x]);
 #pragma unroll
-        for (int ct = 0; ct < 4; ++ct) tk[ct] = t_op(ktile, tr_off, ct, sx);
+      for (int e = 0; e < M - 3; ++e) weight(sa, e);
 #pragma unroll
-        for (int ct = 0; ct < 4; ++ct) acc[ct] = mfma_bf16(tk[ct], dsb, acc[ct]);
-        __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
-      }
+      for (int y = 0; y < 8; ++y) tk[y & 3][y >> 2] = t_op_swz(ring, t_off, y & 3, y >> 2);
+      if (whole <= 0) clear_missing(64 * crow[0]);
+      dp_products(sa, 0, 64 * block_at(R / 2));
     }
-    sk.store(lds_next, t);  // (after the last block: into the buffer nobody reads any more)
-    sv.store(lds_next + 2 * TILE_B, t);
-    __syncthreads();
+    // One step: dQ of tile t from its P (s), dP and K^T operands; S, P, dP and operands of tile t + 1 (after the
+    // last tile: of a copy of the last block, whose results nobody uses; a step that leaves them out made the
+    // allocator spill 330 registers).
+    auto step = [&](int t, v16f (&s)[QT], v16f (&sn)[QT], int key_far) __attribute__((always_inline)) {
+      const unsigned char* kt = ring + ((t + 1) & (R - 1)) * 2 * SWZ_TILE_B;
+      uint4 ds[QT][2];
+      // dS of t, element by element, packed to operands as eight are done
+      constexpr int E1 = QT == 2 ? E - 6 : E;      // of them behind the products of S (from the fourth on: dP of t is done)
+      auto dscores = [&](int from, int to) __attribute__((always_inline)) {
+#pragma unroll
+        for (int e = from; e < to; ++e) {
+          dscore(s, e);
+          if ((e & 7) == 7) ds[e >> 4][(e >> 3) & 1] = acc_operand(s[e >> 4], (e >> 3) & 1);
+        }
+      };
+      // S of t + 1; behind its products dS of t and the reads of V
+#pragma unroll
+      for (int m = 0; m < M; ++m) {
+        const int ks = m / QT, x = m % QT;
+        if (ks == 0) score0(sn[x], ak[0], qf[x][0]); else score(sn[x], ak[ks], qf[x][ks]);
+        if (m == 3) {
+#pragma unroll
+          for (int z = 0; z < QT; ++z) score_done(dp[z]);
+        }
+        if (m >= 3) dscores((m - 3) * E1 / (M - 3), (m - 2) * E1 / (M - 3));
+        if (x == 0) av[ks] = n_op_swz(kt + SWZ_TILE_B, n_off, ks);
+        FENCE
+      }
+      // dQ of t; behind its products the last of dS, the first part of the exponentials of t + 1 and its K^T operands
+#pragma unroll
+      for (int m = 0; m < M; ++m) {
+        const int x = m >> 3, y = m & 7;
+        acc[x][y & 3] = mfma_bf16(tk[y & 3][y >> 2], ds[x][y >> 2], acc[x][y & 3]);
+        if (QT == 2 && m < 3) dscores(E1 + 2 * m, E1 + 2 * m + 2);
+        if (m == 3) {
+#pragma unroll
+          for (int z = 0; z < QT; ++z) score_done(sn[z]);
+        }
+        if (m >= 3) weight(sn, m - 3);
+        if (x == QT - 1) tk[y & 3][y >> 2] = t_op_swz(kt, t_off, y & 3, y >> 2);
+        FENCE
+      }
+      if (__builtin_expect(t + 1 >= whole, 0)) clear_missing(64 * block_at((t + 1) >> 1) + 32 * ((t + 1) & 1));
+      dp_products(sn, t + 1, key_far);
+      hold();
+    };
+#undef FENCE
+    hold();
+    // (list entries are loaded a round before they are needed: a scalar load's latency in every step cost a tenth of it)
+    int j0 = block_at(R / 2), j1 = block_at(R / 2 + 1);
+    for (int t = 0; t < tiles; t += 2) {
+      const int j2 = block_at(t / 2 + R / 2 + 2);
+      step(t, sa, sb, 64 * j0 + 32);
+      step(t + 1, sb, sa, 64 * j1);
+      j0 = j1;
+      j1 = j2;
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70);        // (no copy may land after the workgroup has left)
   }
-  if (qrow < dm.N) {
-    const size_t row = head + qrow * D;          // (the linear branch's share: the library's own tensor)
-    bf16_t* dqrow = slice_of(dq, L_dq, bh, dm.H) + qrow * L_dq.sn;
+#pragma unroll
+  for (int x = 0; x < QT; ++x) {
+    const long long row = row0 + 32 * x + l32;
+    if (row >= dm.N) continue;
+    const float* lin = dq_lin ? dq_lin + ((size_t)bh * dm.N + row) * D : nullptr;   // (the library's own tensor)
+    bf16_t* dqrow = slice_of(dq, L_dq, bh, dm.H) + row * L_dq.sn;
 #pragma unroll
     for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         const int ch = 32 * ct + 8 * g + 4 * hf;
-        store_grad4(dqrow + ch, dq_lin ? dq_lin + row + ch : nullptr, acc[ct][4 * g] * INV_SQRT_D,
-                    acc[ct][4 * g + 1] * INV_SQRT_D, acc[ct][4 * g + 2] * INV_SQRT_D, acc[ct][4 * g + 3] * INV_SQRT_D);
+        const v16f& a = acc[x][ct];
+        store_grad4(dqrow + ch, lin ? lin + ch : nullptr, a[4 * g] * INV_SQRT_D, a[4 * g + 1] * INV_SQRT_D,
+                    a[4 * g + 2] * INV_SQRT_D, a[4 * g + 3] * INV_SQRT_D);
       }
   }
 }
@@ -814,7 +933,7 @@ __device__ __forceinline__ void linear_kv_share(const bf16_t* __restrict__ k, co
 // LDS (no registers, no padding: see TileCopy), the scores are formed in ordinary registers and dK, dV, K, V held in the
 // accumulation registers, so a step is its 64 products, 160 vector instructions and 112 LDS reads with no register
 // copies between the two files (there were 77 a step, and the copies through registers took 56 more).  40 heads x
-// 75600 tokens 29.9 -> 26.7 ms, 12 x 32760 token-major 2.17 -> 2.05 ms; 164 GB past L2 = 6.1 TB/s at 2.0 GHz, the matrix
+// 75600 tokens 29.9 -> 25.9 ms, 12 x 32760 token-major 2.18 -> 1.78 ms; 164 GB past L2 = 6.3 TB/s at 2.0 GHz, the matrix
 // pipe 43 % busy: bound by the lone wavefront's waits between the sections and by the stream.
 template <int KB, int TILES, int PHI, bool ST = false>
 __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ dout,
@@ -979,19 +1098,6 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
   // The same for two tiles per step (one key block per workgroup), laid out so that the vector work of
   // one tile (exponentials, dS, conversions) is issued between the matrix products of the other: a
   // lone wavefront per SIMD has nobody else to fill the matrix pipe while it computes exponentials.
-  // Products whose result the vector ALU works on, written so that they sit in ordinary registers (the compiler put them
-  // into accumulation registers beside dK and dV and copied every element back: 64 copies a step).  The hardware does
-  // not hold back a vector instruction that reads a product's result too early, and the compiler does not see these
-  // products: scores_ready() is that wait (18 states after the last one) and hands the results over.
-  auto score0 = [&](v16f& d, const uint4& a, const v4i& b) __attribute__((always_inline)) {
-    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(__builtin_bit_cast(v4i, a)), "a"(b));
-  };
-  auto score = [&](v16f& d, const uint4& a, const v4i& b) __attribute__((always_inline)) {
-    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(__builtin_bit_cast(v4i, a)), "a"(b));
-  };
-  auto scores_ready = [&](v16f& x, v16f& y) __attribute__((always_inline)) {
-    asm volatile("s_nop 15\n\ts_nop 3" : "+v"(x), "+v"(y));
-  };
   const int n_off = swz_lane_offset(l32, hf), t_off = swz_tr_lane_offset(lane);
   auto compute_interleaved = [&](int buf) __attribute__((always_inline)) {
     const unsigned char* qt0 = lds + buf * BUF_B;
@@ -1046,15 +1152,25 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
       FENCE
     }
     read_stats(0);
-    scores_ready(s[0], dp[0]);
     FENCE
+    // P and dS of a tile behind sixteen products that do not need them, from the fourth on (the tile's own are done then)
+    auto weights_behind = [&](int u, int m) __attribute__((always_inline)) {
+      if (m == 3) {
+        score_done(s[u]);
+        score_done(dp[u]);
+      }
+      if (m >= 3) {
+#pragma unroll
+        for (int r = (m - 3) * 16 / 13; r < (m - 2) * 16 / 13; ++r) weight(u, r);
+      }
+    };
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) {
       if (ks == 0) score0(s[1], bq[0], kf[0]); else score(s[1], bq[ks], kf[ks]);
-      weight(0, 2 * ks);
+      weights_behind(0, 2 * ks);
       FENCE
       if (ks == 0) score0(dp[1], bd[0], vf[0]); else score(dp[1], bd[ks], vf[ks]);
-      weight(0, 2 * ks + 1);
+      weights_behind(0, 2 * ks + 1);
       if (ks & 1) {
         td[ks >> 1] = t_op_swz(dt0, t_off, ks >> 1, 0);
         tq[ks >> 1] = t_op_swz(qt0, t_off, ks >> 1, 0);
@@ -1062,17 +1178,16 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
       FENCE
     }
     read_stats(1);
-    scores_ready(s[1], dp[1]);
     {
       const uint4 pb = acc_operand(p[0], 0), dsb = acc_operand(s[0], 0);
       FENCE
 #pragma unroll
       for (int ct = 0; ct < 4; ++ct) {
         dvt[ct] = mfma_bf16(td[ct], pb, dvt[ct]);
-        weight(1, 2 * ct);
+        weights_behind(1, 2 * ct);
         FENCE
         dkt[ct] = mfma_bf16(tq[ct], dsb, dkt[ct]);
-        weight(1, 2 * ct + 1);
+        weights_behind(1, 2 * ct + 1);
         te[ct] = t_op_swz(dt0, t_off, ct, 1);
         tr[ct] = t_op_swz(qt0, t_off, ct, 1);
         FENCE
@@ -1084,10 +1199,10 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
 #pragma unroll
       for (int ct = 0; ct < 4; ++ct) {
         dvt[ct] = mfma_bf16(te[ct], pb, dvt[ct]);
-        weight(1, 8 + 2 * ct);
+        weights_behind(1, 8 + 2 * ct);
         FENCE
         dkt[ct] = mfma_bf16(tr[ct], dsb, dkt[ct]);
-        weight(1, 8 + 2 * ct + 1);
+        weights_behind(1, 8 + 2 * ct + 1);
         td[ct] = t_op_swz(dt0 + SWZ_TILE_B, t_off, ct, 0);
         tq[ct] = t_op_swz(qt0 + SWZ_TILE_B, t_off, ct, 0);
         FENCE
@@ -1148,7 +1263,7 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
         cd.tile(r0 + 32, dm.N, dst + 3 * SWZ_TILE_B);
         copy_floats(srow + r0, lane * 4, lds0 + 2 * BUF_B + (buf * 2 + ws) * ROWS * 4);
       };
-      auto row_of = [&](int step) __attribute__((always_inline)) { return __builtin_amdgcn_readfirstlane(rows_of(min(step, steps - 1))); };
+      auto row_at = [&](int step) __attribute__((always_inline)) { return rows_of(min(step, steps - 1)); };
       // (names the place of what lives through the loop: the allocator parked operands beside it otherwise)
       auto hold = [&]() __attribute__((always_inline)) {
 #pragma unroll
@@ -1156,21 +1271,23 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks) asm volatile("" : "+a"(kf[ks]), "+a"(vf[ks]));
       };
-      int r1 = row_of(1);
+      int r1 = __builtin_amdgcn_readfirstlane(row_at(1)), ahead;   // (ahead: read from the list in LDS during the step)
       __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the workgroup's own K, V rows are in
-      request(row_of(0), 0);
+      request(__builtin_amdgcn_readfirstlane(row_at(0)), 0);
       copies_barrier<0>();
       for (int step = 0; step < steps; step += 2) {  // (every exit test is uniform over the workgroup)
         hold();
         request(r1, 1);
-        r1 = row_of(step + 2);
+        ahead = row_at(step + 2);
         compute_interleaved(0);
+        r1 = __builtin_amdgcn_readfirstlane(ahead);
         hold();
         copies_barrier<0>();
         if (step + 1 >= steps) break;
         request(r1, 0);
-        r1 = row_of(step + 3);
+        ahead = row_at(step + 3);
         compute_interleaved(1);
+        r1 = __builtin_amdgcn_readfirstlane(ahead);
         hold();
         copies_barrier<0>();
       }
@@ -1336,17 +1453,19 @@ void launch_bwd_delta(const Problem& p, const void* dout, const void* os, const 
 int launch_bwd_dq(const Problem& p, const void* q, const void* dout, const void* k, const void* v, const int32_t* crit,
                   const float* lse2, const float* delta, const float* dq_lin, void* dq, hipStream_t stream) {
   const unsigned grid = (unsigned)(8 * ((p.Tq + 7) / 8) * p.BH);
-  static const bool ok = allow_lds(bwd_dq_kernel<4>) && allow_lds(bwd_dq_kernel<2>) && allow_lds(bwd_dq_kernel<4, true>) &&
-                         allow_lds(bwd_dq_kernel<2, true>);
-  if (!ok) return -1;
   const bool st = !contiguous(p, {&p.lq, &p.lk, &p.lv, &p.ld, &p.ldq});
-#define SLA_DQ(NW, ST) bwd_dq_kernel<NW, ST><<<grid, NW * 64, KV_STAGE_BYTES, stream>>>( \
+  // One tile per wavefront where two would leave SIMDs without a wavefront (query blocks of 64, 4617 tokens, us before ->
+  // now: 3 heads 28.5 -> 27.2, 14 heads 93 -> 79 with one tile; 20 heads 126 -> 102 with two)
+  const bool narrow = (long long)p.Tq * p.BH * (p.block_q / 64) < 1024;
+#define SLA_DQ(WAVES, QT, ST) bwd_dq_kernel<WAVES, QT, ST><<<grid, WAVES * 64, 0, stream>>>( \
       (const bf16_t*)q, (const bf16_t*)dout, (const bf16_t*)k, (const bf16_t*)v, crit, lse2, delta, dq_lin, (bf16_t*)dq, bwd_dims(p))
+#define SLA_DQ_ST(WAVES, QT) { if (st) SLA_DQ(WAVES, QT, true); else SLA_DQ(WAVES, QT, false); }
   if (p.block_q == 128) {
-    if (st) SLA_DQ(4, true); else SLA_DQ(4, false);
+    if (narrow) SLA_DQ_ST(4, 1) else SLA_DQ_ST(2, 2)
   } else {
-    if (st) SLA_DQ(2, true); else SLA_DQ(2, false);
+    if (narrow) SLA_DQ_ST(2, 1) else SLA_DQ_ST(1, 2)
   }
+#undef SLA_DQ_ST
 #undef SLA_DQ
   return 0;
 }
