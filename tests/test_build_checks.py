@@ -81,3 +81,51 @@ def test_w8a8_chains_are_in_place_and_read_late_enough():
                 break                            # overwritten before any read: nothing to wait for
             nop = re.match(r"s_nop (\d+)", l)
             waited += int(nop.group(1)) + 1 if nop else (8 if l.startswith("v_mfma") and l.split(",")[-1].strip().startswith("v[") else 1)
+
+
+@pytest.mark.skipif(_hipcc() is None, reason="hipcc not available")
+def test_backward_scores_are_read_late_enough():
+    """The dQ and dK/dV kernels form S and dP by assembly products in ordinary registers; the vector ALU may read a
+    result 11 wait states after the last product of its chain.  Between the two lie either that many states of
+    `s_nop` or at least two further products (8 states each: one issues only when the one before has left the pipe)."""
+    from paper_2512_16093_amd import build as b
+    src = os.path.join(ROOT, "paper_2512_16093_amd", "csrc", "k_bwd.hip")
+    with tempfile.TemporaryDirectory() as tmp:
+        out = os.path.join(tmp, "k.s")
+        flags = [f for f in b.FLAGS if f not in ("-fPIC",)]
+        r = subprocess.run([_hipcc()] + flags + ["-S", "--cuda-device-only", src, "-o", out], capture_output=True, text=True)
+        assert r.returncode == 0, r.stderr[-2000:]
+        lines = open(out).read().splitlines()
+    kernel, checked, pending = None, {}, {}      # pending: register -> [products since, s_nop states since]
+    for line in lines:
+        name = re.match(r"_ZN3sla\d+(bwd_dq_kernel|bwd_dkv_kernelILi1)\S*:", line)
+        if name:
+            kernel, pending = name.group(1), {}
+        ins = line.split(";")[0].strip()
+        if kernel is None or not re.match(r"[a-z]", ins):
+            continue
+        op, _, operands = ins.partition(" ")
+        if op == "s_endpgm":
+            kernel = None
+        elif op == "s_branch":                   # what follows in the file does not follow in time
+            pending = {}
+        elif op == "s_nop":
+            for p in pending.values():
+                p[1] += int(operands) + 1
+        elif op.startswith("v_mfma"):
+            for p in pending.values():
+                p[0] += 1
+            for reg in _regs(operands.split(",")[0]):
+                pending[reg] = [0, 0]
+        elif op.startswith(("v_", "ds_", "global_store")):
+            dst, _, srcs = operands.partition(",")
+            if not op.startswith(("v_", "ds_read")):
+                dst, srcs = "", operands
+            for reg in _regs(srcs) & set(pending):
+                products, states = pending.pop(reg)
+                assert products >= 2 or states >= 11, (kernel, ins, products, states)
+                checked[kernel] = checked.get(kernel, 0) + 1
+            for reg in _regs(dst):
+                pending.pop(reg, None)
+    # every instance reads at least the 32 scores and 32 dP of a step
+    assert set(checked) == {"bwd_dq_kernel", "bwd_dkv_kernelILi1"} and min(checked.values()) >= 64, checked
