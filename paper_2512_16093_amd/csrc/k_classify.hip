@@ -157,30 +157,44 @@ __global__ void zero_u32_kernel(uint32_t* p, size_t n) {
 
 // What the statistics still need once every block's sums are known; runs as the first workgroups of the scores
 // launch (both depend on pool_stats alone, and a launch of its own cost the smallest calls 11 of 61 us).
-// Workgroups 0 .. 8 BH - 1, eight per (b,h), each for 16 channels: mu_K[c] = sum_j cnt_j kbar[j][c] / N (summed in a
-// fixed order), max|V[:,c]|, delta_V[c] = max|V[:,c]| / 448 (1 if zero).
+// Workgroups 0 .. 8 BH - 1, eight per (b,h), each for 16 channels: mu_K[c] = sum_j cnt_j kbar[j][c] / N, max|V[:,c]|,
+// delta_V[c] = max|V[:,c]| / 448 (1 if zero).  The INT8 codes of K hang on the last bit of the mean, so its order of
+// summation is part of the result: MEAN_RUNS interleaved partial sums (j, j + 64, ...), then those in ascending order.
+// A thread carries MEAN_RUNS / 16 of them, which also keeps that many loads in flight.
+constexpr int MEAN_RUNS = 64;
 __device__ __forceinline__ void finalize_block(int blk, const float* __restrict__ kbar, const float* __restrict__ vmax_part,
                                                int groups, int N, int Tk, float* __restrict__ mu_k,
                                                float* __restrict__ amax_v, float* __restrict__ dv) {
-  __shared__ float red[2][16][17];
+  constexpr int PER = MEAN_RUNS / 16;
+  __shared__ float sums[MEAN_RUNS][17], maxima[16][17];
   const int bh = blk >> 3, c0 = (blk & 7) * 16, t = threadIdx.x, cl = t & 15, rgrp = t >> 4;
-  float s = 0.f, m = 0.f;
-#pragma unroll 8
-  for (int j = rgrp; j < Tk; j += 16) s += kbar[((size_t)bh * Tk + j) * D + c0 + cl] * (float)min(BK, N - j * BK);
+  float s[PER] = {}, m = 0.f;
+  const float* col = kbar + (size_t)bh * Tk * D + c0 + cl;
+  int j0 = 0;
+#pragma unroll 4
+  for (; j0 + MEAN_RUNS <= Tk && (j0 + MEAN_RUNS) * BK <= N; j0 += MEAN_RUNS)   // (whole blocks only)
+#pragma unroll
+    for (int u = 0; u < PER; ++u) s[u] += col[(size_t)(j0 + rgrp + 16 * u) * D] * (float)BK;
+  for (; j0 < Tk; j0 += MEAN_RUNS)
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int j = j0 + rgrp + 16 * u;
+      if (j < Tk) s[u] += col[(size_t)j * D] * (float)min(BK, N - j * BK);
+    }
 #pragma unroll 8
   for (int g = rgrp; g < groups; g += 16) m = fmaxf(m, vmax_part[((size_t)bh * groups + g) * D + c0 + cl]);
-  red[0][rgrp][cl] = s;
-  red[1][rgrp][cl] = m;
+#pragma unroll
+  for (int u = 0; u < PER; ++u) sums[rgrp + 16 * u][cl] = s[u];
+  maxima[rgrp][cl] = m;
   __syncthreads();
   if (t < 16) {
-    s = 0.f;
+    float tot = 0.f;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      s += red[0][r][t];
-      m = fmaxf(m, red[1][r][t]);
-    }
+    for (int r = 0; r < MEAN_RUNS; ++r) tot += sums[r][t];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) m = fmaxf(m, maxima[r][t]);
     const size_t o = (size_t)bh * D + c0 + t;
-    mu_k[o] = s / (float)N;
+    mu_k[o] = tot / (float)N;
     amax_v[o] = m;
     dv[o] = m > 0.f ? m / E4M3_MAX : 1.0f;
   }

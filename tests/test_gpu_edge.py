@@ -193,3 +193,24 @@ def test_codes_of_blocks_with_tiny_maxima():
     out = sla.sla_attention_fwd(q.cuda(), k.cuda(), v.cuda(), 128, 64, 0.5, 0.5).float().cpu().numpy()
     r = pu.oracle_head(cfg, q, k, v, 0, 0, None)
     pu.check_output(out[0, 0], r["out"], "tiny maxima")
+
+
+@pytest.mark.parametrize("N", [40, 1050, 4096, 4097, 4160, 12790])   # 1, 17 (ragged), 64, 65 (one key), 65 and 200 (ragged) key blocks
+def test_mean_of_k_keeps_its_order_of_summation(N):
+    """The INT8 codes of K hang on the last bit of its channel mean, so the order in which the mean is summed is part of
+    the result: 64 interleaved partial sums over the key blocks, then those in ascending order, all in fp32.  Keys that
+    are constant within a block (block means are then exact) make the sum reproducible on the host, bit for bit."""
+    rng = np.random.default_rng(N)
+    Tk = -(-N // 64)
+    rows = torch.from_numpy(rng.standard_normal((2, Tk, 128)) * 2.0 ** rng.integers(-6, 7, (2, Tk, 1))).to(torch.bfloat16)
+    k = rows.repeat_interleave(64, 1)[None, :, :N].contiguous().cuda()
+    mean = sla.sla_debug_quantize_kv(k, k)[2].cpu().numpy()[0]
+    count = np.minimum(64, N - 64 * np.arange(Tk)).astype(np.float32)
+    share = rows.float().numpy() * count[None, :, None]            # (exact: eight bits times at most 64)
+    runs = np.zeros((2, 64, 128), np.float32)
+    for j in range(Tk):
+        runs[:, j % 64] += share[:, j]
+    total = np.zeros((2, 128), np.float32)
+    for r in range(64):
+        total += runs[:, r]
+    assert np.array_equal(mean.view(np.int32), (total / np.float32(N)).view(np.int32))
