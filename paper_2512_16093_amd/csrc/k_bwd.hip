@@ -581,10 +581,11 @@ __device__ __forceinline__ void store_grad4(bf16_t* dst, const float* lin, float
 
 // Products whose result the vector ALU works on, written so that they sit in ordinary registers (where a wavefront has
 // 512, the compiler put them into accumulation registers beside the sums and copied every element back).  The hardware
-// does not hold back a vector instruction that reads a product's result too early (11 wait states after a product of
-// this size), and the compiler does not see these products.  score_done() hands a result over and has to stand behind
-// at least two further products: a product is issued only when the one before has left the pipe (8 states), so they
-// put 16 states between.  score_wait() is the wait by itself, where no products follow.
+// does not hold back a vector instruction that reads a product's result, or writes its registers, too early (12 wait
+// states after a product of this size on gfx950), and the compiler does not see these products.  score_done() hands a
+// result over and has to stand behind at least two further products: a product is issued only when the one before has
+// left the pipe (8 states), so they put 16 states between.  score_wait() is the wait by itself, where no products
+// follow; also of a result that nobody reads, whose registers are given to something else from there on.
 __device__ __forceinline__ void score0(v16f& d, const uint4& a, const v4i& b) {
   asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(__builtin_bit_cast(v4i, a)), "a"(b));
 }
@@ -790,6 +791,9 @@ __global__ void __launch_bounds__(WAVES * 64, 1) bwd_dq_kernel(const bf16_t* __r
       j0 = j1;
       j1 = j2;
     }
+    // (the last step's dP is not used, but it is still on its way to its registers)
+#pragma unroll
+    for (int x = 0; x < QT; ++x) score_wait(dp[x]);
     __builtin_amdgcn_s_waitcnt(0x0F70);        // (no copy may land after the workgroup has left)
   }
 #pragma unroll

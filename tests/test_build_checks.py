@@ -1,13 +1,16 @@
-"""Static check of generated code (CPU only; needs hipcc, which cross-compiles without a GPU).
+"""Static checks of generated code (CPU only; need hipcc, which cross-compiles without a GPU).
 
 The W8A8 product writes each accumulation chain (four MFMAs, the first taking its C operand as an
 inline constant the compiler would otherwise hold in 16 registers) as ONE assembly statement, so the
 chain accumulates in place by construction.  The compiler does not know the statement holds matrix
 products and inserts no wait states before a vector instruction that reads the chain's result (the
 hardware does not interlock that case); the kernel is written so that every such reader comes a
-whole chain later in program order.  This test compiles the kernel to assembly and checks both: the
+whole chain later in program order.  The first test compiles the kernel to assembly and checks both: the
 chains are in place, and at least 18 instructions (the wait states the longest case needs) lie
-between the end of a chain and the first instruction that reads its result."""
+between the end of a chain and the first instruction that reads its result.
+
+The second test follows every path behind every matrix product written in assembly, in all sources that have
+them: nothing reads OR writes the product's result before it has landed, branches and loops included."""
 import os
 import re
 import shutil
@@ -35,17 +38,21 @@ def _regs(operand_text):
     return regs
 
 
-@pytest.mark.skipif(_hipcc() is None, reason="hipcc not available")
-def test_w8a8_chains_are_in_place_and_read_late_enough():
+def _assembly(source):
     from paper_2512_16093_amd import build as b
-    src = os.path.join(ROOT, "paper_2512_16093_amd", "csrc", "k_w8a8.hip")
+    src = os.path.join(ROOT, "paper_2512_16093_amd", "csrc", source)
     with tempfile.TemporaryDirectory() as tmp:
         out = os.path.join(tmp, "k.s")
         flags = [f for f in b.FLAGS if f not in ("-fPIC",)]
         r = subprocess.run([_hipcc()] + flags + ["-S", "--cuda-device-only", src, "-o", out],
                            capture_output=True, text=True)
         assert r.returncode == 0, r.stderr[-2000:]
-        text = open(out).read()
+        return open(out).read()
+
+
+@pytest.mark.skipif(_hipcc() is None, reason="hipcc not available")
+def test_w8a8_chains_are_in_place_and_read_late_enough():
+    text = _assembly("k_w8a8.hip")
     # instructions only (no labels, directives, comments)
     ins = [l.split(";")[0].strip() for l in text.splitlines()]
     ins = [l for l in ins if l and not l.startswith(".") and not l.endswith(":") and re.match(r"[a-z]", l)]
@@ -78,54 +85,152 @@ def test_w8a8_chains_are_in_place_and_read_late_enough():
                 assert waited >= 18, (ins[i], l, "result read after only %d wait states" % waited)
                 break
             if _regs(operands.split(",", 1)[0]) & mine:
-                break                            # overwritten before any read: nothing to wait for
+                break                            # overwritten before any read (how late: the next test)
             nop = re.match(r"s_nop (\d+)", l)
             waited += int(nop.group(1)) + 1 if nop else (8 if l.startswith("v_mfma") and l.split(",")[-1].strip().startswith("v[") else 1)
 
 
-@pytest.mark.skipif(_hipcc() is None, reason="hipcc not available")
-def test_backward_scores_are_read_late_enough():
-    """The dQ and dK/dV kernels form S and dP by assembly products in ordinary registers; the vector ALU may read a
-    result 11 wait states after the last product of its chain.  Between the two lie either that many states of
-    `s_nop` or at least two further products (8 states each: one issues only when the one before has left the pipe)."""
-    from paper_2512_16093_amd import build as b
-    src = os.path.join(ROOT, "paper_2512_16093_amd", "csrc", "k_bwd.hip")
-    with tempfile.TemporaryDirectory() as tmp:
-        out = os.path.join(tmp, "k.s")
-        flags = [f for f in b.FLAGS if f not in ("-fPIC",)]
-        r = subprocess.run([_hipcc()] + flags + ["-S", "--cuda-device-only", src, "-o", out], capture_output=True, text=True)
-        assert r.returncode == 0, r.stderr[-2000:]
-        lines = open(out).read().splitlines()
-    kernel, checked, pending = None, {}, {}      # pending: register -> [products since, s_nop states since]
-    for line in lines:
-        name = re.match(r"_ZN3sla\d+(bwd_dq_kernel|bwd_dkv_kernelILi1)\S*:", line)
+# ---- every access behind an assembly product, on every path
+PASSES = 8    # wait states a 32 x 32 product of either kind occupies the matrix pipe: the next one is issued behind them
+LANDED = 12   # wait states before another instruction may touch its result (gfx950; the compiler puts `s_nop 11` behind its own)
+OPERANDS = 2  # wait states between a vector instruction's result and a product that takes it as an operand
+
+
+class _Ins:
+    def __init__(self, text, in_asm):
+        self.text, self.op = text, text.split()[0]
+        operands = [o.strip() for o in re.split(r",(?![^\[]*\])", text[len(self.op):])]
+        self.operands, self.asm_product = operands, in_asm and self.op.startswith("v_mfma")
+        self.product = self.op.startswith("v_mfma")
+        self.all = _files(" ".join(operands))
+        self.first, self.rest = _files(operands[0]), _files(" ".join(operands[1:]))
+        self.states = int(operands[0]) + 1 if self.op == "s_nop" else 1
+
+
+def _files(text):
+    """Registers named in an operand string, with their file: ("v", 12), ("a", 3)."""
+    regs = set()
+    for f, lo, hi in re.findall(r"\b([va])\[(\d+):(\d+)\]", text):
+        regs.update((f, x) for x in range(int(lo), int(hi) + 1))
+    regs.update((f, int(x)) for f, x in re.findall(r"\b([va])(\d+)\b", text))
+    return frozenset(regs)
+
+
+def _kernels(text):
+    """Mangled name -> (instructions, label -> index of the instruction behind it)."""
+    kernels, cur, in_asm = {}, None, False
+    for line in text.splitlines():
+        name, label = re.match(r"(_Z\w+):", line), re.match(r"(\.LBB\w+):", line)
         if name:
-            kernel, pending = name.group(1), {}
+            cur = kernels.setdefault(name.group(1), ([], {}))
+        elif label and cur:
+            cur[1][label.group(1)] = len(cur[0])
+        in_asm = (in_asm or "#ASMSTART" in line) and "#ASMEND" not in line
         ins = line.split(";")[0].strip()
-        if kernel is None or not re.match(r"[a-z]", ins):
+        if cur and re.match(r"[a-z]\w*(\s|$)", ins):
+            cur[0].append(_Ins(ins, in_asm))
+    return kernels
+
+
+def _next(ins, labels, x):
+    op = ins[x].op
+    if op == "s_endpgm":
+        return []
+    if op == "s_branch":
+        return [labels[ins[x].operands[0]]]
+    return [labels[ins[x].operands[0]], x + 1] if op.startswith("s_cbranch") else [x + 1]
+
+
+def _early_accesses(ins, labels):
+    """(assembly products, [product, instruction that touches its result too early, wait states between])."""
+    products, found = 0, []
+    for x, p in enumerate(ins):
+        if not p.asm_product:
             continue
-        op, _, operands = ins.partition(" ")
-        if op == "s_endpgm":
-            kernel = None
-        elif op == "s_branch":                   # what follows in the file does not follow in time
-            pending = {}
-        elif op == "s_nop":
-            for p in pending.values():
-                p[1] += int(operands) + 1
-        elif op.startswith("v_mfma"):
-            for p in pending.values():
-                p[0] += 1
-            for reg in _regs(operands.split(",")[0]):
-                pending[reg] = [0, 0]
-        elif op.startswith(("v_", "ds_", "global_store")):
-            dst, _, srcs = operands.partition(",")
-            if not op.startswith(("v_", "ds_read")):
-                dst, srcs = "", operands
-            for reg in _regs(srcs) & set(pending):
-                products, states = pending.pop(reg)
-                assert products >= 2 or states >= 11, (kernel, ins, products, states)
-                checked[kernel] = checked.get(kernel, 0) + 1
-            for reg in _regs(dst):
-                pending.pop(reg, None)
-    # every instance reads at least the 32 scores and 32 dP of a step
-    assert set(checked) == {"bwd_dq_kernel", "bwd_dkv_kernelILi1"} and min(checked.values()) >= 64, checked
+        products += 1
+        todo, seen = [(y, 1, PASSES) for y in _next(ins, labels, x)], set()   # (instruction, its time, when the pipe is free)
+        while todo:
+            y, t, free = todo.pop()
+            if (y, t, free) in seen:
+                continue
+            seen.add((y, t, free))
+            i = ins[y]
+            if i.product:
+                t = max(t, free)
+                free = t + PASSES
+            if t > LANDED:
+                continue
+            if i.all & p.first:
+                # the chain goes on in place (or starts again in the same registers): the hardware holds that back
+                if not (i.product and i.first == p.first and not _files(" ".join(i.operands[1:3])) & p.first):
+                    found.append((p.text, i.text, t - 1))
+                continue
+            todo += [(z, t + i.states, free) for z in _next(ins, labels, y)]
+    return products, found
+
+
+def _late_operands(ins, labels):
+    """[vector instruction, assembly product that takes its result too early, wait states between]."""
+    found = []
+    for x, p in enumerate(ins):
+        if not p.op.startswith("v_") or p.product:
+            continue
+        todo = [(y, 0) for y in _next(ins, labels, x)]
+        while todo:
+            y, t = todo.pop()
+            if t >= OPERANDS:
+                continue
+            if ins[y].asm_product and ins[y].rest & p.first:
+                found.append((p.text, ins[y].text, t))
+            else:
+                todo += [(z, t + ins[y].states) for z in _next(ins, labels, y)]
+    return found
+
+
+# kernel -> instances and assembly products of each: the dQ kernel forms S and dP of a prologue and two steps, QT tiles of
+# eight products each; dK/dV (one key block) S and dP of two tiles in two steps; W8A8 chains of four per output tile
+EXPECTED = {
+    "k_bwd.hip": {r"bwd_dq_kernelILi\dELi1": (4, 48), r"bwd_dq_kernelILi\dELi2": (4, 96), r"bwd_dkv_kernelILi1": (6, 64)},
+    "k_w8a8.hip": {r"w8a8_gemm_kernelE": (1, 96), r"w8a8_gemm_splitk_kernelILi2ELi2": (3, 16),
+                   r"w8a8_gemm_splitk_kernelILi1ELi2": (2, 8), r"w8a8_gemm_splitk_kernelILi1ELi1": (2, 4)},
+}
+
+
+@pytest.mark.skipif(_hipcc() is None, reason="hipcc not available")
+@pytest.mark.parametrize("source", sorted(EXPECTED))
+def test_products_have_landed_before_anything_touches_them(source):
+    counts = {}
+    for name, (ins, labels) in _kernels(_assembly(source)).items():
+        products, early = _early_accesses(ins, labels)
+        assert not early, (name, early[:4])
+        assert not _late_operands(ins, labels), (name, _late_operands(ins, labels)[:4])
+        if products:
+            counts[name] = products
+    for pattern, (instances, products) in EXPECTED[source].items():
+        mine = [n for k, n in counts.items() if re.search(pattern, k)]
+        assert mine == [products] * instances, (pattern, mine)
+    assert len(counts) == sum(n for n, _ in EXPECTED[source].values()), sorted(counts)
+
+
+def test_every_source_with_assembly_products_is_checked():
+    csrc = os.path.join(ROOT, "paper_2512_16093_amd", "csrc")
+    assert {f for f in os.listdir(csrc) if 'asm volatile("v_mfma' in open(os.path.join(csrc, f)).read()} == set(EXPECTED)
+
+
+def test_the_check_sees_what_it_is_for():
+    """Planted code: a result read one product later, one overwritten behind a taken branch, one past a loop's back edge."""
+    product = "\t;;#ASMSTART\n\tv_mfma_f32_32x32x16_bf16 v[0:15], v[20:23], a[0:3], 0\n\t;;#ASMEND\n"
+    other = product.replace("v[0:15]", "v[32:47]")
+
+    def early(body):
+        (ins, labels), = _kernels("_Zk:\n" + body + "\ts_endpgm\n").values()
+        return len(_early_accesses(ins, labels)[1])
+    read, write = "\tv_add_f32_e32 v50, v3, v51\n", "\tv_mov_b32_e32 v4, v50\n"
+    assert early(product + read) == early(product + write) == early(product + other + read) == 1
+    assert early(product + other + other + read) == 0 and early(product + "\ts_nop 11\n" + read) == 0
+    assert early(product + "\ts_nop 10\n" + write) == 1
+    assert early(product + "\ts_cbranch_scc1 .LBB0_1\n\ts_nop 15\n" + read + ".LBB0_1:\n" + write) == 1
+    assert early(".LBB0_1:\n" + write + product + "\ts_cbranch_scc0 .LBB0_1\n\ts_nop 15\n") == 1
+    assert early(product + product.replace("a[0:3], 0", "a[0:3], v[0:15]") + "\ts_nop 15\n" + read) == 0
+    (ins, labels), = _kernels("_Zk:\n\tv_mov_b32_e32 v21, v50\n\ts_nop 0\n" + product + "\ts_endpgm\n").values()
+    assert len(_late_operands(ins, labels)) == 1
