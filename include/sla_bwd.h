@@ -23,7 +23,8 @@
  * before and after); inputs are never written; outputs must not alias inputs or the workspace.
  * Returns SLA_OK or a negative sla_status; argument errors are found on the host before any launch.
  * Supported: what sla_attention_fwd supports for shapes, blocks and ratios; contiguous [B,H,N,d]
- * tensors (other layouts: the _strided entry points below); any phi_kind of sla_phi (relu's gradient is taken as 0 at x <= 0).
+ * tensors, which may start at any element (16-byte aligned ones are read fastest; other layouts: the
+ * _strided entry points below); any phi_kind of sla_phi (relu's gradient is taken as 0 at x <= 0).
  */
 #ifndef SLA_BWD_H_
 #define SLA_BWD_H_

@@ -143,11 +143,13 @@ struct TileCopy {
   static constexpr int PPW = 8 / WAVES;
   const char* slice;   // the (b,h) slice's first token
   long long snb;       // bytes from one token to the next
+  unsigned odd;        // 0: 16-byte aligned rows at a stride that the 32-bit offsets below reach
   unsigned off[4];     // this lane's byte offset in pieces i, i + 4 of its wavefront
   int w, lane;
   __device__ __forceinline__ void init(const bf16_t* x, long long sn, int w_, int lane_) {
     slice = (const char*)x;
     snb = 2 * sn;
+    odd = ((unsigned)(uintptr_t)x & 15u) | (unsigned)(snb >> 26);
     w = w_;
     lane = lane_;
 #pragma unroll
@@ -159,7 +161,7 @@ struct TileCopy {
   // rows row0 .. row0 + 31; rows beyond N come as row N - 1 (their weight is zero)
   __device__ __forceinline__ void tile(int row0, int N, unsigned lds_tile) const {
     const unsigned dst = __builtin_amdgcn_readfirstlane(lds_tile + w * PPW * 1024);
-    if (__builtin_expect(row0 + 32 <= N && snb < (1 << 26), 1)) {  // (uniform; beyond that stride the 32-bit offsets do not reach)
+    if (__builtin_expect(row0 + 32 <= N && odd == 0, 1)) {  // (uniform)
       const char* b = slice + row0 * snb;
 #pragma unroll
       for (int i = 0; i < PPW; ++i) copy_piece(i < 4 ? b : b + 16 * snb, off[i & 3], dst + i * 1024);
@@ -169,7 +171,17 @@ struct TileCopy {
 #pragma unroll 1
       for (int i = 0; i < PPW; ++i) {
         const int r = 4 * (PPW * w + i) + (ln >> 4);
-        copy_piece(slice + min(row0 + r, N - 1) * snb + (((ln & 15) ^ swz(r)) << 4), dst + i * 1024);
+        const char* src = slice + min(row0 + r, N - 1) * snb + (((ln & 15) ^ swz(r)) << 4);
+        if ((odd & 15u) == 0) {
+          copy_piece(src, dst + i * 1024);
+        } else {
+          // A contiguous tensor may start at any element.  The asynchronous copies take whole 16-byte units only, an
+          // ordinary load takes any address: through a register.  (It has arrived before the next one is requested, so
+          // waiting by count errs on the safe side.)
+          v4i got;
+          __builtin_memcpy(&got, src, 16);
+          *(__attribute__((address_space(3))) v4i*)(uintptr_t)(dst + i * 1024 + ln * 16) = got;
+        }
       }
     }
   }

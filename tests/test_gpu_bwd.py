@@ -264,3 +264,37 @@ def test_backward_of_many_heads(bq):
         r = bo.sla_backward_head(*(synth.as_f64(t[0, h]) for t in (q, k, v, dout)), mask[0, h], bq, 64)
         for name, got in (("dQ", dq), ("dK", dk), ("dV", dv)):
             _compare("%s head %d" % (name, h), got[0, h].float().cpu().numpy(), r[name])
+
+
+@pytest.mark.parametrize("H,grid,bq,rc,rm", [
+    (2, (5, 10, 20), 128, 0.25, 0.5),     # one tile of 32 queries per wavefront, a ragged last block
+    (2, (5, 10, 20), 64, 0.25, 0.5),
+    (64, (5, 10, 20), 128, 0.25, 0.5),    # two of them
+    (64, (5, 10, 20), 64, 0.25, 0.5),
+    (2, (4, 16, 16), 128, 0.75, 0.25),    # whole blocks; two key blocks per workgroup in dK / dV
+])
+def test_contiguous_tensors_may_start_at_any_element(H, grid, bq, rc, rm):
+    """The calls without strides take contiguous tensors wherever they start (a slice of a flat buffer): the kernels that
+    copy rows of 16-byte units straight to LDS take others through registers.  Same values, so the same bits."""
+    cfg = synth.custom_config(1, H, grid, block_q=bq, topk_ratio=rc, marginal_ratio=rm, use_proj=True, cfg_id=340)
+    q, k, v = synth.make_qkv(cfg)
+    even = [t.cuda() for t in (q, k, v, synth.make_qkv(cfg, seed=7)[2], synth.make_proj(cfg))]
+
+    def moved(t, elements):
+        flat = torch.zeros(t.numel() + 8, dtype=t.dtype, device="cuda")
+        view = flat[elements:elements + t.numel()].view(t.shape)
+        view.copy_(t)
+        assert view.is_contiguous() and view.data_ptr() % 16 == 2 * elements
+        return view
+    for shift in (1, 4):
+        odd = [moved(t, shift) for t in even]
+        got_out, got_saved = sla.sla_attention_fwd_train(*odd[:3], bq, 64, rc, rm, proj_w=odd[4])
+        out, saved = sla.sla_attention_fwd_train(*even[:3], bq, 64, rc, rm, proj_w=even[4])
+        assert torch.equal(got_out, out) and torch.equal(got_saved, saved)
+        for state in (None, saved):
+            kw = dict(want_dw=True, want_db=True, saved=state)
+            grads = tuple(moved(torch.zeros_like(t), shift) for t in even[:3])
+            want = sla.sla_attention_bwd(*even[:4], bq, 64, rc, rm, proj_w=even[4], **kw)
+            got = sla.sla_attention_bwd(*odd[:4], bq, 64, rc, rm, proj_w=odd[4], grads=grads, **kw)
+            for name, a, b in zip(("dQ", "dK", "dV", "dW", "db"), got, want):
+                assert torch.equal(a, b), (name, shift, state is None)
