@@ -184,3 +184,38 @@ def test_every_tile_and_split_of_the_product(M, K, N):
     wc, wsc = (t.cpu().numpy().astype(np.float64) for t in sla.w8a8_debug_unpack(wq, True, N, K))
     ref = wo.linear_from_codes(xc, xs, wc, wsc, synth.as_f64(b))
     assert np.all(np.abs(y - ref) <= product_tolerance(ref, xs, wsc, K)), np.abs(y - ref).max()
+
+
+@pytest.mark.parametrize("M,K,N", [
+    (33, 640, 384), (5, 1152, 2048),          # one block to a wavefront (eight ways); runs of one and two blocks
+    (200, 384, 8192), (513, 640, 5120),       # two ways: runs of one and two, of two and three blocks
+    (128, 1664, 5120), (512, 5120, 1024),     # eight ways over 13 blocks, four over 40
+    (1500, 128, 5120),                        # one block in all
+])
+def test_split_contraction_is_no_less_precise_than_one_walk(M, K, N):
+    """Splitting the contraction must not cost precision.  The yardstick is the kernel's arithmetic in ONE walk over the
+    feature blocks, formed here on the same codes: per block one fma of (constant +- block sum) in fp32, constants of
+    alternating sign, their sum (a rounded product) taken out at the end.  Counted is how many outputs are not the correctly rounded bf16 of
+    the exact sum; both counts are of M x N outputs, their own scatter is well under the 2 % (and 50) allowed."""
+    x, w, _ = synth.make_linear_inputs(M, K, N, seed=9)
+    wq = sla.w8a8_quantize_weight(w.cuda())
+    ws = sla.w8a8_quantize_act(x.cuda())
+    y = sla.w8a8_gemm_fwd(ws, wq, M, N, K)
+    (xc, xs), (wc, wsc) = sla.w8a8_debug_unpack(ws, False, M, K), sla.w8a8_debug_unpack(wq, True, N, K)
+    rows = lambda s, n: s.repeat_interleave(128, 0)[:n]
+    c0 = np.int32(0x3E22F983).view(np.float32).item()
+    exact = torch.zeros((M, N), dtype=torch.float64, device="cuda")
+    walk, csum = torch.zeros((M, N), dtype=torch.float32, device="cuda"), torch.zeros((M, N), dtype=torch.float32, device="cuda")
+    for kb in range(K // 128):
+        block = xc[:, 128 * kb:128 * kb + 128].double() @ wc[:, 128 * kb:128 * kb + 128].double().t().contiguous()
+        scale = rows(xs[:, kb:kb + 1], M) * rows(wsc[:, kb:kb + 1], N).t()          # fp32, as the kernel forms it
+        exact += block * (rows(xs[:, kb:kb + 1], M).double() * rows(wsc[:, kb:kb + 1], N).double().t())
+        sc = (scale * 2.0 ** 26 * (-1.0) ** kb).double()
+        acc = c0 + block * 2.0 ** -26 * (-1.0) ** kb                                # exact: a float of the binade [1/8, 1/4)
+        walk = (acc * sc + walk.double()).float()                                   # (one rounding to fp32, as in an fma)
+        csum = (csum.double() + sc).float()
+    walk = walk - c0 * csum
+    rounded = exact.to(torch.bfloat16)
+    missed, allowed = int((y != rounded).sum()), int((walk.to(torch.bfloat16) != rounded).sum())
+    print("w8a8 %d x %d -> %d: %d outputs not the rounded exact sum, one walk %d" % (M, K, N, missed, allowed))
+    assert missed <= 1.02 * allowed + 50
