@@ -428,9 +428,10 @@ __global__ void __launch_bounds__(NW * 64, 1)
 }
 
 // dW[x] and db[x] = sum over p of part[p][x] in a fixed order.  Workgroups 0 .. 255 take 64 entries of dW each (dw
-// given), the last two 64 of db: 16 threads of four adjacent entries, 16 threads along p (every 16th partial, four
-// loads in flight), added up in LDS.  Bound by reading the partials; with one thread per entry a chain of additions
-// as long as the list bound it (768 partials of 64 KiB, dW and db: 141 us in two launches, now 256 partials and 5 us).
+// given), the last two 64 of db: 16 threads of four adjacent entries, 16 threads along p (every 16th partial, in four
+// sums), joined pairwise in LDS (one after the other, the largest sums were rounded 15 times over: db of 4 x 4617 tokens
+// off by 8.2e-8, now 5.9e-8).  Bound by reading the partials; with one thread per entry a chain of additions as long
+// as the list bound it (768 partials of 64 KiB, dW and db: 141 us in two launches, now 256 partials and 5 us).
 constexpr int RED_ENTRIES = 64;
 __global__ void __launch_bounds__(256) bwd_reduce_partials_kernel(const float* __restrict__ dw_part, const float* __restrict__ db_part,
                                                                   int n_part, float* __restrict__ dw, float* __restrict__ db) {
@@ -439,21 +440,27 @@ __global__ void __launch_bounds__(256) bwd_reduce_partials_kernel(const float* _
   const bool is_db = blk >= dw_blocks;
   const int n = is_db ? D : D * D, x = (is_db ? blk - dw_blocks : blk) * RED_ENTRIES + 4 * col;
   const float* part = (is_db ? db_part : dw_part) + x;
-  float4 s = float4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-  for (int p = row; p < n_part; p += 16) {
-    const float4 v = *(const float4*)(part + (size_t)p * n);
-    s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
-  }
-  red[row][col] = s;
+  auto add = [](float4& a, const float4& b) __attribute__((always_inline)) { a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w; };
+  float4 s[4] = {};
+  int p = row;
+  for (; p + 48 < n_part; p += 64)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) add(s[u], *(const float4*)(part + (size_t)(p + 16 * u) * n));
+  for (; p < n_part; p += 16) add(s[0], *(const float4*)(part + (size_t)p * n));
+  add(s[0], s[1]);
+  add(s[2], s[3]);
+  add(s[0], s[2]);
+  red[row][col] = s[0];
   __syncthreads();
   if (t < 16) {
+    float4 v[16];
 #pragma unroll
-    for (int r = 1; r < 16; ++r) {
-      const float4 v = red[r][t];
-      s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
-    }
-    *(float4*)((is_db ? db : dw) + x) = s;
+    for (int r = 0; r < 16; ++r) v[r] = red[r][t];
+#pragma unroll
+    for (int step = 1; step < 16; step *= 2)
+#pragma unroll
+      for (int r = 0; r < 16; r += 2 * step) add(v[r], v[r + step]);
+    *(float4*)((is_db ? db : dw) + x) = v[0];
   }
 }
 

@@ -298,3 +298,24 @@ def test_contiguous_tensors_may_start_at_any_element(H, grid, bq, rc, rm):
             got = sla.sla_attention_bwd(*odd[:4], bq, 64, rc, rm, proj_w=odd[4], grads=grads, **kw)
             for name, a, b in zip(("dQ", "dK", "dV", "dW", "db"), got, want):
                 assert torch.equal(a, b), (name, shift, state is None)
+
+
+@pytest.mark.parametrize("H,N,bq", [(4, 4617, 64), (12, 32760, 128), (40, 8000, 64)])
+def test_bias_gradient_is_summed_without_long_chains(H, N, bq):
+    """db = sum of dout over every token, in fp32.  An addition rounds its result by a relative variance of about
+    0.18 u^2 (u = 2^-24, mantissas spread evenly over a binade); of sums of random signs a chain of m equal additions
+    then costs m / 2 of those, a pairwise sum 1 + 1/2 + 1/4 + ...  The order asked for: a workgroup's query blocks one
+    after the other (256 workgroups; a block's own tokens add up all but exactly), its partials by 16 threads in four
+    chains of four that are joined pairwise, the 16 pairwise.  Root mean square over four draws, a tenth allowed."""
+    squares = []
+    for seed in range(4):
+        gen = torch.Generator(device="cuda").manual_seed(seed)
+        x = [torch.randn((1, H, N, 128), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(4)]
+        db = sla.sla_attention_bwd(*x, bq, 64, 0.05, 0.3, want_db=True)[4].double()
+        ref = x[3].double().sum((0, 1, 2))
+        squares.append(float(((db - ref).norm() / ref.norm()) ** 2))
+    err = np.mean(squares) ** 0.5
+    blocks = H * -(-N // bq) / 256
+    bound = 1.1 * 2.0 ** -24 * (0.18 * (blocks / 2 + 4 / 2 + 1.5 + 1.875)) ** 0.5
+    print("db %d heads x %d: %.2e (bound %.2e)" % (H, N, err, bound))
+    assert err <= bound
