@@ -319,3 +319,68 @@ def test_bias_gradient_is_summed_without_long_chains(H, N, bq):
     bound = 1.1 * 2.0 ** -24 * (0.18 * (blocks / 2 + 4 / 2 + 1.5 + 1.875)) ** 0.5
     print("db %d heads x %d: %.2e (bound %.2e)" % (H, N, err, bound))
     assert err <= bound
+
+
+def _token_major(t):
+    return t.permute(0, 2, 1, 3).contiguous().permute(0, 2, 1, 3)
+
+
+@pytest.mark.parametrize("bq", [128, 64])
+def test_training_step_of_many_heads_on_token_major_tensors_gives_the_same_bits(bq):
+    """Enough query blocks for two tiles of 32 queries per wavefront, on [B,N,H,d] memory: the statistics and dQ kernels'
+    instances for strided tensors against those for contiguous ones (which test_backward_of_many_heads checks against
+    the oracle), from the saved state and without it, on a ragged sequence."""
+    cfg = synth.custom_config(1, 64, (5, 10, 20), block_q=bq, topk_ratio=0.25, marginal_ratio=0.5, use_proj=True, cfg_id=311)
+    q, k, v = (t.cuda() for t in synth.make_qkv(cfg))
+    dout, W = synth.make_qkv(cfg, seed=7)[2].cuda(), synth.make_proj(cfg).cuda()
+    out, saved = sla.sla_attention_fwd_train(q, k, v, bq, 64, 0.25, 0.5, proj_w=W)
+    tm = [_token_major(t) for t in (q, k, v, dout)]
+    grads = [torch.full_like(t, 7.0) for t in tm[:3]]
+    assert not grads[0].is_contiguous()
+    for state in (saved, None):
+        kw = dict(proj_w=W, want_dw=True, want_db=True, saved=state)
+        ref = sla.sla_attention_bwd(q, k, v, dout, bq, 64, 0.25, 0.5, **kw)
+        dw, db = sla.sla_attention_bwd_strided(*tm, *grads, bq, 64, 0.25, 0.5, **kw)
+        for name, got, want in zip(("dQ", "dK", "dV", "dW", "db"), (*grads, dw, db), ref):
+            assert torch.equal(got, want), (name, state is None)
+
+
+@pytest.mark.parametrize("grid,bq,H", [((1, 5, 5), 64, 1024), ((1, 5, 5), 128, 512), ((1, 9, 9), 64, 512), ((1, 9, 9), 128, 512)])
+def test_backward_of_many_short_sequences(grid, bq, H):
+    """One or two key blocks, the last one ragged (25 keys; 17), two query tiles per wavefront: the copy rings at their
+    shortest, with missing keys in the first block of the walk.  First and last head against the oracle, in both layouts."""
+    cfg = synth.custom_config(1, H, grid, block_q=bq, topk_ratio=0.5, marginal_ratio=0.5, use_proj=False, cfg_id=312)
+    q, k, v = synth.make_qkv(cfg)
+    dout = synth.make_qkv(cfg, seed=7)[2]
+    dev = [t.cuda() for t in (q, k, v, dout)]
+    mask = sla.sla_classify_blocks(dev[0], dev[1], bq, 64, 0.5, 0.5, want_scores=False)[0].cpu().numpy()
+    got = sla.sla_attention_bwd(*dev, bq, 64, 0.5, 0.5)[:3]
+    for h in (0, H - 1):
+        r = bo.sla_backward_head(*(synth.as_f64(t[0, h]) for t in (q, k, v, dout)), mask[0, h], bq, 64)
+        for name, g in zip(("dQ", "dK", "dV"), got):
+            _compare("%s head %d" % (name, h), g[0, h].float().cpu().numpy(), r[name])
+    grads = [torch.full_like(_token_major(t), 7.0) for t in dev[:3]]
+    sla.sla_attention_bwd_strided(*(_token_major(t) for t in dev), *grads, bq, 64, 0.5, 0.5)
+    assert all(torch.equal(a, b) for a, b in zip(grads, got))
+
+
+@pytest.mark.parametrize("token_bytes", [(1 << 26) - 16, 1 << 26])
+def test_backward_at_token_strides_the_offsets_just_reach_and_no_longer_reach(token_bytes):
+    """q, k, v and dout as columns of one buffer whose rows lie 64 MiB apart: the largest stride at which a lane's offset
+    into a tile fits 32 bits, and the next one, which takes addresses per lane.  The contiguous call's bits, for one and
+    two query tiles per wavefront (the second: 512 heads, 97 tokens in two key blocks)."""
+    N, token = 97, token_bytes // 2
+    buf = torch.empty(N * token, dtype=torch.bfloat16, device="cuda")      # (6 GB, of which 97 rows of 0.5 MB are used)
+    for H, bq in ((2, 64), (512, 128), (512, 64)):
+        cfg = synth.custom_config(1, H, (1, 1, N), block_q=bq, topk_ratio=0.5, marginal_ratio=0.5, use_proj=False, cfg_id=313)
+        dev = [t.cuda() for t in (*synth.make_qkv(cfg), synth.make_qkv(cfg, seed=7)[2])]
+        far = []
+        for i, t in enumerate(dev):
+            view = buf.as_strided((1, H, N, 128), (N * token, 128, token, 1), i * H * 128)
+            view.copy_(t)
+            far.append(view)
+        want = sla.sla_attention_bwd(*dev, bq, 64, 0.5, 0.5)[:3]
+        grads = [torch.full_like(t, 7.0) for t in dev[:3]]
+        sla.sla_attention_bwd_strided(*far, *grads, bq, 64, 0.5, 0.5)
+        for name, a, b in zip(("dQ", "dK", "dV"), grads, want):
+            assert torch.equal(a, b), (name, H, bq)
