@@ -364,11 +364,15 @@ __global__ void __launch_bounds__(64 * KS, 2) w8a8_gemm_splitk_kernel(
     int RTx, int RBx, int RTw, int RBw, int MT, int NT) {
   constexpr int PITCH = 36;  // floats per staged row of 32 outputs (16-byte rows, skewed banks)
   __shared__ __attribute__((aligned(16))) float part[KS][32 * RT][PITCH];
-  // XCD x takes a contiguous eighth of the tiles, token tiles fastest: a weight tile is fetched into one L2.
+  // XCD x takes a contiguous eighth of the tiles, along the smaller operand fastest: of the larger one a tile is then
+  // fetched into one L2 only (always along the tokens: 30000 x 8960 -> 256 156 us, now 115; 10000 x 256 -> 1536 17.6, now
+  // 15.5; in large tiles they were 121 and 16.5 before there was a choice).
   const int per = (MT * NT + 7) >> 3, xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
   const int idx = __builtin_amdgcn_readfirstlane(xcd * per + slot);
   if ((int)(blockIdx.x >> 3) >= per || idx >= MT * NT) return;
-  const int nt = __builtin_amdgcn_readfirstlane(idx / MT), mt = idx - nt * MT;
+  const bool tokens_fastest = M <= N;
+  const int major = __builtin_amdgcn_readfirstlane(idx / (tokens_fastest ? MT : NT)), minor = idx - major * (tokens_fastest ? MT : NT);
+  const int nt = tokens_fastest ? major : minor, mt = tokens_fastest ? minor : major;
   const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6), l32 = lane & 31, hf = lane >> 5;
   const int KB = K / QB;
   const int kb0 = KB * w / KS, kb1 = KB * (w + 1) / KS;  // this wavefront's feature blocks (none: an empty run)
@@ -509,10 +513,10 @@ void launch_w8a8_gemm(const int8_t* x8, const float* sx, int MP, const int8_t* w
                       const void* bias, void* y, int M, int N, int K, hipStream_t stream) {
   const int MT = MP / W8_WG_M, NT = N / W8_WG_N, KB = K / QB;
   // Large tiles once every compute unit has one (256 of them), small split tiles below that.  Measured around the
-  // line, large / small in us: 5120 -> 5120 at 1536 tokens (240 tiles) 67.1 / 64.6, at 2048 (320) 79.9 / 85.2;
-  // 1536 -> 1536 at 4096 tokens (192) 22.6 / 20.0, at 8192 (384) 30.6 / 43.9.  A contraction of one or two blocks
+  // line, large / small in us: 5120 -> 5120 at 1536 tokens (240 tiles) 64.3 / 61.3, at 2048 (320) 74.9 / 81.5;
+  // 1536 -> 1536 at 4096 tokens (192) 24.0 / 18.5, at 8192 (384) 30.6 / 33.4.  A contraction of one or two blocks
   // leaves the large kernel's pipeline empty: there the line lies higher (256 -> 5120 at 4096 tokens, 640 tiles,
-  // 21.5 / 17.2; at 16384 tokens, 2560 tiles, 56.5 / 80.9).
+  // 22.9 / 19.5; at 16384 tokens, 2560 tiles, 64.4 / 63.5).
   if (MT * NT < 256 || (KB <= 2 && MT * NT <= 640)) {
     // Of the small variants the one with the most work per wavefront that still brings at least 1024 wavefronts,
     // one per SIMD (5120 -> 5120 in us, the large kernel last: 1 token 6.0 | 67.6, 64: 8.5 | 68.2, 256: 16.1 | 69.3,

@@ -219,3 +219,23 @@ def test_split_contraction_is_no_less_precise_than_one_walk(M, K, N):
     missed, allowed = int((y != rounded).sum()), int((walk.to(torch.bfloat16) != rounded).sum())
     print("w8a8 %d x %d -> %d: %d outputs not the rounded exact sum, one walk %d" % (M, K, N, missed, allowed))
     assert missed <= 1.02 * allowed + 50
+
+
+@pytest.mark.parametrize("M,K,N", [
+    (200, 640, 128), (129, 256, 128),         # one column of output tiles; more tokens than outputs by one
+    (2000, 384, 256), (5000, 1280, 384),      # several, not split and split two ways, ragged last tokens
+    (257, 128, 256), (256, 128, 256),         # one more token than outputs; as many
+])
+def test_small_tiles_of_more_tokens_than_outputs(M, K, N):
+    """The small tiles are dealt to the XCDs along the smaller operand: every tile is still there, once, against the
+    oracle on the same codes with the tolerance of the other product tests."""
+    x, w, b = synth.make_linear_inputs(M, K, N, seed=8)
+    wq = sla.w8a8_quantize_weight(w.cuda())
+    ws = sla.w8a8_quantize_act(x.cuda())
+    guard = torch.full((M + 64, N), 7.0, dtype=torch.bfloat16, device="cuda")   # rows past M must stay as they are
+    y = sla.w8a8_gemm_fwd(ws, wq, M, N, K, bias=b.cuda(), out=guard[:M]).float().cpu().numpy()
+    assert (guard[M:] == 7.0).all()
+    xc, xs = (t.cpu().numpy().astype(np.float64) for t in sla.w8a8_debug_unpack(ws, False, M, K))
+    wc, wsc = (t.cpu().numpy().astype(np.float64) for t in sla.w8a8_debug_unpack(wq, True, N, K))
+    ref = wo.linear_from_codes(xc, xs, wc, wsc, synth.as_f64(b))
+    assert np.all(np.abs(y - ref) <= product_tolerance(ref, xs, wsc, K)), np.abs(y - ref).max()
