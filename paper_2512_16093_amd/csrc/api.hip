@@ -39,7 +39,7 @@ void* static_scratch_ptr() {
 
 // Scratch of the block classification alone: block means, the statistics pass's by-products, scores.
 struct ClassifyScratch {
-  size_t qbar, kbar, dq, amax_v, scores, total;
+  size_t qbar, kbar, dq, scores, total;
 };
 ClassifyScratch make_classify_scratch(const Problem& p, bool own_scores) {
   ClassifyScratch c;
@@ -48,7 +48,7 @@ ClassifyScratch make_classify_scratch(const Problem& p, bool own_scores) {
   c.qbar = take((size_t)p.BH * p.Tq * D * 4);
   c.kbar = take((size_t)p.BH * p.Tk * D * 4);
   c.dq = take((size_t)p.BH * p.Tq * 4);
-  c.amax_v = take((size_t)p.BH * D * 4);
+  take((size_t)p.BH * D * 4);   // (unused; part of the size by which a problem is too large for the static scratch)
   c.scores = take(own_scores ? (size_t)p.BH * p.Tq * p.Tk * 4 : 0);
   c.total = o;
   return c;
@@ -652,8 +652,7 @@ int sla_attention_bwd_strided(const void* q, const void* k, const void* v, const
                      saved_header(p), (const float*)((const unsigned char*)saved + V.lse2), at<float>(ws, X.lse2),
                      at<float>(ws, X.delta), s);
   } else {
-    if (launch_bwd_stats(p, q, k, v, dout, at<int32_t>(ws, W.crit), at<float>(ws, X.lse2), at<float>(ws, X.delta), s) != 0)
-      return SLA_ERR_HIP;
+    launch_bwd_stats(p, q, k, v, dout, at<int32_t>(ws, W.crit), at<float>(ws, X.lse2), at<float>(ws, X.delta), s);
   }
   mark(s, rec, 2);
   // (with no marginal block there is no linear term: the projection and the bias receive no gradient)
@@ -676,9 +675,8 @@ int sla_attention_bwd_strided(const void* q, const void* k, const void* v, const
     launch_lin_accumulate(pt, at<uint32_t>(ws, X.mbits_t), at<bf16_t>(ws, X.dHZ), at<bf16_t>(ws, W.hz), s);
   }
   mark(s, rec, 3);
-  if (launch_bwd_dq(p, q, dout, k, v, at<int32_t>(ws, W.crit), lse2, at<float>(ws, X.delta),
-                    lin ? at<float>(ws, X.dql) : nullptr, dq, s) != 0)
-    return SLA_ERR_HIP;
+  launch_bwd_dq(p, q, dout, k, v, at<int32_t>(ws, W.crit), lse2, at<float>(ws, X.delta),
+                lin ? at<float>(ws, X.dql) : nullptr, dq, s);
   mark(s, rec, 4);
   if (launch_bwd_dkv(p, q, dout, k, v, at<int8_t>(ws, W.mask), lse2, at<float>(ws, X.delta),
                      lin ? at<bf16_t>(ws, W.hz) : nullptr, phi_kind, dk, dv, s) != 0)

@@ -277,7 +277,7 @@ void launch_sparse_fwd(const void* q, const int8_t* q8, const Problem& p, const 
 // Backward pass (k_bwd.hip, k_bwd_lin.hip; the transposed bit matrix lives with lin_accumulate).
 size_t marginal_bits_t_bytes(const Problem& p);
 void launch_marginal_bits_t(const Problem& p, const int8_t* mask, uint32_t* mbits_t, hipStream_t stream);
-int launch_bwd_stats(const Problem& p, const void* q, const void* k, const void* v, const void* dout,
+void launch_bwd_stats(const Problem& p, const void* q, const void* k, const void* v, const void* dout,
                      const int32_t* crit, float* lse2, float* delta, hipStream_t stream);
 // qk_scales: nullptr, or {delta_Q [BH,Tq], delta_K [BH,Tk]} when q and k hold INT8 codes (q_lin: the
 // original Q for the linear term's feature map)
@@ -293,7 +293,7 @@ struct SavedHeader { int magic, B, H, N, block_q, n_c, pad0, pad1; };
 void launch_write_saved_header(const SavedHeader& h, SavedHeader* dst, hipStream_t stream);
 void launch_bwd_delta(const Problem& p, const void* dout, const void* os, const SavedHeader* hdr, const SavedHeader& want,
                       const float* lse_saved, float* lse2, float* delta, hipStream_t stream);
-int launch_bwd_dq(const Problem& p, const void* q, const void* dout, const void* k, const void* v, const int32_t* crit,
+void launch_bwd_dq(const Problem& p, const void* q, const void* dout, const void* k, const void* v, const int32_t* crit,
                    const float* lse2, const float* delta, const float* dq_lin, void* dq, hipStream_t stream);
 int launch_bwd_dkv(const Problem& p, const void* q, const void* dout, const void* k, const void* v, const int8_t* mask,
                     const float* lse2, const float* delta, const bf16_t* G, int phi_kind, void* dk, void* dv, hipStream_t stream);

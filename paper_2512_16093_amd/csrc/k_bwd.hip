@@ -20,7 +20,6 @@
 // product that contracts over the tile's tokens reads the same tile with the transposing LDS read
 // of gfx950 (ds_read_b64_tr_b16), so no transposed copy of any tensor is ever made.
 #include <initializer_list>
-#include <type_traits>
 
 #include "common.h"
 
@@ -112,14 +111,6 @@ __device__ __forceinline__ bool xcd_block(int T, int& block, int& bh) {
   bh = slot / per_xcd;
   block = xcd * per_xcd + (slot - bh * per_xcd);
   return block < T;
-}
-
-// Scores of one key tile, transposed: lane = query, registers = keys.
-__device__ __forceinline__ v16f score_tile(const unsigned char* ktile, const uint4 (&qf)[8], int l32, int hf) {
-  v16f s = v16f{};
-#pragma unroll
-  for (int ks = 0; ks < 8; ++ks) s = mfma_bf16(n_op(ktile, l32, hf, ks), qf[ks], s);
-  return s;
 }
 
 // ---- asynchronous copies of 32-row tiles (32 x 256 bytes) global -> LDS, without registers in between
@@ -1358,9 +1349,9 @@ static BwdDims bwd_dims(const Problem& p) {
   return BwdDims{p.N, p.Tq, p.Tk, p.n_c, p.Tq * (p.block_q / 32), p.H, p.lq, p.lk, p.lv, p.ld, p.ldq, p.ldk, p.ldv, p.lo};
 }
 
-// The launchers below return 0, or -1 when the kernel's LDS allowance could not be set (then nothing is
-// launched; the result of the attribute call is cached, the failure is reported on every call).
-int launch_bwd_stats(const Problem& p, const void* q, const void* k, const void* v, const void* dout,
+// The launchers below that return an int return 0, or -1 when the kernel's LDS allowance could not be set (then nothing
+// is launched; the result of the attribute call is cached, the failure is reported on every call).
+void launch_bwd_stats(const Problem& p, const void* q, const void* k, const void* v, const void* dout,
                      const int32_t* crit, float* lse2, float* delta, hipStream_t stream) {
   const unsigned grid = (unsigned)(8 * ((p.Tq + 7) / 8) * p.BH);
   const bool st = !contiguous(p, {&p.lq, &p.lk, &p.lv, &p.ld});
@@ -1377,7 +1368,6 @@ int launch_bwd_stats(const Problem& p, const void* q, const void* k, const void*
   }
 #undef SLA_STATS_ST
 #undef SLA_STATS
-  return 0;
 }
 
 // The unquantised forward pass; with `codes`, the same on
@@ -1466,7 +1456,7 @@ void launch_bwd_delta(const Problem& p, const void* dout, const void* os, const 
                                                                      rows_padded, p.BH, p.H, p.ld);
 }
 
-int launch_bwd_dq(const Problem& p, const void* q, const void* dout, const void* k, const void* v, const int32_t* crit,
+void launch_bwd_dq(const Problem& p, const void* q, const void* dout, const void* k, const void* v, const int32_t* crit,
                   const float* lse2, const float* delta, const float* dq_lin, void* dq, hipStream_t stream) {
   const unsigned grid = (unsigned)(8 * ((p.Tq + 7) / 8) * p.BH);
   const bool st = !contiguous(p, {&p.lq, &p.lk, &p.lv, &p.ld, &p.ldq});
@@ -1483,7 +1473,6 @@ int launch_bwd_dq(const Problem& p, const void* q, const void* dout, const void*
   }
 #undef SLA_DQ_ST
 #undef SLA_DQ
-  return 0;
 }
 
 template <int PHI, bool ST>

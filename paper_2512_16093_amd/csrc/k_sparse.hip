@@ -227,7 +227,9 @@ __device__ __forceinline__ void stage_barrier() {
 // 40 heads x 75600 tokens, top 15 %, whole call: 18.2 ms against 14.4 ms.)
 // SHARED (query blocks of 64, NW = 4, every key block critical): all lists are the same, so a workgroup serves two
 // adjacent query blocks, wavefronts 0-1 the first and 2-3 the second, and fetches every record once for both
-// (12 heads x 32760 tokens, whole call: 3.43 ms against 3.90 ms one by one; 3.57 ms as merged lists).
+// (12 heads x 32760 tokens, whole call: 3.43 ms against 3.90 ms one by one; 3.57 ms as merged lists).  Lists of 94 % of
+// the blocks and more, but not all of them, are the one place where the merged lists were faster: 4 x 32760 tokens at
+// 97 % 1.20 ms against 1.26 ms (at 90 % 1.27 against 1.23, at 75 % 1.18 against 1.06).
 template <int NW, bool SHARED>
 __global__ void __launch_bounds__(NW * 64, 2) sparse_fwd_kernel(
     const bf16_t* __restrict__ q_, const int8_t* __restrict__ q8_, const int32_t* __restrict__ crit_, const int8_t* __restrict__ k8_,
