@@ -214,7 +214,7 @@ __device__ __forceinline__ void copies_barrier() {
 // A wavefront owns QT tiles of 32 queries; with two an operand read from LDS serves two matrix products (with 32
 // queries each the reads alone asked for all the LDS delivers).  K and V tiles of 32 keys travel in a ring of two each,
 // copied one and a half steps ahead, 32 KB per workgroup, two wavefronts per SIMD; the exponentials are issued between
-// the products of V.  Bound by power: 1.6 GHz with the matrix pipe 60 % busy.  Before (O formed from P in bf16, 32
+// the products of V.  Bound by power: 1.55 GHz with the matrix pipe 61 % busy.  Before (O formed from P in bf16, 32
 // queries per wavefront, copies through registers): 40 heads x 75600 tokens 13.4 -> 12.3 ms, 12 x 32760 with query
 // blocks of 64 1.19 -> 0.92 ms.
 template <int WAVES, int QT, bool ST>
@@ -606,7 +606,7 @@ __device__ __forceinline__ void score_wait(v16f& x) { asm volatile("s_nop 15\n\t
 // issue, one piece per product, and runs across two tiles: S of tile t + 1 with dS of tile t behind its products, dQ of
 // tile t with exponentials of tile t + 1, dP of tile t + 1 with the rest of them.  Operands are read a section early,
 // and the barrier that publishes a tile stands in the middle of a section, whose products cover the first reads of it.
-// 40 heads x 75600 tokens 16.8 -> 16.1 ms (half the LDS traffic lets the clock rise from 1.78 to 1.87 GHz; the matrix pipe
+// 40 heads x 75600 tokens 16.8 -> 16.1 ms (half the LDS traffic lets the clock rise from 1.70 to 1.88 GHz; the matrix pipe
 // is 56 % busy), query blocks of 64 (12 x 32760) 1.42 -> 1.00 ms; 12 x 32760 at 128 token-major 0.96 -> 0.97 ms.
 template <int WAVES, int QT, bool ST>
 __global__ void __launch_bounds__(WAVES * 64, 1) bwd_dq_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ dout,
@@ -940,8 +940,8 @@ __device__ __forceinline__ void linear_kv_share(const bf16_t* __restrict__ k, co
 // LDS (no registers, no padding: see TileCopy), the scores are formed in ordinary registers and dK, dV, K, V held in the
 // accumulation registers, so a step is its 64 products, 160 vector instructions and 112 LDS reads with no register
 // copies between the two files (there were 77 a step, and the copies through registers took 56 more).  40 heads x
-// 75600 tokens 29.9 -> 25.9 ms, 12 x 32760 token-major 2.18 -> 1.78 ms; 164 GB past L2 = 6.3 TB/s at 2.0 GHz, the matrix
-// pipe 43 % busy: bound by the lone wavefront's waits between the sections and by the stream.
+// 75600 tokens 29.9 -> 25.9 ms, 12 x 32760 token-major 2.18 -> 1.78 ms; 164 GB past L2 = 6.2 TB/s at 1.9 GHz, the matrix
+// pipe 46 % busy: bound by the lone wavefront's waits between the sections and by the stream.
 template <int KB, int TILES, int PHI, bool ST = false>
 __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ dout,
                                                       const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
