@@ -129,16 +129,16 @@ Workspace fwd_workspace(const Problem& p, size_t n_c, size_t n_m, size_t code_te
 }
 
 // What follows the statistics pass: the low-bit operands (mean of K, scale of V) and / or the projection in
-// operand order.  The maxima of V per 128 tokens live in the summaries' buffer, which prep_kv fills later.
+// operand order.  The maxima of V per 128 tokens live in the buffer of the sums HZ, which lin_accumulate fills later.
 FinalizeArgs finalize_args(void* ws, const Workspace& W, const void* proj_w, bool quant, bool wfrag) {
-  return FinalizeArgs{at<float>(ws, W.hz), quant ? at<float>(ws, W.mu_k) : nullptr, at<float>(ws, W.amax_v), at<float>(ws, W.dv),
+  return FinalizeArgs{at<float>(ws, W.HZ), quant ? at<float>(ws, W.mu_k) : nullptr, at<float>(ws, W.amax_v), at<float>(ws, W.dv),
                       (const bf16_t*)proj_w, wfrag ? at<bf16_t>(ws, W.wfrag) : nullptr};
 }
 // Statistics of Q and K (quant: and of V, and with want_q8 the codes of Q).
 void run_pool(const void* q, const void* k, const void* v, const Problem& p, void* ws, const Workspace& W, hipStream_t s,
               bool quant, bool want_q8) {
   launch_pool_stats(q, k, quant ? v : nullptr, p, at<float>(ws, W.qbar), at<float>(ws, W.kbar), at<float>(ws, W.dq),
-                    at<float>(ws, W.hz), want_q8 ? at<int8_t>(ws, W.q8) : nullptr, s);
+                    at<float>(ws, W.HZ), want_q8 ? at<int8_t>(ws, W.q8) : nullptr, s);
 }
 void run_stats(const void* q, const void* k, const void* v, const void* proj_w, const Problem& p, void* ws,
                const Workspace& W, hipStream_t s, bool want_q8 = false) {
@@ -150,6 +150,31 @@ void run_stats(const void* q, const void* k, const void* v, const void* proj_w, 
 void run_scores(const void* proj_w, const Problem& p, void* ws, const Workspace& W, hipStream_t s, bool quant, bool wfrag) {
   const FinalizeArgs fin = finalize_args(ws, W, proj_w, quant, wfrag);
   launch_scores(p, at<float>(ws, W.qbar), at<float>(ws, W.kbar), at<float>(ws, W.scores), &fin, s);
+}
+
+PrepArgs run_prep_args(const void* k, const void* v, const Problem& p, void* ws, const Workspace& W, bool quant, bool lin) {
+  return prep_args(k, v, p, at<float>(ws, W.mu_k), at<float>(ws, W.amax_v), at<bf16_t>(ws, W.wfrag), quant, lin, at<int8_t>(ws, W.k8),
+                   at<uint8_t>(ws, W.v8), at<float>(ws, W.dk), at<bf16_t>(ws, W.hz));
+}
+// The rest of the classification and the per-key-block operands, after the statistics pass: scores (with what is left
+// of the statistics), then selection and prep_kv in one launch -- or, for calls of few blocks, all of it in one.
+// delta: of a backward pass with saved state, if any.
+void run_classify_prep(const void* k, const void* v, const void* proj_w, const Problem& p, int phi_kind, void* ws, const Workspace& W,
+                       hipStream_t s, int rec, bool quant, bool lin, int8_t* mask, const DeltaArgs* delta) {
+  PrepArgs P = run_prep_args(k, v, p, ws, W, quant, lin);
+  if (stats_in_prep(p)) {
+    P.qbar = at<float>(ws, W.qbar); P.kbar = at<float>(ws, W.kbar); P.vmax_part = at<float>(ws, W.HZ);
+    P.groups = (p.N + 127) / 128;
+    P.mu_out = at<float>(ws, W.mu_k); P.amax_out = at<float>(ws, W.amax_v); P.dv_out = at<float>(ws, W.dv);
+    P.proj_w = (const bf16_t*)proj_w;
+    P.w_aligned = proj_w && ((uintptr_t)proj_w & 15) == 0;
+  } else {
+    run_scores(proj_w, p, ws, W, s, quant, lin);
+  }
+  mark(s, rec, 2);
+  const SelectArgs S{at<float>(ws, W.scores), p.BH * p.Tq, p.Tq, p.Tk, p.n_c, p.n_m, mask, at<int32_t>(ws, W.crit), nullptr,
+                     lin ? at<uint32_t>(ws, W.m0) : nullptr};
+  launch_select_prep(S, P, delta, p, phi_kind, s);
 }
 
 // The unquantised forward pass (bf16 products): the launch sequence of sla_attention_fwd with
@@ -164,13 +189,13 @@ int fwd_bf16(const void* q, const void* k, const void* v, void* out, const Probl
   mark(s, rec, 0);
   run_pool(q, k, v, p, ws, W, s, codes16, codes16);
   mark(s, rec, 1);
-  run_scores(proj_w, p, ws, W, s, codes16, lin);
-  launch_select(p, at<float>(ws, W.scores), nullptr, at<int32_t>(ws, W.crit), nullptr,
-                lin ? at<uint32_t>(ws, W.m0) : nullptr, s);
-  mark(s, rec, 2);
-  if (lin || codes16)
-    launch_prep_kv(k, v, p, at<float>(ws, W.mu_k), at<float>(ws, W.amax_v), at<bf16_t>(ws, W.wfrag), phi_kind, codes16, lin,
-                   at<int8_t>(ws, W.k8), at<uint8_t>(ws, W.v8), at<float>(ws, W.dk), at<bf16_t>(ws, W.hz), s);
+  if (lin || codes16) {
+    run_classify_prep(k, v, proj_w, p, phi_kind, ws, W, s, rec, codes16, lin, nullptr, nullptr);
+  } else {
+    run_scores(proj_w, p, ws, W, s, false, false);
+    launch_select(p, at<float>(ws, W.scores), nullptr, at<int32_t>(ws, W.crit), nullptr, nullptr, s);
+    mark(s, rec, 2);
+  }
   if (codes16)
     launch_code_tensors(p, at<int8_t>(ws, W.q8), at<int8_t>(ws, W.k8), at<bf16_t>(ws, W.qc), at<bf16_t>(ws, W.kc), s);
   mark(s, rec, 3);
@@ -194,12 +219,7 @@ void run_prepass(const void* q, const void* k, const void* v, const void* proj_w
   mark(s, rec, 0);
   run_pool(q, k, v, p, ws, W, s, true, true);
   mark(s, rec, 1);
-  run_scores(proj_w, p, ws, W, s, true, lin);
-  launch_select(p, at<float>(ws, W.scores), nullptr, at<int32_t>(ws, W.crit), nullptr,
-                lin ? at<uint32_t>(ws, W.m0) : nullptr, s);
-  mark(s, rec, 2);
-  launch_prep_kv(k, v, p, at<float>(ws, W.mu_k), at<float>(ws, W.amax_v), at<bf16_t>(ws, W.wfrag), phi_kind, true, lin,
-                 at<int8_t>(ws, W.k8), at<uint8_t>(ws, W.v8), at<float>(ws, W.dk), at<bf16_t>(ws, W.hz), s);
+  run_classify_prep(k, v, proj_w, p, phi_kind, ws, W, s, rec, true, lin, nullptr, nullptr);
   mark(s, rec, 3);
   if (lin) launch_lin_accumulate(p, at<uint32_t>(ws, W.m0), at<bf16_t>(ws, W.hz), at<bf16_t>(ws, W.HZ), s);
   mark(s, rec, 4);
@@ -455,8 +475,7 @@ int sla_sparse_attn_fwd(const void* q, const void* k, const void* v, const int32
   hipStream_t s = (hipStream_t)stream;
   void* ws = workspace;
   run_stats(q, k, v, nullptr, p, ws, Wmin, s, true);
-  launch_prep_kv(k, v, p, at<float>(ws, Wmin.mu_k), at<float>(ws, Wmin.amax_v), at<bf16_t>(ws, Wmin.wfrag), 0, true,
-                 false, at<int8_t>(ws, Wmin.k8), at<uint8_t>(ws, Wmin.v8), at<float>(ws, Wmin.dk), nullptr, s);
+  launch_prep_kv(run_prep_args(k, v, p, ws, Wmin, true, false), p, 0, s);
   launch_sparse_fwd(q, at<int8_t>(ws, Wmin.q8), p, crit_idx, n_crit, at<int8_t>(ws, Wmin.k8), at<uint8_t>(ws, Wmin.v8),
                     at<float>(ws, Wmin.dq), at<float>(ws, Wmin.dk), at<float>(ws, Wmin.dv), nullptr, nullptr, 0,
                     false, out_s, true, lse, false, s);
@@ -477,8 +496,7 @@ int sla_linear_attn_fwd(const void* q, const void* k, const void* v, const int8_
   hipStream_t s = (hipStream_t)stream;
   void* ws = workspace;
   run_stats(q, k, v, proj_w, p, ws, W, s, true);
-  launch_prep_kv(k, v, p, at<float>(ws, W.mu_k), at<float>(ws, W.amax_v), at<bf16_t>(ws, W.wfrag), phi_kind, false, true, nullptr,
-                 nullptr, nullptr, at<bf16_t>(ws, W.hz), s);
+  launch_prep_kv(run_prep_args(k, v, p, ws, W, false, true), p, phi_kind, s);
   launch_marginal_bits(p, mask, at<uint32_t>(ws, W.m0), s);
   launch_lin_accumulate(p, at<uint32_t>(ws, W.m0), at<bf16_t>(ws, W.hz), at<bf16_t>(ws, W.HZ), s);
   // the attention kernel with an empty critical list leaves only the linear term
@@ -518,8 +536,7 @@ int sla_debug_quantize_kv(const void* k, const void* v, int B, int H, int N, int
   hipStream_t s = (hipStream_t)stream;
   void* ws = workspace;
   run_stats(k, k, v, nullptr, p, ws, W, s);
-  launch_prep_kv(k, v, p, at<float>(ws, W.mu_k), at<float>(ws, W.amax_v), at<bf16_t>(ws, W.wfrag), 0, true, false,
-                 at<int8_t>(ws, W.k8), at<uint8_t>(ws, W.v8), at<float>(ws, W.dk), nullptr, s);
+  launch_prep_kv(run_prep_args(k, v, p, ws, W, true, false), p, 0, s);
   launch_unfragment_kv(p, at<int8_t>(ws, W.k8), at<uint8_t>(ws, W.v8), k_codes, v_codes, s);
   const size_t bhd = (size_t)p.BH * D * 4;
   if (k_scale && hipMemcpyAsync(k_scale, at<float>(ws, W.dk), (size_t)p.BH * p.Tk * 4, hipMemcpyDeviceToDevice, s) != hipSuccess) return SLA_ERR_HIP;
@@ -640,28 +657,30 @@ int sla_attention_bwd_strided(const void* q, const void* k, const void* v, const
   const int rec = (g_prof.ev && g_prof.used < g_prof.capacity) ? g_prof.used++ : -1;
   mark(s, rec, 0);
 
-  // the block mask, exactly as the forward pass finds it
-  run_pool(q, k, v, p, ws, W, s, false, false);
-  run_scores(nullptr, p, ws, W, s, false, lin);   // (no projection folded into the summaries here)
-  launch_select(p, at<float>(ws, W.scores), at<int8_t>(ws, W.mask), at<int32_t>(ws, W.crit), nullptr,
-                lin ? at<uint32_t>(ws, W.m0) : nullptr, s);
-  mark(s, rec, 1);
+  // the block mask, exactly as the forward pass finds it (and, with marginal blocks, the unprojected summaries of the
+  // keys); with the forward pass's statistics at hand, only delta = dO . O^s is left of them
   const float* lse2 = at<float>(ws, X.lse2);
-  if (saved) {  // the forward pass's statistics: only delta = dO . O^s is left to do
-    launch_bwd_delta(p, dout, (const unsigned char*)saved + V.os, (const SavedHeader*)((const unsigned char*)saved + V.hdr),
-                     saved_header(p), (const float*)((const unsigned char*)saved + V.lse2), at<float>(ws, X.lse2),
-                     at<float>(ws, X.delta), s);
+  DeltaArgs da{};
+  if (saved)
+    da = DeltaArgs{(const bf16_t*)dout, (const bf16_t*)((const unsigned char*)saved + V.os), (const SavedHeader*)((const unsigned char*)saved + V.hdr),
+                   saved_header(p), (const float*)((const unsigned char*)saved + V.lse2), at<float>(ws, X.lse2), at<float>(ws, X.delta),
+                   p.N, p.Tq * p.block_q, p.BH, p.H, p.ld};
+  run_pool(q, k, v, p, ws, W, s, false, false);
+  if (lin) {
+    run_classify_prep(k, v, nullptr, p, phi_kind, ws, W, s, -1, false, true, at<int8_t>(ws, W.mask), saved ? &da : nullptr);
   } else {
-    launch_bwd_stats(p, q, k, v, dout, at<int32_t>(ws, W.crit), at<float>(ws, X.lse2), at<float>(ws, X.delta), s);
+    run_scores(nullptr, p, ws, W, s, false, false);
+    launch_select(p, at<float>(ws, W.scores), at<int8_t>(ws, W.mask), at<int32_t>(ws, W.crit), nullptr, nullptr, s);
+    if (saved) launch_bwd_delta(da, p, s);
   }
+  mark(s, rec, 1);
+  if (!saved) launch_bwd_stats(p, q, k, v, dout, at<int32_t>(ws, W.crit), at<float>(ws, X.lse2), at<float>(ws, X.delta), s);
   mark(s, rec, 2);
   // (with no marginal block there is no linear term: the projection and the bias receive no gradient)
   if (dproj_w && !lin) launch_zero_u32((uint32_t*)dproj_w, (size_t)D * D, s);
   if (dproj_b && !lin) launch_zero_u32((uint32_t*)dproj_b, (size_t)D, s);
   if (lin) {
     // H_i, Z_i of the forward pass (unprojected), then the linear branch's gradients
-    launch_prep_kv(k, v, p, at<float>(ws, W.mu_k), at<float>(ws, W.amax_v), at<bf16_t>(ws, W.wfrag), phi_kind, false, true,
-                   at<int8_t>(ws, W.k8), at<uint8_t>(ws, W.v8), at<float>(ws, W.dk), at<bf16_t>(ws, W.hz), s);
     launch_lin_accumulate(p, at<uint32_t>(ws, W.m0), at<bf16_t>(ws, W.hz), at<bf16_t>(ws, W.HZ), s);
     if (launch_bwd_lin_q(p, q, dout, at<bf16_t>(ws, W.HZ), (const bf16_t*)proj_w, phi_kind, at<float>(ws, X.dql),
                          at<bf16_t>(ws, X.dHZ), dproj_w, dproj_b, at<float>(ws, X.dw_part), s) != 0)

@@ -263,9 +263,39 @@ struct FinalizeArgs {
 void launch_scores(const Problem& p, const float* qbar, const float* kbar, float* scores, const FinalizeArgs* fin, hipStream_t stream);
 void launch_select(const Problem& p, const float* scores, int8_t* mask, int32_t* crit, int32_t* marg,
                    uint32_t* mbits, hipStream_t stream);
-void launch_prep_kv(const void* k, const void* v, const Problem& p, const float* mu_k, const float* amax_v,
-                    const bf16_t* wfrag, int phi_kind, bool want_quant, bool want_linear, int8_t* k8,
-                    uint8_t* v8, float* dk, bf16_t* hz, hipStream_t stream);
+// What prep_kv reads and writes per key block.  The second part is for calls that stats_in_prep() names: there the
+// launch joins the statistics and lays out the projection by itself (no launch_scores before it).
+struct PrepArgs {
+  const bf16_t *k, *v;
+  int N, Tk, H;
+  Layout lk, lv;
+  const float *mu_k, *amax_v;     // [BH, D] (quant)
+  const bf16_t* wfrag;            // the projection in operand order (linear)
+  int want_quant, want_linear;
+  int8_t* k8;
+  uint8_t* v8;
+  float* dk;
+  bf16_t* hz;
+  const float *qbar, *kbar, *vmax_part;
+  int groups, w_aligned;          // groups of 128 tokens; proj_w given and 16-byte aligned
+  float *mu_out, *amax_out, *dv_out;
+  const bf16_t* proj_w;
+};
+PrepArgs prep_args(const void* k, const void* v, const Problem& p, const float* mu_k, const float* amax_v, const bf16_t* wfrag,
+                   bool want_quant, bool want_linear, int8_t* k8, uint8_t* v8, float* dk, bf16_t* hz);
+void launch_prep_kv(const PrepArgs& P, const Problem& p, int phi_kind, hipStream_t stream);
+// The selection of one row's blocks; every output may be nullptr.
+struct SelectArgs {
+  const float* scores;            // fp32 [rows, Tk] (unused where stats_in_prep())
+  int rows, Tq, Tk, n_c, n_m;
+  int8_t* mask;
+  int32_t *crit, *marg;
+  uint32_t* mbits;
+};
+struct DeltaArgs;
+bool stats_in_prep(const Problem& p);
+// launch_select, launch_bwd_delta (delta given) and launch_prep_kv in one launch.
+void launch_select_prep(const SelectArgs& S, const PrepArgs& P, const DeltaArgs* delta, const Problem& p, int phi_kind, hipStream_t stream);
 void launch_marginal_bits(const Problem& p, const int8_t* mask, uint32_t* mbits, hipStream_t stream);
 void launch_lin_accumulate(const Problem& p, const uint32_t* mbits, const bf16_t* hz, bf16_t* HZ,
                            hipStream_t stream);
@@ -291,8 +321,18 @@ void launch_code_tensors(const Problem& p, const int8_t* q8, const int8_t* k8, b
 constexpr int SAVED_MAGIC = 0x534C4153;
 struct SavedHeader { int magic, B, H, N, block_q, n_c, pad0, pad1; };
 void launch_write_saved_header(const SavedHeader& h, SavedHeader* dst, hipStream_t stream);
-void launch_bwd_delta(const Problem& p, const void* dout, const void* os, const SavedHeader* hdr, const SavedHeader& want,
-                      const float* lse_saved, float* lse2, float* delta, hipStream_t stream);
+// delta = dO . O^s and the log-sum-exp from a saved state (see delta.h)
+struct DeltaArgs {
+  const bf16_t *dout, *os;
+  const SavedHeader* hdr;
+  SavedHeader want;
+  const float* lse_saved;
+  float *lse2, *delta;
+  int N, rows_padded, BH, H;
+  Layout ld;
+};
+inline int delta_blocks(const Problem& p) { return (int)(((long long)p.BH * p.Tq * p.block_q + 31) / 32); }
+void launch_bwd_delta(const DeltaArgs& X, const Problem& p, hipStream_t stream);
 void launch_bwd_dq(const Problem& p, const void* q, const void* dout, const void* k, const void* v, const int32_t* crit,
                    const float* lse2, const float* delta, const float* dq_lin, void* dq, hipStream_t stream);
 int launch_bwd_dkv(const Problem& p, const void* q, const void* dout, const void* k, const void* v, const int8_t* mask,

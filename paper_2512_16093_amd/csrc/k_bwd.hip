@@ -22,6 +22,7 @@
 #include <initializer_list>
 
 #include "common.h"
+#include "delta.h"
 
 namespace sla {
 
@@ -1413,47 +1414,10 @@ void launch_write_saved_header(const SavedHeader& h, SavedHeader* dst, hipStream
   write_saved_header_kernel<<<1, 64, 0, stream>>>(h, (int*)dst);
 }
 
-// delta[bh][row] = dO[row] . O^s[row] from a saved O^s (rows beyond N: 0); one wavefront per 8 rows.
-// The saved state's header must name this problem (shape, query block size, critical blocks per row): a
-// buffer that no training forward pass of the same problem filled gives delta = lse = NaN, and with them NaN in
-// every gradient, instead of plausible wrong numbers (the host cannot look without synchronising).
-__global__ void __launch_bounds__(256) bwd_delta_kernel(const bf16_t* __restrict__ dout, const bf16_t* __restrict__ os,
-                                                        const SavedHeader* __restrict__ hdr, SavedHeader want,
-                                                        const float* __restrict__ lse_saved, float* __restrict__ lse2,
-                                                        float* __restrict__ delta, int N, int rows_padded, int BH, int H,
-                                                        Layout ld) {
-  const long long gr = (long long)blockIdx.x * 32 + (threadIdx.x >> 3);  // padded row index over all heads
-  if (gr >= (long long)BH * rows_padded) return;
-  const SavedHeader got = *hdr;
-  const bool mine = got.magic == want.magic && got.B == want.B && got.H == want.H && got.N == want.N &&
-                    got.block_q == want.block_q && got.n_c == want.n_c;
-  const int bh = (int)(gr / rows_padded), row = (int)(gr - (long long)bh * rows_padded), part = threadIdx.x & 7;
-  float s = 0.f;
-  if (row < N) {
-    const size_t off = ((size_t)bh * N + row) * D + 16 * part;   // (O^s: the library's own tensor)
-    const bf16_t* drow = slice_of(dout, ld, bh, H) + (long long)row * ld.sn + 16 * part;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const uint4 a = *(const uint4*)(drow + 8 * h), b = *(const uint4*)(os + off + 8 * h);
-      s += bf16_lo(a.x) * bf16_lo(b.x) + bf16_hi(a.x) * bf16_hi(b.x) + bf16_lo(a.y) * bf16_lo(b.y) + bf16_hi(a.y) * bf16_hi(b.y) +
-           bf16_lo(a.z) * bf16_lo(b.z) + bf16_hi(a.z) * bf16_hi(b.z) + bf16_lo(a.w) * bf16_lo(b.w) + bf16_hi(a.w) * bf16_hi(b.w);
-    }
-  }
-  s += __shfl_xor(s, 1);
-  s += __shfl_xor(s, 2);
-  s += __shfl_xor(s, 4);
-  if (part == 0) {  // (the log-sum-exp goes to the workspace copy the other kernels read: poisoned alike)
-    delta[gr] = mine ? s : __builtin_nanf("");
-    lse2[gr] = mine ? lse_saved[gr] : __builtin_nanf("");
-  }
-}
+__global__ void __launch_bounds__(256) bwd_delta_kernel(const DeltaArgs X) { delta_block(X, blockIdx.x); }
 
-void launch_bwd_delta(const Problem& p, const void* dout, const void* os, const SavedHeader* hdr, const SavedHeader& want,
-                      const float* lse_saved, float* lse2, float* delta, hipStream_t stream) {
-  const int rows_padded = p.Tq * p.block_q;
-  const long long total = (long long)p.BH * rows_padded;
-  bwd_delta_kernel<<<(unsigned)((total + 31) / 32), 256, 0, stream>>>((const bf16_t*)dout, (const bf16_t*)os, hdr, want, lse_saved, lse2, delta, p.N,
-                                                                     rows_padded, p.BH, p.H, p.ld);
+void launch_bwd_delta(const DeltaArgs& X, const Problem& p, hipStream_t stream) {
+  bwd_delta_kernel<<<(unsigned)delta_blocks(p), 256, 0, stream>>>(X);
 }
 
 void launch_bwd_dq(const Problem& p, const void* q, const void* dout, const void* k, const void* v, const int32_t* crit,

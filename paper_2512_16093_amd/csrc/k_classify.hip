@@ -7,146 +7,141 @@
 // this library's stated reading, see sla.h).  The same pass over Q, K, V also
 // produces what the low-bit branch needs later: the per-query-block INT8 scale,
 // the channel mean of K (K-smoothing) and the per-channel max |V| (FP8 scale).
-#include "common.h"
+#include "classify.h"
 
 namespace sla {
 
 // ---------------------------------------------------------------------------
-// pool_stats: one workgroup per (b,h, 128-token group); 256 threads; thread
+// pool_stats: one workgroup per (tensor, b,h, 128-token group); 256 threads; thread
 // (rg = t/16, cg = t%16) reads 8 channels of rows rg + 16 r, r = 0..7.
-// HBM-bound: reads Q, K, V exactly once (6 N d bytes per slice); WANT_V = false (no low-bit branch behind it:
-// the 16-bit forward, the backward pass, the classification alone) leaves V out, a third of the reads.
+// HBM-bound: reads Q, K, V exactly once (6 N d bytes per slice), Q's workgroups first, then K's, then V's (which the
+// 16-bit forward, the backward pass and the classification alone leave out: parts = 2).  A workgroup per tensor and
+// not one for all three: a third of the loads, shared memory and reduction steps one behind another, which is what the
+// smallest calls wait for, and three times the workgroups in flight (2 x 1024 tokens 8.2 -> 5.8 us, 24 x 4617 24 -> 17,
+// 12 x 32760 78 -> 66, 40 x 75600 525 -> 500; Q and K alone 4 x 2187 7.3 -> 3.6, 12 x 32760 44 -> 35).
 // The maxima of V leave as one row per workgroup, which finalize_block reduces: nothing has to be cleared
 // beforehand and there are no atomics (the clearing launch alone was 1.4 us of the smallest calls' 61).
 // ---------------------------------------------------------------------------
-template <bool WANT_V>
-__global__ void __launch_bounds__(256) pool_stats_kernel(
-    const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
-    int N, int block_q, int Tq, int Tk, int groups, int H, Layout lq, Layout lk, Layout lv,
-    float* __restrict__ qbar, float* __restrict__ kbar, float* __restrict__ dq,
-    float* __restrict__ vmax_part, int8_t* __restrict__ q8) {
-  __shared__ float sQ[16][2][D];
-  __shared__ float s_qmax[2];
-  __shared__ float sK[16][2][D];
-  __shared__ float sV[WANT_V ? 16 : 1][D];
-  __shared__ float sQa[2][256];
-  const int bh = blockIdx.x / groups, g = blockIdx.x % groups;
+struct PoolArgs {
+  const bf16_t *x[3];   // q, k, v
+  Layout l[3];
+  int N, block_q, Tq, Tk, groups, H, per_part;   // per_part: workgroups per tensor, BH * groups
+  float *qbar, *kbar, *dq, *vmax_part;
+  int8_t* q8;
+};
+__global__ void __launch_bounds__(256) pool_stats_kernel(const PoolArgs A) {
+  __shared__ __attribute__((aligned(16))) float sums[16][2][D];
+  __shared__ float s_amax[2][4], s_qmax[2];
+  const int part = blockIdx.x / A.per_part, blk = blockIdx.x - part * A.per_part;
+  const int bh = blk / A.groups, g = blk - bh * A.groups, N = A.N;
   const int t = threadIdx.x, cg = t & 15, rg = t >> 4;
-  const int b_ = bh / H, h_ = bh - b_ * H;
-  const bf16_t* qs_ = q + b_ * lq.sb + h_ * lq.sh;
-  const bf16_t* ks_ = k + b_ * lk.sb + h_ * lk.sh;
-  const bf16_t* vs_ = WANT_V ? v + b_ * lv.sb + h_ * lv.sh : nullptr;
+  const int b_ = bh / A.H, h_ = bh - b_ * A.H;
+  const Layout L = part == 0 ? A.l[0] : part == 1 ? A.l[1] : A.l[2];
+  const bf16_t* src = (part == 0 ? A.x[0] : part == 1 ? A.x[1] : A.x[2]) + b_ * L.sb + h_ * L.sh + cg * 8;
   const int row0 = g * 128;
-
-  float qs[2][8] = {}, ks[2][8] = {}, va[8] = {}, qa[2] = {0.f, 0.f};
-  uint4 qkeep[8];  // this thread's Q values, kept for the codes (formed once the block maxima are known)
+  uint4 x[8];
 #pragma unroll
-  for (int r = 0; r < 8; ++r) {
-    const int row = row0 + rg + 16 * r, half = r >> 2;
-    qkeep[r] = make_uint4(0u, 0u, 0u, 0u);
-    if (row < N) {
-      const uint4 xq = *(const uint4*)(qs_ + row * lq.sn + cg * 8);
-      qkeep[r] = xq;
-      const uint4 xk = *(const uint4*)(ks_ + row * lk.sn + cg * 8);
-      uint4 xv = make_uint4(0u, 0u, 0u, 0u);
-      if constexpr (WANT_V) xv = *(const uint4*)(vs_ + row * lv.sn + cg * 8);
-      const uint32_t wq[4] = {xq.x, xq.y, xq.z, xq.w}, wk[4] = {xk.x, xk.y, xk.z, xk.w},
-                     wv[4] = {xv.x, xv.y, xv.z, xv.w};
+  for (int r = 0; r < 8; ++r) {  // (all eight in flight: rows past the end are read as the last one and dropped)
+    const int row = row0 + rg + 16 * r;
+    x[r] = *(const uint4*)(src + min(row, N - 1) * L.sn);
+    if (row >= N) x[r] = make_uint4(0u, 0u, 0u, 0u);
+  }
+  float s[2][8] = {}, amax[2] = {0.f, 0.f};
+  if (part == 2) {
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      const uint32_t w[4] = {x[r].x, x[r].y, x[r].z, x[r].w};
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const float q0 = bf16_lo(wq[e]), q1 = bf16_hi(wq[e]);
-        qs[half][2 * e] += q0;
-        qs[half][2 * e + 1] += q1;
-        qa[half] = fmaxf(qa[half], fmaxf(fabsf(q0), fabsf(q1)));
-        ks[half][2 * e] += bf16_lo(wk[e]);
-        ks[half][2 * e + 1] += bf16_hi(wk[e]);
-        if constexpr (WANT_V) {
-          va[2 * e] = fmaxf(va[2 * e], fabsf(bf16_lo(wv[e])));
-          va[2 * e + 1] = fmaxf(va[2 * e + 1], fabsf(bf16_hi(wv[e])));
-        }
+        s[0][2 * e] = fmaxf(s[0][2 * e], fabsf(bf16_lo(w[e])));
+        s[0][2 * e + 1] = fmaxf(s[0][2 * e + 1], fabsf(bf16_hi(w[e])));
+      }
+    }
+  } else {
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      const uint32_t w[4] = {x[r].x, x[r].y, x[r].z, x[r].w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float lo = bf16_lo(w[e]), hi = bf16_hi(w[e]);
+        s[r >> 2][2 * e] += lo;
+        s[r >> 2][2 * e + 1] += hi;
+        amax[r >> 2] = fmaxf(amax[r >> 2], fmaxf(fabsf(lo), fabsf(hi)));
       }
     }
   }
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    sQ[rg][0][cg * 8 + e] = qs[0][e];
-    sQ[rg][1][cg * 8 + e] = qs[1][e];
-    sK[rg][0][cg * 8 + e] = ks[0][e];
-    sK[rg][1][cg * 8 + e] = ks[1][e];
-    if constexpr (WANT_V) sV[rg][cg * 8 + e] = va[e];
+  for (int h = 0; h < 2; ++h) {
+    *(float4*)&sums[rg][h][cg * 8] = make_float4(s[h][0], s[h][1], s[h][2], s[h][3]);
+    *(float4*)&sums[rg][h][cg * 8 + 4] = make_float4(s[h][4], s[h][5], s[h][6], s[h][7]);
   }
-  sQa[0][t] = qa[0];
-  sQa[1][t] = qa[1];
-  __syncthreads();
-
-  const int half = t >> 7, c = t & 127;
-  float sq = 0.f, sk = 0.f;
+  if (part == 0) {
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    sq += sQ[r][half][c];
-    sk += sK[r][half][c];
+    for (int h = 0; h < 2; ++h) {
+      for (int o = 32; o > 0; o >>= 1) amax[h] = fmaxf(amax[h], __shfl_xor(amax[h], o));
+      if ((t & 63) == 0) s_amax[h][t >> 6] = amax[h];
+    }
   }
-  const int cnt0 = min(64, max(0, N - row0)), cnt1 = min(64, max(0, N - row0 - 64));
-  const int cnt = half ? cnt1 : cnt0;
-  if (cnt > 0) kbar[((size_t)bh * Tk + 2 * g + half) * D + c] = sk / (float)cnt;
-  if (block_q == 64) {
-    if (cnt > 0) qbar[((size_t)bh * Tq + 2 * g + half) * D + c] = sq / (float)cnt;
-  } else {
-    // both halves belong to query block g: combine the two partial sums
-    __syncthreads();
-    sQ[0][half][c] = sq;
-    __syncthreads();
-    if (half == 0) qbar[((size_t)bh * Tq + g) * D + c] = (sQ[0][0][c] + sQ[0][1][c]) / (float)(cnt0 + cnt1);
-  }
-  if constexpr (WANT_V) {
+  __syncthreads();
+  const int half = t >> 7, c = t & 127;
+  if (part == 2) {
     if (t < 128) {
       float m = 0.f;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) m = fmaxf(m, sV[r][t]);
-      vmax_part[(size_t)blockIdx.x * D + t] = m;
+      for (int r = 0; r < 16; ++r) m = fmaxf(m, sums[r][0][t]);
+      A.vmax_part[(size_t)blk * D + t] = m;
     }
+    return;
   }
-  if (t < 64) {  // wave 0 reduces the |Q| maxima of both halves
-    float m0 = 0.f, m1 = 0.f;
-    for (int r = t; r < 256; r += 64) {
-      m0 = fmaxf(m0, sQa[0][r]);
-      m1 = fmaxf(m1, sQa[1][r]);
+  float tot = 0.f;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) tot += sums[r][half][c];
+  const int cnt0 = min(64, max(0, N - row0)), cnt1 = min(64, max(0, N - row0 - 64)), cnt = half ? cnt1 : cnt0;
+  if (part == 1) {
+    if (cnt > 0) A.kbar[((size_t)bh * A.Tk + 2 * g + half) * D + c] = tot / (float)cnt;
+    return;
+  }
+  if (A.block_q == 64) {
+    if (cnt > 0) A.qbar[((size_t)bh * A.Tq + 2 * g + half) * D + c] = tot / (float)cnt;
+  } else {
+    // both halves belong to query block g: combine the two partial sums
+    __syncthreads();
+    sums[0][half][c] = tot;
+    __syncthreads();
+    if (half == 0) A.qbar[((size_t)bh * A.Tq + g) * D + c] = (sums[0][0][c] + sums[0][1][c]) / (float)(cnt0 + cnt1);
+  }
+  if (t == 0) {
+    float m[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) m[h] = fmaxf(fmaxf(s_amax[h][0], s_amax[h][1]), fmaxf(s_amax[h][2], s_amax[h][3]));
+    if (A.block_q == 64) {
+      if (cnt0 > 0) A.dq[(size_t)bh * A.Tq + 2 * g] = m[0] > 0.f ? m[0] / 127.0f : 1.0f;
+      if (cnt1 > 0) A.dq[(size_t)bh * A.Tq + 2 * g + 1] = m[1] > 0.f ? m[1] / 127.0f : 1.0f;
+    } else {
+      m[0] = m[1] = fmaxf(m[0], m[1]);
+      A.dq[(size_t)bh * A.Tq + g] = m[0] > 0.f ? m[0] / 127.0f : 1.0f;
     }
-    for (int o = 32; o > 0; o >>= 1) {
-      m0 = fmaxf(m0, __shfl_xor(m0, o));
-      m1 = fmaxf(m1, __shfl_xor(m1, o));
-    }
-    if (t == 0) {
-      if (block_q == 64) {
-        if (cnt0 > 0) dq[(size_t)bh * Tq + 2 * g] = m0 > 0.f ? m0 / 127.0f : 1.0f;
-        if (cnt1 > 0) dq[(size_t)bh * Tq + 2 * g + 1] = m1 > 0.f ? m1 / 127.0f : 1.0f;
-        s_qmax[0] = m0;
-        s_qmax[1] = m1;
-      } else {
-        const float m = fmaxf(m0, m1);
-        dq[(size_t)bh * Tq + g] = m > 0.f ? m / 127.0f : 1.0f;
-        s_qmax[0] = s_qmax[1] = m;
-      }
-    }
+    s_qmax[0] = m[0];
+    s_qmax[1] = m[1];
   }
   // ---- INT8 codes of Q at the scale just found (max|Q block| / 127), ties exact: every row's 128 bytes in the
   // order the attention kernel's lanes take them (q8_byte_offset); this thread: 8 adjacent bytes of 8 rows.
-  if (q8 == nullptr) return;  // (uniform)
+  if (A.q8 == nullptr) return;  // (uniform)
   __syncthreads();
-  int8_t* dst = q8 + ((size_t)(bh * groups + g) * 128) * D + q8_byte_offset(cg * 8);
+  int8_t* dst = A.q8 + ((size_t)blk * 128) * D + q8_byte_offset(cg * 8);
 #pragma unroll
   for (int r = 0; r < 8; ++r) {
     const int rl = rg + 16 * r;
     if (row0 + rl >= N) continue;
     const CodeScale cs = code_scale(s_qmax[r >> 2], 127.0f);
-    const uint32_t wq[4] = {qkeep[r].x, qkeep[r].y, qkeep[r].z, qkeep[r].w};
-    uint32_t c[8];
+    const uint32_t w[4] = {x[r].x, x[r].y, x[r].z, x[r].w};
+    uint32_t code[8];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      c[2 * e] = int8_code_word_exact(bf16_lo(wq[e]), cs);
-      c[2 * e + 1] = int8_code_word_exact(bf16_hi(wq[e]), cs);
+      code[2 * e] = int8_code_word_exact(bf16_lo(w[e]), cs);
+      code[2 * e + 1] = int8_code_word_exact(bf16_hi(w[e]), cs);
     }
-    *(uint2*)(dst + (size_t)rl * D) = make_uint2(pack_low_bytes(c[0], c[1], c[2], c[3]), pack_low_bytes(c[4], c[5], c[6], c[7]));
+    *(uint2*)(dst + (size_t)rl * D) = make_uint2(pack_low_bytes(code[0], code[1], code[2], code[3]), pack_low_bytes(code[4], code[5], code[6], code[7]));
   }
 }
 
@@ -159,9 +154,7 @@ __global__ void zero_u32_kernel(uint32_t* p, size_t n) {
 // launch (both depend on pool_stats alone, and a launch of its own cost the smallest calls 11 of 61 us).
 // Workgroups 0 .. 8 BH - 1, eight per (b,h), each for 16 channels: mu_K[c] = sum_j cnt_j kbar[j][c] / N, max|V[:,c]|,
 // delta_V[c] = max|V[:,c]| / 448 (1 if zero).  The INT8 codes of K hang on the last bit of the mean, so its order of
-// summation is part of the result: MEAN_RUNS interleaved partial sums (j, j + 64, ...), then those in ascending order.
-// A thread carries MEAN_RUNS / 16 of them, which also keeps that many loads in flight.
-constexpr int MEAN_RUNS = 64;
+// summation is part of the result (MEAN_RUNS).  A thread carries MEAN_RUNS / 16 of them, which also keeps that many loads in flight.
 __device__ __forceinline__ void finalize_block(int blk, const float* __restrict__ kbar, const float* __restrict__ vmax_part,
                                                int groups, int N, int Tk, float* __restrict__ mu_k,
                                                float* __restrict__ amax_v, float* __restrict__ dv) {
@@ -174,12 +167,12 @@ __device__ __forceinline__ void finalize_block(int blk, const float* __restrict_
 #pragma unroll 4
   for (; j0 + MEAN_RUNS <= Tk && (j0 + MEAN_RUNS) * BK <= N; j0 += MEAN_RUNS)   // (whole blocks only)
 #pragma unroll
-    for (int u = 0; u < PER; ++u) s[u] += col[(size_t)(j0 + rgrp + 16 * u) * D] * (float)BK;
+    for (int u = 0; u < PER; ++u) s[u] = __builtin_fmaf(col[(size_t)(j0 + rgrp + 16 * u) * D], (float)BK, s[u]);
   for (; j0 < Tk; j0 += MEAN_RUNS)
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
       const int j = j0 + rgrp + 16 * u;
-      if (j < Tk) s[u] += col[(size_t)j * D] * (float)min(BK, N - j * BK);
+      if (j < Tk) s[u] = __builtin_fmaf(col[(size_t)j * D], (float)min(BK, N - j * BK), s[u]);
     }
 #pragma unroll 8
   for (int g = rgrp; g < groups; g += 16) m = fmaxf(m, vmax_part[((size_t)bh * groups + g) * D + c0 + cl]);
@@ -272,118 +265,10 @@ __global__ void __launch_bounds__(256, 2) scores_kernel(const ScoresArgs A) {
   }
 }
 
-// select: one WAVEFRONT per (b,h,i) row; the row's scores live in registers (KPL per lane,
-// block j = lane + 64 m in register m) as order-preserving 32-bit keys.  The n_c-th and the
-// (n_c+n_m)-th largest keys are found exactly, bit by bit from the top: a bit of the threshold
-// is set when at least `rank` keys are >= the candidate with that bit set.  The counts come
-// from wave-wide compares (one vector compare per register, the population count and the sum
-// on the scalar unit), so there is no shared-memory traffic and no atomic.  Blocks whose key
-// equals a threshold key are ranked by ascending j with ballots, so equal scores rank by
-// ascending block index and the result is exact and deterministic.  Outputs: the int8 mask
-// row, the ascending critical list, and the marginal ballots as words of the bit matrix the
-// accumulation kernel reads (see lin_accumulate).
-__device__ __forceinline__ uint32_t order_bits(float f) {
-  const uint32_t u = __float_as_uint(f);
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-
 template <int KPL>
-__global__ void __launch_bounds__(256) select_kernel(const float* __restrict__ scores, int rows, int Tq, int Tk,
-                                                     int n_c, int n_m, int8_t* __restrict__ mask,
-                                                     int32_t* __restrict__ crit, int32_t* __restrict__ marg,
-                                                     uint32_t* __restrict__ mbits) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const unsigned long long lt = (1ull << lane) - 1ull;
-  const size_t row = (size_t)blockIdx.x * 4 + w;
-  if (row >= (size_t)rows) return;  // whole wavefront; no workgroup barrier is used below
-  const float* srow = scores + row * Tk;
-  uint32_t key[KPL];
-#pragma unroll
-  for (int m = 0; m < KPL; ++m) {
-    const int j = lane + 64 * m;
-    key[m] = j < Tk ? order_bits(srow[j]) : 0u;
-  }
-  // Subtract the row minimum and shift out the common leading zeros: order and ties are
-  // unchanged, padding (key 0) ties with the minimum, and the search below only has to visit
-  // the bits in which the keys can differ.
-  int low;
-  {
-    uint32_t kmin = 0xffffffffu, kmax = 0u;
-#pragma unroll
-    for (int m = 0; m < KPL; ++m)
-      if (lane + 64 * m < Tk) {
-        kmin = min(kmin, key[m]);
-        kmax = max(kmax, key[m]);
-      }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, o));
-      kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, o));
-    }
-    const uint32_t span = kmax - kmin;
-    const int lz = span ? __builtin_clz(span) : 0;
-    low = span ? lz : 32;  // all keys equal: nothing to search
-#pragma unroll
-    for (int m = 0; m < KPL; ++m) key[m] = (lane + 64 * m < Tk) ? ((key[m] - kmin) << lz) : 0u;  // padding ties with the minimum: never above a threshold
-  }
-  // k1 / k2: the n_c-th / (n_c+n_m)-th largest key; t1 / t2: how many of the keys equal to
-  // it belong to the top n_c / n_c+n_m (>= 1).  Bits below `low` are zero in every key.
-  // A threshold's search stops early once exactly the wanted number of keys reaches the
-  // candidate c: the set is then {key >= c}, which the code below takes as "key > c - 1" with
-  // no ties to rank (with ~1000 distinct keys that happens after about log2(Tk) + 2 bits).
-  uint32_t k1 = 0, k2 = 0;
-  const int rank2 = n_c + n_m;
-  bool open1 = true, open2 = n_m > 0;
-  for (int bit = 31; bit >= low && (open1 || open2); --bit) {
-    const uint32_t c1 = k1 | (1u << bit), c2 = k2 | (1u << bit);
-    int n1 = 0, n2 = 0;
-#pragma unroll
-    for (int m = 0; m < KPL; ++m) {  // (padding keys are 0 and never reach a candidate)
-      if (open1) n1 += __popcll(__ballot(key[m] >= c1));
-      if (open2) n2 += __popcll(__ballot(key[m] >= c2));
-    }
-    if (open1) {
-      if (n1 == n_c) { k1 = c1 - 1u; open1 = false; }
-      else if (n1 > n_c) k1 = c1;
-    }
-    if (open2) {
-      if (n2 == rank2) { k2 = c2 - 1u; open2 = false; }
-      else if (n2 > rank2) k2 = c2;
-    }
-  }
-  int t1 = n_c, t2 = rank2;
-#pragma unroll
-  for (int m = 0; m < KPL; ++m) {
-    t1 -= __popcll(__ballot(key[m] > k1));
-    if (n_m > 0) t2 -= __popcll(__ballot(key[m] > k2));
-  }
-
-  const int bh = (int)(row / Tq), i = (int)(row % Tq);
-  const int KT = (Tk + 31) / 32, TqP = (Tq + 383) / 384 * 384 + 128;  // layout of the marginal bit matrix (see lin_accumulate)
-  int eq1 = 0, eq2 = 0, nc = 0, nm = 0;  // running counts in ascending-j order
-#pragma unroll
-  for (int m = 0; m < KPL; ++m) {
-    const int j = lane + 64 * m;
-    if (64 * m >= Tk) break;
-    const bool valid = j < Tk;
-    const bool e1 = valid && key[m] == k1, e2 = valid && n_m > 0 && key[m] == k2;
-    const unsigned long long b1 = __ballot(e1), b2 = __ballot(e2);
-    const int r1 = eq1 + __popcll(b1 & lt), r2 = eq2 + __popcll(b2 & lt);
-    eq1 += __popcll(b1);
-    eq2 += __popcll(b2);
-    const bool is_c = valid && (key[m] > k1 || (e1 && r1 < t1));
-    const bool is_m = valid && !is_c && n_m > 0 && (key[m] > k2 || (e2 && r2 < t2));
-    if (mask && valid) mask[row * Tk + j] = is_c ? 1 : (is_m ? 0 : -1);
-    const unsigned long long bc = __ballot(is_c), bm = __ballot(is_m);
-    if (crit && is_c) crit[row * n_c + nc + __popcll(bc & lt)] = j;
-    if (marg && is_m) marg[row * n_m + nm + __popcll(bm & lt)] = j;
-    nc += __popcll(bc);
-    nm += __popcll(bm);
-    if (mbits && lane < 2) {  // the marginal ballot of these 64 key blocks = two words of the bit matrix
-      const int kt = 2 * m + lane;
-      if (kt < KT) mbits[((size_t)bh * KT + kt) * TqP + i] = (uint32_t)(bm >> (32 * lane));
-    }
-  }
+__global__ void __launch_bounds__(256) select_kernel(const SelectArgs S) {
+  const size_t row = (size_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (row < (size_t)S.rows) select_row<KPL>(S, row, S.scores + row * S.Tk);  // (no workgroup barrier: whole wavefronts may leave)
 }
 
 // ---------------------------------------------------------------------------
@@ -393,11 +278,10 @@ void launch_zero_u32(uint32_t* p, size_t n, hipStream_t stream) {
 
 void launch_pool_stats(const void* q, const void* k, const void* v, const Problem& p, float* qbar,
                        float* kbar, float* dq, float* vmax_part, int8_t* q8, hipStream_t stream) {
-  const int groups = (p.N + 127) / 128;
-#define SLA_POOL(WANT_V) pool_stats_kernel<WANT_V><<<p.BH * groups, 256, 0, stream>>>((const bf16_t*)q, (const bf16_t*)k, \
-      (const bf16_t*)v, p.N, p.block_q, p.Tq, p.Tk, groups, p.H, p.lq, p.lk, p.lv, qbar, kbar, dq, vmax_part, q8)
-  if (v) SLA_POOL(true); else SLA_POOL(false);
-#undef SLA_POOL
+  const int groups = (p.N + 127) / 128, per_part = p.BH * groups;
+  pool_stats_kernel<<<(v ? 3u : 2u) * (unsigned)per_part, 256, 0, stream>>>(
+      PoolArgs{{(const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v}, {p.lq, p.lk, p.lv}, p.N, p.block_q, p.Tq, p.Tk, groups, p.H, per_part,
+               qbar, kbar, dq, vmax_part, q8});
 }
 
 void launch_scores(const Problem& p, const float* qbar, const float* kbar, float* scores, const FinalizeArgs* fin,
@@ -430,8 +314,8 @@ void launch_scores(const Problem& p, const float* qbar, const float* kbar, float
 void launch_select(const Problem& p, const float* scores, int8_t* mask, int32_t* crit, int32_t* marg,
                    uint32_t* mbits, hipStream_t stream) {
   const int rows = p.BH * p.Tq, need = (p.Tk + 63) / 64;
-  const unsigned grid = (unsigned)((rows + 3) / 4);
-#define SLA_SELECT(K) select_kernel<K><<<grid, 256, 0, stream>>>(scores, rows, p.Tq, p.Tk, p.n_c, p.n_m, mask, crit, marg, mbits)
+  const SelectArgs S{scores, rows, p.Tq, p.Tk, p.n_c, p.n_m, mask, crit, marg, mbits};
+#define SLA_SELECT(K) select_kernel<K><<<(unsigned)((rows + 3) / 4), 256, 0, stream>>>(S)
   // registers per lane: the smallest instantiation that holds the row
   if (need <= 2) SLA_SELECT(2);
   else if (need <= 4) SLA_SELECT(4);

@@ -15,19 +15,90 @@
 //
 // One workgroup (4 wavefronts) per (b,h,j).  HBM-bound: reads 32 KiB, writes 16 KiB of
 // codes and 33 KiB of summaries per block.
-#include "common.h"
+#include "classify.h"
+#include "delta.h"
 
 namespace sla {
 
+struct MidArgs {
+  SelectArgs S;
+  DeltaArgs X;
+  PrepArgs P;
+  int select_blocks, delta_blocks;   // leading workgroups of the selection, then those of delta
+};
+
 constexpr int STAGE_STRIDE = 2 * D + 16;  // bytes per staged hz row (padded against bank conflicts)
 
-template <int PHI>
-__global__ void __launch_bounds__(256, 4) prep_kv_kernel(
-    const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, int N, int Tk, int H, Layout lk, Layout lv,
-    const float* __restrict__ mu_k, const float* __restrict__ amax_v,
-    const bf16_t* __restrict__ wfrag,
-    int want_quant, int want_linear, int8_t* __restrict__ k8, uint8_t* __restrict__ v8,
-    float* __restrict__ dk, bf16_t* __restrict__ hz) {
+// The statistics of slice bh joined over its (at most MEAN_RUNS) key blocks: stat[c] = mean of K, stat[128 + c] = max|V|.  The
+// sums are finalize_block's, in its order.
+__device__ __forceinline__ void slice_stats(const PrepArgs& P, int bh, bool publish, float* stat) {
+  const int t = threadIdx.x, c = t & 127, N = P.N, Tk = P.Tk;
+  if (t < 128) {
+    const float* col = P.kbar + (size_t)bh * Tk * D + c;
+    float tot = 0.f;
+#pragma unroll 16
+    for (int r = 0; r < Tk; ++r) tot += __builtin_fmaf(col[(size_t)r * D], (float)min(BK, N - r * BK), 0.f);
+    stat[c] = tot / (float)N;
+    if (publish) P.mu_out[(size_t)bh * D + c] = stat[c];
+  } else {
+    float m = 0.f;
+#pragma unroll 8
+    for (int g = 0; g < P.groups; ++g) m = fmaxf(m, P.vmax_part[((size_t)bh * P.groups + g) * D + c]);
+    stat[D + c] = m;
+    if (publish) {
+      P.amax_out[(size_t)bh * D + c] = m;
+      P.dv_out[(size_t)bh * D + c] = m > 0.f ? m / E4M3_MAX : 1.0f;
+    }
+  }
+}
+// W[row][col .. col + 7] (the identity if no projection is given), straight from the caller's matrix.
+__device__ __forceinline__ v8bf w_operand(const PrepArgs& P, int row, int col) {
+  if (P.w_aligned) return *(const v8bf*)(P.proj_w + row * D + col);
+  union { bf16_t e[8]; v8bf v; } x;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) x.e[e] = P.proj_w ? P.proj_w[row * D + col + e] : (row == col + e ? (bf16_t)0x3f80 : (bf16_t)0);
+  return x.v;
+}
+// The four query blocks 4 blk .. 4 blk + 3 of a slice: their scores against all (at most 64 KPL) key blocks, formed as
+// scores_kernel forms them (the same products in the same order; a wavefront has a tile of 32 key blocks, 28 of the 32
+// rows of the product are copies), kept in LDS, then one row per wavefront selected from there.
+template <int KPL>
+__device__ __forceinline__ void classify_rows(const SelectArgs& S, const float* qbar, const float* kbar, int blk) {
+  __shared__ float sc[4][64 * KPL];
+  const int Tq = S.Tq, Tk = S.Tk, per = (Tq + 3) / 4, bh = blk / per, i0 = 4 * (blk - bh * per);
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, h = lane >> 5;
+  for (int jt = w; jt * 32 < Tk; jt += 4) {
+    const float4* ap = (const float4*)(qbar + ((size_t)bh * Tq + min(i0 + (l32 & 3), Tq - 1)) * D + 64 * h);
+    const float4* bp = (const float4*)(kbar + ((size_t)bh * Tk + min(jt * 32 + l32, Tk - 1)) * D + 64 * h);
+    v16f acc = {};
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const float4 a = ap[u], b = bp[u];
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.x, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b.y, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, b.z, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, b.w, acc, 0, 0, 0);
+    }
+    if (h == 0) {  // (accumulator registers 0..3 of the lower lane half: rows 0..3)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sc[r][jt * 32 + l32] = acc[r] / 11.313708498984761f;
+    }
+  }
+  __syncthreads();
+  if (i0 + w < Tq) select_row<KPL>(S, (size_t)bh * Tq + i0 + w, sc[w]);
+}
+
+// STATS (calls of few key blocks): nobody has joined the statistics over the slice yet or laid out W; every workgroup does
+// that for itself (mean of K and max|V| of at most 64 key blocks, W's operands from where they are).
+template <int PHI, bool STATS>
+__device__ __forceinline__ void prep_block(const PrepArgs& P, int blk) {
+  const bf16_t *k = P.k, *v = P.v, *wfrag = P.wfrag;
+  const int N = P.N, Tk = P.Tk, H = P.H, want_quant = P.want_quant, want_linear = P.want_linear;
+  const Layout &lk = P.lk, &lv = P.lv;
+  int8_t* k8 = P.k8;
+  uint8_t* v8 = P.v8;
+  float* dk = P.dk;
+  bf16_t* hz = P.hz;
   __shared__ __attribute__((aligned(16))) unsigned char smem[128 * STAGE_STRIDE + 4 * D * 4];
   __shared__ float wave_amax[4];
   unsigned char* kq = smem;                       // [8192]  K codes, fragment order
@@ -35,9 +106,9 @@ __global__ void __launch_bounds__(256, 4) prep_kv_kernel(
   unsigned char* vbf = smem;                      // [64][STAGE_STRIDE] V rows as bf16 (aliases kq / vq, after their last read)
   unsigned char* phit = smem + BK * STAGE_STRIDE; // [16384] phi(K)^T bf16, B-operand order
   unsigned char* stage = smem;                    // [128][STAGE_STRIDE] aliases everything above
-  float* zred = (float*)(smem + 128 * STAGE_STRIDE);  // [4][128] per-wavefront column sums of phi(K)
+  float* zred = (float*)(smem + 128 * STAGE_STRIDE);  // [4][128] per-wavefront column sums of phi(K); before that STATS' mean and maxima
 
-  const int bh = blockIdx.x / Tk, j = blockIdx.x % Tk;
+  const int bh = blk / Tk, j = blk % Tk;
   const int t = threadIdx.x, cg = t & 15, m = t >> 4, lane = t & 63, w = t >> 6;
   const int valid = min(BK, N - j * BK);
   const int b_ = bh / H, h_ = bh - b_ * H;
@@ -64,12 +135,19 @@ __global__ void __launch_bounds__(256, 4) prep_kv_kernel(
   }
 
   if (want_quant) {
+    const float *mu_k = P.mu_k + (size_t)bh * D, *amax_v = P.amax_v + (size_t)bh * D;
+    if constexpr (STATS) {
+      slice_stats(P, bh, j == 0, zred);
+      mu_k = zred;
+      amax_v = zred + D;
+      __syncthreads();
+    }
     float mu[8];
     CodeScale vcs[8];  // per channel: max|V| (its scale is this / 448), its reciprocal, 448
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      mu[e] = mu_k[(size_t)bh * D + cg * 8 + e];
-      vcs[e] = code_scale(amax_v[(size_t)bh * D + cg * 8 + e], E4M3_MAX);
+      mu[e] = mu_k[cg * 8 + e];
+      vcs[e] = code_scale(amax_v[cg * 8 + e], E4M3_MAX);
     }
     float kt[4][8], amax = 0.f;
 #pragma unroll
@@ -189,7 +267,7 @@ __global__ void __launch_bounds__(256, 4) prep_kv_kernel(
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) {
       const v8bf a = *(const v8bf*)(vbf + row * STAGE_STRIDE + 32 * ks + 16 * hfl);
-      const v8bf b = *(const v8bf*)(wfrag + ((w * 8 + ks) * 64 + lane) * 8);
+      const v8bf b = STATS ? w_operand(P, 32 * w + l32, 16 * ks + 8 * hfl) : *(const v8bf*)(wfrag + ((w * 8 + ks) * 64 + lane) * 8);
       d1[rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, d1[rt], 0, 0, 0);
     }
   }
@@ -236,6 +314,27 @@ __global__ void __launch_bounds__(256, 4) prep_kv_kernel(
     *(uint4*)(dst + d * 8) = *(const uint4*)(stage + o * STAGE_STRIDE + cq * 16);
   }
   if (t < D) dst[D * D + t] = f32_to_bf16(zsum);
+}
+
+// One launch for everything that only waits for the statistics pass (and, without STATS, for the scores): the selection
+// of the critical and marginal blocks, delta = dO . O^s of a backward pass with saved state, and the workgroups of
+// prep_block.  They need nothing of one another, and the selection, which is all compares and latency, runs under
+// prep_block's traffic (its workgroups first; spread among prep_block's they were 2 to 5 % slower).
+// STATS: the scores themselves are formed here as well, four query blocks per workgroup.
+template <int PHI, int KPL, bool STATS>
+__global__ void __launch_bounds__(256, 4) select_prep_kernel(const MidArgs A) {
+  int blk = blockIdx.x;
+  if (blk < A.select_blocks) {
+    if constexpr (STATS) classify_rows<KPL>(A.S, A.P.qbar, A.P.kbar, blk);
+    else {
+      const size_t row = (size_t)blk * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+      if (row < (size_t)A.S.rows) select_row<KPL>(A.S, row, A.S.scores + row * A.S.Tk);
+    }
+    return;
+  }
+  blk -= A.select_blocks;
+  if (blk < A.delta_blocks) return delta_block(A.X, blk);
+  prep_block<PHI, STATS>(A.P, blk - A.delta_blocks);
 }
 
 // Plain-layout copies of the codes (tests only).
@@ -285,18 +384,56 @@ __global__ void e4m3_encode_kernel(const float* __restrict__ in, uint8_t* __rest
   if (i < n) out[i] = (uint8_t)(cvt_pk_e4m3(clamp_e4m3(in[i]), 0.f, 0, false) & 0xff);
 }
 
-void launch_prep_kv(const void* k, const void* v, const Problem& p, const float* mu_k, const float* amax_v,
-                    const bf16_t* wfrag, int phi_kind, bool want_quant, bool want_linear, int8_t* k8,
-                    uint8_t* v8, float* dk, bf16_t* hz, hipStream_t stream) {
+PrepArgs prep_args(const void* k, const void* v, const Problem& p, const float* mu_k, const float* amax_v, const bf16_t* wfrag,
+                   bool want_quant, bool want_linear, int8_t* k8, uint8_t* v8, float* dk, bf16_t* hz) {
+  PrepArgs P{};
+  P.k = (const bf16_t*)k; P.v = (const bf16_t*)v;
+  P.N = p.N; P.Tk = p.Tk; P.H = p.H; P.lk = p.lk; P.lv = p.lv;
+  P.mu_k = mu_k; P.amax_v = amax_v; P.wfrag = wfrag;
+  P.want_quant = want_quant; P.want_linear = want_linear;
+  P.k8 = k8; P.v8 = v8; P.dk = dk; P.hz = hz;
+  return P;
+}
+
+void launch_prep_kv(const PrepArgs& P, const Problem& p, int phi_kind, hipStream_t stream) {
+  MidArgs A{};
+  A.P = P;
   const unsigned grid = (unsigned)(p.BH * p.Tk);
-  const bf16_t* kk = (const bf16_t*)k;
-  const bf16_t* vv = (const bf16_t*)v;
-  if (phi_kind == 0)
-    prep_kv_kernel<0><<<grid, 256, 0, stream>>>(kk, vv, p.N, p.Tk, p.H, p.lk, p.lv, mu_k, amax_v, wfrag, want_quant, want_linear, k8, v8, dk, hz);
-  else if (phi_kind == 1)
-    prep_kv_kernel<1><<<grid, 256, 0, stream>>>(kk, vv, p.N, p.Tk, p.H, p.lk, p.lv, mu_k, amax_v, wfrag, want_quant, want_linear, k8, v8, dk, hz);
-  else
-    prep_kv_kernel<2><<<grid, 256, 0, stream>>>(kk, vv, p.N, p.Tk, p.H, p.lk, p.lv, mu_k, amax_v, wfrag, want_quant, want_linear, k8, v8, dk, hz);
+  if (phi_kind == 0) select_prep_kernel<0, 2, false><<<grid, 256, 0, stream>>>(A);
+  else if (phi_kind == 1) select_prep_kernel<1, 2, false><<<grid, 256, 0, stream>>>(A);
+  else select_prep_kernel<2, 2, false><<<grid, 256, 0, stream>>>(A);
+}
+
+// One launch for scores, selection and operands where a slice has at most 64 key blocks: the statistics that every
+// workgroup then joins for itself cost as much as a launch from there on (2 slices, us for the whole forward call, two
+// launches / one: 16 blocks 38.2 / 33.6, 64 blocks 47.1 / 43.8, 128 blocks 55.6 / 57.0; 8 slices of 64 blocks 66.1 / 66.0),
+// and while its workgroups of four query blocks, each of which pays for a product of 32 rows, are few (40 slices of 16
+// blocks, 160 workgroups, 75.0 / 73.6).
+bool stats_in_prep(const Problem& p) { return p.Tk <= 64 && (long long)p.BH * ((p.Tq + 3) / 4) <= 1024; }
+
+void launch_select_prep(const SelectArgs& S, const PrepArgs& P, const DeltaArgs* delta, const Problem& p, int phi_kind, hipStream_t stream) {
+  MidArgs A{};
+  A.S = S; A.P = P;
+  const bool stats = stats_in_prep(p);
+  const int need = (p.Tk + 63) / 64;
+  if (delta) {
+    A.X = *delta;
+    A.delta_blocks = delta_blocks(p);
+  }
+  // Long rows are selected in a launch of their own: 40 slices of 591 x 1182 blocks take 163 us there and 1003 us with
+  // prep_block's, in one launch 1020 (prep_block's shared memory leaves the selection half of the wavefronts it hides
+  // its latency with); 12 slices of 256 x 512 blocks 137 us in two, 124 in one.
+  if (!stats && need > 8) {
+    launch_select(p, S.scores, S.mask, S.crit, S.marg, S.mbits, stream);
+  } else {
+    A.select_blocks = stats ? p.BH * ((p.Tq + 3) / 4) : (S.rows + 3) / 4;
+  }
+  const unsigned grid = (unsigned)(A.select_blocks + A.delta_blocks + p.BH * p.Tk);
+#define SLA_MID(PHI) { if (stats) select_prep_kernel<PHI, 1, true><<<grid, 256, 0, stream>>>(A); \
+                       else if (need <= 2) select_prep_kernel<PHI, 2, false><<<grid, 256, 0, stream>>>(A); \
+                       else select_prep_kernel<PHI, 8, false><<<grid, 256, 0, stream>>>(A); }
+  if (phi_kind == 0) SLA_MID(0) else if (phi_kind == 1) SLA_MID(1) else SLA_MID(2)
+#undef SLA_MID
 }
 
 void launch_unfragment_kv(const Problem& p, const int8_t* k8, const uint8_t* v8, int8_t* k_codes,
