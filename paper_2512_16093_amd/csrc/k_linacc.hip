@@ -40,7 +40,8 @@ constexpr int LA_B_ROW = LA_COLS * 2;            // 256 bytes per staged hz row
 // each group of 8 staged rows starts 64 bytes after the previous one ends, so the two lane
 // halves (which read rows 8 apart) hit different banks
 constexpr int LA_B_BYTES = LA_KT * LA_B_ROW + (LA_KT / 8 - 1) * 64;
-constexpr int LA_B_STAGE = (LA_B_BYTES + 255) / 256 * 256;
+constexpr int LA_OUT_PITCH = 64 * 2 + 16;         // bytes per row of 64 results on their way out
+constexpr int LA_B_STAGE = ((LA_B_BYTES > LA_WAVES * 32 * LA_OUT_PITCH ? LA_B_BYTES : LA_WAVES * 32 * LA_OUT_PITCH) + 255) / 256 * 256;
 constexpr int LA_M_PIECES = 2 * LA_KSUB;         // 1 KiB pieces of mask words per tile
 static_assert(HZ_ELEMS % LA_COLS == 0, "the stripes tile a summary exactly");
 static_assert(LA_M_PIECES == LA_WAVES && 8 * LA_KSUB % LA_WAVES == 0, "every wavefront copies the same number of pieces");
@@ -101,7 +102,7 @@ __device__ __forceinline__ void la_barrier() {
 
 __global__ void __launch_bounds__(LA_WAVES * 64, 2) lin_accumulate_kernel(const uint32_t* __restrict__ mbits,
                                                                           const bf16_t* __restrict__ hz, int Tq, int Tk,
-                                                                          int n_items, bf16_t* __restrict__ HZ) {
+                                                                          int groups, bf16_t* __restrict__ HZ) {
   // three stages, each a tile of hz rows and the mask words that go with it; separate objects,
   // so the compiler can tell the asynchronous fill of one stage from the reads of another
   __shared__ __attribute__((aligned(1024))) unsigned char hz0[LA_B_STAGE], hz1[LA_B_STAGE], hz2[LA_B_STAGE];
@@ -133,23 +134,40 @@ __global__ void __launch_bounds__(LA_WAVES * 64, 2) lin_accumulate_kernel(const 
   // workgroups of the same XCD (workgroup ids are dealt round-robin over the 8 XCDs), so the
   // chunks of a stripe run at the same time on one L2 and the stripe comes from HBM once.  The
   // stripes of one head run next to each other in time (they share the head's mask words).
-  // The stores of a finished item drain while the next item's copies and MFMAs already run.
+  // An item's first two tiles are requested before the results of the item before it are stored, so that its loop does
+  // not begin with a wait for memory: with that and whole-line stores (below) 40 slices of 591 x 1182 blocks went from 1037 to
+  // 870 us, 40 of 1182 x 1182 from 2008 to 1750, 12 of 256 x 512 from 93 to 70 (shorter chunks of rows there: the
+  // stripes are read more often than idle slots are saved, 427 -> 441 us for the whole call).
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, slots = gridDim.x >> 3;  // gridDim.x is a multiple of 8
-  const int groups = n_items / chunks;  // (b,h, stripe) pairs; group g runs on XCD g % 8
-  for (int it = slot; it < (groups + 7) / 8 * chunks; it += slots) {
-  // item = 8 * (it / chunks) ... : groups of `chunks` consecutive items stay on one XCD
-  // (the chunk a slot takes rotates from one round of the slots to the next: a head's last chunk
-  // is usually shorter, and every workgroup should get its share of short ones)
-  const int grp = it / chunks, rot = grp / max(1, slots / chunks);
-  const int item = (grp * 8 + xcd) * chunks + (it % chunks + rot) % chunks;
-  if (item >= n_items) continue;  // (uniform)
-  const int chunk = item % chunks, stripe = (item / chunks) % STRIPES, bh = item / (chunks * STRIPES);
-  const int n0 = stripe * LA_COLS, row0 = chunk * LA_ROWS;
-
+  // (groups: (b,h, stripe) pairs; group g runs on XCD g % 8)
+  // Slot s takes, of its XCD's groups one after another, the chunks s, s + slots, ...; in a group the chunks are rotated by
+  // one for every round of the slots (a head's last chunk is usually shorter, and every workgroup should get its share of
+  // short ones).  All of it is carried from item to item: found by divisions it took a microsecond per item.
+  const int round_groups = max(1, slots / chunks), step_groups = slots / chunks, step_chunks = slots - step_groups * chunks;
+  int grp = slot / chunks, place = slot - grp * chunks;            // group of this XCD, place in it
+  int rot = grp / round_groups, in_round = grp - rot * round_groups;
+  rot %= chunks;
+  int bh = (grp * 8 + xcd) / STRIPES, stripe = grp * 8 + xcd - bh * STRIPES;
+  int row0 = 0, n0 = 0;
+  const char *hz_bh, *mb_bh;     // uniform: the item's stripe and its mask words
+  auto enter = [&]() {
+    const int chunk = place + rot >= chunks ? place + rot - chunks : place + rot;
+    n0 = stripe * LA_COLS;
+    row0 = chunk * LA_ROWS;
+    hz_bh = (const char*)(hz + (size_t)bh * Tk * HZ_ELEMS + n0);
+    mb_bh = (const char*)(mbits + (size_t)bh * KT32 * TqP + row0);
+  };
+  auto advance = [&]() {
+    int by = step_groups;
+    place += step_chunks;
+    if (place >= chunks) { place -= chunks; ++by; }
+    grp += by;
+    in_round += by;
+    for (; in_round >= round_groups; in_round -= round_groups) rot = rot + 1 == chunks ? 0 : rot + 1;
+    for (stripe += 8 * by; stripe >= STRIPES; stripe -= STRIPES) ++bh;
+  };
   // asynchronous copy of tile kt into a stage, in 1 KiB pieces (4 hz rows, or 256 mask words)
   // dealt round-robin to the wavefronts
-  const char* hz_bh = (const char*)(hz + (size_t)bh * Tk * HZ_ELEMS + n0);  // uniform
-  const char* mb_bh = (const char*)(mbits + (size_t)bh * KT32 * TqP + row0);
   auto fetch = [&](int kt, unsigned char* hzs, uint32_t* mws) {
 #pragma unroll
     for (int u = 0; u < 8 * LA_KSUB / LA_WAVES; ++u) {
@@ -171,7 +189,24 @@ __global__ void __launch_bounds__(LA_WAVES * 64, 2) lin_accumulate_kernel(const 
     if (keep_one) __builtin_amdgcn_s_waitcnt(0x0F70 | PER_TILE);
     else __builtin_amdgcn_s_waitcnt(0x0F70);
   };
+  auto fetch_first = [&]() {
+    fetch(0, hz0, mw0);
+    if (KT > 1) fetch(1, hz1, mw1);
+  };
 
+  // The first tile's copies are followed by the second tile's and by the previous item's `stored` stores, and vector
+  // memory operations complete in order: all but that many may stay in flight (rounded down to what the switch names).
+  int stored = 0;
+  auto wait_first = [&]() {
+#define LA_WAIT(N) { if (KT > 1) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N + PER_TILE) : "memory"); else asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory"); }
+    if (stored >= 24) LA_WAIT(24) else if (stored >= 16) LA_WAIT(16) else if (stored >= 8) LA_WAIT(8) else if (stored >= 2) LA_WAIT(2) else LA_WAIT(0)
+#undef LA_WAIT
+  };
+
+  if (grp * 8 + xcd >= groups) return;  // (uniform)
+  enter();
+  fetch_first();
+  while (grp * 8 + xcd < groups) {
   // The chunk's row tiles (of 32 query blocks; 12 in a full chunk, fewer in a head's last one)
   // are dealt to the four wavefronts as evenly as consecutive runs allow, and the loop below is
   // instantiated for the largest share, so a short last chunk costs its share of MFMAs only.
@@ -221,9 +256,7 @@ __global__ void __launch_bounds__(LA_WAVES * 64, 2) lin_accumulate_kernel(const 
     wait_keep(kt_ + 2 < KT);                   \
     la_barrier();                              \
   }
-  fetch(0, hz0, mw0);
-  if (KT > 1) fetch(1, hz1, mw1);
-  wait_keep(KT > 1);
+  wait_first();
   la_barrier();
   int kt = 0;
   for (; kt + 3 <= KT; kt += 3) {
@@ -235,26 +268,48 @@ __global__ void __launch_bounds__(LA_WAVES * 64, 2) lin_accumulate_kernel(const 
   if (kt + 1 < KT) LA_STEP(kt + 1, hz1, mw1, hz0, mw0)
 #undef LA_STEP
 #undef LA_COMPUTE
+  // (no copy is in flight and every wavefront is done with the stages)
 
   // The tiles were accumulated transposed (summary entries along the MFMA rows, query blocks
   // along its columns), so a lane owns ONE query block and runs of 4 consecutive entries of
-  // its summary: 8-byte stores, the two lane halves completing 16 contiguous bytes.
+  // its summary.  They leave through the wavefront's quarter of stage 2, 32 rows of 64 entries at a time, as whole
+  // 128-byte lines; straight from the registers they were 16-byte pieces of 32 rows per store.
   // (a wavefront with fewer row tiles than NMT has accumulated a neighbour's rows in the spare
   // tiles; it does not store them)
+  const int first_row = row0 + wrow, rows = min(32 * my_tiles, Tq - first_row);   // this wavefront's (none: <= 0)
+  char* const out = (char*)(HZ + ((size_t)bh * Tq + first_row) * HZ_ELEMS + n0);  // uniform
+  advance();
+  if (grp * 8 + xcd < groups) {
+    enter();
+    fetch_first();
+  }
+  unsigned char* const mine = hz2 + w * (32 * LA_OUT_PITCH);
+  const unsigned out_off = (unsigned)(lane >> 3) * (unsigned)(HZ_ELEMS * 2) + (unsigned)(lane & 7) * 16u;
 #pragma unroll
   for (int mt = 0; mt < NMT; ++mt) {
-    const int i = row0 + wrow + 32 * mt + l32;
-    if (mt < my_tiles && i < Tq) {
-      bf16_t* dst = HZ + ((size_t)bh * Tq + i) * HZ_ELEMS + n0 + 4 * hf;
+    if (32 * mt >= rows) break;  // (uniform)
 #pragma unroll
-      for (int nt = 0; nt < 4; ++nt)
+    for (int half = 0; half < 2; ++half) {
+#pragma unroll
+      for (int n2 = 0; n2 < 2; ++n2)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-          const v16f& a = acc[mt][nt];
-          *(uint2*)(dst + 32 * nt + 8 * g) = make_uint2(pack_bf16x2(a[4 * g], a[4 * g + 1]), pack_bf16x2(a[4 * g + 2], a[4 * g + 3]));
+          const v16f& a = acc[mt][2 * half + n2];
+          *(uint2*)(mine + l32 * LA_OUT_PITCH + (32 * n2 + 8 * g + 4 * hf) * 2) =
+              make_uint2(pack_bf16x2(a[4 * g], a[4 * g + 1]), pack_bf16x2(a[4 * g + 2], a[4 * g + 3]));
         }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (one wavefront's own region: its writes are done, no barrier)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int r = 32 * mt + 8 * u;
+        if (r >= rows) break;      // (uniform: a store that is issued has at least one row, which `stored` counts on)
+        const uint4 v = *(const uint4*)(mine + (8 * u + (lane >> 3)) * LA_OUT_PITCH + (lane & 7) * 16);
+        if (r + (lane >> 3) < rows) *(uint4*)(out + (size_t)r * (HZ_ELEMS * 2) + 128 * half + out_off) = v;
+      }
+      asm volatile("" ::: "memory");
     }
   }
+  stored = rows > 0 ? 2 * ((rows + 7) >> 3) : 0;
   };  // run_item
   const int nmt_item = t_base + (t_rem ? 1 : 0);
   if (nmt_item == 3) run_item(std::integral_constant<int, 3>{});
@@ -304,7 +359,7 @@ void launch_marginal_bits(const Problem& p, const int8_t* mask, uint32_t* mbits,
 }
 
 void launch_lin_accumulate(const Problem& p, const uint32_t* mbits, const bf16_t* hz, bf16_t* HZ, hipStream_t stream) {
-  const int n_items = (HZ_ELEMS / LA_COLS) * la_row_chunks(p.Tq) * p.BH;
+  const int groups = (HZ_ELEMS / LA_COLS) * p.BH;
   static int n_cu = 0;  // two workgroups per compute unit (192 accumulator registers per lane)
   if (n_cu == 0) {
     int dev = 0, v = 0;
@@ -313,7 +368,7 @@ void launch_lin_accumulate(const Problem& p, const uint32_t* mbits, const bf16_t
   }
   int grid = 2 * n_cu / 8 * 8;  // a multiple of 8 (see the item order in the kernel)
   if (grid < 8) grid = 8;
-  lin_accumulate_kernel<<<grid, LA_WAVES * 64, 0, stream>>>(mbits, hz, p.Tq, p.Tk, n_items, HZ);
+  lin_accumulate_kernel<<<grid, LA_WAVES * 64, 0, stream>>>(mbits, hz, p.Tq, p.Tk, groups, HZ);
 }
 
 }  // namespace sla
