@@ -178,13 +178,13 @@ void run_classify_prep(const void* k, const void* v, const void* proj_w, const P
 }
 
 // The unquantised forward pass (bf16 products): the launch sequence of sla_attention_fwd with
-// SLA_QUANT_NONE; save_lse2 / save_os, if given, receive what a backward pass can reuse.
+// SLA_QUANT_NONE; save, if given, receives what a backward pass can reuse.
 // With codes16 (SLA_QUANT_QK_INT8) the scores are the integer products of the INT8 codes of Q and of the
 // smoothed K: the codes travel as bf16 numbers, whose products and fp32 sums are exact, through the same
 // kernel; P and V stay 16-bit.
 int fwd_bf16(const void* q, const void* k, const void* v, void* out, const Problem& p, const void* proj_w,
-             const void* proj_b, int phi_kind, void* ws, const Workspace& W, hipStream_t s, int rec, float* save_lse2,
-             void* save_os, bool codes16 = false) {
+             const void* proj_b, int phi_kind, void* ws, const Workspace& W, hipStream_t s, int rec,
+             const SaveTo* save, bool codes16 = false) {
   const bool lin = p.n_m > 0;
   mark(s, rec, 0);
   run_pool(q, k, v, p, ws, W, s, codes16, codes16);
@@ -199,11 +199,11 @@ int fwd_bf16(const void* q, const void* k, const void* v, void* out, const Probl
   if (codes16)
     launch_code_tensors(p, at<int8_t>(ws, W.q8), at<int8_t>(ws, W.k8), at<bf16_t>(ws, W.qc), at<bf16_t>(ws, W.kc), s);
   mark(s, rec, 3);
-  if (lin) launch_lin_accumulate(p, at<uint32_t>(ws, W.m0), at<bf16_t>(ws, W.hz), at<bf16_t>(ws, W.HZ), s);
+  if (lin) launch_lin_accumulate(p, at<uint32_t>(ws, W.m0), at<bf16_t>(ws, W.hz), at<bf16_t>(ws, W.HZ), LinRiders{}, s);
   mark(s, rec, 4);
   const CodeScales cs{at<float>(ws, W.dq), at<float>(ws, W.dk), q};
   if (launch_fwd_bf16(p, codes16 ? at<bf16_t>(ws, W.qc) : q, codes16 ? at<bf16_t>(ws, W.kc) : k, v, at<int32_t>(ws, W.crit),
-                      lin ? at<bf16_t>(ws, W.HZ) : nullptr, (const bf16_t*)proj_b, phi_kind, out, save_lse2, save_os,
+                      lin ? at<bf16_t>(ws, W.HZ) : nullptr, (const bf16_t*)proj_b, phi_kind, out, save,
                       codes16 ? &cs : nullptr, s) != 0)
     return SLA_ERR_HIP;
   mark(s, rec, 5);
@@ -221,7 +221,7 @@ void run_prepass(const void* q, const void* k, const void* v, const void* proj_w
   mark(s, rec, 1);
   run_classify_prep(k, v, proj_w, p, phi_kind, ws, W, s, rec, true, lin, nullptr, nullptr);
   mark(s, rec, 3);
-  if (lin) launch_lin_accumulate(p, at<uint32_t>(ws, W.m0), at<bf16_t>(ws, W.hz), at<bf16_t>(ws, W.HZ), s);
+  if (lin) launch_lin_accumulate(p, at<uint32_t>(ws, W.m0), at<bf16_t>(ws, W.hz), at<bf16_t>(ws, W.HZ), LinRiders{}, s);
   mark(s, rec, 4);
 }
 
@@ -344,7 +344,7 @@ int sla_attention_fwd_strided(const void* q, const void* k, const void* v, void*
   hipStream_t s = (hipStream_t)stream;
   const int rec = (g_prof.ev && g_prof.used < g_prof.capacity) ? g_prof.used++ : -1;
   if (quant_mode != SLA_QUANT_QK_INT8_PV_FP8)
-    return fwd_bf16(q, k, v, out, p, proj_w, proj_b, phi_kind, workspace, W, s, rec, nullptr, nullptr,
+    return fwd_bf16(q, k, v, out, p, proj_w, proj_b, phi_kind, workspace, W, s, rec, nullptr,
                     quant_mode == SLA_QUANT_QK_INT8);
   run_prepass(q, k, v, proj_w, p, phi_kind, workspace, W, s, rec);
   run_attend(q, out, proj_b, p, phi_kind, workspace, W, s);
@@ -498,7 +498,7 @@ int sla_linear_attn_fwd(const void* q, const void* k, const void* v, const int8_
   run_stats(q, k, v, proj_w, p, ws, W, s, true);
   launch_prep_kv(run_prep_args(k, v, p, ws, W, false, true), p, phi_kind, s);
   launch_marginal_bits(p, mask, at<uint32_t>(ws, W.m0), s);
-  launch_lin_accumulate(p, at<uint32_t>(ws, W.m0), at<bf16_t>(ws, W.hz), at<bf16_t>(ws, W.HZ), s);
+  launch_lin_accumulate(p, at<uint32_t>(ws, W.m0), at<bf16_t>(ws, W.hz), at<bf16_t>(ws, W.HZ), LinRiders{}, s);
   // the attention kernel with an empty critical list leaves only the linear term
   launch_sparse_fwd(q, at<int8_t>(ws, W.q8), p, nullptr, 0, at<int8_t>(ws, W.k8), at<uint8_t>(ws, W.v8), at<float>(ws, W.dq),
                     at<float>(ws, W.dk), at<float>(ws, W.dv), at<bf16_t>(ws, W.HZ), (const bf16_t*)proj_b,
@@ -603,9 +603,8 @@ int sla_attention_fwd_train_strided(const void* q, const void* k, const void* v,
   const SavedState V = make_saved(p);
   if ((st = check_ws(saved, saved_bytes, V.total)) != SLA_OK) return st;
   const int rec = (g_prof.ev && g_prof.used < g_prof.capacity) ? g_prof.used++ : -1;
-  launch_write_saved_header(saved_header(p), at<SavedHeader>(saved, V.hdr), (hipStream_t)stream);
-  return fwd_bf16(q, k, v, out, p, proj_w, proj_b, phi_kind, workspace, W, (hipStream_t)stream, rec,
-                  at<float>(saved, V.lse2), at<bf16_t>(saved, V.os));
+  const SaveTo save{saved_header(p), at<int>(saved, V.hdr), at<float>(saved, V.lse2), at<bf16_t>(saved, V.os)};
+  return fwd_bf16(q, k, v, out, p, proj_w, proj_b, phi_kind, workspace, W, (hipStream_t)stream, rec, &save);
 }
 
 int sla_attention_bwd(const void* q, const void* k, const void* v, const void* dout, const void* proj_w,
@@ -681,17 +680,18 @@ int sla_attention_bwd_strided(const void* q, const void* k, const void* v, const
   if (dproj_b && !lin) launch_zero_u32((uint32_t*)dproj_b, (size_t)D, s);
   if (lin) {
     // H_i, Z_i of the forward pass (unprojected), then the linear branch's gradients
-    launch_lin_accumulate(p, at<uint32_t>(ws, W.m0), at<bf16_t>(ws, W.hz), at<bf16_t>(ws, W.HZ), s);
+    LinRiders first{}, second{};
+    first.mbits_t = at<uint32_t>(ws, X.mbits_t);
+    launch_lin_accumulate(p, at<uint32_t>(ws, W.m0), at<bf16_t>(ws, W.hz), at<bf16_t>(ws, W.HZ), first, s);
     if (launch_bwd_lin_q(p, q, dout, at<bf16_t>(ws, W.HZ), (const bf16_t*)proj_w, phi_kind, at<float>(ws, X.dql),
-                         at<bf16_t>(ws, X.dHZ), dproj_w, dproj_b, at<float>(ws, X.dw_part), s) != 0)
+                         at<bf16_t>(ws, X.dHZ), dproj_w, dproj_b, at<float>(ws, X.dw_part), &second.reduce, s) != 0)
       return SLA_ERR_HIP;
     // G_j = sum of dH_i over the query blocks that hold key block j as marginal: the forward's
     // accumulation kernel on the transposed mask (its output reuses the per-key-block summaries' buffer)
     Problem pt = p;
     pt.Tq = p.Tk;
     pt.Tk = p.Tq;
-    launch_marginal_bits_t(p, at<int8_t>(ws, W.mask), at<uint32_t>(ws, X.mbits_t), s);
-    launch_lin_accumulate(pt, at<uint32_t>(ws, X.mbits_t), at<bf16_t>(ws, X.dHZ), at<bf16_t>(ws, W.hz), s);
+    launch_lin_accumulate(pt, at<uint32_t>(ws, X.mbits_t), at<bf16_t>(ws, X.dHZ), at<bf16_t>(ws, W.hz), second, s);
   }
   mark(s, rec, 3);
   launch_bwd_dq(p, q, dout, k, v, at<int32_t>(ws, W.crit), lse2, at<float>(ws, X.delta),

@@ -297,7 +297,19 @@ bool stats_in_prep(const Problem& p);
 // launch_select, launch_bwd_delta (delta given) and launch_prep_kv in one launch.
 void launch_select_prep(const SelectArgs& S, const PrepArgs& P, const DeltaArgs* delta, const Problem& p, int phi_kind, hipStream_t stream);
 void launch_marginal_bits(const Problem& p, const int8_t* mask, uint32_t* mbits, hipStream_t stream);
-void launch_lin_accumulate(const Problem& p, const uint32_t* mbits, const bf16_t* hz, bf16_t* HZ,
+// dW, db = sums of n_part partial sums each (dw / db == nullptr: not wanted)
+struct ReduceArgs {
+  const float *dw_part, *db_part;
+  int n_part;
+  float *dw, *db;
+};
+// Small work that waits for the same launches as lin_accumulate does and runs as workgroups in front of its own: the bit
+// matrix transposed for the backward pass (mbits_t given; see lin_accumulate), a reduction (its outputs given).
+struct LinRiders {
+  uint32_t* mbits_t;
+  ReduceArgs reduce;
+};
+void launch_lin_accumulate(const Problem& p, const uint32_t* mbits, const bf16_t* hz, bf16_t* HZ, const LinRiders& riders,
                            hipStream_t stream);
 // (all_critical: every list names all key blocks in ascending order)
 void launch_sparse_fwd(const void* q, const int8_t* q8, const Problem& p, const int32_t* crit, int n_c, const int8_t* k8,
@@ -306,21 +318,27 @@ void launch_sparse_fwd(const void* q, const int8_t* q8, const Problem& p, const 
                        void* out, bool out_f32, float* lse, bool all_critical, hipStream_t stream);
 // Backward pass (k_bwd.hip, k_bwd_lin.hip; the transposed bit matrix lives with lin_accumulate).
 size_t marginal_bits_t_bytes(const Problem& p);
-void launch_marginal_bits_t(const Problem& p, const int8_t* mask, uint32_t* mbits_t, hipStream_t stream);
 void launch_bwd_stats(const Problem& p, const void* q, const void* k, const void* v, const void* dout,
                      const int32_t* crit, float* lse2, float* delta, hipStream_t stream);
+// First bytes of the state a training forward pass saves: which problem it belongs to.
+constexpr int SAVED_MAGIC = 0x534C4153;
+struct SavedHeader { int magic, B, H, N, block_q, n_c, pad0, pad1; };
+// Where that state goes: the header (256 bytes, written in full, so that two buffers filled for one problem are the same
+// bytes), the rows' base-2 log-sum-exp (padded to whole query blocks), O^s.
+struct SaveTo {
+  SavedHeader hdr;
+  int* hdr_dst;
+  float* lse2;
+  bf16_t* os;
+};
 // qk_scales: nullptr, or {delta_Q [BH,Tq], delta_K [BH,Tk]} when q and k hold INT8 codes (q_lin: the
 // original Q for the linear term's feature map)
 struct CodeScales { const float* dq; const float* dk; const void* q_lin; };
 int launch_fwd_bf16(const Problem& p, const void* q, const void* k, const void* v, const int32_t* crit,
-                    const bf16_t* HZ, const bf16_t* proj_b, int phi_kind, void* out, float* save_lse2, void* save_os,
+                    const bf16_t* HZ, const bf16_t* proj_b, int phi_kind, void* out, const SaveTo* save,
                     const CodeScales* codes, hipStream_t stream);
 void launch_unpack_q8(const Problem& p, const int8_t* q8, int8_t* q_codes, hipStream_t stream);
 void launch_code_tensors(const Problem& p, const int8_t* q8, const int8_t* k8, bf16_t* qc, bf16_t* kc, hipStream_t stream);
-// First bytes of the state a training forward pass saves: which problem it belongs to.
-constexpr int SAVED_MAGIC = 0x534C4153;
-struct SavedHeader { int magic, B, H, N, block_q, n_c, pad0, pad1; };
-void launch_write_saved_header(const SavedHeader& h, SavedHeader* dst, hipStream_t stream);
 // delta = dO . O^s and the log-sum-exp from a saved state (see delta.h)
 struct DeltaArgs {
   const bf16_t *dout, *os;
@@ -340,7 +358,7 @@ int launch_bwd_dkv(const Problem& p, const void* q, const void* dout, const void
 size_t bwd_lin_q_partial_bytes(const Problem& p);
 double launch_mfma_rate(int kind, int iters, int n_cu, float* sink, hipStream_t stream);
 int launch_bwd_lin_q(const Problem& p, const void* q, const void* dout, const bf16_t* HZ, const bf16_t* proj_w,
-                     int phi_kind, float* dq_lin, bf16_t* dHZ, float* dW, float* db, float* partials, hipStream_t stream);
+                     int phi_kind, float* dq_lin, bf16_t* dHZ, float* dW, float* db, float* partials, ReduceArgs* reduce, hipStream_t stream);
 void launch_zero_u32(uint32_t* p, size_t n, hipStream_t stream);
 void launch_unfragment_kv(const Problem& p, const int8_t* k8, const uint8_t* v8, int8_t* k_codes,
                           uint8_t* v_codes, hipStream_t stream);

@@ -361,6 +361,8 @@ struct FwdEpilogue {
   int phi;
   float* save_lse2;    // [BH, 32 T32q] or nullptr: the rows' log-sum-exp (base 2), as bwd_lse_delta_kernel writes it
   bf16_t* save_os;     // [BH, N, D] or nullptr: O^s alone (for delta = dO . O^s of a later backward pass)
+  int* save_hdr;       // 64 words or nullptr: the saved state's header, zeros behind it (the first workgroup writes it)
+  SavedHeader hdr;
   // CODES: q and k hold INT8 codes as bf16 numbers; a score is their (exact) product times
   // delta_Q[i] delta_K[j] / sqrt(d), and the feature map of the linear term reads the original Q
   const float* code_dq;  // [BH, Tq]
@@ -374,6 +376,14 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) fwd_bf16_kernel(cons
                                                             BwdDims dm, FwdEpilogue fe) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_all[];  // two buffers of: K (2 tiles) then V (2 tiles) of a key block
   int i, bh;
+  if (fe.save_hdr && blockIdx.x == 0 && threadIdx.x < 64) {
+    const int v[8] = {fe.hdr.magic, fe.hdr.B, fe.hdr.H, fe.hdr.N, fe.hdr.block_q, fe.hdr.n_c, fe.hdr.pad0, fe.hdr.pad1};
+    int x = 0;
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      if ((int)threadIdx.x == e) x = v[e];
+    fe.save_hdr[threadIdx.x] = x;
+  }
   if (!xcd_block(dm.Tq, i, bh)) return;
   SLA_BWD_LAYOUTS
   const int t = threadIdx.x, lane = t & 63, w = t >> 6, l32 = lane & 31, hf = lane >> 5;
@@ -1374,7 +1384,7 @@ void launch_bwd_stats(const Problem& p, const void* q, const void* k, const void
 // The unquantised forward pass; with `codes`, the same on
 // INT8 codes of Q and K (SLA_QUANT_QK_INT8: integer products, 16-bit P and V).
 int launch_fwd_bf16(const Problem& p, const void* q, const void* k, const void* v, const int32_t* crit,
-                    const bf16_t* HZ, const bf16_t* proj_b, int phi_kind, void* out, float* save_lse2, void* save_os,
+                    const bf16_t* HZ, const bf16_t* proj_b, int phi_kind, void* out, const SaveTo* save,
                     const CodeScales* codes, hipStream_t stream) {
   const unsigned grid = (unsigned)(8 * ((p.Tq + 7) / 8) * p.BH);
   static const bool ok = allow_lds(fwd_bf16_kernel<4, false, false>) && allow_lds(fwd_bf16_kernel<2, false, false>) &&
@@ -1382,7 +1392,8 @@ int launch_fwd_bf16(const Problem& p, const void* q, const void* k, const void* 
                          allow_lds(fwd_bf16_kernel<4, false, true>) && allow_lds(fwd_bf16_kernel<2, false, true>) &&
                          allow_lds(fwd_bf16_kernel<4, true, true>) && allow_lds(fwd_bf16_kernel<2, true, true>);
   if (!ok) return -1;
-  const FwdEpilogue fe{HZ, HZ ? proj_b : nullptr, (bf16_t*)out, phi_kind, save_lse2, (bf16_t*)save_os,
+  const FwdEpilogue fe{HZ, HZ ? proj_b : nullptr, (bf16_t*)out, phi_kind, save ? save->lse2 : nullptr, save ? save->os : nullptr,
+                       save ? save->hdr_dst : nullptr, save ? save->hdr : SavedHeader{},
                        codes ? codes->dq : nullptr, codes ? codes->dk : nullptr, codes ? (const bf16_t*)codes->q_lin : nullptr, p.lq};
   BwdDims dm = bwd_dims(p);
   if (codes) dm.lq = dm.lk = contiguous_layout(p.H, p.N);   // the code tensors are the library's own
@@ -1398,20 +1409,6 @@ int launch_fwd_bf16(const Problem& p, const void* q, const void* k, const void* 
 #undef SLA_FWD16_ST
 #undef SLA_FWD16
   return 0;
-}
-
-// (the header's 256 bytes are written in full, so that two buffers filled for one problem are the same bytes)
-__global__ void write_saved_header_kernel(SavedHeader h, int* __restrict__ dst) {
-  const int v[8] = {h.magic, h.B, h.H, h.N, h.block_q, h.n_c, h.pad0, h.pad1};
-  int x = 0;
-#pragma unroll
-  for (int e = 0; e < 8; ++e)
-    if ((int)threadIdx.x == e) x = v[e];
-  dst[threadIdx.x] = x;
-}
-
-void launch_write_saved_header(const SavedHeader& h, SavedHeader* dst, hipStream_t stream) {
-  write_saved_header_kernel<<<1, 64, 0, stream>>>(h, (int*)dst);
 }
 
 __global__ void __launch_bounds__(256) bwd_delta_kernel(const DeltaArgs X) { delta_block(X, blockIdx.x); }

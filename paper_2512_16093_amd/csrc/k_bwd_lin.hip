@@ -403,7 +403,7 @@ __global__ void __launch_bounds__(NW * 64, 1)
     if (db_part) tile_sums(Hl, t, dbacc, [](int) { return 1.0f; });
     lds_barrier();               // every tile is consumed
   }
-  // This workgroup's share of dW and db goes to its own slice; bwd_reduce_partials_kernel adds the
+  // This workgroup's share of dW and db goes to its own slice; reduce_block adds the
   // slices in a fixed order, so the sums do not depend on which workgroup finishes first.
   if (dW_part) {
     float* mine = dW_part + (size_t)blockIdx.x * (D * D);
@@ -427,43 +427,6 @@ __global__ void __launch_bounds__(NW * 64, 1)
   }
 }
 
-// dW[x] and db[x] = sum over p of part[p][x] in a fixed order.  Workgroups 0 .. 255 take 64 entries of dW each (dw
-// given), the last two 64 of db: 16 threads of four adjacent entries, 16 threads along p (every 16th partial, in four
-// sums), joined pairwise in LDS (one after the other, the largest sums were rounded 15 times over: db of 4 x 4617 tokens
-// off by 8.2e-8, now 5.9e-8).  Bound by reading the partials; with one thread per entry a chain of additions as long
-// as the list bound it (768 partials of 64 KiB, dW and db: 141 us in two launches, now 256 partials and 5 us).
-constexpr int RED_ENTRIES = 64;
-__global__ void __launch_bounds__(256) bwd_reduce_partials_kernel(const float* __restrict__ dw_part, const float* __restrict__ db_part,
-                                                                  int n_part, float* __restrict__ dw, float* __restrict__ db) {
-  __shared__ float4 red[16][16];
-  const int dw_blocks = dw ? D * D / RED_ENTRIES : 0, blk = blockIdx.x, t = threadIdx.x, col = t & 15, row = t >> 4;
-  const bool is_db = blk >= dw_blocks;
-  const int n = is_db ? D : D * D, x = (is_db ? blk - dw_blocks : blk) * RED_ENTRIES + 4 * col;
-  const float* part = (is_db ? db_part : dw_part) + x;
-  auto add = [](float4& a, const float4& b) __attribute__((always_inline)) { a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w; };
-  float4 s[4] = {};
-  int p = row;
-  for (; p + 48 < n_part; p += 64)
-#pragma unroll
-    for (int u = 0; u < 4; ++u) add(s[u], *(const float4*)(part + (size_t)(p + 16 * u) * n));
-  for (; p < n_part; p += 16) add(s[0], *(const float4*)(part + (size_t)p * n));
-  add(s[0], s[1]);
-  add(s[2], s[3]);
-  add(s[0], s[2]);
-  red[row][col] = s[0];
-  __syncthreads();
-  if (t < 16) {
-    float4 v[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) v[r] = red[r][t];
-#pragma unroll
-    for (int step = 1; step < 16; step *= 2)
-#pragma unroll
-      for (int r = 0; r < 16; r += 2 * step) add(v[r], v[r + step]);
-    *(float4*)((is_db ? db : dw) + x) = v[0];
-  }
-}
-
 // ---------------------------------------------------------------------------------------------
 // One workgroup per compute unit at most: the partial sums' buffer is sized by it.
 constexpr int LIN_Q_WORKGROUPS = 256;
@@ -472,7 +435,7 @@ size_t bwd_lin_q_partial_bytes(const Problem& p) { return (size_t)lin_q_grid(p) 
 
 template <int PHI>
 static int launch_bwd_lin_q_phi(const Problem& p, const void* q, const void* dout, const bf16_t* HZ, const bf16_t* proj_w,
-                                float* dq_lin, bf16_t* dHZ, float* dW, float* db, float* partials, hipStream_t stream) {
+                                float* dq_lin, bf16_t* dHZ, float* dW, float* db, float* partials, ReduceArgs* reduce, hipStream_t stream) {
   constexpr int LDS4 = 4 * 128 * TP + (2 + 4) * 128 * 4, LDS2 = (2 * 128 + 2 * 64) * TP + (2 + 2) * 128 * 4;
   static const bool ok =
       hipFuncSetAttribute((const void*)bwd_lin_q_kernel<4, PHI>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS4) == hipSuccess &&
@@ -486,16 +449,15 @@ static int launch_bwd_lin_q_phi(const Problem& p, const void* q, const void* dou
       (const bf16_t*)q, (const bf16_t*)dout, HZ, proj_w, dq_lin, dHZ, dW_part, db_part, p.N, p.Tq, p.BH * p.Tq, p.H, p.lq, p.ld)
   if (p.block_q == 128) SLA_LIN_Q(4, LDS4); else SLA_LIN_Q(2, LDS2);
 #undef SLA_LIN_Q
-  const int blocks = (dW ? D * D / RED_ENTRIES : 0) + (db ? D / RED_ENTRIES : 0);
-  if (blocks > 0) bwd_reduce_partials_kernel<<<(unsigned)blocks, 256, 0, stream>>>(dW_part, db_part, n_part, dW, db);
+  *reduce = ReduceArgs{dW_part, db_part, n_part, dW, db};
   return 0;
 }
 
 int launch_bwd_lin_q(const Problem& p, const void* q, const void* dout, const bf16_t* HZ, const bf16_t* proj_w,
-                     int phi_kind, float* dq_lin, bf16_t* dHZ, float* dW, float* db, float* partials, hipStream_t stream) {
-  if (phi_kind == 0) return launch_bwd_lin_q_phi<0>(p, q, dout, HZ, proj_w, dq_lin, dHZ, dW, db, partials, stream);
-  if (phi_kind == 1) return launch_bwd_lin_q_phi<1>(p, q, dout, HZ, proj_w, dq_lin, dHZ, dW, db, partials, stream);
-  return launch_bwd_lin_q_phi<2>(p, q, dout, HZ, proj_w, dq_lin, dHZ, dW, db, partials, stream);
+                     int phi_kind, float* dq_lin, bf16_t* dHZ, float* dW, float* db, float* partials, ReduceArgs* reduce, hipStream_t stream) {
+  if (phi_kind == 0) return launch_bwd_lin_q_phi<0>(p, q, dout, HZ, proj_w, dq_lin, dHZ, dW, db, partials, reduce, stream);
+  if (phi_kind == 1) return launch_bwd_lin_q_phi<1>(p, q, dout, HZ, proj_w, dq_lin, dHZ, dW, db, partials, reduce, stream);
+  return launch_bwd_lin_q_phi<2>(p, q, dout, HZ, proj_w, dq_lin, dHZ, dW, db, partials, reduce, stream);
 }
 
 }  // namespace sla

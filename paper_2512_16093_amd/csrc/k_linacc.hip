@@ -25,9 +25,10 @@
 // as they are (n contiguous) and read back with the LDS transposing read of gfx950
 // (ds_read_b64_tr_b16): the contraction index j is the slow index of hz, so one transposition
 // is unavoidable, and this one costs 8 LDS reads per 12 MFMAs and no vector-ALU work.
+#include <algorithm>
 #include <type_traits>
 
-#include "common.h"
+#include "reduce.h"
 
 namespace sla {
 
@@ -100,15 +101,47 @@ __device__ __forceinline__ void la_barrier() {
   asm volatile("" ::: "memory");
 }
 
+// The same bit matrix for the transposed mask (backward pass: sums over the query blocks that hold a key block as
+// marginal): mbits_t[bh][qt][j] (qt < ceil(Tq/32), j < la_rows_padded(Tk)): bit e = 1 where key block j is marginal for
+// query block 32 qt + e.  A wavefront transposes 64 query blocks x 32 key blocks by ballots; from the int8 mask,
+// byte by byte, it was a launch of 37 us at 40 slices of 591 x 1182 blocks and of 8 at 4 of 35 x 35.
+__device__ __forceinline__ void transpose_bits(const uint32_t* __restrict__ mbits, int Tq, int Tk, int BH, uint32_t* __restrict__ mbits_t,
+                                               int blk, int blocks) {
+  const int KT = la_k_tiles(Tk), TqP = la_rows_padded(Tq), QT = la_k_tiles(Tq), TkP = la_rows_padded(Tk), Q64 = (Tq + 63) / 64;
+  const int lane = threadIdx.x & 63;
+  const unsigned total = (unsigned)BH * KT * Q64;
+  for (unsigned x = blk * LA_WAVES + (threadIdx.x >> 6); x < total; x += blocks * LA_WAVES) {
+    const int bk = (int)(x / (unsigned)Q64), q64 = (int)(x - (unsigned)bk * Q64), bh = bk / KT, kt = bk - bh * KT;
+    const int i = 64 * q64 + lane;
+    const uint32_t word = i < Tq ? mbits[((size_t)bh * KT + kt) * TqP + i] : 0u;
+    uint32_t out = 0;
+#pragma unroll 4   // (all 32 at once would take every scalar register)
+    for (int b = 0; b < 32; ++b) {
+      const unsigned long long col = __ballot((word >> b) & 1u);
+      const uint32_t half = lane < 32 ? (uint32_t)col : (uint32_t)(col >> 32);
+      if ((lane & 31) == b) out = half;
+    }
+    const int qt = 2 * q64 + (lane >> 5);
+    if (qt < QT) mbits_t[((size_t)bh * QT + qt) * TkP + 32 * kt + (lane & 31)] = out;
+  }
+}
+
+// (RIDERS: an instance of its own, the branch to the small work costs the other one registers: 12 spilled, 2 to 4 % of short calls)
+template <bool RIDERS>
 __global__ void __launch_bounds__(LA_WAVES * 64, 2) lin_accumulate_kernel(const uint32_t* __restrict__ mbits,
                                                                           const bf16_t* __restrict__ hz, int Tq, int Tk,
-                                                                          int groups, bf16_t* __restrict__ HZ) {
+                                                                          int groups, bf16_t* __restrict__ HZ, int rider_blocks, int BH, LinRiders riders) {
   // three stages, each a tile of hz rows and the mask words that go with it; separate objects,
   // so the compiler can tell the asynchronous fill of one stage from the reads of another
   __shared__ __attribute__((aligned(1024))) unsigned char hz0[LA_B_STAGE], hz1[LA_B_STAGE], hz2[LA_B_STAGE];
   __shared__ __attribute__((aligned(1024))) uint32_t mw0[LA_KSUB * LA_M_ROWS], mw1[LA_KSUB * LA_M_ROWS], mw2[LA_KSUB * LA_M_ROWS];
   __shared__ uint4 lut[256];
   const int t = threadIdx.x, lane = t & 63, l32 = lane & 31, hf = lane >> 5;
+  if (RIDERS && (int)blockIdx.x < rider_blocks) {  // (the small work in front, LinRiders)
+    if (riders.mbits_t) transpose_bits(mbits, Tq, Tk, BH, riders.mbits_t, blockIdx.x, rider_blocks);
+    else reduce_block(riders.reduce, blockIdx.x, (float4(*)[16])hz0);
+    return;
+  }
   const int w = __builtin_amdgcn_readfirstlane(t >> 6);
   const int KT32 = la_k_tiles(Tk), KT = (KT32 + LA_KSUB - 1) / LA_KSUB, TqP = la_rows_padded(Tq);
   constexpr int STRIPES = HZ_ELEMS / LA_COLS;
@@ -138,7 +171,9 @@ __global__ void __launch_bounds__(LA_WAVES * 64, 2) lin_accumulate_kernel(const 
   // not begin with a wait for memory: with that and whole-line stores (below) 40 slices of 591 x 1182 blocks went from 1037 to
   // 870 us, 40 of 1182 x 1182 from 2008 to 1750, 12 of 256 x 512 from 93 to 70 (shorter chunks of rows there: the
   // stripes are read more often than idle slots are saved, 427 -> 441 us for the whole call).
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, slots = gridDim.x >> 3;  // gridDim.x is a multiple of 8
+  if constexpr (!RIDERS) rider_blocks = 0;
+  const int wg = blockIdx.x - rider_blocks;                          // (rider_blocks and the rest are multiples of 8)
+  const int xcd = wg & 7, slot = wg >> 3, slots = (gridDim.x - rider_blocks) >> 3;
   // (groups: (b,h, stripe) pairs; group g runs on XCD g % 8)
   // Slot s takes, of its XCD's groups one after another, the chunks s, s + slots, ...; in a group the chunks are rotated by
   // one for every round of the slots (a head's last chunk is usually shorter, and every workgroup should get its share of
@@ -318,33 +353,8 @@ __global__ void __launch_bounds__(LA_WAVES * 64, 2) lin_accumulate_kernel(const 
   }  // work items
 }
 
-// The same bit matrix for the transposed mask (backward pass: sums over the query blocks that hold a
-// key block as marginal): mbits_t[bh][qt][j] (qt < ceil(Tq/32), j < la_rows_padded(Tk)): bit e = 1 where
-// key block j is marginal for query block 32 qt + e.
-__global__ void marginal_bits_t_kernel(const int8_t* __restrict__ mask, int Tq, int Tk, int BH,
-                                       uint32_t* __restrict__ mbits_t) {
-  const int QT = la_k_tiles(Tq), TkP = la_rows_padded(Tk);
-  const size_t total = (size_t)BH * QT * Tk;
-  for (size_t x = (size_t)blockIdx.x * blockDim.x + threadIdx.x; x < total; x += (size_t)gridDim.x * blockDim.x) {
-    const int j = (int)(x % Tk), qt = (int)((x / Tk) % QT), bh = (int)(x / ((size_t)Tk * QT));
-    uint32_t w = 0;
-    for (int e = 0; e < 32; ++e) {
-      const int i = qt * 32 + e;
-      if (i < Tq && mask[((size_t)bh * Tq + i) * Tk + j] == 0) w |= 1u << e;
-    }
-    mbits_t[((size_t)bh * QT + qt) * TkP + j] = w;
-  }
-}
-
 size_t marginal_bits_t_bytes(const Problem& p) {
   return (size_t)p.BH * la_k_tiles(p.Tq) * la_rows_padded(p.Tk) * 4;
-}
-
-void launch_marginal_bits_t(const Problem& p, const int8_t* mask, uint32_t* mbits_t, hipStream_t stream) {
-  const size_t total = (size_t)p.BH * la_k_tiles(p.Tq) * p.Tk;
-  const size_t want = (total + 255) / 256;
-  const unsigned grid = (unsigned)(want < 1048560 ? want : 1048560);
-  marginal_bits_t_kernel<<<grid, 256, 0, stream>>>(mask, p.Tq, p.Tk, p.BH, mbits_t);
 }
 
 size_t marginal_bits_bytes(const Problem& p) {
@@ -358,7 +368,8 @@ void launch_marginal_bits(const Problem& p, const int8_t* mask, uint32_t* mbits,
   marginal_bits_kernel<<<grid, 256, 0, stream>>>(mask, p.Tq, p.Tk, p.BH, mbits);
 }
 
-void launch_lin_accumulate(const Problem& p, const uint32_t* mbits, const bf16_t* hz, bf16_t* HZ, hipStream_t stream) {
+void launch_lin_accumulate(const Problem& p, const uint32_t* mbits, const bf16_t* hz, bf16_t* HZ, const LinRiders& riders,
+                           hipStream_t stream) {
   const int groups = (HZ_ELEMS / LA_COLS) * p.BH;
   static int n_cu = 0;  // two workgroups per compute unit (192 accumulator registers per lane)
   if (n_cu == 0) {
@@ -368,7 +379,13 @@ void launch_lin_accumulate(const Problem& p, const uint32_t* mbits, const bf16_t
   }
   int grid = 2 * n_cu / 8 * 8;  // a multiple of 8 (see the item order in the kernel)
   if (grid < 8) grid = 8;
-  lin_accumulate_kernel<<<grid, LA_WAVES * 64, 0, stream>>>(mbits, hz, p.Tq, p.Tk, groups, HZ);
+  // (at most 128 workgroups of the transposition: a quarter of the slots for 8 us at 40 slices of 591 x 1182 blocks)
+  int rb = 0;
+  if (riders.mbits_t) rb = (int)std::min<long long>(128, ((long long)p.BH * la_k_tiles(p.Tk) * ((p.Tq + 63) / 64) + LA_WAVES - 1) / LA_WAVES);
+  else rb = reduce_blocks(riders.reduce);
+  rb = (rb + 7) & ~7;
+  if (rb > 0) lin_accumulate_kernel<true><<<grid + rb, LA_WAVES * 64, 0, stream>>>(mbits, hz, p.Tq, p.Tk, groups, HZ, rb, p.BH, riders);
+  else lin_accumulate_kernel<false><<<grid, LA_WAVES * 64, 0, stream>>>(mbits, hz, p.Tq, p.Tk, groups, HZ, 0, p.BH, riders);
 }
 
 }  // namespace sla
