@@ -216,14 +216,12 @@ __global__ void __launch_bounds__(256, 2) w8a8_gemm_kernel(
 #pragma unroll
     for (int u = 0; u < 4; ++u) w8_copy16(src, (unsigned)((w * 4 + u) * 1024 + lane * 16), dst + (w * 4 + u) * 1024);
   };
-  auto load_a = [&](int kb, v4i (&a)[2][4]) {
+
+  auto load_half = [&](int kb, int rtl, v4i (&a)[2][4]) __attribute__((always_inline)) {  // one of the two row tiles
     const unsigned char* src = xa + (size_t)kb * xkb;
 #pragma unroll
-    for (int rtl = 0; rtl < 2; ++rtl)
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) a[rtl][ks] = *(const v4i*)(src + (rtl * 4 + ks) * 1024);
+    for (int ks = 0; ks < 4; ++ks) a[rtl][ks] = *(const v4i*)(src + (rtl * 4 + ks) * 1024);
   };
-
   v16f facc[2][4];
 #pragma unroll
   for (int r = 0; r < 2; ++r)
@@ -246,7 +244,7 @@ __global__ void __launch_bounds__(256, 2) w8a8_gemm_kernel(
   // window (and the registers it needs).
   v16i pend = bias16;   // finished chain still to be scaled in (token tile 1, output tile 3); none yet: s = 0
   float pend_sc = 0.f;
-  auto compute = [&](int kb, const v4i (&a)[2][4]) {
+  auto compute = [&](int kb, const v4i (&a)[2][4], auto more) __attribute__((always_inline)) {
     const float mag = sx[(size_t)kb * RBx + rb] * sw[(size_t)kb * RBw + nt] * W8_STEP_INV;
     const float sc = (kb & 1) ? -mag : mag;
     const uint4* st = bst[kb % 3];
@@ -274,6 +272,7 @@ __global__ void __launch_bounds__(256, 2) w8a8_gemm_kernel(
       w8_scale_in(acc0, sc, facc[0][ct]);
       asm volatile("" : "+v"(facc[0][ct]) : : "memory");
       asm volatile("" : "+v"(pend) : : "memory");
+      more(ct);
       __builtin_amdgcn_sched_barrier(0);
     }
     csum += sc;
@@ -281,20 +280,25 @@ __global__ void __launch_bounds__(256, 2) w8a8_gemm_kernel(
 
   // Pipeline.  The weight tiles run two feature blocks ahead of the products (three LDS stages),
   // the activation operands one block ahead (two register sets).  At the top of step kb
-  // everything this wavefront has requested is waited for -- all of it was requested at least a
-  // whole block earlier; the barrier then publishes everybody's share of stage kb and retires
-  // stage kb - 1, which the copy of block kb + 2 overwrites.
+  // everything this wavefront has requested is waited for -- all of it was requested at least
+  // half a block earlier; the barrier then publishes everybody's share of stage kb and retires
+  // stage kb - 1, which the copy of block kb + 2 overwrites.  The activations are requested behind
+  // the first and the second quarter of the products, not in one burst behind the barrier: the memory path
+  // has to deliver 47 of its 64 bytes per clock and compute unit at full matrix rate.  With that and the bias read
+  // at once (below) the layer went from 2120 to 1990 us at 75600 x 5120 -> 5120, from 550 to 473 at 32760 x 1536 -> 8960; with
+  // no operand loads at all (timing only) it would be 1610 us.  Requests ahead into L2 made it slower (2040 us): it is
+  // not the latency.
   fetch_b(0);
   if (KB > 1) fetch_b(1);
-  load_a(0, a0);
+  load_half(0, 0, a0);
+  load_half(0, 1, a0);
 #define W8_STEP(KBI, ACUR, ANEXT)                       \
   {                                                     \
     const int kb_ = (KBI);                              \
     __builtin_amdgcn_s_waitcnt(0x0F70); /* vmcnt(0) */  \
     w8_barrier();                                       \
     if (kb_ + 2 < KB) fetch_b(kb_ + 2);                 \
-    if (kb_ + 1 < KB) load_a(kb_ + 1, ANEXT);           \
-    compute(kb_, ACUR);                                 \
+    compute(kb_, ACUR, [&](int ct) __attribute__((always_inline)) { if (ct < 2) load_half(min(kb_ + 1, KB - 1), ct, ANEXT); }); \
   }
   {
     int kb = 0;
@@ -315,17 +319,25 @@ __global__ void __launch_bounds__(256, 2) w8a8_gemm_kernel(
   w8_barrier();  // every wavefront is done with the stages
   unsigned char* my = (unsigned char*)bst + w * (32 * W8_EPI_STRIDE);
   const int n0 = nt * W8_WG_N;
+  uint2 bw[4][4];   // (all sixteen at once: one by one behind a test for a bias each waited for memory by itself)
+#pragma unroll
+  for (int ct = 0; ct < 4; ++ct)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) bw[ct][g] = make_uint2(0u, 0u);
+  if (bias) {
+#pragma unroll
+    for (int ct = 0; ct < 4; ++ct)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) bw[ct][g] = *(const uint2*)(bias + n0 + 32 * ct + 8 * g + 4 * hf);
+  }
 #pragma unroll
   for (int r = 0; r < 2; ++r) {
 #pragma unroll
     for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
-        float bv[4] = {0.f, 0.f, 0.f, 0.f};
-        if (bias) {
-          const uint2 bw = *(const uint2*)(bias + n0 + 32 * ct + 8 * g + 4 * hf);
-          bv[0] = bf16_lo(bw.x); bv[1] = bf16_hi(bw.x); bv[2] = bf16_lo(bw.y); bv[3] = bf16_hi(bw.y);
-        }
+        const uint2 b4 = bw[ct][g];
+        const float bv[4] = {bf16_lo(b4.x), bf16_hi(b4.x), bf16_lo(b4.y), bf16_hi(b4.y)};
         const v16f& f = facc[r][ct];
         *(uint2*)(my + l32 * W8_EPI_STRIDE + (32 * ct + 8 * g + 4 * hf) * 2) =
             make_uint2(pack_bf16x2(f[4 * g] - corr + bv[0], f[4 * g + 1] - corr + bv[1]),
@@ -512,12 +524,11 @@ static void launch_splitk(const int8_t* x8, const float* sx, int MP, const int8_
 void launch_w8a8_gemm(const int8_t* x8, const float* sx, int MP, const int8_t* w8, const float* sw,
                       const void* bias, void* y, int M, int N, int K, hipStream_t stream) {
   const int MT = MP / W8_WG_M, NT = N / W8_WG_N, KB = K / QB;
-  // Large tiles once every compute unit has one (256 of them), small split tiles below that.  Measured around the
-  // line, large / small in us: 5120 -> 5120 at 1536 tokens (240 tiles) 64.3 / 61.3, at 2048 (320) 74.9 / 81.5;
-  // 1536 -> 1536 at 4096 tokens (192) 24.0 / 18.5, at 8192 (384) 30.6 / 33.4.  A contraction of one or two blocks
-  // leaves the large kernel's pipeline empty: there the line lies higher (256 -> 5120 at 4096 tokens, 640 tiles,
-  // 22.9 / 19.5; at 16384 tokens, 2560 tiles, 64.4 / 63.5).
-  if (MT * NT < 256 || (KB <= 2 && MT * NT <= 640)) {
+  // Large tiles once they occupy most compute units, small split tiles below that.  Measured around the line, whole layer
+  // in us, large / small: 5120 -> 5120 at 1024 tokens (160 tiles) 60.7 / 54.0, 1280 (200) 61.4 / 60.6, 1536 (240) 63.0 / 67.4;
+  // 1536 -> 1536 at 4096 tokens (192) 29.2 / 28.1, at 6144 (288) 36.4 / 41.6.  Of a short contraction splitting has less to
+  // win: 640 -> 2560 at 2048 tokens (160) 16.1 / 18.3, 512 -> 2560 at 1300 (120) 16.6 / 17.2, at 1000 (80) 15.9 / 15.2.
+  if (MT * NT < (KB <= 5 ? 128 : 200)) {
     // Of the small variants the one with the most work per wavefront that still brings at least 1024 wavefronts,
     // one per SIMD (5120 -> 5120 in us, the large kernel last: 1 token 6.0 | 67.6, 64: 8.5 | 68.2, 256: 16.1 | 69.3,
     // 512: 23.8 | 72.9, 1024: 46 | 74.4).

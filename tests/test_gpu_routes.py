@@ -43,3 +43,32 @@ def test_few_and_many_slices_give_the_same_bits(N, block_q, rc, rm, w, quant):
     few = sla.sla_attention_fwd(*(x[:, pick].contiguous() for x in (q, k, v)), block_q, 64, rc, rm, **kw)
     assert torch.isfinite(few).all()
     assert torch.equal(whole[:, pick], few)
+
+
+@pytest.mark.parametrize("M, K, N", [
+    (2032, 640, 2048),    # 128 tiles of 256 x 128 (the last token tile ragged), five feature blocks: large tiles
+    (1792, 640, 2304),    # 126: small ones
+    (6145, 128, 1024),    # one feature block, 25 token tiles of which the last holds one token
+    (2560, 768, 2560),    # 200 tiles, six blocks: large
+    (2304, 768, 2816),    # 198: small
+])
+@pytest.mark.parametrize("with_bias", [True, False])
+def test_linear_layer_on_both_sides_of_the_tile_rule(M, K, N, with_bias):
+    """Against the product of the layer's own codes in 64 bits.  Bound per output: a bf16 step (twice its rounding), and of each of
+    the K / 128 blocks two steps of its scale (the accumulation rounds at a magnitude of at most 2^25 steps)."""
+    g = torch.Generator(device="cuda").manual_seed(M + K)
+    x = torch.randn((M, K), generator=g, device="cuda").to(torch.bfloat16)
+    w = (torch.randn((N, K), generator=g, device="cuda") / K ** 0.5).to(torch.bfloat16)
+    b = (0.1 * torch.randn((N,), generator=g, device="cuda")).to(torch.bfloat16) if with_bias else None
+    wq = sla.w8a8_quantize_weight(w)
+    xc, xs = sla.w8a8_debug_unpack(sla.w8a8_quantize_act(x), False, M, K)
+    wc, ws = sla.w8a8_debug_unpack(wq, True, N, K)
+    ref = torch.zeros((M, N), dtype=torch.float64, device="cuda") + (b.double() if with_bias else 0.0)
+    steps = torch.zeros((M, N), dtype=torch.float64, device="cuda")
+    for kb in range(K // 128):
+        scale = xs[:, kb].double().repeat_interleave(128)[:M, None] * ws[:, kb].double().repeat_interleave(128)[None, :]
+        ref += scale * (xc[:, kb * 128:(kb + 1) * 128].double() @ wc[:, kb * 128:(kb + 1) * 128].double().T)
+        steps += 2.0 * scale
+    y = sla.w8a8_linear_fwd(x, wq, N, bias=b).double()
+    assert ((y - ref).abs() <= steps + 2.0 ** -8 * ref.abs()).all()
+    assert torch.linalg.norm(y - ref) / torch.linalg.norm(ref) < 3e-3
