@@ -51,13 +51,24 @@ __device__ __forceinline__ void slice_stats(const PrepArgs& P, int bh, bool publ
     }
   }
 }
-// W[row][col .. col + 7] (the identity if no projection is given), straight from the caller's matrix.
-__device__ __forceinline__ v8bf w_operand(const PrepArgs& P, int row, int col) {
-  if (P.w_aligned) return *(const v8bf*)(P.proj_w + row * D + col);
-  union { bf16_t e[8]; v8bf v; } x;
+// Row `row` of W (the identity if no projection is given) as product 1's operands, columns 16 ks + col .. + 7, straight
+// from the caller's matrix.  (One test for all of them: behind a test each they waited for memory one by one.)
+__device__ __forceinline__ void w_operands(const PrepArgs& P, int row, int col, v8bf (&out)[8]) {
+  if (P.w_aligned) {
 #pragma unroll
-  for (int e = 0; e < 8; ++e) x.e[e] = P.proj_w ? P.proj_w[row * D + col + e] : (row == col + e ? (bf16_t)0x3f80 : (bf16_t)0);
-  return x.v;
+    for (int ks = 0; ks < 8; ++ks) out[ks] = *(const v8bf*)(P.proj_w + row * D + 16 * ks + col);
+  } else {
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+      union { bf16_t e[8]; v8bf v; } x;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int c = 16 * ks + col + e;
+        x.e[e] = P.proj_w ? P.proj_w[row * D + c] : (row == c ? (bf16_t)0x3f80 : (bf16_t)0);
+      }
+      out[ks] = x.v;
+    }
+  }
 }
 // The four query blocks 4 blk .. 4 blk + 3 of a slice: their scores against all (at most 64 KPL) key blocks, formed as
 // scores_kernel forms them (the same products in the same order; a wavefront has a tile of 32 key blocks, 28 of the 32
@@ -255,10 +266,16 @@ __device__ __forceinline__ void prep_block(const PrepArgs& P, int blk) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) *(uint4*)(vbf + (4 * m + r) * STAGE_STRIDE + cg * 16) = vraw[r];
   }
+  const int hfl = lane >> 5, l32 = lane & 31;
+  v8bf wop[8];   // this wavefront's 32 rows of W
+  if constexpr (STATS) w_operands(P, 32 * w + l32, 8 * hfl, wop);
+  else {
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) wop[ks] = *(const v8bf*)(wfrag + ((w * 8 + ks) * 64 + lane) * 8);
+  }
   __syncthreads();  // phit, zred and the V rows are complete
 
   // ---- product 1: VW[row][o] for o in this wavefront's tile of 32 output channels
-  const int hfl = lane >> 5, l32 = lane & 31;
   v16f d1[2];
 #pragma unroll
   for (int rt = 0; rt < 2; ++rt) {
@@ -267,8 +284,7 @@ __device__ __forceinline__ void prep_block(const PrepArgs& P, int blk) {
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) {
       const v8bf a = *(const v8bf*)(vbf + row * STAGE_STRIDE + 32 * ks + 16 * hfl);
-      const v8bf b = STATS ? w_operand(P, 32 * w + l32, 16 * ks + 8 * hfl) : *(const v8bf*)(wfrag + ((w * 8 + ks) * 64 + lane) * 8);
-      d1[rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, d1[rt], 0, 0, 0);
+      d1[rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, wop[ks], d1[rt], 0, 0, 0);
     }
   }
 
