@@ -19,6 +19,7 @@
 // product that contracts over the channels reads its operand with one 16-byte read per step; a
 // product that contracts over the tile's tokens reads the same tile with the transposing LDS read
 // of gfx950 (ds_read_b64_tr_b16), so no transposed copy of any tensor is ever made.
+#include <algorithm>
 #include <initializer_list>
 
 #include "common.h"
@@ -940,6 +941,67 @@ __device__ __forceinline__ void linear_kv_share(const bf16_t* __restrict__ k, co
   __syncthreads();  // the staged G is consumed: the caller may reuse the LDS
 }
 
+// The order in which dK/dV's workgroups (KB = 1) are started.  Their lists differ in length by more than threefold, and in the
+// order of the key blocks the last long ones ran on alone: of 12 heads x 512 key blocks the slots stood empty for a
+// seventh of the launch, of 40 x 1182 for 3.5 %.  Longest first (in classes of four query blocks) leaves 1 %; the order
+// costs two small launches.  Each XCD orders its own eighth: of every eight consecutive key blocks one, at a place
+// that changes from group to group.
+__device__ __forceinline__ int dkv_dealt(int g, int xcd) { return 8 * g + ((xcd - (g + (g >> 3) + (g >> 6))) & 7); }
+// counts[bh * Tk + j] = query blocks that hold key block j of slice bh as critical; 64 key blocks x 16 rows per workgroup.
+__global__ void __launch_bounds__(1024) dkv_counts_kernel(const int8_t* __restrict__ mask, int Tq, int Tk, int* __restrict__ counts) {
+  __shared__ int part[16][64];
+  const int runs = (Tk + 63) / 64, bh = blockIdx.x / runs, l = threadIdx.x & 63, rg = threadIdx.x >> 6;
+  const int j = 64 * (blockIdx.x - bh * runs) + l;
+  const int8_t* col = mask + (size_t)bh * Tq * Tk + min(j, Tk - 1);
+  int n = 0;
+#pragma unroll 8
+  for (int i = rg; i < Tq; i += 16) n += col[(size_t)i * Tk] == 1 ? 1 : 0;
+  part[rg][l] = n;
+  __syncthreads();
+  if (rg == 0 && j < Tk) {
+#pragma unroll
+    for (int r = 1; r < 16; ++r) n += part[r][l];
+    counts[(size_t)bh * Tk + j] = n;
+  }
+}
+// order[xcd * per + slot] = first + x (x = bh * Tk + j of the ordered heads), lists of more query blocks first (-1: no
+// workgroup); one workgroup per XCD.
+constexpr int DKV_CLASSES = 2048;
+__global__ void __launch_bounds__(1024) dkv_order_kernel(const int* __restrict__ counts, int total, int per, int first,
+                                                         int* __restrict__ order) {
+  __shared__ int start[DKV_CLASSES];   // of each class, the longest lists' first
+  __shared__ int wsum[16];
+  const int t = threadIdx.x, xcd = blockIdx.x, lane = t & 63, w = t >> 6;
+  auto place = [&](int g) {            // class of this XCD's key block of group g
+    const int x = dkv_dealt(g, xcd);
+    return DKV_CLASSES - 1 - (x < total ? min(DKV_CLASSES - 1, 1 + (counts[x] >> 2)) : 0);
+  };
+  for (int c = t; c < DKV_CLASSES; c += 1024) start[c] = 0;
+  __syncthreads();
+  for (int g = t; g < per; g += 1024) atomicAdd(&start[place(g)], 1);
+  __syncthreads();
+  // exclusive sums over the classes, two per thread
+  const int a = start[2 * t], b = start[2 * t + 1];
+  int sum = a + b;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int up = __shfl_up(sum, o);
+    if (lane >= o) sum += up;
+  }
+  if (lane == 63) wsum[w] = sum;
+  __syncthreads();
+  int before = sum - a - b;
+  for (int x = 0; x < w; ++x) before += wsum[x];
+  start[2 * t] = before;
+  start[2 * t + 1] = before + a;
+  __syncthreads();
+  // (which of two equally long lists goes first is left to the atomics: the results do not depend on the order)
+  for (int g = t; g < per; g += 1024) {
+    const int x = dkv_dealt(g, xcd), slot = atomicAdd(&start[place(g)], 1);
+    order[(size_t)xcd * per + slot] = x < total ? first + x : -1;
+  }
+}
+
 // One workgroup of four wavefronts per PAIR of adjacent key blocks (2 J, 2 J + 1): wavefronts 0, 1
 // own the two key tiles of the first block, wavefronts 2, 3 those of the second (one key per lane
 // pair).  The workgroup walks over the query blocks that hold either block as critical (found from
@@ -959,7 +1021,7 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
                                                       const int8_t* __restrict__ mask, const float* __restrict__ lse2,
                                                       const float* __restrict__ delta, const bf16_t* __restrict__ G,
                                                       bf16_t* __restrict__ dk, bf16_t* __restrict__ dv, int pair_shift,
-                                                      BwdDims dm) {
+                                                      const int* __restrict__ order, int natural, BwdDims dm) {
   constexpr int NT = 128 * KB, ROWS = 32 * TILES;  // threads; query rows per step
   // two buffers of: Q (TILES tiles) then dO (TILES tiles) of ROWS consecutive query rows; then their lse, delta
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
@@ -968,7 +1030,14 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
   unsigned short* qlist = (unsigned short*)(lds + 2 * BUF_B + 2 * 2 * ROWS * 4);  // [Tq]
   __shared__ int wcnt[4];
   int J, bh;
-  if (!xcd_block((dm.Tk + KB - 1) / KB, J, bh)) return;
+  if (KB == 1 && (int)blockIdx.x >= natural) {
+    const int x = order[(blockIdx.x & 7) * ((gridDim.x - natural) >> 3) + ((blockIdx.x - natural) >> 3)];   // (natural: a multiple of 8)
+    if (x < 0) return;
+    bh = x / dm.Tk;
+    J = x - bh * dm.Tk;
+  } else if (!xcd_block((dm.Tk + KB - 1) / KB, J, bh)) {
+    return;
+  }
   const int t = threadIdx.x, lane = t & 63, w = t >> 6, l32 = lane & 31, hf = lane >> 5;
   const int tr_off = tr_lane_offset(lane);
   const int half = KB == 2 ? w >> 1 : 0;
@@ -1438,7 +1507,7 @@ void launch_bwd_dq(const Problem& p, const void* q, const void* dout, const void
 
 template <int PHI, bool ST>
 static int launch_bwd_dkv_phi(const Problem& p, const void* q, const void* dout, const void* k, const void* v, const int8_t* mask,
-                               const float* lse2, const float* delta, const bf16_t* G, void* dk, void* dv, hipStream_t stream) {
+                               const float* lse2, const float* delta, const bf16_t* G, void* dk, void* dv, int* order_ws, hipStream_t stream) {
   // dynamic LDS: two staging buffers, the rows' lse and delta, the list of query blocks
   const int list_bytes = (2 * p.Tq + 15) & ~15;
   const int lds2 = 2 * 4 * TILE_B + 2 * 2 * 64 * 4 + list_bytes;
@@ -1456,27 +1525,40 @@ static int launch_bwd_dkv_phi(const Problem& p, const void* q, const void* dout,
     const int pairs = (p.Tk + 1) / 2;
     bwd_dkv_kernel<2, 2, PHI, ST><<<(unsigned)(8 * ((pairs + 7) / 8) * p.BH), 256, lds2, stream>>>(
         (const bf16_t*)q, (const bf16_t*)dout, (const bf16_t*)k, (const bf16_t*)v, mask, lse2, delta, G,
-        (bf16_t*)dk, (bf16_t*)dv, tiles == 4 ? 1 : 0, bwd_dims(p));
+        (bf16_t*)dk, (bf16_t*)dv, tiles == 4 ? 1 : 0, nullptr, 0, bwd_dims(p));
   } else {
-    bwd_dkv_kernel<1, 2, PHI, ST><<<(unsigned)(8 * ((p.Tk + 7) / 8) * p.BH), 128, lds1, stream>>>(
+    // An order only where workgroups wait for a place (two fit a compute unit), and only of the last heads, as many as
+    // the memory-side cache holds Q and dO of: what counts is the end of the launch, and with all of 40 x 75600 tokens
+    // under way at once 25.8 ms became 29.6.
+    const long long head_bytes = 4ll * p.N * D;
+    const int heads = (int)std::min<long long>(p.BH, std::max<long long>(1, (224ll << 20) / head_bytes));
+    const bool ordered = order_ws && p.BH * p.Tk > 2 * 256;
+    const int first = ordered ? p.BH - heads : p.BH, total = heads * p.Tk, per = (total + 7) / 8;
+    const int natural = 8 * ((p.Tk + 7) / 8) * first;
+    int *counts = order_ws, *order = order_ws + total;
+    if (ordered) {
+      dkv_counts_kernel<<<(unsigned)(heads * ((p.Tk + 63) / 64)), 1024, 0, stream>>>(mask + (size_t)first * p.Tq * p.Tk, p.Tq, p.Tk, counts);
+      dkv_order_kernel<<<8, 1024, 0, stream>>>(counts, total, per, first * p.Tk, order);
+    }
+    bwd_dkv_kernel<1, 2, PHI, ST><<<(unsigned)natural + (ordered ? 8u * (unsigned)per : 0u), 128, lds1, stream>>>(
         (const bf16_t*)q, (const bf16_t*)dout, (const bf16_t*)k, (const bf16_t*)v, mask, lse2, delta, G,
-        (bf16_t*)dk, (bf16_t*)dv, tiles == 4 ? 1 : 0, bwd_dims(p));
+        (bf16_t*)dk, (bf16_t*)dv, tiles == 4 ? 1 : 0, order, natural, bwd_dims(p));
   }
   return 0;
 }
 
 // (the feature map matters to the prologue only -- the linear branch's share -- and only when G is given)
 int launch_bwd_dkv(const Problem& p, const void* q, const void* dout, const void* k, const void* v, const int8_t* mask,
-                   const float* lse2, const float* delta, const bf16_t* G, int phi_kind, void* dk, void* dv, hipStream_t stream) {
+                   const float* lse2, const float* delta, const bf16_t* G, int phi_kind, void* dk, void* dv, int* order_ws, hipStream_t stream) {
   const int phi = G ? phi_kind : 0;
   if (contiguous(p, {&p.lq, &p.lk, &p.lv, &p.ld, &p.ldk, &p.ldv})) {
-    if (phi == 0) return launch_bwd_dkv_phi<0, false>(p, q, dout, k, v, mask, lse2, delta, G, dk, dv, stream);
-    if (phi == 1) return launch_bwd_dkv_phi<1, false>(p, q, dout, k, v, mask, lse2, delta, G, dk, dv, stream);
-    return launch_bwd_dkv_phi<2, false>(p, q, dout, k, v, mask, lse2, delta, G, dk, dv, stream);
+    if (phi == 0) return launch_bwd_dkv_phi<0, false>(p, q, dout, k, v, mask, lse2, delta, G, dk, dv, order_ws, stream);
+    if (phi == 1) return launch_bwd_dkv_phi<1, false>(p, q, dout, k, v, mask, lse2, delta, G, dk, dv, order_ws, stream);
+    return launch_bwd_dkv_phi<2, false>(p, q, dout, k, v, mask, lse2, delta, G, dk, dv, order_ws, stream);
   }
-  if (phi == 0) return launch_bwd_dkv_phi<0, true>(p, q, dout, k, v, mask, lse2, delta, G, dk, dv, stream);
-  if (phi == 1) return launch_bwd_dkv_phi<1, true>(p, q, dout, k, v, mask, lse2, delta, G, dk, dv, stream);
-  return launch_bwd_dkv_phi<2, true>(p, q, dout, k, v, mask, lse2, delta, G, dk, dv, stream);
+  if (phi == 0) return launch_bwd_dkv_phi<0, true>(p, q, dout, k, v, mask, lse2, delta, G, dk, dv, order_ws, stream);
+  if (phi == 1) return launch_bwd_dkv_phi<1, true>(p, q, dout, k, v, mask, lse2, delta, G, dk, dv, order_ws, stream);
+  return launch_bwd_dkv_phi<2, true>(p, q, dout, k, v, mask, lse2, delta, G, dk, dv, order_ws, stream);
 }
 
 }  // namespace sla

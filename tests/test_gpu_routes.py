@@ -72,3 +72,26 @@ def test_linear_layer_on_both_sides_of_the_tile_rule(M, K, N, with_bias):
     y = sla.w8a8_linear_fwd(x, wq, N, bias=b).double()
     assert ((y - ref).abs() <= steps + 2.0 ** -8 * ref.abs()).all()
     assert torch.linalg.norm(y - ref) / torch.linalg.norm(ref) < 3e-3
+
+
+@pytest.mark.parametrize("H, N, block_q, rc, rm", [
+    (9, 4033, 128, 0.1, 0.2),    # 9 x 64 key blocks: just more than the chip holds at a time, all in the order of their lists' lengths
+    (41, 1000, 64, 0.2, 0.4),    # 41 x 16, a last group of eight that is short
+    (513, 65, 64, 0.5, 0.0),     # two query blocks per slice: no room for an order, the order of the key blocks
+    (60, 8192, 128, 0.05, 0.1),  # Q and dO of the last 56 heads fit the memory-side cache: four heads before them in their own order
+])
+def test_order_of_the_key_blocks_leaves_their_gradients_alone(H, N, block_q, rc, rm):
+    """dK and dV of a slice, from a saved state, do not depend on how many others there are and when their workgroups start."""
+    g = torch.Generator(device="cuda").manual_seed(N)
+    q, k, v, do = (torch.randn((1, H, N, D), generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(4))
+
+    def grads(*xs):
+        _, saved = sla.sla_attention_fwd_train(*xs[:3], block_q, 64, rc, rm)
+        return sla.sla_attention_bwd(*xs, block_q, 64, rc, rm, saved=saved)[1:3]
+
+    whole = grads(q, k, v, do)
+    pick = [0, 3, H - 1]
+    few = grads(*(x[:, pick].contiguous() for x in (q, k, v, do)))
+    for a, b in zip(whole, few):
+        assert torch.isfinite(b).all()
+        assert torch.equal(a[:, pick], b)
