@@ -171,9 +171,10 @@ void run_classify_prep(const void* k, const void* v, const void* proj_w, const P
   } else {
     run_scores(proj_w, p, ws, W, s, quant, lin);
   }
-  mark(s, rec, 2);
   const SelectArgs S{at<float>(ws, W.scores), p.BH * p.Tq, p.Tq, p.Tk, p.n_c, p.n_m, mask, at<int32_t>(ws, W.crit), nullptr,
                      lin ? at<uint32_t>(ws, W.m0) : nullptr};
+  if (!select_in_prep(p)) launch_select(p, S.scores, S.mask, S.crit, S.marg, S.mbits, s);
+  mark(s, rec, 2);
   launch_select_prep(S, P, delta, p, phi_kind, s);
 }
 

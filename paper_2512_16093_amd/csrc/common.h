@@ -184,8 +184,8 @@ struct Workspace {
   size_t m0;                // uint32 marginal bit matrix [BH, ceil(Tk/32), Tq rounded up to 384, + 128]: bit e of word (kt, i) = block 32 kt + e marginal for query block i
   size_t crit, marg;        // int32 [BH,Tq,n_c], [BH,Tq,n_m]
   size_t k8, v8;            // [BH,Tk] records of KV_FRAG_BYTES
-  size_t hz;                // bf16 [BH,Tk,HZ_ROWS,D] (before prep_kv: max|V| per 128 tokens, fp32 [BH,ceil(N/128),D])
-  size_t HZ;                // bf16 [BH,Tq,HZ_ROWS,D]
+  size_t hz;                // bf16 [BH,Tk,HZ_ROWS,D]
+  size_t HZ;                // bf16 [BH,Tq,HZ_ROWS,D] (before lin_accumulate: max|V| per 128 tokens, fp32 [BH,ceil(N/128),D])
   size_t wfrag;             // bf16 [D,D]: the projection (identity if none) in the operand order of prep_kv
   size_t qc, kc;            // bf16 [BH,N,D]: INT8 codes of Q and K as bf16 numbers (SLA_QUANT_QK_INT8 only)
   size_t total;
@@ -294,7 +294,8 @@ struct SelectArgs {
 };
 struct DeltaArgs;
 bool stats_in_prep(const Problem& p);
-// launch_select, launch_bwd_delta (delta given) and launch_prep_kv in one launch.
+bool select_in_prep(const Problem& p);
+// launch_select (where select_in_prep()), launch_bwd_delta (delta given) and launch_prep_kv in one launch.
 void launch_select_prep(const SelectArgs& S, const PrepArgs& P, const DeltaArgs* delta, const Problem& p, int phi_kind, hipStream_t stream);
 void launch_marginal_bits(const Problem& p, const int8_t* mask, uint32_t* mbits, hipStream_t stream);
 // dW, db = sums of n_part partial sums each (dw / db == nullptr: not wanted)

@@ -20,7 +20,7 @@
 // is dealt to the wavefronts in even runs of row tiles and runs a copy of the loop with fewer
 // tiles per wavefront.  Tiles are accumulated transposed (the hz fragment is the MFMA's A
 // operand) so that a lane ends up with runs of consecutive entries of one query block's
-// summary and can store 8 bytes at a time.  Operand tiles for 64 key blocks at a time are
+// summary, which leave through LDS as whole lines.  Operand tiles for 64 key blocks at a time are
 // copied global -> LDS asynchronously, three stages deep (one barrier per tile).  hz rows are copied
 // as they are (n contiguous) and read back with the LDS transposing read of gfx950
 // (ds_read_b64_tr_b16): the contraction index j is the slow index of hz, so one transposition

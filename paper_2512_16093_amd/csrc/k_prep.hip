@@ -427,6 +427,11 @@ void launch_prep_kv(const PrepArgs& P, const Problem& p, int phi_kind, hipStream
 // blocks, 160 workgroups, 75.0 / 73.6).
 bool stats_in_prep(const Problem& p) { return p.Tk <= 64 && (long long)p.BH * ((p.Tq + 3) / 4) <= 1024; }
 
+// Long rows are selected in a launch of their own: 40 slices of 591 x 1182 blocks take 163 us there and 1003 us with
+// prep_block's, in one launch 1020 (prep_block's shared memory leaves the selection half of the wavefronts it hides
+// its latency with); 12 slices of 256 x 512 blocks 137 us in two, 124 in one.
+bool select_in_prep(const Problem& p) { return p.Tk <= 8 * 64; }
+
 void launch_select_prep(const SelectArgs& S, const PrepArgs& P, const DeltaArgs* delta, const Problem& p, int phi_kind, hipStream_t stream) {
   MidArgs A{};
   A.S = S; A.P = P;
@@ -436,14 +441,7 @@ void launch_select_prep(const SelectArgs& S, const PrepArgs& P, const DeltaArgs*
     A.X = *delta;
     A.delta_blocks = delta_blocks(p);
   }
-  // Long rows are selected in a launch of their own: 40 slices of 591 x 1182 blocks take 163 us there and 1003 us with
-  // prep_block's, in one launch 1020 (prep_block's shared memory leaves the selection half of the wavefronts it hides
-  // its latency with); 12 slices of 256 x 512 blocks 137 us in two, 124 in one.
-  if (!stats && need > 8) {
-    launch_select(p, S.scores, S.mask, S.crit, S.marg, S.mbits, stream);
-  } else {
-    A.select_blocks = stats ? p.BH * ((p.Tq + 3) / 4) : (S.rows + 3) / 4;
-  }
+  if (select_in_prep(p)) A.select_blocks = stats ? p.BH * ((p.Tq + 3) / 4) : (S.rows + 3) / 4;
   const unsigned grid = (unsigned)(A.select_blocks + A.delta_blocks + p.BH * p.Tk);
 #define SLA_MID(PHI) { if (stats) select_prep_kernel<PHI, 1, true><<<grid, 256, 0, stream>>>(A); \
                        else if (need <= 2) select_prep_kernel<PHI, 2, false><<<grid, 256, 0, stream>>>(A); \

@@ -315,7 +315,6 @@ __global__ void __launch_bounds__(256, 2) w8a8_gemm_kernel(
   // Epilogue: constant share out, bias in, bf16, through LDS so that rows leave as 256 contiguous
   // bytes.  Lane = token 32 rt + l32 of this wavefront; registers 4 g .. 4 g + 3 of tile ct =
   // outputs 32 ct + 8 g + 4 hf + 0..3.
-  const float corr = W8_C0 * csum;
   w8_barrier();  // every wavefront is done with the stages
   unsigned char* my = (unsigned char*)bst + w * (32 * W8_EPI_STRIDE);
   const int n0 = nt * W8_WG_N;
@@ -339,9 +338,10 @@ __global__ void __launch_bounds__(256, 2) w8a8_gemm_kernel(
         const uint2 b4 = bw[ct][g];
         const float bv[4] = {bf16_lo(b4.x), bf16_hi(b4.x), bf16_lo(b4.y), bf16_hi(b4.y)};
         const v16f& f = facc[r][ct];
+        auto sum = [&](float x) __attribute__((always_inline)) { return __builtin_fmaf(-W8_C0, csum, x); };   // (the constants' share, not rounded by itself)
         *(uint2*)(my + l32 * W8_EPI_STRIDE + (32 * ct + 8 * g + 4 * hf) * 2) =
-            make_uint2(pack_bf16x2(f[4 * g] - corr + bv[0], f[4 * g + 1] - corr + bv[1]),
-                       pack_bf16x2(f[4 * g + 2] - corr + bv[2], f[4 * g + 3] - corr + bv[3]));
+            make_uint2(pack_bf16x2(sum(f[4 * g]) + bv[0], sum(f[4 * g + 1]) + bv[1]),
+                       pack_bf16x2(sum(f[4 * g + 2]) + bv[2], sum(f[4 * g + 3]) + bv[3]));
       }
     __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wavefront's staging writes are done
     asm volatile("" ::: "memory");
