@@ -126,7 +126,7 @@ __device__ __forceinline__ void transpose_bits(const uint32_t* __restrict__ mbit
   }
 }
 
-// (RIDERS: an instance of its own, the branch to the small work costs the other one registers: 12 spilled, 2 to 4 % of short calls)
+// (RIDERS: an instance of its own: one for both spilled registers and made short forward calls 2 to 4 % slower)
 template <bool RIDERS>
 __global__ void __launch_bounds__(LA_WAVES * 64, 2) lin_accumulate_kernel(const uint32_t* __restrict__ mbits,
                                                                           const bf16_t* __restrict__ hz, int Tq, int Tk,
@@ -319,7 +319,11 @@ __global__ void __launch_bounds__(LA_WAVES * 64, 2) lin_accumulate_kernel(const 
     fetch_first();
   }
   unsigned char* const mine = hz2 + w * (32 * LA_OUT_PITCH);
-  const unsigned out_off = (unsigned)(lane >> 3) * (unsigned)(HZ_ELEMS * 2) + (unsigned)(lane & 7) * 16u;
+  unsigned ln = lane;
+  asm volatile("" : "+v"(ln));   // (the addresses below are formed per item: kept through the loop they cost registers that it has not got)
+  const unsigned out_off = (ln >> 3) * (unsigned)(HZ_ELEMS * 2) + (ln & 7) * 16u;
+  unsigned char* const put = mine + (ln & 31) * LA_OUT_PITCH + (ln >> 5) * 8;
+  const unsigned char* const get = mine + (ln >> 3) * LA_OUT_PITCH + (ln & 7) * 16;
 #pragma unroll
   for (int mt = 0; mt < NMT; ++mt) {
     if (32 * mt >= rows) break;  // (uniform)
@@ -330,7 +334,7 @@ __global__ void __launch_bounds__(LA_WAVES * 64, 2) lin_accumulate_kernel(const 
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const v16f& a = acc[mt][2 * half + n2];
-          *(uint2*)(mine + l32 * LA_OUT_PITCH + (32 * n2 + 8 * g + 4 * hf) * 2) =
+          *(uint2*)(put + (32 * n2 + 8 * g) * 2) =
               make_uint2(pack_bf16x2(a[4 * g], a[4 * g + 1]), pack_bf16x2(a[4 * g + 2], a[4 * g + 3]));
         }
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (one wavefront's own region: its writes are done, no barrier)
@@ -338,8 +342,8 @@ __global__ void __launch_bounds__(LA_WAVES * 64, 2) lin_accumulate_kernel(const 
       for (int u = 0; u < 4; ++u) {
         const int r = 32 * mt + 8 * u;
         if (r >= rows) break;      // (uniform: a store that is issued has at least one row, which `stored` counts on)
-        const uint4 v = *(const uint4*)(mine + (8 * u + (lane >> 3)) * LA_OUT_PITCH + (lane & 7) * 16);
-        if (r + (lane >> 3) < rows) *(uint4*)(out + (size_t)r * (HZ_ELEMS * 2) + 128 * half + out_off) = v;
+        const uint4 v = *(const uint4*)(get + 8 * u * LA_OUT_PITCH);
+        if (r + (int)(ln >> 3) < rows) *(uint4*)(out + (size_t)r * (HZ_ELEMS * 2) + 128 * half + out_off) = v;
       }
       asm volatile("" ::: "memory");
     }
