@@ -287,7 +287,8 @@ __global__ void __launch_bounds__(256, 2) w8a8_gemm_kernel(
   // has to deliver 47 of its 64 bytes per clock and compute unit at full matrix rate.  With that and the bias read
   // at once (below) the layer went from 2120 to 1990 us at 75600 x 5120 -> 5120, from 550 to 473 at 32760 x 1536 -> 8960; with
   // no operand loads at all (timing only) it would be 1610 us.  Requests ahead into L2 made it slower (2040 us): it is
-  // not the latency.
+  // not the latency.  (The last step requests its own block's activations once more, 8 KiB per wavefront that nobody
+  // reads: the schedule stays the same for every step.)
   fetch_b(0);
   if (KB > 1) fetch_b(1);
   load_half(0, 0, a0);
@@ -524,14 +525,19 @@ static void launch_splitk(const int8_t* x8, const float* sx, int MP, const int8_
 void launch_w8a8_gemm(const int8_t* x8, const float* sx, int MP, const int8_t* w8, const float* sw,
                       const void* bias, void* y, int M, int N, int K, hipStream_t stream) {
   const int MT = MP / W8_WG_M, NT = N / W8_WG_N, KB = K / QB;
-  // Large tiles once they occupy most compute units, small split tiles below that.  Measured around the line, whole layer
-  // in us, large / small: 5120 -> 5120 at 1024 tokens (160 tiles) 60.7 / 54.0, 1280 (200) 61.4 / 60.6, 1536 (240) 63.0 / 67.4;
-  // 1536 -> 1536 at 4096 tokens (192) 29.2 / 28.1, at 6144 (288) 36.4 / 41.6.  Of a short contraction splitting has less to
-  // win: 640 -> 2560 at 2048 tokens (160) 16.1 / 18.3, 512 -> 2560 at 1300 (120) 16.6 / 17.2, at 1000 (80) 15.9 / 15.2.
-  if (MT * NT < (KB <= 5 ? 128 : 200)) {
+  // Large tiles once they occupy most compute units, small split tiles below that; of a short contraction splitting has
+  // less to win, so its line lies lower.  Whole layer in us, large / small, around each line:
+  // one or two feature blocks (128 tiles): 128 -> 1024 at 4096 tokens (128 tiles) 11.7 / 11.6, -> 256 at 23243 (182) 11.7 /
+  //   12.9, -> 5120 at 4096 (640) 16.8 / 21.2; 256 -> 4096 at 1024 (128) 11.8 / 11.6, -> 2560 at 2048 (160) 12.2 / 12.7,
+  //   -> 5120 at 4096 (640) 19.6 / 24.2;
+  // three to five (160): 640 -> 1024 at 4096 (128) 15.2 / 14.2, -> 2048 at 2304 (144) 15.2 / 14.5, -> 2176 at 2304 (153)
+  //   15.8 / 14.7, -> 1024 at 5120 (160) 15.4 / 15.3, -> 4096 at 1280 (160) 14.7 / 15.3, -> 1152 at 6400 (225) 17.3 / 18.3;
+  //   384 -> 1024 at 4096 (128) 13.1 / 12.5, -> 4096 at 1280 (160) 12.8 / 13.2;
+  // more (200): 1536 -> 1536 at 4096 (192) 26.2 / 24.8, -> 5120 at 1280 (200) 23.2 / 24.4; 5120 -> 1536 at 4096 (192)
+  //   60.2 / 56.4, -> 5120 at 1280 (200) 54.7 / 55.0, -> 5120 at 1536 (240) 56.1 / 62.6.
+  if (MT * NT < (KB <= 2 ? 128 : KB <= 5 ? 160 : 200)) {
     // Of the small variants the one with the most work per wavefront that still brings at least 1024 wavefronts,
-    // one per SIMD (5120 -> 5120 in us, the large kernel last: 1 token 6.0 | 67.6, 64: 8.5 | 68.2, 256: 16.1 | 69.3,
-    // 512: 23.8 | 72.9, 1024: 46 | 74.4).
+    // one per SIMD (the product of 5120 -> 5120 at 1 token 6.0 us, 64 8.5, 256 16.1, 512 23.8, 1024 46).
     auto waves = [&](int rt, int ct, int ks) { return (long long)((M + 32 * rt - 1) / (32 * rt)) * (N / (32 * ct)) * ks; };
 #define W8_SPLITK(RT, CT, KS) launch_splitk<RT, CT, KS>(x8, sx, MP, w8, sw, bias, y, M, N, K, stream)
     if (waves(2, 2, 1) >= 1024) W8_SPLITK(2, 2, 1);

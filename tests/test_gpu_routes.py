@@ -46,8 +46,11 @@ def test_few_and_many_slices_give_the_same_bits(N, block_q, rc, rm, w, quant):
 
 
 @pytest.mark.parametrize("M, K, N", [
-    (2032, 640, 2048),    # 128 tiles of 256 x 128 (the last token tile ragged), five feature blocks: large tiles
-    (1792, 640, 2304),    # 126: small ones
+    (2032, 256, 2048),    # 128 tiles of 256 x 128 (the last token tile ragged), two feature blocks: large tiles
+    (1792, 256, 2304),    # 126: small ones
+    (2300, 384, 2304),    # 162 tiles, three blocks: large
+    (2560, 640, 2048),    # 160 tiles, five blocks: large
+    (2300, 640, 2176),    # 153: small
     (6145, 128, 1024),    # one feature block, 25 token tiles of which the last holds one token
     (2560, 768, 2560),    # 200 tiles, six blocks: large
     (2304, 768, 2816),    # 198: small
