@@ -421,15 +421,18 @@ void launch_prep_kv(const PrepArgs& P, const Problem& p, int phi_kind, hipStream
 }
 
 // One launch for scores, selection and operands where a slice has at most 64 key blocks: the statistics that every
-// workgroup then joins for itself cost as much as a launch from there on (2 slices, us for the whole forward call, two
-// launches / one: 16 blocks 38.2 / 33.6, 64 blocks 47.1 / 43.8, 128 blocks 55.6 / 57.0; 8 slices of 64 blocks 66.1 / 66.0),
-// and while its workgroups of four query blocks, each of which pays for a product of 32 rows, are few (40 slices of 16
-// blocks, 160 workgroups, 75.0 / 73.6).
-bool stats_in_prep(const Problem& p) { return p.Tk <= 64 && (long long)p.BH * ((p.Tq + 3) / 4) <= 1024; }
+// workgroup then joins for itself cost as much as a launch from there on (2 slices of 128 blocks, us for the whole forward
+// call, two launches / one: 55.6 / 57.0), and while the workgroups of four query blocks, each of which pays for a product of 32
+// rows, are few.  Query blocks of 64, slices x key blocks: 2 x 16 34.2 / 29.8, 40 x 16 (160 workgroups) 71.9 / 68.8, 8 x 64 (128)
+// 60.8 / 57.6, 24 x 64 (384) 115.6 / 115.8, 40 x 48 (480) 141.4 / 140.5, 40 x 64 (640) 194.1 / 202.0, 64 x 64 (1024) 297.7 / 312.5;
+// of 128: 40 x 64 (320) 173.1 / 172.7, 64 x 48 (384) 214.5 / 213.1, 80 x 48 (480) 257.8 / 260.7, 80 x 64 (640) 315.0 / 339.7.
+bool stats_in_prep(const Problem& p) { return p.Tk <= 64 && (long long)p.BH * ((p.Tq + 3) / 4) <= 384; }
 
 // Long rows are selected in a launch of their own: 40 slices of 591 x 1182 blocks take 163 us there and 1003 us with
 // prep_block's, in one launch 1020 (prep_block's shared memory leaves the selection half of the wavefronts it hides
-// its latency with); 12 slices of 256 x 512 blocks 137 us in two, 124 in one.
+// its latency with).  Up to 512 blocks one launch is never slower (everything before the attention kernel in us, two / one: 12
+// slices of 256 x 512 288 / 270, 40 of 256 x 512 847 / 835, 40 of 512 x 512 1046 / 1045); instances for longer rows would still
+// help few slices (2 of 350 x 700 110 / 89, 12 of 450 x 900 565 / 550) and not many (40 of 700 x 700 1585 / 1593).
 bool select_in_prep(const Problem& p) { return p.Tk <= 8 * 64; }
 
 void launch_select_prep(const SelectArgs& S, const PrepArgs& P, const DeltaArgs* delta, const Problem& p, int phi_kind, hipStream_t stream) {

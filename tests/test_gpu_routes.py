@@ -24,12 +24,12 @@ def _weight(offset, seed=4):
 
 @pytest.mark.parametrize("quant", [sla.QUANT_QK_INT8_PV_FP8, sla.QUANT_NONE])
 @pytest.mark.parametrize("N, block_q, rc, rm, w", [
-    (25, 64, 1.0, 0.0, None),     # one short key block, no linear branch
+    (25, 64, 1.0, 0.0, None),     # one short key block, no linear branch (in 16 bits both sides take the same launches)
     (81, 128, 0.5, 0.5, 0),       # two key blocks, the projection aligned
     (189, 64, 0.34, 0.66, 1),     # three query blocks (one wavefront of the four without a row), W off by two bytes
     (1000, 128, 0.2, 0.4, None),  # a ragged last key block, no projection
     (4033, 64, 0.1, 0.2, 1),      # 64 key blocks, the last of one token: the longest slice of the one-launch route
-    (4097, 128, 0.1, 0.2, 0),     # 65: the shortest of the other
+    (4097, 128, 0.1, 0.2, 0),     # 65: the shortest of the other, whatever its company: both sides take the same launches
 ])
 def test_few_and_many_slices_give_the_same_bits(N, block_q, rc, rm, w, quant):
     """Few slices of few blocks are classified, joined and quantised in one launch, many of them in two; a slice's
@@ -43,6 +43,32 @@ def test_few_and_many_slices_give_the_same_bits(N, block_q, rc, rm, w, quant):
     few = sla.sla_attention_fwd(*(x[:, pick].contiguous() for x in (q, k, v)), block_q, 64, rc, rm, **kw)
     assert torch.isfinite(few).all()
     assert torch.equal(whole[:, pick], few)
+
+
+@pytest.mark.parametrize("saved", [True, False])
+@pytest.mark.parametrize("N, block_q, rc, rm, w, phi", [
+    (81, 128, 0.5, 0.5, 0, sla.PHI_ELU1),        # two key blocks, one query block
+    (189, 64, 0.34, 0.66, None, sla.PHI_RELU),   # three query blocks, no projection
+    (1000, 64, 0.2, 0.4, 1, sla.PHI_SOFTMAX),    # a ragged last block, W off by two bytes
+    (4033, 128, 0.1, 0.2, 0, sla.PHI_ELU1),      # 64 key blocks, the last of one token
+])
+def test_gradients_of_few_and_many_slices_have_the_same_bits(N, block_q, rc, rm, w, phi, saved):
+    """The backward pass takes more from the launch that few slices share: the mask, the unprojected summaries, delta."""
+    many = 1024 // (((N + block_q - 1) // block_q + 3) // 4) + 1
+    q, k, v = _qkv(many, N)
+    do = _qkv(many, N, seed=5)[2]
+    kw = dict(proj_w=None if w is None else _weight(w), phi_kind=phi)
+
+    def grads(*xs):
+        state = sla.sla_attention_fwd_train(*xs[:3], block_q, 64, rc, rm, **kw)[1] if saved else None
+        return sla.sla_attention_bwd(*xs, block_q, 64, rc, rm, saved=state, **kw)[:3]
+
+    whole = grads(q, k, v, do)
+    pick = [0, many // 2, many - 1]
+    few = grads(*(x[:, pick].contiguous() for x in (q, k, v, do)))
+    for a, b in zip(whole, few):
+        assert torch.isfinite(b).all()
+        assert torch.equal(a[:, pick], b)
 
 
 @pytest.mark.parametrize("M, K, N", [
