@@ -247,6 +247,15 @@ struct Problem {
   Layout ld, ldq, ldk, ldv;  // backward pass: of dout, dq, dk and dv
 };
 
+// Compute units of the device that was current at the first call (the library's workspaces and kernels are for one kind of GPU).
+inline int compute_units() {
+  static const int n = [] {
+    int dev = 0, v = 0;
+    return hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0 ? v : 256;
+  }();
+  return n;
+}
+
 // Launchers (one per kernel file); every one only enqueues work on `stream`.
 // (v == nullptr: no statistics of V, vmax_part unused; vmax_part: fp32 [BH, ceil(N/128), D])
 void launch_pool_stats(const void* q, const void* k, const void* v, const Problem& p, float* qbar,

@@ -375,13 +375,8 @@ void launch_marginal_bits(const Problem& p, const int8_t* mask, uint32_t* mbits,
 void launch_lin_accumulate(const Problem& p, const uint32_t* mbits, const bf16_t* hz, bf16_t* HZ, const LinRiders& riders,
                            hipStream_t stream) {
   const int groups = (HZ_ELEMS / LA_COLS) * p.BH;
-  static int n_cu = 0;  // two workgroups per compute unit (192 accumulator registers per lane)
-  if (n_cu == 0) {
-    int dev = 0, v = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0) v = 256;
-    n_cu = v;
-  }
-  int grid = 2 * n_cu / 8 * 8;  // a multiple of 8 (see the item order in the kernel)
+  // two workgroups per compute unit (192 accumulator registers per lane); a multiple of 8 (see the item order in the kernel)
+  int grid = 2 * compute_units() / 8 * 8;
   if (grid < 8) grid = 8;
   // (at most 128 workgroups of the transposition: a quarter of the slots for 8 us at 40 slices of 591 x 1182 blocks)
   int rb = 0;
