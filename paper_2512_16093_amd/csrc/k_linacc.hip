@@ -43,6 +43,11 @@ constexpr int LA_B_ROW = LA_COLS * 2;            // 256 bytes per staged hz row
 constexpr int LA_B_BYTES = LA_KT * LA_B_ROW + (LA_KT / 8 - 1) * 64;
 constexpr int LA_OUT_PITCH = 64 * 2 + 16;         // bytes per row of 64 results on their way out
 constexpr int LA_B_STAGE = ((LA_B_BYTES > LA_WAVES * 32 * LA_OUT_PITCH ? LA_B_BYTES : LA_WAVES * 32 * LA_OUT_PITCH) + 255) / 256 * 256;
+// Heads of at most this many query blocks store their results straight from the registers: a wavefront or two have a row tile,
+// and the way through LDS costs them more than whole lines save.  Query blocks, heads x key blocks, us through LDS / directly:
+// 16, 40 x 16 28.4 / 24.1; 24, 40 x 48 32.4 / 26.5; 36, 12 x 72 19.8 / 18.3; 40, 40 x 40 31.9 / 30.3; 40, 40 x 80 46.2 / 46.3;
+// 44, 40 x 88 48.3 / 55.5; 64, 40 x 128 57.4 / 75.1.
+constexpr int LA_DIRECT_ROWS = 40;
 constexpr int LA_M_PIECES = 2 * LA_KSUB;         // 1 KiB pieces of mask words per tile
 static_assert(HZ_ELEMS % LA_COLS == 0, "the stripes tile a summary exactly");
 static_assert(LA_M_PIECES == LA_WAVES && 8 * LA_KSUB % LA_WAVES == 0, "every wavefront copies the same number of pieces");
@@ -308,7 +313,7 @@ __global__ void __launch_bounds__(LA_WAVES * 64, 2) lin_accumulate_kernel(const 
   // The tiles were accumulated transposed (summary entries along the MFMA rows, query blocks
   // along its columns), so a lane owns ONE query block and runs of 4 consecutive entries of
   // its summary.  They leave through the wavefront's quarter of stage 2, 32 rows of 64 entries at a time, as whole
-  // 128-byte lines; straight from the registers they were 16-byte pieces of 32 rows per store.
+  // 128-byte lines; straight from the registers (short heads) they are 16-byte pieces of 32 rows per store.
   // (a wavefront with fewer row tiles than NMT has accumulated a neighbour's rows in the spare
   // tiles; it does not store them)
   const int first_row = row0 + wrow, rows = min(32 * my_tiles, Tq - first_row);   // this wavefront's (none: <= 0)
@@ -318,9 +323,25 @@ __global__ void __launch_bounds__(LA_WAVES * 64, 2) lin_accumulate_kernel(const 
     enter();
     fetch_first();
   }
-  unsigned char* const mine = hz2 + w * (32 * LA_OUT_PITCH);
   unsigned ln = lane;
   asm volatile("" : "+v"(ln));   // (the addresses below are formed per item: kept through the loop they cost registers that it has not got)
+  if constexpr (NMT == 1) {
+    if (Tq <= LA_DIRECT_ROWS) {  // (uniform) straight from the registers, 8 bytes per lane, the lane halves completing 16
+      if ((int)(ln & 31) < rows) {
+        char* const dst = out + (ln & 31) * (HZ_ELEMS * 2) + 8 * (ln >> 5);
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            const v16f& a = acc[0][nt];
+            *(uint2*)(dst + (32 * nt + 8 * g) * 2) = make_uint2(pack_bf16x2(a[4 * g], a[4 * g + 1]), pack_bf16x2(a[4 * g + 2], a[4 * g + 3]));
+          }
+      }
+      stored = rows > 0 ? 16 : 0;
+      return;
+    }
+  }
+  unsigned char* const mine = hz2 + w * (32 * LA_OUT_PITCH);
   const unsigned out_off = (ln >> 3) * (unsigned)(HZ_ELEMS * 2) + (ln & 7) * 16u;
   unsigned char* const put = mine + (ln & 31) * LA_OUT_PITCH + (ln >> 5) * 8;
   const unsigned char* const get = mine + (ln >> 3) * LA_OUT_PITCH + (ln & 7) * 16;
