@@ -418,6 +418,22 @@ def main_bwd(args):
     return result
 
 
+# Up to this many key blocks the block selection shares prep_kv's launch and counts to its stage (sla.h).
+SELECT_SHARES_PREP_UP_TO = 512
+
+
+def hbm_stage_bytes(BH, N, d, Tq, Tk, n_m, quant):
+    """Algorithmic bytes (each operand once) of the stages whose time is that of their memory traffic, by stage name."""
+    bhnd = float(BH) * N * d
+    hz_row = 129 * 128 * 2.0                      # one block summary: 128 x 128 + 128 bf16 values
+    out = {"pool_stats": 6.0 * bhnd + (1.0 * bhnd if quant != "none" else 0.0)}  # Q, K, V read once (bf16); Q codes written
+    if Tk > SELECT_SHARES_PREP_UP_TO and (quant != "none" or n_m > 0):
+        out["prep_kv"] = 4.0 * bhnd + (2.0 * bhnd if quant == "int8fp8" else 0.0) + (BH * Tk * hz_row if n_m > 0 else 0.0)
+    if n_m > 0:
+        out["lin_accumulate"] = BH * (Tk + Tq) * hz_row  # summaries in once, sums out once
+    return out
+
+
 def main():
     args = parse()
     if args.gpus != 1:
@@ -494,14 +510,8 @@ def main():
 
     flops = 4.0 * cfg.B * cfg.H * float(cfg.N) ** 2 * cfg.d
     value = flops / (ms_per_step * 1e-3) / 1e12
-    # HBM-bound stages: algorithmic bytes (each operand once) over the stage's median time
-    bhnd = float(cfg.B * cfg.H) * cfg.N * cfg.d
-    hz_row = 129 * 128 * 2.0                      # one block summary: 128 x 128 + 128 bf16 values
-    stage_bytes = {
-        "pool_stats": 6.0 * bhnd + (1.0 * bhnd if args.quant != "none" else 0.0),  # Q, K, V read once (bf16); Q codes written
-        "prep_kv": 4.0 * bhnd + (2.0 * bhnd if low_bit else 0.0) + (cfg.B * cfg.H * Tk * hz_row if n_m > 0 else 0.0),
-        "lin_accumulate": cfg.B * cfg.H * (Tk + Tq) * hz_row if n_m > 0 else 0.0,  # summaries in once, sums out once
-    }
+    # HBM-bound stages: algorithmic bytes over the stage's median time
+    stage_bytes = hbm_stage_bytes(cfg.B * cfg.H, cfg.N, cfg.d, Tq, Tk, n_m, args.quant)
     stage_hbm = {}
     for name, nbytes in stage_bytes.items():
         t = stage_ms[sla.STAGE_NAMES.index(name)]
@@ -533,6 +543,8 @@ def main():
                    "n_crit": n_c, "n_marg": n_m, "Tq": Tq, "Tk": Tk},
         "stage_ms": dict(zip(sla.STAGE_NAMES, [round(x, 4) for x in stage_ms])),
         "stage_hbm": stage_hbm,
+        "stage_note": None if "prep_kv" in stage_bytes or (n_m == 0 and args.quant == "none") else
+                      "the block selection (short calls: the scores too) shares prep_kv's launch and counts to its stage",
         "roofline": {"kernel": "sparse_fwd_kernel" if low_bit else "fwd_bf16_kernel",
                      "bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak,
                      "traffic": traffic if low_bit else None, "traffic_unit": "bytes per launch",

@@ -221,7 +221,11 @@ int sla_linear_attn_fwd(const void* q, const void* k, const void* v, const int8_
 /* Optional per-stage timing of sla_attention_fwd (for benchmarks; off by default).
  * The stages are: 0 pooling + statistics, 1 scores + block selection, 2 K/V
  * quantisation + linear summaries, 3 marginal-summary accumulation, 4 the fused
- * sparse attention kernel.
+ * sparse attention kernel.  Work of stages 1 and 2 that shares a launch counts to
+ * stage 2: in calls that have work for it (quantisation, or marginal blocks) the
+ * block selection where there are at most 512 key blocks, and in short calls (at
+ * most 64 key blocks in few slices) the scores and what is left of the statistics
+ * too -- stage 1 is then empty.
  *   sla_profile_enable(n): creates the HIP events (host objects, no device memory)
  *     for timing up to n calls; n <= 0 disables timing and destroys them.  While
  *     enabled, each sla_attention_fwd call records SLA_N_STAGES + 1 events on its

@@ -53,11 +53,12 @@ size_t sla_bwd_workspace_bytes(int B, int H, int N, int d, int block_q, int bloc
  *                  wanted.  Zero when there is no marginal block (the forward pass then adds no
  *                  bias).
  * Every output is deterministic: dproj_w and dproj_b are per-workgroup partial sums added in a
- * fixed order by a second kernel (no floating-point atomics anywhere).
+ * fixed order ahead of the launch that follows (no floating-point atomics anywhere).
  * With sla_profile_enable (sla.h) a call records the same number of stage events as a forward
- * call; the stages are: 0 block mask, 1 softmax statistics (lse, delta),
- * 2 linear branch and projection (summaries, dQ share, transposed accumulation, dK / dV shares),
- * 3 dQ, 4 dK and dV. */
+ * call; the stages are: 0 block mask and, with marginal blocks, the summaries of the keys (and a
+ * saved state's delta), which share its last launch, 1 softmax statistics (lse, delta; empty where
+ * stage 0 had delta), 2 linear branch and projection (accumulation, dQ share, transposed
+ * accumulation), 3 dQ, 4 dK and dV (with their shares of the linear branch). */
 int sla_attention_bwd(const void* q, const void* k, const void* v, const void* dout, const void* proj_w,
                       void* dq, void* dk, void* dv, float* dproj_w, float* dproj_b, int B, int H, int N, int d,
                       int block_q, int block_k, double topk_ratio, double marginal_ratio, int phi_kind,

@@ -671,9 +671,9 @@ int sla_attention_bwd_strided(const void* q, const void* k, const void* v, const
   } else {
     run_scores(nullptr, p, ws, W, s, false, false);
     launch_select(p, at<float>(ws, W.scores), at<int8_t>(ws, W.mask), at<int32_t>(ws, W.crit), nullptr, nullptr, s);
-    if (saved) launch_bwd_delta(da, p, s);
   }
   mark(s, rec, 1);
+  if (saved && !lin) launch_bwd_delta(da, p, s);
   if (!saved) launch_bwd_stats(p, q, k, v, dout, at<int32_t>(ws, W.crit), at<float>(ws, X.lse2), at<float>(ws, X.delta), s);
   mark(s, rec, 2);
   // (with no marginal block there is no linear term: the projection and the bias receive no gradient)
