@@ -43,11 +43,12 @@ constexpr int LA_B_ROW = LA_COLS * 2;            // 256 bytes per staged hz row
 constexpr int LA_B_BYTES = LA_KT * LA_B_ROW + (LA_KT / 8 - 1) * 64;
 constexpr int LA_OUT_PITCH = 64 * 2 + 16;         // bytes per row of 64 results on their way out
 constexpr int LA_B_STAGE = ((LA_B_BYTES > LA_WAVES * 32 * LA_OUT_PITCH ? LA_B_BYTES : LA_WAVES * 32 * LA_OUT_PITCH) + 255) / 256 * 256;
-// Heads of at most this many query blocks store their results straight from the registers: a wavefront or two have a row tile,
-// and the way through LDS costs them more than whole lines save.  Query blocks, heads x key blocks, us through LDS / directly:
-// 16, 40 x 16 28.4 / 24.1; 24, 40 x 48 32.4 / 26.5; 36, 12 x 72 19.8 / 18.3; 40, 40 x 40 31.9 / 30.3; 40, 40 x 80 46.2 / 46.3;
-// 44, 40 x 88 48.3 / 55.5; 64, 40 x 128 57.4 / 75.1.
-constexpr int LA_DIRECT_ROWS = 40;
+// Heads of at most this many query blocks store their results straight from the registers: one wavefront has a row tile, and the
+// way through LDS costs it more than whole lines save.  Query blocks (of 64; the last of 128), heads, us for whole calls,
+// forward and backward from a saved state, through LDS / directly: 8, 40 62.8 / 58.7 and 159.4 / 151.4; 16, 12 41.8 / 40.5 and
+// 108.2 / 106.6; 24, 40 84.0 / 80.6 and 265.7 / 258.1; 36, 40 117.6 / 115.6 but 389.8 / 394.2; 40, 40 129.2 / 124.7 but 451.0 /
+// 456.4 (the sums' reader pays for the partial lines); 30, 40 177.6 / 178.7 and 526.1 / 528.0.  The product alone at 64, 40: 57 / 75.
+constexpr int LA_DIRECT_ROWS = 24;
 constexpr int LA_M_PIECES = 2 * LA_KSUB;         // 1 KiB pieces of mask words per tile
 static_assert(HZ_ELEMS % LA_COLS == 0, "the stripes tile a summary exactly");
 static_assert(LA_M_PIECES == LA_WAVES && 8 * LA_KSUB % LA_WAVES == 0, "every wavefront copies the same number of pieces");
@@ -326,7 +327,7 @@ __global__ void __launch_bounds__(LA_WAVES * 64, 2) lin_accumulate_kernel(const 
   unsigned ln = lane;
   asm volatile("" : "+v"(ln));   // (the addresses below are formed per item: kept through the loop they cost registers that it has not got)
   if constexpr (NMT == 1) {
-    if (Tq <= LA_DIRECT_ROWS) {  // (uniform) straight from the registers, 8 bytes per lane, the lane halves completing 16
+    if (Tq <= LA_DIRECT_ROWS) {  // (uniform) 8 bytes per lane, the lane halves completing 16
       if ((int)(ln & 31) < rows) {
         char* const dst = out + (ln & 31) * (HZ_ELEMS * 2) + 8 * (ln >> 5);
 #pragma unroll
