@@ -1529,11 +1529,11 @@ static int launch_bwd_dkv_phi(const Problem& p, const void* q, const void* dout,
   } else {
     // An order only where workgroups wait for a place (two fit a compute unit), and only of the last heads, as many as
     // the memory-side cache holds Q and dO of: what counts is the end of the launch, and with all of 40 x 75600 tokens
-    // under way at once 25.8 ms became 29.6.  Whole backward pass in us, without / with an order, heads x key blocks: 33 x 16 (528,
-    // lists of three query blocks) 174.7 / 179.8, 13 x 40 (520) 174.8 / 174.3, 24 x 24 (576) 184.2 / 181.7, 12 x 48 (576) 185.8 /
-    // 182.4, 8 x 73 (584) 241.5 / 238.3, 5 x 126 (630) 243.9 / 235.2, 12 x 73 (876) 246.7 / 234.6, 80 x 16 (1280) 313.9 / 308.7,
-    // 2 x 512 (1024) 611 / 528, 12 x 126 (1512) 420 / 393, 24 x 512 (12288) 6283 / 6024, but 80 x 40 (3200) 671 / 678.  (10 heads of 37, 370 workgroups, none of
-    // which waits: 123.1 / 128.8.  Lists of one length, as white noise has them, gain nothing and pay the 5 to 10 us.)
+    // under way at once 25.8 ms became 29.6.  Whole backward pass in us, without / with an order, heads x key blocks: 33 x 16
+    // (528) 174.7 / 179.8, 13 x 40 (520) 174.8 / 174.3, 24 x 24 (576) 184.2 / 181.7, 12 x 48 (576) 185.8 / 182.4, 8 x 73 (584)
+    // 241.5 / 238.3, 5 x 126 (630) 243.9 / 235.2, 12 x 73 (876) 246.7 / 234.6, 2 x 512 (1024) 611 / 528, 80 x 16 (1280) 313.9 /
+    // 308.7, 12 x 126 (1512) 420 / 393, 24 x 512 (12288) 6283 / 6024, but 80 x 40 (3200) 671 / 678; 10 x 37, where none of the
+    // 370 workgroups waits, 123.1 / 128.8.  Lists of one length, as white noise has them, gain nothing and pay the 5 to 10 us.
     const long long head_bytes = 4ll * p.N * D;
     const int heads = (int)std::min<long long>(p.BH, std::max<long long>(1, (224ll << 20) / head_bytes));
     const bool ordered = order_ws && p.BH * p.Tk > 2 * compute_units();

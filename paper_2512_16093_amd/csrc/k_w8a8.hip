@@ -285,7 +285,7 @@ __global__ void __launch_bounds__(256, 2) w8a8_gemm_kernel(
   // stage kb - 1, which the copy of block kb + 2 overwrites.  The activations are requested behind
   // the first and the second quarter of the products, not in one burst behind the barrier: the memory path
   // has to deliver 47 of its 64 bytes per clock and compute unit at full matrix rate.  With that and the bias read
-  // at once (below) the layer went from 2120 to 1990 us at 75600 x 5120 -> 5120, from 550 to 473 at 32760 x 1536 -> 8960; with
+  // at once (below) the layer went from 2129 to 1977 us at 75600 x 5120 -> 5120, from 573 to 488 at 32760 x 1536 -> 8960; with
   // no operand loads at all (timing only) it would be 1610 us.  Requests ahead into L2 made it slower (2040 us): it is
   // not the latency.  (The last step requests its own block's activations once more, 8 KiB per wavefront that nobody
   // reads: the schedule stays the same for every step.)
