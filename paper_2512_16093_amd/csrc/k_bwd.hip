@@ -130,6 +130,16 @@ __device__ __forceinline__ void copy_piece(const char* base, unsigned off, unsig
 __device__ __forceinline__ void copy_piece(const char* addr, unsigned lds_addr) {  // (an address per lane)
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(addr), "s"(lds_addr) : "memory", "m0");
 }
+// Two consecutive pieces of a tile (FIRST and the next one), of no lane (mask 0) or all of them (-1; no wavefront here ever
+// has a lane switched off).  The instruction's immediate offset moves both addresses, so lds_tile is that of the
+// wavefront's first piece and base, off as TileCopy::base3 and off3 give them.
+template <int FIRST>
+__device__ __forceinline__ void copy_pieces_if(long long mask, const char* base, unsigned off0, unsigned off1, unsigned lds_tile) {
+  asm volatile("s_mov_b32 m0, %3\n\ts_mov_b64 exec, %4\n\t"
+               "global_load_lds_dwordx4 %1, %0 offset:%5\n\t"
+               "global_load_lds_dwordx4 %2, %0 offset:%6\n\ts_mov_b64 exec, -1"
+               : : "s"(base), "v"(off0), "v"(off1), "s"(lds_tile), "s"(mask), "n"(FIRST * 1024), "n"(FIRST * 1024 + 1024) : "memory", "m0");
+}
 // One tensor's copies by the WAVES wavefronts of a workgroup, 8 / WAVES pieces each.
 template <int WAVES>
 struct TileCopy {
@@ -151,30 +161,38 @@ struct TileCopy {
       off[i] = (unsigned)((4 * PPW * w + r) * snb) + (((lane & 15) ^ swz(4 * PPW * w + r)) << 4);
     }
   }
+  // For copies of several pieces with immediate offsets: piece i reads base3 + off3(i) + 1024 i.
+  __device__ __forceinline__ const char* base3(int row0) const { return slice + row0 * snb - 3072; }
+  __device__ __forceinline__ unsigned off3(int i) const { return off[i] + (3072 - 1024 * i); }
+  __device__ __forceinline__ unsigned dst(unsigned lds_tile) const { return __builtin_amdgcn_readfirstlane(lds_tile + w * PPW * 1024); }
+  // Are rows row0 .. row0 + rows - 1 whole, and their copies of the plain kind?  (uniform)
+  __device__ __forceinline__ bool plain(int row0, int rows, int N) const { return row0 + rows <= N && odd == 0; }
   // rows row0 .. row0 + 31; rows beyond N come as row N - 1 (their weight is zero)
   __device__ __forceinline__ void tile(int row0, int N, unsigned lds_tile) const {
-    const unsigned dst = __builtin_amdgcn_readfirstlane(lds_tile + w * PPW * 1024);
-    if (__builtin_expect(row0 + 32 <= N && odd == 0, 1)) {  // (uniform)
+    if (__builtin_expect(plain(row0, 32, N), 1)) {
       const char* b = slice + row0 * snb;
 #pragma unroll
-      for (int i = 0; i < PPW; ++i) copy_piece(i < 4 ? b : b + 16 * snb, off[i & 3], dst + i * 1024);
+      for (int i = 0; i < PPW; ++i) copy_piece(i < 4 ? b : b + 16 * snb, off[i & 3], dst(lds_tile) + i * 1024);
     } else {
-      int ln = lane;
-      asm volatile("" : "+v"(ln));            // (nothing of this path is worth a register outside of it)
+      tile_any(row0, N, lds_tile);
+    }
+  }
+  __device__ __forceinline__ void tile_any(int row0, int N, unsigned lds_tile) const {
+    int ln = lane;
+    asm volatile("" : "+v"(ln));            // (nothing of this path is worth a register outside of it)
 #pragma unroll 1
-      for (int i = 0; i < PPW; ++i) {
-        const int r = 4 * (PPW * w + i) + (ln >> 4);
-        const char* src = slice + min(row0 + r, N - 1) * snb + (((ln & 15) ^ swz(r)) << 4);
-        if ((odd & 15u) == 0) {
-          copy_piece(src, dst + i * 1024);
-        } else {
-          // A contiguous tensor may start at any element.  The asynchronous copies take whole 16-byte units only, an
-          // ordinary load takes any address: through a register.  (It has arrived before the next one is requested, so
-          // waiting by count errs on the safe side.)
-          v4i got;
-          __builtin_memcpy(&got, src, 16);
-          *(__attribute__((address_space(3))) v4i*)(uintptr_t)(dst + i * 1024 + ln * 16) = got;
-        }
+    for (int i = 0; i < PPW; ++i) {
+      const int r = 4 * (PPW * w + i) + (ln >> 4);
+      const char* src = slice + min(row0 + r, N - 1) * snb + (((ln & 15) ^ swz(r)) << 4);
+      if ((odd & 15u) == 0) {
+        copy_piece(src, dst(lds_tile) + i * 1024);
+      } else {
+        // A contiguous tensor may start at any element.  The asynchronous copies take whole 16-byte units only, an
+        // ordinary load takes any address: through a register.  (It has arrived before the next one is requested, so
+        // waiting by count errs on the safe side.)
+        v4i got;
+        __builtin_memcpy(&got, src, 16);
+        *(__attribute__((address_space(3))) v4i*)(uintptr_t)(dst(lds_tile) + i * 1024 + ln * 16) = got;
       }
     }
   }
@@ -1011,10 +1029,13 @@ __global__ void __launch_bounds__(1024) dkv_order_kernel(const int* __restrict__
 // over its own list, 64 query rows per step as well, and two workgroups share a compute unit: every
 // staged tile then serves one key block only, but no wavefront ever sits out.  With KB = 1 rows are copied straight to
 // LDS (no registers, no padding: see TileCopy), the scores are formed in ordinary registers and dK, dV, K, V held in the
-// accumulation registers, so a step is its 64 products, 160 vector instructions and 112 LDS reads with no register
-// copies between the two files (there were 77 a step, and the copies through registers took 56 more).  40 heads x
-// 75600 tokens 29.9 -> 25.9 ms, 12 x 32760 token-major 2.18 -> 1.78 ms; 164 GB past L2 = 6.2 TB/s at 1.9 GHz, the matrix
-// pipe 46 % busy: bound by the lone wavefront's waits between the sections and by the stream.
+// accumulation registers, so a step has no register copies between the two files (there were 77, and the copies through
+// registers took 56 more): 40 heads x 75600 tokens 29.9 -> 25.9 ms, 12 x 32760 token-major 2.18 -> 1.78 ms.  Cycle stamps
+// then showed 3450 cycles a step for 2048 of products: 650 in which the next step's copies went out one behind another,
+// 350 at the barrier, and the wavefront's own issue (a lone one gets an instruction away every five cycles or so).  With
+// the copies between the products, two to an m0, the barrier ahead of the step's last section, the next step's first
+// operands read behind that section's products and dP started from delta (no subtraction): 2900 cycles at 40 x 75600,
+// 430 instructions instead of 504; whole backward pass 59.6 -> 57.8 ms (same box), 4 x 2187 (training step) 185 -> 180 us.
 template <int KB, int TILES, int PHI, bool ST = false>
 __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ dout,
                                                       const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
@@ -1078,6 +1099,9 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) vf[ks] = __builtin_bit_cast(v4i, f[ks]);
   }
+  // KB = 1: with V negated and the rows' delta in its registers beforehand the product gives delta - dP (no subtraction per
+  // element), so dK collects with the other sign.
+  constexpr float DK_SIGN = KB == 1 ? -1.0f : 1.0f;
   // the accumulators start from the linear branch's share (G = nullptr: there is none); dK is scaled
   // by 1 / sqrt(d) at the end, so its share goes in multiplied by sqrt(d)
   v16f dkt[4], dvt[4];
@@ -1091,7 +1115,7 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
 #pragma unroll
     for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) dkt[ct][r] *= 11.313708498984761f;
+      for (int r = 0; r < 16; ++r) dkt[ct][r] *= DK_SIGN * 11.313708498984761f;
   } else {
 #pragma unroll
     for (int ct = 0; ct < 4; ++ct) {
@@ -1103,7 +1127,13 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
   // memory -> registers -> LDS: while step s is computed from one LDS buffer, step s + 1 is moved from
   // registers to the other buffer and step s + 2 is on its way from memory; one barrier per step.  Within a step
   // the two tiles are independent, which lets the matrix products of one run under the exponentials of the other.
-  const int steps = nq << pair_shift, pair_mask = (1 << pair_shift) - 1;
+  if constexpr (KB == 1) {
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) vf[ks][e] ^= (int)0x80008000u;
+  }
+  const int steps = __builtin_amdgcn_readfirstlane(nq << pair_shift), pair_mask = (1 << pair_shift) - 1;
   RowStage<NT, ROWS> sq0, sd0, sq1, sd1;
   float ps0 = 0.f, ps1 = 0.f;
   auto rows_of = [&](int step) { return ROWS * (((qlist[step >> pair_shift] & 0x3fff) << pair_shift) + (step & pair_mask)); };
@@ -1182,143 +1212,6 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
       }
     }
   };
-  // The same for two tiles per step (one key block per workgroup), laid out so that the vector work of
-  // one tile (exponentials, dS, conversions) is issued between the matrix products of the other: a
-  // lone wavefront per SIMD has nobody else to fill the matrix pipe while it computes exponentials.
-  const int n_off = swz_lane_offset(l32, hf), t_off = swz_tr_lane_offset(lane);
-  auto compute_interleaved = [&](int buf) __attribute__((always_inline)) {
-    const unsigned char* qt0 = lds + buf * BUF_B;
-    const unsigned char* dt0 = qt0 + 2 * SWZ_TILE_B;
-    v16f s[2], dp[2], p[2];
-    float4 ls[4], dl[4];
-    uint4 aq[8], ad[8];
-    auto read_ops = [&](int u) __attribute__((always_inline)) {
-#pragma unroll
-      for (int ks = 0; ks < 8; ++ks) {
-        aq[ks] = n_op_swz(qt0 + u * SWZ_TILE_B, n_off, ks);
-        ad[ks] = n_op_swz(dt0 + u * SWZ_TILE_B, n_off, ks);
-      }
-    };
-    auto read_stats = [&](int u) __attribute__((always_inline)) {
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        ls[g] = *(const float4*)&stat[buf][0][32 * u + 8 * g + 4 * hf];
-        dl[g] = *(const float4*)&stat[buf][1][32 * u + 8 * g + 4 * hf];
-      }
-    };
-    auto weight = [&](int u, int r) __attribute__((always_inline)) {  // P and dS of tile u, accumulator register r
-      const float4 l4 = ls[r >> 2], d4 = dl[r >> 2];
-      const float lv = (r & 3) == 0 ? l4.x : (r & 3) == 1 ? l4.y : (r & 3) == 2 ? l4.z : l4.w;
-      const float dv_ = (r & 3) == 0 ? d4.x : (r & 3) == 1 ? d4.y : (r & 3) == 2 ? d4.z : d4.w;
-      const float pe = __builtin_amdgcn_exp2f(s[u][r] * QK_LOG2 - lv);  // (a key beyond N: a finite value in a column that is never stored)
-      p[u][r] = pe;
-      s[u][r] = pe * (dp[u][r] - dv_);
-    };
-    // The step as an explicit schedule: every piece ends with a full scheduling fence, so the order
-    // below is the order of issue.  Tile 0's scores; tile 1's scores with tile 0's exponentials
-    // between the products; tile 0's gradient products with tile 1's exponentials between them;
-    // tile 1's gradient products.  The LDS reads of each section are issued one section early, a
-    // pair behind every product that has just consumed its operands (whose registers they take
-    // over), so that no section starts by waiting for its reads.
-#define FENCE __builtin_amdgcn_sched_barrier(0);
-    uint4 bq[8], bd[8];          // tile 1's score operands
-    uint4 td[4], tq[4], te[4], tr[4];  // transposed operands of the gradient products, two sets in turn
-    read_ops(0);
-    FENCE
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-      if (ks == 0) {
-        score0(s[0], aq[0], kf[0]);
-        score0(dp[0], ad[0], vf[0]);
-      } else {
-        score(s[0], aq[ks], kf[ks]);
-        score(dp[0], ad[ks], vf[ks]);
-      }
-      bq[ks] = n_op_swz(qt0 + SWZ_TILE_B, n_off, ks);
-      bd[ks] = n_op_swz(dt0 + SWZ_TILE_B, n_off, ks);
-      FENCE
-    }
-    read_stats(0);
-    FENCE
-    // P and dS of a tile behind sixteen products that do not need them, from the fourth on (the tile's own are done then)
-    auto weights_behind = [&](int u, int m) __attribute__((always_inline)) {
-      if (m == 3) {
-        score_done(s[u]);
-        score_done(dp[u]);
-      }
-      if (m >= 3) {
-#pragma unroll
-        for (int r = (m - 3) * 16 / 13; r < (m - 2) * 16 / 13; ++r) weight(u, r);
-      }
-    };
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-      if (ks == 0) score0(s[1], bq[0], kf[0]); else score(s[1], bq[ks], kf[ks]);
-      weights_behind(0, 2 * ks);
-      FENCE
-      if (ks == 0) score0(dp[1], bd[0], vf[0]); else score(dp[1], bd[ks], vf[ks]);
-      weights_behind(0, 2 * ks + 1);
-      if (ks & 1) {
-        td[ks >> 1] = t_op_swz(dt0, t_off, ks >> 1, 0);
-        tq[ks >> 1] = t_op_swz(qt0, t_off, ks >> 1, 0);
-      }
-      FENCE
-    }
-    read_stats(1);
-    {
-      const uint4 pb = acc_operand(p[0], 0), dsb = acc_operand(s[0], 0);
-      FENCE
-#pragma unroll
-      for (int ct = 0; ct < 4; ++ct) {
-        dvt[ct] = mfma_bf16(td[ct], pb, dvt[ct]);
-        weights_behind(1, 2 * ct);
-        FENCE
-        dkt[ct] = mfma_bf16(tq[ct], dsb, dkt[ct]);
-        weights_behind(1, 2 * ct + 1);
-        te[ct] = t_op_swz(dt0, t_off, ct, 1);
-        tr[ct] = t_op_swz(qt0, t_off, ct, 1);
-        FENCE
-      }
-    }
-    {
-      const uint4 pb = acc_operand(p[0], 1), dsb = acc_operand(s[0], 1);
-      FENCE
-#pragma unroll
-      for (int ct = 0; ct < 4; ++ct) {
-        dvt[ct] = mfma_bf16(te[ct], pb, dvt[ct]);
-        weights_behind(1, 8 + 2 * ct);
-        FENCE
-        dkt[ct] = mfma_bf16(tr[ct], dsb, dkt[ct]);
-        weights_behind(1, 8 + 2 * ct + 1);
-        td[ct] = t_op_swz(dt0 + SWZ_TILE_B, t_off, ct, 0);
-        tq[ct] = t_op_swz(qt0 + SWZ_TILE_B, t_off, ct, 0);
-        FENCE
-      }
-    }
-    {
-      const uint4 pb = acc_operand(p[1], 0), dsb = acc_operand(s[1], 0);
-      FENCE
-#pragma unroll
-      for (int ct = 0; ct < 4; ++ct) {
-        dvt[ct] = mfma_bf16(td[ct], pb, dvt[ct]);
-        dkt[ct] = mfma_bf16(tq[ct], dsb, dkt[ct]);
-        te[ct] = t_op_swz(dt0 + SWZ_TILE_B, t_off, ct, 1);
-        tr[ct] = t_op_swz(qt0 + SWZ_TILE_B, t_off, ct, 1);
-        FENCE
-      }
-    }
-    {
-      const uint4 pb = acc_operand(p[1], 1), dsb = acc_operand(s[1], 1);
-      FENCE
-#pragma unroll
-      for (int ct = 0; ct < 4; ++ct) {
-        dvt[ct] = mfma_bf16(te[ct], pb, dvt[ct]);
-        dkt[ct] = mfma_bf16(tr[ct], dsb, dkt[ct]);
-      }
-      FENCE
-    }
-#undef FENCE
-  };
   // One step: load step S + 2 into the set that step S has left, compute S, publish S + 1.  Every
   // step issues the same loads and stores whatever the step number (past the end the last step is
   // loaded again and a stale set is published to the buffer nobody reads any more; rows beyond N
@@ -1333,8 +1226,15 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
   DKV_STORE(SQN, SDN, PSN, 1 - (BUF))                          \
   __syncthreads();
   if constexpr (KB == 1) {
-    // Copies straight to LDS: while step s is computed from one buffer, step s + 1 travels into the other (the last
-    // step is copied again past the end); 16 pieces and one row of lse or delta per wavefront and step.
+    // Copies straight to LDS, two buffers; 16 pieces and one row of lse or delta per wavefront and step (past the end the
+    // last step is copied again).  A lone wavefront per SIMD has nobody to fill the matrix pipe while it does anything
+    // else, so a step is written in the order of issue, one piece per product, each ended by a full scheduling
+    // fence: the exponentials, dS and conversions of one tile behind the products of the other, the LDS reads of a section
+    // one section early, behind products that have just consumed the operands whose registers they take over, and the
+    // barrier that publishes the next step's rows and frees this one's ahead of the last section, which needs no more
+    // of them: behind its products the next step's first operands are read and the first copies of the step after it
+    // requested, one per product (all at once they held the wavefront up for 650 of 3500 cycles, the path from
+    // memory takes 64 bytes a cycle).
     if (steps > 0) {
       const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
       const int ws = __builtin_amdgcn_readfirstlane(w);
@@ -1342,15 +1242,33 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
       cq.init(qh, L_q.sn, ws, lane);
       cd.init(doh, L_d.sn, ws, lane);
       const float* srow = (ws ? delta : lse2) + (size_t)bh * dm.T32q * 32;
-      auto request = [&](int r0, int buf) __attribute__((always_inline)) {
-        const unsigned dst = lds0 + buf * BUF_B;
-        cq.tile(r0, dm.N, dst);
-        cq.tile(r0 + 32, dm.N, dst + SWZ_TILE_B);
-        cd.tile(r0, dm.N, dst + 2 * SWZ_TILE_B);
-        cd.tile(r0 + 32, dm.N, dst + 3 * SWZ_TILE_B);
-        copy_floats(srow + r0, lane * 4, lds0 + 2 * BUF_B + (buf * 2 + ws) * ROWS * 4);
-      };
       auto row_at = [&](int step) __attribute__((always_inline)) { return rows_of(min(step, steps - 1)); };
+      auto request_stats = [&](int r0, int buf) __attribute__((always_inline)) { copy_floats(srow + r0, lane * 4, lds0 + 2 * BUF_B + (buf * 2 + ws) * ROWS * 4); };
+      auto request = [&](int r0, int buf) __attribute__((always_inline)) {
+        const unsigned to = lds0 + buf * BUF_B;
+        cq.tile(r0, dm.N, to);
+        cq.tile(r0 + 32, dm.N, to + SWZ_TILE_B);
+        cd.tile(r0, dm.N, to + 2 * SWZ_TILE_B);
+        cd.tile(r0 + 32, dm.N, to + 3 * SWZ_TILE_B);
+        request_stats(r0, buf);
+      };
+      // the request under way, two pieces at a time: tile x / 2 of Q 0, Q 1, dO 0, dO 1, its first or last two pieces
+      const char *rq = cq.base3(0), *rd = cd.base3(0);
+      const int odd = (int)(cq.odd | cd.odd), always = ~((odd | -odd) >> 31);
+      int rmask = 0;                     // -1: all its rows exist and are copied the plain way, 0: it was made at once
+      unsigned oq[4], od[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        oq[i] = cq.off3(i);
+        od[i] = cd.off3(i);
+      }
+      auto request_pieces = [&](long long mask, int x, int buf) __attribute__((always_inline)) {
+        const int tile = x >> 1;
+        const char* from = tile < 2 ? rq + (tile & 1) * 32 * cq.snb : rd + (tile & 1) * 32 * cd.snb;
+        const unsigned(&o)[4] = tile < 2 ? oq : od;
+        const unsigned to = cq.dst(lds0 + buf * BUF_B + tile * SWZ_TILE_B);
+        if (x & 1) copy_pieces_if<2>(mask, from, o[2], o[3], to); else copy_pieces_if<0>(mask, from, o[0], o[1], to);
+      };
       // (names the place of what lives through the loop: the allocator parked operands beside it otherwise)
       auto hold = [&]() __attribute__((always_inline)) {
 #pragma unroll
@@ -1358,26 +1276,162 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks) asm volatile("" : "+a"(kf[ks]), "+a"(vf[ks]));
       };
-      int r1 = __builtin_amdgcn_readfirstlane(row_at(1)), ahead;   // (ahead: read from the list in LDS during the step)
+      const int n_off = swz_lane_offset(l32, hf), t_off = swz_tr_lane_offset(lane);
+      uint4 aq[8], ad[8];                // tile 0's score operands
+      v16f dp0;                          // and its rows' delta, where its dP starts from
+#define FENCE __builtin_amdgcn_sched_barrier(0);
+      auto read_delta = [&](v16f& x, int buf, int u, int g) __attribute__((always_inline)) {
+        const float4 d4 = *(const float4*)&stat[buf][1][32 * u + 8 * g + 4 * hf];
+        x[4 * g] = d4.x; x[4 * g + 1] = d4.y; x[4 * g + 2] = d4.z; x[4 * g + 3] = d4.w;
+      };
+      auto do_step = [&](int step, int buf) __attribute__((always_inline)) {
+        const unsigned char *qt0 = lds + buf * BUF_B, *dt0 = qt0 + 2 * SWZ_TILE_B;
+        const unsigned char *qn = lds + (1 - buf) * BUF_B, *dn = qn + 2 * SWZ_TILE_B;
+        v16f s[2], dp[2];
+        float4 ls[4];
+        uint4 bq[8], bd[8];              // tile 1's score operands
+        uint4 td[4], tq[4], te[4], tr[4];  // transposed operands of the gradient products, two sets in turn
+        v4i pb[2][2], sb[2][2];          // P and minus dS of both tiles as operands
+        float pe = 0.f, se = 0.f;        // the even element of the pair under way
+        auto read_lse = [&](int u, int g) __attribute__((always_inline)) { ls[g] = *(const float4*)&stat[buf][0][32 * u + 8 * g + 4 * hf]; };
+        auto anchor = [&](int u, int half) __attribute__((always_inline)) {  // (P and dS stay in their section: the compiler sank them past branches)
+          asm volatile("" : "+v"(pb[u][half]), "+v"(sb[u][half]));
+        };
+        auto weight = [&](int e) __attribute__((always_inline)) {  // P and dS: accumulator register e % 16 of tile e / 16
+          const int u = e >> 4, r = e & 15;
+          const float4 l4 = ls[r >> 2];
+          const float lv = (r & 3) == 0 ? l4.x : (r & 3) == 1 ? l4.y : (r & 3) == 2 ? l4.z : l4.w;
+          const float p1 = __builtin_amdgcn_exp2f(s[u][r] * QK_LOG2 - lv);  // (a key beyond N: a finite value in a column that is never stored)
+          const float s1 = p1 * dp[u][r];    // (minus dS)
+          if (r & 1) {
+            pb[u][r >> 3][(r & 7) >> 1] = (int)pack_bf16x2(pe, p1);
+            sb[u][r >> 3][(r & 7) >> 1] = (int)pack_bf16x2(se, s1);
+          } else {
+            pe = p1;
+            se = s1;
+          }
+        };
+        int ahead = row_at(step + 2), mask_now;
+        // (carried round the loop in a vector register: the builtin folds away.  The wait state is for the instruction that
+        // may have written that register just before: the compiler puts it behind its own lane reads only)
+        asm("s_nop 1\n\tv_readfirstlane_b32 %0, %1" : "=s"(mask_now) : "v"(rmask));
+        // tile 0's scores
+        dp[0] = dp0;
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) {
+          if (ks == 0) score0(s[0], aq[0], kf[0]); else score(s[0], aq[ks], kf[ks]);
+          bq[ks] = n_op_swz(qt0 + SWZ_TILE_B, n_off, ks);
+          if (ks < 7) request_pieces(mask_now, 1 + ks, 1 - buf);      // (the rest of what the step before has begun to request)
+          FENCE
+          score(dp[0], ad[ks], vf[ks]);
+          bd[ks] = n_op_swz(dt0 + SWZ_TILE_B, n_off, ks);
+          if (ks >= 4) read_lse(0, ks - 4); else read_delta(dp[1], buf, 1, ks);
+          FENCE
+        }
+        // tile 1's scores; P and dS of tile 0 from the fourth product on (its own are done then)
+#pragma unroll
+        for (int m = 0; m < 16; ++m) {
+          const int ks = m >> 1;
+          if (m & 1) {
+            score(dp[1], bd[ks], vf[ks]);
+          } else {
+            if (ks == 0) score0(s[1], bq[0], kf[0]); else score(s[1], bq[ks], kf[ks]);
+          }
+          if (m == 3) {
+            score_done(s[0]);
+            score_done(dp[0]);
+          }
+          if (m >= 3) weight(m - 3);           // 0 .. 12
+          if ((m & 3) == 1) td[m >> 2] = t_op_swz(dt0, t_off, m >> 2, 0);
+          if ((m & 3) == 3) tq[m >> 2] = t_op_swz(qt0, t_off, m >> 2, 0);
+          if (m >= 13) read_lse(1, m - 13);
+          FENCE
+        }
+        anchor(0, 0);
+        const int rows_ahead = __builtin_amdgcn_readfirstlane(ahead);
+        // (by integer arithmetic: as a truth value the compiler kept it in vector registers)
+        const int mask_next = always & ~((dm.N - ROWS - rows_ahead) >> 31);
+        rmask = mask_next;
+        rq = cq.base3(rows_ahead);
+        rd = cd.base3(rows_ahead);
+        // tile 0's gradient products, first half
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+          const int ct = m >> 1;
+          if (m & 1) dkt[ct] = mfma_bf16(tq[ct], __builtin_bit_cast(uint4, sb[0][0]), dkt[ct]); else dvt[ct] = mfma_bf16(td[ct], __builtin_bit_cast(uint4, pb[0][0]), dvt[ct]);
+          if (m < 3) weight(13 + m);
+          if (m == 2) read_lse(1, 3);
+          if (m == 3) {
+            score_done(s[1]);
+            score_done(dp[1]);
+          }
+          if (m >= 3) weight(16 + m - 3);      // 16 .. 20
+          if (m & 1) tr[ct] = t_op_swz(qt0, t_off, ct, 1); else te[ct] = t_op_swz(dt0, t_off, ct, 1);
+          FENCE
+        }
+        anchor(0, 1);
+        // second half
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+          const int ct = m >> 1;
+          if (m & 1) dkt[ct] = mfma_bf16(tr[ct], __builtin_bit_cast(uint4, sb[0][1]), dkt[ct]); else dvt[ct] = mfma_bf16(te[ct], __builtin_bit_cast(uint4, pb[0][1]), dvt[ct]);
+          if (m < 6) weight(21 + m);           // 21 .. 26
+          if (m & 1) tq[ct] = t_op_swz(qt0 + SWZ_TILE_B, t_off, ct, 0); else td[ct] = t_op_swz(dt0 + SWZ_TILE_B, t_off, ct, 0);
+          FENCE
+        }
+        anchor(1, 0);
+        // tile 1's, first half
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+          const int ct = m >> 1;
+          if (m & 1) dkt[ct] = mfma_bf16(tq[ct], __builtin_bit_cast(uint4, sb[1][0]), dkt[ct]); else dvt[ct] = mfma_bf16(td[ct], __builtin_bit_cast(uint4, pb[1][0]), dvt[ct]);
+          if (m < 5) weight(27 + m);           // 27 .. 31
+          if (m & 1) tr[ct] = t_op_swz(qt0 + SWZ_TILE_B, t_off, ct, 1); else te[ct] = t_op_swz(dt0 + SWZ_TILE_B, t_off, ct, 1);
+          FENCE
+        }
+        anchor(1, 1);
+        copies_barrier<0>();             // the next step's rows have landed; this step's are consumed
+        if (__builtin_expect(mask_next == 0, 0)) {
+#pragma unroll 1
+          for (int u = 0; u < 2; ++u) {
+            cq.tile_any(rows_ahead + 32 * u, dm.N, lds0 + buf * BUF_B + u * SWZ_TILE_B);
+            cd.tile_any(rows_ahead + 32 * u, dm.N, lds0 + buf * BUF_B + (2 + u) * SWZ_TILE_B);
+          }
+        }
+        // second half
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+          const int ct = m >> 1;
+          if (m & 1) dkt[ct] = mfma_bf16(tr[ct], __builtin_bit_cast(uint4, sb[1][1]), dkt[ct]); else dvt[ct] = mfma_bf16(te[ct], __builtin_bit_cast(uint4, pb[1][1]), dvt[ct]);
+          aq[m] = n_op_swz(qn, n_off, m);
+          ad[m] = n_op_swz(dn, n_off, m);
+          if (m < 4) read_delta(dp0, 1 - buf, 0, m);
+          if (m == 4) request_stats(rows_ahead, buf);
+          if (m == 6) request_pieces(mask_next, 0, buf);
+          FENCE
+        }
+        hold();
+      };
+      const int r0 = __builtin_amdgcn_readfirstlane(row_at(0)), r1 = __builtin_amdgcn_readfirstlane(row_at(1));
       __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the workgroup's own K, V rows are in
-      request(__builtin_amdgcn_readfirstlane(row_at(0)), 0);
+      request(r0, 0);
+      request(r1, 1);
       copies_barrier<0>();
-      for (int step = 0; step < steps; step += 2) {  // (every exit test is uniform over the workgroup)
-        hold();
-        request(r1, 1);
-        ahead = row_at(step + 2);
-        compute_interleaved(0);
-        r1 = __builtin_amdgcn_readfirstlane(ahead);
-        hold();
-        copies_barrier<0>();
-        if (step + 1 >= steps) break;
-        request(r1, 0);
-        ahead = row_at(step + 3);
-        compute_interleaved(1);
-        r1 = __builtin_amdgcn_readfirstlane(ahead);
-        hold();
-        copies_barrier<0>();
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks) {
+        aq[ks] = n_op_swz(lds, n_off, ks);
+        ad[ks] = n_op_swz(lds + 2 * SWZ_TILE_B, n_off, ks);
+        if (ks < 4) read_delta(dp0, 0, 0, ks);
       }
+      FENCE
+      hold();
+      for (int step = 0; step < steps; step += 2) {  // (every exit test is uniform over the workgroup)
+        do_step(step, 0);
+        if (step + 1 >= steps) break;
+        do_step(step + 1, 1);
+      }
+#undef FENCE
+      __builtin_amdgcn_s_waitcnt(0x0F70);  // (no copy may land after the workgroup has left)
     }
   } else {
     if (steps > 0) {
@@ -1403,8 +1457,8 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         const int ch = 32 * ct + 8 * g + 4 * hf;
-        store_grad4(dkrow + ch, nullptr, dkt[ct][4 * g] * INV_SQRT_D, dkt[ct][4 * g + 1] * INV_SQRT_D,
-                    dkt[ct][4 * g + 2] * INV_SQRT_D, dkt[ct][4 * g + 3] * INV_SQRT_D);
+        store_grad4(dkrow + ch, nullptr, dkt[ct][4 * g] * (DK_SIGN * INV_SQRT_D), dkt[ct][4 * g + 1] * (DK_SIGN * INV_SQRT_D),
+                    dkt[ct][4 * g + 2] * (DK_SIGN * INV_SQRT_D), dkt[ct][4 * g + 3] * (DK_SIGN * INV_SQRT_D));
         store_grad4(dvrow + ch, nullptr, dvt[ct][4 * g], dvt[ct][4 * g + 1], dvt[ct][4 * g + 2], dvt[ct][4 * g + 3]);
       }
   }
