@@ -853,39 +853,29 @@ __global__ void __launch_bounds__(WAVES * 64, 1) bwd_dq_kernel(const bf16_t* __r
 // of dZ_i, in the summaries' storage order (hz_frag_chunk):
 //     d phi(K)^T[c][n] = sum_o G[c][o] V[n][o] + dZ[c]   ->  dK[n] = phi o (d phi - phi . d phi)
 //     dV^T[o][n]       = sum_c G[c][o] phi(K)[n][c]
-// Called by every thread of the workgroup (NT of them): G_j is staged in LDS transposed (gc,
-// 128 rows of GP elements; gz, 128 floats); both barriers are inside.  Results in the accumulator
-// layout of the sparse-branch kernels (lane = key, registers = channels).
-constexpr int GP = 136;  // row pitch of the staged G (elements)
-template <int NT, int PHI>
-__device__ __forceinline__ void linear_kv_share(const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,   // (the token's rows)
-                                                bool ok, const bf16_t* __restrict__ rec, bf16_t* gc, float* gz, int t,
-                                                int lane, v16f (&dk_share)[4], v16f (&dv_share)[4]) {
-  const int l32 = lane & 31, hf = lane >> 5;
-  for (int x = t; x < 2048; x += NT) {
-    const int ln = x & 63, ks = (x >> 6) & 7, ot = x >> 9;
-    const int o = 32 * ot + (ln & 31), c0 = 32 * (ks >> 1) + 16 * (ln >> 5) + 8 * (ks & 1);
-    const uint4 val = *(const uint4*)(rec + (size_t)x * 8);
-    const uint32_t wv[4] = {val.x, val.y, val.z, val.w};
+// Called by the 128 threads of a key block with everything already on its way to registers: kr, vr the token's rows, g the
+// block's chunks 128 u + t of G_j, z entries 2 (t % 64), 2 (t % 64) + 1 of its dZ.  G_j is published row by row ([o][c], pitch TP), so that the one product
+// reads it as it is and the other with the transposing read.  Both barriers are inside.  Results in the accumulator
+// layout of the sparse-branch kernels (lane = key, registers = channels).  Bound by its own chain of instructions: 23 000
+// cycles of every workgroup when G_j was fetched chunk by chunk and transposed by 2-byte writes, now 10 000 (4 x 2187; whole
+// backward pass with the requests ahead of the list, below, and the rows stored through LDS: 24 heads x 8000, query blocks
+// of 64 1146 -> 1077 us, 40 x 75600 56.5 -> 54.6 ms).
+constexpr int G_CHUNKS = D * D / 8 / 128;
+template <int PHI>
+__device__ __forceinline__ void linear_kv_share(const v4i (&kr)[8], const v4i (&vr)[8], bool ok, const v4i (&g)[G_CHUNKS], uint32_t z,
+                                                unsigned char* gl, float* gz, int t, int lane, v16f (&dk_share)[4], v16f (&dv_share)[4]) {
+  const int l32 = lane & 31, hf = lane >> 5, tr_off = tr_lane_offset(lane);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) gc[(c0 + e) * GP + o] = (bf16_t)(e & 1 ? wv[e >> 1] >> 16 : wv[e >> 1] & 0xffffu);
+  for (int u = 0; u < G_CHUNKS; ++u) {
+    const int x = u * 128 + t, ln = x & 63, ks = (x >> 6) & 7, ot = x >> 9;
+    *(v4i*)(gl + (32 * ot + (ln & 31)) * TP + (32 * (ks >> 1) + 16 * (ln >> 5) + 8 * (ks & 1)) * 2) = g[u];
   }
-  if (t < 128) gz[t] = bf16_to_f32(rec[128 * 128 + t]);
-  __syncthreads();
-  // phi(K[n]) at the channels the storage order feeds per step: 32 (ks / 2) + 16 hf + 8 (ks % 2) + kk
+  if (t < 64) *(float2*)(gz + 2 * t) = float2{bf16_lo(z), bf16_hi(z)};
+  // phi(K[n]) at channels 16 ks + 8 hf + kk
   float cv[64];
-  uint4 cf[8], vf[8];
+  uint4 cf[8];
 #pragma unroll
-  for (int ks = 0; ks < 8; ++ks) {
-    uint4 kv = uint4{0u, 0u, 0u, 0u};
-    vf[ks] = kv;
-    if (ok) {
-      kv = *(const uint4*)(k + 32 * (ks >> 1) + 16 * hf + 8 * (ks & 1));
-      vf[ks] = *(const uint4*)(v + 16 * ks + 8 * hf);
-    }
-    cv[8 * ks] = bf16_lo(kv.x); cv[8 * ks + 1] = bf16_hi(kv.x); cv[8 * ks + 2] = bf16_lo(kv.y); cv[8 * ks + 3] = bf16_hi(kv.y);
-    cv[8 * ks + 4] = bf16_lo(kv.z); cv[8 * ks + 5] = bf16_hi(kv.z); cv[8 * ks + 6] = bf16_lo(kv.w); cv[8 * ks + 7] = bf16_hi(kv.w);
-  }
+  for (int ks = 0; ks < 8; ++ks) unpack8(__builtin_bit_cast(uint4, kr[ks]), &cv[8 * ks]);
   float kmax = 0.f, sum = 1.0f;
   if constexpr (PHI == 0) {
     kmax = cv[0];
@@ -908,55 +898,66 @@ __device__ __forceinline__ void linear_kv_share(const bf16_t* __restrict__ k, co
   for (int ks = 0; ks < 8; ++ks) {
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) cv[8 * ks + kk] *= rsum;
-    cf[ks] = uint4{pack_bf16x2(cv[8 * ks], cv[8 * ks + 1]), pack_bf16x2(cv[8 * ks + 2], cv[8 * ks + 3]),
-                   pack_bf16x2(cv[8 * ks + 4], cv[8 * ks + 5]), pack_bf16x2(cv[8 * ks + 6], cv[8 * ks + 7])};
+    cf[ks] = pack8(&cv[8 * ks]);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int ot = 0; ot < 4; ++ot) {   // (the operand reads of a tile grouped ahead of its products)
+    uint4 a[8];
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) a[ks] = n_op(gl + 32 * ot * TP, l32, hf, ks);
+    __builtin_amdgcn_sched_barrier(0);
+    dv_share[ot] = v16f{};
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) dv_share[ot] = mfma_bf16(a[ks], cf[ks], dv_share[ot]);
   }
 #pragma unroll
-  for (int ot = 0; ot < 4; ++ot) {
-    uint4 ag[8], ac[8];  // operand reads grouped ahead of the matrix products
+  for (int ks = 0; ks < 8; ++ks) cf[ks] = pair_order(__builtin_bit_cast(uint4, vr[ks]));
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-      ag[ks] = *(const uint4*)(rec + (size_t)hz_frag_chunk(ot, ks, lane) * 8);  // the stored chunks are this product's A operand as they are
-      ac[ks] = *(const uint4*)(gc + (32 * ot + l32) * GP + 16 * ks + 8 * hf);
-    }
-    dv_share[ot] = v16f{};
-    dk_share[ot] = v16f{};
+  for (int ct = 0; ct < 4; ++ct) {
+    uint4 a[8];
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-      dv_share[ot] = mfma_bf16(ag[ks], cf[ks], dv_share[ot]);
-      dk_share[ot] = mfma_bf16(ac[ks], vf[ks], dk_share[ot]);  // d phi(K)^T for now
-    }
-    __builtin_amdgcn_sched_group_barrier(0x020, 8, 0);
-    __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
-    __builtin_amdgcn_sched_group_barrier(0x008, 16, 0);
+    for (int ks = 0; ks < 8; ++ks) a[ks] = t_op(gl + 32 * (ks >> 1) * TP, tr_off, ct, ks & 1);
+    __builtin_amdgcn_sched_barrier(0);
+    dk_share[ct] = v16f{};
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) dk_share[ct] = mfma_bf16(a[ks], cf[ks], dk_share[ct]);  // d phi(K)^T for now
   }
   // through the feature map: phi at the accumulator's channels 32 ct + 8 g + 4 hf + e, from K again
   float sdot = 0.f;
-  uint2 kw[4][4];
+#pragma unroll
+  for (int ks = 0; ks < 8; ++ks) cf[ks] = pair_order(__builtin_bit_cast(uint4, kr[ks]));
+  auto k_at = [&](int ct, int g4, float (&xk)[4]) __attribute__((always_inline)) {
+    const uint4& kk = cf[2 * ct + (g4 >> 1)];
+    const uint32_t k0 = g4 & 1 ? kk.z : kk.x, k1 = g4 & 1 ? kk.w : kk.y;
+    xk[0] = bf16_lo(k0); xk[1] = bf16_hi(k0); xk[2] = bf16_lo(k1); xk[3] = bf16_hi(k1);
+  };
 #pragma unroll
   for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int c0 = 32 * ct + 8 * g + 4 * hf;
-      kw[ct][g] = ok ? *(const uint2*)(k + c0) : uint2{0u, 0u};
-      const float xk[4] = {bf16_lo(kw[ct][g].x), bf16_hi(kw[ct][g].x), bf16_lo(kw[ct][g].y), bf16_hi(kw[ct][g].y)};
+    for (int g4 = 0; g4 < 4; ++g4) {
+      const float4 z4 = *(const float4*)(gz + 32 * ct + 8 * g4 + 4 * hf);
+      const float zz[4] = {z4.x, z4.y, z4.z, z4.w};
+      float xk[4];
+      k_at(ct, g4, xk);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        dk_share[ct][4 * g + e] += gz[c0 + e];
-        if constexpr (PHI == 0) sdot += phi_value<0>(xk[e], kmax, rsum) * dk_share[ct][4 * g + e];
+        dk_share[ct][4 * g4 + e] += zz[e];
+        if constexpr (PHI == 0) sdot += phi_value<0>(xk[e], kmax, rsum) * dk_share[ct][4 * g4 + e];
       }
     }
   sdot += partner_f32(sdot);
 #pragma unroll
   for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const float xk[4] = {bf16_lo(kw[ct][g].x), bf16_hi(kw[ct][g].x), bf16_lo(kw[ct][g].y), bf16_hi(kw[ct][g].y)};
+    for (int g4 = 0; g4 < 4; ++g4) {
+      float xk[4];
+      k_at(ct, g4, xk);
 #pragma unroll
       for (int e = 0; e < 4; ++e)
-        dk_share[ct][4 * g + e] = phi_backward<PHI>(xk[e], phi_value<PHI>(xk[e], kmax, rsum), dk_share[ct][4 * g + e], sdot);
+        dk_share[ct][4 * g4 + e] = phi_backward<PHI>(xk[e], phi_value<PHI>(xk[e], kmax, rsum), dk_share[ct][4 * g4 + e], sdot);
     }
-  __syncthreads();  // the staged G is consumed: the caller may reuse the LDS
+  __syncthreads();  // the published G is consumed: the caller may reuse the LDS
 }
 
 // The order in which dK/dV's workgroups (KB = 1) are started.  Their lists differ in length by more than threefold, and in the
@@ -1049,7 +1050,7 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
   constexpr int BUF_B = KB == 1 ? 4 * SWZ_TILE_B : 2 * TILES * TILE_B;
   float (*stat)[2][ROWS] = (float (*)[2][ROWS])(lds + 2 * BUF_B);
   unsigned short* qlist = (unsigned short*)(lds + 2 * BUF_B + 2 * 2 * ROWS * 4);  // [Tq]
-  __shared__ int wcnt[4];
+  __shared__ int wcnt[8][4];
   int J, bh;
   if (KB == 1 && (int)blockIdx.x >= natural) {
     const int x = order[(blockIdx.x & 7) * ((gridDim.x - natural) >> 3) + ((blockIdx.x - natural) >> 3)];   // (natural: a multiple of 8)
@@ -1062,26 +1063,6 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
   const int t = threadIdx.x, lane = t & 63, w = t >> 6, l32 = lane & 31, hf = lane >> 5;
   const int tr_off = tr_lane_offset(lane);
   const int half = KB == 2 ? w >> 1 : 0;
-  // ---- the query blocks of the two key blocks, ascending; bit 14 / 15 = first / second block has it
-  int nq = 0;
-  const bool has2 = KB == 2 && 2 * J + 1 < dm.Tk;
-  for (int base = 0; base < dm.Tq; base += NT) {
-    const int i = base + t;
-    int fl = 0;
-    if (i < dm.Tq) {
-      const int8_t* mrow = mask + ((size_t)bh * dm.Tq + i) * dm.Tk + KB * J;
-      fl = (mrow[0] == 1 ? 1 : 0) | (has2 && mrow[1] == 1 ? 2 : 0);
-    }
-    const unsigned long long bal = __ballot(fl != 0);
-    if (lane == 0) wcnt[w] = __popcll(bal);
-    __syncthreads();
-    int off = nq + __popcll(bal & ((1ull << lane) - 1ull));
-    for (int x = 0; x < w; ++x) off += wcnt[x];
-    if (fl) qlist[off] = (unsigned short)(i | (fl << 14));
-#pragma unroll
-    for (int x = 0; x < NT / 64; ++x) nq += wcnt[x];
-    __syncthreads();
-  }
   SLA_BWD_LAYOUTS
   const bf16_t* kh = slice_of(k, L_k, bh, dm.H);
   const bf16_t* vh = slice_of(v, L_v, bh, dm.H);
@@ -1089,16 +1070,77 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
   const bf16_t* doh = slice_of(dout, L_d, bh, dm.H);
   const long long key = 64ll * (KB * J + half) + 32 * (w & 1) + l32;
   const bool kok = key < dm.N;
+  // Everything that is needed ahead of the loop is requested before anything is waited for: the mask column(s) of the
+  // first SCAN * NT query blocks, the wavefront's own rows, the block's G (one after the other they cost every
+  // workgroup 18 000 cycles of 430 000 at 40 heads x 75600 tokens).
+  constexpr int SCAN = 8;
+  const bool has2 = KB == 2 && 2 * J + 1 < dm.Tk;
+  const int8_t* mcol = mask + (size_t)bh * dm.Tq * dm.Tk + KB * J;
+  int fl[SCAN];
+  auto load_flags = [&](int base) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < SCAN; ++u) {
+      const int8_t* m = mcol + (size_t)min(base + u * NT + t, dm.Tq - 1) * dm.Tk;
+      fl[u] = (m[0] & 0xff) | (KB == 2 ? (has2 ? m[1] & 0xff : 0) << 8 : 0);
+    }
+  };
+  load_flags(0);
+  // (rows beyond N come as row N - 1: a finite value in a column that is never stored)
   v4i kf[8], vf[8];
   {
-    uint4 f[8];
-    own_rows(kh, L_k.sn, key, dm.N, hf, f);
+    const long long row = kok ? key : dm.N - 1;
+    const bf16_t *kr = kh + row * L_k.sn + 8 * hf, *vr = vh + row * L_v.sn + 8 * hf;
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) kf[ks] = __builtin_bit_cast(v4i, f[ks]);
-    own_rows(vh, L_v.sn, key, dm.N, hf, f);
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) vf[ks] = __builtin_bit_cast(v4i, f[ks]);
+    for (int ks = 0; ks < 8; ++ks) {
+      kf[ks] = *(const v4i*)(kr + 16 * ks);
+      vf[ks] = *(const v4i*)(vr + 16 * ks);
+    }
   }
+  v4i g[G_CHUNKS];
+  uint32_t gz2 = 0;                      // (a pair of dZ: a single one, widened here, would be waited for here)
+#pragma unroll
+  for (int u = 0; u < G_CHUNKS; ++u) g[u] = v4i{};
+  if (G) {
+    const int jb = min(KB * J + half, dm.Tk - 1);  // (the missing second block of an odd last pair: its keys do not exist)
+    const bf16_t* rec = G + ((size_t)bh * dm.Tk + jb) * HZ_ELEMS;
+#pragma unroll
+    for (int u = 0; u < G_CHUNKS; ++u) {
+      const v4i got = *(const v4i*)(rec + (size_t)(u * 128 + (t & 127)) * 8);
+      g[u] = got;
+    }
+    gz2 = *(const uint32_t*)(rec + D * D + 2 * (t & 63));
+  }
+  // ---- the query blocks of the key block(s), ascending; bit 14 / 15 = first / second block has it
+  int nq = 0;
+  for (int base = 0; base < dm.Tq; base += SCAN * NT) {
+    if (base) {
+      __syncthreads();                   // (the counts of the round before have been read)
+      load_flags(base);
+    }
+    unsigned long long bal[SCAN];
+#pragma unroll
+    for (int u = 0; u < SCAN; ++u) {
+      const int i = base + u * NT + t;
+      fl[u] = i < dm.Tq ? ((fl[u] & 0xff) == 1 ? 1 : 0) | ((fl[u] >> 8) == 1 ? 2 : 0) : 0;
+      bal[u] = __ballot(fl[u] != 0);
+      if (lane == 0) wcnt[u][w] = __popcll(bal[u]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < SCAN; ++u) {
+      if (base + u * NT < dm.Tq) {       // (uniform)
+        int off = nq + __popcll(bal[u] & ((1ull << lane) - 1ull));
+#pragma unroll
+        for (int x = 0; x < NT / 64; ++x) {
+          const int n = wcnt[u][x];
+          if (x < w) off += n;
+          nq += n;
+        }
+        if (fl[u]) qlist[off] = (unsigned short)((base + u * NT + t) | (fl[u] << 14));
+      }
+    }
+  }
+  __syncthreads();                       // (the list is complete)
   // KB = 1: with V negated and the rows' delta in its registers beforehand the product gives delta - dP (no subtraction per
   // element), so dK collects with the other sign.
   constexpr float DK_SIGN = KB == 1 ? -1.0f : 1.0f;
@@ -1106,12 +1148,9 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
   // by 1 / sqrt(d) at the end, so its share goes in multiplied by sqrt(d)
   v16f dkt[4], dvt[4];
   if (G) {
-    // each key block's two wavefronts stage its G_j in their own part of the (still unused) staging buffers
-    constexpr int LIN_B = 128 * GP * 2 + 128 * 4;
-    static_assert(KB * LIN_B <= 2 * BUF_B, "the staged G fits in the staging buffers");
-    const int jb = min(KB * J + half, dm.Tk - 1);  // (the missing second block of an odd last pair: its keys do not exist)
-    linear_kv_share<128, PHI>(kh + (kok ? key : 0) * L_k.sn, vh + (kok ? key : 0) * L_v.sn, kok, G + ((size_t)bh * dm.Tk + jb) * HZ_ELEMS,
-                         (bf16_t*)(lds + half * LIN_B), (float*)(lds + half * LIN_B + 128 * GP * 2), t & 127, lane, dkt, dvt);
+    // each key block's two wavefronts publish its G_j in their own part of the (still unused) staging buffers
+    static_assert(KB * 128 * TP <= 2 * BUF_B && KB * 128 <= 2 * 2 * ROWS, "the published G and dZ fit");
+    linear_kv_share<PHI>(kf, vf, kok, g, gz2, lds + half * 128 * TP, (float*)stat + half * 128, t & 127, lane, dkt, dvt);
 #pragma unroll
     for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
@@ -1123,16 +1162,16 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
       dvt[ct] = v16f{};
     }
   }
-  // Steps = (list entry, pair of tiles of its query block): 64 query rows at a time.  With KB = 2 they travel
-  // memory -> registers -> LDS: while step s is computed from one LDS buffer, step s + 1 is moved from
-  // registers to the other buffer and step s + 2 is on its way from memory; one barrier per step.  Within a step
-  // the two tiles are independent, which lets the matrix products of one run under the exponentials of the other.
   if constexpr (KB == 1) {
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks)
 #pragma unroll
       for (int e = 0; e < 4; ++e) vf[ks][e] ^= (int)0x80008000u;
   }
+  // Steps = (list entry, pair of tiles of its query block): 64 query rows at a time.  With KB = 2 they travel
+  // memory -> registers -> LDS: while step s is computed from one LDS buffer, step s + 1 is moved from
+  // registers to the other buffer and step s + 2 is on its way from memory; one barrier per step.  Within a step
+  // the two tiles are independent, which lets the matrix products of one run under the exponentials of the other.
   const int steps = __builtin_amdgcn_readfirstlane(nq << pair_shift), pair_mask = (1 << pair_shift) - 1;
   RowStage<NT, ROWS> sq0, sd0, sq1, sd1;
   float ps0 = 0.f, ps1 = 0.f;
@@ -1449,19 +1488,36 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
 #undef DKV_STEP
 #undef DKV_LOAD
 #undef DKV_STORE
-  if (kok) {
-    bf16_t* dkrow = slice_of(dk, L_dk, bh, dm.H) + key * L_dk.sn;
-    bf16_t* dvrow = slice_of(dv, L_dv, bh, dm.H) + key * L_dv.sn;
+  // Out through LDS, so that whole rows of 256 bytes leave at a time: a wavefront's 32 keys of dK, then of dV.
+  __syncthreads();                       // (nobody reads the staging buffers, and no copy lands in them any more)
+  constexpr int OP = 256 + 16;           // bytes per staged row
+  static_assert(2 * KB * 32 * OP <= 2 * BUF_B, "a wavefront's rows fit");
+  unsigned char* my = lds + w * 32 * OP;
+  const int row0 = 64 * (KB * J + half) + 32 * (w & 1);
+  auto store_rows = [&](const v16f (&x)[4], float scale, bf16_t* dst, const Layout& L) __attribute__((always_inline)) {
+    bf16_t* to = slice_of(dst, L, bh, dm.H) + (row0 + (lane >> 4)) * L.sn + (lane & 15) * 8;
 #pragma unroll
     for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int ch = 32 * ct + 8 * g + 4 * hf;
-        store_grad4(dkrow + ch, nullptr, dkt[ct][4 * g] * (DK_SIGN * INV_SQRT_D), dkt[ct][4 * g + 1] * (DK_SIGN * INV_SQRT_D),
-                    dkt[ct][4 * g + 2] * (DK_SIGN * INV_SQRT_D), dkt[ct][4 * g + 3] * (DK_SIGN * INV_SQRT_D));
-        store_grad4(dvrow + ch, nullptr, dvt[ct][4 * g], dvt[ct][4 * g + 1], dvt[ct][4 * g + 2], dvt[ct][4 * g + 3]);
-      }
-  }
+      for (int g4 = 0; g4 < 4; ++g4)
+        *(uint2*)(my + l32 * OP + (32 * ct + 8 * g4 + 4 * hf) * 2) =
+            uint2{pack_bf16x2(x[ct][4 * g4] * scale, x[ct][4 * g4 + 1] * scale), pack_bf16x2(x[ct][4 * g4 + 2] * scale, x[ct][4 * g4 + 3] * scale)};
+    __builtin_amdgcn_wave_barrier();     // (a wavefront's LDS operations execute in order: only the compiler has to keep it)
+    v4i out[8];
+#pragma unroll
+    for (int it = 0; it < 8; ++it) out[it] = *(const v4i*)(my + (4 * it + (lane >> 4)) * OP + (lane & 15) * 16);
+    __builtin_amdgcn_wave_barrier();
+    if (row0 + 32 <= dm.N) {             // (uniform)
+#pragma unroll
+      for (int it = 0; it < 8; ++it) __builtin_memcpy(to + 4 * it * L.sn, &out[it], 16);
+    } else {
+#pragma unroll
+      for (int it = 0; it < 8; ++it)
+        if (row0 + 4 * it + (lane >> 4) < dm.N) __builtin_memcpy(to + 4 * it * L.sn, &out[it], 16);
+    }
+  };
+  store_rows(dkt, DK_SIGN * INV_SQRT_D, dk, L_dk);
+  store_rows(dvt, 1.0f, dv, L_dv);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1609,14 +1665,11 @@ static int launch_bwd_dkv_phi(const Problem& p, const void* q, const void* dout,
 int launch_bwd_dkv(const Problem& p, const void* q, const void* dout, const void* k, const void* v, const int8_t* mask,
                    const float* lse2, const float* delta, const bf16_t* G, int phi_kind, void* dk, void* dv, int* order_ws, hipStream_t stream) {
   const int phi = G ? phi_kind : 0;
-  if (contiguous(p, {&p.lq, &p.lk, &p.lv, &p.ld, &p.ldk, &p.ldv})) {
-    if (phi == 0) return launch_bwd_dkv_phi<0, false>(p, q, dout, k, v, mask, lse2, delta, G, dk, dv, order_ws, stream);
-    if (phi == 1) return launch_bwd_dkv_phi<1, false>(p, q, dout, k, v, mask, lse2, delta, G, dk, dv, order_ws, stream);
-    return launch_bwd_dkv_phi<2, false>(p, q, dout, k, v, mask, lse2, delta, G, dk, dv, order_ws, stream);
-  }
-  if (phi == 0) return launch_bwd_dkv_phi<0, true>(p, q, dout, k, v, mask, lse2, delta, G, dk, dv, order_ws, stream);
-  if (phi == 1) return launch_bwd_dkv_phi<1, true>(p, q, dout, k, v, mask, lse2, delta, G, dk, dv, order_ws, stream);
-  return launch_bwd_dkv_phi<2, true>(p, q, dout, k, v, mask, lse2, delta, G, dk, dv, order_ws, stream);
+  const bool st = !contiguous(p, {&p.lq, &p.lk, &p.lv, &p.ld, &p.ldk, &p.ldv});
+#define SLA_DKV(PHI) (st ? launch_bwd_dkv_phi<PHI, true>(p, q, dout, k, v, mask, lse2, delta, G, dk, dv, order_ws, stream) \
+                         : launch_bwd_dkv_phi<PHI, false>(p, q, dout, k, v, mask, lse2, delta, G, dk, dv, order_ws, stream))
+  return phi == 0 ? SLA_DKV(0) : phi == 1 ? SLA_DKV(1) : SLA_DKV(2);
+#undef SLA_DKV
 }
 
 }  // namespace sla

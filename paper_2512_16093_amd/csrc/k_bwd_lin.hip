@@ -45,14 +45,6 @@ __device__ __forceinline__ void softmax_stats(float (&x)[64], float& mx, float& 
   rsum = 1.0f / s;
 }
 
-__device__ __forceinline__ void unpack8(const uint4& v, float* out) {
-  out[0] = bf16_lo(v.x); out[1] = bf16_hi(v.x); out[2] = bf16_lo(v.y); out[3] = bf16_hi(v.y);
-  out[4] = bf16_lo(v.z); out[5] = bf16_hi(v.z); out[6] = bf16_lo(v.w); out[7] = bf16_hi(v.w);
-}
-__device__ __forceinline__ uint4 pack8(const float* x) {
-  return uint4{pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]), pack_bf16x2(x[6], x[7])};
-}
-
 }  // namespace
 
 // Workgroup barrier that publishes LDS writes and retires LDS reads but leaves global loads and stores in flight
@@ -62,15 +54,6 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
-}
-
-// A token's 16 channels of step ks, lane half hf holding 16 ks + 8 hf + 0..7, regrouped over the lane pair: lane half
-// hf gets channels 16 ks + 4 hf + 0..3 (x, y) and 16 ks + 8 + 4 hf + 0..3 (z, w) -- the row order of the accumulators
-// and of the transposing reads.
-__device__ __forceinline__ uint4 pair_order(const uint4& v) {
-  const auto a = __builtin_amdgcn_permlane32_swap(v.x, v.z, false, false);
-  const auto b = __builtin_amdgcn_permlane32_swap(v.y, v.w, false, false);
-  return uint4{(uint32_t)a[0], (uint32_t)b[0], (uint32_t)a[1], (uint32_t)b[1]};
 }
 
 // Column sums over the tokens of a staged [BQ][128] tile, weighted: thread (channel group t % 16, eight tokens from
