@@ -622,6 +622,9 @@ __device__ __forceinline__ void store_grad4(bf16_t* dst, const float* lin, float
 __device__ __forceinline__ void score0(v16f& d, const uint4& a, const v4i& b) {
   asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(__builtin_bit_cast(v4i, a)), "a"(b));
 }
+__device__ __forceinline__ void score_from(v16f& d, const uint4& a, const v4i& b, const v16f& c) {
+  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" : "=&v"(d) : "v"(__builtin_bit_cast(v4i, a)), "a"(b), "v"(c));
+}
 __device__ __forceinline__ void score(v16f& d, const uint4& a, const v4i& b) {
   asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(__builtin_bit_cast(v4i, a)), "a"(b));
 }
@@ -637,7 +640,10 @@ __device__ __forceinline__ void score_wait(v16f& x) { asm volatile("s_nop 15\n\t
 // tile t with exponentials of tile t + 1, dP of tile t + 1 with the rest of them.  Operands are read a section early,
 // and the barrier that publishes a tile stands in the middle of a section, whose products cover the first reads of it.
 // 40 heads x 75600 tokens 16.8 -> 16.1 ms (half the LDS traffic lets the clock rise from 1.70 to 1.88 GHz; the matrix pipe
-// is 56 % busy), query blocks of 64 (12 x 32760) 1.42 -> 1.00 ms; 12 x 32760 at 128 token-major 0.96 -> 0.97 ms.
+// was 56 % busy), query blocks of 64 (12 x 32760) 1.42 -> 1.00 ms.  A tile's copies go between the products of two sections, a
+// pair at a time (in one burst behind the barrier they held the wavefront up), and dP starts from minus delta (32 of 325
+// instructions of a step less): 16.1 -> 15.2 ms, 1.00 -> 0.93 ms.  With another 10 instructions and two waits of a step
+// taken out it is no faster: bound by power.
 template <int WAVES, int QT, bool ST>
 __global__ void __launch_bounds__(WAVES * 64, 1) bwd_dq_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ dout,
                                                               const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
@@ -654,6 +660,7 @@ __global__ void __launch_bounds__(WAVES * 64, 1) bwd_dq_kernel(const bf16_t* __r
   v4i qf[QT][8], dof[QT][8];
   v16f acc[QT][4];
   float lse[QT], del[QT];
+  v16f from[QT];   // dP starts from minus delta (no subtraction per element)
 #pragma unroll
   for (int x = 0; x < QT; ++x)
 #pragma unroll
@@ -673,6 +680,39 @@ __global__ void __launch_bounds__(WAVES * 64, 1) bwd_dq_kernel(const bf16_t* __r
       ck.tile(key, dm.N, dst);
       cv.tile(key, dm.N, dst + SWZ_TILE_B);
     };
+    // The request under way: tile + R into the place of the tile consumed last, in pairs of pieces, K's first.
+    constexpr int PAIRS = TileCopy<WAVES>::PPW;
+    const int odd = (int)(ck.odd | cv.odd), always = ~((odd | -odd) >> 31);
+    const char *rk = ck.base3(0), *rv = cv.base3(0);
+    unsigned to_k = 0;
+    int rmask = 0;                             // -1: all its rows exist and are copied the plain way, 0: it was made at once
+    unsigned ok[4], ov[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      ok[u] = ck.off3(u);
+      ov[u] = cv.off3(u);
+    }
+    auto begin_request = [&](int tile, int key_) __attribute__((always_inline)) {
+      const int key = __builtin_amdgcn_readfirstlane(key_);
+      const unsigned dst = lds0 + (tile & (R - 1)) * 2 * SWZ_TILE_B;
+      const int mask = always & ~((dm.N - 32 - key) >> 31);   // (by integer arithmetic: as a truth value the compiler kept it in vector registers)
+      rmask = mask;
+      rk = ck.base3(key);
+      rv = cv.base3(key);
+      to_k = ck.dst(dst);
+      if (__builtin_expect(mask == 0, 0)) {
+        ck.tile_any(key, dm.N, dst);
+        cv.tile_any(key, dm.N, dst + SWZ_TILE_B);
+      }
+      return mask;
+    };
+    auto request_pair = [&](long long mask, int x) __attribute__((always_inline)) {
+      const int first = 2 * x % PAIRS;         // of its tensor's pieces; four on the offsets repeat, sixteen rows on
+      const char* from = (2 * x < PAIRS ? rk : rv) + (first < 4 ? 0 : 16 * ck.snb + (2 * x < PAIRS ? 0 : 16 * (cv.snb - ck.snb)));
+      const unsigned(&o)[4] = 2 * x < PAIRS ? ok : ov;
+      const unsigned to = to_k + (2 * x < PAIRS ? 0 : SWZ_TILE_B) + (first < 4 ? 0 : 4096);
+      if (first & 2) copy_pieces_if<2>(mask, from, o[2], o[3], to); else copy_pieces_if<0>(mask, from, o[0], o[1], to);
+    };
     // (names the place of what lives through the loop)
     auto hold = [&]() __attribute__((always_inline)) {
 #pragma unroll
@@ -681,6 +721,7 @@ __global__ void __launch_bounds__(WAVES * 64, 1) bwd_dq_kernel(const bf16_t* __r
         for (int ct = 0; ct < 4; ++ct) asm volatile("" : "+a"(acc[x][ct]));
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks) asm volatile("" : "+a"(qf[x][ks]), "+a"(dof[x][ks]));
+        asm volatile("" : "+v"(from[x]));
       }
     };
 #pragma unroll
@@ -704,13 +745,17 @@ __global__ void __launch_bounds__(WAVES * 64, 1) bwd_dq_kernel(const bf16_t* __r
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) ak[ks] = n_op_swz(ring, n_off, ks);
     v16f sa[QT], sb[QT], dp[QT];
+#pragma unroll
+    for (int x = 0; x < QT; ++x)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) from[x][r] = -del[x];
     // the sequence's last key block can only be the last entry of the ascending list: from tile `whole` on keys are missing
     const int whole = crow[dm.n_c - 1] * 64 + 64 <= dm.N ? tiles : tiles - 2;
 #define FENCE __builtin_amdgcn_sched_barrier(0);
     auto weight = [&](v16f (&s)[QT], int e) __attribute__((always_inline)) {   // P: element e % 16 of query tile e / 16
       s[e >> 4][e & 15] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e >> 4][e & 15], QK_LOG2, -lse[e >> 4]));
     };
-    auto dscore = [&](v16f (&s)[QT], int e) __attribute__((always_inline)) { s[e >> 4][e & 15] *= dp[e >> 4][e & 15] - del[e >> 4]; };
+    auto dscore = [&](v16f (&s)[QT], int e) __attribute__((always_inline)) { s[e >> 4][e & 15] *= dp[e >> 4][e & 15]; };
     // Keys beyond N (the sequence's last key block only) came as key N - 1, so their P and dS are finite: their column
     // of K^T is cleared.
     auto clear_missing = [&](int key0) __attribute__((always_inline)) {
@@ -730,19 +775,22 @@ __global__ void __launch_bounds__(WAVES * 64, 1) bwd_dq_kernel(const bf16_t* __r
     // dP of a tile (V operands in av); behind its products the second part of its exponentials and, once the tile is
     // consumed and the next one has landed, the reads of the next one's K
     constexpr int M = 8 * QT, E = 16 * QT;   // products of a section; elements per lane of the query tiles' P, dS
+    constexpr int EARLY = PAIRS / 2;         // pairs of the request that go behind the products of dP, the rest behind those of S
     auto dp_products = [&](v16f (&s)[QT], int tile, int key_far) __attribute__((always_inline)) {   // key_far: of tile + R
       const unsigned char* next = ring + ((tile + 1) & (R - 1)) * 2 * SWZ_TILE_B;
+      int mask_next = 0;
 #pragma unroll
       for (int m = 0; m < M; ++m) {
         const int ks = m / QT, x = m % QT;
-        if (ks == 0) score0(dp[x], av[0], dof[x][0]); else score(dp[x], av[ks], dof[x][ks]);
+        if (ks == 0) score_from(dp[x], av[0], dof[x][0], from[x]); else score(dp[x], av[ks], dof[x][ks]);
 #pragma unroll
         for (int e = M - 3 + m * (E - M + 3) / M; e < M - 3 + (m + 1) * (E - M + 3) / M; ++e) weight(s, e);
         if (m == M / 2 - 1) {
           FENCE
           copies_barrier<(R - 2) * PER_TILE>();    // the next tile has landed; this one is consumed
-          request(tile + R, key_far);
+          mask_next = begin_request(tile + R, key_far);
         }
+        if (m >= M / 2 && (m - M / 2) % (M / 2 / EARLY) == M / 2 / EARLY - 1) request_pair(mask_next, (m - M / 2) / (M / 2 / EARLY));
         if (m >= M / 2 && x == 0) {
           ak[2 * (ks - 4)] = n_op_swz(next, n_off, 2 * (ks - 4));
           ak[2 * (ks - 4) + 1] = n_op_swz(next, n_off, 2 * (ks - 4) + 1);
@@ -782,7 +830,12 @@ __global__ void __launch_bounds__(WAVES * 64, 1) bwd_dq_kernel(const bf16_t* __r
           if ((e & 7) == 7) ds[e >> 4][(e >> 3) & 1] = acc_operand(s[e >> 4], (e >> 3) & 1);
         }
       };
-      // S of t + 1; behind its products dS of t and the reads of V
+      int mask_now;
+      // (carried round the loop in a vector register: the builtin folds away.  The wait state is for the instruction that
+      // may have written that register just before: the compiler puts it behind its own lane reads only)
+      asm("s_nop 1\n\tv_readfirstlane_b32 %0, %1" : "=s"(mask_now) : "v"(rmask));
+      // S of t + 1; behind its products dS of t, the rest of the request and the reads of V
+      constexpr int GAP = R == 2 ? 2 : M / (PAIRS - EARLY);   // (two tiles only: what is requested here is waited for this step)
 #pragma unroll
       for (int m = 0; m < M; ++m) {
         const int ks = m / QT, x = m % QT;
@@ -793,6 +846,7 @@ __global__ void __launch_bounds__(WAVES * 64, 1) bwd_dq_kernel(const bf16_t* __r
         }
         if (m >= 3) dscores((m - 3) * E1 / (M - 3), (m - 2) * E1 / (M - 3));
         if (x == 0) av[ks] = n_op_swz(kt + SWZ_TILE_B, n_off, ks);
+        if (m % GAP == GAP - 1 && m / GAP < PAIRS - EARLY) request_pair(mask_now, EARLY + m / GAP);
         FENCE
       }
       // dQ of t; behind its products the last of dS, the first part of the exponentials of t + 1 and its K^T operands
