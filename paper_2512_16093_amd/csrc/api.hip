@@ -203,10 +203,8 @@ int fwd_bf16(const void* q, const void* k, const void* v, void* out, const Probl
   if (lin) launch_lin_accumulate(p, at<uint32_t>(ws, W.m0), at<bf16_t>(ws, W.hz), at<bf16_t>(ws, W.HZ), LinRiders{}, s);
   mark(s, rec, 4);
   const CodeScales cs{at<float>(ws, W.dq), at<float>(ws, W.dk), q};
-  if (launch_fwd_bf16(p, codes16 ? at<bf16_t>(ws, W.qc) : q, codes16 ? at<bf16_t>(ws, W.kc) : k, v, at<int32_t>(ws, W.crit),
-                      lin ? at<bf16_t>(ws, W.HZ) : nullptr, (const bf16_t*)proj_b, phi_kind, out, save,
-                      codes16 ? &cs : nullptr, s) != 0)
-    return SLA_ERR_HIP;
+  launch_fwd_bf16(p, codes16 ? at<bf16_t>(ws, W.qc) : q, codes16 ? at<bf16_t>(ws, W.kc) : k, v, at<int32_t>(ws, W.crit),
+                  lin ? at<bf16_t>(ws, W.HZ) : nullptr, (const bf16_t*)proj_b, phi_kind, out, save, codes16 ? &cs : nullptr, s);
   mark(s, rec, 5);
   return launch_status();
 }

@@ -361,8 +361,8 @@ struct SaveTo {
 // qk_scales: nullptr, or {delta_Q [BH,Tq], delta_K [BH,Tk]} when q and k hold INT8 codes (q_lin: the
 // original Q for the linear term's feature map)
 struct CodeScales { const float* dq; const float* dk; const void* q_lin; };
-int launch_fwd_bf16(const Problem& p, const void* q, const void* k, const void* v, const int32_t* crit,
-                    const bf16_t* HZ, const bf16_t* proj_b, int phi_kind, void* out, const SaveTo* save,
+void launch_fwd_bf16(const Problem& p, const void* q, const void* k, const void* v, const int32_t* crit,
+                     const bf16_t* HZ, const bf16_t* proj_b, int phi_kind, void* out, const SaveTo* save,
                     const CodeScales* codes, hipStream_t stream);
 void launch_unpack_q8(const Problem& p, const int8_t* q8, int8_t* q_codes, hipStream_t stream);
 void launch_code_tensors(const Problem& p, const int8_t* q8, const int8_t* k8, bf16_t* qc, bf16_t* kc, hipStream_t stream);

@@ -20,6 +20,7 @@
 // product that contracts over the tile's tokens reads the same tile with the transposing LDS read
 // of gfx950 (ds_read_b64_tr_b16), so no transposed copy of any tensor is ever made.
 #include <algorithm>
+#include <cfloat>
 #include <initializer_list>
 
 #include "common.h"
@@ -59,29 +60,13 @@ __device__ __forceinline__ bf16_t* slice_of(bf16_t* x, const Layout& L, int bh, 
 }
 
 // ROWS consecutive token rows of a [N, 128] tensor -> LDS tile(s), through registers (loaded one
-// step ahead); rows beyond N are zero.  NT threads take part.
+// step ahead).  NT threads take part.
 template <int NT, int ROWS>
 struct RowStage {
   static constexpr int PER = ROWS * 16 / NT;
   uint4 pf[PER];
-  __device__ __forceinline__ void load(const bf16_t* x, long long sn, long long r0, int N, int t) {
-    if (r0 + ROWS <= N) {  // (uniform) every row exists: no per-row test
-#pragma unroll
-      for (int u = 0; u < PER; ++u) {
-        const int c = u * NT + t;
-        pf[u] = *(const uint4*)(x + (r0 + (c >> 4)) * sn + (c & 15) * 8);
-      }
-    } else {
-#pragma unroll
-      for (int u = 0; u < PER; ++u) {
-        const int c = u * NT + t;
-        const long long r = r0 + (c >> 4);
-        pf[u] = r < N ? *(const uint4*)(x + r * sn + (c & 15) * 8) : uint4{0u, 0u, 0u, 0u};
-      }
-    }
-  }
-  // The same with rows beyond N replaced by row N - 1 and no branch: for callers that give such rows
-  // a weight of exactly zero and want every call to issue the same loads (N > 0).
+  // Rows beyond N come as row N - 1 and without a branch: the caller gives such rows a weight of exactly zero and
+  // wants every call to issue the same loads (N > 0).
   __device__ __forceinline__ void load_clamped(const bf16_t* x, long long sn, int r0, int N, int t) {
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
@@ -389,11 +374,21 @@ struct FwdEpilogue {
   const bf16_t* q_lin;   // the original Q, laid out by lq_lin
   Layout lq_lin;
 };
+//
+// A wavefront owns 32 queries, K and V come in steps of KT tiles of 32 keys, copied one step ahead, and two wavefronts
+// share a SIMD: one's exponentials hide behind the other's products and, 16 keys on, behind its own.  With four
+// wavefronts two tiles a step (64 KB a workgroup, a barrier every 64 keys), with two one tile (32 KB: four workgroups
+// stay on a compute unit; with two tiles there was one wavefront per SIMD, 12 x 32760 tokens 1280 instead of 1095 us a
+// call; four wavefronts with one tile: 936 instead of 910).  Through registers (up to 64 of them) and with 78 KB for
+// either size the call took: query blocks of 128, 12 x 32760 tokens 944 -> 863 us, 40 x 75600 15.1 -> 13.5 ms; of 64 1392 ->
+// 1055 us, 23.0 -> 20.5 ms.  Bound by the exponentials beside the products (12 x 32760: 0.84 of 1.9 PFLOP/s in the
+// kernel), at query blocks of 64 by the stream of K and V, 32 KB for every 64 x 64 scores: 9 TB/s past the LDS.
 template <int NW, bool CODES, bool ST>
-__global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) fwd_bf16_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
+__global__ void __launch_bounds__(NW * 64, 2) fwd_bf16_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                                                             const bf16_t* __restrict__ v, const int32_t* __restrict__ crit,
                                                             BwdDims dm, FwdEpilogue fe) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char lds_all[];  // two buffers of: K (2 tiles) then V (2 tiles) of a key block
+  constexpr int KT = NW / 2, STEP_B = 2 * KT * SWZ_TILE_B;
+  __shared__ __attribute__((aligned(16))) unsigned char ring[2 * STEP_B];  // two steps' tiles: KT of K, then KT of V
   int i, bh;
   if (fe.save_hdr && blockIdx.x == 0 && threadIdx.x < 64) {
     const int v[8] = {fe.hdr.magic, fe.hdr.B, fe.hdr.H, fe.hdr.N, fe.hdr.block_q, fe.hdr.n_c, fe.hdr.pad0, fe.hdr.pad1};
@@ -405,110 +400,117 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) fwd_bf16_kernel(cons
   }
   if (!xcd_block(dm.Tq, i, bh)) return;
   SLA_BWD_LAYOUTS
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6, l32 = lane & 31, hf = lane >> 5;
-  const int tr_off = tr_lane_offset(lane);
+  const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6), l32 = lane & 31, hf = lane >> 5;
   const int T = i * NW + w;
   const long long qrow = 32ll * T + l32;
   const bool qok = qrow < dm.N;
   const size_t head = (size_t)bh * dm.N * D;   // (of the library's own contiguous tensors)
   const bf16_t* qh = slice_of(q, L_q, bh, dm.H);
-  const bf16_t* kh = slice_of(k, L_k, bh, dm.H);
-  const bf16_t* vh = slice_of(v, L_v, bh, dm.H);
   uint4 qf[8];
   own_rows(qh, L_q.sn, qrow, dm.N, hf, qf);
-  const int32_t* crow = crit + ((size_t)bh * dm.Tq + i) * dm.n_c;
-  RowStage<NW * 64, 64> sk, sv;
+  const int32_t* __restrict__ crow = crit + ((size_t)bh * dm.Tq + i) * dm.n_c;
   v16f o[4];
 #pragma unroll
   for (int ct = 0; ct < 4; ++ct) o[ct] = v16f{};
-  float m = -INFINITY;
+  float m = -FLT_MAX;    // (finite: a tile may hold no valid key, and then its P have to be 0 and not NaN)
   const float qscale = CODES ? QK_LOG2 * fe.code_dq[(size_t)bh * dm.Tq + i] : QK_LOG2;
   v16f lacc = v16f{};  // register 0: the running sum of P over the keys (see the ones operand below)
-  // key blocks travel memory -> registers -> LDS one step ahead, into the buffer the step before
-  // last has left: one barrier per step
   if (dm.n_c > 0) {
-    sk.load(kh, L_k.sn, 64ll * crow[0], dm.N, t);
-    sv.load(vh, L_v.sn, 64ll * crow[0], dm.N, t);
-    sk.store(lds_all, t);
-    sv.store(lds_all + 2 * TILE_B, t);
-  }
-  // Everything requested so far has to be in before the loop: a load the compiler cannot prove
-  // finished on every path into the loop would be waited for each time round, in the middle of the
-  // products and together with the loads of the next block just issued.  For the same reason the
-  // loop's own loads and stores are unconditional (rows beyond N come as row N - 1; their P is 0).
-  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-  __syncthreads();
-  for (int b = 0; b < dm.n_c; ++b) {
-    const int j = crow[b];
-    const float c2 = CODES ? qscale * fe.code_dk[(size_t)bh * dm.Tk + j] : QK_LOG2;   // score -> base-2 logit
-    const unsigned char* lds = lds_all + (b & 1) * 4 * TILE_B;
-    unsigned char* lds_next = lds_all + ((b + 1) & 1) * 4 * TILE_B;
-    {  // the next block (after the last one: the last one again), the same loads every time round -- see below
-      const int jn = 64 * crow[min(b + 1, dm.n_c - 1)];
-      sk.load_clamped(kh, L_k.sn, jn, dm.N, t);
-      sv.load_clamped(vh, L_v.sn, jn, dm.N, t);
-    }
-    v16f s[2];
-    float mx = -INFINITY;
+    const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void*)ring;
+    TileCopy<NW> ck, cv;
+    ck.init(slice_of(k, L_k, bh, dm.H), L_k.sn, w, lane);
+    cv.init(slice_of(v, L_v, bh, dm.H), L_v.sn, w, lane);
+    const int n_off = swz_lane_offset(l32, hf), t_off = swz_tr_lane_offset(lane);
+    auto request = [&](int key0, int half) __attribute__((always_inline)) {
 #pragma unroll
-    for (int kt = 0; kt < 2; ++kt) {
-      uint4 ak[8];  // operand reads grouped ahead of the matrix products that use them
+      for (int kt = 0; kt < KT; ++kt) {
+        ck.tile(key0 + 32 * kt, dm.N, lds0 + half * STEP_B + kt * SWZ_TILE_B);
+        cv.tile(key0 + 32 * kt, dm.N, lds0 + half * STEP_B + (KT + kt) * SWZ_TILE_B);
+      }
+    };
+    // KT tiles of 32 keys from key0 on, in half `half` of the ring; next: the step behind this one starts there (< 0: none)
+    auto step = [&](int key0, float c2, int half, int next) __attribute__((always_inline)) {   // c2: score -> base-2 logit
+      copies_barrier<0>();                     // this step's tiles have landed; those of the step before are consumed
+      if (next >= 0) request(next, half ^ 1);
+      // (a half of the ring is a multiple of the bits that the reads flip: added to the lane's offset)
+      int no = n_off + half * STEP_B, to = t_off + half * STEP_B;
+      asm volatile("" : "+v"(no), "+v"(to));
+      v16f s[KT];
+      float mx = -INFINITY;
+      uint4 ak[8], tv[2][4];
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks) ak[ks] = n_op(lds + kt * TILE_B, l32, hf, ks);
-      s[kt] = v16f{};
+      for (int ks = 0; ks < 8; ++ks) ak[ks] = n_op_swz(ring, no, ks);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks) s[kt] = mfma_bf16(ak[ks], qf[ks], s[kt]);
-      __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
-      __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
-      if (64 * j + 64 <= dm.N) {  // (uniform) only the sequence's last key block can hold keys that do not exist
+      for (int kt = 0; kt < KT; ++kt) {
+        s[kt] = v16f{};
 #pragma unroll
-        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[kt][r]);
-      } else {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int key = 64 * j + 32 * kt + 8 * (r >> 2) + 4 * hf + (r & 3);
-          if (key >= dm.N) s[kt][r] = -INFINITY;
-          mx = fmaxf(mx, s[kt][r]);
+        for (int ks = 0; ks < 8; ++ks) {       // behind a product: the read of the next tile's operand, at the end V's first ones
+          s[kt] = mfma_bf16(ak[ks], qf[ks], s[kt]);
+          if (kt + 1 < KT) ak[ks] = n_op_swz(ring + (kt + 1) * SWZ_TILE_B, no, ks);
+          else if (ks >= 4) tv[0][ks - 4] = t_op_swz(ring + KT * SWZ_TILE_B, to, ks - 4, 0);
+          __builtin_amdgcn_sched_barrier(0);
         }
       }
-    }
-    // The reference m moves only when the block's maximum exceeds it by more than 2^8: P then stays
-    // below 2^8 (harmless in bf16 and fp32) and the accumulators are rescaled a few times per row
-    // instead of every step.  (mx is finite: a block holds at least one valid key.)
-    mx = fmaxf(mx, partner_f32(mx)) * c2;
-    const bool moves = mx > m + 8.0f;
-    if (__any(moves)) {
-      const float m_new = moves ? mx : m;
-      const float alpha = __builtin_amdgcn_exp2f(m - m_new);
-      m = m_new;
-      lacc[0] *= alpha;
 #pragma unroll
-      for (int ct = 0; ct < 4; ++ct)
+      for (int kt = 0; kt < KT; ++kt) {
+        if (key0 + 32 * kt + 32 > dm.N) {      // (uniform) only the sequence's last key block can hold keys that do not exist
 #pragma unroll
-        for (int r = 0; r < 16; ++r) o[ct][r] *= alpha;
-    }
+          for (int r = 0; r < 16; ++r)
+            if (key0 + 32 * kt + 8 * (r >> 2) + 4 * hf + (r & 3) >= dm.N) s[kt][r] = -INFINITY;
+        }
 #pragma unroll
-    for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) s[kt][r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kt][r], c2, -m));
-    const uint4 ones = uint4{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};  // bf16 1.0: sums P over the keys
-#pragma unroll
-    for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-      for (int sx = 0; sx < 2; ++sx) {
-        const uint4 pb = acc_operand(s[kt], sx);
-        uint4 tv[4];
-#pragma unroll
-        for (int ct = 0; ct < 4; ++ct) tv[ct] = t_op(lds + (2 + kt) * TILE_B, tr_off, ct, sx);
-#pragma unroll
-        for (int ct = 0; ct < 4; ++ct) o[ct] = mfma_bf16(tv[ct], pb, o[ct]);
-        lacc = mfma_bf16(ones, pb, lacc);  // every row of this tile = the key sum of P (as rounded for the product above)
-        __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 5, 0);
+        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[kt][r]);
       }
-    sk.store(lds_next, t);  // (after the last block: into the buffer nobody reads any more)
-    sv.store(lds_next + 2 * TILE_B, t);
-    __syncthreads();
+      // The reference m moves only when the tiles' maximum exceeds it by more than 2^8: P then stays below 2^8 (harmless
+      // in bf16 and fp32) and the accumulators are rescaled a few times per row instead of every step.
+      if (__any(mx * c2 > m + 8.0f)) {
+        mx = fmaxf(mx, partner_f32(mx)) * c2;
+        const float m_new = mx > m + 8.0f ? mx : m;
+        const float alpha = __builtin_amdgcn_exp2f(m - m_new);
+        m = m_new;
+        lacc[0] *= alpha;
+#pragma unroll
+        for (int ct = 0; ct < 4; ++ct)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) o[ct][r] *= alpha;
+      }
+      auto weight = [&](int e) __attribute__((always_inline)) {   // P of element e % 16 of tile e / 16
+        s[e >> 4][e & 15] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e >> 4][e & 15], c2, -m));
+      };
+      const uint4 ones = uint4{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};  // bf16 1.0: sums P over the keys
+#pragma unroll
+      for (int e = 0; e < 8; ++e) weight(e);
+#pragma unroll
+      for (int g = 0; g < 2 * KT; ++g) {       // 16 keys; behind their products the next ones' exponentials and operand reads
+        const uint4 pb = acc_operand(s[g >> 1], g & 1);
+#pragma unroll
+        for (int ct = 0; ct < 4; ++ct) {
+          o[ct] = mfma_bf16(tv[g & 1][ct], pb, o[ct]);
+          if (g + 1 < 2 * KT) {
+            tv[(g + 1) & 1][ct] = t_op_swz(ring + (KT + ((g + 1) >> 1)) * SWZ_TILE_B, to, ct, (g + 1) & 1);
+            weight(8 * g + 8 + 2 * ct);
+            weight(8 * g + 9 + 2 * ct);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        lacc = mfma_bf16(ones, pb, lacc);      // every row of this tile = the key sum of P (as rounded for the product above)
+      }
+    };
+    auto scale_of = [&](int j) __attribute__((always_inline)) { return CODES ? qscale * fe.code_dk[(size_t)bh * dm.Tk + j] : QK_LOG2; };
+    int j = crow[0];
+    request(64 * j, 0);
+    for (int b = 0; b < dm.n_c; ++b) {
+      const int jn = crow[min(b + 1, dm.n_c - 1)], next = b + 1 < dm.n_c ? 64 * jn : -1;
+      const float c2 = scale_of(j);
+      if constexpr (KT == 2) {
+        step(64 * j, c2, b & 1, next);
+      } else {
+        step(64 * j, c2, 0, 64 * j + 32);
+        step(64 * j + 32, c2, 1, next);
+      }
+      j = jn;
+    }
   }
   const float l = lacc[0];
   const float inv_l = dm.n_c > 0 ? 1.0f / l : 0.f;
@@ -1575,12 +1577,6 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
 }
 
 // ---------------------------------------------------------------------------------------------
-constexpr int KV_STAGE_BYTES = 2 * 4 * TILE_B;  // dynamic LDS of the two per-query-block kernels
-template <class K>
-static bool allow_lds(K kernel) {
-  return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, KV_STAGE_BYTES) == hipSuccess;
-}
-
 // Do all of these layouts equal the contiguous [B,H,N,d] one?  (Then the instances with compile-time strides serve.)
 static bool contiguous(const Problem& p, std::initializer_list<const Layout*> ls) {
   const Layout c = contiguous_layout(p.H, p.N);
@@ -1616,22 +1612,17 @@ void launch_bwd_stats(const Problem& p, const void* q, const void* k, const void
 
 // The unquantised forward pass; with `codes`, the same on
 // INT8 codes of Q and K (SLA_QUANT_QK_INT8: integer products, 16-bit P and V).
-int launch_fwd_bf16(const Problem& p, const void* q, const void* k, const void* v, const int32_t* crit,
+void launch_fwd_bf16(const Problem& p, const void* q, const void* k, const void* v, const int32_t* crit,
                     const bf16_t* HZ, const bf16_t* proj_b, int phi_kind, void* out, const SaveTo* save,
                     const CodeScales* codes, hipStream_t stream) {
   const unsigned grid = (unsigned)(8 * ((p.Tq + 7) / 8) * p.BH);
-  static const bool ok = allow_lds(fwd_bf16_kernel<4, false, false>) && allow_lds(fwd_bf16_kernel<2, false, false>) &&
-                         allow_lds(fwd_bf16_kernel<4, true, false>) && allow_lds(fwd_bf16_kernel<2, true, false>) &&
-                         allow_lds(fwd_bf16_kernel<4, false, true>) && allow_lds(fwd_bf16_kernel<2, false, true>) &&
-                         allow_lds(fwd_bf16_kernel<4, true, true>) && allow_lds(fwd_bf16_kernel<2, true, true>);
-  if (!ok) return -1;
   const FwdEpilogue fe{HZ, HZ ? proj_b : nullptr, (bf16_t*)out, phi_kind, save ? save->lse2 : nullptr, save ? save->os : nullptr,
                        save ? save->hdr_dst : nullptr, save ? save->hdr : SavedHeader{},
                        codes ? codes->dq : nullptr, codes ? codes->dk : nullptr, codes ? (const bf16_t*)codes->q_lin : nullptr, p.lq};
   BwdDims dm = bwd_dims(p);
   if (codes) dm.lq = dm.lk = contiguous_layout(p.H, p.N);   // the code tensors are the library's own
   const bool st = codes ? !contiguous(p, {&p.lv, &p.lo}) : !contiguous(p, {&p.lq, &p.lk, &p.lv, &p.lo});
-#define SLA_FWD16(NW, CODES, ST) fwd_bf16_kernel<NW, CODES, ST><<<grid, NW * 64, KV_STAGE_BYTES, stream>>>( \
+#define SLA_FWD16(NW, CODES, ST) fwd_bf16_kernel<NW, CODES, ST><<<grid, NW * 64, 0, stream>>>( \
       (const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, crit, dm, fe)
 #define SLA_FWD16_ST(NW, CODES) { if (st) SLA_FWD16(NW, CODES, true); else SLA_FWD16(NW, CODES, false); }
   if (p.block_q == 128) {
@@ -1641,7 +1632,6 @@ int launch_fwd_bf16(const Problem& p, const void* q, const void* k, const void* 
   }
 #undef SLA_FWD16_ST
 #undef SLA_FWD16
-  return 0;
 }
 
 __global__ void __launch_bounds__(256) bwd_delta_kernel(const DeltaArgs X) { delta_block(X, blockIdx.x); }

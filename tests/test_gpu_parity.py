@@ -303,6 +303,31 @@ def test_unquantised_forward_matches_oracle(H, grid, bq, rc, rm, proj, phi):
         assert np.linalg.norm(got - r["out"]) / np.linalg.norm(r["out"]) <= 5e-3
 
 
+@pytest.mark.parametrize("quant", [so.QUANT_NONE, so.QUANT_QK_INT8])
+@pytest.mark.parametrize("bq", [64, 128])
+@pytest.mark.parametrize("N", [31, 33, 65, 96, 97, 223, 289])
+def test_sixteen_bit_forward_at_the_edges_of_its_key_tiles(N, bq, quant):
+    """Key tiles of 32 with one key, all of them, all but one or none at all (the second tile of the last block), one
+    and several query blocks, V from an odd element on.  Bounds: those of the two tests of the modes (bf16 roundings of
+    P, the summaries and the output)."""
+    cfg = _cfg(2, (1, 1, N), bq, 1.0 if N < 200 else 0.5, 0.0 if N < 200 else 0.5, cid=420)
+    q, k, v = synth.make_qkv(cfg)
+    W = synth.make_proj(cfg)
+    qd, kd, Wd = pu.to_dev(q, k, W)
+    vd = torch.empty(v.numel() + 1, dtype=torch.bfloat16, device="cuda")[1:].view(v.shape).copy_(v)
+    rc, rm = cfg.topk_ratio, cfg.marginal_ratio
+    out = sla.sla_attention_fwd(qd, kd, vd, bq, 64, rc, rm, proj_w=Wd,
+                                quant_mode=sla.QUANT_NONE if quant == so.QUANT_NONE else sla.QUANT_QK_INT8)
+    mask = sla.sla_classify_blocks(qd, kd, bq, 64, rc, rm, want_scores=False)[0].cpu().numpy()
+    torch.cuda.synchronize()
+    for h in range(2):
+        ref = so.sla_forward_head(synth.as_f64(q[0, h]), synth.as_f64(k[0, h]), synth.as_f64(v[0, h]), bq, 64, rc, rm,
+                                  proj_w=synth.as_f64(W), quant=quant, mask=mask[0, h])["out"]
+        got = out[0, h].float().cpu().numpy().astype(np.float64)
+        pu.check_output(got, ref, "N = %d head %d" % (N, h))
+        assert np.linalg.norm(got - ref) / np.linalg.norm(ref) <= 5e-3
+
+
 @pytest.mark.parametrize("mode", ["none", "qk_int8"])
 def test_sixteen_bit_forward_takes_token_major_layouts(mode):
     """The strided entry point with SLA_QUANT_NONE / SLA_QUANT_QK_INT8 on [B,N,H,d] memory and on one packed
