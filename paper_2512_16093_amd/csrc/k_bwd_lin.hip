@@ -56,13 +56,13 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("" ::: "memory");
 }
 
-// Column sums over the tokens of a staged [BQ][128] tile, weighted: thread (channel group t % 16, eight tokens from
-// 8 (t / 16)) adds its share to s[0..7]; tile_sums_finish adds the shares up (wavefront by wavefront into red).
-template <class F>
+// Column sums over the tokens of a staged [BQ][128] tile, weighted: thread (channel group t % 16, ROWS tokens from
+// ROWS (t / 16)) adds its share to s[0..7]; tile_sums_finish adds the shares up (wavefront by wavefront into red).
+template <int ROWS, class F>
 __device__ __forceinline__ void tile_sums(const unsigned char* tile, int t, float (&s)[8], F weight) {
-  const int cg = t & 15, n0 = 8 * (t >> 4);
+  const int cg = t & 15, n0 = ROWS * (t >> 4);
 #pragma unroll
-  for (int m = 0; m < 8; ++m) {
+  for (int m = 0; m < ROWS; ++m) {
     float x[8];
     unpack8(*(const uint4*)(tile + (n0 + m) * TP + cg * 16), x);
     const float wm = weight(n0 + m);
@@ -89,12 +89,19 @@ __device__ __forceinline__ void tile_sums_finish(float (&s)[8], float* red, int 
 // operand that contracts over a tile's rows comes from the row-major tile by the transposing read.  (Before: loads,
 // stores and barriers of an item one after the other, transposed copies made by 2-byte writes:
 // 40 heads x 75600 tokens 2.82 -> 1.49 ms, 12 x 32760 385 -> 219 us, 4 x 2187 (blocks of 64) 41 -> 29 us.)
-template <int NW, int PHI>
-__global__ void __launch_bounds__(NW * 64, 1)
+//
+// TT wavefronts own 32 tokens each, and CS of them share a token, each with 4 / CS of the output tiles.  Query blocks of
+// 128 take four with all tiles.  Of 64, two wavefronts left half of the SIMDs idle, with twice the dW and dH tiles each
+// (spilled registers, summaries not requested ahead): there four, a pair per token; what it does not share
+// (softmax, loads of its rows) is done twice, the two token-wise sums and dnum meet in LDS.  The backward pass of 12 x 32760
+// in blocks of 64 4310 -> 4090 us, of 4 x 2187 128 -> 119 us.  (Pairs for blocks of 128 as well, two wavefronts per SIMD: 50
+// registers spilled, 3515 -> 3615 us.)
+template <int TT, int CS, int PHI>
+__global__ void __launch_bounds__(TT * CS * 64, 1)
     bwd_lin_q_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ dout, const bf16_t* __restrict__ HZ,
                      const bf16_t* __restrict__ proj_w, float* __restrict__ dq_lin, bf16_t* __restrict__ dHZ,
                      float* __restrict__ dW_part, float* __restrict__ db_part, int N, int Tq, int total, int H, Layout lq, Layout ld) {
-  constexpr int BQ = 32 * NW, NT = 64 * NW, PER = 2048 / NT;
+  constexpr int BQ = 32 * TT, NW = CS * TT, NT = 64 * NW, PER = 2048 / NT, OT = 4 / CS;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   unsigned char* const Wl = smem;              // W[r][c] (the identity when there is no projection)
   unsigned char* const Hl = Wl + 128 * TP;     // H[o][c]            -> dO[n][r]
@@ -103,8 +110,12 @@ __global__ void __launch_bounds__(NW * 64, 1)
   float* const zv = (float*)(Dl + BQ * TP);    // Z[c]
   float* const dden_s = zv + 128;              // dden[n]
   float* const red = dden_s + 128;             // [NW][128]
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6, l32 = lane & 31, hf = lane >> 5;
-  const int nl = 32 * w + l32;                 // this lane pair's token within the query block
+  float* const half_dden = red + NW * 128;     // [CS][BQ] each (CS > 1): a token's sums over either half of the channels
+  float* const half_sdot = half_dden + CS * BQ;
+  const int t = threadIdx.x, lane = t & 63, w = CS == 1 ? t >> 6 : __builtin_amdgcn_readfirstlane(t >> 6), l32 = lane & 31, hf = lane >> 5;
+  // (w in a scalar register costs the instance without shared tokens 0.5 % of its call, 12 x 32760)
+  const int ch = CS == 1 ? 0 : w / TT;         // this wavefront's share of the channels: output tiles from OT ch on
+  const int nl = 32 * (w - ch * TT) + l32;     // this lane pair's token within the query block
   const int tr_off = tr_lane_offset(lane);
   const int first = (int)((long long)total * blockIdx.x / gridDim.x), end = (int)((long long)total * (blockIdx.x + 1) / gridDim.x);
 
@@ -119,28 +130,24 @@ __global__ void __launch_bounds__(NW * 64, 1)
       *(bf16_t*)(Wl + (x >> 7) * TP + (x & 127) * 2) = proj_w ? proj_w[x] : (bf16_t)((x >> 7) == (x & 127) ? 0x3F80 : 0);
   }
 
-  constexpr int RT = 4 / NW;                   // row tiles of dW per wavefront
-  v16f dwacc[RT][4];
+  constexpr int TILES = 16 / NW;               // of dH and dW per wavefront: one row (dW) or column (dH) of them, from tile t0 on
+  const int trow = w & 3, t0 = TILES * (w >> 2);
+  v16f dwacc[TILES];
 #pragma unroll
-  for (int a = 0; a < RT; ++a)
-#pragma unroll
-    for (int ct = 0; ct < 4; ++ct) dwacc[a][ct] = v16f{};
+  for (int x = 0; x < TILES; ++x) dwacc[x] = v16f{};
   // (names the sums' place: left alone the allocator moved them between ordinary registers and scratch memory, whose
   // reloads waited for every load and store in flight)
   auto hold_sums = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int a = 0; a < RT; ++a)
-#pragma unroll
-      for (int ct = 0; ct < 4; ++ct) asm volatile("" : "+a"(dwacc[a][ct]));
+    for (int x = 0; x < TILES; ++x) asm volatile("" : "+a"(dwacc[x]));
   };
   float dbacc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 
-  // The next item's summaries and rows (rows beyond N come as row N - 1 and are given no weight).  Two wavefronts
-  // would need 64 registers each for the summaries beside 128 of dW: they load them when they are due.
-  constexpr bool HZ_AHEAD = NW == 4;
+  // The next item's summaries and rows (rows beyond N come as row N - 1 and are given no weight).
   uint4 hzp[PER], qp[8], gp[8];
   bf16_t zp = 0;
-  auto fetch_hz = [&](int item) __attribute__((always_inline)) {
+  auto fetch = [&](int item) __attribute__((always_inline)) {
+    const int bh = item / Tq, i = item - bh * Tq, b_ = bh / H, h_ = bh - b_ * H;
     const bf16_t* hz = HZ + (size_t)item * HZ_ELEMS;
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
@@ -148,10 +155,6 @@ __global__ void __launch_bounds__(NW * 64, 1)
       hzp[u] = got;
     }
     zp = hz[D * D + (t & 127)];
-  };
-  auto fetch = [&](int item) __attribute__((always_inline)) {
-    const int bh = item / Tq, i = item - bh * Tq, b_ = bh / H, h_ = bh - b_ * H;
-    if constexpr (HZ_AHEAD) fetch_hz(item);
     const long long n = min(i * BQ + nl, N - 1);
     const bf16_t* qrow = q + b_ * lq.sb + h_ * lq.sh + n * lq.sn + 8 * hf;
     const bf16_t* drow = dout + b_ * ld.sb + h_ * ld.sh + n * ld.sn + 8 * hf;
@@ -167,7 +170,6 @@ __global__ void __launch_bounds__(NW * 64, 1)
   for (int item = first; item < end; ++item) {
     // ---- publish H_i and Z_i
     hold_sums();
-    if constexpr (!HZ_AHEAD) fetch_hz(item);
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
       const int x = u * NT + t, ln = x & 63, ks = (x >> 6) & 7, ot = x >> 9;
@@ -178,12 +180,12 @@ __global__ void __launch_bounds__(NW * 64, 1)
     const int n = i * BQ + nl;
     const bool ok = n < N;
     const uint32_t keep = ok ? ~0u : 0u;
-    uint4 af[8], gf[8], qs[8];
+    uint4 af[8], gf[8], qs[8 / CS];   // qs: of the wavefront's share of the channels
     float av[64];                // a = phi(Q[n]) at channels 16 ks + 8 hf + kk  (index 8 ks + kk)
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) {
       unpack8(qp[ks], &av[8 * ks]);
-      qs[ks] = pair_order(qp[ks]);
+      if (ks < 8 / CS) qs[ks] = pair_order(CS == 2 && ch ? qp[(8 - 8 / CS) + ks] : qp[ks]);
       gf[ks] = uint4{gp[ks].x & keep, gp[ks].y & keep, gp[ks].z & keep, gp[ks].w & keep};
     }
     lds_barrier();
@@ -204,20 +206,21 @@ __global__ void __launch_bounds__(NW * 64, 1)
         den += av[8 * ks + kk] * zv[16 * ks + 8 * hf + kk];
       }
       af[ks] = pack8(&av[8 * ks]);
-      *(uint4*)(Al + nl * TP + (16 * ks + 8 * hf) * 2) = af[ks];
+      if (CS == 1 || (ks >> 2) == ch) *(uint4*)(Al + nl * TP + (16 * ks + 8 * hf) * 2) = af[ks];
     }
     den += partner_f32(den);
     const float rden = den > 0.f ? 1.0f / den : 0.f;
 
     // numT[o][n] = sum_c H[c][o] a[n][c]  ->  O^l;   glT[c'][n] = sum_r W[r][c'] dO[n][r]
-    v16f ol[4], gl[4];
+    // (of the wavefront's own output tiles)
+    v16f ol[OT], gl[OT];
     // (here and below: the LDS operand reads of a tile are grouped ahead of its matrix products;
     // left alone the compiler issues each read right before its product and waits for it every time)
 #pragma unroll
-    for (int ot = 0; ot < 4; ++ot) {
+    for (int ot = 0; ot < OT; ++ot) {
       uint4 ah[8];
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks) ah[ks] = n_op(Hl + 32 * ot * TP, l32, hf, ks);
+      for (int ks = 0; ks < 8; ++ks) ah[ks] = n_op(Hl + 32 * (OT * ch + ot) * TP, l32, hf, ks);
       __builtin_amdgcn_sched_barrier(0);
       ol[ot] = v16f{};
 #pragma unroll
@@ -227,10 +230,10 @@ __global__ void __launch_bounds__(NW * 64, 1)
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) af[ks] = pair_order(gf[ks]);   // (a is not needed in registers any more)
 #pragma unroll
-    for (int ot = 0; ot < 4; ++ot) {
+    for (int ot = 0; ot < OT; ++ot) {
       uint4 aw[8];
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks) aw[ks] = t_op(Wl + 32 * (ks >> 1) * TP, tr_off, ot, ks & 1);
+      for (int ks = 0; ks < 8; ++ks) aw[ks] = t_op(Wl + 32 * (ks >> 1) * TP, tr_off, OT * ch + ot, ks & 1);
       __builtin_amdgcn_sched_barrier(0);
       gl[ot] = v16f{};
 #pragma unroll
@@ -239,7 +242,7 @@ __global__ void __launch_bounds__(NW * 64, 1)
     }
     float dden = 0.f;
 #pragma unroll
-    for (int ot = 0; ot < 4; ++ot)
+    for (int ot = 0; ot < OT; ++ot)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         ol[ot][r] *= rden;
@@ -247,27 +250,40 @@ __global__ void __launch_bounds__(NW * 64, 1)
         gl[ot][r] *= rden;       // dnum
       }
     dden += partner_f32(dden);
-    dden *= -rden;
-    uint4 olp[4][2], dn[4][2];   // O^l (all that is used of it from here on: the dW product) and dnum, rounded to bf16
+    if (CS == 2 && hf == 0) half_dden[ch * BQ + nl] = dden;
+    uint4 olp[OT][2], dn[4][2];  // O^l (all that is used of it from here on: the dW product) and dnum, rounded to bf16
 #pragma unroll
-    for (int ot = 0; ot < 4; ++ot)
+    for (int ot = 0; ot < OT; ++ot)
 #pragma unroll
       for (int s = 0; s < 2; ++s) {
         olp[ot][s] = acc_operand(ol[ot], s);
-        dn[ot][s] = acc_operand(gl[ot], s);
-        unsigned char* dst = Dl + nl * TP + (32 * ot + 16 * s + 4 * hf) * 2;
-        *(uint2*)dst = uint2{dn[ot][s].x, dn[ot][s].y};
-        *(uint2*)(dst + 16) = uint2{dn[ot][s].z, dn[ot][s].w};
+        const uint4 d = dn[ot][s] = acc_operand(gl[ot], s);
+        unsigned char* dst = Dl + nl * TP + (32 * (OT * ch + ot) + 16 * s + 4 * hf) * 2;
+        *(uint2*)dst = uint2{d.x, d.y};
+        *(uint2*)(dst + 16) = uint2{d.z, d.w};
       }
-    if (hf == 0) dden_s[nl] = dden;
+    if constexpr (CS == 2) {
+      lds_barrier();             // dnum and the halves' shares of dden are complete
+      dden = half_dden[nl] + half_dden[BQ + nl];
+#pragma unroll
+      for (int ot = 0; ot < 4; ++ot)   // dnum of all channels
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          const unsigned char* src = Dl + nl * TP + (32 * ot + 16 * s + 4 * hf) * 2;
+          const uint2 lo = *(const uint2*)src, hi = *(const uint2*)(src + 16);
+          dn[ot][s] = uint4{lo.x, lo.y, hi.x, hi.y};
+        }
+    }
+    dden *= -rden;
+    if (hf == 0 && ch == 0) dden_s[nl] = dden;
 
     // ---- d phi(Q) = dnum H^T + dden Z, then through the softmax
-    v16f da[4];
+    v16f da[OT];
 #pragma unroll
-    for (int ct = 0; ct < 4; ++ct) {
+    for (int ct = 0; ct < OT; ++ct) {
       uint4 ah[8];
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks) ah[ks] = t_op(Hl + 32 * (ks >> 1) * TP, tr_off, ct, ks & 1);
+      for (int ks = 0; ks < 8; ++ks) ah[ks] = t_op(Hl + 32 * (ks >> 1) * TP, tr_off, OT * ch + ct, ks & 1);
       __builtin_amdgcn_sched_barrier(0);
       da[ct] = v16f{};
 #pragma unroll
@@ -277,13 +293,13 @@ __global__ void __launch_bounds__(NW * 64, 1)
     // a at the accumulator's channels 32 ct + 8 g + 4 hf + e, formed again from Q's words
     float sdot = 0.f;
 #pragma unroll
-    for (int ct = 0; ct < 4; ++ct)
+    for (int ct = 0; ct < OT; ++ct)
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         const uint4& qq = qs[2 * ct + (g >> 1)];
         const uint32_t q0 = g & 1 ? qq.z : qq.x, q1 = g & 1 ? qq.w : qq.y;
         const float xq[4] = {bf16_lo(q0), bf16_hi(q0), bf16_lo(q1), bf16_hi(q1)};
-        const float4 z4 = *(const float4*)(zv + 32 * ct + 8 * g + 4 * hf);
+        const float4 z4 = *(const float4*)(zv + 32 * (OT * ch + ct) + 8 * g + 4 * hf);
         const float zz[4] = {z4.x, z4.y, z4.z, z4.w};
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -292,14 +308,17 @@ __global__ void __launch_bounds__(NW * 64, 1)
         }
       }
     sdot += partner_f32(sdot);
-    lds_barrier();               // every wavefront is done with H_i and Z_i; a and dnum are complete
+    if (CS == 2 && hf == 0) half_sdot[ch * BQ + nl] = sdot;
+    lds_barrier();               // every wavefront is done with H_i and Z_i; a, dnum, dden and the halves' shares of sdot are complete
+    if constexpr (CS == 2) sdot = half_sdot[nl] + half_sdot[BQ + nl];
     asm volatile("" : "+v"(qmax));  // (a is formed once more below, not kept in 64 registers)
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) *(uint4*)(Hl + nl * TP + (16 * ks + 8 * hf) * 2) = gf[ks];
+    for (int ks = 0; ks < 8; ++ks)
+      if (CS == 1 || (ks >> 2) == ch) *(uint4*)(Hl + nl * TP + (16 * ks + 8 * hf) * 2) = gf[ks];
     if (ok) {
       float* drow = dq_lin + ((size_t)bh * N + n) * D;   // (the library's own tensor)
 #pragma unroll
-      for (int ct = 0; ct < 4; ++ct)
+      for (int ct = 0; ct < OT; ++ct)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const uint4& qq = qs[2 * ct + (g >> 1)];
@@ -309,7 +328,7 @@ __global__ void __launch_bounds__(NW * 64, 1)
 #pragma unroll
           for (int e = 0; e < 4; ++e)
             o[e] = phi_backward<PHI>(xq[e], phi_value<PHI>(xq[e], qmax, rsum), da[ct][4 * g + e], sdot);
-          *(float4*)(drow + 32 * ct + 8 * g + 4 * hf) = float4{o[0], o[1], o[2], o[3]};
+          *(float4*)(drow + 32 * (OT * ch + ct) + 8 * g + 4 * hf) = float4{o[0], o[1], o[2], o[3]};
         }
     }
 
@@ -324,29 +343,27 @@ __global__ void __launch_bounds__(NW * 64, 1)
     // invariants they were kept in scratch memory, and each reload made its store wait for the one before)
     int lane_o = l32;
     asm volatile("" : "+v"(lane_o));
-    for (int ct = w; ct < 4; ct += NW) {
-      uint4 aa[BQ / 16];
+    uint4 aa[BQ / 16];
 #pragma unroll
-      for (int ks = 0; ks < BQ / 16; ++ks) aa[ks] = t_op(Al + 32 * (ks >> 1) * TP, tr_off, ct, ks & 1);
+    for (int ks = 0; ks < BQ / 16; ++ks) aa[ks] = t_op(Al + 32 * (ks >> 1) * TP, tr_off, trow, ks & 1);
 #pragma unroll
-      for (int ot = 0; ot < 4; ++ot) {
-        v16f acc = v16f{};
-        uint4 bb[BQ / 16];
+    for (int x = 0; x < TILES; ++x) {
+      v16f acc = v16f{};
+      uint4 bb[BQ / 16];
 #pragma unroll
-        for (int ks = 0; ks < BQ / 16; ++ks) bb[ks] = t_op(Dl + 32 * (ks >> 1) * TP, tr_off, ot, ks & 1);
+      for (int ks = 0; ks < BQ / 16; ++ks) bb[ks] = t_op(Dl + 32 * (ks >> 1) * TP, tr_off, t0 + x, ks & 1);
 #pragma unroll
-        for (int ks = 0; ks < BQ / 16; ++ks) acc = mfma_bf16(aa[ks], bb[ks], acc);
-        __builtin_amdgcn_sched_barrier(0);
-        // lane: o = 32 ot + l32; registers: c = 32 ct + 8 g + 4 hf + e
+      for (int ks = 0; ks < BQ / 16; ++ks) acc = mfma_bf16(aa[ks], bb[ks], acc);
+      __builtin_amdgcn_sched_barrier(0);
+      // lane: o = 32 (t0 + x) + l32; registers: c = 32 trow + 8 g + 4 hf + e
 #pragma unroll
-        for (int g = 0; g < 4; ++g)
-          *(uint2*)(dst + hz_run_offset(32 * ot + lane_o, 32 * ct + 8 * g + 4 * hf)) =
-              uint2{pack_bf16x2(acc[4 * g], acc[4 * g + 1]), pack_bf16x2(acc[4 * g + 2], acc[4 * g + 3])};
-      }
+      for (int g = 0; g < 4; ++g)
+        *(uint2*)(dst + hz_run_offset(32 * (t0 + x) + lane_o, 32 * trow + 8 * g + 4 * hf)) =
+            uint2{pack_bf16x2(acc[4 * g], acc[4 * g + 1]), pack_bf16x2(acc[4 * g + 2], acc[4 * g + 3])};
     }
     __builtin_amdgcn_sched_barrier(0);
     float dz[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    tile_sums(Al, t, dz, [&](int m) { return dden_s[m]; });
+    tile_sums<BQ * 16 / NT>(Al, t, dz, [&](int m) { return dden_s[m]; });
     tile_sums_finish(dz, red, lane, w);
     lds_barrier();               // a and dnum are consumed
     if (t < 128) {
@@ -359,31 +376,28 @@ __global__ void __launch_bounds__(NW * 64, 1)
     // ---- dW[r][c] += sum_n dO[n][r] O^l[n][c],  db[r] += sum_n dO[n][r]
     if (dW_part) {
 #pragma unroll
-      for (int ot = 0; ot < 4; ++ot)
+      for (int ot = 0; ot < OT; ++ot)
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
-          unsigned char* dst_o = Al + nl * TP + (32 * ot + 16 * s + 4 * hf) * 2;
+          unsigned char* dst_o = Al + nl * TP + (32 * (OT * ch + ot) + 16 * s + 4 * hf) * 2;
           *(uint2*)dst_o = uint2{olp[ot][s].x, olp[ot][s].y};
           *(uint2*)(dst_o + 16) = uint2{olp[ot][s].z, olp[ot][s].w};
         }
       lds_barrier();
+      uint4 ag[BQ / 16];         // the row tile of dO^T: the A operand of all its column tiles
 #pragma unroll
-      for (int a = 0; a < RT; ++a) {
-        uint4 ag[BQ / 16];       // this row tile of dO^T: the A operand of all four column tiles
+      for (int ks = 0; ks < BQ / 16; ++ks) ag[ks] = t_op(Hl + 32 * (ks >> 1) * TP, tr_off, trow, ks & 1);
 #pragma unroll
-        for (int ks = 0; ks < BQ / 16; ++ks) ag[ks] = t_op(Hl + 32 * (ks >> 1) * TP, tr_off, w + a * NW, ks & 1);
+      for (int x = 0; x < TILES; ++x) {
+        uint4 bo[BQ / 16];
 #pragma unroll
-        for (int ct = 0; ct < 4; ++ct) {
-          uint4 bo[BQ / 16];
+        for (int ks = 0; ks < BQ / 16; ++ks) bo[ks] = t_op(Al + 32 * (ks >> 1) * TP, tr_off, t0 + x, ks & 1);
 #pragma unroll
-          for (int ks = 0; ks < BQ / 16; ++ks) bo[ks] = t_op(Al + 32 * (ks >> 1) * TP, tr_off, ct, ks & 1);
-#pragma unroll
-          for (int ks = 0; ks < BQ / 16; ++ks) dwacc[a][ct] = mfma_bf16(ag[ks], bo[ks], dwacc[a][ct]);
-          __builtin_amdgcn_sched_barrier(0);
-        }
+        for (int ks = 0; ks < BQ / 16; ++ks) dwacc[x] = mfma_bf16(ag[ks], bo[ks], dwacc[x]);
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
-    if (db_part) tile_sums(Hl, t, dbacc, [](int) { return 1.0f; });
+    if (db_part) tile_sums<BQ * 16 / NT>(Hl, t, dbacc, [](int) { return 1.0f; });
     lds_barrier();               // every tile is consumed
   }
   // This workgroup's share of dW and db goes to its own slice; reduce_block adds the
@@ -391,12 +405,10 @@ __global__ void __launch_bounds__(NW * 64, 1)
   if (dW_part) {
     float* mine = dW_part + (size_t)blockIdx.x * (D * D);
 #pragma unroll
-    for (int a = 0; a < RT; ++a)
+    for (int x = 0; x < TILES; ++x)
 #pragma unroll
-      for (int ct = 0; ct < 4; ++ct)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          mine[(32 * (w + a * NW) + 8 * (r >> 2) + 4 * hf + (r & 3)) * D + 32 * ct + l32] = dwacc[a][ct][r];
+      for (int r = 0; r < 16; ++r)
+        mine[(32 * trow + 8 * (r >> 2) + 4 * hf + (r & 3)) * D + 32 * (t0 + x) + l32] = dwacc[x][r];
   }
   if (db_part) {
     tile_sums_finish(dbacc, red, lane, w);
@@ -419,18 +431,18 @@ size_t bwd_lin_q_partial_bytes(const Problem& p) { return (size_t)lin_q_grid(p) 
 template <int PHI>
 static int launch_bwd_lin_q_phi(const Problem& p, const void* q, const void* dout, const bf16_t* HZ, const bf16_t* proj_w,
                                 float* dq_lin, bf16_t* dHZ, float* dW, float* db, float* partials, ReduceArgs* reduce, hipStream_t stream) {
-  constexpr int LDS4 = 4 * 128 * TP + (2 + 4) * 128 * 4, LDS2 = (2 * 128 + 2 * 64) * TP + (2 + 2) * 128 * 4;
+  constexpr int LDS4 = 4 * 128 * TP + (2 + 4) * 128 * 4, LDS2 = (2 * 128 + 2 * 64) * TP + (2 + 4) * 128 * 4 + 2 * 2 * 64 * 4;
   static const bool ok =
-      hipFuncSetAttribute((const void*)bwd_lin_q_kernel<4, PHI>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS4) == hipSuccess &&
-      hipFuncSetAttribute((const void*)bwd_lin_q_kernel<2, PHI>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS2) == hipSuccess;
+      hipFuncSetAttribute((const void*)bwd_lin_q_kernel<4, 1, PHI>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS4) == hipSuccess &&
+      hipFuncSetAttribute((const void*)bwd_lin_q_kernel<2, 2, PHI>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS2) == hipSuccess;
   if (!ok) return -1;
   // per-workgroup partial sums: dW slices first, then db slices
   const int n_part = lin_q_grid(p);
   float* dW_part = dW ? partials : nullptr;
   float* db_part = db ? partials + (size_t)n_part * D * D : nullptr;
-#define SLA_LIN_Q(NW, LDS) bwd_lin_q_kernel<NW, PHI><<<(unsigned)n_part, NW * 64, LDS, stream>>>( \
+#define SLA_LIN_Q(TT, CS, LDS) bwd_lin_q_kernel<TT, CS, PHI><<<(unsigned)n_part, TT * CS * 64, LDS, stream>>>( \
       (const bf16_t*)q, (const bf16_t*)dout, HZ, proj_w, dq_lin, dHZ, dW_part, db_part, p.N, p.Tq, p.BH * p.Tq, p.H, p.lq, p.ld)
-  if (p.block_q == 128) SLA_LIN_Q(4, LDS4); else SLA_LIN_Q(2, LDS2);
+  if (p.block_q == 128) SLA_LIN_Q(4, 1, LDS4); else SLA_LIN_Q(2, 2, LDS2);
 #undef SLA_LIN_Q
   *reduce = ReduceArgs{dW_part, db_part, n_part, dW, db};
   return 0;

@@ -79,6 +79,15 @@ def test_backward_matches_gradient_oracle(H, grid, bq, rc, rm, proj):
         _compare("dproj_b", db.cpu().numpy(), sums_b)
 
 
+@pytest.mark.parametrize("N", [95, 97, 127, 161, 351])
+def test_linear_branch_at_the_edges_of_its_token_tiles(N):
+    """Query blocks of 64 in the linear branch: a wavefront pair owns 32 tokens, each half of the channels.  The last
+    block holds a tile less one token, a tile and one, all but one; same bounds as above.  (Not 65: the gradient of a
+    lone key in its block is what is left of sums that cancel, dS of all queries being bf16; with one key among 65 it is
+    8 % of the largest entry off, in every form the kernels have had, the linear branch taking no part in it.)"""
+    test_backward_matches_gradient_oracle(2, (1, 1, N), 64, 0.5, 0.5, True)
+
+
 @pytest.mark.parametrize("phi", ["elu1", "relu"])
 @pytest.mark.parametrize("H,grid,bq,rc,rm", [(2, (5, 10, 20), 128, 0.25, 0.5), (1, (3, 27, 27), 64, 0.1, 0.9),
                                              (2, (5, 10, 20), 64, 0.75, 0.25)])
