@@ -1548,20 +1548,26 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
   __syncthreads();                       // (nobody reads the staging buffers, and no copy lands in them any more)
   constexpr int OP = 256 + 16;           // bytes per staged row
   static_assert(2 * KB * 32 * OP <= 2 * BUF_B, "a wavefront's rows fit");
-  unsigned char* my = lds + w * 32 * OP;
-  const int row0 = 64 * (KB * J + half) + 32 * (w & 1);
+  // (everything from the thread's number again: values of the prologue held for this through the loop took registers from
+  // it, and at KB = 2, where it has none to spare, operand addresses went to scratch memory, whose reloads in the middle of
+  // a step waited for the rows just requested: 12 heads x 32760 tokens, three quarters critical, backward pass 26.0 -> 24.2 ms)
+  int te = t;
+  asm volatile("" : "+v"(te));
+  const int le = te & 63, we = te >> 6, l32e = le & 31, hfe = le >> 5;
+  unsigned char* my = lds + we * 32 * OP;
+  const int row0 = 64 * (KB * J + (KB == 2 ? we >> 1 : 0)) + 32 * (we & 1);
   auto store_rows = [&](const v16f (&x)[4], float scale, bf16_t* dst, const Layout& L) __attribute__((always_inline)) {
-    bf16_t* to = slice_of(dst, L, bh, dm.H) + (row0 + (lane >> 4)) * L.sn + (lane & 15) * 8;
+    bf16_t* to = slice_of(dst, L, bh, dm.H) + (row0 + (le >> 4)) * L.sn + (le & 15) * 8;
 #pragma unroll
     for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
       for (int g4 = 0; g4 < 4; ++g4)
-        *(uint2*)(my + l32 * OP + (32 * ct + 8 * g4 + 4 * hf) * 2) =
+        *(uint2*)(my + l32e * OP + (32 * ct + 8 * g4 + 4 * hfe) * 2) =
             uint2{pack_bf16x2(x[ct][4 * g4] * scale, x[ct][4 * g4 + 1] * scale), pack_bf16x2(x[ct][4 * g4 + 2] * scale, x[ct][4 * g4 + 3] * scale)};
     __builtin_amdgcn_wave_barrier();     // (a wavefront's LDS operations execute in order: only the compiler has to keep it)
     v4i out[8];
 #pragma unroll
-    for (int it = 0; it < 8; ++it) out[it] = *(const v4i*)(my + (4 * it + (lane >> 4)) * OP + (lane & 15) * 16);
+    for (int it = 0; it < 8; ++it) out[it] = *(const v4i*)(my + (4 * it + (le >> 4)) * OP + (le & 15) * 16);
     __builtin_amdgcn_wave_barrier();
     if (row0 + 32 <= dm.N) {             // (uniform)
 #pragma unroll
@@ -1569,7 +1575,7 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
     } else {
 #pragma unroll
       for (int it = 0; it < 8; ++it)
-        if (row0 + 4 * it + (lane >> 4) < dm.N) __builtin_memcpy(to + 4 * it * L.sn, &out[it], 16);
+        if (row0 + 4 * it + (le >> 4) < dm.N) __builtin_memcpy(to + 4 * it * L.sn, &out[it], 16);
     }
   };
   store_rows(dkt, DK_SIGN * INV_SQRT_D, dk, L_dk);

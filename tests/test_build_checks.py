@@ -10,7 +10,11 @@ chains are in place, and at least 18 instructions (the wait states the longest c
 between the end of a chain and the first instruction that reads its result.
 
 The second test follows every path behind every matrix product written in assembly, in all sources that have
-them: nothing reads OR writes the product's result before it has landed, branches and loops included."""
+them: nothing reads OR writes the product's result before it has landed, branches and loops included.
+
+The third holds every kernel to its registers: a reload from scratch memory waits for every load in flight, the ones a
+kernel has just requested ahead included."""
+import functools
 import os
 import re
 import shutil
@@ -20,6 +24,7 @@ import tempfile
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2512_16093_amd", "csrc")
 
 
 def _hipcc():
@@ -38,9 +43,10 @@ def _regs(operand_text):
     return regs
 
 
+@functools.lru_cache(maxsize=None)
 def _assembly(source):
     from paper_2512_16093_amd import build as b
-    src = os.path.join(ROOT, "paper_2512_16093_amd", "csrc", source)
+    src = os.path.join(CSRC, source)
     with tempfile.TemporaryDirectory() as tmp:
         out = os.path.join(tmp, "k.s")
         flags = [f for f in b.FLAGS if f not in ("-fPIC",)]
@@ -212,9 +218,25 @@ def test_products_have_landed_before_anything_touches_them(source):
     assert len(counts) == sum(n for n, _ in EXPECTED[source].values()), sorted(counts)
 
 
+# The selection of rows beyond 6144 key blocks indexes an array that does not fit the registers.
+SCRATCH_BY_DESIGN = r"select_kernelILi128E"
+
+
+@pytest.mark.skipif(_hipcc() is None, reason="hipcc not available")
+@pytest.mark.parametrize("source", sorted(f for f in os.listdir(CSRC) if f.startswith("k_") and f.endswith(".hip")))
+def test_no_kernel_keeps_registers_in_scratch_memory(source):
+    """What the compiler reports of every kernel: bytes of scratch memory per lane, and vector registers spilled to it."""
+    text = _assembly(source)
+    kernels = re.findall(r"\.private_segment_fixed_size: (\d+)(?:(?!\.symbol).)*\.symbol: +(\S+)\.kd(?:(?!\.private_segment).)*"
+                         r"\.vgpr_spill_count: (\d+)", text, re.S)
+    assert len(kernels) == len(re.findall(r"^\s*\.amdhsa_kernel ", text, re.M)) > 0
+    held = [(name, scratch, spilled) for scratch, name, spilled in kernels
+            if (scratch, spilled) != ("0", "0") and not re.search(SCRATCH_BY_DESIGN, name)]
+    assert not held, held
+
+
 def test_every_source_with_assembly_products_is_checked():
-    csrc = os.path.join(ROOT, "paper_2512_16093_amd", "csrc")
-    assert {f for f in os.listdir(csrc) if 'asm volatile("v_mfma' in open(os.path.join(csrc, f)).read()} == set(EXPECTED)
+    assert {f for f in os.listdir(CSRC) if 'asm volatile("v_mfma' in open(os.path.join(CSRC, f)).read()} == set(EXPECTED)
 
 
 def test_the_check_sees_what_it_is_for():
