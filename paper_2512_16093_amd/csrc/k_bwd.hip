@@ -452,16 +452,28 @@ __global__ void __launch_bounds__(NW * 64, 2) fwd_bf16_kernel(const bf16_t* __re
           __builtin_amdgcn_sched_barrier(0);
         }
       }
+      if (__builtin_expect(key0 + 32 * KT > dm.N, 0)) {   // (uniform) only the sequence's last key block can hold keys that do not exist
 #pragma unroll
-      for (int kt = 0; kt < KT; ++kt) {
-        if (key0 + 32 * kt + 32 > dm.N) {      // (uniform) only the sequence's last key block can hold keys that do not exist
+        for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
           for (int r = 0; r < 16; ++r)
             if (key0 + 32 * kt + 8 * (r >> 2) + 4 * hf + (r & 3) >= dm.N) s[kt][r] = -INFINITY;
+        // Their rows came as row N - 1.  Their weight is zero, but zero times an infinite V is not: V's are cleared.
+        int th = t;
+        asm volatile("" : "+v"(th));           // (nothing of this is worth a register outside of it)
+        if (key0 + (th >> 2) >= dm.N) {        // four threads to a row
+          uint4* row = (uint4*)(ring + half * STEP_B + KT * SWZ_TILE_B + th * 64);
+#pragma unroll
+          for (int u = 0; u < 4; ++u) row[u] = uint4{0u, 0u, 0u, 0u};
         }
+        copies_barrier<63>();                  // (the copies in flight stay in flight)
+#pragma unroll
+        for (int ct = 0; ct < 4; ++ct) tv[0][ct] = t_op_swz(ring + KT * SWZ_TILE_B, to, ct, 0);
+      }
+#pragma unroll
+      for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
         for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[kt][r]);
-      }
       // The reference m moves only when the tiles' maximum exceeds it by more than 2^8: P then stays below 2^8 (harmless
       // in bf16 and fp32) and the accumulators are rescaled a few times per row instead of every step.
       if (__any(mx * c2 > m + 8.0f)) {

@@ -328,6 +328,23 @@ def test_sixteen_bit_forward_at_the_edges_of_its_key_tiles(N, bq, quant):
         assert np.linalg.norm(got - ref) / np.linalg.norm(ref) <= 5e-3
 
 
+@pytest.mark.parametrize("bq", [64, 128])
+@pytest.mark.parametrize("N", [20, 33, 63, 97, 130, 161])
+def test_sixteen_bit_forward_keeps_an_infinite_value_of_the_last_token(N, bq):
+    """Keys beyond the sequence take the last token's place in its tile with a weight of zero, and zero times infinity is
+    not a number: infinite entries of the last value row come out infinite (every key critical, so every query holds
+    them), and the other channels keep their bits."""
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    q, k, v = (torch.randn((1, 2, N, 128), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3))
+    inf = v.clone()
+    inf[:, :, N - 1, 5], inf[:, :, N - 1, 66] = float("inf"), float("-inf")
+    for mode in (sla.QUANT_NONE, sla.QUANT_QK_INT8):
+        out, ref = (sla.sla_attention_fwd(q, k, x, bq, 64, 1.0, 0.0, quant_mode=mode) for x in (inf, v))
+        assert torch.isposinf(out[..., 5]).all() and torch.isneginf(out[..., 66]).all()
+        rest = [c for c in range(128) if c not in (5, 66)]
+        assert torch.equal(out[..., rest], ref[..., rest]) and torch.isfinite(ref).all()
+
+
 @pytest.mark.parametrize("mode", ["none", "qk_int8"])
 def test_sixteen_bit_forward_takes_token_major_layouts(mode):
     """The strided entry point with SLA_QUANT_NONE / SLA_QUANT_QK_INT8 on [B,N,H,d] memory and on one packed
