@@ -14,6 +14,7 @@ import pytest
 import torch
 
 from oracle import sla_bwd_oracle as bo
+from oracle import sla_oracle as so
 from paper_2512_16093_amd import binding as sla
 from paper_2512_16093_amd import synth
 
@@ -82,10 +83,61 @@ def test_backward_matches_gradient_oracle(H, grid, bq, rc, rm, proj):
 @pytest.mark.parametrize("N", [95, 97, 127, 161, 351])
 def test_linear_branch_at_the_edges_of_its_token_tiles(N):
     """Query blocks of 64 in the linear branch: a wavefront pair owns 32 tokens, each half of the channels.  The last
-    block holds a tile less one token, a tile and one, all but one; same bounds as above.  (Not 65: the gradient of a
-    lone key in its block is what is left of sums that cancel, dS of all queries being bf16; with one key among 65 it is
-    8 % of the largest entry off, in every form the kernels have had, the linear branch taking no part in it.)"""
+    block holds a tile less one token, a tile and one, all but one; same bounds as above.  (One token: next test.)"""
     test_backward_matches_gradient_oracle(2, (1, 1, N), 64, 0.5, 0.5, True)
+
+
+def _lone_key_bound(Q, K, V, dO, W, mask):
+    """How far the roundings of the linear branch's bf16 operands move dK of the sequence's last key, if it is alone in its
+    block: an array over the channels.
+
+    d phi(K)[c] = sum_o G[c][o] V[o] + dZ[c].  Where that key is all a query block holds as marginal, O^l is its V whatever
+    Q is, so the two terms cancel exactly, however large they are; what the roundings leave of them is the result.  Between
+    the inputs and G V stand seven (phi(K), h, H, phi(Q), dnum, dH, G), independent from output channel to output channel, to
+    dZ five (z, Z, phi(Q), dZ of a block, their sum).  A rounding is off by up to 2^-9, evenly spread: four standard
+    deviations of the sum, then through the softmax, dK = phi o (d phi - phi . d phi)."""
+    j = mask.shape[1] - 1
+    qs, PQ, PK = so.block_slices(len(Q), 64), so.feature_map(Q, "softmax"), so.feature_map(K, "softmax")
+    h, z = so.linear_summaries(K, V, 64, "softmax")
+    G, dZ = np.zeros((128, 128)), np.zeros(128)
+    for i in np.flatnonzero(mask[:, j] == 0):
+        marg, a = np.flatnonzero(mask[i] == 0), PQ[qs[i]]
+        den, dOl = a @ z[marg].sum(0), dO[qs[i]] @ W
+        G += a.T @ (dOl / den[:, None])
+        dZ -= a.T @ ((dOl * (a @ h[marg].sum(0))).sum(1) / den ** 2)
+    sigma = 2.0 ** -9 / 3 ** 0.5 * np.sqrt(7 * ((G * V[-1]) ** 2).sum(1) + 5 * dZ ** 2)
+    return 4 * PK[-1] * (sigma + np.sqrt(((PK[-1] * sigma) ** 2).sum()))
+
+
+@pytest.mark.parametrize("N", [65, 129])
+def test_gradient_of_a_key_alone_in_its_block(N):
+    """The last block holds one token.  Every gradient but the lone key's dK is held to the bounds above.  That one may be
+    what is left of sums that cancel (1000 and 2000 here, where the largest entry of dK is 1.5 and 1.2): 8 % and 18 % of the
+    largest entry off with the bf16 summaries that the branch keeps, which the bound of `_lone_key_bound` allows for."""
+    cfg = synth.custom_config(1, 2, (1, 1, N), block_q=64, topk_ratio=0.5, marginal_ratio=0.5, use_proj=True, cfg_id=300)
+    q, k, v = synth.make_qkv(cfg)
+    dout, W = synth.make_qkv(cfg, seed=7)[2], synth.make_proj(cfg)
+    dev = [t.cuda() for t in (q, k, v, dout)]
+    mask = sla.sla_classify_blocks(dev[0], dev[1], 64, 64, 0.5, 0.5, want_scores=False)[0].cpu().numpy()
+    dq, dk, dv, dw, db = sla.sla_attention_bwd(*dev, 64, 64, 0.5, 0.5, proj_w=W.cuda(), want_dw=True, want_db=True)
+    sums_w, sums_b, lone = 0.0, 0.0, 0
+    for h in range(2):
+        x, Wf = [synth.as_f64(t[0, h]) for t in (q, k, v, dout)], synth.as_f64(W)
+        r = bo.sla_backward_head(*x, mask[0, h], 64, 64, proj_w=Wf, has_bias=True)
+        gk = dk[0, h].float().cpu().numpy().astype(np.float64)
+        _compare("dq", dq[0, h].float().cpu().numpy(), r["dQ"])
+        _compare("dk", gk[:-1], r["dK"][:-1])
+        _compare("dv", dv[0, h].float().cpu().numpy(), r["dV"])
+        bound = _lone_key_bound(*x, Wf, mask[0, h])
+        lone += int((mask[0, h, :, -1] == 0).any())
+        err, scale = np.abs(gk[-1] - r["dK"][-1]), np.abs(r["dK"]).max()
+        print("N %d head %d: lone key's dK off by %.3f of the largest entry, %.2f of its bound" % (
+            N, h, err.max() / scale, (err / (bound + REL_MAX * scale)).max()), flush=True)
+        assert (err <= bound + REL_MAX * scale).all()
+        sums_w, sums_b = sums_w + r["dW"], sums_b + r["db"]
+    assert lone                                        # (a head in which the lone key is marginal)
+    _compare("dproj_w", dw.cpu().numpy(), sums_w)
+    _compare("dproj_b", db.cpu().numpy(), sums_b)
 
 
 @pytest.mark.parametrize("phi", ["elu1", "relu"])
