@@ -106,7 +106,7 @@ class _Ins:
     def __init__(self, text, in_asm):
         self.text, self.op = text, text.split()[0]
         operands = [o.strip() for o in re.split(r",(?![^\[]*\])", text[len(self.op):])]
-        self.operands, self.asm_product = operands, in_asm and self.op.startswith("v_mfma")
+        self.operands, self.in_asm, self.asm_product = operands, in_asm, in_asm and self.op.startswith("v_mfma")
         self.product = self.op.startswith("v_mfma")
         self.all = _files(" ".join(operands))
         self.first, self.rest = _files(operands[0]), _files(" ".join(operands[1:]))
@@ -216,6 +216,78 @@ def test_products_have_landed_before_anything_touches_them(source):
         mine = [n for k, n in counts.items() if re.search(pattern, k)]
         assert mine == [products] * instances, (pattern, mine)
     assert len(counts) == sum(n for n, _ in EXPECTED[source].values()), sorted(counts)
+
+
+# ---- assembly that switches lanes off and, behind its copies, all of them on: it may stand only where all of them are on
+def _scalars(operand):
+    m = re.match(r"s\[(\d+):(\d+)\]$", operand) or re.match(r"s(\d+)$", operand)
+    return range(int(m.group(1)), int(m.group(m.lastindex)) + 1) if m else range(106, 108) if operand == "vcc" else range(0)
+
+
+def _narrowed(ins, labels):
+    """(assembly writes of exec from a register, those of them that some path reaches with a lane switched off).  Known along
+    every path: are all lanes on, and which scalar registers hold a mask of all of them (halves of pairs; `lane` names a
+    vector register's lane, where the compiler parks scalar registers)."""
+    state, todo, writes, found = {0: (True, frozenset())}, [0], set(), set()
+    while todo:
+        x = todo.pop()
+        full, masks = state[x]
+        i = ins[x]
+        op, o = i.op, i.operands
+        holds = lambda name: full if name == "exec" else name == "-1" or (len(_scalars(name)) == 2 and masks.issuperset(_scalars(name)))
+        if i.in_asm and o[0] == "exec" and o[1] != "-1":
+            writes.add(x)
+            if not full:
+                found.add(x)
+        after, parked = full, masks
+        if op in ("s_and_saveexec_b64", "s_andn2_saveexec_b64", "s_or_saveexec_b64"):
+            after = op.startswith("s_or") and (full or holds(o[1]))
+            parked = masks - set(_scalars(o[0])) | (set(_scalars(o[0])) if full else set())
+        elif o[0] == "exec":
+            after = {"s_mov_b64": holds(o[1]), "s_or_b64": any(holds(y) for y in o[1:])}.get(op, False)
+        elif op == "s_mov_b64":
+            parked = masks - set(_scalars(o[0])) | (set(_scalars(o[0])) if holds(o[1]) else set())
+        elif op in ("v_writelane_b32", "v_readlane_b32"):
+            lane = lambda v, l: ("lane", v, l)
+            gone, source = ({lane(o[0], o[2])}, set(_scalars(o[1]))) if op[2] == "w" else (set(_scalars(o[0])), {lane(o[1], o[2])})
+            parked = masks - gone | (gone if source and masks >= source else set())
+        elif not op.startswith(("s_cbranch", "s_branch", "s_cmp", "s_bitcmp", "s_waitcnt", "s_nop", "s_barrier", "global_load", "ds_")):
+            parked = masks - set(_scalars(o[0])) - set(_scalars(o[1]) if len(o) > 1 and op.startswith("v_") else ())
+        for y in _next(ins, labels, x):
+            old = state.get(y)
+            new = (after, parked) if old is None else (after and old[0], parked & old[1])
+            if new != old:
+                state[y] = new
+                todo.append(y)
+    return len(writes), [ins[x].text for x in sorted(found)]
+
+
+@pytest.mark.skipif(_hipcc() is None, reason="hipcc not available")
+def test_copies_of_some_lanes_stand_where_all_lanes_are_on():
+    writes = {}
+    for name, (ins, labels) in _kernels(_assembly("k_bwd.hip")).items():
+        n, found = _narrowed(ins, labels)
+        assert not found, (name, found[:4])
+        if n:
+            writes[re.match(r"_ZN3sla\d+(\w+?)I", name).group(1)] = writes.get(re.match(r"_ZN3sla\d+(\w+?)I", name).group(1), 0) + 1
+    assert writes == {"bwd_dq_kernel": 8, "bwd_dkv_kernel": 6}, writes
+
+
+def test_the_check_of_lanes_sees_what_it_is_for():
+    copies = "\t;;#ASMSTART\n\ts_mov_b64 exec, s[4:5]\n\ts_mov_b64 exec, -1\n\t;;#ASMEND\n"
+
+    def found(body):
+        (ins, labels), = _kernels("_Zk:\n" + body + "\ts_endpgm\n").values()
+        n, bad = _narrowed(ins, labels)
+        assert n == 1
+        return len(bad)
+    branch = "\ts_and_saveexec_b64 s[0:1], vcc\n\ts_cbranch_execz .LBB0_1\n%s.LBB0_1:\n\ts_or_b64 exec, exec, s[0:1]\n%s"
+    assert found(copies) == found(branch % ("", copies)) == 0
+    assert found(branch % (copies, "")) == found("\ts_mov_b32 s0, 0\n" + copies.join(("\ts_and_b64 exec, exec, vcc\n", ""))) == 1
+    assert found(branch % ("\ts_mov_b32 s1, s2\n", copies)) == 1      # (the saved mask is gone)
+    assert found(branch % ("\tv_writelane_b32 v9, s0, 3\n\tv_writelane_b32 v9, s1, 4\n\ts_mov_b64 s[0:1], 0\n"
+                           "\tv_readlane_b32 s0, v9, 3\n\tv_readlane_b32 s1, v9, 4\n", copies)) == 0
+    assert found(".LBB0_1:\n" + copies + "\ts_andn2_b64 exec, exec, s[6:7]\n\ts_cbranch_execnz .LBB0_1\n") == 1
 
 
 # The selection of rows beyond 6144 key blocks indexes an array that does not fit the registers.

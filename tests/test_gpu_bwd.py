@@ -429,10 +429,11 @@ def test_backward_of_many_short_sequences(grid, bq, H):
 def test_backward_at_token_strides_the_offsets_just_reach_and_no_longer_reach(token_bytes):
     """q, k, v and dout as columns of one buffer whose rows lie 64 MiB apart: the largest stride at which a lane's offset
     into a tile fits 32 bits, and the next one, which takes addresses per lane.  The contiguous call's bits, for one and
-    two query tiles per wavefront (the second: 512 heads, 97 tokens in two key blocks)."""
+    two query tiles per wavefront (the second: 512 heads, 97 tokens in two key blocks); so for the 16-bit forward pass,
+    in steps of one key tile and of two, on the values and on INT8 codes of Q and K (V alone is the caller's there)."""
     N, token = 97, token_bytes // 2
     buf = torch.empty(N * token, dtype=torch.bfloat16, device="cuda")      # (6 GB, of which 97 rows of 0.5 MB are used)
-    for H, bq in ((2, 64), (512, 128), (512, 64)):
+    for H, bq in ((2, 64), (2, 128), (512, 128), (512, 64)):
         cfg = synth.custom_config(1, H, (1, 1, N), block_q=bq, topk_ratio=0.5, marginal_ratio=0.5, use_proj=False, cfg_id=313)
         dev = [t.cuda() for t in (*synth.make_qkv(cfg), synth.make_qkv(cfg, seed=7)[2])]
         far = []
@@ -445,3 +446,9 @@ def test_backward_at_token_strides_the_offsets_just_reach_and_no_longer_reach(to
         sla.sla_attention_bwd_strided(*far, *grads, bq, 64, 0.5, 0.5)
         for name, a, b in zip(("dQ", "dK", "dV"), grads, want):
             assert torch.equal(a, b), (name, H, bq)
+        for mode in (sla.QUANT_NONE, sla.QUANT_QK_INT8):
+            want = sla.sla_attention_fwd(*dev[:3], bq, 64, 0.5, 0.5, quant_mode=mode)
+            out = torch.full_like(want, 7.0)
+            sla.sla_attention_fwd_strided(*far[:3], out, bq, 64, 0.5, 0.5, quant_mode=mode,
+                                          workspace=sla.alloc_workspace(1, H, N, 128, bq, 64, 0.5, 0.5, quant_mode=mode))
+            assert torch.equal(out, want), (mode, H, bq)

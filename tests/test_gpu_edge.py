@@ -100,11 +100,12 @@ def test_degenerate_inputs_low_bit_forward(name, bq):
         assert (mask[..., :n_c] == 1).all() and (mask[..., n_c:n_c + n_m] == 0).all() and (mask[..., n_c + n_m:] == -1).all()
 
 
+@pytest.mark.parametrize("bq", [128, 64])
 @pytest.mark.parametrize("name", sorted(CASES))
-def test_degenerate_inputs_unquantised_forward_and_backward(name):
-    """The same inputs through the 16-bit forward pass and the backward pass (bf16 products, fp32 statistics)."""
+def test_degenerate_inputs_unquantised_forward_and_backward(name, bq):
+    """The same inputs through the 16-bit forward pass (steps of two key tiles and of one) and the backward pass (bf16
+    products, fp32 statistics)."""
     from oracle import sla_bwd_oracle as bo
-    bq = 128
     cfg = synth.custom_config(1, 1, (5, 10, 20), block_q=bq, topk_ratio=0.25, marginal_ratio=0.5, cfg_id=701)
     q, k, v = CASES[name](*synth.make_qkv(cfg))
     W = synth.make_proj(cfg)
