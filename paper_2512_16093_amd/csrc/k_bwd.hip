@@ -152,16 +152,18 @@ struct TileCopy {
   __device__ __forceinline__ unsigned dst(unsigned lds_tile) const { return __builtin_amdgcn_readfirstlane(lds_tile + w * PPW * 1024); }
   // Are rows row0 .. row0 + rows - 1 whole, and their copies of the plain kind?  (uniform)
   __device__ __forceinline__ bool plain(int row0, int rows, int N) const { return row0 + rows <= N && odd == 0; }
-  // rows row0 .. row0 + 31; rows beyond N come as row N - 1 (their weight is zero)
+  // rows row0 .. row0 + 31; rows beyond N come as row N - 1 (their weight is zero) or, if asked for, as zeros
+  template <bool ZEROS = false>
   __device__ __forceinline__ void tile(int row0, int N, unsigned lds_tile) const {
     if (__builtin_expect(plain(row0, 32, N), 1)) {
       const char* b = slice + row0 * snb;
 #pragma unroll
       for (int i = 0; i < PPW; ++i) copy_piece(i < 4 ? b : b + 16 * snb, off[i & 3], dst(lds_tile) + i * 1024);
     } else {
-      tile_any(row0, N, lds_tile);
+      tile_any<ZEROS>(row0, N, lds_tile);
     }
   }
+  template <bool ZEROS = false>
   __device__ __forceinline__ void tile_any(int row0, int N, unsigned lds_tile) const {
     int ln = lane;
     asm volatile("" : "+v"(ln));            // (nothing of this path is worth a register outside of it)
@@ -169,7 +171,9 @@ struct TileCopy {
     for (int i = 0; i < PPW; ++i) {
       const int r = 4 * (PPW * w + i) + (ln >> 4);
       const char* src = slice + min(row0 + r, N - 1) * snb + (((ln & 15) ^ swz(r)) << 4);
-      if ((odd & 15u) == 0) {
+      if (ZEROS && row0 + r >= N) {         // (fewer copies may be under way then than the caller counts: it waits for all of them)
+        *(__attribute__((address_space(3))) v4i*)(uintptr_t)(dst(lds_tile) + i * 1024 + ln * 16) = v4i{};
+      } else if ((odd & 15u) == 0) {
         copy_piece(src, dst(lds_tile) + i * 1024);
       } else {
         // A contiguous tensor may start at any element.  The asynchronous copies take whole 16-byte units only, an
@@ -425,7 +429,7 @@ __global__ void __launch_bounds__(NW * 64, 2) fwd_bf16_kernel(const bf16_t* __re
 #pragma unroll
       for (int kt = 0; kt < KT; ++kt) {
         ck.tile(key0 + 32 * kt, dm.N, lds0 + half * STEP_B + kt * SWZ_TILE_B);
-        cv.tile(key0 + 32 * kt, dm.N, lds0 + half * STEP_B + (KT + kt) * SWZ_TILE_B);
+        cv.template tile<true>(key0 + 32 * kt, dm.N, lds0 + half * STEP_B + (KT + kt) * SWZ_TILE_B);   // (zero times an infinite V would not be zero)
       }
     };
     // KT tiles of 32 keys from key0 on, in half `half` of the ring; next: the step behind this one starts there (< 0: none)
@@ -452,28 +456,16 @@ __global__ void __launch_bounds__(NW * 64, 2) fwd_bf16_kernel(const bf16_t* __re
           __builtin_amdgcn_sched_barrier(0);
         }
       }
-      if (__builtin_expect(key0 + 32 * KT > dm.N, 0)) {   // (uniform) only the sequence's last key block can hold keys that do not exist
 #pragma unroll
-        for (int kt = 0; kt < KT; ++kt)
+      for (int kt = 0; kt < KT; ++kt) {
+        if (key0 + 32 * kt + 32 > dm.N) {      // (uniform) only the sequence's last key block can hold keys that do not exist
 #pragma unroll
           for (int r = 0; r < 16; ++r)
             if (key0 + 32 * kt + 8 * (r >> 2) + 4 * hf + (r & 3) >= dm.N) s[kt][r] = -INFINITY;
-        // Their rows came as row N - 1.  Their weight is zero, but zero times an infinite V is not: V's are cleared.
-        int th = t;
-        asm volatile("" : "+v"(th));           // (nothing of this is worth a register outside of it)
-        if (key0 + (th >> 2) >= dm.N) {        // four threads to a row
-          uint4* row = (uint4*)(ring + half * STEP_B + KT * SWZ_TILE_B + th * 64);
-#pragma unroll
-          for (int u = 0; u < 4; ++u) row[u] = uint4{0u, 0u, 0u, 0u};
         }
-        copies_barrier<63>();                  // (the copies in flight stay in flight)
-#pragma unroll
-        for (int ct = 0; ct < 4; ++ct) tv[0][ct] = t_op_swz(ring + KT * SWZ_TILE_B, to, ct, 0);
-      }
-#pragma unroll
-      for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
         for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[kt][r]);
+      }
       // The reference m moves only when the tiles' maximum exceeds it by more than 2^8: P then stays below 2^8 (harmless
       // in bf16 and fp32) and the accumulators are rescaled a few times per row instead of every step.
       if (__any(mx * c2 > m + 8.0f)) {
@@ -512,6 +504,9 @@ __global__ void __launch_bounds__(NW * 64, 2) fwd_bf16_kernel(const bf16_t* __re
     auto scale_of = [&](int j) __attribute__((always_inline)) { return CODES ? qscale * fe.code_dk[(size_t)bh * dm.Tk + j] : QK_LOG2; };
     int j = crow[0];
     request(64 * j, 0);
+    // Where the loop lies within the 64-byte lines of the instruction cache is worth up to 2 % (12 x 32760, in steps of 8
+    // bytes: 1081 us here and 24 bytes on, 1086 to 1100 at four of the other six places): it does not depend on the code ahead.
+    if constexpr (KT == 1) asm volatile(".p2align 6\n\t.rept 4\n\ts_nop 0\n\t.endr");
     for (int b = 0; b < dm.n_c; ++b) {
       const int jn = crow[min(b + 1, dm.n_c - 1)], next = b + 1 < dm.n_c ? 64 * jn : -1;
       const float c2 = scale_of(j);
@@ -1258,7 +1253,7 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
     if (t < 2 * ROWS) stat[BUF][t / ROWS][t & (ROWS - 1)] = PS;                                      \
   }
   auto compute = [&](int step, int buf) __attribute__((always_inline)) {
-    if (!((qlist[step >> pair_shift] >> (14 + half)) & 1)) return;  // (wave-uniform; always set when KB == 1)
+    if (!((qlist[step >> pair_shift] >> (14 + half)) & 1)) return;  // (wave-uniform)
     const unsigned char* qt0 = lds + buf * BUF_B;
     const unsigned char* dt0 = qt0 + TILES * TILE_B;
     v16f s[TILES], dp[TILES], p[TILES];
@@ -1564,7 +1559,7 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
   // it, and at KB = 2, where it has none to spare, operand addresses went to scratch memory, whose reloads in the middle of
   // a step waited for the rows just requested: 12 heads x 32760 tokens, three quarters critical, backward pass 26.0 -> 24.2 ms)
   int te = t;
-  asm volatile("" : "+v"(te));
+  if constexpr (KB == 2) asm volatile("" : "+v"(te));
   const int le = te & 63, we = te >> 6, l32e = le & 31, hfe = le >> 5;
   unsigned char* my = lds + we * 32 * OP;
   const int row0 = 64 * (KB * J + (KB == 2 ? we >> 1 : 0)) + 32 * (we & 1);
