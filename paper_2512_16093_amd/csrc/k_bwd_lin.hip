@@ -94,7 +94,7 @@ __device__ __forceinline__ void tile_sums_finish(float (&s)[8], float* red, int 
 // 128 take four with all tiles.  Of 64, two wavefronts left half of the SIMDs idle, with twice the dW and dH tiles each
 // (spilled registers, summaries not requested ahead): there four, a pair per token; what it does not share
 // (softmax, loads of its rows) is done twice, the two token-wise sums and dnum meet in LDS.  The backward pass of 12 x 32760
-// in blocks of 64 4310 -> 4090 us, of 4 x 2187 128 -> 119 us.  (Pairs for blocks of 128 as well, two wavefronts per SIMD: 50
+// in blocks of 64 4290 -> 4040 us, of 4 x 2187 128 -> 119 us.  (Pairs for blocks of 128 as well, two wavefronts per SIMD: 50
 // registers spilled, 3515 -> 3615 us.)
 template <int TT, int CS, int PHI>
 __global__ void __launch_bounds__(TT * CS * 64, 1)
@@ -130,8 +130,8 @@ __global__ void __launch_bounds__(TT * CS * 64, 1)
       *(bf16_t*)(Wl + (x >> 7) * TP + (x & 127) * 2) = proj_w ? proj_w[x] : (bf16_t)((x >> 7) == (x & 127) ? 0x3F80 : 0);
   }
 
-  constexpr int TILES = 16 / NW;               // of dH and dW per wavefront: one row (dW) or column (dH) of them, from tile t0 on
-  const int trow = w & 3, t0 = TILES * (w >> 2);
+  static_assert(NW == 4, "of dH and dW a wavefront forms four tiles: row (dW) or column (dH) w of them");
+  constexpr int TILES = 4;
   v16f dwacc[TILES];
 #pragma unroll
   for (int x = 0; x < TILES; ++x) dwacc[x] = v16f{};
@@ -345,20 +345,20 @@ __global__ void __launch_bounds__(TT * CS * 64, 1)
     asm volatile("" : "+v"(lane_o));
     uint4 aa[BQ / 16];
 #pragma unroll
-    for (int ks = 0; ks < BQ / 16; ++ks) aa[ks] = t_op(Al + 32 * (ks >> 1) * TP, tr_off, trow, ks & 1);
+    for (int ks = 0; ks < BQ / 16; ++ks) aa[ks] = t_op(Al + 32 * (ks >> 1) * TP, tr_off, w, ks & 1);
 #pragma unroll
     for (int x = 0; x < TILES; ++x) {
       v16f acc = v16f{};
       uint4 bb[BQ / 16];
 #pragma unroll
-      for (int ks = 0; ks < BQ / 16; ++ks) bb[ks] = t_op(Dl + 32 * (ks >> 1) * TP, tr_off, t0 + x, ks & 1);
+      for (int ks = 0; ks < BQ / 16; ++ks) bb[ks] = t_op(Dl + 32 * (ks >> 1) * TP, tr_off, x, ks & 1);
 #pragma unroll
       for (int ks = 0; ks < BQ / 16; ++ks) acc = mfma_bf16(aa[ks], bb[ks], acc);
       __builtin_amdgcn_sched_barrier(0);
-      // lane: o = 32 (t0 + x) + l32; registers: c = 32 trow + 8 g + 4 hf + e
+      // lane: o = 32 x + l32; registers: c = 32 w + 8 g + 4 hf + e
 #pragma unroll
       for (int g = 0; g < 4; ++g)
-        *(uint2*)(dst + hz_run_offset(32 * (t0 + x) + lane_o, 32 * trow + 8 * g + 4 * hf)) =
+        *(uint2*)(dst + hz_run_offset(32 * x + lane_o, 32 * w + 8 * g + 4 * hf)) =
             uint2{pack_bf16x2(acc[4 * g], acc[4 * g + 1]), pack_bf16x2(acc[4 * g + 2], acc[4 * g + 3])};
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -386,12 +386,12 @@ __global__ void __launch_bounds__(TT * CS * 64, 1)
       lds_barrier();
       uint4 ag[BQ / 16];         // the row tile of dO^T: the A operand of all its column tiles
 #pragma unroll
-      for (int ks = 0; ks < BQ / 16; ++ks) ag[ks] = t_op(Hl + 32 * (ks >> 1) * TP, tr_off, trow, ks & 1);
+      for (int ks = 0; ks < BQ / 16; ++ks) ag[ks] = t_op(Hl + 32 * (ks >> 1) * TP, tr_off, w, ks & 1);
 #pragma unroll
       for (int x = 0; x < TILES; ++x) {
         uint4 bo[BQ / 16];
 #pragma unroll
-        for (int ks = 0; ks < BQ / 16; ++ks) bo[ks] = t_op(Al + 32 * (ks >> 1) * TP, tr_off, t0 + x, ks & 1);
+        for (int ks = 0; ks < BQ / 16; ++ks) bo[ks] = t_op(Al + 32 * (ks >> 1) * TP, tr_off, x, ks & 1);
 #pragma unroll
         for (int ks = 0; ks < BQ / 16; ++ks) dwacc[x] = mfma_bf16(ag[ks], bo[ks], dwacc[x]);
         __builtin_amdgcn_sched_barrier(0);
@@ -408,7 +408,7 @@ __global__ void __launch_bounds__(TT * CS * 64, 1)
     for (int x = 0; x < TILES; ++x)
 #pragma unroll
       for (int r = 0; r < 16; ++r)
-        mine[(32 * trow + 8 * (r >> 2) + 4 * hf + (r & 3)) * D + 32 * (t0 + x) + l32] = dwacc[x][r];
+        mine[(32 * w + 8 * (r >> 2) + 4 * hf + (r & 3)) * D + 32 * x + l32] = dwacc[x][r];
   }
   if (db_part) {
     tile_sums_finish(dbacc, red, lane, w);
