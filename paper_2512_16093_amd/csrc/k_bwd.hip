@@ -223,7 +223,7 @@ __device__ __forceinline__ void copies_barrier() {
 // A wavefront owns QT tiles of 32 queries; with two an operand read from LDS serves two matrix products (with 32
 // queries each the reads alone asked for all the LDS delivers).  K and V tiles of 32 keys travel in a ring of two each,
 // copied one and a half steps ahead, 32 KB per workgroup, two wavefronts per SIMD; the exponentials are issued between
-// the products of V.  Bound by power: 1.55 GHz with the matrix pipe 61 % busy.  Before (O formed from P in bf16, 32
+// the products of V.  Bound by power: 1.56 to 1.60 GHz with the matrix pipe 60 % busy.  Before (O formed from P in bf16, 32
 // queries per wavefront, copies through registers): 40 heads x 75600 tokens 13.4 -> 12.3 ms, 12 x 32760 with query
 // blocks of 64 1.19 -> 0.92 ms.
 template <int WAVES, int QT, bool ST>
@@ -385,8 +385,10 @@ struct FwdEpilogue {
 // stay on a compute unit; with two tiles there was one wavefront per SIMD, 12 x 32760 tokens 1280 instead of 1095 us a
 // call; four wavefronts with one tile: 936 instead of 910).  Through registers (up to 64 of them) and with 78 KB for
 // either size the call took: query blocks of 128, 12 x 32760 tokens 944 -> 863 us, 40 x 75600 15.1 -> 13.5 ms; of 64 1392 ->
-// 1055 us, 23.0 -> 20.5 ms.  Bound by the exponentials beside the products (12 x 32760: 0.84 of 1.9 PFLOP/s in the
-// kernel), at query blocks of 64 by the stream of K and V, 32 KB for every 64 x 64 scores: 9 TB/s past the LDS.
+// 1055 us, 23.0 -> 20.5 ms.  Bound, as counted at 40 x 75600: query blocks of 128 by power (1.58 GHz, the matrix pipe 65 %
+// busy, 52 GB past L2 in 12.2 ms); of 64 by the stream of K and V, 32 KB for every 64 x 64 scores: 128 GB past L2 in 16.7 ms =
+// 7.6 TB/s, what a plain reader of such tiles gets, with the pipe 44 % busy.  At 12 x 32760 the pipe is 57 and 50 % busy, 2.0
+// and 4.4 GB go past L2 in 0.82 and 0.95 ms: the exponentials beside the products.
 template <int NW, bool CODES, bool ST>
 __global__ void __launch_bounds__(NW * 64, 2) fwd_bf16_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                                                             const bf16_t* __restrict__ v, const int32_t* __restrict__ crit,
@@ -652,7 +654,7 @@ __device__ __forceinline__ void score_wait(v16f& x) { asm volatile("s_nop 15\n\t
 // was 56 % busy), query blocks of 64 (12 x 32760) 1.42 -> 1.00 ms.  A tile's copies go between the products of two sections, a
 // pair at a time (in one burst behind the barrier they held the wavefront up), and dP starts from minus delta (32 of 325
 // instructions of a step less): 16.1 -> 15.2 ms, 1.00 -> 0.93 ms.  With another 10 instructions and two waits of a step
-// taken out it is no faster: bound by power.
+// taken out it is no faster: bound by power (1.75 to 1.80 GHz, the matrix pipe 61 % busy).
 template <int WAVES, int QT, bool ST>
 __global__ void __launch_bounds__(WAVES * 64, 1) bwd_dq_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ dout,
                                                               const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
@@ -1100,6 +1102,8 @@ __global__ void __launch_bounds__(1024) dkv_order_kernel(const int* __restrict__
 // the copies between the products, two to an m0, the barrier ahead of the step's last section, the next step's first
 // operands read behind that section's products and dP started from delta (no subtraction): 2900 cycles at 40 x 75600,
 // 430 instructions instead of 504; whole backward pass 59.6 -> 57.8 ms (same box), 4 x 2187 (training step) 185 -> 180 us.
+// Counted at 40 x 75600: 159 GB fetched past L2 at 6.6 to 6.9 TB/s, where a plain reader gets 6.9 to 7.6, and 1.67 to 1.72 GHz
+// with the matrix pipe 56 % busy: bound by both, the stream and power.
 template <int KB, int TILES, int PHI, bool ST = false>
 __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ dout,
                                                       const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
