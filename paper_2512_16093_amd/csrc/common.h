@@ -160,6 +160,67 @@ __device__ __forceinline__ uint4 pair_order(const uint4& v) {
   return uint4{(uint32_t)a[0], (uint32_t)b[0], (uint32_t)a[1], (uint32_t)b[1]};
 }
 
+// phi(Q) of a token as operands of the linear term O_l = phi(Q) H / (phi(Q) . Z), from its channels as they are: operand ks
+// is those of raw[ks].  The quotient does not change when a token's phi(Q) is scaled, so softmax is left without its sum
+// and its division (a third of the instructions: the attention kernels' epilogues are bound by issuing them).
+__device__ __forceinline__ void phi_q_operands(const uint4 (&raw)[8], int phi, uint4 (&b)[8]) {
+  float x[64];
+#pragma unroll
+  for (int s = 0; s < 8; ++s) unpack8(raw[s], x + 8 * s);
+  if (phi == 0) {
+    float m[4] = {x[0], x[1], x[2], x[3]};
+#pragma unroll
+    for (int e = 4; e < 64; e += 8) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) m[c] = e + 4 + c < 64 ? fmaxf(fmaxf(m[c], x[e + c]), x[e + 4 + c]) : fmaxf(m[c], x[e + c]);
+    }
+    const float mx = fmaxf(fmaxf(m[0], m[1]), fmaxf(m[2], m[3])), off = -LOG2E * fmaxf(mx, partner_f32(mx));
+#pragma unroll
+    for (int e = 0; e < 64; ++e) x[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(x[e], LOG2E, off));
+  } else if (phi == 1) {
+#pragma unroll
+    for (int e = 0; e < 64; ++e) x[e] = x[e] > 0.f ? x[e] + 1.0f : __builtin_amdgcn_exp2f(x[e] * LOG2E);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 64; ++e) x[e] = fmaxf(x[e], 0.f);
+  }
+#pragma unroll
+  for (int s = 0; s < 8; ++s) b[s] = pack8(x + 8 * s);
+}
+
+// A wavefront's 32 tokens x 128 channels (lane = token, registers = channels, the accumulators' order) as bf16 rows: through
+// 8 KiB of LDS that are its own (16-byte aligned), so that whole rows of 256 bytes leave at a time.  A row's 16-byte chunks
+// and their halves are permuted by its number: no two rows that a group of lanes writes meet in a bank.  to: the first
+// token's row (any alignment: a contiguous tensor may start at any element); sn: elements from row to row; rows: that exist.
+__device__ __forceinline__ void pack_rows(const v16f (&x)[4], uint2 (&p)[16]) {
+#pragma unroll
+  for (int ct = 0; ct < 4; ++ct)
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      p[4 * ct + g] = uint2{pack_bf16x2(x[ct][4 * g], x[ct][4 * g + 1]), pack_bf16x2(x[ct][4 * g + 2], x[ct][4 * g + 3])};
+}
+__device__ __forceinline__ void store_rows(unsigned char* my, const uint2 (&p)[16], int lane, bf16_t* to, long long sn, int rows) {
+  const int l32 = lane & 31, hf = lane >> 5, c = lane & 15;
+  __builtin_amdgcn_wave_barrier();     // (a wavefront's LDS operations execute in order: only the compiler has to keep it)
+#pragma unroll
+  for (int e = 0; e < 16; ++e) *(uint2*)(my + l32 * 256 + ((e ^ (l32 & 15)) << 4) + ((hf ^ (l32 >> 4)) << 3)) = p[e];
+  __builtin_amdgcn_wave_barrier();
+  bf16_t* mine = to + (lane >> 4) * sn + 8 * c;
+#pragma unroll
+  for (int it = 0; it < 8; ++it) {
+    const int r = 4 * it + (lane >> 4);
+    const v4i got = *(const v4i*)(my + r * 256 + ((c ^ (r & 15)) << 4));
+    const v4i val = it < 4 ? got : v4i{got[2], got[3], got[0], got[1]};
+    if (r < rows) __builtin_memcpy(mine + 4 * it * sn, &val, 16);
+  }
+  __builtin_amdgcn_wave_barrier();
+}
+__device__ __forceinline__ void store_rows(unsigned char* my, const v16f (&x)[4], int lane, bf16_t* to, long long sn, int rows) {
+  uint2 p[16];
+  pack_rows(x, p);
+  store_rows(my, p, lane, to, sn, rows);
+}
+
 constexpr int TP = 304;             // bytes per staged row: 256 of data + 48 of skew (76 dwords: within a group of 16 lanes neither
                                     // the 16-byte operand reads nor the transposing reads collide)
 constexpr int TILE_B = 32 * TP;     // one 32-token tile

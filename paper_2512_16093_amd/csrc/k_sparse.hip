@@ -25,7 +25,12 @@
 //
 // Epilogue: O_s = acc * delta_V / l;  optional linear term phi(Q) H_i / (phi(Q).Z_i) as bf16 MFMA
 // (H_i already contains the output projection), bias, then a transposing pass through LDS so
-// the global stores are row-contiguous.
+// the global stores are row-contiguous.  Of a short list it is the longer part of a workgroup's life (7 key blocks: 13 000 of
+// 36 000 cycles, 15 000 in the loop), a chain of waits for memory and of instructions: H_i is copied behind the list's last
+// blocks, everything else requested in one go, softmax in phi(Q) left unnormalised, phi(Q).Z formed by the matrix pipe.
+// Whole call: 24 slices of 4617 tokens 148.6 -> 143.3 us, 2 x 1024 30.7 -> 29.5, 12 x 32760 686 -> 677, 40 x 75600 9.42 -> 9.32 ms.
+#include <type_traits>
+
 #include "common.h"
 
 namespace sla {
@@ -66,20 +71,6 @@ constexpr int EPI_STRIDE = 32 * 4 + 16;         // bytes per staged output row (
 constexpr int BIAS_I = 0x3E22F983;
 constexpr int BIAS_FLOOR = 0x3E000000;          // pattern below every reachable score (masked keys)
 constexpr float SCORE_STEP = 1.0f / 67108864.f;  // 2^-26: what one score unit adds to the float
-
-__device__ __forceinline__ void load_q16(const bf16_t* p, bool ok, float* x) {
-  uint4 a = make_uint4(0, 0, 0, 0), b = a;
-  if (ok) {
-    a = ((const uint4*)p)[0];
-    b = ((const uint4*)p)[1];
-  }
-  const uint32_t w[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    x[2 * e] = bf16_lo(w[e]);
-    x[2 * e + 1] = bf16_hi(w[e]);
-  }
-}
 
 // Row state (per lane = per query): `r` is the running reference level, an INTEGER number of
 // binary orders of magnitude (r = max over the 32-key tiles seen so far of ceil(log2(e) * row
@@ -245,7 +236,7 @@ __global__ void __launch_bounds__(NW * 64, 2) sparse_fwd_kernel(
   constexpr int BQ = NW * 32;
   // Rings of four K and four V staging buffers, declared as separate objects so the compiler
   // can tell the asynchronous fill of one from the reads of another; after the main loop
-  // wavefront w reuses K buffer w for the output transposition.
+  // the K slots hold H_i and wavefront w reuses V buffer w for the output transposition.
   __shared__ uint4 kst0[KV_FRAG_BYTES / 16], kst1[KV_FRAG_BYTES / 16], kst2[KV_FRAG_BYTES / 16], kst3[KV_FRAG_BYTES / 16];
   __shared__ uint4 vst0[KV_FRAG_BYTES / 16], vst1[KV_FRAG_BYTES / 16], vst2[KV_FRAG_BYTES / 16], vst3[KV_FRAG_BYTES / 16];
   constexpr int SLOT = KV_FRAG_BYTES / 16;
@@ -321,9 +312,8 @@ __global__ void __launch_bounds__(NW * 64, 2) sparse_fwd_kernel(
   // does not know copies are in flight: it would otherwise make every LDS read it cannot prove
   // disjoint wait for ALL of them.  The pipeline waits for them by explicit counts (loads the
   // compiler does not know about only make its own waits more conservative).
-  auto fetch_rec = [&](const char* base_bh, int j, uint4* dst) {
-    static_assert(KV_FRAG_BYTES == 1 << 13, "record size");
-    const char* rec = base_bh + (unsigned)__builtin_amdgcn_readfirstlane(j << 13);
+  static_assert(KV_FRAG_BYTES == 1 << 13, "record size");
+  auto copy_rec = [&](const char* rec, uint4* dst) {
     const unsigned lds_addr = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(lds_ptr_t)(dst + w_s * PW * 64));
     if constexpr (PW == 2) {
       asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\t"
@@ -343,6 +333,17 @@ __global__ void __launch_bounds__(NW * 64, 2) sparse_fwd_kernel(
                    : "memory", "m0");
     }
   };
+  auto fetch_rec = [&](const char* base_bh, int j, uint4* dst) { copy_rec(base_bh + (unsigned)__builtin_amdgcn_readfirstlane(j << 13), dst); };
+  // K of list entry e; behind the list's end come the four quarters of H_i (one per output tile, as large as a record),
+  // which the epilogue reads from the slots: copied in the last steps, where the copies past the end brought the last
+  // block once more, they cost nothing, and the epilogue has no memory to wait for (it took them from memory tile by tile,
+  // every wavefront for itself).
+  const int k_end = A.has_lin ? n_c : 0x7fffffff;
+  const char* const h_rec = (const char*)(A.HZ + (size_t)rowid * HZ_ELEMS);
+  auto fetch_k = [&](int e, int j, uint4* dst) {
+    copy_rec(e >= k_end ? h_rec + (unsigned)((e - k_end) << 13) : k8_bh + (unsigned)__builtin_amdgcn_readfirstlane(j << 13), dst);
+  };
+  auto fetch_k_in = [&](int, int j, uint4* dst) { fetch_rec(k8_bh, j, dst); };   // (an entry that the list has)
   auto dk_of = [&](int j) { return *(const float*)((const char*)dkrow + (unsigned)__builtin_amdgcn_readfirstlane(j << 2)); };
   const int kvalid_last = A.N - (A.Tk - 1) * BK;  // valid keys of the last key block
   const bool ragged = kvalid_last < BK;
@@ -358,8 +359,8 @@ __global__ void __launch_bounds__(NW * 64, 2) sparse_fwd_kernel(
   //            of block b-1;  vector: s1 -> ... -> codes of keys 32..63 of block b
   // Each phase starts by reading from LDS the fragments the NEXT phase's MFMAs need (V of block
   // b-1, K of block b+1) and by starting the copy of K(b+4) resp. V(b+2) into the ring slot
-  // retired in step b-1 (past the end of the list the last block is copied again, into slots
-  // nothing reads any more: the step stays free of branches).  At its end the wavefront waits
+  // retired in step b-1 (past the end of the list come the quarters of H_i in place of K, and V of the last block
+  // again, into slots nothing reads any more: the step stays free of branches).  At its end the wavefront waits
   // for its own pieces of K(b+2) / V(b) and meets the others at one barrier, which publishes
   // those and retires K slot (b+1)%4 and V slot (b-1)%4.  The L2 / HBM latency of a block is thus
   // covered by the arithmetic of two to three steps.  A ragged last key block can only be the
@@ -401,13 +402,13 @@ __global__ void __launch_bounds__(NW * 64, 2) sparse_fwd_kernel(
     offs_ = bc_.lnb - r;                                                                              \
     moved = 1;                                                                                        \
   }
-#define SLA_STEP(B, KNEXT, VPREV, KFILL, VFILL, PBP, PBN)                                           \
+#define SLA_STEP(B, FETCH_K, KNEXT, VPREV, KFILL, VFILL, PBP, PBN)                                  \
   {                                                                                                   \
     const int b_ = (B);                                                                               \
     /* ---- phase 1 */                                                                                \
     read4(VPREV, lane, 0, vfa);                                                                       \
     read4(KNEXT, lane, 0, kfA);                                                                       \
-    if constexpr (SMALL) fetch_rec(v8_bh, j0, VFILL); else fetch_rec(k8_bh, j4, KFILL);               \
+    if constexpr (SMALL) fetch_rec(v8_bh, j0, VFILL); else FETCH_K(b_ + 4, j4, KFILL);                \
     const int jn_ = crow[min(b_ + (SMALL ? 4 : 5), last)];                                            \
     const float dn_ = dk_of(SMALL ? j3 : j4);                                                         \
     const BlockConsts bc_ = block_consts(cq * d0);                                                    \
@@ -432,7 +433,7 @@ __global__ void __launch_bounds__(NW * 64, 2) sparse_fwd_kernel(
     /* ---- phase 2 */                                                                                \
     read4(VPREV, lane, 4, vfb);                                                                       \
     read4(KNEXT, lane, 4, kfB);                                                                       \
-    if constexpr (SMALL) fetch_rec(k8_bh, j3, KFILL); else fetch_rec(v8_bh, j2, VFILL);               \
+    if constexpr (SMALL) FETCH_K(b_ + 3, j3, KFILL); else fetch_rec(v8_bh, j2, VFILL);                \
     SB s0 = qk_step(kfA[0], q8[0], bias16);                                                           \
     SB const int mB_ = half_max<false>(s1, 32, hf, 0);                                                \
     SB s0 = qk_step(kfA[1], q8[1], s0);                                                               \
@@ -458,6 +459,25 @@ __global__ void __launch_bounds__(NW * 64, 2) sparse_fwd_kernel(
     __builtin_amdgcn_s_waitcnt(WAIT_KEEP2);                                                           \
     stage_barrier();                                                                                  \
   }
+  auto k_slot = [&](int e) -> uint4* { const int x = e & 3; return x == 0 ? kst0 : x == 1 ? kst1 : x == 2 ? kst2 : kst3; };
+  // What the epilogue needs of memory beside H_i, requested in one go behind the loop (one by one, each where it was used,
+  // these loads were the longest part of a short list's workgroup): the wavefront's Q rows for phi(Q), two channels of
+  // delta_V, Z_i and the bias per lane.
+  uint4 qraw[8];
+  float2 dv2 = make_float2(0.f, 0.f);
+  uint32_t z2 = 0, b2 = 0;
+  auto request_epilogue = [&]() __attribute__((always_inline)) {
+    dv2 = *(const float2*)(A.dv + (size_t)bh * D + 2 * lane);
+    if (!SHARED && A.has_lin) {
+      const bf16_t* Hi = A.HZ + (size_t)rowid * HZ_ELEMS;
+      z2 = *(const uint32_t*)(Hi + D * D + 2 * lane);
+#pragma unroll
+      for (int s = 0; s < 8; ++s)   // (rows beyond N come as row 0 of the slice; what they give is not stored)
+        qraw[s] = *(const uint4*)(qptr + 32 * (s >> 1) + 16 * hf + 8 * (s & 1));
+      if (A.bias) b2 = (uint32_t)A.bias[2 * lane] | (uint32_t)A.bias[2 * lane + 1] << 16;
+    }
+    asm volatile("" ::: "memory");   // (requested here, not where they are used)
+  };
   int moved = 1;              // did the reference level of any query of this wavefront rise in the last step?
 
   if (n_c > 0) {  // (an empty list leaves only the linear term of the epilogue)
@@ -470,15 +490,15 @@ __global__ void __launch_bounds__(NW * 64, 2) sparse_fwd_kernel(
     float d0 = dk_of(j0), d1 = dk_of(j1), d2 = dk_of(j2), d3 = dk_of(j3);
     // three groups of copies, in the order the steps will wait for them
     if constexpr (SMALL) {
-      fetch_rec(k8_bh, j0, ring);
-      fetch_rec(k8_bh, j1, ring + SLOT);
-      fetch_rec(k8_bh, j2, ring + 2 * SLOT);
+      fetch_k(0, j0, ring);
+      fetch_k(1, j1, ring + SLOT);
+      fetch_k(2, j2, ring + 2 * SLOT);
     } else {
-      fetch_rec(k8_bh, j0, kst0);
-      fetch_rec(k8_bh, j1, kst1);
-      fetch_rec(k8_bh, j2, kst2);
+      fetch_k(0, j0, kst0);
+      fetch_k(1, j1, kst1);
+      fetch_k(2, j2, kst2);
       fetch_rec(v8_bh, j0, vst0);
-      fetch_rec(k8_bh, j3, kst3);
+      fetch_k(3, j3, kst3);
       fetch_rec(v8_bh, j1, vst1);
     }
     __builtin_amdgcn_s_waitcnt(WAIT_KEEP2);  // K(0), K(1) have landed
@@ -500,42 +520,57 @@ __global__ void __launch_bounds__(NW * 64, 2) sparse_fwd_kernel(
       uint4 *const v0 = ring + 3 * SLOT, *const v1 = ring + 4 * SLOT;
 #define SLA_TURN { const int t_ = kn; kn = k2; k2 = kf; kf = t_; }
       for (; b + 2 <= nb_main; b += 2) {
-        SLA_STEP(b, ring + kn, v1, ring + kf, v0, pb_b, pb_a)
+        SLA_STEP(b, fetch_k, ring + kn, v1, ring + kf, v0, pb_b, pb_a)
         SLA_TURN
-        SLA_STEP(b + 1, ring + kn, v0, ring + kf, v1, pb_a, pb_b)
+        SLA_STEP(b + 1, fetch_k, ring + kn, v0, ring + kf, v1, pb_a, pb_b)
         SLA_TURN
       }
       if (b < nb_main) {
-        SLA_STEP(b, ring + kn, v1, ring + kf, v0, pb_b, pb_a)
+        SLA_STEP(b, fetch_k, ring + kn, v1, ring + kf, v0, pb_b, pb_a)
         pb_b = pb_a;
       }
 #undef SLA_TURN
-      if (has_tail) fetch_rec(v8_bh, j0, (last & 1) ? v1 : v0);   // (the main loop's steps copy their own block's V)
+      if (has_tail) {
+        fetch_rec(v8_bh, j0, (last & 1) ? v1 : v0);               // (the main loop's steps copy their own block's V)
+        if (A.has_lin) fetch_k(n_c + 2, 0, ring + last % 3 * SLOT);   // (and bring the first two quarters only)
+      }
     } else {
+      // (up to plain_end a step's K copy is of a block that the list has or, without a linear branch, of whatever: with the
+      // choice in every step 12 x 32760 tokens, every block critical, took 0.5 % longer; query blocks of 64 do not care)
+      const int plain_end = A.has_lin ? n_c - 4 : nb_main;
+      for (; b + 4 <= plain_end; b += 4) {
+        SLA_STEP(b, fetch_k_in, kst1, vst3, kst0, vst2, pb_b, pb_a)
+        SLA_STEP(b + 1, fetch_k_in, kst2, vst0, kst1, vst3, pb_a, pb_b)
+        SLA_STEP(b + 2, fetch_k_in, kst3, vst1, kst2, vst0, pb_b, pb_a)
+        SLA_STEP(b + 3, fetch_k_in, kst0, vst2, kst3, vst1, pb_a, pb_b)
+      }
       for (; b + 4 <= nb_main; b += 4) {
-        SLA_STEP(b, kst1, vst3, kst0, vst2, pb_b, pb_a)
-        SLA_STEP(b + 1, kst2, vst0, kst1, vst3, pb_a, pb_b)
-        SLA_STEP(b + 2, kst3, vst1, kst2, vst0, pb_b, pb_a)
-        SLA_STEP(b + 3, kst0, vst2, kst3, vst1, pb_a, pb_b)
+        SLA_STEP(b, fetch_k, kst1, vst3, kst0, vst2, pb_b, pb_a)
+        SLA_STEP(b + 1, fetch_k, kst2, vst0, kst1, vst3, pb_a, pb_b)
+        SLA_STEP(b + 2, fetch_k, kst3, vst1, kst2, vst0, pb_b, pb_a)
+        SLA_STEP(b + 3, fetch_k, kst0, vst2, kst3, vst1, pb_a, pb_b)
       }
       // the (up to three) remaining steps keep the a/b alternation by copying the codes back
       if (b < nb_main) {
-        SLA_STEP(b, kst1, vst3, kst0, vst2, pb_b, pb_a)
+        SLA_STEP(b, fetch_k, kst1, vst3, kst0, vst2, pb_b, pb_a)
         pb_b = pb_a;
       }
       if (b + 1 < nb_main) {
-        SLA_STEP(b + 1, kst2, vst0, kst1, vst3, pb_b, pb_a)
+        SLA_STEP(b + 1, fetch_k, kst2, vst0, kst1, vst3, pb_b, pb_a)
         pb_b = pb_a;
       }
       if (b + 2 < nb_main) {
-        SLA_STEP(b + 2, kst3, vst1, kst2, vst0, pb_b, pb_a)
+        SLA_STEP(b + 2, fetch_k, kst3, vst1, kst2, vst0, pb_b, pb_a)
         pb_b = pb_a;
       }
     }
-    // drain: wait for every copy (the repeated ones too) and publish; from here on plain reads
-    __builtin_amdgcn_s_waitcnt(WAIT_ALL);
-    stage_barrier();
+    if constexpr (!SMALL) {
+      if (has_tail && A.has_lin) fetch_k(n_c + 3, 0, k_slot(n_c + 3));   // (the place of the last K block, which is consumed)
+    }
+    request_epilogue();
     if (has_tail) {  // the ragged last key block: s0 and kfB are ready, P.V of the block before it is due
+      __builtin_amdgcn_s_waitcnt(WAIT_ALL);   // (its V is not waited for yet)
+      stage_barrier();
       const int sp = (nb_main + 3) & 3;
       const uint4* vp = SMALL ? ring + (3 + (sp & 1)) * SLOT : sp == 0 ? vst0 : sp == 1 ? vst1 : sp == 2 ? vst2 : vst3;
       read4(vp, lane, 0, vfa);
@@ -563,7 +598,7 @@ __global__ void __launch_bounds__(NW * 64, 2) sparse_fwd_kernel(
       if (__any(r - R > 64.f)) renormalise(r, R, Rm127, acc, accl);
       sc_prev = level_scale(hf ? r : rAt, Rm127);
     }
-    {  // P.V of the last block
+    {  // P.V of the last block (it has landed: the last step, or the wait above, has waited for it)
       const int sl = last & 3;
       const uint4* vc = SMALL ? ring + (3 + (sl & 1)) * SLOT : sl == 0 ? vst0 : sl == 1 ? vst1 : sl == 2 ? vst2 : vst3;
       read4(vc, lane, 0, vfa);
@@ -574,99 +609,104 @@ __global__ void __launch_bounds__(NW * 64, 2) sparse_fwd_kernel(
       pv_tile(vfb[2], vfb[3], pb_b, sc_prev, acc[3]);
       pv_rowsum(ones, pb_b, sc_prev, accl);
     }
+  } else {
+    if (A.has_lin) {
+      if constexpr (SMALL) {
+        for (int e = 0; e < 3; ++e) fetch_k(e, 0, ring + e * SLOT);
+      } else {
+        for (int e = 0; e < 4; ++e) fetch_k(e, 0, k_slot(e));
+      }
+    }
+    request_epilogue();
   }
 #undef SLA_STEP
 #undef SLA_RAISE
 #undef SB
+  // Every copy has landed, H_i is published; nobody reads V any more: V slot w is wavefront w's own from here on (its LDS
+  // operations execute in the order it issues them, only the compiler has to be kept from changing it).
+  __builtin_amdgcn_s_waitcnt(WAIT_ALL);
+  stage_barrier();
+  uint4 h3[8];   // query blocks of 64, whose three K slots hold three quarters of H_i: the last one
+  if (SMALL && A.has_lin) {
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) h3[ks] = *(const uint4*)(h_rec + (size_t)hz_frag_chunk(3, ks, lane) * 16);
+  }
+  unsigned char* my = (unsigned char*)(SMALL ? ring + (3 + w) * SLOT : w == 0 ? vst0 : w == 1 ? vst1 : w == 2 ? vst2 : vst3);
+  // delta_V, Z_i and the bias, two channels of each per lane, laid out to be read by every lane
+  *(float2*)(my + 8 * lane) = dv2;
+  *(uint32_t*)(my + 512 + 4 * lane) = z2;
+  *(uint32_t*)(my + 768 + 4 * lane) = b2;
+  *(uint32_t*)(my + 1024 + 4 * lane) = 0u;
+  __builtin_amdgcn_wave_barrier();
 
-  // ---- normalise: O_s[q][ch] = acc * delta_V[ch] / l
+  // ---- normalise: O_s[q][ch] = acc * delta_V[ch] / l (+ the bias, which comes with the linear term only)
   const float ltot = accl[0];  // sum of the rounded P (scaled by 448), at level R
   const float inv_l = ltot > 0.f ? 1.0f / ltot : 0.f;
   if (A.lse && hf == 0 && qok)
     A.lse[(size_t)bh * A.N + qrow] = (R + __builtin_amdgcn_logf(ltot) - LOG2_448) * LN2;
+  auto normalise = [&](auto bias) __attribute__((always_inline)) {
 #pragma unroll
-  for (int ct = 0; ct < 4; ++ct)
+    for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const float4 d4 = *(const float4*)(A.dv + (size_t)bh * D + 32 * ct + 8 * g + 4 * hf);
-      acc[ct][4 * g + 0] *= d4.x * inv_l;
-      acc[ct][4 * g + 1] *= d4.y * inv_l;
-      acc[ct][4 * g + 2] *= d4.z * inv_l;
-      acc[ct][4 * g + 3] *= d4.w * inv_l;
-    }
+      for (int g = 0; g < 4; ++g) {
+        const int c = 32 * ct + 8 * g + 4 * hf;
+        const float4 d4 = *(const float4*)(my + c * 4);
+        const float dv4[4] = {d4.x, d4.y, d4.z, d4.w};
+        uint2 b4 = make_uint2(0u, 0u);
+        if (bias) b4 = *(const uint2*)(my + 768 + c * 2);
+        const float bv[4] = {bf16_lo(b4.x), bf16_hi(b4.x), bf16_lo(b4.y), bf16_hi(b4.y)};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          acc[ct][4 * g + e] = bias ? __builtin_fmaf(acc[ct][4 * g + e], dv4[e] * inv_l, bv[e]) : acc[ct][4 * g + e] * (dv4[e] * inv_l);
+      }
+  };
+  if (!SHARED && A.bias) normalise(std::true_type{}); else normalise(std::false_type{});
 
-  // ---- linear branch: O_l^T[o][q] = sum_c H[o][c] phi(Q)[q][c], divided by phi(Q).Z
-  if (A.has_lin) {
-    const bf16_t* Hi = A.HZ + (size_t)rowid * HZ_ELEMS;
-    v8bf bq[8];
-    float den = 0.f;
-    {
-      float x[64];
+  // ---- linear branch: O_l^T[o][q] = sum_c H[o][c] phi(Q)[q][c], divided by phi(Q).Z (which comes out of the matrix pipe
+  // like the row sum of P: a fifth tile with Z in rows 0 and 4 gives it in register 0 of both lanes of a query)
+  if (!SHARED && A.has_lin) {
+    uint4 bq[8];
+    phi_q_operands(qraw, A.phi, bq);
+    const unsigned char* zrow = my + (l32 == 0 || l32 == 4 ? 512 : 1024) + 32 * hf;
+    const uint4* h[4];
 #pragma unroll
-      for (int s = 0; s < 4; ++s) load_q16(qptr + 32 * s + 16 * hf, qok, x + 16 * s);
-      if (A.phi == 0) {
-        float mx = x[0];
+    for (int ot = 0; ot < 4; ++ot) h[ot] = (SMALL ? ring + (n_c + ot) % 3 * SLOT : k_slot(n_c + ot)) + lane;
+    auto h_op = [&](int ot, int ks) __attribute__((always_inline)) { return SMALL && ot == 3 ? h3[ks] : h[ot][ks * 64]; };
+    v16f den = v16f{}, al[2] = {v16f{}, v16f{}};
 #pragma unroll
-        for (int e = 1; e < 64; ++e) mx = fmaxf(mx, x[e]);
-        mx = fmaxf(mx, partner_f32(mx));
-        float sum = 0.f;
+    for (int ks = 0; ks < 8; ++ks) {
+      den = mfma_bf16(*(const uint4*)(zrow + 64 * (ks >> 1) + 16 * (ks & 1)), bq[ks], den);
+      al[0] = mfma_bf16(h_op(0, ks), bq[ks], al[0]);
+      al[1] = mfma_bf16(h_op(1, ks), bq[ks], al[1]);
+    }
+    const float inv_den = den[0] != 0.f ? 1.0f / den[0] : 0.f;  // no marginal block: no linear term
 #pragma unroll
-        for (int e = 0; e < 64; ++e) {
-          x[e] = __builtin_amdgcn_exp2f((x[e] - mx) * LOG2E);
-          sum += x[e];
-        }
-        sum += partner_f32(sum);
-        const float inv = 1.0f / sum;
+    for (int half = 0; half < 2; ++half) {
 #pragma unroll
-        for (int e = 0; e < 64; ++e) x[e] *= inv;
-      } else if (A.phi == 1) {
+      for (int u = 0; u < 2; ++u)
 #pragma unroll
-        for (int e = 0; e < 64; ++e) x[e] = x[e] > 0.f ? x[e] + 1.0f : __builtin_amdgcn_exp2f(x[e] * LOG2E);
-      } else {
+        for (int r = 0; r < 16; ++r) acc[2 * half + u][r] = __builtin_fmaf(al[u][r], inv_den, acc[2 * half + u][r]);
+      if (half == 0) {
+        al[0] = al[1] = v16f{};
 #pragma unroll
-        for (int e = 0; e < 64; ++e) x[e] = fmaxf(x[e], 0.f);
-      }
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        float z[16];
-        load_q16(Hi + D * D + 32 * s + 16 * hf, true, z);
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const __bf16 pb16 = (__bf16)x[16 * s + e];
-          bq[2 * s + (e >> 3)][e & 7] = pb16;
-          den = __builtin_fmaf((float)pb16, z[e], den);
+        for (int ks = 0; ks < 8; ++ks) {
+          al[0] = mfma_bf16(h_op(2, ks), bq[ks], al[0]);
+          al[1] = mfma_bf16(h_op(3, ks), bq[ks], al[1]);
         }
       }
-    }
-    den += partner_f32(den);
-    const float inv_den = den != 0.f ? 1.0f / den : 0.f;  // no marginal block: no linear term
-#pragma unroll
-    for (int ot = 0; ot < 4; ++ot) {
-      v16f al = v16f{};
-#pragma unroll
-      for (int ks = 0; ks < 8; ++ks) {
-        const v8bf a = *(const v8bf*)(Hi + (size_t)hz_frag_chunk(ot, ks, lane) * 8);  // 1 KiB contiguous per wavefront
-        al = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bq[ks], al, 0, 0, 0);
-      }
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[ot][r] = __builtin_fmaf(al[r], inv_den, acc[ot][r]);
-    }
-    if (A.bias) {
-#pragma unroll
-      for (int ct = 0; ct < 4; ++ct)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          acc[ct][r] += bf16_to_f32(A.bias[32 * ct + 8 * (r >> 2) + 4 * hf + (r & 3)]);
     }
   }
 
-  // ---- transpose through LDS (per wavefront: 32 rows x 32 channels fp32 at a time) and store.
-  // Wavefront w stages in K slot w, which nobody reads or fills any more (the drain barrier above came
-  // after the last read of a K slot and after every copy had landed), so no workgroup barrier is
-  // needed: a wavefront's LDS operations execute in the order it issues them.
-  unsigned char* my = (unsigned char*)(SMALL ? ring + w * SLOT : w == 0 ? kst0 : w == 1 ? kst1 : w == 2 ? kst2 : kst3);
+  // ---- transpose through LDS (per wavefront, in its own slot) and store
+  __builtin_amdgcn_wave_barrier();
+  const int row0 = i * BQ + 32 * w;
+  const size_t out0 = (size_t)(b_ * A.lo.sb + h_ * A.lo.sh + row0 * A.lo.sn);
+  if (!A.out_f32) {
+    store_rows(my, acc, lane, (bf16_t*)A.out + out0, A.lo.sn, A.N - row0);
+    return;
+  }
 #pragma unroll
-  for (int ct = 0; ct < 4; ++ct) {
+  for (int ct = 0; ct < 4; ++ct) {     // 32 channels in fp32 at a time
     __builtin_amdgcn_wave_barrier();   // (compiler fence: the stores below stay behind the reads of the pass before)
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
@@ -677,16 +717,8 @@ __global__ void __launch_bounds__(NW * 64, 2) sparse_fwd_kernel(
 #pragma unroll
     for (int it = 0; it < 4; ++it) {
       const int rr = it * 8 + (lane >> 3), c4 = lane & 7;
-      const int grow = i * BQ + 32 * w + rr;
       const float4 val = *(const float4*)(my + rr * EPI_STRIDE + c4 * 16);
-      if (grow < A.N) {
-        const size_t o = (size_t)(b_ * A.lo.sb + h_ * A.lo.sh + grow * A.lo.sn) + 32 * ct + 4 * c4;
-        if (A.out_f32) {
-          *(float4*)((float*)A.out + o) = val;
-        } else {
-          *(uint2*)((bf16_t*)A.out + o) = make_uint2(pack_bf16x2(val.x, val.y), pack_bf16x2(val.z, val.w));
-        }
-      }
+      if (row0 + rr < A.N) *(float4*)((float*)A.out + out0 + rr * A.lo.sn + 32 * ct + 4 * c4) = val;
     }
   }
 }

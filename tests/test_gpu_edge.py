@@ -162,6 +162,32 @@ def test_every_list_length_through_the_sparse_stage(n_c, bq):
         assert dl.max() < 2e-2 and np.median(dl) < 1e-5
 
 
+@pytest.mark.parametrize("quant", [sla.QUANT_QK_INT8_PV_FP8, sla.QUANT_NONE])
+@pytest.mark.parametrize("bq", [128, 64])
+@pytest.mark.parametrize("n_c", [1, 2, 3, 4, 5, 6, 7, 8, 9, 11])
+def test_every_list_length_with_the_linear_branch(n_c, bq, quant):
+    """The summaries of a query block take the places of the staged key blocks behind the end of its list (which place
+    depends on the list's length and on whether it ends in the ragged block); bias and result start at any element."""
+    cfg = synth.custom_config(1, 2, (6, 7, 25), block_q=bq, topk_ratio=n_c / 17, marginal_ratio=4 / 17, cfg_id=711)   # N = 1050, Tk = 17
+    q, k, v = synth.make_qkv(cfg, seed=n_c)
+    W, bias = synth.make_proj(cfg), synth.make_qkv(cfg, seed=3)[0][0, 0, 0].contiguous()
+    odd = torch.zeros(129, dtype=torch.bfloat16, device="cuda")
+    odd[1:] = bias.cuda()
+    out = torch.empty(q.numel() + 1, dtype=torch.bfloat16, device="cuda")[1:].view(q.shape)
+    args = (bq, 64, cfg.topk_ratio, cfg.marginal_ratio)
+    sla.sla_attention_fwd(*pu.to_dev(q, k, v), *args, proj_w=W.cuda(), proj_b=odd[1:], quant_mode=quant, out=out)
+    mask = sla.sla_classify_blocks(*pu.to_dev(q, k), *args, want_scores=False)[0].cpu().numpy()
+    assert ((mask == 1).sum(-1) == n_c).all() and (mask[..., -1] == 1).any() and (mask[..., -1] != 1).any()   # both kinds of end
+    for h in range(cfg.H):
+        ref = so.sla_forward_head(*(synth.as_f64(x[0, h]) for x in (q, k, v)), *args, proj_w=synth.as_f64(W),
+                                  proj_b=synth.as_f64(bias), mask=mask[0, h], ref_tile=pu.REF_TILE,
+                                  quant=so.QUANT_NONE if quant == sla.QUANT_NONE else so.QUANT_QK_INT8_PV_FP8)["out"]
+        got = out[0, h].float().cpu().numpy().astype(np.float64)
+        pu.check_output(got, ref, "n_c %d head %d" % (n_c, h))
+        # (bf16 results: 1.7e-3 of rounding; 5e-3 as in the parity tests)
+        assert np.linalg.norm(got - ref) / np.linalg.norm(ref) <= 5e-3
+
+
 @pytest.mark.parametrize("grid", [(6, 7, 25), (1, 8, 24), (2, 8, 8), (1, 5, 5)])   # 17 (ragged), 3, 2 and 1 query blocks
 def test_all_critical_blocks_of_64_queries_share_a_workgroup(grid):
     """Every key block critical at query blocks of 64: two adjacent blocks then share one walk over the records.
