@@ -389,12 +389,16 @@ struct FwdEpilogue {
 // busy, 52 GB past L2 in 12.2 ms); of 64 by the stream of K and V, 32 KB for every 64 x 64 scores: 128 GB past L2 in 16.7 ms =
 // 7.6 TB/s, what a plain reader of such tiles gets, with the pipe 44 % busy.  At 12 x 32760 the pipe is 57 and 50 % busy, 2.0
 // and 4.4 GB go past L2 in 0.82 and 0.95 ms: the exponentials beside the products.
+// The epilogue's H_i comes into the ring during the last step (with two wavefronts half of it; the rest behind the last step),
+// its other operands in one go, phi(Q) is left unnormalised where that cancels, rows leave whole: attention kernel 750 ->
+// 709 us at 12 x 32760 token-major with O^s saved; 4 x 2187, query blocks of 64 (19 us) no difference.
 template <int NW, bool CODES, bool ST>
 __global__ void __launch_bounds__(NW * 64, 2) fwd_bf16_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                                                             const bf16_t* __restrict__ v, const int32_t* __restrict__ crit,
                                                             BwdDims dm, FwdEpilogue fe) {
   constexpr int KT = NW / 2, STEP_B = 2 * KT * SWZ_TILE_B;
   __shared__ __attribute__((aligned(16))) unsigned char ring[2 * STEP_B];  // two steps' tiles: KT of K, then KT of V
+  __shared__ __attribute__((aligned(16))) unsigned char side[NW * 768];    // a wavefront's Z_i, bias, zeros
   int i, bh;
   if (fe.save_hdr && blockIdx.x == 0 && threadIdx.x < 64) {
     const int v[8] = {fe.hdr.magic, fe.hdr.B, fe.hdr.H, fe.hdr.N, fe.hdr.block_q, fe.hdr.n_c, fe.hdr.pad0, fe.hdr.pad1};
@@ -421,8 +425,19 @@ __global__ void __launch_bounds__(NW * 64, 2) fwd_bf16_kernel(const bf16_t* __re
   float m = -FLT_MAX;    // (finite: a tile may hold no valid key, and then its P have to be 0 and not NaN)
   const float qscale = CODES ? QK_LOG2 * fe.code_dq[(size_t)bh * dm.Tq + i] : QK_LOG2;
   v16f lacc = v16f{};  // register 0: the running sum of P over the keys (see the ones operand below)
+  const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void*)ring;
+  // The epilogue's H_i (four quarters of 8 KB, one per output tile): as many as fit come into half `half` of the ring during the
+  // last step, copied by all wavefronts.
+  constexpr int H_HALF = STEP_B / 8192;        // quarters there: 4 or 2
+  const char* const h_rec = (const char*)(fe.HZ + ((size_t)bh * dm.Tq + i) * HZ_ELEMS);
+  auto request_h = [&](int half, int first) __attribute__((always_inline)) {   // quarters first .. first + H_HALF - 1
+    if (fe.HZ) {
+#pragma unroll
+      for (int u = 0; u < STEP_B / 1024 / NW; ++u)
+        copy_piece(h_rec + first * 8192, (unsigned)(1024 * (w + u * NW) + 16 * lane), lds0 + half * STEP_B + 1024 * (w + u * NW));
+    }
+  };
   if (dm.n_c > 0) {
-    const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void*)ring;
     TileCopy<NW> ck, cv;
     ck.init(slice_of(k, L_k, bh, dm.H), L_k.sn, w, lane);
     cv.init(slice_of(v, L_v, bh, dm.H), L_v.sn, w, lane);
@@ -434,10 +449,11 @@ __global__ void __launch_bounds__(NW * 64, 2) fwd_bf16_kernel(const bf16_t* __re
         cv.template tile<true>(key0 + 32 * kt, dm.N, lds0 + half * STEP_B + (KT + kt) * SWZ_TILE_B);   // (zero times an infinite V would not be zero)
       }
     };
-    // KT tiles of 32 keys from key0 on, in half `half` of the ring; next: the step behind this one starts there (< 0: none)
+    // KT tiles of 32 keys from key0 on, in half `half` of the ring; next: the step behind this one starts there (< 0: none,
+    // the epilogue's operands come instead)
     auto step = [&](int key0, float c2, int half, int next) __attribute__((always_inline)) {   // c2: score -> base-2 logit
       copies_barrier<0>();                     // this step's tiles have landed; those of the step before are consumed
-      if (next >= 0) request(next, half ^ 1);
+      if (next >= 0) request(next, half ^ 1); else request_h(half ^ 1, 0);
       // (a half of the ring is a multiple of the bits that the reads flip: added to the lane's offset)
       int no = n_off + half * STEP_B, to = t_off + half * STEP_B;
       asm volatile("" : "+v"(no), "+v"(to));
@@ -521,97 +537,91 @@ __global__ void __launch_bounds__(NW * 64, 2) fwd_bf16_kernel(const bf16_t* __re
       j = jn;
     }
   }
+  const int last_half = NW == 4 ? (dm.n_c - 1) & 1 : 1;   // of the ring, which the last step has read
+  if (dm.n_c <= 0) request_h(last_half ^ 1, 0);
+  // What the epilogue needs of memory beside that, in one go: Q for phi(Q), two channels of Z_i and of the bias per lane.
+  uint4 qraw[8];
+  uint32_t z2 = 0, b2 = 0;
+  if (fe.HZ) {
+    // (rows beyond N come as row N - 1: what they give is not stored)
+    const long long row = qok ? qrow : dm.N - 1;
+    const bf16_t* ql = CODES ? slice_of(fe.q_lin, fe.lq_lin, bh, dm.H) + row * fe.lq_lin.sn : qh + row * L_q.sn;
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) qraw[ks] = *(const uint4*)(ql + 32 * (ks >> 1) + 16 * hf + 8 * (ks & 1));
+    z2 = *(const uint32_t*)(h_rec + D * D * 2 + 4 * lane);
+    if (fe.bias) b2 = (uint32_t)fe.bias[2 * lane] | (uint32_t)fe.bias[2 * lane + 1] << 16;
+  }
+  if constexpr (H_HALF < 4) {                  // the other two quarters take the place of the last step's tiles
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    request_h(last_half, H_HALF);
+  }
   const float l = lacc[0];
   const float inv_l = dm.n_c > 0 ? 1.0f / l : 0.f;
 #pragma unroll
   for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
     for (int r = 0; r < 16; ++r) o[ct][r] *= inv_l;
-  if (fe.save_lse2) {  // what a backward pass needs of this one
-    if (hf == 0) fe.save_lse2[(size_t)bh * dm.T32q * 32 + 32 * T + l32] = (qok && dm.n_c > 0) ? m + __builtin_amdgcn_logf(l) : INFINITY;
-    if (qok) {
-#pragma unroll
-      for (int ct = 0; ct < 4; ++ct)
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-          *(uint2*)(fe.save_os + head + qrow * D + 32 * ct + 8 * g + 4 * hf) =
-              uint2{pack_bf16x2(o[ct][4 * g], o[ct][4 * g + 1]), pack_bf16x2(o[ct][4 * g + 2], o[ct][4 * g + 3])};
-    }
+  // what a backward pass needs of this one: the log-sum-exp, and O^s below
+  if (fe.save_lse2 && hf == 0) fe.save_lse2[(size_t)bh * dm.T32q * 32 + 32 * T + l32] = (qok && dm.n_c > 0) ? m + __builtin_amdgcn_logf(l) : INFINITY;
+  uint4 bq[8];
+  if (fe.HZ) phi_q_operands(qraw, fe.phi, bq);
+  copies_barrier<0>();                         // H_i has landed; nobody reads the last step's tiles any more
+  const int rows = dm.N - 32 * T;              // of this wavefront's 32 that exist (32 and more: all)
+  unsigned char* out_lds = ring + last_half * STEP_B + w * 8192;
+  uint2 os[16];
+  auto store_os = [&]() __attribute__((always_inline)) { store_rows(out_lds, os, lane, fe.save_os + head + 32ll * T * D, D, rows); };
+  if (fe.save_lse2) {
+    pack_rows(o, os);
+    if (H_HALF == 4) store_os();               // (with less there, that half is still in use)
   }
   if (fe.HZ) {
     // linear term, transposed like everything else: O_l^T[o][n] = sum_c H'[c][o] phi(Q)[n][c]; the
-    // stored chunks of H' are this product's A operand, phi(Q) follows their channel order
-    const bf16_t* Hi = fe.HZ + ((size_t)bh * dm.Tq + i) * HZ_ELEMS;
-    float x[64];
-    uint4 bq[8];
+    // stored chunks of H' are this product's A operand, phi(Q) follows their channel order.  phi(Q) . Z comes out of the
+    // matrix pipe as well: a fifth tile with Z in rows 0 and 4 gives it in register 0 of both lanes of a query.
+    unsigned char* my = side + 768 * w;
+    *(uint32_t*)(my + 4 * lane) = z2;
+    *(uint32_t*)(my + 256 + 4 * lane) = b2;
+    *(uint32_t*)(my + 512 + 4 * lane) = 0u;
+    __builtin_amdgcn_wave_barrier();
+    const unsigned char* zrow = my + (l32 == 0 || l32 == 4 ? 0 : 512) + 32 * hf;
+    auto h_op = [&](int ot, int ks) __attribute__((always_inline)) {
+      return *(const uint4*)(ring + (ot < H_HALF ? last_half ^ 1 : last_half) * STEP_B + (ot % H_HALF * 8 + ks) * 1024 + 16 * lane);
+    };
+    v16f den = v16f{};
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-      const int c0 = 32 * (ks >> 1) + 16 * hf + 8 * (ks & 1);
-      const bf16_t* ql = CODES ? slice_of(fe.q_lin, fe.lq_lin, bh, dm.H) + qrow * fe.lq_lin.sn : qh + qrow * L_q.sn;
-      const uint4 qv = qok ? *(const uint4*)(ql + c0) : uint4{0u, 0u, 0u, 0u};
-      x[8 * ks] = bf16_lo(qv.x); x[8 * ks + 1] = bf16_hi(qv.x); x[8 * ks + 2] = bf16_lo(qv.y); x[8 * ks + 3] = bf16_hi(qv.y);
-      x[8 * ks + 4] = bf16_lo(qv.z); x[8 * ks + 5] = bf16_hi(qv.z); x[8 * ks + 6] = bf16_lo(qv.w); x[8 * ks + 7] = bf16_hi(qv.w);
-    }
-    if (fe.phi == 0) {
-      float mx = x[0];
+    for (int ks = 0; ks < 8; ++ks) den = mfma_bf16(*(const uint4*)(zrow + 64 * (ks >> 1) + 16 * (ks & 1)), bq[ks], den);
+    const float inv_den = den[0] != 0.f ? 1.0f / den[0] : 0.f;  // no marginal block: no linear term
 #pragma unroll
-      for (int e = 1; e < 64; ++e) mx = fmaxf(mx, x[e]);
-      mx = fmaxf(mx, partner_f32(mx));
-      float sum = 0.f;
+    for (int op = 0; op < 4; op += 2) {        // (two output tiles at a time: their products do not wait for each other)
+      v16f al[2] = {v16f{}, v16f{}};
 #pragma unroll
-      for (int e = 0; e < 64; ++e) {
-        x[e] = __builtin_amdgcn_exp2f((x[e] - mx) * LOG2E);
-        sum += x[e];
-      }
-      sum += partner_f32(sum);
-      const float inv = 1.0f / sum;
+      for (int ks = 0; ks < 8; ++ks)
 #pragma unroll
-      for (int e = 0; e < 64; ++e) x[e] *= inv;
-    } else if (fe.phi == 1) {
+        for (int u = 0; u < 2; ++u)
+          al[u] = mfma_bf16(h_op(op + u, ks), bq[ks], al[u]);
 #pragma unroll
-      for (int e = 0; e < 64; ++e) x[e] = x[e] > 0.f ? x[e] + 1.0f : __builtin_amdgcn_exp2f(x[e] * LOG2E);
-    } else {
+      for (int u = 0; u < 2; ++u)
 #pragma unroll
-      for (int e = 0; e < 64; ++e) x[e] = fmaxf(x[e], 0.f);
-    }
-    float den = 0.f;
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-      const int c0 = 32 * (ks >> 1) + 16 * hf + 8 * (ks & 1);
-      const uint4 zv = *(const uint4*)(Hi + D * D + c0);
-      const float z[8] = {bf16_lo(zv.x), bf16_hi(zv.x), bf16_lo(zv.y), bf16_hi(zv.y),
-                          bf16_lo(zv.z), bf16_hi(zv.z), bf16_lo(zv.w), bf16_hi(zv.w)};
-      bq[ks] = uint4{pack_bf16x2(x[8 * ks], x[8 * ks + 1]), pack_bf16x2(x[8 * ks + 2], x[8 * ks + 3]),
-                     pack_bf16x2(x[8 * ks + 4], x[8 * ks + 5]), pack_bf16x2(x[8 * ks + 6], x[8 * ks + 7])};
-      const uint32_t bw[4] = {bq[ks].x, bq[ks].y, bq[ks].z, bq[ks].w};
-#pragma unroll
-      for (int e = 0; e < 8; ++e) den = __builtin_fmaf(e & 1 ? bf16_hi(bw[e >> 1]) : bf16_lo(bw[e >> 1]), z[e], den);
-    }
-    den += partner_f32(den);
-    const float inv_den = den != 0.f ? 1.0f / den : 0.f;  // no marginal block: no linear term
-#pragma unroll
-    for (int ot = 0; ot < 4; ++ot) {
-      v16f al = v16f{};
-#pragma unroll
-      for (int ks = 0; ks < 8; ++ks) al = mfma_bf16(*(const uint4*)(Hi + (size_t)hz_frag_chunk(ot, ks, lane) * 8), bq[ks], al);
-#pragma unroll
-      for (int r = 0; r < 16; ++r) o[ot][r] = __builtin_fmaf(al[r], inv_den, o[ot][r]);
+        for (int r = 0; r < 16; ++r) o[op + u][r] = __builtin_fmaf(al[u][r], inv_den, o[op + u][r]);
     }
     if (fe.bias) {
 #pragma unroll
       for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) o[ct][r] += bf16_to_f32(fe.bias[32 * ct + 8 * (r >> 2) + 4 * hf + (r & 3)]);
+        for (int g = 0; g < 4; ++g) {
+          const uint2 b4 = *(const uint2*)(my + 256 + (32 * ct + 8 * g + 4 * hf) * 2);
+          o[ct][4 * g] += bf16_lo(b4.x);
+          o[ct][4 * g + 1] += bf16_hi(b4.x);
+          o[ct][4 * g + 2] += bf16_lo(b4.y);
+          o[ct][4 * g + 3] += bf16_hi(b4.y);
+        }
     }
   }
-  if (qok) {
-#pragma unroll
-    for (int ct = 0; ct < 4; ++ct)
-#pragma unroll
-      for (int g = 0; g < 4; ++g)
-        *(uint2*)(slice_of(fe.out, L_o, bh, dm.H) + qrow * L_o.sn + 32 * ct + 8 * g + 4 * hf) =
-            uint2{pack_bf16x2(o[ct][4 * g], o[ct][4 * g + 1]), pack_bf16x2(o[ct][4 * g + 2], o[ct][4 * g + 3])};
+  if constexpr (H_HALF < 4) {
+    copies_barrier<0>();                       // (the quarters of H_i there are consumed)
+    if (fe.save_lse2) store_os();
   }
+  store_rows(out_lds, o, lane, slice_of(fe.out, L_o, bh, dm.H) + 32ll * T * L_o.sn, L_o.sn, rows);
 }
 
 // 4 accumulated values of one 8-channel group -> bf16, plus the linear branch's share if given.
