@@ -58,7 +58,8 @@ size_t sla_bwd_workspace_bytes(int B, int H, int N, int d, int block_q, int bloc
  * call; the stages are: 0 block mask and, with marginal blocks, the summaries of the keys (and a
  * saved state's delta), which share its last launch, 1 softmax statistics (lse, delta; empty where
  * stage 0 had delta), 2 linear branch and projection (accumulation, dQ share, transposed
- * accumulation), 3 dQ, 4 dK and dV (with their shares of the linear branch). */
+ * accumulation), 3 dQ, 4 dK and dV (with their shares of the linear branch).  In calls of few
+ * query blocks dQ shares the launch of dK and dV and counts to stage 4 -- stage 3 is then empty. */
 int sla_attention_bwd(const void* q, const void* k, const void* v, const void* dout, const void* proj_w,
                       void* dq, void* dk, void* dv, float* dproj_w, float* dproj_b, int B, int H, int N, int d,
                       int block_q, int block_k, double topk_ratio, double marginal_ratio, int phi_kind,

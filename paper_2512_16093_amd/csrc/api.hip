@@ -693,12 +693,14 @@ int sla_attention_bwd_strided(const void* q, const void* k, const void* v, const
     launch_lin_accumulate(pt, at<uint32_t>(ws, X.mbits_t), at<bf16_t>(ws, X.dHZ), at<bf16_t>(ws, W.hz), second, s);
   }
   mark(s, rec, 3);
-  launch_bwd_dq(p, q, dout, k, v, at<int32_t>(ws, W.crit), lse2, at<float>(ws, X.delta),
-                lin ? at<float>(ws, X.dql) : nullptr, dq, s);
+  const DqWith with{at<int32_t>(ws, W.crit), lin ? at<float>(ws, X.dql) : nullptr, dq};
+  const bool one_launch = bwd_dq_with_dkv(p);
+  if (!one_launch) launch_bwd_dq(p, q, dout, k, v, with.crit, lse2, at<float>(ws, X.delta), with.dq_lin, dq, s);
   mark(s, rec, 4);
   // (the scores, BH Tq Tk words, are read no more: the launch orders its workgroups in their place)
   if (launch_bwd_dkv(p, q, dout, k, v, at<int8_t>(ws, W.mask), lse2, at<float>(ws, X.delta),
-                     lin ? at<bf16_t>(ws, W.hz) : nullptr, phi_kind, dk, dv, p.Tq >= 4 ? at<int>(ws, W.scores) : nullptr, s) != 0)
+                     lin ? at<bf16_t>(ws, W.hz) : nullptr, phi_kind, dk, dv, p.Tq >= 4 ? at<int>(ws, W.scores) : nullptr,
+                     one_launch ? &with : nullptr, s) != 0)
     return SLA_ERR_HIP;
   mark(s, rec, 5);
   return launch_status();

@@ -441,9 +441,11 @@ inline int delta_blocks(const Problem& p) { return (int)(((long long)p.BH * p.Tq
 void launch_bwd_delta(const DeltaArgs& X, const Problem& p, hipStream_t stream);
 void launch_bwd_dq(const Problem& p, const void* q, const void* dout, const void* k, const void* v, const int32_t* crit,
                    const float* lse2, const float* delta, const float* dq_lin, void* dq, hipStream_t stream);
-// (order_ws: room for 2 BH Tk + 7 words, or nullptr)
+// (order_ws: room for 2 BH Tk + 7 words, or nullptr; with: dQ in the same launch, where bwd_dq_with_dkv())
+bool bwd_dq_with_dkv(const Problem& p);
+struct DqWith { const int32_t* crit; const float* dq_lin; void* dq; };
 int launch_bwd_dkv(const Problem& p, const void* q, const void* dout, const void* k, const void* v, const int8_t* mask,
-                    const float* lse2, const float* delta, const bf16_t* G, int phi_kind, void* dk, void* dv, int* order_ws, hipStream_t stream);
+                    const float* lse2, const float* delta, const bf16_t* G, int phi_kind, void* dk, void* dv, int* order_ws, const DqWith* with, hipStream_t stream);
 size_t bwd_lin_q_partial_bytes(const Problem& p);
 double launch_mfma_rate(int kind, int iters, int n_cu, float* sink, hipStream_t stream);
 int launch_bwd_lin_q(const Problem& p, const void* q, const void* dout, const bf16_t* HZ, const bf16_t* proj_w,

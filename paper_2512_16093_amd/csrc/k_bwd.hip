@@ -93,8 +93,8 @@ struct BwdDims {
 // Workgroup -> (block, head) for a 1-D grid of 8 * ceil(T / 8) * BH workgroups.  Consecutive workgroup
 // ids go to the 8 XCDs in turn; this order gives each XCD a contiguous run of a head's blocks, so
 // the workgroups resident on one XCD at a time work on neighbouring blocks.  Returns false for the padding.
-__device__ __forceinline__ bool xcd_block(int T, int& block, int& bh) {
-  const int per_xcd = (T + 7) >> 3, xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+__device__ __forceinline__ bool xcd_block(int T, int& block, int& bh, int number = blockIdx.x) {
+  const int per_xcd = (T + 7) >> 3, xcd = number & 7, slot = number >> 3;
   bh = slot / per_xcd;
   block = xcd * per_xcd + (slot - bh * per_xcd);
   return block < T;
@@ -665,19 +665,21 @@ __device__ __forceinline__ void score_wait(v16f& x) { asm volatile("s_nop 15\n\t
 // pair at a time (in one burst behind the barrier they held the wavefront up), and dP starts from minus delta (32 of 325
 // instructions of a step less): 16.1 -> 15.2 ms, 1.00 -> 0.93 ms.  With another 10 instructions and two waits of a step
 // taken out it is no faster: bound by power (1.75 to 1.80 GHz, the matrix pipe 61 % busy).
+// dq_block: one workgroup's part, `unit` counting workgroups of a slice (PER of them serve a query block: 32 WAVES QT rows
+// each), in `ring` of dq_lds(WAVES) bytes.
+constexpr int dq_ring(int waves) { return waves == 1 ? 2 : 4; }   // (four workgroups of one wavefront have 40 KB of LDS each)
+constexpr int dq_lds(int waves) { return dq_ring(waves) * 2 * SWZ_TILE_B; }
 template <int WAVES, int QT, bool ST>
-__global__ void __launch_bounds__(WAVES * 64, 1) bwd_dq_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ dout,
-                                                              const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
-                                                              const int32_t* __restrict__ crit, const float* __restrict__ lse2,
-                                                              const float* __restrict__ delta, const float* __restrict__ dq_lin,
-                                                              bf16_t* __restrict__ dq, BwdDims dm) {
-  constexpr int R = WAVES == 1 ? 2 : 4;   // (four workgroups of one wavefront have 40 KB of LDS each)
-  __shared__ __attribute__((aligned(16))) unsigned char ring[R * 2 * SWZ_TILE_B];  // K, V tile by tile
-  int i, bh;
-  if (!xcd_block(dm.Tq, i, bh)) return;
+__device__ __forceinline__ void dq_block(const bf16_t* __restrict__ q, const bf16_t* __restrict__ dout, const bf16_t* __restrict__ k,
+                                         const bf16_t* __restrict__ v, const int32_t* __restrict__ crit,
+                                         const float* __restrict__ lse2, const float* __restrict__ delta,
+                                         const float* __restrict__ dq_lin, bf16_t* __restrict__ dq, const BwdDims& dm,
+                                         unsigned char* ring, int unit, int per, int bh) {
+  constexpr int R = dq_ring(WAVES);
+  const int i = per == 1 ? unit : unit / per;
   SLA_BWD_LAYOUTS
   const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6), l32 = lane & 31, hf = lane >> 5;
-  const int row0 = 32 * QT * (i * WAVES + w);
+  const int row0 = 32 * QT * (unit * WAVES + w);
   v4i qf[QT][8], dof[QT][8];
   v16f acc[QT][4];
   float lse[QT], del[QT];
@@ -921,6 +923,17 @@ __global__ void __launch_bounds__(WAVES * 64, 1) bwd_dq_kernel(const bf16_t* __r
       }
   }
 }
+template <int WAVES, int QT, bool ST>
+__global__ void __launch_bounds__(WAVES * 64, 1) bwd_dq_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ dout,
+                                                              const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
+                                                              const int32_t* __restrict__ crit, const float* __restrict__ lse2,
+                                                              const float* __restrict__ delta, const float* __restrict__ dq_lin,
+                                                              bf16_t* __restrict__ dq, BwdDims dm) {
+  __shared__ __attribute__((aligned(16))) unsigned char ring[dq_lds(WAVES)];  // K, V tile by tile
+  int i, bh;
+  if (!xcd_block(dm.Tq, i, bh)) return;
+  dq_block<WAVES, QT, ST>(q, dout, k, v, crit, lse2, delta, dq_lin, dq, dm, ring, i, 1, bh);
+}
 
 // The linear branch's share of dK and dV for the 32 keys of a wavefront (Section 1.2's operator:
 // h_j = phi(K_j)^T V_j, z_j = column sums of phi(K_j), phi = softmax over the channels), given
@@ -1114,27 +1127,28 @@ __global__ void __launch_bounds__(1024) dkv_order_kernel(const int* __restrict__
 // 430 instructions instead of 504; whole backward pass 59.6 -> 57.8 ms (same box), 4 x 2187 (training step) 185 -> 180 us.
 // Counted at 40 x 75600: 159 GB fetched past L2 at 6.6 to 6.9 TB/s, where a plain reader gets 6.9 to 7.6, and 1.67 to 1.72 GHz
 // with the matrix pipe 56 % busy: bound by both, the stream and power.
-template <int KB, int TILES, int PHI, bool ST = false>
-__global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ dout,
-                                                      const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
-                                                      const int8_t* __restrict__ mask, const float* __restrict__ lse2,
-                                                      const float* __restrict__ delta, const bf16_t* __restrict__ G,
-                                                      bf16_t* __restrict__ dk, bf16_t* __restrict__ dv, int pair_shift,
-                                                      const int* __restrict__ order, int natural, BwdDims dm) {
+// dkv_block: the part of workgroup `number` of `count`, in `lds`.
+template <int KB, int TILES, int PHI, bool ST>
+__device__ __forceinline__ void dkv_block(const bf16_t* __restrict__ q, const bf16_t* __restrict__ dout,
+                                          const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
+                                          const int8_t* __restrict__ mask, const float* __restrict__ lse2,
+                                          const float* __restrict__ delta, const bf16_t* __restrict__ G,
+                                          bf16_t* __restrict__ dk, bf16_t* __restrict__ dv, int pair_shift,
+                                          const int* __restrict__ order, int natural, const BwdDims& dm, unsigned char* lds,
+                                          int number, int count) {
   constexpr int NT = 128 * KB, ROWS = 32 * TILES;  // threads; query rows per step
   // two buffers of: Q (TILES tiles) then dO (TILES tiles) of ROWS consecutive query rows; then their lse, delta
-  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   constexpr int BUF_B = KB == 1 ? 4 * SWZ_TILE_B : 2 * TILES * TILE_B;
   float (*stat)[2][ROWS] = (float (*)[2][ROWS])(lds + 2 * BUF_B);
   unsigned short* qlist = (unsigned short*)(lds + 2 * BUF_B + 2 * 2 * ROWS * 4);  // [Tq]
   __shared__ int wcnt[8][4];
   int J, bh;
-  if (KB == 1 && (int)blockIdx.x >= natural) {
-    const int x = order[(blockIdx.x & 7) * ((gridDim.x - natural) >> 3) + ((blockIdx.x - natural) >> 3)];   // (natural: a multiple of 8)
+  if (KB == 1 && number >= natural) {
+    const int x = order[(number & 7) * ((count - natural) >> 3) + ((number - natural) >> 3)];   // (natural: a multiple of 8)
     if (x < 0) return;
     bh = x / dm.Tk;
     J = x - bh * dm.Tk;
-  } else if (!xcd_block((dm.Tk + KB - 1) / KB, J, bh)) {
+  } else if (!xcd_block((dm.Tk + KB - 1) / KB, J, bh, number)) {
     return;
   }
   const int t = threadIdx.x, lane = t & 63, w = t >> 6, l32 = lane & 31, hf = lane >> 5;
@@ -1602,6 +1616,41 @@ __global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restr
   store_rows(dkt, DK_SIGN * INV_SQRT_D, dk, L_dk);
   store_rows(dvt, 1.0f, dv, L_dv);
 }
+template <int KB, int TILES, int PHI, bool ST = false>
+__global__ void __launch_bounds__(128 * KB) bwd_dkv_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ dout,
+                                                      const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
+                                                      const int8_t* __restrict__ mask, const float* __restrict__ lse2,
+                                                      const float* __restrict__ delta, const bf16_t* __restrict__ G,
+                                                      bf16_t* __restrict__ dk, bf16_t* __restrict__ dv, int pair_shift,
+                                                      const int* __restrict__ order, int natural, BwdDims dm) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+  dkv_block<KB, TILES, PHI, ST>(q, dout, k, v, mask, lse2, delta, G, dk, dv, pair_shift, order, natural, dm, lds, blockIdx.x, gridDim.x);
+}
+// dK/dV and, in the workgroups behind theirs, dQ (two wavefronts of 32 query rows each), which needs nothing of it: for
+// calls whose workgroups of either kind leave compute units empty or end one by one.
+struct DqPart {
+  const int32_t* crit;
+  const float* dq_lin;
+  bf16_t* dq;
+  int first, per;                // number of the first workgroup of dQ; workgroups per query block
+};
+template <int PHI, bool ST>
+__global__ void __launch_bounds__(128, 1) bwd_dq_dkv_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ dout,
+                                                           const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
+                                                           const int8_t* __restrict__ mask, const float* __restrict__ lse2,
+                                                           const float* __restrict__ delta, const bf16_t* __restrict__ G,
+                                                           bf16_t* __restrict__ dk, bf16_t* __restrict__ dv, int pair_shift,
+                                                           const int* __restrict__ order, int natural, DqPart part, BwdDims dm) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+  const int number = (int)blockIdx.x - part.first;
+  if (number < 0) {
+    dkv_block<1, 2, PHI, ST>(q, dout, k, v, mask, lse2, delta, G, dk, dv, pair_shift, order, natural, dm, lds, blockIdx.x, part.first);
+  } else {
+    int unit, bh;
+    if (xcd_block(part.per * dm.Tq, unit, bh, number))
+      dq_block<2, 1, ST>(q, dout, k, v, part.crit, lse2, delta, part.dq_lin, part.dq, dm, lds, unit, part.per, bh);
+  }
+}
 
 // ---------------------------------------------------------------------------------------------
 // Do all of these layouts equal the contiguous [B,H,N,d] one?  (Then the instances with compile-time strides serve.)
@@ -1667,13 +1716,26 @@ void launch_bwd_delta(const DeltaArgs& X, const Problem& p, hipStream_t stream) 
   bwd_delta_kernel<<<(unsigned)delta_blocks(p), 256, 0, stream>>>(X);
 }
 
+// One tile per wavefront where two would leave SIMDs without a wavefront (query blocks of 64, 4617 tokens, us before ->
+// now: 3 heads 28.5 -> 27.2, 14 heads 93 -> 79 with one tile; 20 heads 126 -> 102 with two)
+static bool dq_narrow(const Problem& p) { return (long long)p.Tq * p.BH * (p.block_q / 64) < 1024; }
+// Two key blocks per workgroup halve the bytes streamed where their lists coincide and idle half
+// a workgroup where they do not: worth it only when most blocks are critical (at the paper's
+// 10-15 % the lists of neighbours share 60 % and one key block per workgroup is 25 % faster).
+static bool dkv_paired(const Problem& p) { return 2 * p.n_c > p.Tk; }
+// dQ with dK and dV in one launch: either kind alone leaves wavefronts' places empty or runs on with a few long lists, and
+// neither needs anything of the other.  Backward pass in us, two launches / one: 4 x 2187 in blocks of 64 (140 workgroups each)
+// 119 / 95, 3 x 4617 136 / 113, 12 x 4617 262 / 244, 8 x 1024 82 / 71, 40 x 1024 in blocks of 128 178 / 161, 7 x 4617 200 / 165,
+// 1 x 37800 629 / 533, 3 x 16380 363 / 328.  From 1024 wavefronts' worth of query rows on dQ's wavefronts own 64 rows each; an
+// instance of that form here gained on a training step 4 % of 40 x 4617, 2 % of 8 x 16380, nothing from 3 x 32760 on and lost
+// 1 % of 8 x 75600: not kept.
+bool bwd_dq_with_dkv(const Problem& p) { return dq_narrow(p) && !dkv_paired(p); }
+
 void launch_bwd_dq(const Problem& p, const void* q, const void* dout, const void* k, const void* v, const int32_t* crit,
                   const float* lse2, const float* delta, const float* dq_lin, void* dq, hipStream_t stream) {
   const unsigned grid = (unsigned)(8 * ((p.Tq + 7) / 8) * p.BH);
   const bool st = !contiguous(p, {&p.lq, &p.lk, &p.lv, &p.ld, &p.ldq});
-  // One tile per wavefront where two would leave SIMDs without a wavefront (query blocks of 64, 4617 tokens, us before ->
-  // now: 3 heads 28.5 -> 27.2, 14 heads 93 -> 79 with one tile; 20 heads 126 -> 102 with two)
-  const bool narrow = (long long)p.Tq * p.BH * (p.block_q / 64) < 1024;
+  const bool narrow = dq_narrow(p);
 #define SLA_DQ(WAVES, QT, ST) bwd_dq_kernel<WAVES, QT, ST><<<grid, WAVES * 64, 0, stream>>>( \
       (const bf16_t*)q, (const bf16_t*)dout, (const bf16_t*)k, (const bf16_t*)v, crit, lse2, delta, dq_lin, (bf16_t*)dq, bwd_dims(p))
 #define SLA_DQ_ST(WAVES, QT) { if (st) SLA_DQ(WAVES, QT, true); else SLA_DQ(WAVES, QT, false); }
@@ -1688,21 +1750,18 @@ void launch_bwd_dq(const Problem& p, const void* q, const void* dout, const void
 
 template <int PHI, bool ST>
 static int launch_bwd_dkv_phi(const Problem& p, const void* q, const void* dout, const void* k, const void* v, const int8_t* mask,
-                               const float* lse2, const float* delta, const bf16_t* G, void* dk, void* dv, int* order_ws, hipStream_t stream) {
+                               const float* lse2, const float* delta, const bf16_t* G, void* dk, void* dv, int* order_ws, const DqWith* with, hipStream_t stream) {
   // dynamic LDS: two staging buffers, the rows' lse and delta, the list of query blocks
   const int list_bytes = (2 * p.Tq + 15) & ~15;
   const int lds2 = 2 * 4 * TILE_B + 2 * 2 * 64 * 4 + list_bytes;
   const int lds1 = 2 * 4 * SWZ_TILE_B + 2 * 2 * 64 * 4 + list_bytes;
   static const bool ok =
       hipFuncSetAttribute((const void*)bwd_dkv_kernel<2, 2, PHI, ST>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 256) == hipSuccess &&
-      hipFuncSetAttribute((const void*)bwd_dkv_kernel<1, 2, PHI, ST>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 256) == hipSuccess;
+      hipFuncSetAttribute((const void*)bwd_dkv_kernel<1, 2, PHI, ST>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 256) == hipSuccess &&
+      hipFuncSetAttribute((const void*)bwd_dq_dkv_kernel<PHI, ST>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 256) == hipSuccess;
   if (!ok) return -1;
   const int tiles = p.block_q / 32;  // of a query block: 2 or 4
-  // Two key blocks per workgroup halve the bytes streamed where their lists coincide and idle half
-  // a workgroup where they do not: worth it only when most blocks are critical (at the paper's
-  // 10-15 % the lists of neighbours share 60 % and one key block per workgroup is 25 % faster).
-  const bool paired = 2 * p.n_c > p.Tk;
-  if (paired) {
+  if (dkv_paired(p)) {
     const int pairs = (p.Tk + 1) / 2;
     bwd_dkv_kernel<2, 2, PHI, ST><<<(unsigned)(8 * ((pairs + 7) / 8) * p.BH), 256, lds2, stream>>>(
         (const bf16_t*)q, (const bf16_t*)dout, (const bf16_t*)k, (const bf16_t*)v, mask, lse2, delta, G,
@@ -1725,7 +1784,16 @@ static int launch_bwd_dkv_phi(const Problem& p, const void* q, const void* dout,
       dkv_counts_kernel<<<(unsigned)(heads * ((p.Tk + 63) / 64)), 1024, 0, stream>>>(mask + (size_t)first * p.Tq * p.Tk, p.Tq, p.Tk, counts);
       dkv_order_kernel<<<8, 1024, 0, stream>>>(counts, total, per, first * p.Tk, order);
     }
-    bwd_dkv_kernel<1, 2, PHI, ST><<<(unsigned)natural + (ordered ? 8u * (unsigned)per : 0u), 128, lds1, stream>>>(
+    const unsigned grid = (unsigned)natural + (ordered ? 8u * (unsigned)per : 0u);
+    if (with) {
+      const int units = p.block_q / 64;
+      const DqPart part{with->crit, with->dq_lin, (bf16_t*)with->dq, (int)grid, units};
+      bwd_dq_dkv_kernel<PHI, ST><<<grid + (unsigned)(8 * ((units * p.Tq + 7) / 8) * p.BH), 128, lds1, stream>>>(
+          (const bf16_t*)q, (const bf16_t*)dout, (const bf16_t*)k, (const bf16_t*)v, mask, lse2, delta, G,
+          (bf16_t*)dk, (bf16_t*)dv, tiles == 4 ? 1 : 0, order, natural, part, bwd_dims(p));
+      return 0;
+    }
+    bwd_dkv_kernel<1, 2, PHI, ST><<<grid, 128, lds1, stream>>>(
         (const bf16_t*)q, (const bf16_t*)dout, (const bf16_t*)k, (const bf16_t*)v, mask, lse2, delta, G,
         (bf16_t*)dk, (bf16_t*)dv, tiles == 4 ? 1 : 0, order, natural, bwd_dims(p));
   }
@@ -1734,11 +1802,11 @@ static int launch_bwd_dkv_phi(const Problem& p, const void* q, const void* dout,
 
 // (the feature map matters to the prologue only -- the linear branch's share -- and only when G is given)
 int launch_bwd_dkv(const Problem& p, const void* q, const void* dout, const void* k, const void* v, const int8_t* mask,
-                   const float* lse2, const float* delta, const bf16_t* G, int phi_kind, void* dk, void* dv, int* order_ws, hipStream_t stream) {
+                   const float* lse2, const float* delta, const bf16_t* G, int phi_kind, void* dk, void* dv, int* order_ws, const DqWith* with, hipStream_t stream) {
   const int phi = G ? phi_kind : 0;
-  const bool st = !contiguous(p, {&p.lq, &p.lk, &p.lv, &p.ld, &p.ldk, &p.ldv});
-#define SLA_DKV(PHI) (st ? launch_bwd_dkv_phi<PHI, true>(p, q, dout, k, v, mask, lse2, delta, G, dk, dv, order_ws, stream) \
-                         : launch_bwd_dkv_phi<PHI, false>(p, q, dout, k, v, mask, lse2, delta, G, dk, dv, order_ws, stream))
+  const bool st = !contiguous(p, {&p.lq, &p.lk, &p.lv, &p.ld, &p.ldk, &p.ldv}) || (with && !contiguous(p, {&p.ldq}));
+#define SLA_DKV(PHI) (st ? launch_bwd_dkv_phi<PHI, true>(p, q, dout, k, v, mask, lse2, delta, G, dk, dv, order_ws, with, stream) \
+                         : launch_bwd_dkv_phi<PHI, false>(p, q, dout, k, v, mask, lse2, delta, G, dk, dv, order_ws, with, stream))
   return phi == 0 ? SLA_DKV(0) : phi == 1 ? SLA_DKV(1) : SLA_DKV(2);
 #undef SLA_DKV
 }

@@ -196,7 +196,8 @@ def _late_operands(ins, labels):
 # kernel -> instances and assembly products of each: the dQ kernel forms S and dP of a prologue and two steps, QT tiles of
 # eight products each; dK/dV (one key block) S and dP of two tiles in two steps; W8A8 chains of four per output tile
 EXPECTED = {
-    "k_bwd.hip": {r"bwd_dq_kernelILi\dELi1": (4, 48), r"bwd_dq_kernelILi\dELi2": (4, 96), r"bwd_dkv_kernelILi1": (6, 64)},
+    "k_bwd.hip": {r"bwd_dq_kernelILi\dELi1": (4, 48), r"bwd_dq_kernelILi\dELi2": (4, 96), r"bwd_dkv_kernelILi1": (6, 64),
+                  r"bwd_dq_dkv_kernel": (6, 64 + 48)},
     "k_w8a8.hip": {r"w8a8_gemm_kernelE": (1, 96), r"w8a8_gemm_splitk_kernelILi2ELi2": (3, 16),
                    r"w8a8_gemm_splitk_kernelILi1ELi2": (2, 8), r"w8a8_gemm_splitk_kernelILi1ELi1": (2, 4)},
 }
@@ -270,7 +271,7 @@ def test_copies_of_some_lanes_stand_where_all_lanes_are_on():
         assert not found, (name, found[:4])
         if n:
             writes[re.match(r"_ZN3sla\d+(\w+?)I", name).group(1)] = writes.get(re.match(r"_ZN3sla\d+(\w+?)I", name).group(1), 0) + 1
-    assert writes == {"bwd_dq_kernel": 8, "bwd_dkv_kernel": 6}, writes
+    assert writes == {"bwd_dq_kernel": 8, "bwd_dkv_kernel": 6, "bwd_dq_dkv_kernel": 6}, writes
 
 
 def test_the_check_of_lanes_sees_what_it_is_for():

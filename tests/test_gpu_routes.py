@@ -142,3 +142,26 @@ def test_order_of_the_key_blocks_leaves_their_gradients_alone(H, N, block_q, rc,
     for a, b in zip(whole, few):
         assert torch.isfinite(b).all()
         assert torch.equal(a[:, pick], b)
+
+
+@pytest.mark.parametrize("H, N, block_q, rc, rm", [
+    (3, 129, 128, 0.34, 0.66),   # a query block of one row: the second workgroup of dQ has none
+    (9, 4033, 128, 0.1, 0.2),    # dK/dV's workgroups in the order of their lists' lengths, dQ's behind them
+    (7, 1000, 64, 0.2, 0.4),     # one workgroup of dQ per query block
+    (15, 1000, 128, 0.2, 0.0),   # 240 half query blocks, no linear branch
+])
+def test_gradients_of_one_launch_and_of_two_have_the_same_bits(H, N, block_q, rc, rm):
+    """Calls of few query blocks form dQ in the launch of dK and dV, dq wherever its caller wants it."""
+    many = 1024 // ((N + block_q - 1) // block_q * (block_q // 64)) + 1
+    q, k, v, do = _qkv(many, N) + _qkv(many, N, seed=5)[:1]
+    args = (block_q, 64, rc, rm)
+    two = sla.sla_attention_bwd(q, k, v, do, *args, proj_w=_weight(0))[:3]
+    few = [x[:, :H].contiguous() for x in (q, k, v, do)]
+    one = sla.sla_attention_bwd(*few, *args, proj_w=_weight(0))[:3]
+    token_major = torch.empty((1, N, H, D), dtype=torch.bfloat16, device="cuda").permute(0, 2, 1, 3)
+    strided = (token_major, torch.empty_like(few[0]), torch.empty_like(few[0]))
+    sla.sla_attention_bwd_strided(*few, *strided, *args, proj_w=_weight(0))
+    for a, b, c in zip(two, one, strided):
+        assert torch.isfinite(b).all()
+        assert torch.equal(a[:, :H], b)
+        assert torch.equal(c, b)
