@@ -497,6 +497,157 @@ __global__ void __launch_bounds__(64 * KS, 2) w8a8_gemm_splitk_kernel(
   }
 }
 
+// The same with larger tiles, one wavefront per SIMD (the fp32 sums of a 64 x 160 tile alone take 160 registers): per
+// product 0.7 KiB have to come from L2 instead of 1, and between 64 x 96 and 128 x 96 there is a tile that deals out in one
+// round where 64 x 64 ones leave a last round nearly empty (512 x 5120 -> 5120: 256 tiles of 64 x 160, one per compute unit;
+// of 64 x 64 there are 2.5).  The operands are held in accumulation registers, where the sums cannot be, the activations
+// of a feature block requested a whole block ahead (two sets), a weight fragment behind its last product: with one set, half
+// a block ahead, 512 x 5120 -> 5120 took 22.1 instead of 19.8 us.  Bound by what comes into the L2s (47 MB there) and from
+// them (287 MB, 0.8 of the 64 bytes per clock and compute unit).
+// A tile's outputs may span two quantisation blocks (CT = 3, 5: two scales), and the last tile of a row may reach past N (its
+// operands are then the last fragment's once more and nothing of it is stored).
+// (w8_chain with both operands in accumulation registers; 0x3e22f983 is W8_BIAS_I, the same inline constant)
+__device__ __forceinline__ v16i w8_chain_acc(const v4i (&b)[4], const v4i (&ar)[4], v16i& carry) {
+  v16i acc;
+  asm volatile("v_mfma_i32_32x32x32_i8 %0, %1, %2, 0x3e22f983" : "=&v"(acc) : "a"(b[0]), "a"(ar[0]));
+  asm volatile("v_mfma_i32_32x32x32_i8 %0, %2, %3, %0" : "+v"(acc), "+v"(carry) : "a"(b[1]), "a"(ar[1]));
+  asm volatile("v_mfma_i32_32x32x32_i8 %0, %1, %2, %0" : "+v"(acc) : "a"(b[2]), "a"(ar[2]));
+  asm volatile("v_mfma_i32_32x32x32_i8 %0, %1, %2, %0" : "+v"(acc) : "a"(b[3]), "a"(ar[3]));
+  return acc;
+}
+template <int RT, int CT, int KS>
+__global__ void __launch_bounds__(64 * KS, 1) w8a8_gemm_wide_kernel(
+    const int8_t* __restrict__ x8, const float* __restrict__ sx, const int8_t* __restrict__ w8,
+    const float* __restrict__ sw, const bf16_t* __restrict__ bias, bf16_t* __restrict__ y, int M, int N, int K,
+    int RTx, int RBx, int RTw, int RBw, int MT, int NT) {
+  static_assert(CT <= 5 && (RT == 1 || RT == 2 || RT == 4), "a tile lies in one block of tokens and at most two of outputs");
+  constexpr int PITCH = 36;  // floats per staged row of 32 outputs (16-byte rows, skewed banks)
+  __shared__ __attribute__((aligned(16))) float part[2][KS][32 * RT][PITCH];
+  const int per = (MT * NT + 7) >> 3, xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;   // (dealt as above)
+  const int idx = __builtin_amdgcn_readfirstlane(xcd * per + slot);
+  if (slot >= per || idx >= MT * NT) return;
+  const bool tokens_fastest = M <= N;
+  const int major = __builtin_amdgcn_readfirstlane(idx / (tokens_fastest ? MT : NT)), minor = idx - major * (tokens_fastest ? MT : NT);
+  const int nt = tokens_fastest ? major : minor, mt = tokens_fastest ? minor : major;
+  const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6), l32 = lane & 31, hf = lane >> 5;
+  const int KB = K / QB;
+  // This wavefront's feature blocks, in pairs (the two sets of activations in turn): an odd last one is followed by a block
+  // that does not exist, whose scale is zero.
+  const int pairs = (KB + 1) >> 1, kb0 = 2 * (pairs * w / KS), kb1 = 2 * (pairs * (w + 1) / KS);
+  const int ct0 = nt * CT, rb = mt * RT / 4, nb0 = ct0 >> 2, nb1 = min(nb0 + 1, RBw - 1);
+  auto second = [&](int c) { return ((ct0 + c) >> 2) != nb0; };
+  const unsigned char* xa = (const unsigned char*)x8 + (size_t)(mt * RT) * 4096 + (size_t)lane * 16;
+  const unsigned char* wb = (const unsigned char*)w8 + (size_t)lane * 16;
+  const size_t xkb = (size_t)RTx * 4096, wkb = (size_t)RTw * 4096;
+  size_t wct[CT];
+#pragma unroll
+  for (int c = 0; c < CT; ++c) wct[c] = (size_t)min(ct0 + c, RTw - 1) * 4096;
+
+  // (a run's sums start from minus the constant share of its first block: see above)
+  auto mag_of = [&](int kb, int nb) { return sx[(size_t)kb * RBx + rb] * sw[(size_t)kb * RBw + nb] * W8_STEP_INV; };
+  float mag[2] = {0.f, 0.f}, base[2] = {0.f, 0.f}, csum[2] = {0.f, 0.f};
+  if (kb0 < kb1) {
+    mag[0] = mag_of(kb0, nb0);
+    mag[1] = mag_of(kb0, nb1);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) base[u] = KS == 1 ? 0.f : W8_C0 * ((kb0 & 1) ? mag[u] : -mag[u]);
+  }
+  v16f facc[RT][CT];
+#pragma unroll
+  for (int r = 0; r < RT; ++r)
+#pragma unroll
+    for (int c = 0; c < CT; ++c) {
+      const float from = second(c) ? base[1] : base[0];
+#pragma unroll
+      for (int e = 0; e < 16; ++e) facc[r][c][e] = from;
+    }
+  if (kb0 < kb1) {
+    v4i a0[RT][4], a1[RT][4], b[CT][4];
+    auto load_frag = [&](const unsigned char* tile, v4i (&f)[4]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) f[ks] = *(const v4i*)(tile + ks * 1024);
+    };
+#pragma unroll
+    for (int c = 0; c < CT; ++c) load_frag(wb + (size_t)kb0 * wkb + wct[c], b[c]);
+    v16i pend;              // finished chain still to be scaled in; none yet: any finite pattern at scale 0
+#pragma unroll
+    for (int e = 0; e < 16; ++e) pend[e] = W8_BIAS_I;
+    float pend_sc = 0.f;
+    // (an even number of chains, so that the two accumulators end a step where they began it: a copy would read one too early)
+    static_assert(RT * CT % 2 == 0, "two accumulators in turn");
+    auto step = [&](int kb, const v4i (&a)[RT][4], v4i (&an)[RT][4]) __attribute__((always_inline)) {
+      float sc[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) sc[u] = kb < KB ? ((kb & 1) ? -mag[u] : mag[u]) : 0.f;
+      const int kn = min(kb + 1, KB - 1);   // (past the end the last block once more: the loop stays free of branches)
+      mag[0] = mag_of(kn, nb0);
+      mag[1] = mag_of(kn, nb1);
+#pragma unroll
+      for (int c = 0; c < CT; ++c)
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
+          v16i fresh = w8_chain_acc(b[c], a[r], pend);   // (from here on the previous chain's result may be read)
+          v16f& prev = r > 0 ? facc[r - 1][c] : facc[RT - 1][(c + CT - 1) % CT];
+          w8_scale_in(pend, pend_sc, prev);
+          asm volatile("" : "+v"(prev) : : "memory");
+          asm volatile("" : "+v"(fresh) : : "memory");
+          if (c == 0) load_frag(xa + (size_t)kn * xkb + r * 4096, an[r]);
+          if (r == RT - 1) load_frag(wb + (size_t)kn * wkb + wct[c], b[c]);
+          __builtin_amdgcn_sched_barrier(0);
+          pend = fresh;
+          pend_sc = second(c) ? sc[1] : sc[0];
+        }
+      csum[0] += sc[0];
+      csum[1] += sc[1];
+    };
+#pragma unroll
+    for (int r = 0; r < RT; ++r) load_frag(xa + (size_t)kb0 * xkb + r * 4096, a0[r]);
+    for (int kb = kb0; kb < kb1; kb += 2) {
+      step(kb, a0, a1);
+      step(kb + 1, a1, a0);
+    }
+    asm volatile(W8_READ_WAIT : "+v"(pend));
+    w8_scale_in(pend, pend_sc, facc[RT - 1][CT - 1]);
+  }
+
+  // Partial sums (constant share out) through LDS, one column tile at a time in two buffers; lane = token, registers
+  // 4 g .. 4 g + 3 = outputs 8 g + 4 hf + 0..3.  Each thread then adds eight outputs of a token, in wavefront order.
+  const float corr[2] = {__builtin_fmaf(W8_C0, csum[0], base[0]), __builtin_fmaf(W8_C0, csum[1], base[1])};
+#pragma unroll
+  for (int c = 0; c < CT; ++c) {
+    if (ct0 + c >= RTw) break;               // (uniform)
+    const float out = second(c) ? corr[1] : corr[0];
+#pragma unroll
+    for (int r = 0; r < RT; ++r)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const v16f& f = facc[r][c];
+        *(float4*)&part[c & 1][w][32 * r + l32][8 * g + 4 * hf] =
+            make_float4(f[4 * g] - out, f[4 * g + 1] - out, f[4 * g + 2] - out, f[4 * g + 3] - out);
+      }
+    __syncthreads();
+    const int n0 = (ct0 + c) * 32;
+    for (int u = t; u < 32 * RT * 4; u += 64 * KS) {
+      const int row = u >> 2, o = 8 * (u & 3), m = mt * 32 * RT + row;
+      if (m >= M) continue;
+      float v[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = part[c & 1][0][row][o + e];
+#pragma unroll
+      for (int p = 1; p < KS; ++p)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] += part[c & 1][p][row][o + e];
+      if (bias) {
+        const uint2 b0 = *(const uint2*)(bias + n0 + o), b1 = *(const uint2*)(bias + n0 + o + 4);
+        v[0] += bf16_lo(b0.x); v[1] += bf16_hi(b0.x); v[2] += bf16_lo(b0.y); v[3] += bf16_hi(b0.y);
+        v[4] += bf16_lo(b1.x); v[5] += bf16_hi(b1.x); v[6] += bf16_lo(b1.y); v[7] += bf16_hi(b1.y);
+      }
+      *(uint4*)(y + (size_t)m * N + n0 + o) = make_uint4(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]),
+                                                        pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7]));
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------
 void launch_w8a8_quantize(const void* a, int R, int K, int RP, bool negate_odd, int8_t* codes, float* scales,
                           hipStream_t stream) {
@@ -522,6 +673,14 @@ static void launch_splitk(const int8_t* x8, const float* sx, int MP, const int8_
       x8, sx, w8, sw, (const bf16_t*)bias, (bf16_t*)y, M, N, K, MP / 32, MP / QB, N / 32, N / QB, MT, NT);
 }
 
+template <int RT, int CT, int KS>
+static void launch_wide(const int8_t* x8, const float* sx, int MP, const int8_t* w8, const float* sw, const void* bias,
+                        void* y, int M, int N, int K, hipStream_t stream) {
+  const int MT = (M + 32 * RT - 1) / (32 * RT), NT = (N / 32 + CT - 1) / CT;
+  w8a8_gemm_wide_kernel<RT, CT, KS><<<(unsigned)(8 * ((MT * NT + 7) / 8)), 64 * KS, 0, stream>>>(
+      x8, sx, w8, sw, (const bf16_t*)bias, (bf16_t*)y, M, N, K, MP / 32, MP / QB, N / 32, N / QB, MT, NT);
+}
+
 void launch_w8a8_gemm(const int8_t* x8, const float* sx, int MP, const int8_t* w8, const float* sw,
                       const void* bias, void* y, int M, int N, int K, hipStream_t stream) {
   const int MT = MP / W8_WG_M, NT = N / W8_WG_N, KB = K / QB;
@@ -535,6 +694,35 @@ void launch_w8a8_gemm(const int8_t* x8, const float* sx, int MP, const int8_t* w
   //   384 -> 1024 at 4096 (128) 13.1 / 12.5, -> 4096 at 1280 (160) 12.8 / 13.2;
   // more (200): 1536 -> 1536 at 4096 (192) 26.2 / 24.8, -> 5120 at 1280 (200) 23.2 / 24.4; 5120 -> 1536 at 4096 (192)
   //   60.2 / 56.4, -> 5120 at 1280 (200) 54.7 / 55.0, -> 5120 at 1536 (240) 56.1 / 62.6.
+  // Long contractions that do not fill the chip with large tiles: of the wide tiles the smallest that deal out in one round (a
+  // wavefront per SIMD).  The product in us, before / wide: 3072 -> 1024 at 1280 tokens
+  // (320 tiles of 64 x 64, taken as 64 x 96) 11.2 / 9.7, -> 3072 at 640 (480, 64 x 128) 14.4 / 12.1; 5120 -> 5120 at 256 16.3 /
+  // 14.0, 384 22.0 / 17.0, 512 (64 x 160) 23.9 / 20.7, 768 (64 x 128, two wavefronts) 31.3 / 28.7, 1024 (64 x 160, two) 40.9 / 34.8;
+  // 5120 -> 13824 at 128 22.5 / 18.4, 384 (128 x 96, two) 48.9 / 37.4; 8960 -> 1536 at 2048 (128 x 96) 41.6 / 36.1, 4096 77.6 /
+  // 64.3; 2048 -> 2048 at 1024 10.8 / 9.9, 2048 17.6 / 16.6.  On the other side: 240 tiles (8960 -> 1536 at 640) 18.5 / 20.7,
+  // 256 (3072 -> 1024 at 1024) 10.4 / 10.3; in two rounds 5120 -> 5120 at 1280 49.1 / 55.8; 12 blocks (1536 -> 8960 at 256) 10.4 / 10.7.
+  // The round has to be filled: products of 32 x 32 x 128 against those that its wavefronts would go through at full tiles and
+  // the longest run of blocks (odd numbers of blocks deal out unevenly), 65 % with four wavefronts a tile, 75 % with two (4096 ->
+  // 4096 at 700, 64 x 128 by two, 69 %: 26.9 / 27.9), and of few blocks two wavefronts have to get the same number or nearly
+  // (2176 -> 2560 at 2000, 10 of 17 blocks in the longer run: 28.2 / 29.1).  Up to 64 tokens it is the stream of the weights that counts, and more wavefronts
+  // ask for it (2048 -> 16384 at 33: 12.7 / 13.3).
+  if (M > 64 && KB >= 16) {
+    const long long work = 4ll * ((M + 63) / 64) * (N / 64) * KB;
+    auto one_round = [&](int rt, int ct, int ks) {
+      const long long tiles = (long long)((M + 32 * rt - 1) / (32 * rt)) * ((N / 32 + ct - 1) / ct);
+      const int run = 2 * (((KB + 1) / 2 + ks - 1) / ks);
+      return tiles * ks <= 1024 && 20 * work >= (ks == 4 ? 13 : 15) * 1024ll * rt * ct * run && (ks == 4 || KB >= 24 || 10 * KB >= 9 * ks * run);
+    };
+#define W8_WIDE(RT, CT, KS) if (one_round(RT, CT, KS)) return launch_wide<RT, CT, KS>(x8, sx, MP, w8, sw, bias, y, M, N, K, stream)
+    W8_WIDE(2, 3, 4);
+    W8_WIDE(2, 4, 4);
+    W8_WIDE(2, 5, 4);
+    W8_WIDE(4, 3, 4);
+    W8_WIDE(2, 4, 2);
+    W8_WIDE(2, 5, 2);
+    W8_WIDE(4, 3, 2);
+#undef W8_WIDE
+  }
   if (MT * NT < (KB <= 2 ? 128 : KB <= 5 ? 160 : 200)) {
     // Of the small variants the one with the most work per wavefront that still brings at least 1024 wavefronts,
     // one per SIMD (the product of 5120 -> 5120 at 1 token 6.0 us, 64 8.5, 256 16.1, 512 23.8, 1024 46).

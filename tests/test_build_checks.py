@@ -199,7 +199,9 @@ EXPECTED = {
     "k_bwd.hip": {r"bwd_dq_kernelILi\dELi1": (4, 48), r"bwd_dq_kernelILi\dELi2": (4, 96), r"bwd_dkv_kernelILi1": (6, 64),
                   r"bwd_dq_dkv_kernel": (6, 64 + 48)},
     "k_w8a8.hip": {r"w8a8_gemm_kernelE": (1, 96), r"w8a8_gemm_splitk_kernelILi2ELi2": (3, 16),
-                   r"w8a8_gemm_splitk_kernelILi1ELi2": (2, 8), r"w8a8_gemm_splitk_kernelILi1ELi1": (2, 4)},
+                   r"w8a8_gemm_splitk_kernelILi1ELi2": (2, 8), r"w8a8_gemm_splitk_kernelILi1ELi1": (2, 4),
+                   r"w8a8_gemm_wide_kernelILi2ELi3": (1, 48), r"w8a8_gemm_wide_kernelILi2ELi4": (2, 64),
+                   r"w8a8_gemm_wide_kernelILi2ELi5": (2, 80), r"w8a8_gemm_wide_kernelILi4ELi3": (2, 96)},
 }
 
 

@@ -103,6 +103,23 @@ def test_linear_layer_on_both_sides_of_the_tile_rule(M, K, N, with_bias):
     assert torch.linalg.norm(y - ref) / torch.linalg.norm(ref) < 3e-3
 
 
+@pytest.mark.parametrize("with_bias", [True, False])
+@pytest.mark.parametrize("M, K, N", [
+    (1025, 2048, 1024),   # 64 x 96: the last tile of a row reaches 32 outputs past the end, one token in the last row of tiles
+    (1090, 4224, 1152),   # the same with 33 feature blocks: the last wavefront has one that does not exist
+    (200, 2048, 8064),    # 64 x 128
+    (1200, 2048, 1792),   # 64 x 160, the last tile of a row reaches 128 outputs past the end
+    (2050, 2048, 1408),   # 128 x 96
+    (257, 2048, 12288),   # 64 x 128 by two wavefronts
+    (833, 3968, 5120),    # 64 x 160 by two, 31 blocks
+    (3000, 3968, 1920),   # 128 x 96 by two
+    (65, 2048, 16384),    # the fewest tokens
+])
+def test_linear_layer_in_wide_tiles(M, K, N, with_bias):
+    """Middling sizes with long contractions; the bound is that of the test above."""
+    test_linear_layer_on_both_sides_of_the_tile_rule(M, K, N, with_bias)
+
+
 @pytest.mark.parametrize("block_q", [64, 128])
 @pytest.mark.parametrize("Tq", [1, 8, 23, 24])
 def test_sums_of_short_heads_stored_directly_have_the_same_bits(Tq, block_q):
