@@ -43,12 +43,6 @@ constexpr int LA_B_ROW = LA_COLS * 2;            // 256 bytes per staged hz row
 constexpr int LA_B_BYTES = LA_KT * LA_B_ROW + (LA_KT / 8 - 1) * 64;
 constexpr int LA_OUT_PITCH = 64 * 2 + 16;         // bytes per row of 64 results on their way out
 constexpr int LA_B_STAGE = ((LA_B_BYTES > LA_WAVES * 32 * LA_OUT_PITCH ? LA_B_BYTES : LA_WAVES * 32 * LA_OUT_PITCH) + 255) / 256 * 256;
-// Heads of at most this many query blocks store their results straight from the registers: one wavefront has a row tile, and the
-// way through LDS costs it more than whole lines save.  Query blocks (of 64; the last of 128), heads, us for whole calls,
-// forward and backward from a saved state, through LDS / directly: 8, 40 62.8 / 58.7 and 159.4 / 151.4; 16, 12 41.8 / 40.5 and
-// 108.2 / 106.6; 24, 40 84.0 / 80.6 and 265.7 / 258.1; 36, 40 117.6 / 115.6 but 389.8 / 394.2; 40, 40 129.2 / 124.7 but 451.0 /
-// 456.4 (the sums' reader pays for the partial lines); 30, 40 177.6 / 178.7 and 526.1 / 528.0.  The product alone at 64, 40: 57 / 75.
-constexpr int LA_DIRECT_ROWS = 24;
 constexpr int LA_M_PIECES = 2 * LA_KSUB;         // 1 KiB pieces of mask words per tile
 static_assert(HZ_ELEMS % LA_COLS == 0, "the stripes tile a summary exactly");
 static_assert(LA_M_PIECES == LA_WAVES && 8 * LA_KSUB % LA_WAVES == 0, "every wavefront copies the same number of pieces");
@@ -314,7 +308,7 @@ __global__ void __launch_bounds__(LA_WAVES * 64, 2) lin_accumulate_kernel(const 
   // The tiles were accumulated transposed (summary entries along the MFMA rows, query blocks
   // along its columns), so a lane owns ONE query block and runs of 4 consecutive entries of
   // its summary.  They leave through the wavefront's quarter of stage 2, 32 rows of 64 entries at a time, as whole
-  // 128-byte lines; straight from the registers (short heads) they are 16-byte pieces of 32 rows per store.
+  // 128-byte lines.
   // (a wavefront with fewer row tiles than NMT has accumulated a neighbour's rows in the spare
   // tiles; it does not store them)
   const int first_row = row0 + wrow, rows = min(32 * my_tiles, Tq - first_row);   // this wavefront's (none: <= 0)
@@ -326,22 +320,6 @@ __global__ void __launch_bounds__(LA_WAVES * 64, 2) lin_accumulate_kernel(const 
   }
   unsigned ln = lane;
   asm volatile("" : "+v"(ln));   // (the addresses below are formed per item: kept through the loop they cost registers that it has not got)
-  if constexpr (NMT == 1) {
-    if (Tq <= LA_DIRECT_ROWS) {  // (uniform) 8 bytes per lane, the lane halves completing 16
-      if ((int)(ln & 31) < rows) {
-        char* const dst = out + (ln & 31) * (HZ_ELEMS * 2) + 8 * (ln >> 5);
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            const v16f& a = acc[0][nt];
-            *(uint2*)(dst + (32 * nt + 8 * g) * 2) = make_uint2(pack_bf16x2(a[4 * g], a[4 * g + 1]), pack_bf16x2(a[4 * g + 2], a[4 * g + 3]));
-          }
-      }
-      stored = rows > 0 ? 16 : 0;
-      return;
-    }
-  }
   unsigned char* const mine = hz2 + w * (32 * LA_OUT_PITCH);
   const unsigned out_off = (ln >> 3) * (unsigned)(HZ_ELEMS * 2) + (ln & 7) * 16u;
   unsigned char* const put = mine + (ln & 31) * LA_OUT_PITCH + (ln >> 5) * 8;
@@ -379,6 +357,123 @@ __global__ void __launch_bounds__(LA_WAVES * 64, 2) lin_accumulate_kernel(const 
   }  // work items
 }
 
+// The same sums for short heads (at most LS_MAX_ROWS query blocks and LS_MAX_KEYS key blocks): there a stripe is one or two staged
+// tiles, and the kernel above waits for memory at every item, with three barriers around two dozen products.  Here
+// nothing is staged: a wavefront takes 64 columns of all key blocks straight to registers, one dword (two adjacent columns)
+// per lane and row, and makes of eight rows' dwords the operands of two products, one of the even columns and one of
+// the odd; requested again for its next 64 columns as soon as they are consumed, so that a compute unit has up to 100 KB
+// under way without a barrier.  The mask operands of its 32 RT query blocks are made once per head.  The contraction goes in
+// the same steps in the same order (same bits).  A lane ends up with eight consecutive entries of a query block's summary:
+// 16-byte stores, the lane halves' side by side.  Bound by memory: 24 slices of 37 x 73 blocks 29.8 -> 22.1 us (87 MB), 4 of
+// 35 x 35 7.6 -> 6.4, 2 of 16 x 16 4.4 -> 3.4.
+// Where the line lies (slices of query x key blocks, whole forward calls in us, staged / this): 40 of 16 x 16 65.7 / 54.7, of 8 x
+// 16 63.6 / 52.5, of 48 x 48 137.1 / 132.0, of 32 x 64 171.5 / 166.4, of 40 x 80 224.7 / 221.4, 4 of 40 x 80 53.4 / 51.9; but (in an
+// instance for more) 40 of 48 x 96 269.7 / 270.4, 24 of 56 x 112 202.6 / 206.9, 40 of 64 x 64 187.2 / 194.8.
+constexpr int LS_MAX_ROWS = 48, LS_MAX_KEYS = 80;
+constexpr int LS_COLS = 64;
+constexpr int ls_waves(int ksteps, int rt) { return ksteps == 4 || rt == 1 ? 3 : 2; }   // wavefronts per SIMD that its registers leave room for
+static_assert(HZ_ELEMS % (4 * LS_COLS) != 0 && HZ_ELEMS % LS_COLS == 0, "64 columns at a time, a head's last four wavefronts not all busy");
+template <int KSTEPS, int RT, bool RIDERS>
+__global__ void __launch_bounds__(256, ls_waves(KSTEPS, RT)) lin_short_kernel(const uint32_t* __restrict__ mbits, const bf16_t* __restrict__ hz, int Tq, int Tk,
+                                                           int BH, bf16_t* __restrict__ HZ, int rider_blocks, LinRiders riders) {
+  const int t = threadIdx.x, lane = t & 63, l32 = lane & 31, hf = lane >> 5, w = __builtin_amdgcn_readfirstlane(t >> 6);
+  if constexpr (RIDERS) {
+    __shared__ float4 sums[16][16];
+    if ((int)blockIdx.x < rider_blocks) {
+      if (riders.mbits_t) transpose_bits(mbits, Tq, Tk, BH, riders.mbits_t, blockIdx.x, rider_blocks);
+      else reduce_block(riders.reduce, blockIdx.x, sums);
+      return;
+    }
+  } else {
+    rider_blocks = 0;
+  }
+  constexpr int GROUPS = HZ_ELEMS / LS_COLS, QUADS = (GROUPS + 3) / 4;   // of four wavefronts side by side
+  const int KT32 = la_k_tiles(Tk), TqP = la_rows_padded(Tq);
+  const int total = BH * QUADS, wg = blockIdx.x - rider_blocks, wgs = gridDim.x - rider_blocks;
+  const int first = (int)((long long)total * wg / wgs), end = (int)((long long)total * (wg + 1) / wgs);
+  const unsigned lane_off = (unsigned)(8 * hf * (HZ_ELEMS * 2) + 4 * l32);
+  uint32_t x[KSTEPS][8];             // rows 16 ks + 8 hf + m of the columns under way
+  v8bf mask[RT][KSTEPS];
+  auto column = [&](int item) { return min(4 * (item % QUADS) + w, GROUPS - 1); };   // (past the end the last one again, not stored)
+  auto request = [&](int item, int ks) __attribute__((always_inline)) {
+    const char* from = (const char*)(hz + (size_t)(item / QUADS) * Tk * HZ_ELEMS) + column(item) * (LS_COLS * 2);
+    // (the addresses are formed per load, a row's in scalar registers: as loop invariants they took 64 vector registers)
+    if (16 * ks + 16 <= Tk) {        // (uniform)
+#pragma unroll
+      for (int m = 0; m < 8; ++m) {
+        const char* row = from + (size_t)(16 * ks + m) * (HZ_ELEMS * 2);
+        asm volatile("" : "+s"(row));
+        x[ks][m] = *(const uint32_t*)(row + lane_off);
+      }
+    } else {                         // (rows past Tk repeat the last one: their mask bits are 0)
+      int first_row = 16 * ks + 8 * hf;
+      asm volatile("" : "+v"(first_row));
+#pragma unroll
+      for (int m = 0; m < 8; ++m) x[ks][m] = *(const uint32_t*)(from + ((unsigned)min(first_row + m, Tk - 1) * (unsigned)(HZ_ELEMS * 2) + 4u * l32));
+    }
+  };
+  int have = -1;                     // whose mask operands these are
+  if (first < end) {
+#pragma unroll
+    for (int ks = 0; ks < KSTEPS; ++ks)
+      if (16 * ks < Tk) request(first, ks);
+  }
+  for (int item = first; item < end; ++item) {
+    const int bh = item / QUADS;
+    if (bh != have) {                // (uniform)
+      have = bh;
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) {
+        const uint32_t* words = mbits + (size_t)bh * KT32 * TqP + 32 * rt + l32;
+#pragma unroll
+        for (int k2 = 0; k2 < KSTEPS / 2; ++k2) {
+          const uint32_t word = 32 * k2 < Tk ? words[(size_t)k2 * TqP] : 0u;
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const uint32_t byte = word >> (16 * h + 8 * hf);
+            union { uint32_t u[4]; v8bf v; } b;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) b.u[e] = ((byte >> (2 * e)) & 1u) * 0x3f80u + ((byte >> (2 * e + 1)) & 1u) * 0x3f800000u;
+            mask[rt][2 * k2 + h] = b.v;
+          }
+        }
+      }
+    }
+    v16f acc[RT][2];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) acc[rt][0] = acc[rt][1] = v16f{};
+    const int next = min(item + 1, end - 1);
+#pragma unroll
+    for (int ks = 0; ks < KSTEPS; ++ks) {
+      if (16 * ks >= Tk) break;      // (uniform)
+      union { uint32_t u[4]; v8bf v; } even, odd;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        even.u[e] = __builtin_amdgcn_perm(x[ks][2 * e + 1], x[ks][2 * e], 0x05040100u);
+        odd.u[e] = __builtin_amdgcn_perm(x[ks][2 * e + 1], x[ks][2 * e], 0x07060302u);
+      }
+      request(next, ks);
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) {
+        acc[rt][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(even.v, mask[rt][ks], acc[rt][0], 0, 0, 0);
+        acc[rt][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(odd.v, mask[rt][ks], acc[rt][1], 0, 0, 0);
+      }
+    }
+    if (4 * (item - bh * QUADS) + w < GROUPS) {
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) {
+        const int row = 32 * rt + l32;
+        if (row >= Tq) continue;
+        char* dst = (char*)(HZ + ((size_t)bh * Tq + row) * HZ_ELEMS) + column(item) * (LS_COLS * 2) + 16 * hf;
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          *(uint4*)(dst + 32 * g) = uint4{pack_bf16x2(acc[rt][0][4 * g], acc[rt][1][4 * g]), pack_bf16x2(acc[rt][0][4 * g + 1], acc[rt][1][4 * g + 1]),
+                                          pack_bf16x2(acc[rt][0][4 * g + 2], acc[rt][1][4 * g + 2]), pack_bf16x2(acc[rt][0][4 * g + 3], acc[rt][1][4 * g + 3])};
+      }
+    }
+  }
+}
+
 size_t marginal_bits_t_bytes(const Problem& p) {
   return (size_t)p.BH * la_k_tiles(p.Tq) * la_rows_padded(p.Tk) * 4;
 }
@@ -405,6 +500,16 @@ void launch_lin_accumulate(const Problem& p, const uint32_t* mbits, const bf16_t
   if (riders.mbits_t) rb = (int)std::min<long long>(128, ((long long)p.BH * la_k_tiles(p.Tk) * ((p.Tq + 63) / 64) + LA_WAVES - 1) / LA_WAVES);
   else rb = reduce_blocks(riders.reduce);
   rb = (rb + 7) & ~7;
+  if (p.Tq <= LS_MAX_ROWS && p.Tk <= LS_MAX_KEYS) {
+    const int rt = p.Tq <= 32 ? 1 : 2, ksteps = p.Tk <= 64 ? 4 : 6, quads = (HZ_ELEMS / LS_COLS + 3) / 4;
+    const unsigned wgs = (unsigned)std::min<long long>(ls_waves(ksteps, rt) * compute_units(), (long long)p.BH * quads);
+#define LS_GO(KSTEPS, RT) { if (rb > 0) lin_short_kernel<KSTEPS, RT, true><<<wgs + rb, 256, 0, stream>>>(mbits, hz, p.Tq, p.Tk, p.BH, HZ, rb, riders); \
+                            else lin_short_kernel<KSTEPS, RT, false><<<wgs, 256, 0, stream>>>(mbits, hz, p.Tq, p.Tk, p.BH, HZ, 0, riders); }
+    if (ksteps == 4) { if (rt == 1) LS_GO(4, 1) else LS_GO(4, 2) }
+    else { if (rt == 1) LS_GO(6, 1) else LS_GO(6, 2) }
+#undef LS_GO
+    return;
+  }
   if (rb > 0) lin_accumulate_kernel<true><<<grid + rb, LA_WAVES * 64, 0, stream>>>(mbits, hz, p.Tq, p.Tk, groups, HZ, rb, p.BH, riders);
   else lin_accumulate_kernel<false><<<grid, LA_WAVES * 64, 0, stream>>>(mbits, hz, p.Tq, p.Tk, groups, HZ, 0, p.BH, riders);
 }

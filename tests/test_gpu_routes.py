@@ -138,6 +138,24 @@ def test_sums_of_short_heads_stored_directly_have_the_same_bits(Tq, block_q):
     assert torch.equal(few, more[:, :, :N])
 
 
+@pytest.mark.parametrize("Tq, block_q", [(1, 128), (7, 64), (32, 64), (33, 64), (33, 128), (40, 128), (41, 128), (48, 64), (49, 64)])
+def test_sums_of_short_heads_and_of_long_ones_have_the_same_bits(Tq, block_q):
+    """Heads of up to 80 key blocks and 48 query blocks go from memory to registers, others are staged: the same blocks in
+    front of more tokens whose key blocks nobody holds as marginal give the same rows."""
+    H, N, longer = 3, Tq * block_q - 5, 87 * 64 + 9
+    q, k, v = _qkv(H, longer)
+    g = torch.Generator(device="cuda").manual_seed(Tq)
+    Tk, whole = N // 64, (longer + 63) // 64        # (of the short head's last, ragged key block nothing is marginal)
+    mask = torch.full((1, H, (longer + block_q - 1) // block_q, whole), -1, dtype=torch.int8, device="cuda")
+    mask[:, :, :Tq, :Tk] = torch.randint(-1, 2, (1, H, Tq, Tk), generator=g, device="cuda", dtype=torch.int8)
+    short = [x[:, :, :N].contiguous() for x in (q, k, v)]
+    few = sla.sla_linear_attn_fwd(*short, mask[:, :, :Tq, :(N + 63) // 64].contiguous(), block_q, 64, proj_w=_weight(0))
+    more = sla.sla_linear_attn_fwd(q, k, v, mask, block_q, 64, proj_w=_weight(0))
+    assert torch.isfinite(few).all()
+    assert Tk == 1 or few.abs().max() > 0
+    assert torch.equal(few, more[:, :, :N])
+
+
 @pytest.mark.parametrize("H, N, block_q, rc, rm", [
     (9, 4033, 128, 0.1, 0.2),    # 9 x 64 key blocks: just more than the chip holds at a time, all in the order of their lists' lengths
     (41, 1000, 64, 0.2, 0.4),    # 41 x 16, a last group of eight that is short
