@@ -106,6 +106,38 @@ __device__ __forceinline__ int partner_i32(int x) {
   return (threadIdx.x & 32) ? r[0] : r[1];
 }
 
+// Sums and maxima over the lanes of a wavefront on the vector ALU (shuffles go through LDS).  Over a lane's row of 16, by
+// rotations: the same pairs in the same order as lane ^ 8, ^ 4, ^ 2, ^ 1.
+template <int N>
+__device__ __forceinline__ float row_rotated(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x120 + N, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float row_sum(float x) {
+  x += row_rotated<8>(x);
+  x += row_rotated<4>(x);
+  x += row_rotated<2>(x);
+  return x + row_rotated<1>(x);
+}
+__device__ __forceinline__ float row_max(float x) {
+  x = fmaxf(x, row_rotated<8>(x));
+  x = fmaxf(x, row_rotated<4>(x));
+  x = fmaxf(x, row_rotated<2>(x));
+  return fmaxf(x, row_rotated<1>(x));
+}
+// Over the four rows (lane ^ 16, then ^ 32).
+__device__ __forceinline__ float rows_sum(float x) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_int(x), __float_as_int(x), false, false);
+  x = __int_as_float(a[0]) + __int_as_float(a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_int(x), __float_as_int(x), false, false);
+  return __int_as_float(b[0]) + __int_as_float(b[1]);
+}
+__device__ __forceinline__ float rows_max(float x) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_int(x), __float_as_int(x), false, false);
+  x = fmaxf(__int_as_float(a[0]), __int_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_int(x), __float_as_int(x), false, false);
+  return fmaxf(__int_as_float(b[0]), __int_as_float(b[1]));
+}
+
 // ---------------------------------------------------------------------------
 // Fragment order of the quantised K / V tiles (one 8 KiB record per key block).
 //

@@ -13,8 +13,10 @@
 //    operand directly from registers (the contraction order of the second product is
 //    permuted to match, for both operands).
 //
-// One workgroup (4 wavefronts) per (b,h,j).  HBM-bound: reads 32 KiB, writes 16 KiB of
-// codes and 33 KiB of summaries per block.
+// One workgroup (4 wavefronts) per (b,h,j): reads 32 KiB, writes 16 KiB of codes and 33 KiB of summaries.  With the staged codes
+// and phi(K) free of bank conflicts (a row's codes met in four banks) and reductions on the vector ALU instead of through LDS the
+// launch, selection included, takes 699 us at 40 x 75600 tokens (before: 816), 5.5 TB/s, what a large copy gets; 102 at 12 x 32760
+// (122), 29.7 at 24 x 4617 (41.4); there, with 6 to 8 wavefronts' worth of instructions per SIMD, by issuing them.
 #include "classify.h"
 #include "delta.h"
 
@@ -28,6 +30,15 @@ struct MidArgs {
 };
 
 constexpr int STAGE_STRIDE = 2 * D + 16;  // bytes per staged hz row (padded against bank conflicts)
+
+// Where bytes of a K or V record (at offset o) and 16-byte chunk q of phi(K)^T are staged in LDS: the chunks are permuted
+// within groups of 8 and 16, or the lanes that write a row's codes, or the same row of 16 channels, would meet in four banks
+// of 64 (16 lanes in each).
+__device__ __forceinline__ int staged_code(int o) {
+  const int p = o >> 4;
+  return o ^ (((((p >> 4) ^ (p >> 6)) & 1) | ((p >> 5) & 1) << 1 | ((p >> 7) & 1) << 2) << 4);
+}
+__device__ __forceinline__ int staged_phi(int q) { return (q ^ ((q >> 4) & 15)) << 4; }
 
 // The statistics of slice bh joined over its (at most MEAN_RUNS) key blocks: stat[c] = mean of K, stat[128 + c] = max|V|.  The
 // sums are finalize_block's, in its order.
@@ -168,7 +179,7 @@ __device__ __forceinline__ void prep_block(const PrepArgs& P, int blk) {
         kt[r][e] = (4 * m + r < valid) ? kf[r][e] - mu[e] : 0.f;
         amax = fmaxf(amax, fabsf(kt[r][e]));
       }
-    for (int o = 32; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o));
+    amax = rows_max(row_max(amax));
     if (lane == 0) wave_amax[w] = amax;
     __syncthreads();
     amax = fmaxf(fmaxf(wave_amax[0], wave_amax[1]), fmaxf(wave_amax[2], wave_amax[3]));
@@ -189,7 +200,7 @@ __device__ __forceinline__ void prep_block(const PrepArgs& P, int blk) {
                                                 __builtin_amdgcn_perm(b[1], b[0], 0x0c0c0400u), 0x05040100u);
       const uint32_t hi = __builtin_amdgcn_perm(__builtin_amdgcn_perm(b[7], b[6], 0x0c0c0400u),
                                                 __builtin_amdgcn_perm(b[5], b[4], 0x0c0c0400u), 0x05040100u);
-      *(uint2*)(kq + kfrag_offset(4 * m + r, cg * 8)) = make_uint2(lo, hi);
+      *(uint2*)(kq + staged_code(kfrag_offset(4 * m + r, cg * 8))) = make_uint2(lo, hi);
     }
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
@@ -206,15 +217,15 @@ __device__ __forceinline__ void prep_block(const PrepArgs& P, int blk) {
       }
       int code = cvt_pk_e4m3(x[0], x[1], 0, false);
       code = cvt_pk_e4m3(x[2], x[3], code, true);
-      *(int*)(vq + vfrag_offset(4 * m, cg * 8 + e)) = code;
+      *(int*)(vq + staged_code(vfrag_offset(4 * m, cg * 8 + e))) = code;
     }
     __syncthreads();
     const size_t rec = ((size_t)bh * Tk + j) * KV_FRAG_BYTES;
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       const int o = (u * 256 + t) * 16;
-      *(uint4*)(k8 + rec + o) = *(const uint4*)(kq + o);
-      *(uint4*)(v8 + rec + o) = *(const uint4*)(vq + o);
+      *(uint4*)(k8 + rec + o) = *(const uint4*)(kq + staged_code(o));
+      *(uint4*)(v8 + rec + o) = *(const uint4*)(vq + staged_code(o));
     }
   }
   if (!want_linear) return;
@@ -228,14 +239,14 @@ __device__ __forceinline__ void prep_block(const PrepArgs& P, int blk) {
       float mx = kf[r][0];
 #pragma unroll
       for (int e = 1; e < 8; ++e) mx = fmaxf(mx, kf[r][e]);
-      for (int o = 8; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+      mx = row_max(mx);
       float s = 0.f;
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         ph[r][e] = __builtin_amdgcn_exp2f((kf[r][e] - mx) * LOG2E);
         s += ph[r][e];
       }
-      for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o);
+      s = row_sum(s);
       const float inv = ok ? 1.0f / s : 0.f;
 #pragma unroll
       for (int e = 0; e < 8; ++e) ph[r][e] *= inv;
@@ -257,10 +268,9 @@ __device__ __forceinline__ void prep_block(const PrepArgs& P, int blk) {
     for (int e = 0; e < 8; ++e) {
       const int c = cg * 8 + e;
       const uint2 pk = make_uint2(pack_bf16x2(ph[0][e], ph[1][e]), pack_bf16x2(ph[2][e], ph[3][e]));
-      *(uint2*)(phit + ((s2 * 128 + c) * 2 + hf) * 16 + (g & 1) * 8) = pk;
+      *(uint2*)(phit + staged_phi((s2 * 128 + c) * 2 + hf) + (g & 1) * 8) = pk;
       float zs = ph[0][e] + ph[1][e] + ph[2][e] + ph[3][e];  // 4 rows of this thread, then the 4 row groups of the wavefront
-      zs += __shfl_xor(zs, 16);
-      zs += __shfl_xor(zs, 32);
+      zs = rows_sum(zs);
       if (lane < 16) zred[w * D + c] = zs;
     }
 #pragma unroll
@@ -300,7 +310,7 @@ __device__ __forceinline__ void prep_block(const PrepArgs& P, int blk) {
     for (int e = 0; e < 8; ++e) a[e] = (__bf16)d1[s2 >> 1][8 * (s2 & 1) + e];
 #pragma unroll
     for (int ct = 0; ct < 4; ++ct) {
-      const v8bf b = *(const v8bf*)(phit + ((s2 * 128 + 32 * ct + l32) * 2 + hfl) * 16);
+      const v8bf b = *(const v8bf*)(phit + staged_phi((s2 * 128 + 32 * ct + l32) * 2 + hfl));
       d2[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, a, d2[ct], 0, 0, 0);
     }
   }
