@@ -5,7 +5,7 @@
 
 namespace sla {
 
-// select_row: one WAVEFRONT per (b,h,i) row; the row's scores live in registers (KPL per lane,
+// select_row: one WAVEFRONT per (b,h,i) row; the row's scores (score(j), j < Tk) live in registers (KPL per lane,
 // block j = lane + 64 m in register m) as order-preserving 32-bit keys.  The n_c-th and the
 // (n_c+n_m)-th largest keys are found exactly, bit by bit from the top: a bit of the threshold
 // is set when at least `rank` keys are >= the candidate with that bit set.  The counts come
@@ -20,8 +20,13 @@ __device__ __forceinline__ uint32_t order_bits(float f) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-template <int KPL>
-__device__ __forceinline__ void select_row(const SelectArgs& S, size_t row, const float* srow) {
+struct ScoresOf {
+  const float* row;
+  __device__ __forceinline__ float operator()(int j) const { return row[j]; }
+};
+template <int KPL, class Score>
+__device__ __forceinline__ void select_row(const SelectArgs& S, unsigned row_, Score score) {
+  const size_t row = row_;
   const int Tq = S.Tq, Tk = S.Tk, n_c = S.n_c, n_m = S.n_m;
   const int lane = threadIdx.x & 63;
   const unsigned long long lt = (1ull << lane) - 1ull;
@@ -29,7 +34,7 @@ __device__ __forceinline__ void select_row(const SelectArgs& S, size_t row, cons
 #pragma unroll
   for (int m = 0; m < KPL; ++m) {
     const int j = lane + 64 * m;
-    key[m] = j < Tk ? order_bits(srow[j]) : 0u;
+    key[m] = j < Tk ? order_bits(score(j)) : 0u;
   }
   // Subtract the row minimum and shift out the common leading zeros: order and ties are
   // unchanged, padding (key 0) ties with the minimum, and the search below only has to visit
@@ -43,11 +48,8 @@ __device__ __forceinline__ void select_row(const SelectArgs& S, size_t row, cons
         kmin = min(kmin, key[m]);
         kmax = max(kmax, key[m]);
       }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, o));
-      kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, o));
-    }
+    kmin = __builtin_amdgcn_readfirstlane(rows_reduce(row_reduce(kmin, OpMin{}), OpMin{}));
+    kmax = __builtin_amdgcn_readfirstlane(rows_reduce(row_reduce(kmax, OpMax{}), OpMax{}));
     const uint32_t span = kmax - kmin;
     const int lz = span ? __builtin_clz(span) : 0;
     low = span ? lz : 32;  // all keys equal: nothing to search
@@ -86,7 +88,7 @@ __device__ __forceinline__ void select_row(const SelectArgs& S, size_t row, cons
     if (n_m > 0) t2 -= __popcll(__ballot(key[m] > k2));
   }
 
-  const int bh = (int)(row / Tq), i = (int)(row % Tq);
+  const int bh = (int)(row_ / (unsigned)Tq), i = (int)(row_ - (unsigned)bh * (unsigned)Tq);
   const int KT = (Tk + 31) / 32, TqP = (Tq + 383) / 384 * 384 + 128;  // layout of the marginal bit matrix (see lin_accumulate)
   int eq1 = 0, eq2 = 0, nc = 0, nm = 0;  // running counts in ascending-j order
 #pragma unroll

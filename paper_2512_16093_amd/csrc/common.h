@@ -106,37 +106,35 @@ __device__ __forceinline__ int partner_i32(int x) {
   return (threadIdx.x & 32) ? r[0] : r[1];
 }
 
-// Sums and maxima over the lanes of a wavefront on the vector ALU (shuffles go through LDS).  Over a lane's row of 16, by
-// rotations: the same pairs in the same order as lane ^ 8, ^ 4, ^ 2, ^ 1.
-template <int N>
-__device__ __forceinline__ float row_rotated(float x) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x120 + N, 0xf, 0xf, true));
+// Reductions over the lanes of a wavefront on the vector ALU (shuffles go through LDS); every lane gets the result.  Over a
+// lane's row of 16, by rotations: the same pairs in the same order as lane ^ 8, ^ 4, ^ 2, ^ 1; over the four rows, lane ^ 16,
+// then ^ 32, by swapping rows.  T: a 32-bit type, op commutative.
+template <int N, class T>
+__device__ __forceinline__ T row_rotated(T x) {
+  return __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x120 + N, 0xf, 0xf, true));
 }
-__device__ __forceinline__ float row_sum(float x) {
-  x += row_rotated<8>(x);
-  x += row_rotated<4>(x);
-  x += row_rotated<2>(x);
-  return x + row_rotated<1>(x);
+template <class T, class Op>
+__device__ __forceinline__ T row_reduce(T x, Op op) {
+  x = op(x, row_rotated<8>(x));
+  x = op(x, row_rotated<4>(x));
+  x = op(x, row_rotated<2>(x));
+  return op(x, row_rotated<1>(x));
 }
-__device__ __forceinline__ float row_max(float x) {
-  x = fmaxf(x, row_rotated<8>(x));
-  x = fmaxf(x, row_rotated<4>(x));
-  x = fmaxf(x, row_rotated<2>(x));
-  return fmaxf(x, row_rotated<1>(x));
+template <class T, class Op>
+__device__ __forceinline__ T rows_reduce(T x, Op op) {
+  const int a = __builtin_bit_cast(int, x);
+  const auto p = __builtin_amdgcn_permlane16_swap(a, a, false, false);
+  const int b = __builtin_bit_cast(int, op(__builtin_bit_cast(T, (int)p[0]), __builtin_bit_cast(T, (int)p[1])));
+  const auto r = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+  return op(__builtin_bit_cast(T, (int)r[0]), __builtin_bit_cast(T, (int)r[1]));
 }
-// Over the four rows (lane ^ 16, then ^ 32).
-__device__ __forceinline__ float rows_sum(float x) {
-  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_int(x), __float_as_int(x), false, false);
-  x = __int_as_float(a[0]) + __int_as_float(a[1]);
-  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_int(x), __float_as_int(x), false, false);
-  return __int_as_float(b[0]) + __int_as_float(b[1]);
-}
-__device__ __forceinline__ float rows_max(float x) {
-  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_int(x), __float_as_int(x), false, false);
-  x = fmaxf(__int_as_float(a[0]), __int_as_float(a[1]));
-  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_int(x), __float_as_int(x), false, false);
-  return fmaxf(__int_as_float(b[0]), __int_as_float(b[1]));
-}
+struct OpAdd { __device__ __forceinline__ float operator()(float a, float b) const { return a + b; } };
+struct OpMax { template <class T> __device__ __forceinline__ T operator()(T a, T b) const { return max(a, b); } };
+struct OpMin { template <class T> __device__ __forceinline__ T operator()(T a, T b) const { return min(a, b); } };
+__device__ __forceinline__ float row_sum(float x) { return row_reduce(x, OpAdd{}); }
+__device__ __forceinline__ float row_max(float x) { return row_reduce(x, OpMax{}); }
+__device__ __forceinline__ float rows_sum(float x) { return rows_reduce(x, OpAdd{}); }
+__device__ __forceinline__ float rows_max(float x) { return rows_reduce(x, OpMax{}); }
 
 // ---------------------------------------------------------------------------
 // Fragment order of the quantised K / V tiles (one 8 KiB record per key block).

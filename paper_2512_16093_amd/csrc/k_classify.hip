@@ -78,7 +78,7 @@ __global__ void __launch_bounds__(256) pool_stats_kernel(const PoolArgs A) {
   if (part == 0) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      for (int o = 32; o > 0; o >>= 1) amax[h] = fmaxf(amax[h], __shfl_xor(amax[h], o));
+      amax[h] = rows_max(row_max(amax[h]));
       if ((t & 63) == 0) s_amax[h][t >> 6] = amax[h];
     }
   }
@@ -267,8 +267,8 @@ __global__ void __launch_bounds__(256, 2) scores_kernel(const ScoresArgs A) {
 
 template <int KPL>
 __global__ void __launch_bounds__(256) select_kernel(const SelectArgs S) {
-  const size_t row = (size_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (row < (size_t)S.rows) select_row<KPL>(S, row, S.scores + row * S.Tk);  // (no workgroup barrier: whole wavefronts may leave)
+  const unsigned row = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (row < (unsigned)S.rows) select_row<KPL>(S, row, ScoresOf{S.scores + (size_t)row * S.Tk});  // (no workgroup barrier: whole wavefronts may leave)
 }
 
 // ---------------------------------------------------------------------------

@@ -81,33 +81,40 @@ __device__ __forceinline__ void w_operands(const PrepArgs& P, int row, int col, 
     }
   }
 }
-// The four query blocks 4 blk .. 4 blk + 3 of a slice: their scores against all (at most 64 KPL) key blocks, formed as
-// scores_kernel forms them (the same products in the same order; a wavefront has a tile of 32 key blocks, 28 of the 32
-// rows of the product are copies), kept in LDS, then one row per wavefront selected from there.
-template <int KPL>
-__device__ __forceinline__ void classify_rows(const SelectArgs& S, const float* qbar, const float* kbar, int blk) {
-  __shared__ float sc[4][64 * KPL];
-  const int Tq = S.Tq, Tk = S.Tk, per = (Tq + 3) / 4, bh = blk / per, i0 = 4 * (blk - bh * per);
-  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, h = lane >> 5;
-  for (int jt = w; jt * 32 < Tk; jt += 4) {
-    const float4* ap = (const float4*)(qbar + ((size_t)bh * Tq + min(i0 + (l32 & 3), Tq - 1)) * D + 64 * h);
-    const float4* bp = (const float4*)(kbar + ((size_t)bh * Tk + min(jt * 32 + l32, Tk - 1)) * D + 64 * h);
-    v16f acc = {};
+// The four query blocks 4 blk .. 4 blk + 3 of a slice, one per wavefront: the scores against all (at most 64) key blocks, one per
+// lane, then the selection, without LDS.  scores_kernel's matrix product adds up channels t and 64 + t step by step, and
+// an fp32 product of the matrix pipe is a chain of fused operations: so are these, in the same order, bit for bit the same
+// (on 32 rows of which 28 were copies the product alone took 4096 cycles: training step of 4 x 2187 tokens 118.5 -> 114.0 us).
+__device__ __forceinline__ void classify_rows(const SelectArgs& S, const float* __restrict__ qbar, const float* __restrict__ kbar, int blk) {
+  const int Tq = S.Tq, Tk = S.Tk, per = (Tq + 3) / 4, bh = blk / per;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), i = 4 * (blk - bh * per) + w;
+  if (i >= Tq) return;               // (whole wavefront; no barriers here)
+  const unsigned row = (unsigned)(bh * Tq + i);
+  // (uniform, and written by an earlier launch: through the scalar unit)
+  const __attribute__((address_space(4))) float* qrow = (const __attribute__((address_space(4))) float*)(uintptr_t)(qbar + (size_t)row * D);
+  const float4* krow = (const float4*)(kbar + ((size_t)bh * Tk + min(lane, Tk - 1)) * D);
+  float sum = 0.f;
 #pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const float4 a = ap[u], b = bp[u];
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.x, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b.y, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, b.z, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, b.w, acc, 0, 0, 0);
+  for (int part = 0; part < 2; ++part) {
+    float4 lo[8], hi[8];             // channels 32 part .. + 31 and 64 on
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      lo[u] = krow[8 * part + u];
+      hi[u] = krow[16 + 8 * part + u];
     }
-    if (h == 0) {  // (accumulator registers 0..3 of the lower lane half: rows 0..3)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) sc[r][jt * 32 + l32] = acc[r] / 11.313708498984761f;
+    for (int u = 0; u < 8; ++u) {
+      const float b0[4] = {lo[u].x, lo[u].y, lo[u].z, lo[u].w}, b1[4] = {hi[u].x, hi[u].y, hi[u].z, hi[u].w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int c = 32 * part + 4 * u + e;
+        sum = __builtin_fmaf(qrow[c], b0[e], sum);
+        sum = __builtin_fmaf(qrow[64 + c], b1[e], sum);
+      }
     }
   }
-  __syncthreads();
-  if (i0 + w < Tq) select_row<KPL>(S, (size_t)bh * Tq + i0 + w, sc[w]);
+  const float score = sum / 11.313708498984761f;
+  select_row<1>(S, row, [&](int) { return score; });
 }
 
 // STATS (calls of few key blocks): nobody has joined the statistics over the slice yet or laid out W; every workgroup does
@@ -138,17 +145,22 @@ __device__ __forceinline__ void prep_block(const PrepArgs& P, int blk) {
   const bf16_t* vblk = v + b_ * lv.sb + h_ * lv.sh + (long long)j * BK * lv.sn;
 
   float kf[4][8];
-  uint4 vraw[4];  // V stays packed: it is quantised from these words and staged for product 1 as they are
+  uint4 kraw[4], vraw[4];  // V stays packed: it is quantised from these words and staged for product 1 as they are
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int row = 4 * m + r;
-    uint4 xk = make_uint4(0, 0, 0, 0);
-    vraw[r] = make_uint4(0, 0, 0, 0);
+    kraw[r] = vraw[r] = make_uint4(0, 0, 0, 0);
     if (row < valid) {
-      xk = *(const uint4*)(kblk + row * lk.sn + cg * 8);
+      kraw[r] = *(const uint4*)(kblk + row * lk.sn + cg * 8);
       vraw[r] = *(const uint4*)(vblk + row * lv.sn + cg * 8);
     }
-    const uint32_t wk[4] = {xk.x, xk.y, xk.z, xk.w};
+  }
+  if constexpr (STATS) {             // (under way together with the rows)
+    if (want_quant) slice_stats(P, bh, j == 0, zred);
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const uint32_t wk[4] = {kraw[r].x, kraw[r].y, kraw[r].z, kraw[r].w};
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       kf[r][2 * e] = bf16_lo(wk[e]);
@@ -159,7 +171,6 @@ __device__ __forceinline__ void prep_block(const PrepArgs& P, int blk) {
   if (want_quant) {
     const float *mu_k = P.mu_k + (size_t)bh * D, *amax_v = P.amax_v + (size_t)bh * D;
     if constexpr (STATS) {
-      slice_stats(P, bh, j == 0, zred);
       mu_k = zred;
       amax_v = zred + D;
       __syncthreads();
@@ -351,10 +362,12 @@ template <int PHI, int KPL, bool STATS>
 __global__ void __launch_bounds__(256, 4) select_prep_kernel(const MidArgs A) {
   int blk = blockIdx.x;
   if (blk < A.select_blocks) {
-    if constexpr (STATS) classify_rows<KPL>(A.S, A.P.qbar, A.P.kbar, blk);
-    else {
-      const size_t row = (size_t)blk * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-      if (row < (size_t)A.S.rows) select_row<KPL>(A.S, row, A.S.scores + row * A.S.Tk);
+    if constexpr (STATS) {
+      static_assert(KPL == 1, "a key block per lane");
+      classify_rows(A.S, A.P.qbar, A.P.kbar, blk);
+    } else {
+      const unsigned row = (unsigned)blk * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+      if (row < (unsigned)A.S.rows) select_row<KPL>(A.S, row, ScoresOf{A.S.scores + (size_t)row * A.S.Tk});
     }
     return;
   }
