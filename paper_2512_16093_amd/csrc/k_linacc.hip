@@ -12,7 +12,8 @@
 // from HBM once, and M0 travels as bits: one 32-bit word per (query block,
 // tile of 32 key blocks), 3 KiB per staged tile against 8 KiB of hz.  The bf16 A operand of a
 // wavefront is made from its mask byte through a 256-entry table in LDS (entry b = the eight
-// bf16 values 0.0 / 1.0 of the bits of b), one 16-byte LDS read per fragment.
+// bf16 values 0.0 / 1.0 of the bits of b), one 16-byte LDS read per fragment (two reads of a 16-entry
+// table whose entries never meet in a bank: 2 to 6 % slower).
 //
 // Workgroup = 4 wavefronts, two workgroups per CU (independent, so the two wavefronts of a
 // SIMD are not in step); in a full chunk wavefront w owns query blocks [96 w, 96 w + 96) x 128
@@ -38,9 +39,12 @@ constexpr int LA_ROWS = 384, LA_COLS = 128;      // workgroup tile
 constexpr int LA_WAVES = 4;
 constexpr int LA_M_ROWS = 512;                   // mask words staged per 32-block group (two 1 KiB pieces; 384 used)
 constexpr int LA_B_ROW = LA_COLS * 2;            // 256 bytes per staged hz row
-// each group of 8 staged rows starts 64 bytes after the previous one ends, so the two lane
-// halves (which read rows 8 apart) hit different banks
-constexpr int LA_B_BYTES = LA_KT * LA_B_ROW + (LA_KT / 8 - 1) * 64;
+// A row's sixteen 16-byte chunks are staged permuted, chunk c of row r at position c ^ la_swz(r): the 16 lanes of a transposing
+// read's group address four rows, which at 256 bytes apart met in the same banks (70 % of the LDS's cycles were conflicts and
+// the LDS busy for two thirds of the time: 40 slices of 591 x 1182 blocks 897 us, now 812, of 1182 x 1182 1793 / 1590, 12 of
+// 256 x 512 70.4 / 67.0).
+__device__ __forceinline__ int la_swz(int r) { return ((r & 3) << 2) | ((r >> 2) & 3); }
+constexpr int LA_B_BYTES = LA_KT * LA_B_ROW;
 constexpr int LA_OUT_PITCH = 64 * 2 + 16;         // bytes per row of 64 results on their way out
 constexpr int LA_B_STAGE = ((LA_B_BYTES > LA_WAVES * 32 * LA_OUT_PITCH ? LA_B_BYTES : LA_WAVES * 32 * LA_OUT_PITCH) + 255) / 256 * 256;
 constexpr int LA_M_PIECES = 2 * LA_KSUB;         // 1 KiB pieces of mask words per tile
@@ -157,9 +161,10 @@ __global__ void __launch_bounds__(LA_WAVES * 64, 2) lin_accumulate_kernel(const 
 
   const unsigned lane16 = (unsigned)lane * 16u;
   // this lane's address inside a B patch for the transposing reads: lane group g = lane / 16
-  // serves columns 16 (g % 2) .. +15 and staged rows 8 (g / 2) + (0..3) [+ 4 for the second read]
-  const int tr_off = (8 * (lane >> 5) + ((lane & 15) >> 2)) * LA_B_ROW + (lane >> 5) * 64 +
-                     (16 * ((lane >> 4) & 1) + 4 * (lane & 3)) * 2;
+  // serves columns 16 (g % 2) .. +15 and staged rows 8 (g / 2) + (0..3) [+ 4 for the second read, whose chunks are
+  // permuted by one more]; the column tile is flipped into the address
+  const int tr_row = 8 * (lane >> 5) + ((lane & 15) >> 2);
+  const int tr_off = tr_row * LA_B_ROW + (((2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ la_swz(tr_row)) << 4) + 8 * (lane & 1);
   __syncthreads();  // publishes the table
 
   // Persistent workgroups, two per compute unit: each takes work items (b,h, stripe, row chunk)
@@ -207,9 +212,9 @@ __global__ void __launch_bounds__(LA_WAVES * 64, 2) lin_accumulate_kernel(const 
 #pragma unroll
     for (int u = 0; u < 8 * LA_KSUB / LA_WAVES; ++u) {
       const int p = w + LA_WAVES * u;
-      const int j = min(kt * LA_KT + 4 * p + (lane >> 4), Tk - 1);  // rows past Tk repeat the last one (their mask bits are 0)
-      const unsigned off = (unsigned)j * (unsigned)(HZ_ELEMS * 2) + (unsigned)(lane & 15) * 16u;
-      la_copy16(hz_bh, off, hzs + p * 1024 + (p >> 1) * 64);
+      const int r = 4 * p + (lane >> 4), j = min(kt * LA_KT + r, Tk - 1);  // rows past Tk repeat the last one (their mask bits are 0)
+      const unsigned off = (unsigned)j * (unsigned)(HZ_ELEMS * 2) + (unsigned)((lane & 15) ^ la_swz(r)) * 16u;
+      la_copy16(hz_bh, off, hzs + p * 1024);
     }
     {
       const int sub = w >> 1, part = w & 1;  // one mask piece per wavefront
@@ -272,9 +277,9 @@ __global__ void __launch_bounds__(LA_WAVES * 64, 2) lin_accumulate_kernel(const 
       _Pragma("unroll") for (int nt = 0; nt < 4; ++nt) {                                                  \
         /* staged rows r0 + 8 hf + (0..7) of column 32 nt + l32, by two transposing reads */              \
         union { v4s h[2]; v8bf v; } u;                                                                    \
-        const int r0 = 32 * sub + 16 * ks, c0 = 64 * nt;                                                  \
-        u.h[0] = la_read_tr(&HZS[tr_off + r0 * LA_B_ROW + (r0 >> 3) * 64 + c0]);                          \
-        u.h[1] = la_read_tr(&HZS[tr_off + (r0 + 4) * LA_B_ROW + (r0 >> 3) * 64 + c0]);                    \
+        const int r0 = 32 * sub + 16 * ks;                                                                \
+        u.h[0] = la_read_tr(&HZS[(tr_off ^ (nt << 6)) + r0 * LA_B_ROW]);                                  \
+        u.h[1] = la_read_tr(&HZS[(tr_off ^ (nt << 6) ^ 16) + (r0 + 4) * LA_B_ROW]);                       \
         bop[nt] = u.v;                                                                                    \
       }                                                                                                   \
       _Pragma("unroll") for (int mt = 0; mt < NMT; ++mt)                                                  \
