@@ -389,9 +389,12 @@ struct FwdEpilogue {
 // busy, 52 GB past L2 in 12.2 ms); of 64 by the stream of K and V, 32 KB for every 64 x 64 scores: 128 GB past L2 in 16.7 ms =
 // 7.6 TB/s, what a plain reader of such tiles gets, with the pipe 44 % busy.  At 12 x 32760 the pipe is 57 and 50 % busy, 2.0
 // and 4.4 GB go past L2 in 0.82 and 0.95 ms: the exponentials beside the products.
-// The epilogue's H_i comes into the ring during the last step (with two wavefronts half of it; the rest behind the last step),
-// its other operands in one go, phi(Q) is left unnormalised where that cancels, rows leave whole: attention kernel 750 ->
-// 709 us at 12 x 32760 token-major with O^s saved; 4 x 2187, query blocks of 64 (19 us) no difference.
+// The epilogue's H_i comes into the ring behind the loop (with two wavefronts half of it, the rest when the last step's tiles are
+// consumed), its other operands in one go, phi(Q) is left unnormalised where that cancels, rows leave whole: attention kernel 750 ->
+// 709 us at 12 x 32760 token-major with O^s saved; 4 x 2187, query blocks of 64 (19 us) no difference.  Asked for inside the last
+// step, by a branch in the loop, H_i cost blocks of 64 with long lists more than it hid (whole call, in the loop / behind it /
+// without any of this: 40 x 32760 at 10 % 3570 / 3415 / 3544, at 20 % 6411 / 5950 / 6134; 12 x 32760 1081 / 1070 / 1108; blocks of
+// 128 at 30 % 6745 / 6705 / 6760).
 template <int NW, bool CODES, bool ST>
 __global__ void __launch_bounds__(NW * 64, 2) fwd_bf16_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                                                             const bf16_t* __restrict__ v, const int32_t* __restrict__ crit,
@@ -426,8 +429,8 @@ __global__ void __launch_bounds__(NW * 64, 2) fwd_bf16_kernel(const bf16_t* __re
   const float qscale = CODES ? QK_LOG2 * fe.code_dq[(size_t)bh * dm.Tq + i] : QK_LOG2;
   v16f lacc = v16f{};  // register 0: the running sum of P over the keys (see the ones operand below)
   const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void*)ring;
-  // The epilogue's H_i (four quarters of 8 KB, one per output tile): as many as fit come into half `half` of the ring during the
-  // last step, copied by all wavefronts.
+  // The epilogue's H_i (four quarters of 8 KB, one per output tile): as many as fit come into half `half` of the ring,
+  // copied by all wavefronts.
   constexpr int H_HALF = STEP_B / 8192;        // quarters there: 4 or 2
   const char* const h_rec = (const char*)(fe.HZ + ((size_t)bh * dm.Tq + i) * HZ_ELEMS);
   auto request_h = [&](int half, int first) __attribute__((always_inline)) {   // quarters first .. first + H_HALF - 1
@@ -449,11 +452,10 @@ __global__ void __launch_bounds__(NW * 64, 2) fwd_bf16_kernel(const bf16_t* __re
         cv.template tile<true>(key0 + 32 * kt, dm.N, lds0 + half * STEP_B + (KT + kt) * SWZ_TILE_B);   // (zero times an infinite V would not be zero)
       }
     };
-    // KT tiles of 32 keys from key0 on, in half `half` of the ring; next: the step behind this one starts there (< 0: none,
-    // the epilogue's operands come instead)
+    // KT tiles of 32 keys from key0 on, in half `half` of the ring; next: the step behind this one starts there (< 0: none)
     auto step = [&](int key0, float c2, int half, int next) __attribute__((always_inline)) {   // c2: score -> base-2 logit
       copies_barrier<0>();                     // this step's tiles have landed; those of the step before are consumed
-      if (next >= 0) request(next, half ^ 1); else request_h(half ^ 1, 0);
+      if (next >= 0) request(next, half ^ 1);
       // (a half of the ring is a multiple of the bits that the reads flip: added to the lane's offset)
       int no = n_off + half * STEP_B, to = t_off + half * STEP_B;
       asm volatile("" : "+v"(no), "+v"(to));
@@ -538,7 +540,7 @@ __global__ void __launch_bounds__(NW * 64, 2) fwd_bf16_kernel(const bf16_t* __re
     }
   }
   const int last_half = NW == 4 ? (dm.n_c - 1) & 1 : 1;   // of the ring, which the last step has read
-  if (dm.n_c <= 0) request_h(last_half ^ 1, 0);
+  request_h(last_half ^ 1, 0);                 // (the last step does not read that half, and everybody is past the one before)
   // What the epilogue needs of memory beside that, in one go: Q for phi(Q), two channels of Z_i and of the bias per lane.
   uint4 qraw[8];
   uint32_t z2 = 0, b2 = 0;
