@@ -241,3 +241,37 @@ def test_mean_of_k_keeps_its_order_of_summation(N):
     for r in range(64):
         total += runs[:, r]
     assert np.array_equal(mean.view(np.int32), (total / np.float32(N)).view(np.int32))
+
+
+@pytest.mark.parametrize("bq", [128, 64])
+def test_linear_term_of_query_tokens_of_any_magnitude(bq):
+    """softmax in phi(Q) subtracts a token's maximum before anything is scaled: at every finite magnitude its largest channel has
+    the largest weight, in the low-bit kernel (the stage alone: no INT8 scores of such tokens) and in the unquantised forward
+    pass (keys of 1e-36: its scores stay in range)."""
+    cfg = synth.custom_config(1, 2, (5, 10, 20), block_q=bq, topk_ratio=0.25, marginal_ratio=0.5, cfg_id=712)   # N = 1000
+    q, k, v = synth.make_qkv(cfg)
+    rng = np.random.default_rng(bq)
+    size = 10.0 ** rng.uniform(0, 30, (1, cfg.H, cfg.N, 1))
+    size[:, :, 7::bq] = 2.0 ** rng.uniform(126, 127.99, size[:, :, 7::bq].shape)   # one token per query block (its mean has to stay finite)
+    q = torch.from_numpy(rng.uniform(-1, 1, q.shape) * size).to(torch.bfloat16)
+    W = synth.make_proj(cfg)
+    args = (bq, 64, cfg.topk_ratio, cfg.marginal_ratio)
+    for name, keys in (("stage", k), ("unquantised", (k.float() * 1e-36).to(torch.bfloat16))):
+        qd, kd, vd, Wd = pu.to_dev(q, keys, v, W)
+        if name == "stage":
+            mask = torch.from_numpy(rng.integers(-1, 2, (1, cfg.H, -(-cfg.N // bq), -(-cfg.N // 64)), dtype=np.int8)).cuda()
+            out = sla.sla_linear_attn_fwd(qd, kd, vd, mask, bq, 64, proj_w=Wd)
+        else:
+            mask = sla.sla_classify_blocks(qd, kd, *args, want_scores=False)[0]
+            out = sla.sla_attention_fwd(qd, kd, vd, *args, proj_w=Wd, quant_mode=sla.QUANT_NONE)
+        for h in range(cfg.H):
+            Q, K, V = (synth.as_f64(x[0, h]) for x in (q, keys, v))
+            m = mask[0, h].cpu().numpy()
+            if name == "stage":
+                ref = so.linear_branch(Q, K, V, m, bq, 64) @ synth.as_f64(W).T
+            else:
+                ref = so.sla_forward_head(Q, K, V, *args, proj_w=synth.as_f64(W), quant=so.QUANT_NONE, mask=m)["out"]
+            got = out[0, h].float().cpu().numpy().astype(np.float64)
+            pu.check_output(got, ref, "%s head %d" % (name, h))
+            # (bf16 results and summaries: 1.7e-3 of rounding each; 5e-3 as in the parity tests)
+            assert np.linalg.norm(got - ref) / np.linalg.norm(ref) <= 5e-3, name
