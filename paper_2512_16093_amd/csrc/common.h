@@ -192,8 +192,10 @@ __device__ __forceinline__ uint4 pair_order(const uint4& v) {
 
 // phi(Q) of a token as operands of the linear term O_l = phi(Q) H / (phi(Q) . Z), from its channels as they are: operand ks
 // is those of raw[ks].  The quotient does not change when a token's phi(Q) is scaled, so softmax is left without its sum
-// and its division (a third of the instructions: the attention kernels' epilogues are bound by issuing them).  The maximum
-// is subtracted before anything is rounded (scaled by log2(e) first, its rounding alone passed the exponent range at |Q| of 2^31).
+// and its division (a third of the instructions: the attention kernels' epilogues are bound by issuing them).  Its weights are
+// 2^-7 times exp(x - max): they sum to at most 1, so that phi(Q) H stays finite wherever H is (without the 2^-7, values from
+// 1e36 on overflowed), and the maximum is subtracted before anything is rounded (scaled by log2(e) first, its rounding alone
+// passed the exponent range at |Q| of 2^31).
 __device__ __forceinline__ void phi_q_operands(const uint4 (&raw)[8], int phi, uint4 (&b)[8]) {
   float x[64];
 #pragma unroll
@@ -208,7 +210,7 @@ __device__ __forceinline__ void phi_q_operands(const uint4 (&raw)[8], int phi, u
     float mx = fmaxf(fmaxf(m[0], m[1]), fmaxf(m[2], m[3]));
     mx = fmaxf(mx, partner_f32(mx));
 #pragma unroll
-    for (int e = 0; e < 64; ++e) x[e] = __builtin_amdgcn_exp2f((x[e] - mx) * LOG2E);
+    for (int e = 0; e < 64; ++e) x[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(x[e] - mx, LOG2E, -7.f));
   } else if (phi == 1) {
 #pragma unroll
     for (int e = 0; e < 64; ++e) x[e] = x[e] > 0.f ? x[e] + 1.0f : __builtin_amdgcn_exp2f(x[e] * LOG2E);

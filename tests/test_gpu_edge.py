@@ -275,3 +275,30 @@ def test_linear_term_of_query_tokens_of_any_magnitude(bq):
             pu.check_output(got, ref, "%s head %d" % (name, h))
             # (bf16 results and summaries: 1.7e-3 of rounding each; 5e-3 as in the parity tests)
             assert np.linalg.norm(got - ref) / np.linalg.norm(ref) <= 5e-3, name
+
+
+@pytest.mark.parametrize("bq", [128, 64])
+def test_linear_term_of_values_near_the_largest(bq):
+    """phi(Q) sums to at most 1 over the channels when it meets H_i: what the quotient leaves finite does not overflow ahead of it.
+    768 values of 6e35 under flat weights: H_i holds 3.6e36 per channel, of which 128 channels of weight 0.95 would make 4.4e38.
+    (Not larger: V's quantisation takes 448 times a value.)"""
+    cfg = synth.custom_config(1, 1, (4, 16, 16), block_q=bq, topk_ratio=0.25, marginal_ratio=0.75, cfg_id=713)   # N = 1024
+    q, k, v = synth.make_qkv(cfg)
+    q, k = ((x.float() / 64).to(torch.bfloat16) for x in (q, k))
+    v = ((1.0 + 0.1 * v.float().clamp(-2, 2)) * 6e35).to(torch.bfloat16)
+    qd, kd, vd = pu.to_dev(q, k, v)
+    args = (bq, 64, cfg.topk_ratio, cfg.marginal_ratio)
+    mask = sla.sla_classify_blocks(qd, kd, *args, want_scores=False)[0]
+    m = mask[0, 0].cpu().numpy()
+    Q, K, V = (synth.as_f64(x[0, 0]) for x in (q, k, v))
+    got = {"stage": sla.sla_linear_attn_fwd(qd, kd, vd, mask, bq, 64)}
+    want = {"stage": so.linear_branch(Q, K, V, m, bq, 64)}
+    for name, quant, oq in (("unquantised", sla.QUANT_NONE, so.QUANT_NONE),
+                            ("low-bit", sla.QUANT_QK_INT8_PV_FP8, so.QUANT_QK_INT8_PV_FP8)):
+        got[name] = sla.sla_attention_fwd(qd, kd, vd, *args, quant_mode=quant)
+        want[name] = so.sla_forward_head(Q, K, V, *args, mask=m, quant=oq, ref_tile=pu.REF_TILE)["out"]
+    for name in got:
+        x = got[name][0, 0].float().cpu().numpy().astype(np.float64)
+        assert np.isfinite(x).all(), name
+        # (as above; of the low-bit core's FP8 weights and values, flat here, 448 levels are left: 1e-2)
+        assert np.linalg.norm(x - want[name]) / np.linalg.norm(want[name]) <= (1e-2 if name == "low-bit" else 5e-3), name
