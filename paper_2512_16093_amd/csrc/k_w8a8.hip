@@ -696,22 +696,34 @@ void launch_w8a8_gemm(const int8_t* x8, const float* sx, int MP, const int8_t* w
   //   60.2 / 56.4, -> 5120 at 1280 (200) 54.7 / 55.0, -> 5120 at 1536 (240) 56.1 / 62.6.
   // Long contractions that do not fill the chip with large tiles: of the wide tiles the smallest that deal out in one round (a
   // wavefront per SIMD).  The product in us, before / wide: 3072 -> 1024 at 1280 tokens
-  // (320 tiles of 64 x 64, taken as 64 x 96) 11.2 / 9.7, -> 3072 at 640 (480, 64 x 128) 14.4 / 12.1; 5120 -> 5120 at 256 16.3 /
-  // 14.0, 384 22.0 / 17.0, 512 (64 x 160) 23.9 / 20.7, 768 (64 x 128, two wavefronts) 31.3 / 28.7, 1024 (64 x 160, two) 40.9 / 34.8;
-  // 5120 -> 13824 at 128 22.5 / 18.4, 384 (128 x 96, two) 48.9 / 37.4; 8960 -> 1536 at 2048 (128 x 96) 41.6 / 36.1, 4096 77.6 /
-  // 64.3; 2048 -> 2048 at 1024 10.8 / 9.9, 2048 17.6 / 16.6.  On the other side: 240 tiles (8960 -> 1536 at 640) 18.5 / 20.7,
-  // 256 (3072 -> 1024 at 1024) 10.4 / 10.3; in two rounds 5120 -> 5120 at 1280 49.1 / 55.8; 12 blocks (1536 -> 8960 at 256) 10.4 / 10.7.
+  // (320 tiles of 64 x 64, taken as 64 x 96) 9.6 / 8.5, at 1024 (256 tiles) 9.2 / 9.1, -> 3072 at 640 (480, 64 x 128) 12.4 / 10.1;
+  // 5120 -> 5120 at 256 14.9 / 13.0, 512 (64 x 160) 21.5 / 18.0, 768 (64 x 128, two wavefronts) 29.0 / 26.2, 1024 (64 x 160, two)
+  // 37.4 / 31.4; 5120 -> 13824 at 128 20.9 / 17.0, 384 (128 x 96, two) 48.9 / 37.4; 8960 -> 1536 at 2048 (128 x 96) 39.2 / 33.2, 4096
+  // 77.6 / 64.3; 2048 -> 2048 at 1024 9.4 / 8.4, 2048 16.2 / 14.8.  On the other side: 240 tiles (8960 -> 1536 at 640) 18.5 / 20.7;
+  // in two rounds 5120 -> 5120 at 1280 49.1 / 55.8; 12 blocks (1536 -> 8960 at 256) 10.4 / 10.7.
   // The round has to be filled: products of 32 x 32 x 128 against those that its wavefronts would go through at full tiles and
   // the longest run of blocks (odd numbers of blocks deal out unevenly), 65 % with four wavefronts a tile, 75 % with two (4096 ->
   // 4096 at 700, 64 x 128 by two, 69 %: 26.9 / 27.9), and of few blocks two wavefronts have to get the same number or nearly
-  // (2176 -> 2560 at 2000, 10 of 17 blocks in the longer run: 28.2 / 29.1).  Up to 64 tokens it is the stream of the weights that counts, and more wavefronts
-  // ask for it (2048 -> 16384 at 33: 12.7 / 13.3).
+  // (2176 -> 2560 at 2000, 10 of 17 blocks in the longer run: 28.2 / 29.1).  Below 36 blocks, where a wavefront's start and the sums'
+  // way through LDS are a third of its life, rows of 32 tokens that do not exist count as idle with four wavefronts (2560 -> 8960 at
+  // 129, five of six such rows, 8.8 / 9.9; 3584 -> 12416 at 83 12.4 / 13.2), the round has to be filled to 61 % of what is left, to 64
+  // by 64 x 128, to 75 by 128 x 96, and tiles above 64 x 128 by runs of nearly one length (2176 -> 1280 at 2290, runs of 6, 4, 4 and
+  // 3 blocks, 11.2 / 13.2; 3200 -> 3200 at 860 15.3 / 16.3), unless the small tiles would be eight wavefronts' in more than one round
+  // (4096 -> 8832 at 80: 0.64 of their time; in one round 4096 -> 5376 at 140 9.3 / 9.9).  Of 342 sizes drawn at random, most of them near
+  // these lines, the wide tiles were slower by more than 3 % in 46 without this paragraph, in 4 with it.
+  // Up to 64 tokens it is the stream of the weights that counts, and more wavefronts ask for it (2048 -> 16384 at 33: 12.7 / 13.3).
   if (M > 64 && KB >= 16) {
-    const long long work = 4ll * ((M + 63) / 64) * (N / 64) * KB;
+    const long long tiles64 = (long long)((M + 63) / 64) * (N / 64), work = 4 * tiles64 * KB;
+    const long long exist = (long long)((M + 31) / 32) * (N / 32) * KB;
+    const bool any = KB >= 36 || (KB >= 32 && tiles64 > 256 && (long long)((M + 31) / 32) * (N / 64) < 512);
     auto one_round = [&](int rt, int ct, int ks) {
       const long long tiles = (long long)((M + 32 * rt - 1) / (32 * rt)) * ((N / 32 + ct - 1) / ct);
       const int run = 2 * (((KB + 1) / 2 + ks - 1) / ks);
-      return tiles * ks <= 1024 && 20 * work >= (ks == 4 ? 13 : 15) * 1024ll * rt * ct * run && (ks == 4 || KB >= 24 || 10 * KB >= 9 * ks * run);
+      const long long full = 1024ll * rt * ct * run;
+      if (tiles * ks > 1024 || 20 * work < (ks == 4 ? 13 : 15) * full || (ks == 2 && KB < 24 && 10 * KB < 9 * ks * run)) return false;
+      if (any) return true;
+      if (ks == 4 && rt * ct > 8 && 5 * KB < 4 * ks * run) return false;
+      return ks == 2 || 100 * exist >= (rt == 4 ? 75 : ct == 4 ? 64 : 61) * full;
     };
 #define W8_WIDE(RT, CT, KS) if (one_round(RT, CT, KS)) return launch_wide<RT, CT, KS>(x8, sx, MP, w8, sw, bias, y, M, N, K, stream)
     W8_WIDE(2, 3, 4);
