@@ -377,7 +377,7 @@ __global__ void __launch_bounds__(LA_WAVES * 64, 2) lin_accumulate_kernel(const 
 constexpr int LS_MAX_ROWS = 48, LS_MAX_KEYS = 80;
 constexpr int LS_COLS = 64;
 constexpr int ls_waves(int ksteps, int rt) { return ksteps == 4 || rt == 1 ? 3 : 2; }   // wavefronts per SIMD that its registers leave room for
-static_assert(HZ_ELEMS % (4 * LS_COLS) != 0 && HZ_ELEMS % LS_COLS == 0, "64 columns at a time, a head's last four wavefronts not all busy");
+static_assert(HZ_ELEMS % LS_COLS == 0, "64 columns at a time");
 template <int KSTEPS, int RT, bool RIDERS>
 __global__ void __launch_bounds__(256, ls_waves(KSTEPS, RT)) lin_short_kernel(const uint32_t* __restrict__ mbits, const bf16_t* __restrict__ hz, int Tq, int Tk,
                                                            int BH, bf16_t* __restrict__ HZ, int rider_blocks, LinRiders riders) {

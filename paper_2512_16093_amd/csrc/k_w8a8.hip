@@ -520,7 +520,7 @@ __global__ void __launch_bounds__(64 * KS, 1) w8a8_gemm_wide_kernel(
     const int8_t* __restrict__ x8, const float* __restrict__ sx, const int8_t* __restrict__ w8,
     const float* __restrict__ sw, const bf16_t* __restrict__ bias, bf16_t* __restrict__ y, int M, int N, int K,
     int RTx, int RBx, int RTw, int RBw, int MT, int NT) {
-  static_assert(CT <= 5 && (RT == 1 || RT == 2 || RT == 4), "a tile lies in one block of tokens and at most two of outputs");
+  static_assert(CT <= 5 && (RT == 2 || RT == 4) && KS > 1, "a tile lies in one block of tokens and at most two of outputs");
   constexpr int PITCH = 36;  // floats per staged row of 32 outputs (16-byte rows, skewed banks)
   __shared__ __attribute__((aligned(16))) float part[2][KS][32 * RT][PITCH];
   const int per = (MT * NT + 7) >> 3, xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;   // (dealt as above)
@@ -550,7 +550,7 @@ __global__ void __launch_bounds__(64 * KS, 1) w8a8_gemm_wide_kernel(
     mag[0] = mag_of(kb0, nb0);
     mag[1] = mag_of(kb0, nb1);
 #pragma unroll
-    for (int u = 0; u < 2; ++u) base[u] = KS == 1 ? 0.f : W8_C0 * ((kb0 & 1) ? mag[u] : -mag[u]);
+    for (int u = 0; u < 2; ++u) base[u] = -W8_C0 * mag[u];   // (kb0 is even)
   }
   v16f facc[RT][CT];
 #pragma unroll
