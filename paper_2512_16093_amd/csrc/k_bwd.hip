@@ -1728,10 +1728,27 @@ static bool dkv_paired(const Problem& p) { return 2 * p.n_c > p.Tk; }
 // dQ with dK and dV in one launch: either kind alone leaves wavefronts' places empty or runs on with a few long lists, and
 // neither needs anything of the other.  Backward pass in us, two launches / one: 4 x 2187 in blocks of 64 (140 workgroups each)
 // 119 / 95, 3 x 4617 136 / 113, 12 x 4617 262 / 244, 8 x 1024 82 / 71, 40 x 1024 in blocks of 128 178 / 161, 7 x 4617 200 / 165,
-// 1 x 37800 629 / 533, 3 x 16380 363 / 328.  From 1024 wavefronts' worth of query rows on dQ's wavefronts own 64 rows each; an
-// instance of that form here gained on a training step 4 % of 40 x 4617, 2 % of 8 x 16380, nothing from 3 x 32760 on and lost
+// 1 x 37800 629 / 533, 3 x 16380 363 / 328 (10 % critical).  From 1024 wavefronts' worth of query rows on dQ's wavefronts own 64 rows
+// each; an instance of that form here gained on a training step 4 % of 40 x 4617, 2 % of 8 x 16380, nothing from 3 x 32760 on and lost
 // 1 % of 8 x 75600: not kept.
-bool bwd_dq_with_dkv(const Problem& p) { return dq_narrow(p) && !dkv_paired(p); }
+// Long lists are nearly of one length, and what counts is whether the workgroups of both kinds, two at a time on a compute unit,
+// go round in fewer turns than those of each: they do where the last turn of either is at most half full.  From a saved state,
+// us, with lists of 20, 35 and 50 % of the blocks.  512 workgroups of dQ: 1 x 32760 in blocks of 128 533 / 534, 760 / 781, 999 /
+// 1016; 782: 1 x 50000 1156 / 1024, 1708 / 1736, 2417 / 2540; 876: 2 x 28000 in blocks of 64 698 / 698, 1083 / 1115, 1465 /
+// 1530; 880: 4 x 14000 410 / 407, 596 / 614, 787 / 817; 938: 1 x 60000 1435 / 1399, 2250 / 2312, 3194 / 3323; but 256: 1 x 16380
+// 319 / 258, 373 / 292, 432 / 319; 626: 1 x 40000 825 / 740, 1278 / 1164, 1802 / 1603; 628: 2 x 20000 479 / 416, 711 632, 966 /
+// 850; and where each kind has one turn, of blocks of 64, whose K and V one launch streams no more often, 438: 1 x 28000 456 /
+// 454, 644 / 644, 828 / 798, 512: 2 x 16380 at 20, 30 and 50 % 350 / 317, 415 / 404, 560 / 555, and of 128 up to a third of the
+// blocks (one launch's time at 25, 30 and 50 %: 314, 1 x 20000 0.85, 0.91, 0.99; 376, 1 x 24000 0.95, 0.97, 1.02; 2 x 16380
+// 0.95, 0.98, 1.02).  Up to 48 blocks a list's length does not settle it (852: 6 x 9000, 49 and 70 blocks 431 / 434 and 549 /
+// 567; 426: 3 x 9000, 42 blocks 233 / 223).
+bool bwd_dq_with_dkv(const Problem& p) {
+  if (!dq_narrow(p) || dkv_paired(p)) return false;
+  const int places = 2 * compute_units();
+  const long long units = (long long)p.Tq * p.BH * (p.block_q / 64);
+  return p.n_c <= 48 || 5 * p.n_c <= p.Tk || (units - 1) % places < places / 2 ||
+         (units <= places && (p.block_q == 64 || 3 * p.n_c <= p.Tk));
+}
 
 void launch_bwd_dq(const Problem& p, const void* q, const void* dout, const void* k, const void* v, const int32_t* crit,
                   const float* lse2, const float* delta, const float* dq_lin, void* dq, hipStream_t stream) {

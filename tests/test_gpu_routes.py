@@ -188,6 +188,8 @@ def test_order_of_the_key_blocks_leaves_their_gradients_alone(H, N, block_q, rc,
     (9, 4033, 128, 0.1, 0.2),    # dK/dV's workgroups in the order of their lists' lengths, dQ's behind them
     (7, 1000, 64, 0.2, 0.4),     # one workgroup of dQ per query block
     (15, 1000, 128, 0.2, 0.0),   # 240 half query blocks, no linear branch
+    (4, 9000, 128, 0.4, 0.2),    # long lists, 568 workgroups of dQ: their second turn nearly empty, one launch
+    (6, 9000, 128, 0.4, 0.2),    # 852: two launches
 ])
 def test_gradients_of_one_launch_and_of_two_have_the_same_bits(H, N, block_q, rc, rm):
     """Calls of few query blocks form dQ in the launch of dK and dV, dq wherever its caller wants it."""
