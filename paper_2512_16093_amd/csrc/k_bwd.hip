@@ -1736,7 +1736,7 @@ static bool dkv_paired(const Problem& p) { return 2 * p.n_c > p.Tk; }
 // us, with lists of 20, 35 and 50 % of the blocks.  512 workgroups of dQ: 1 x 32760 in blocks of 128 533 / 534, 760 / 781, 999 /
 // 1016; 782: 1 x 50000 1156 / 1024, 1708 / 1736, 2417 / 2540; 876: 2 x 28000 in blocks of 64 698 / 698, 1083 / 1115, 1465 /
 // 1530; 880: 4 x 14000 410 / 407, 596 / 614, 787 / 817; 938: 1 x 60000 1435 / 1399, 2250 / 2312, 3194 / 3323; but 256: 1 x 16380
-// 319 / 258, 373 / 292, 432 / 319; 626: 1 x 40000 825 / 740, 1278 / 1164, 1802 / 1603; 628: 2 x 20000 479 / 416, 711 632, 966 /
+// 319 / 258, 373 / 292, 432 / 319; 626: 1 x 40000 825 / 740, 1278 / 1164, 1802 / 1603; 628: 2 x 20000 479 / 416, 711 / 632, 966 /
 // 850; and where each kind has one turn, of blocks of 64, whose K and V one launch streams no more often, 438: 1 x 28000 456 /
 // 454, 644 / 644, 828 / 798, 512: 2 x 16380 at 20, 30 and 50 % 350 / 317, 415 / 404, 560 / 555, and of 128 up to a third of the
 // blocks (one launch's time at 25, 30 and 50 %: 314, 1 x 20000 0.85, 0.91, 0.99; 376, 1 x 24000 0.95, 0.97, 1.02; 2 x 16380

@@ -443,13 +443,18 @@ void launch_prep_kv(const PrepArgs& P, const Problem& p, int phi_kind, hipStream
   else select_prep_kernel<2, 2, false><<<grid, 256, 0, stream>>>(A);
 }
 
-// One launch for scores, selection and operands where a slice has at most 64 key blocks: the statistics that every
-// workgroup then joins for itself cost as much as a launch from there on (2 slices of 128 blocks, us for the whole forward
-// call, two launches / one: 55.6 / 57.0), and while the workgroups of four query blocks, each of which pays for a product of 32
-// rows, are few.  Query blocks of 64, slices x key blocks: 2 x 16 34.2 / 29.8, 40 x 16 (160 workgroups) 71.9 / 68.8, 8 x 64 (128)
-// 60.8 / 57.6, 24 x 64 (384) 115.6 / 115.8, 40 x 48 (480) 141.4 / 140.5, 40 x 64 (640) 194.1 / 202.0, 64 x 64 (1024) 297.7 / 312.5;
-// of 128: 40 x 64 (320) 173.1 / 172.7, 64 x 48 (384) 214.5 / 213.1, 80 x 48 (480) 257.8 / 260.7, 80 x 64 (640) 315.0 / 339.7.
-bool stats_in_prep(const Problem& p) { return p.Tk <= 64 && (long long)p.BH * ((p.Tq + 3) / 4) <= 384; }
+// One launch for scores, selection and operands where a slice has at most 64 key blocks (2 slices of 128 blocks, us for the whole
+// forward call, two launches / one: 55.6 / 57.0) and the workgroups of the key blocks, which all join their slice's statistics for
+// themselves, stand on the chip at once, four on a compute unit: later ones repeat it behind those.  Slices x key blocks: 16 x 64 in
+// blocks of 64 69.7 / 68.3, of 128 67.6 / 67.0, 32 x 32 70.5 / 68.1 and 64.0 / 61.1, 64 x 16 66.3 / 64.0 and 60.1 / 56.3, 2 x 64 39.1 /
+// 34.4; but 20 x 64 85.3 / 88.0 and 81.6 / 81.9, 32 x 40 85.4 / 88.1 and 80.7 / 82.7, 64 x 24 96.3 / 100.1 and 93.8 / 94.9, 40 x 64 164.2 /
+// 169.3 and 150.9 / 154.0, 64 x 56 230.5 / 246.4 and 218.3 / 230.5.  Up to 16 key blocks there is little to join, and the line lies where
+// the workgroups of four query blocks are few: 96 x 16 (384 of them in blocks of 64) 95.2 / 93.5 and 86.4 / 82.9, 128 x 16 (512 and 256)
+// 1.00 and 0.97 of the time; 150 x 10 (450) 1.02, 200 x 14 (800) 1.05.  (Training steps, which do not quantise, take 0.98 to 1.00 of
+// the time on either side.)
+bool stats_in_prep(const Problem& p) {
+  return p.Tk <= 64 && ((long long)p.BH * p.Tk <= 4 * compute_units() || (p.Tk <= 16 && (long long)p.BH * ((p.Tq + 3) / 4) <= 384));
+}
 
 // Long rows are selected in a launch of their own: 40 slices of 591 x 1182 blocks take 163 us there and 1003 us with
 // prep_block's, in one launch 1020 (prep_block's shared memory leaves the selection half of the wavefronts it hides
