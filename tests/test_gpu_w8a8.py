@@ -170,6 +170,10 @@ def test_full_size_attention_projection_sampled():
     (200, 384, 8192), (257, 640, 8192),      # 32 x 64 and 64 x 64 split in two
     (1023, 384, 4096), (1025, 256, 5120),    # 64 x 64, not split; two feature blocks
     (2049, 384, 3712),                       # the large tiles: nine bands of token tiles, a ragged last patch
+    # long contractions in one round of wide tiles; by four wavefronts 64 x 96 (the last tile of a row reaches past the outputs,
+    # the last of a column holds one row of tokens), the same with an odd number of blocks, 64 x 128, 64 x 160 and 128 x 96
+    (1025, 2048, 1024), (1090, 4224, 1152), (200, 2048, 8064), (1200, 2048, 1792), (2050, 2048, 1408),
+    (257, 2048, 12288), (833, 3968, 5120), (3000, 3968, 1920),   # by two: 64 x 128, 64 x 160, 128 x 96
 ])
 def test_every_tile_and_split_of_the_product(M, K, N):
     """The product's variants (tile size, ways the contraction is split) at the edges of what selects them, against
@@ -197,7 +201,28 @@ def test_split_contraction_is_no_less_precise_than_one_walk(M, K, N):
     feature blocks, formed here on the same codes: per block one fma of (constant +- block sum) in fp32, constants of
     alternating sign, their sum (a rounded product) taken out at the end.  Counted is how many outputs are not the correctly rounded bf16 of
     the exact sum; both counts are of M x N outputs, their own scatter is well under the 2 % (and 50) allowed."""
-    x, w, _ = synth.make_linear_inputs(M, K, N, seed=9)
+    missed, allowed = _not_the_rounded_exact_sum(M, K, N, 9)
+    print("w8a8 %d x %d -> %d: %d outputs not the rounded exact sum, one walk %d" % (M, K, N, missed, allowed))
+    assert missed <= 1.02 * allowed + 50
+
+
+@pytest.mark.parametrize("M,K,N", [
+    (512, 5120, 5120), (1090, 4224, 1152),    # by four wavefronts: 40 blocks, 33 (the last run's last does not exist)
+    (2050, 2048, 1408), (833, 3968, 5120),    # 128 x 96 by four, 64 x 160 by two (31 blocks)
+])
+def test_wide_tiles_are_no_less_precise_than_one_walk(M, K, N):
+    """The same of the wide tiles, whose runs all have an even number of blocks.  Which constants are left standing while a run
+    goes on depends on where the blocks with outlier features (scales ten to thirty times the others') lie in it: the ratio of
+    the two counts was 0.46 to 1.31 over twelve inputs of these sizes, 0.75 to 0.89 on average, so eight inputs are added up
+    (their mean scatters by a third of the single ones' 0.2)."""
+    missed, allowed = np.sum([_not_the_rounded_exact_sum(M, K, N, seed) for seed in range(9, 17)], axis=0)
+    print("w8a8 %d x %d -> %d: %d outputs not the rounded exact sum, one walk %d" % (M, K, N, missed, allowed))
+    assert missed <= allowed
+
+
+def _not_the_rounded_exact_sum(M, K, N, seed):
+    """(outputs of the product, outputs of one walk) that are not the exact sum rounded to bf16."""
+    x, w, _ = synth.make_linear_inputs(M, K, N, seed=seed)
     wq = sla.w8a8_quantize_weight(w.cuda())
     ws = sla.w8a8_quantize_act(x.cuda())
     y = sla.w8a8_gemm_fwd(ws, wq, M, N, K)
@@ -216,9 +241,7 @@ def test_split_contraction_is_no_less_precise_than_one_walk(M, K, N):
         csum = (csum.double() + sc).float()
     walk = walk - c0 * csum
     rounded = exact.to(torch.bfloat16)
-    missed, allowed = int((y != rounded).sum()), int((walk.to(torch.bfloat16) != rounded).sum())
-    print("w8a8 %d x %d -> %d: %d outputs not the rounded exact sum, one walk %d" % (M, K, N, missed, allowed))
-    assert missed <= 1.02 * allowed + 50
+    return int((y != rounded).sum()), int((walk.to(torch.bfloat16) != rounded).sum())
 
 
 @pytest.mark.parametrize("M,K,N", [
