@@ -40,9 +40,9 @@ constexpr int LA_WAVES = 4;
 constexpr int LA_M_ROWS = 512;                   // mask words staged per 32-block group (two 1 KiB pieces; 384 used)
 constexpr int LA_B_ROW = LA_COLS * 2;            // 256 bytes per staged hz row
 // A row's sixteen 16-byte chunks are staged permuted, chunk c of row r at position c ^ la_swz(r): the 16 lanes of a transposing
-// read's group address four rows, which at 256 bytes apart met in the same banks (70 % of the LDS's cycles were conflicts and
-// the LDS busy for two thirds of the time: 40 slices of 591 x 1182 blocks 897 us, now 812, of 1182 x 1182 1793 / 1590, 12 of
-// 256 x 512 70.4 / 67.0).
+// read's group address four rows, which at 256 bytes apart met in the same banks: 222 of the LDS's 321 M cycles of 40 slices of 591 x
+// 1182 blocks were conflicts, now 71 of 170 M, and nearly all of those are of the table, whose entries meet at random (9 M with one
+// entry read always).  There 897 us, now 812, of 1182 x 1182 1793 / 1590, 12 of 256 x 512 70.4 / 67.0.
 __device__ __forceinline__ int la_swz(int r) { return ((r & 3) << 2) | ((r >> 2) & 3); }
 constexpr int LA_B_BYTES = LA_KT * LA_B_ROW;
 constexpr int LA_OUT_PITCH = 64 * 2 + 16;         // bytes per row of 64 results on their way out
@@ -371,9 +371,12 @@ __global__ void __launch_bounds__(LA_WAVES * 64, 2) lin_accumulate_kernel(const 
 // the same steps in the same order (same bits).  A lane ends up with eight consecutive entries of a query block's summary:
 // 16-byte stores, the lane halves' side by side.  Bound by memory: 24 slices of 37 x 73 blocks 29.8 -> 22.1 us (87 MB), 4 of
 // 35 x 35 7.6 -> 6.4, 2 of 16 x 16 4.4 -> 3.4.
-// Where the line lies (slices of query x key blocks, whole forward calls in us, staged / this): 40 of 16 x 16 65.7 / 54.7, of 8 x
-// 16 63.6 / 52.5, of 48 x 48 137.1 / 132.0, of 32 x 64 171.5 / 166.4, of 40 x 80 224.7 / 221.4, 4 of 40 x 80 53.4 / 51.9; but (in an
-// instance for more) 40 of 48 x 96 269.7 / 270.4, 24 of 56 x 112 202.6 / 206.9, 40 of 64 x 64 187.2 / 194.8.
+// Where the line lies (slices of query x key blocks, whole forward calls in us, staged / this): 40 of 16 x 16 59.7 / 49.5, of 8 x
+// 16 57.8 / 45.9, of 32 x 64 163.0 / 156.7, 2 of 16 x 16 25.8 / 24.9, 24 of 37 x 73 112.6 / 110.0, 6 of 35 x 70 51.0 / 49.6, 3 of 40 x 80
+// 44.0 / 43.6; but (in an instance for more) 40 of 48 x 96 269.7 / 270.4, 24 of 56 x 112 202.6 / 206.9, 40 of 64 x 64 187.2 / 194.8.  Above
+// 32 query blocks, where the second product's rows are up to half empty, forward calls are within 2 % of each other whichever it is: 1 of 40
+// x 80 38.9 / 39.4, 28 of 40 x 40 84.2 / 82.9, 40 of 48 x 48 122.3 / 122.9 (12 of 48 x 48, 780 workgroups' worth in 768 places, 50.5 /
+// 53.7); staged where that alone was faster (33 to 48 query blocks of few slices) a training step of 4 of 35 x 35 took 1 % longer.
 constexpr int LS_MAX_ROWS = 48, LS_MAX_KEYS = 80;
 constexpr int LS_COLS = 64;
 constexpr int ls_waves(int ksteps, int rt) { return ksteps == 4 || rt == 1 ? 3 : 2; }   // wavefronts per SIMD that its registers leave room for

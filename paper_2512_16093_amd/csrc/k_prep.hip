@@ -14,9 +14,10 @@
 //    permuted to match, for both operands).
 //
 // One workgroup (4 wavefronts) per (b,h,j): reads 32 KiB, writes 16 KiB of codes and 33 KiB of summaries.  With the staged codes
-// and phi(K) free of bank conflicts (a row's codes met in four banks) and reductions on the vector ALU instead of through LDS the
-// launch, selection included, takes 699 us at 40 x 75600 tokens (before: 816), 5.5 TB/s, what a large copy gets; 102 at 12 x 32760
-// (122), 29.7 at 24 x 4617 (41.4); there, with 6 to 8 wavefronts' worth of instructions per SIMD, by issuing them.
+// and phi(K) spread over the banks (a row's codes met in four: of 344 M LDS cycles at 40 x 75600 tokens 234 M were conflicts, now 32
+// of 100 M) and reductions on the vector ALU instead of through LDS the launch, selection included, takes 699 us there (before: 816),
+// 5.5 TB/s, what a large copy gets; 102 at 12 x 32760 (122), 29.7 at 24 x 4617 (41.4); there, with 6 to 8 wavefronts' worth of
+// instructions per SIMD, by issuing them.
 #include "classify.h"
 #include "delta.h"
 

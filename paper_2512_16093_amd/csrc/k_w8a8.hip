@@ -502,8 +502,10 @@ __global__ void __launch_bounds__(64 * KS, 2) w8a8_gemm_splitk_kernel(
 // round where 64 x 64 ones leave a last round nearly empty (512 x 5120 -> 5120: 256 tiles of 64 x 160, one per compute unit;
 // of 64 x 64 there are 2.5).  The operands are held in accumulation registers, where the sums cannot be, the activations
 // of a feature block requested a whole block ahead (two sets), a weight fragment behind its last product: with one set, half
-// a block ahead, 512 x 5120 -> 5120 took 22.1 instead of 19.8 us.  Bound by what comes into the L2s (47 MB there) and from
-// them (287 MB, 0.8 of the 64 bytes per clock and compute unit).
+// a block ahead, 512 x 5120 -> 5120 took 22.1 instead of 19.8 us.  Of a wavefront's 32.8 k cycles
+// there (products alone: 12.8 k) 2.8 k pass until its first operands are requested, 3.0 k with its first pair of blocks, 20.7 k with the
+// other four, 6.3 k while the sums go through LDS; 2590 a block, in which the products take 1280 and the compute unit gets 115 KB from
+// L2, 44 bytes per clock of the 64 that the path carries.  Bound by no unit alone: by that path in the loop, by waiting around it.
 // A tile's outputs may span two quantisation blocks (CT = 3, 5: two scales), and the last tile of a row may reach past N (its
 // operands are then the last fragment's once more and nothing of it is stored).
 // (w8_chain with both operands in accumulation registers; 0x3e22f983 is W8_BIAS_I, the same inline constant)
