@@ -497,15 +497,15 @@ __global__ void __launch_bounds__(64 * KS, 2) w8a8_gemm_splitk_kernel(
   }
 }
 
-// The same with larger tiles, one wavefront per SIMD (the fp32 sums of a 64 x 160 tile alone take 160 registers): per
-// product 0.7 KiB have to come from L2 instead of 1, and between 64 x 96 and 128 x 96 there is a tile that deals out in one
-// round where 64 x 64 ones leave a last round nearly empty (512 x 5120 -> 5120: 256 tiles of 64 x 160, one per compute unit;
-// of 64 x 64 there are 2.5).  The operands are held in accumulation registers, where the sums cannot be, the activations
-// of a feature block requested a whole block ahead (two sets), a weight fragment behind its last product: with one set, half
-// a block ahead, 512 x 5120 -> 5120 took 22.1 instead of 19.8 us.  Of a wavefront's 32.8 k cycles
-// there (products alone: 12.8 k) 2.8 k pass until its first operands are requested, 3.0 k with its first pair of blocks, 20.7 k with the
-// other four, 6.3 k while the sums go through LDS; 2590 a block, in which the products take 1280 and the compute unit gets 115 KB from
-// L2, 44 bytes per clock of the 64 that the path carries.  Bound by no unit alone: by that path in the loop, by waiting around it.
+// The same with larger tiles, one wavefront per SIMD (the fp32 sums of a 64 x 160 tile alone take 160 registers): per product
+// 0.7 KiB have to come from L2 instead of 1, and between 64 x 96 and 128 x 96 there is a tile that deals out in one round
+// where 64 x 64 ones leave a last round nearly empty (512 x 5120 -> 5120: 256 tiles of 64 x 160, one per compute unit; of 64 x
+// 64 there are 2.5).  The operands are held in accumulation registers, where the sums cannot be, the activations of a feature
+// block requested a whole block ahead (two sets), a weight fragment behind its last product: with one set, half a block ahead,
+// 512 x 5120 -> 5120 took 22.1 instead of 19.8 us.  Of a wavefront's 32.8 k cycles there (products alone: 12.8 k) 2.8 k pass
+// until its first operands are requested, 3.0 k with its first pair of blocks, 20.7 k with the other four, 6.3 k while the
+// sums go through LDS; 2590 a block, in which the products take 1280 and the compute unit gets 115 KB from L2, 44 bytes per
+// clock of the 64 that the path carries.  Bound by no unit alone: by that path in the loop, by waiting around it.
 // A tile's outputs may span two quantisation blocks (CT = 3, 5: two scales), and the last tile of a row may reach past N (its
 // operands are then the last fragment's once more and nothing of it is stored).
 // (w8_chain with both operands in accumulation registers; 0x3e22f983 is W8_BIAS_I, the same inline constant)
@@ -704,15 +704,16 @@ void launch_w8a8_gemm(const int8_t* x8, const float* sx, int MP, const int8_t* w
   // 77.6 / 64.3; 2048 -> 2048 at 1024 9.4 / 8.4, 2048 16.2 / 14.8.  On the other side: 240 tiles (8960 -> 1536 at 640) 18.5 / 20.7;
   // in two rounds 5120 -> 5120 at 1280 49.1 / 55.8; 12 blocks (1536 -> 8960 at 256) 10.4 / 10.7.
   // The round has to be filled: products of 32 x 32 x 128 against those that its wavefronts would go through at full tiles and
-  // the longest run of blocks (odd numbers of blocks deal out unevenly), 65 % with four wavefronts a tile, 75 % with two (4096 ->
-  // 4096 at 700, 64 x 128 by two, 69 %: 26.9 / 27.9), and of few blocks two wavefronts have to get the same number or nearly
-  // (2176 -> 2560 at 2000, 10 of 17 blocks in the longer run: 28.2 / 29.1).  Below 36 blocks, where a wavefront's start and the sums'
-  // way through LDS are a third of its life, rows of 32 tokens that do not exist count as idle with four wavefronts (2560 -> 8960 at
-  // 129, five of six such rows, 8.8 / 9.9; 3584 -> 12416 at 83 12.4 / 13.2), the round has to be filled to 61 % of what is left, to 64
-  // by 64 x 128, to 75 by 128 x 96, and tiles above 64 x 128 by runs of nearly one length (2176 -> 1280 at 2290, runs of 6, 4, 4 and
-  // 3 blocks, 11.2 / 13.2; 3200 -> 3200 at 860 15.3 / 16.3), unless the small tiles would be eight wavefronts' in more than one round
-  // (4096 -> 8832 at 80: 0.64 of their time; in one round 4096 -> 5376 at 140 9.3 / 9.9).  Of 342 sizes drawn at random, most of them near
-  // these lines, the wide tiles were slower by more than 3 % in 46 without this paragraph, in 4 with it.
+  // the longest run of blocks (odd numbers of blocks deal out unevenly), 65 % with four wavefronts a tile, 75 % with two (4096
+  // -> 4096 at 700, 64 x 128 by two, 69 %: 26.9 / 27.9), and of few blocks two wavefronts have to get the same number or
+  // nearly (2176 -> 2560 at 2000, 10 of 17 blocks in the longer run: 28.2 / 29.1).  Below 36 blocks, where a wavefront's start
+  // and the sums' way through LDS are a third of its life, rows of 32 tokens that do not exist count as idle with four
+  // wavefronts (2560 -> 8960 at 129, where of six such rows five exist, 8.8 / 9.9; 3584 -> 12416 at 83 12.4 / 13.2), the round
+  // has to be filled to 61 % of what is left, to 64 by 64 x 128, to 75 by 128 x 96, and tiles above 64 x 128 by runs of nearly
+  // one length (2176 -> 1280 at 2290, runs of 4, 4, 4 and 5 blocks, 11.2 / 13.2; 3200 -> 3200 at 860 15.3 / 16.3), unless the
+  // small tiles would be eight wavefronts' in more than one round (4096 -> 8832 at 80: 0.64 of their time; in one round 4096
+  // -> 5376 at 140 9.3 / 9.9).  Of 342 sizes drawn at random, most of them near these lines, the wide tiles were slower by
+  // more than 3 % in 46 without this paragraph, in 4 with it.
   // Up to 64 tokens it is the stream of the weights that counts, and more wavefronts ask for it (2048 -> 16384 at 33: 12.7 / 13.3).
   if (M > 64 && KB >= 16) {
     const long long tiles64 = (long long)((M + 63) / 64) * (N / 64), work = 4 * tiles64 * KB;

@@ -81,7 +81,7 @@ def test_gradients_of_few_and_many_slices_have_the_same_bits(N, block_q, rc, rm,
     (2560, 768, 2560),    # 200 tiles, six blocks: large
     (2304, 768, 2816),    # 198: small
     (129, 2560, 8960),    # one round of 64 x 128 tiles, of whose rows of 32 tokens one in six does not exist: 32 x 64 instead
-    (2290, 2176, 1280),   # 17 blocks dealt as 6, 4, 4 and 3 to the wavefronts of 128 x 96 tiles: small
+    (2290, 2176, 1280),   # 17 blocks dealt as 4, 4, 4 and 5 to the wavefronts of 128 x 96 tiles: small
     (140, 4096, 5376),    # 252 tiles of 64 x 64, one round of eight wavefronts each
     (80, 4096, 8832),     # 276, more than one round: wide ones
 ])
